@@ -48,11 +48,13 @@ typedef enum {
 
 typedef enum { FC_F32 = 0, FC_BF16 = 1 } fc_dtype;
 
-/* Realisation of the low-pass projection (both compute the same Base KV). */
+/* Realisation of the low-pass projection (all compute the same Base KV). */
 typedef enum {
   FC_PATH_AUTO = 0,  /* FC_PATH_FFT where it applies, else FC_PATH_DENSE */
-  FC_PATH_DENSE = 1, /* explicit basis: C = B^T X, base = B C, on the matrix cores; any N,
-                        head_dim <= 256 */
+  FC_PATH_DENSE = 1, /* products with stored bases on the matrix cores; any N, head_dim <= 256.  Short
+                        token axes use the basis itself (C = B^T X, base = B C); from about 400 tokens on
+                        and for cut-offs up to N/2 the banded factors of the resampled transform, whose
+                        cost does not grow with r * N */
   FC_PATH_FFT = 2    /* fast cosine transform on the vector ALUs: N a multiple of 1024 (up to
                         132 * 1024), or of 256 (up to 64 * 1024, head_dim a multiple of 16);
                         head_dim a multiple of 8; any cut-off 1 <= r <= N */

@@ -18,6 +18,7 @@ UNITS = [
     ("fft.hip", "fft_r16.o", ["-DFC_FFT_R=16"]),
     ("fft.hip", "fft_r2.o", ["-DFC_FFT_R=2"]),
     ("fft.hip", "fft_r1.o", ["-DFC_FFT_R=1"]),
+    ("resample.hip", "resample.o", []),
     ("dense.hip", "dense.o", []),
     ("decode.hip", "decode.o", []),
     ("select_gather.hip", "select_gather.o", []),

@@ -40,6 +40,25 @@ int32_t resolve(const fc_kv_desc& d, int32_t r, int32_t path) {
   }
 }
 
+// What runs behind a path: the explicit basis, the streaming transform or the resampled transform.
+enum class Real { kNone, kDense, kFft, kResample };
+
+Real realisation(const fc_kv_desc& d, int32_t r, int32_t path) {
+  const int32_t p = resolve(d, r, path);
+  if (!p) return Real::kNone;
+  if (p == FC_PATH_FFT) return Real::kFft;
+  return resample_supported(d, r) ? Real::kResample : Real::kDense;
+}
+
+size_t score_workspace(const fc_kv_desc& d, int32_t r, int32_t path) {
+  switch (realisation(d, r, path)) {
+    case Real::kDense: return dense_layout(d, r).total;
+    case Real::kFft: return fft_layout(d, r).total;
+    case Real::kResample: return resample_layout(d, r).total;
+    default: return 0;
+  }
+}
+
 }  // namespace
 
 extern "C" {
@@ -70,11 +89,7 @@ int32_t flashcache_resolve_path(const fc_kv_desc* desc, int32_t r, int32_t path)
 
 size_t flashcache_workspace_bytes(const fc_kv_desc* desc, int32_t r, int32_t path) {
   if (check_desc(desc) != FC_OK || r < 1 || r > desc->n_tokens) return 0;
-  switch (resolve(*desc, r, path)) {
-    case FC_PATH_DENSE: return dense_layout(*desc, r).total;
-    case FC_PATH_FFT: return fft_layout(*desc, r).total;
-    default: return 0;
-  }
+  return score_workspace(*desc, r, path);
 }
 
 size_t flashcache_select_workspace_bytes(const fc_kv_desc* desc) {
@@ -87,15 +102,19 @@ fc_status flashcache_prepare(const fc_kv_desc* desc, int32_t r, int32_t path, vo
   fc_status st = check_desc(desc);
   if (st != FC_OK) return st;
   if (r < 1 || r > desc->n_tokens) return FC_EINVAL;
-  const int32_t p = resolve(*desc, r, path);
-  if (!p) return FC_EUNSUPPORTED;
+  const Real real = realisation(*desc, r, path);
+  if (real == Real::kNone) return FC_EUNSUPPORTED;
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) % kWsAlign) != 0) return FC_EWORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   hipError_t e;
-  if (p == FC_PATH_DENSE) {
+  if (real == Real::kDense) {
     DenseLayout lay = dense_layout(*desc, r);
     if (workspace_bytes < lay.total) return FC_EWORKSPACE;
     e = dense_prepare(*desc, r, lay, workspace, s);
+  } else if (real == Real::kResample) {
+    ResampleLayout lay = resample_layout(*desc, r);
+    if (workspace_bytes < lay.total) return FC_EWORKSPACE;
+    e = resample_prepare(*desc, r, lay, workspace, s);
   } else {
     FftLayout lay = fft_layout(*desc, r);
     if (workspace_bytes < lay.total) return FC_EWORKSPACE;
@@ -120,18 +139,22 @@ static fc_status score_common(const void* K, const void* V, const fc_kv_desc* de
   fc_status st = check_desc(desc);
   if (st != FC_OK) return st;
   if (r < 1 || r > desc->n_tokens) return FC_EINVAL;
-  const int32_t p = resolve(*desc, r, path);
-  if (!p) return FC_EUNSUPPORTED;
+  const Real real = realisation(*desc, r, path);
+  if (real == Real::kNone) return FC_EUNSUPPORTED;
   if (desc->batch == 0) return FC_OK;
   if (!K || !V || !scores || !energy) return FC_EINVAL;
   if (!aligned16(K) || !aligned16(V) || !aligned16(scores) || !aligned16(energy)) return FC_EINVAL;
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) % kWsAlign) != 0) return FC_EWORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   hipError_t e;
-  if (p == FC_PATH_DENSE) {
+  if (real == Real::kDense) {
     DenseLayout lay = dense_layout(*desc, r);
     if (workspace_bytes < lay.total) return FC_EWORKSPACE;
     e = dense_score(K, V, *desc, r, lay, scores, energy, workspace, um, s);
+  } else if (real == Real::kResample) {
+    ResampleLayout lay = resample_layout(*desc, r);
+    if (workspace_bytes < lay.total) return FC_EWORKSPACE;
+    e = resample_score(K, V, *desc, r, lay, scores, energy, workspace, um, s);
   } else {
     FftLayout lay = fft_layout(*desc, r);
     if (workspace_bytes < lay.total) return FC_EWORKSPACE;
@@ -161,17 +184,21 @@ fc_status flashcache_lowpass_energy(const fc_kv_desc* desc, int32_t r, int32_t p
   fc_status st = check_desc(desc);
   if (st != FC_OK) return st;
   if (r < 1 || r > desc->n_tokens) return FC_EINVAL;
-  const int32_t p = resolve(*desc, r, path);
-  if (!p) return FC_EUNSUPPORTED;
+  const Real real = realisation(*desc, r, path);
+  if (real == Real::kNone) return FC_EUNSUPPORTED;
   if (desc->batch == 0) return FC_OK;
   if (!lowpass_energy || (reinterpret_cast<uintptr_t>(lowpass_energy) & 7u)) return FC_EINVAL;
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) % kWsAlign) != 0) return FC_EWORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   hipError_t e;
-  if (p == FC_PATH_DENSE) {
+  if (real == Real::kDense) {
     DenseLayout lay = dense_layout(*desc, r);
     if (workspace_bytes < lay.total) return FC_EWORKSPACE;
     e = dense_lowpass(*desc, lay, workspace, lowpass_energy, s);
+  } else if (real == Real::kResample) {
+    ResampleLayout lay = resample_layout(*desc, r);
+    if (workspace_bytes < lay.total) return FC_EWORKSPACE;
+    e = resample_lowpass(*desc, lay, workspace, lowpass_energy, s);
   } else {
     FftLayout lay = fft_layout(*desc, r);
     if (workspace_bytes < lay.total) return FC_EWORKSPACE;

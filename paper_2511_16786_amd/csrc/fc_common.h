@@ -38,7 +38,16 @@ struct FftLayout {
   size_t twiddle, phase, partial, etot, epart, resid, total;
 };
 
+// ... and of the resampled realisation.
+struct ResampleLayout {
+  int32_t m, steps, tpw, wins;    // grid points; 32-token steps per grid tile; 16-token tiles per window; windows
+  int32_t nb, wpu, chunk;         // 8-column blocks per tensor; waves per unit; units per round
+  size_t wfwd, winv, t0, k0, filt, twid, elow, epart, grid, total;
+};
+
 DenseLayout dense_layout(const fc_kv_desc& d, int32_t r);
+bool resample_supported(const fc_kv_desc& d, int32_t r);
+ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r);
 bool fft_supported(const fc_kv_desc& d, int32_t r);
 FftLayout fft_layout(const fc_kv_desc& d, int32_t r);
 
@@ -53,6 +62,11 @@ __host__ __device__ inline int64_t out_unit(const UnitMap& m, int u) {
 hipError_t dense_score(const void* K, const void* V, const fc_kv_desc& d, int32_t r,
                        const DenseLayout& lay, float* scores, double* energy, void* ws, UnitMap um,
                        hipStream_t s);
+hipError_t resample_prepare(const fc_kv_desc& d, int32_t r, const ResampleLayout& lay, void* ws, hipStream_t s);
+hipError_t resample_score(const void* K, const void* V, const fc_kv_desc& d, int32_t r, const ResampleLayout& lay,
+                          float* scores, double* energy, void* ws, UnitMap um, hipStream_t s);
+hipError_t resample_lowpass(const fc_kv_desc& d, const ResampleLayout& lay, void* ws, double* lowpass,
+                            hipStream_t s);
 hipError_t dense_lowpass(const fc_kv_desc& d, const DenseLayout& lay, void* ws, double* lowpass, hipStream_t s);
 hipError_t fft_lowpass(const fc_kv_desc& d, int32_t r, const FftLayout& lay, void* ws, double* lowpass,
                        hipStream_t s);
