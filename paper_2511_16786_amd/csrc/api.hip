@@ -46,14 +46,14 @@ enum class Real { kNone, kDense, kFft, kResample };
 Real realisation(const fc_kv_desc& d, int32_t r, int32_t path) {
   const int32_t p = resolve(d, r, path);
   if (!p) return Real::kNone;
-  if (p == FC_PATH_FFT) return Real::kFft;
-  return resample_supported(d, r) ? Real::kResample : Real::kDense;
+  if (resample_supported(d, r)) return Real::kResample;
+  return p == FC_PATH_FFT ? Real::kFft : Real::kDense;
 }
 
 size_t score_workspace(const fc_kv_desc& d, int32_t r, int32_t path) {
+  if (resolve(d, r, path) == FC_PATH_FFT) return fft_layout(d, r).total + resample_reserve(d);
   switch (realisation(d, r, path)) {
     case Real::kDense: return dense_layout(d, r).total;
-    case Real::kFft: return fft_layout(d, r).total;
     case Real::kResample: return resample_layout(d, r).total;
     default: return 0;
   }

@@ -42,12 +42,13 @@ struct FftLayout {
 struct ResampleLayout {
   int32_t m, steps, tpw, wins;    // grid points; 32-token steps per grid tile; 16-token tiles per window; windows
   int32_t nb, wpu, chunk;         // 8-column blocks per tensor; waves per unit; units per round
-  size_t wfwd, winv, t0, k0, filt, twid, elow, epart, grid, total;
+  size_t wfwd, winv, s0, k0, filt, twid, elow, epart, grid, total;
 };
 
 DenseLayout dense_layout(const fc_kv_desc& d, int32_t r);
 bool resample_supported(const fc_kv_desc& d, int32_t r);
 ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r);
+size_t resample_reserve(const fc_kv_desc& d);
 bool fft_supported(const fc_kv_desc& d, int32_t r);
 FftLayout fft_layout(const fc_kv_desc& d, int32_t r);
 

@@ -28,7 +28,9 @@ constexpr int kPathResample = 3;       // header tag of a workspace prepared for
 constexpr int kMaxTilesPerWin = 16;    // 16-token tiles one wave of the residual kernel walks
 constexpr float kInvWeightScale = 4096.0f;   // fp16 weights are stored times 2^12 (their tails stay normal numbers)
 
-typedef short bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef short s16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16v8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -66,35 +68,36 @@ __device__ double weight_at(double u, int k, int m, double beta, double inv_i0) 
          window(2.0 * m - 1.0 - k - u, beta, inv_i0);
 }
 
-__device__ __forceinline__ uint32_t bf16_rne(float x) {
-  const uint32_t u = __float_as_uint(x);
-  return (u + ((u >> 16) & 1u) + 0x7FFFu) >> 16;
-}
-
 // position of grid point k in the order the transform takes its input (even points ascending, then
 // odd points descending)
 __device__ __forceinline__ int grid_pos(int k, int m) { return (k & 1) ? m - 1 - (k >> 1) : k >> 1; }
 
 struct TablePtrs {
   WsHeader* hdr;
-  uint16_t* wfwd;    // [M/16][steps][3][64][8] bf16
+  float* wfwd;       // [M/16][steps][2][64][4]
   _Float16* winv;    // [tokens/16][2][64][8] fp16
-  int* t0;           // [M/16] first token of a grid tile
+  int* s0;           // [M/16] first 32-token step of a grid tile
   int* k0;           // [windows] first grid point of a window
   float2* filt;      // [M] (f[m] + f[M-m]) / 2, (f[m] - f[M-m]) / 2
   float2* twid;      // see GridFft
 };
 
-// twiddle table: six powers (1,2,3,4,8,12) of w_{16 Ns} for Ns = 16 and 256, then the last pass's
-// powers w_M^{t q}, q = 1..R-1, then e^{i pi t / M}, t < M/16 each
-__host__ __device__ constexpr int last_radix(int m) { return m % 4096 == 0 ? (m == 4096 ? 1 : m / 4096) : m / 256; }
-__host__ __device__ constexpr int twid16_off() { return 0; }
-__host__ __device__ constexpr int twid256_off() { return 6 * 16; }
-__host__ __device__ constexpr int twid_last_off(int m) { return 6 * 16 + (m >= 4096 ? 6 * 256 : 0); }
-__host__ __device__ constexpr int twid_phase_off(int m) {
-  return twid_last_off(m) + (last_radix(m) > 1 ? (last_radix(m) - 1) * (m / 16) : 0);
+// Passes of the grid transform: M = R0 R1 R2 by M / P threads that keep P points each.  Three passes at every
+// length; short lengths take small radices, so that a pair is spread over more threads (a short grid usually comes
+// with few pairs).  Twiddle table: powers 1..7 and 8, 16, .. (below R) of w_{R NS}^j for the second pass (NS = R0,
+// j < NS) and for the last (NS = R0 R1, j < threads), then e^{i pi t / M}.
+__host__ __device__ constexpr int grid_points_per_thread(int m) {
+  return m % 3 == 0 ? (m <= 1536 ? 24 : 48) : (m <= 2048 ? 16 : 32);
 }
-__host__ __device__ constexpr int twid_size(int m) { return twid_phase_off(m) + m / 16; }
+__host__ __device__ constexpr int grid_radix0(int m) { return m == 16384 ? 32 : (m <= 2048 ? 8 : 16); }
+__host__ __device__ constexpr int grid_radix1(int m) { return m == 16384 ? 32 : (m <= 1536 ? 8 : 16); }
+__host__ __device__ constexpr int grid_radix2(int m) { return m / (grid_radix0(m) * grid_radix1(m)); }
+__host__ __device__ constexpr int twid_powers(int r) { return (r < 8 ? r : 8) - 1 + (r - 1) / 8; }
+__host__ __device__ constexpr int twid_last_off(int m) { return twid_powers(grid_radix1(m)) * grid_radix0(m); }
+__host__ __device__ constexpr int twid_phase_off(int m) {
+  return twid_last_off(m) + twid_powers(grid_radix2(m)) * (m / grid_points_per_thread(m));
+}
+__host__ __device__ constexpr int twid_size(int m) { return twid_phase_off(m) + m / grid_points_per_thread(m); }
 
 __device__ float2 unit_root(double frac) {        // e^{-2 pi i frac}
   double s, c;
@@ -117,23 +120,16 @@ __global__ __launch_bounds__(256) void resample_table_kernel(TablePtrs tp, int n
   }
   if (id < n_wfwd) {
     const int lane = id & 63, step = (id >> 6) % steps, tile = (id >> 6) / steps;
-    int t0 = (int)ceil(dd * (16.0 * tile - 0.5 * kW + 0.5) - 0.5);
-    t0 = max(0, min(t0, n - 32 * steps));
-    if (lane == 0 && step == 0) tp.t0[tile] = t0;
+    int s0 = max(0, (int)ceil(dd * (16.0 * tile - 0.5 * kW + 0.5) - 0.5)) / 32;
+    s0 = min(s0, (n + 31) / 32 - steps);
+    if (lane == 0 && step == 0) tp.s0[tile] = s0;
     const int k = 16 * tile + (lane & 15);
-    const int i0 = t0 + 32 * step + 8 * (lane >> 4);
-    uint16_t p[3][8];
-    for (int e = 0; e < 8; ++e) {
-      const double w = weight_at((i0 + e + 0.5) * inv_dd - 0.5, k, m, beta, inv_i0);
-      double rest = w;
-      for (int q = 0; q < 3; ++q) {
-        const uint32_t b = bf16_rne((float)rest);
-        p[q][e] = (uint16_t)b;
-        rest -= (double)bf16_to_f32(b);
-      }
-    }
-    for (int q = 0; q < 3; ++q)
-      for (int e = 0; e < 8; ++e) tp.wfwd[((size_t)(tile * steps + step) * 3 + q) * 512 + lane * 8 + e] = p[q][e];
+    // the last step slides back to end with the last token and takes only what earlier steps have not
+    const int i0 = min(32 * (s0 + step), n - 32) + 8 * (lane >> 4);
+    float* w = tp.wfwd + (size_t)(tile * steps + step) * 512 + lane * 4;
+    for (int e = 0; e < 8; ++e)
+      w[(e >> 2) * 256 + (e & 3)] =
+          i0 + e >= 32 * (s0 + step) ? (float)weight_at((i0 + e + 0.5) * inv_dd - 0.5, k, m, beta, inv_i0) : 0.0f;
     return;
   }
   id -= n_wfwd;
@@ -147,7 +143,7 @@ __global__ __launch_bounds__(256) void resample_table_kernel(TablePtrs tp, int n
     const double u = (i + 0.5) * inv_dd - 0.5;
     for (int e = 0; e < 8; ++e) {
       // the order in which the residual kernel's loads deliver the window's grid points
-      const int k = g < 2 ? k0 + 2 * (8 * g + e) : k0 + 2 * (7 + 8 * (g - 2) - e) + 1;
+      const int k = e < 4 ? k0 + 2 * (8 * (e >> 1) + 2 * g + (e & 1)) : k0 + 2 * (31 - 8 * (e >> 1) - 2 * g - (e & 1)) + 1;
       const double w = i < n ? kInvWeightScale * weight_at(u, k, m, beta, inv_i0) : 0.0;
       const _Float16 hi = (_Float16)(float)w;
       tp.winv[(size_t)tile * 1024 + lane * 8 + e] = hi;
@@ -170,16 +166,17 @@ __global__ __launch_bounds__(256) void resample_table_kernel(TablePtrs tp, int n
   }
   id -= m;
   if (id >= twid_size(m)) return;
-  const int pw[6] = {1, 2, 3, 4, 8, 12};
+  const int r0 = grid_radix0(m), threads = m / grid_points_per_thread(m);
+  auto power = [](int slot, int radix) {
+    const int low = (radix < 8 ? radix : 8) - 1;
+    return slot < low ? slot + 1 : 8 * (slot - low + 1);
+  };
   float2 v;
-  if (id < twid256_off()) {
-    v = unit_root((double)(pw[id / 16] * (id % 16)) / 256.0);
-  } else if (id < twid_last_off(m)) {
-    const int j = id - twid256_off();
-    v = unit_root((double)(pw[j / 256] * (j % 256)) / 4096.0);
+  if (id < twid_last_off(m)) {
+    v = unit_root((double)(power(id / r0, grid_radix1(m)) * (id % r0)) / (double)(r0 * grid_radix1(m)));
   } else if (id < twid_phase_off(m)) {
-    const int j = id - twid_last_off(m), t = m / 16;
-    v = unit_root((double)((long long)(j / t + 1) * (j % t)) / (double)m);
+    const int j = id - twid_last_off(m);
+    v = unit_root((double)(power(j / threads, grid_radix2(m)) * (j % threads)) / (double)m);
   } else {
     v = unit_root(-0.5 * (double)(id - twid_phase_off(m)) / (double)m);
   }
@@ -218,107 +215,138 @@ __device__ __forceinline__ f32x4 mfma_f16(const Frag& a, const Frag& b, f32x4 c)
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(a.h, b.h, c, 0, 0, 0);
 }
 
-// acc[j] += (column j of the 8 rows in x, for 16 slots) x (weights of this step)
-__device__ __forceinline__ void fold_rows(const RowPiece<uint16_t> (&x)[8], const Frag (&w)[3], f32x4 (&acc)[8]) {
+// Operand of column j of the 8 rows in x (a lane's 8 rows are 8 consecutive terms of the contraction).
+__device__ __forceinline__ void column_frag(const RowPiece<uint16_t> (&x)[8], int j, Frag (&a)[1]) {
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    Frag a;
+  for (int p = 0; p < 4; ++p)
+    a[0].u[p] = __builtin_amdgcn_perm(x[2 * p + 1].v[j >> 1], x[2 * p].v[j >> 1], (j & 1) ? 0x07060302u : 0x05040100u);
+}
+// Word h of three operands that hold a and b in bf16 terms, a = t0 + t1 + t2 (24 bits), each rounded to nearest.
+__device__ __forceinline__ void bf16_terms(float a, float b, Frag (&t)[3], int h) {
 #pragma unroll
-    for (int p = 0; p < 4; ++p)
-      a.u[p] = __builtin_amdgcn_perm(x[2 * p + 1].v[j >> 1], x[2 * p].v[j >> 1], (j & 1) ? 0x07060302u : 0x05040100u);
-#pragma unroll
-    for (int q = 2; q >= 0; --q) acc[j] = mfma_bf16(a, w[q], acc[j]);
+  for (int q = 0; q < 3; ++q) {
+    const bf16x2 p = __builtin_convertvector((f32x2{a, b}), bf16x2);
+    const uint32_t u = __builtin_bit_cast(uint32_t, p);
+    t[q].u[h] = u;
+    a -= __uint_as_float(u << 16);
+    b -= __uint_as_float(u & 0xFFFF0000u);
   }
 }
-
-__device__ __forceinline__ void fold_rows(const RowPiece<float> (&x)[8], const Frag (&w)[3], f32x4 (&acc)[8]) {
+__device__ __forceinline__ void column_frag(const RowPiece<float> (&x)[8], int j, Frag (&a)[3]) {
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    // x = x0 + x1 + x2 in bf16 terms; the products below 2^-24 of the whole are left out
-    Frag a[3];
+  for (int p = 0; p < 4; ++p)
+    bf16_terms(j < 4 ? x[2 * p].a[j & 3] : x[2 * p].b[j & 3], j < 4 ? x[2 * p + 1].a[j & 3] : x[2 * p + 1].b[j & 3],
+               a, p);
+}
+__device__ __forceinline__ f32x4 fold_column(const Frag (&a)[1], const Frag (&w)[3], f32x4 acc) {
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      uint32_t t[3][2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        float v = j < 4 ? x[2 * p + h].a[j & 3] : x[2 * p + h].b[j & 3];
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-          t[q][h] = bf16_rne(v);
-          v -= bf16_to_f32(t[q][h]);
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < 3; ++q) a[q].u[p] = t[q][0] | (t[q][1] << 16);
-    }
-    acc[j] = mfma_bf16(a[2], w[0], acc[j]);
-    acc[j] = mfma_bf16(a[0], w[2], acc[j]);
-    acc[j] = mfma_bf16(a[1], w[1], acc[j]);
-    acc[j] = mfma_bf16(a[1], w[0], acc[j]);
-    acc[j] = mfma_bf16(a[0], w[1], acc[j]);
-    acc[j] = mfma_bf16(a[0], w[0], acc[j]);
-  }
+  for (int q = 2; q >= 0; --q) acc = mfma_bf16(a[0], w[q], acc);
+  return acc;
+}
+__device__ __forceinline__ f32x4 fold_column(const Frag (&a)[3], const Frag (&w)[3], f32x4 acc) {
+  // the products below 2^-24 of the whole are left out
+  acc = mfma_bf16(a[2], w[0], acc);
+  acc = mfma_bf16(a[0], w[2], acc);
+  acc = mfma_bf16(a[1], w[1], acc);
+  acc = mfma_bf16(a[1], w[0], acc);
+  acc = mfma_bf16(a[0], w[1], acc);
+  return mfma_bf16(a[0], w[0], acc);
 }
 
-// One wave: 16 grid points x 16 slots (128 columns), walking the tokens under the tile's windows 32
-// at a time.  Rows go from memory straight into matrix operands: a lane loads 16 bytes of 8 consecutive
-// rows and swaps the two halves of the words in registers (the order of the contraction is free).
-template <typename T>
-__global__ __launch_bounds__(256) void decimate_kernel(const T* __restrict__ K, const T* __restrict__ V,
-                                                       KvStrides st, int u0, int u1, int n, int r, int d,
-                                                       int dtype, int m, int steps, SlotMap sm, int tiles_per_xcd,
-                                                       WsHeader* hdr, const uint16_t* __restrict__ wfwd,
-                                                       const int* __restrict__ t0s, float2* __restrict__ grid) {
+constexpr int kMinWorkgroups = 512;   // two for each compute unit
+constexpr int kDecWaves = 4;          // waves of a workgroup: 4 slots' worth of rows under the same tiles
+
+// One wave: GT tiles of 16 grid points x 16 slots (128 columns), walking the tokens under the tiles'
+// windows in steps of 32.  Rows go from memory straight into matrix operands: a lane loads 16 bytes of 8
+// consecutive rows and swaps the halves of the words in registers (the order of the contraction is free).
+// The tiles' weights are in LDS as fp32 and are split in three bf16 terms when a step uses them.
+// Bound by the rows' way through the fabric: 16 tiles apart, rows under the seams are read twice, so GT is
+// as large as registers allow; results do not depend on it (a tile's steps and their order are its own).
+template <typename T, int GT>
+__global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
+    const T* __restrict__ K, const T* __restrict__ V, KvStrides st, int u0, int u1, int n, int r, int d, int dtype,
+    int m, int steps, SlotMap sm, int supers_per_xcd, WsHeader* hdr, const float* __restrict__ wfwd,
+    const int* __restrict__ s0s, float2* __restrict__ grid) {
+  constexpr int kTerms = sizeof(T) == 2 ? 1 : 3;
+  constexpr int kBuf = sizeof(T) == 2 ? 2 : 1;    // steps of rows under way (a step's registers are refilled in place)
+  extern __shared__ f32x4 wlds[];                 // [GT][steps][2][64]
   if (ws_mismatch(hdr, kPathResample, n, r, d, dtype)) return;
   const int xcd = blockIdx.x & 7, slot_id = blockIdx.x >> 3;
-  const int tile = xcd * tiles_per_xcd + slot_id % tiles_per_xcd;
-  if (tile >= m / 16) return;
+  const int super = xcd * supers_per_xcd + slot_id % supers_per_xcd;
+  if (super >= (m / 16 + GT - 1) / GT) return;
+  const int tile0 = super * GT, n_tiles = min(GT, m / 16 - tile0);
   const int lane = threadIdx.x & 63;
-  const int gw = (slot_id / tiles_per_xcd) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int gw = (slot_id / supers_per_xcd) * kDecWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int unit = u0 + gw / sm.wpu, part = gw % sm.wpu;
-  if (unit >= u1) return;
+  const bool mine = unit < u1;
   const int s_mine = part * 16 + (lane & 15);
   const int slot = s_mine < 2 * sm.nb ? s_mine : 0;
   const bool second = slot >= sm.nb;
-  const int t0 = t0s[tile];
-  const T* p = (second ? V : K) + unit_offset(st, unit) + (slot - (second ? sm.nb : 0)) * 8 +
-               (int64_t)(t0 + 8 * (lane >> 4)) * st.sn;
-  const u32x4* wp = reinterpret_cast<const u32x4*>(wfwd) + (size_t)tile * steps * 192 + lane;
-
-  f32x4 acc[8];
+  int first[GT];                                  // a tile's first step
 #pragma unroll
-  for (int j = 0; j < 8; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  RowPiece<T> x[8];
-  Frag w[3];
+  for (int q = 0; q < GT; ++q) first[q] = s0s[tile0 + min(q, n_tiles - 1)];
+  const int s_end = first[GT - 1] + steps;
+  const T* p = (second ? V : K) + unit_offset(st, mine ? unit : u0) + (slot - (second ? sm.nb : 0)) * 8 +
+               (int64_t)(8 * (lane >> 4)) * st.sn;
+  RowPiece<T> x[kBuf][8];
+  auto load = [&](RowPiece<T> (&v)[8], int s) {
+    const T* ps = p + min(32 * s, n - 32) * st.sn;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) x[e].load(p + e * st.sn);
+    for (int e = 0; e < 8; ++e) v[e].load(ps + e * st.sn);
+  };
 #pragma unroll
-  for (int q = 0; q < 3; ++q) w[q].u = wp[q * 64];
-  for (int s = 1; s < steps; ++s) {
-    p += 32 * st.sn;
-    wp += 192;
-    RowPiece<T> xn[8];
-    Frag wn[3];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) xn[e].load(p + e * st.sn);
-#pragma unroll
-    for (int q = 0; q < 3; ++q) wn[q].u = wp[q * 64];
-    fold_rows(x, w, acc);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] = xn[e];
-#pragma unroll
-    for (int q = 0; q < 3; ++q) w[q] = wn[q];
+  for (int b = 0; b < kBuf; ++b)
+    if (b == 0 || first[0] + b < s_end) load(x[b], first[0] + b);
+  {
+    const f32x4* src = reinterpret_cast<const f32x4*>(wfwd) + (size_t)tile0 * steps * 128;
+    for (int i = threadIdx.x; i < n_tiles * steps * 128; i += 64 * kDecWaves) wlds[i] = src[i];
   }
-  fold_rows(x, w, acc);
+  __syncthreads();
+  if (!mine) return;
 
-  const int pos = grid_pos(16 * tile + (lane & 15), m);
+  f32x4 acc[GT][8];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int s_out = part * 16 + 4 * (lane >> 4) + i;
-    if (s_out < 2 * sm.nb) {
-      float2* o = grid + ((size_t)(unit - u0) * 2 * sm.nb + s_out) * 4 * m + pos;
+  for (int q = 0; q < GT; ++q)
 #pragma unroll
-      for (int jp = 0; jp < 4; ++jp) o[(size_t)jp * m] = make_float2(acc[2 * jp][i], acc[2 * jp + 1][i]);
+    for (int j = 0; j < 8; ++j) acc[q][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto step = [&](RowPiece<T> (&v)[8], int s) {
+#pragma unroll
+    for (int q = 0; q < GT; ++q) {
+      const int k = s - first[q];
+      if (k >= 0 && k < steps && q < n_tiles) {
+        const f32x4* wp = wlds + (q * steps + k) * 128 + lane;
+        const f32x4 wa = wp[0], wb = wp[64];
+        Frag w[3];
+#pragma unroll
+        for (int h = 0; h < 4; ++h)
+          bf16_terms(h < 2 ? wa[2 * h] : wb[2 * h - 4], h < 2 ? wa[2 * h + 1] : wb[2 * h - 3], w, h);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          Frag a[kTerms];
+          column_frag(v, j, a);
+          acc[q][j] = fold_column(a, w, acc[q][j]);
+        }
+      }
+    }
+    if (s + kBuf < s_end) load(v, s + kBuf);
+  };
+  for (int s = first[0]; s < s_end; s += kBuf)
+#pragma unroll
+    for (int b = 0; b < kBuf; ++b)
+      if (s + b < s_end) step(x[b], s + b);
+
+#pragma unroll
+  for (int q = 0; q < GT; ++q) {
+    if (q >= n_tiles) break;
+    const int pos = grid_pos(16 * (tile0 + q) + (lane & 15), m);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int s_out = part * 16 + 4 * (lane >> 4) + i;
+      if (s_out < 2 * sm.nb) {
+        float2* o = grid + ((size_t)(unit - u0) * 2 * sm.nb + s_out) * 4 * m + pos;
+#pragma unroll
+        for (int jp = 0; jp < 4; ++jp) o[(size_t)jp * m] = make_float2(acc[q][2 * jp][i], acc[q][2 * jp + 1][i]);
+      }
     }
   }
 }
@@ -332,177 +360,236 @@ __device__ __forceinline__ float2 cmul(float2 a, float2 w) {      // a * w, or a
   return INV ? make_float2(fmaf(a.x, w.x, a.y * w.y), fmaf(a.y, w.x, -a.x * w.y))
              : make_float2(fmaf(a.x, w.x, -a.y * w.y), fmaf(a.y, w.x, a.x * w.y));
 }
-template <bool INV>
-__device__ __forceinline__ void fft4(float2& a, float2& b, float2& c, float2& d) {
-  const float2 s = cadd(a, c), t = csub(a, c), u = cadd(b, d), v = csub(b, d);
-  a = cadd(s, u);
-  c = csub(s, u);
-  const float2 p = make_float2(t.x + v.y, t.y - v.x), q = make_float2(t.x - v.y, t.y + v.x);
-  b = INV ? q : p;
-  d = INV ? p : q;
-}
-// w_16^k, k < 16, as e^{-2 pi i k / 16}
-__device__ constexpr float kCos16[16] = {1.f, 0.92387953251128674f, 0.70710678118654752f, 0.38268343236508977f,
-                                         0.f, -0.38268343236508977f, -0.70710678118654752f, -0.92387953251128674f,
-                                         -1.f, -0.92387953251128674f, -0.70710678118654752f, -0.38268343236508977f,
-                                         0.f, 0.38268343236508977f, 0.70710678118654752f, 0.92387953251128674f};
-__device__ __forceinline__ constexpr float2 w16(int k) { return float2{kCos16[k & 15], kCos16[(k + 4) & 15]}; }
 
-// x[q] -> X[q], result q at x[4 (q % 4) + q / 4]
+// cos(2 pi k / 192) of the first quadrant; every constant root the transforms use is on this circle
+__device__ constexpr float kCos192[49] = {
+    1.f, 0.99946458747636568f, 0.99785892323860348f, 0.99518472667219693f, 0.99144486137381038f,
+    0.98664333208487898f, 0.98078528040323043f, 0.97387697927733363f, 0.96592582628906831f,
+    0.95694033573220882f, 0.94693012949510569f, 0.93590592675732576f, 0.92387953251128674f,
+    0.91086382492117579f, 0.89687274153268837f, 0.88192126434835505f, 0.86602540378443871f,
+    0.84920218152657889f, 0.83146961230254524f, 0.81284668459161524f, 0.79335334029123517f,
+    0.77301045336273699f, 0.75183980747897738f, 0.72986407269783571f, 0.70710678118654757f,
+    0.68359230202287125f, 0.65934581510006884f, 0.63439328416364549f, 0.60876142900872066f,
+    0.58247769686780215f, 0.5555702330196024f, 0.5280678506503681f, 0.50000000000000011f, 0.47139673682599759f,
+    0.44228869021900125f, 0.41270702980439472f, 0.38268343236508984f, 0.3522500479212336f, 0.3214394653031617f,
+    0.2902846772544625f, 0.25881904510252074f, 0.22707626303437345f, 0.19509032201612833f, 0.16289547339458882f,
+    0.13052619222005171f, 0.098017140329560548f, 0.06540312923014327f, 0.032719082821776165f, 0.f};
+__device__ constexpr float cos192(int k) {
+  k %= 192;
+  if (k > 96) k = 192 - k;
+  return k <= 48 ? kCos192[k] : -kCos192[96 - k];
+}
+// e^{-2 pi i k / n}, n a divisor of 192
+__device__ __forceinline__ constexpr float2 root(int k, int n) {
+  return float2{cos192(k * (192 / n)), cos192(k * (192 / n) + 48)};
+}
+
 template <bool INV>
-__device__ __forceinline__ void fft16(float2 (&x)[16]) {
+__device__ __forceinline__ void dft2(float2 (&v)[2]) {
+  const float2 a = v[0], b = v[1];
+  v[0] = cadd(a, b);
+  v[1] = csub(a, b);
+}
+template <bool INV>
+__device__ __forceinline__ void dft3(float2 (&v)[3]) {
+  const float2 t = cadd(v[1], v[2]), d = csub(v[1], v[2]);
+  const float k = INV ? -0.86602540378443865f : 0.86602540378443865f;
+  const float2 m = make_float2(fmaf(-0.5f, t.x, v[0].x), fmaf(-0.5f, t.y, v[0].y));
+  v[0] = cadd(v[0], t);
+  v[1] = make_float2(fmaf(k, d.y, m.x), fmaf(-k, d.x, m.y));
+  v[2] = make_float2(fmaf(-k, d.y, m.x), fmaf(k, d.x, m.y));
+}
+template <bool INV>
+__device__ __forceinline__ void dft4(float2 (&v)[4]) {
+  const float2 s = cadd(v[0], v[2]), t = csub(v[0], v[2]), u = cadd(v[1], v[3]), w = csub(v[1], v[3]);
+  const float2 p = make_float2(t.x + w.y, t.y - w.x), q = make_float2(t.x - w.y, t.y + w.x);
+  v[0] = cadd(s, u);
+  v[1] = INV ? q : p;
+  v[2] = csub(s, u);
+  v[3] = INV ? p : q;
+}
+
+// Transform of R points in registers, natural order on both sides: R = A * B with A-point transforms
+// over the strided points, constant factors, B-point transforms.
+template <int R>
+constexpr int first_factor() { return R == 2 || R == 3 || R == 4 ? R : (R % 4 == 0 ? 4 : 2); }
+template <int R, bool INV>
+__device__ __forceinline__ void dft(float2 (&v)[R]) {
+  if constexpr (R == 2) dft2<INV>(v);
+  else if constexpr (R == 3) dft3<INV>(v);
+  else if constexpr (R == 4) dft4<INV>(v);
+  else {
+    constexpr int A = first_factor<R>(), B = R / A;
+    float2 y[A][B];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) fft4<INV>(x[i], x[i + 4], x[i + 8], x[i + 12]);
+    for (int b = 0; b < B; ++b) {
+      float2 u[A];
 #pragma unroll
-  for (int k = 1; k < 4; ++k)
+      for (int a = 0; a < A; ++a) u[a] = v[B * a + b];
+      dft<A, INV>(u);
 #pragma unroll
-    for (int i = 1; i < 4; ++i) {
-      float2& v = x[i + 4 * k];
-      if (i * k == 4) v = INV ? make_float2(-v.y, v.x) : make_float2(v.y, -v.x);
-      else v = cmul<INV>(v, w16(i * k));
+      for (int a = 0; a < A; ++a) {
+        if (a * b == 0) y[a][b] = u[a];
+        else if (4 * a * b == R) y[a][b] = INV ? make_float2(-u[a].y, u[a].x) : make_float2(u[a].y, -u[a].x);
+        else y[a][b] = cmul<INV>(u[a], root(a * b, R));
+      }
     }
 #pragma unroll
-  for (int k = 0; k < 4; ++k) fft4<INV>(x[4 * k], x[4 * k + 1], x[4 * k + 2], x[4 * k + 3]);
+    for (int a = 0; a < A; ++a) {
+      dft<B, INV>(y[a]);
+#pragma unroll
+      for (int b = 0; b < B; ++b) v[a + A * b] = y[a][b];
+    }
+  }
 }
-__device__ __forceinline__ constexpr int rev16(int q) { return 4 * (q & 3) + (q >> 2); }
 
-__device__ __forceinline__ int lds_pad(int i) { return i + (i >> 4); }   // keeps stride-16 writes off one bank
+template <int M>
+struct GridPlan {
+  static constexpr int P = grid_points_per_thread(M), T = M / P;
+  static constexpr int R0 = grid_radix0(M), R1 = grid_radix1(M), R2 = grid_radix2(M);
+  static constexpr int kPadShift = R0 == 8 ? 3 : (R0 == 16 ? 4 : 5);   // one slot of padding per R0: the strided
+  static constexpr int kLds = M + (M >> kPadShift) + 1;                // writes of a pass fall on distinct banks
+};
 
-// Length-M complex transform of one column pair by M/16 threads; thread t holds the points t + (M/16) q
-// before and after (natural order both sides), exchanges go through LDS.
+// element i + k of a table: uniform base and constant part, 32-bit part of the lane
+__device__ __forceinline__ float2 at(const float2* __restrict__ base, int k, uint32_t i) {
+  return *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(base + k) + i * (uint32_t)sizeof(float2));
+}
+
+// Length-M complex transform of one column pair; natural order before and after, exchanges through LDS.
 template <int M, bool INV>
 struct GridFft {
-  static constexpr int T = M / 16, R = last_radix(M);
-  static __device__ __forceinline__ void exchange(float2 (&x)[16], float2* lds, int base, int ns, int t) {
+  using G = GridPlan<M>;
+  static constexpr int P = G::P, T = G::T;
+  // slot of point i; T and NS * R are multiples of 2^kPadShift, so that pad(i + T q) = pad(i) + pad(T q)
+  static __device__ __forceinline__ constexpr int pad(int i) { return i + (i >> G::kPadShift); }
+
+  // Pass of radix R after NS-point transforms are done: butterfly j = t + T c takes the points j + (M/R) q,
+  // which are this thread's own, times w_{R NS}^{(j mod NS) q}.
+  template <int R, int NS>
+  static __device__ __forceinline__ void pass(float2 (&x)[P], float* lds, const float2* __restrict__ tw, int t) {
+    constexpr int C = P / R;
+    float re[P];
+    constexpr bool kLast = R * NS == M;
+    if constexpr (NS > 1) {
+      // factors q = lo + 8 hi from stored powers lo = 1..7 and 8 hi; butterflies of one thread differ by a
+      // constant factor in the last pass, and by none before
+      constexpr int HI = (R - 1) / 8;
+      const int j = kLast ? t : t & (NS - 1);
+      constexpr int stride = kLast ? T : NS;
+      float2 lo[8], hi[HI + 1];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) lds[lds_pad(base + q * ns)] = x[rev16(q)];
-    __syncthreads();
+      for (int q = 1; q < 8; ++q)
+        if (q < R) lo[q] = at(tw, (q - 1) * stride, j);
 #pragma unroll
-    for (int q = 0; q < 16; ++q) x[q] = lds[lds_pad(t + T * q)];
-    __syncthreads();
-  }
-  static __device__ __forceinline__ void twiddle(float2 (&x)[16], const float2* __restrict__ tw, int ns, int j) {
-    float2 p[6];
+      for (int q = 1; q <= HI; ++q) hi[q] = at(tw, ((R < 8 ? R : 8) - 1 + q - 1) * stride, j);
 #pragma unroll
-    for (int i = 0; i < 6; ++i) p[i] = tw[i * ns + j];
+      for (int q = 1; q < R; ++q) {
+        const float2 w = q < 8 ? lo[q] : (q % 8 == 0 ? hi[q / 8] : cmul<false>(lo[q % 8], hi[q / 8]));
 #pragma unroll
-    for (int q = 1; q < 16; ++q) {
-      const int lo = q & 3, hi = q >> 2;
-      if (hi == 0) x[q] = cmul<INV>(x[q], p[lo - 1]);
-      else if (lo == 0) x[q] = cmul<INV>(x[q], p[2 + hi]);
-      else x[q] = cmul<INV>(x[q], cmul<false>(p[lo - 1], p[2 + hi]));
-    }
-  }
-  static __device__ __forceinline__ void run(float2 (&x)[16], float2* lds, const float2* __restrict__ twid, int t) {
-    fft16<INV>(x);
-    exchange(x, lds, t * 16, 1, t);
-    twiddle(x, twid + twid16_off(), 16, t & 15);
-    fft16<INV>(x);
-    exchange(x, lds, (t >> 4) * 256 + (t & 15), 16, t);
-    if (M >= 4096) {
-      twiddle(x, twid + twid256_off(), 256, t & 255);
-      fft16<INV>(x);
-      if (M > 4096) {
-        exchange(x, lds, (t >> 8) * 4096 + (t & 255), 256, t);
-      } else {
-        float2 y[16];
-#pragma unroll
-        for (int q = 0; q < 16; ++q) y[q] = x[rev16(q)];
-#pragma unroll
-        for (int q = 0; q < 16; ++q) x[q] = y[q];
+        for (int c = 0; c < C; ++c)
+          x[c + C * q] = cmul<INV>(x[c + C * q], kLast && c > 0 ? cmul<false>(w, root(c * q, P)) : w);
+        if (q % 8 == 7) __builtin_amdgcn_sched_barrier(0);
       }
     }
-    if (R > 1) {
-      constexpr int C = 16 / (R > 1 ? R : 2);       // butterflies of this thread: points c + C q
-      float2 b[R > 1 ? R : 2];
 #pragma unroll
-      for (int q = 1; q < R; ++q) b[q] = twid[twid_last_off(M) + (q - 1) * T + t];
+    for (int c = 0; c < C; ++c) {
+      float2 v[R];
 #pragma unroll
-      for (int c = 0; c < C; ++c) {
+      for (int q = 0; q < R; ++q) v[q] = x[c + C * q];
+      __builtin_amdgcn_sched_barrier(0);
+      dft<R, INV>(v);
 #pragma unroll
-        for (int q = 1; q < R; ++q) {
-          // w_M^{(t + T c) q} = w_M^{t q} w_16^{c q}
-          const float2 w = (c == 0) ? b[q] : cmul<false>(b[q], w16(c * q));
-          x[c + C * q] = cmul<INV>(x[c + C * q], w);
-        }
-        if (R == 2) {
-          const float2 a = x[c], v = x[c + C];
-          x[c] = cadd(a, v);
-          x[c + C] = csub(a, v);
-        } else if (R == 4) {
-          fft4<INV>(x[c], x[c + C], x[c + 2 * C], x[c + 3 * C]);
-        } else if (R == 8) {
-          // even and odd inputs, then the eighth-root butterflies
-          float2 e0 = x[c], e1 = x[c + 2 * C], e2 = x[c + 4 * C], e3 = x[c + 6 * C];
-          float2 o0 = x[c + C], o1 = x[c + 3 * C], o2 = x[c + 5 * C], o3 = x[c + 7 * C];
-          fft4<INV>(e0, e1, e2, e3);
-          fft4<INV>(o0, o1, o2, o3);
-          o1 = cmul<INV>(o1, w16(2));
-          o2 = INV ? make_float2(-o2.y, o2.x) : make_float2(o2.y, -o2.x);
-          o3 = cmul<INV>(o3, w16(6));
-          x[c] = cadd(e0, o0); x[c + 4 * C] = csub(e0, o0);
-          x[c + C] = cadd(e1, o1); x[c + 5 * C] = csub(e1, o1);
-          x[c + 2 * C] = cadd(e2, o2); x[c + 6 * C] = csub(e2, o2);
-          x[c + 3 * C] = cadd(e3, o3); x[c + 7 * C] = csub(e3, o3);
-        }
-      }
+      for (int q = 0; q < R; ++q) x[c + C * q] = v[q];
     }
+    if constexpr (!kLast) {
+      // Real parts, then imaginary parts, through the same half: half the LDS keeps twice the waves resident.
+      // Point (j / NS) NS R + j % NS + q NS of butterfly j = t + T c (T is a multiple of NS).
+      float* o = lds + pad((t / NS) * (NS * R) + (t & (NS - 1)));
+      const float* in = lds + pad(t);
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int q = 0; q < R; ++q) o[pad(T * c * R) + (NS == 1 ? q : pad(q * NS))] = x[c + C * q].x;
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < P; ++q) re[q] = in[pad(T * q)];
+      __syncthreads();
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int q = 0; q < R; ++q) o[pad(T * c * R) + (NS == 1 ? q : pad(q * NS))] = x[c + C * q].y;
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < P; ++q) x[q] = make_float2(re[q], in[pad(T * q)]);
+      __syncthreads();
+      // (table loads of the next pass stay behind the exchange: hoisted, they cost the registers of a pass)
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  static __device__ __forceinline__ void run(float2 (&x)[P], float* lds, const float2* __restrict__ twid, int t) {
+    pass<G::R0, 1>(x, lds, twid, t);
+    pass<G::R1, G::R0>(x, lds, twid, t);
+    pass<G::R2, G::R0 * G::R1>(x, lds, twid + twid_last_off(M), t);
   }
 };
 
-// One column pair (as real and imaginary part) per M/16 threads, in place: transform, keep and weight the
+// One column pair (as real and imaginary part) per M/P threads, in place: transform, keep and weight the
 // modes below the cut-off, transform back.  With the permuted input order the DFT carries DCT modes m and
 // M-m in the pair of bins (m, M-m):
 //     W'[m] = (f[m] + f[M-m])/2 W[m] + (f[m] - f[M-m])/2 e^{i pi m/M} W[M-m].
 // sum_m Re(conj(W) W') is the kept energy of both columns (the operator is symmetric).
 template <int M>
-__global__ __launch_bounds__(M / 16 < 64 ? 64 : M / 16) void grid_filter_kernel(
+__global__ __launch_bounds__(GridPlan<M>::T < 64 ? 64 : GridPlan<M>::T, 2) void grid_filter_kernel(
     float2* __restrict__ grid, int pairs, int n, int r, int d, int dtype, WsHeader* hdr,
     const float2* __restrict__ filt, const float2* __restrict__ twid, double* __restrict__ elow) {
-  constexpr int T = M / 16, PB = T < 64 ? 64 / T : 1;
-  extern __shared__ float2 lds_all[];
+  using G = GridPlan<M>;
+  using F = GridFft<M, false>;
+  constexpr int P = G::P, T = G::T, PB = T < 64 ? 64 / T : 1;
+  extern __shared__ float lds_all[];
   __shared__ double wsum[T < 64 ? 1 : T / 64];
   if (ws_mismatch(hdr, kPathResample, n, r, d, dtype)) return;
   const int t = threadIdx.x % T, pb = threadIdx.x / T;
-  float2* lds = lds_all + pb * (M + M / 16);
-  const int pair = min(blockIdx.x * PB + pb, pairs - 1);   // (a surplus half wave repeats the last pair)
-  float2* g = grid + (size_t)pair * M;
-  float2 x[16];
+  float* lds = lds_all + pb * G::kLds;
+  const int pair = min(blockIdx.x * PB + pb, pairs - 1);   // (surplus lanes repeat the last pair)
+  float2* g = grid + (size_t)blockIdx.x * PB * M;
+  uint32_t lane_at = (uint32_t)((pair - blockIdx.x * PB) * M + t);
+  float2 x[P];
 #pragma unroll
-  for (int q = 0; q < 16; ++q) x[q] = g[t + T * q];
-  GridFft<M, false>::run(x, lds, twid, t);
+  for (int q = 0; q < P; ++q) x[q] = at(g, T * q, lane_at);
+  F::run(x, lds, twid, t);
 
+  // each bin's mirror, W[M - m] (with W[M] = W[0])
+  float2 o[P];
 #pragma unroll
-  for (int q = 0; q < 16; ++q) lds[lds_pad(t + T * q)] = x[q];
-  __syncthreads();
-  const float2 ph = twid[twid_phase_off(M) + t];
+  for (int h = 0; h < 2; ++h) {
+#pragma unroll
+    for (int q = 0; q < P; ++q) lds[F::pad(t) + F::pad(T * q)] = h ? x[q].y : x[q].x;
+    if (t == 0) lds[F::pad(M)] = h ? x[0].y : x[0].x;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < P; ++q) (h ? o[q].y : o[q].x) = lds[F::pad(M - T * q) + F::pad(-t)];
+    __syncthreads();
+  }
+  const float2 ph = at(twid, twid_phase_off(M), t);
   float e = 0.f;
 #pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int m = t + T * q;
-    const float2 o = lds[lds_pad((M - m) & (M - 1))];
-    const float2 f = filt[m];
-    // e^{i pi q / 16} as a constant: cos and sin of q/32 turns
-    constexpr float cq[16] = {1.f, 0.98078528040323044f, 0.92387953251128674f, 0.83146961230254524f,
-                              0.70710678118654752f, 0.55557023301960222f, 0.38268343236508977f,
-                              0.19509032201612827f, 0.f, -0.19509032201612827f, -0.38268343236508977f,
-                              -0.55557023301960222f, -0.70710678118654752f, -0.83146961230254524f,
-                              -0.92387953251128674f, -0.98078528040323044f};
-    constexpr float sq[16] = {0.f, 0.19509032201612827f, 0.38268343236508977f, 0.55557023301960222f,
-                              0.70710678118654752f, 0.83146961230254524f, 0.92387953251128674f,
-                              0.98078528040323044f, 1.f, 0.98078528040323044f, 0.92387953251128674f,
-                              0.83146961230254524f, 0.70710678118654752f, 0.55557023301960222f,
-                              0.38268343236508977f, 0.19509032201612827f};
-    const float2 w = cmul<false>(ph, make_float2(cq[q], sq[q]));
-    const float2 z = cmul<false>(o, w);
+  for (int q = 0; q < P; ++q) {
+    if (q % 8 == 0) __builtin_amdgcn_sched_barrier(0);
+    const float2 f = at(filt, T * q, t);
+    const float2 z = cmul<false>(o[q], cmul<true>(ph, root(q, 2 * P)));    // e^{i pi (t + T q) / M}
     const float2 y = make_float2(fmaf(f.y, z.x, f.x * x[q].x), fmaf(f.y, z.y, f.x * x[q].y));
     e = fmaf(x[q].x, y.x, fmaf(x[q].y, y.y, e));
     x[q] = y;
   }
-  __syncthreads();
+  __builtin_amdgcn_sched_barrier(0);
+  // the way back loads its factors again: kept from the way there they would cost 100 registers
+  asm volatile("" : "+s"(twid));
   GridFft<M, true>::run(x, lds, twid, t);
+  asm volatile("" : "+v"(lane_at));                        // (nor are the load addresses worth keeping)
 #pragma unroll
-  for (int q = 0; q < 16; ++q) g[t + T * q] = x[q];
+  for (int q = 0; q < P; ++q)
+    *reinterpret_cast<float2*>(reinterpret_cast<char*>(g + T * q) + lane_at * (uint32_t)sizeof(float2)) = x[q];
 
   double es = (double)e;
 #pragma unroll
@@ -522,6 +609,7 @@ __global__ __launch_bounds__(M / 16 < 64 ? 64 : M / 16) void grid_filter_kernel(
 
 // ---------------------------------------------------------------------------- residual and score
 
+// squares of (row - inv * base) and of the row, 8 columns of token i of the tile
 __device__ __forceinline__ void residual8(const RowPiece<uint16_t>& x, const f32x4 (&acc)[8], int i, float inv,
                                           float& hp, float& tot) {
 #pragma unroll
@@ -531,8 +619,7 @@ __device__ __forceinline__ void residual8(const RowPiece<uint16_t>& x, const f32
     const float dl = fmaf(-inv, acc[2 * c][i], lo), dh = fmaf(-inv, acc[2 * c + 1][i], hi);
     hp = fmaf(dl, dl, hp);
     hp = fmaf(dh, dh, hp);
-    tot = fmaf(lo, lo, tot);
-    tot = fmaf(hi, hi, tot);
+    tot = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(s16x2, w), __builtin_bit_cast(s16x2, w), tot, false);
   }
 }
 __device__ __forceinline__ void residual8(const RowPiece<float>& x, const f32x4 (&acc)[8], int i, float inv,
@@ -546,157 +633,204 @@ __device__ __forceinline__ void residual8(const RowPiece<float>& x, const f32x4 
   }
 }
 
-// One wave: one window of 32 grid points x 16 slots, applied to the 16-token tiles it covers.  The four
-// waves of a workgroup share the window (their weights come from L1) and hold different slots or units.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+// Sums of v[0..3] over the 16 lanes of a row; a lane returns the sum of v[lane & 3].
+__device__ __forceinline__ float row_sums(const float (&v)[4], int lane) {
+  const bool b0 = lane & 1, b1 = lane & 2;
+  const float s01 = (b0 ? v[1] : v[0]) + dpp<0xB1>(b0 ? v[0] : v[1]);      // quad_perm 1,0,3,2
+  const float s23 = (b0 ? v[3] : v[2]) + dpp<0xB1>(b0 ? v[2] : v[3]);
+  float s = (b1 ? s23 : s01) + dpp<0x4E>(b1 ? s01 : s23);                  // quad_perm 2,3,0,1
+  s += dpp<0x124>(s);                                                      // row_ror:4
+  s += dpp<0x128>(s);                                                      // row_ror:8
+  return s;
+}
+
+constexpr int kResWorkgroups = 512;   // residual kernel: two for each compute unit, all resident
+
+// One wave applies windows (32 grid points each) to the 16-token tiles they cover, 16 slots at a time.  Its work
+// is a list of segments: a window, a unit (four units at a time, one for each wave of a workgroup), a part of the
+// unit's slots.  Rows are requested two tiles ahead and grid values one window ahead, across segments.
+// Neighbouring windows read the same lines of the grid: an XCD takes a contiguous range of windows and its
+// workgroups walk (units, window) side by side, window fastest, so that its L2 serves what they share.
+// A lane holds slot lane & 15 throughout: columns 8 slot + j of tokens 4 (lane >> 4) + i, so that a load reads whole
+// rows, and of a window the points that its loads deliver in 64-byte pieces (see resample_table_kernel).
 template <typename T>
-__global__ __launch_bounds__(256) void residual_kernel(const T* __restrict__ K, const T* __restrict__ V, KvStrides st,
-                                                       int u0, int u1, int n, int r, int d, int dtype, int m, int tpw,
-                                                       int wins, SlotMap sm, int wins_per_xcd, WsHeader* hdr,
-                                                       const _Float16* __restrict__ winv, const int* __restrict__ k0s,
-                                                       const float2* __restrict__ grid, float* __restrict__ scores,
-                                                       double* __restrict__ epart, UnitMap um) {
+__global__ __launch_bounds__(256, 2) void residual_kernel(
+    const T* __restrict__ K, const T* __restrict__ V, KvStrides st, int u0, int u1, int n, int r, int d, int dtype,
+    int m, int tpw, int wins, SlotMap sm, WsHeader* hdr, const _Float16* __restrict__ winv,
+    const int* __restrict__ k0s, const float2* __restrict__ grid, float* __restrict__ scores,
+    double* __restrict__ epart, UnitMap um) {
+  constexpr int kBuf = sizeof(T) == 2 ? 2 : 1;             // tiles of rows under way
   __shared__ float part_sum[4][16 * kMaxTilesPerWin];
-  __shared__ double part_e[4][4];
   if (ws_mismatch(hdr, kPathResample, n, r, d, dtype)) return;
-  const int xcd = blockIdx.x & 7, slot_id = blockIdx.x >> 3;
-  const int win = xcd * wins_per_xcd + slot_id % wins_per_xcd;
-  if (win >= wins) return;
-  const int lane = threadIdx.x & 63, g = lane >> 4, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int gw0 = (slot_id / wins_per_xcd) * 4, gw = gw0 + wave;
-  const int unit = u0 + gw / sm.wpu, part = gw % sm.wpu;
-  const int tiles = min(tpw, (n + 15) / 16 - win * tpw);
-  if (unit < u1) {
-    // grid values of the window: lane holds 8 points of the columns of slot 4 (row & 3) + (row >> 2)
-    const int row = lane & 15;
-    const int s_mine = part * 16 + 4 * (row & 3) + (row >> 2);
-    const int slot = s_mine < 2 * sm.nb ? s_mine : 0;
-    const int n0 = k0s[win] >> 1;
-    const int pos = g < 2 ? n0 + 8 * g : m - 8 - n0 - 8 * (g - 2);
-    const float2* gp = grid + ((size_t)(unit - u0) * 2 * sm.nb + slot) * 4 * m + pos;
-    Frag bh[8], bl[8];
-    float inv;
-    {
-      f32x4 v[4][4];
+  const int lane = threadIdx.x & 63, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int quads = (u1 - u0 + 3) >> 2, tok_tiles = (n + 15) >> 4;
+  const int xcd = blockIdx.x & 7, peers = gridDim.x >> 3;
+  const int w_first = (int)((int64_t)wins * xcd >> 3), w_count = (int)((int64_t)wins * (xcd + 1) >> 3) - w_first;
+  const int items = w_count * quads;
+  int item = blockIdx.x >> 3, part = 0;                    // segment under way
+  if (item >= items) return;
+
+  struct Seg {
+    int win, unit, part, tiles;
+    const T* rows;                                         // this lane's columns of token 4 g
+    const float2* gp;                                      // this lane's first column pair on the grid
+  };
+  auto segment = [&](int it, int pt) {
+    Seg s;
+    s.part = pt;
+    const int quad = it / w_count;
+    s.win = w_first + it - quad * w_count;
+    s.unit = min(u0 + 4 * quad + wave, u1 - 1);            // (a surplus wave repeats the last unit)
+    s.tiles = max(min(tpw, tok_tiles - s.win * tpw), kBuf);   // (a tile too many is worked on and dropped)
+    const int mine = pt * 16 + (lane & 15), slot = mine < 2 * sm.nb ? mine : 0;
+    const bool second = slot >= sm.nb;
+    s.rows = (second ? V : K) + unit_offset(st, s.unit) + (slot - (second ? sm.nb : 0)) * 8 + (int64_t)(4 * g) * st.sn;
+    s.gp = grid + ((size_t)(s.unit - u0) * 2 * sm.nb + slot) * 4 * m + 2 * g;
+    return s;
+  };
+  auto following = [&](const Seg& s) {                     // (the last segment follows itself)
+    int it = item, pt = part + 1;
+    if (pt == sm.wpu) { pt = 0; it += peers; }
+    return it < items ? segment(it, pt) : s;
+  };
+  f32x4 v[4][4];
+  auto load_window = [&](const Seg& s) {
+    const int n0 = k0s[s.win] >> 1;
 #pragma unroll
-      for (int jp = 0; jp < 4; ++jp)
+    for (int jp = 0; jp < 4; ++jp)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) v[jp][c] = *reinterpret_cast<const f32x4*>(gp + (size_t)jp * m + 2 * c);
-      float mx = 0.f;
+      for (int c = 0; c < 4; ++c)
+        v[jp][c] = *reinterpret_cast<const f32x4*>(s.gp + (size_t)jp * m + (c < 2 ? n0 + 8 * c : m - 32 - n0 + 8 * c));
+  };
+  auto load_rows = [&](RowPiece<T> (&x)[4], const Seg& s, int tl) {
+    const int t = (s.win * tpw + tl) * 16;
+    if (t + 16 <= n) {
+      const T* p = s.rows + t * st.sn;
 #pragma unroll
-      for (int jp = 0; jp < 4; ++jp)
+      for (int i = 0; i < 4; ++i) x[i].load(p + i * st.sn);
+    } else {                                               // rows past the end repeat the last one
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) mx = fmaxf(mx, fabsf(v[jp][c][q]));
-#pragma unroll
-      for (int s = 1; s < 64; s <<= 1) mx = fmaxf(mx, __shfl_xor(mx, s, 64));
-      // largest magnitude of the window into [2^14, 2^15); powers of two, so nothing is rounded
-      const int eb = max(14, min((int)(__float_as_uint(mx) >> 23), 254));
-      const float scale = __uint_as_float((uint32_t)(268 - eb) << 23);
-      inv = ldexpf(1.0f / kInvWeightScale, eb - 141);
-#pragma unroll
-      for (int jp = 0; jp < 4; ++jp)
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const float b = v[jp][c][q] * scale;
-            const _Float16 h = (_Float16)b;
-            bh[2 * jp + (q & 1)].hs[2 * c + (q >> 1)] = h;
-            bl[2 * jp + (q & 1)].hs[2 * c + (q >> 1)] = (_Float16)(b - (float)h);
-          }
+      for (int i = 0; i < 4; ++i) x[i].load(s.rows + (int64_t)(min(t + 4 * g + i, n - 1) - 4 * g) * st.sn);
     }
-    // rows: register i of a lane belongs to slot 4 i + g of token lane & 15
-    const int tok0 = win * tpw * 16 + (lane & 15);
-    const int64_t ubase = unit_offset(st, unit);
-    const T* px[4];
+  };
+  Frag wn[2];
+  auto load_weights = [&](const Seg& s, int tl) {
+    const u32x4* p = reinterpret_cast<const u32x4*>(winv) + (size_t)(s.win * tpw + min(tl, tpw - 1)) * 128 + lane;
+    wn[0].u = p[0];
+    wn[1].u = p[64];
+  };
+
+  Seg cur = segment(item, part), nxt = following(cur);
+  RowPiece<T> x[kBuf][4];
+  load_window(cur);
+  load_weights(cur, 0);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int so = part * 16 + 4 * i + g;
-      const int sl = so < 2 * sm.nb ? so : 0;
-      const bool second = sl >= sm.nb;
-      px[i] = (second ? V : K) + ubase + (sl - (second ? sm.nb : 0)) * 8;
-    }
-    const u32x4* wp = reinterpret_cast<const u32x4*>(winv) + (size_t)win * tpw * 128 + lane;
-    float hp[4] = {0.f, 0.f, 0.f, 0.f}, tot[4] = {0.f, 0.f, 0.f, 0.f};
-    RowPiece<T> x[4];
-    Frag wh, wl;
-    {
-      const int64_t off = (int64_t)min(tok0, n - 1) * st.sn;
+  for (int k = 0; k < kBuf; ++k) load_rows(x[k], cur, k);
+  int tl = 0;
+  bool more = true;
+  Frag bh[8], bl[8];
+  float inv = 0.f, hp = 0.f, tot = 0.f;
+
+  auto take_window = [&]() {
+    float mx = 0.f;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) x[i].load(px[i] + off);
-      wh.u = wp[0];
-      wl.u = wp[64];
-    }
-    for (int tl = 0; tl < tiles; ++tl) {
-      const int nx = min(tl + 1, tiles - 1);
-      const int64_t off = (int64_t)min(tok0 + 16 * nx, n - 1) * st.sn;
-      RowPiece<T> xn[4];
-      Frag whn, wln;
+    for (int jp = 0; jp < 4; ++jp)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) xn[i].load(px[i] + off);
-      whn.u = wp[nx * 128];
-      wln.u = wp[nx * 128 + 64];
-      f32x4 acc[8];
+      for (int c = 0; c < 4; ++c)
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        acc[j] = mfma_f16(bl[j], wh, f32x4{0.f, 0.f, 0.f, 0.f});
-        acc[j] = mfma_f16(bh[j], wl, acc[j]);
-        acc[j] = mfma_f16(bh[j], wh, acc[j]);
-      }
-      const bool in = tok0 + 16 * tl < n;
-      float row_sum = 0.f;
+        for (int q = 0; q < 4; ++q) mx = fmaxf(mx, fabsf(v[jp][c][q]));
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float h = 0.f, t2 = 0.f;
-        residual8(x[i], acc, i, inv, h, t2);
-        const bool use = in && part * 16 + 4 * i + g < 2 * sm.nb;
-        h = use ? h : 0.f;
-        t2 = use ? t2 : 0.f;
-        hp[i] += h;
-        tot[i] += t2;
-        row_sum += h;
-      }
-      row_sum += __shfl_xor(row_sum, 16, 64);
-      row_sum += __shfl_xor(row_sum, 32, 64);
-      if (lane < 16) part_sum[wave][16 * tl + lane] = row_sum;
+    for (int s = 1; s < 64; s <<= 1) mx = fmaxf(mx, __shfl_xor(mx, s, 64));
+    // largest magnitude of the window into [2^14, 2^15); powers of two, so nothing is rounded
+    const int eb = max(14, min((int)(__float_as_uint(mx) >> 23), 254));
+    const float scale = __uint_as_float((uint32_t)(268 - eb) << 23);
+    inv = ldexpf(1.0f / kInvWeightScale, eb - 141);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) x[i] = xn[i];
-      wh = whn;
-      wl = wln;
-    }
-    double ev[4] = {0.0, 0.0, 0.0, 0.0};                // Ehp_k, Ehp_v, Etot_k, Etot_v
+    for (int jp = 0; jp < 4; ++jp)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const bool second = part * 16 + 4 * i + g >= sm.nb;
-      ev[second ? 1 : 0] += (double)hp[i];
-      ev[second ? 3 : 2] += (double)tot[i];
-    }
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float b = v[jp][c][q] * scale;
+          const _Float16 h = (_Float16)b;
+          bh[2 * jp + (q & 1)].hs[2 * c + (q >> 1)] = h;
+          bl[2 * jp + (q & 1)].hs[2 * c + (q >> 1)] = (_Float16)(b - (float)h);
+        }
+    // (the operands are made here, before their sources' registers are loaded again)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) asm volatile("" : "+v"(bh[j].u), "+v"(bl[j].u));
+    hp = tot = 0.f;
+    load_window(nxt);
+  };
+  // energies of the segment: Ehp_k, Ehp_v, Etot_k, Etot_v
+  auto record = [&]() {
+    const int mine = cur.part * 16 + (lane & 15);
+    const bool use = mine < 2 * sm.nb, second = mine >= sm.nb;
+    double ev[4] = {use && !second ? (double)hp : 0.0, use && second ? (double)hp : 0.0,
+                    use && !second ? (double)tot : 0.0, use && second ? (double)tot : 0.0};
+    double* e = epart + (((size_t)cur.unit * wins + cur.win) * sm.wpu + cur.part) * 4;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
 #pragma unroll
       for (int s = 1; s < 64; s <<= 1) ev[k] += __shfl_xor(ev[k], s, 64);
-      if (lane == 0) part_e[wave][k] = ev[k];
+      if (lane == 0) e[k] = ev[k];
     }
-  }
-  __syncthreads();
-  const int upw = 4 / sm.wpu;                            // units of this workgroup
-  const int span = 16 * tiles, tokens = min(span, n - win * tpw * 16);
-  for (int k = threadIdx.x; k < upw * span; k += 256) {
-    const int ul = k / span, tk = k % span, u = u0 + gw0 / sm.wpu + ul;
-    if (u < u1 && tk < tokens) {
-      float s = part_sum[ul * sm.wpu][tk];
-      for (int p = 1; p < sm.wpu; ++p) s += part_sum[ul * sm.wpu + p][tk];
-      scores[(size_t)out_unit(um, u) * n + win * tpw * 16 + tk] = s / (float)d;
+  };
+  auto step = [&](RowPiece<T> (&xb)[4]) {
+    if (tl == 0) take_window();
+    const Frag wh = wn[0], wl = wn[1];
+    f32x4 acc[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      acc[j] = mfma_f16(wh, bl[j], f32x4{0.f, 0.f, 0.f, 0.f});
+      acc[j] = mfma_f16(wl, bh[j], acc[j]);
+      acc[j] = mfma_f16(wh, bh[j], acc[j]);
     }
-  }
-  if (threadIdx.x < 4 * upw) {
-    const int ul = threadIdx.x >> 2, k = threadIdx.x & 3, u = u0 + gw0 / sm.wpu + ul;
-    if (u < u1) {
-      double s = 0.0;
-      for (int p = 0; p < sm.wpu; ++p) s += part_e[ul * sm.wpu + p][k];
-      epart[((size_t)u * wins + win) * 4 + k] = s;
+    const bool last = tl + 1 == cur.tiles;
+    if (!last) load_weights(cur, tl + 1);
+    else load_weights(nxt, 0);
+    const int t0 = (cur.win * tpw + tl) * 16;
+    const bool slot_used = cur.part * 16 + (lane & 15) < 2 * sm.nb;
+    float h[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float h1 = 0.f, t1 = 0.f;
+      residual8(xb[i], acc, i, inv, h1, t1);
+      // tokens past the end, tiles past the window's own (they are the next window's) and slots past the last
+      const uint32_t use = slot_used && t0 + 4 * g + i < n && tl < tpw ? ~0u : 0u;
+      h[i] = __uint_as_float(__float_as_uint(h1) & use);
+      hp += h[i];
+      tot += __uint_as_float(__float_as_uint(t1) & use);
     }
+    float sum = row_sums(h, lane);
+    if ((lane & 15) < 4) {
+      const int k = 4 * g + (lane & 3), token = t0 + k;
+      if (cur.part > 0) sum += part_sum[wave][16 * tl + k];
+      if (cur.part + 1 < sm.wpu) part_sum[wave][16 * tl + k] = sum;
+      else if (token < n && tl < tpw) scores[(size_t)out_unit(um, cur.unit) * n + token] = sum / (float)d;
+    }
+    if (tl + kBuf < cur.tiles) load_rows(xb, cur, tl + kBuf);
+    else load_rows(xb, nxt, tl + kBuf - cur.tiles);
+    ++tl;
+    if (last) {
+      asm volatile("");                                    // (keeps what follows out of every tile's path)
+      record();
+      if (++part == sm.wpu) { part = 0; item += peers; }
+      more = item < items;
+      cur = nxt;
+      nxt = following(cur);
+      tl = 0;
+    }
+  };
+  while (more) {
+#pragma unroll
+    for (int k = 0; k < kBuf; ++k)
+      if (more) step(x[k]);
   }
 }
 
@@ -713,8 +847,8 @@ __global__ void resample_lowpass_kernel(const double* __restrict__ elow, int pai
 template <int M>
 hipError_t launch_filter(float2* grid, int pairs, int n, int r, int d, int dtype, WsHeader* hdr, const float2* filt,
                          const float2* twid, double* elow, hipStream_t s) {
-  constexpr int T = M / 16, PB = T < 64 ? 64 / T : 1;
-  const size_t lds = (size_t)PB * (M + M / 16) * sizeof(float2);
+  constexpr int T = GridPlan<M>::T, PB = T < 64 ? 64 / T : 1;
+  const size_t lds = (size_t)PB * GridPlan<M>::kLds * sizeof(float);
   auto kern = grid_filter_kernel<M>;
   if (lds > 64 * 1024) {
     // raising the dynamic LDS limit is per kernel and per device, and idempotent
@@ -732,15 +866,16 @@ hipError_t launch_filter(float2* grid, int pairs, int n, int r, int d, int dtype
 
 // Bytes of input rows and grid one round of the three kernels works on (see resample_layout).
 static size_t resample_chunk_bytes() {
-  return (size_t)1 << 30;
+  return (size_t)4 << 30;
 }
 
 // Grid length for this shape and cut-off, 0 if the realisation does not apply.
 static int grid_length(const fc_kv_desc& d, int32_t r) {
   if (d.head_dim % 8 != 0 || d.head_dim > 256 || r < 1 || 2 * (int64_t)r > d.n_tokens) return 0;
-  for (int m = 512; m <= 16384; m *= 2)
-    if (4 * (int64_t)m >= 7 * (int64_t)r)                       // M >= 1.75 r: see the accuracy note above
-      return 5 * (int64_t)d.n_tokens >= 4 * (int64_t)m ? m : 0;  // a 16-token tile and its windows fit 32 points
+  for (int m2 = 512; m2 <= 16384; m2 *= 2)
+    for (int m = m2; m <= 16384 && m <= m2 + m2 / 2; m += m2 / 2)   // 2^k and 3 2^(k-1)
+      if (4 * (int64_t)m >= 7 * (int64_t)r && 16 * (int64_t)m >= d.n_tokens)   // M >= 1.75 r: the accuracy above
+        return 5 * (int64_t)d.n_tokens >= 4 * (int64_t)m ? m : 0;   // a 16-token tile and its windows fit 32 points
   return 0;
 }
 
@@ -751,8 +886,8 @@ ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
   const int64_t n = d.n_tokens, m = grid_length(d, r);
   const size_t units = (size_t)d.batch * d.layers * d.kv_heads;
   lay.m = (int)m;
-  // tokens under a tile of 16 grid points: at most (15 + W) N/M + 1
-  lay.steps = (int)(((15 + kW) * n / m + 2 + 31) / 32);
+  // tokens under a tile of 16 grid points: at most (15 + W) N/M + 1, and the 32-token steps they lie in
+  lay.steps = (int)std::min(((15 + kW) * n / m + 31) / 32 + 1, (n + 31) / 32);
   // tiles whose windows fit 32 grid points when the first point is rounded down to a multiple of 4
   lay.tpw = (int)std::min<int64_t>(kMaxTilesPerWin, ((28 - kW) * n / m + 1) / 16);
   if (lay.tpw < 1) lay.tpw = 1;
@@ -768,23 +903,36 @@ ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
   lay.chunk = (int)std::max<size_t>(1, std::min(std::max<size_t>(units, 1), resample_chunk_bytes() / unit_bytes));
   auto up = [](size_t x) { return (x + kWsAlign - 1) / kWsAlign * kWsAlign; };
   size_t off = sizeof(WsHeader);
-  lay.wfwd = off; off = up(off + (size_t)(m / 16) * lay.steps * 3 * 512 * 2);
+  lay.wfwd = off; off = up(off + (size_t)(m / 16) * lay.steps * 512 * sizeof(float));
   lay.winv = off; off = up(off + (size_t)lay.wins * lay.tpw * 1024 * 2);
-  lay.t0 = off; off = up(off + (size_t)(m / 16) * 4);
+  lay.s0 = off; off = up(off + (size_t)(m / 16) * 4);
   lay.k0 = off; off = up(off + (size_t)lay.wins * 4);
   lay.filt = off; off = up(off + (size_t)m * sizeof(float2));
   lay.twid = off; off = up(off + (size_t)twid_size((int)m) * sizeof(float2));
   lay.elow = off; off = up(off + units * 2 * lay.nb * 4 * sizeof(double));
-  lay.epart = off; off = up(off + units * lay.wins * 4 * sizeof(double));
+  lay.epart = off; off = up(off + units * lay.wins * lay.wpu * 4 * sizeof(double));
   lay.grid = off; off = up(off + (size_t)lay.chunk * 2 * lay.nb * 4 * m * sizeof(float2));
   lay.total = off;
   return lay;
 }
 
+// Upper bound, over all cut-offs, of what this realisation needs beyond the streaming transform's
+// partial sums: one workspace size per shape and cut-off serves both.
+size_t resample_reserve(const fc_kv_desc& d) {
+  const size_t n = d.n_tokens, nb = d.head_dim / 8, units = (size_t)d.batch * d.layers * d.kv_heads;
+  const size_t m = std::min<size_t>(16384, n * 5 / 4);
+  const size_t tables = 232 * n + 280 * m + (256 << 10);
+  const size_t records = units * (64 * nb + 2 * n * (nb <= 8 ? 1 : (nb <= 16 ? 2 : 4)) + 64 * 4);
+  const size_t grid = std::max<size_t>(resample_chunk_bytes(), 64 * nb * m);
+  const size_t need = tables + records + std::min<size_t>(grid, units * 64 * nb * m);
+  const size_t have = units * 2 * (nb / 2) * n * sizeof(float);
+  return need > have ? (need - have + kWsAlign - 1) / kWsAlign * kWsAlign : 0;
+}
+
 hipError_t resample_prepare(const fc_kv_desc& d, int32_t r, const ResampleLayout& lay, void* ws, hipStream_t s) {
   char* base = static_cast<char*>(ws);
-  TablePtrs tp{reinterpret_cast<WsHeader*>(base), reinterpret_cast<uint16_t*>(base + lay.wfwd),
-               reinterpret_cast<_Float16*>(base + lay.winv), reinterpret_cast<int*>(base + lay.t0),
+  TablePtrs tp{reinterpret_cast<WsHeader*>(base), reinterpret_cast<float*>(base + lay.wfwd),
+               reinterpret_cast<_Float16*>(base + lay.winv), reinterpret_cast<int*>(base + lay.s0),
                reinterpret_cast<int*>(base + lay.k0), reinterpret_cast<float2*>(base + lay.filt),
                reinterpret_cast<float2*>(base + lay.twid)};
   const int n_wfwd = lay.m / 16 * lay.steps * 64, n_winv = lay.wins * lay.tpw * 64;
@@ -793,6 +941,41 @@ hipError_t resample_prepare(const fc_kv_desc& d, int32_t r, const ResampleLayout
   hipLaunchKernelGGL(resample_table_kernel, dim3((total + 255) / 256), dim3(256), 0, s, tp, d.n_tokens, r, lay.m,
                      d.head_dim, d.dtype, lay.steps, lay.tpw, n_wfwd, n_winv);
   return hipGetLastError();
+}
+
+template <typename T, int GT>
+static hipError_t launch_decimate_gt(const T* K, const T* V, KvStrides st, int u0, int u1, int n, int r,
+                                     const fc_kv_desc& d, int m, const ResampleLayout& lay, SlotMap sm, WsHeader* hdr,
+                                     const float* wfwd, const int* s0, float2* grid, hipStream_t s) {
+  auto kern = decimate_kernel<T, GT>;
+  const size_t lds = (size_t)GT * lay.steps * 2048;
+  if (lds > 64 * 1024) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  const int supers = (m / 16 + GT - 1) / GT, spx = (supers + 7) / 8;
+  const int groups = ((u1 - u0) * sm.wpu + kDecWaves - 1) / kDecWaves;
+  ProfileScope ps("decimate_kernel", s);
+  hipLaunchKernelGGL(kern, dim3(8 * spx * groups), dim3(64 * kDecWaves), lds, s, K, V, st, u0, u1, n, r, d.head_dim,
+                     d.dtype, m, lay.steps, sm, spx, hdr, wfwd, s0, grid);
+  return hipGetLastError();
+}
+
+// Tiles per wave: four while two workgroups' weights fit a compute unit's LDS (N/M up to 11) and the launch
+// still has several workgroups for each of them, else two or one.  fp32 rows leave registers for two.
+template <typename T>
+static hipError_t launch_decimate(const T* K, const T* V, KvStrides st, int u0, int u1, int n, int r,
+                                  const fc_kv_desc& d, int m, const ResampleLayout& lay, SlotMap sm, WsHeader* hdr,
+                                  const float* wfwd, const int* s0, float2* grid, hipStream_t s) {
+  const int groups = ((u1 - u0) * sm.wpu + kDecWaves - 1) / kDecWaves;
+  auto fits = [&](int gt) {
+    return gt * lay.steps * 2048 <= 78 * 1024 && (int64_t)(m / 16 / gt) * groups >= kMinWorkgroups;
+  };
+  if constexpr (sizeof(T) == 2)
+    if (fits(4)) return launch_decimate_gt<T, 4>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, s0, grid, s);
+  if (fits(2)) return launch_decimate_gt<T, 2>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, s0, grid, s);
+  return launch_decimate_gt<T, 1>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, s0, grid, s);
 }
 
 template <typename T>
@@ -809,39 +992,34 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
   const KvStrides st = strides_of(d);
   // each XCD takes a contiguous range of tiles (or windows), so that its L2 holds that range's weights
   // and the rows neighbouring tiles share
-  const int tpx = (m / 16 + 7) / 8, wpx = (lay.wins + 7) / 8;
   for (int u0 = 0; u0 < units; u0 += lay.chunk) {
     const int u1 = std::min(units, u0 + lay.chunk);
-    const int groups = ((u1 - u0) * lay.wpu + 3) / 4;
-    {
-      ProfileScope ps("decimate_kernel", s);
-      hipLaunchKernelGGL(decimate_kernel<T>, dim3(8 * tpx * groups), dim3(256), 0, s, K, V, st, u0, u1, n, r,
-                         d.head_dim, d.dtype, m, lay.steps, sm, tpx, hdr,
-                         reinterpret_cast<const uint16_t*>(base + lay.wfwd),
-                         reinterpret_cast<const int*>(base + lay.t0), grid);
-    }
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_decimate<T>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr,
+                                      reinterpret_cast<const float*>(base + lay.wfwd),
+                                      reinterpret_cast<const int*>(base + lay.s0), grid, s);
     if (e != hipSuccess) return e;
     double* elow = reinterpret_cast<double*>(base + lay.elow) + (size_t)u0 * 2 * lay.nb * 4;
     const int pairs = (u1 - u0) * 2 * lay.nb * 4;
 #define FC_FILTER(MV) case MV: e = launch_filter<MV>(grid, pairs, n, r, d.head_dim, d.dtype, hdr, filt, twid, elow, s); break;
     switch (m) {
-      FC_FILTER(512) FC_FILTER(1024) FC_FILTER(2048) FC_FILTER(4096) FC_FILTER(8192) FC_FILTER(16384)
+      FC_FILTER(512) FC_FILTER(768) FC_FILTER(1024) FC_FILTER(1536) FC_FILTER(2048) FC_FILTER(3072) FC_FILTER(4096)
+      FC_FILTER(6144) FC_FILTER(8192) FC_FILTER(12288) FC_FILTER(16384)
       default: e = hipErrorInvalidValue;
     }
 #undef FC_FILTER
     if (e != hipSuccess) return e;
     {
       ProfileScope ps("residual_kernel", s);
-      hipLaunchKernelGGL(residual_kernel<T>, dim3(8 * wpx * groups), dim3(256), 0, s, K, V, st, u0, u1, n, r,
-                         d.head_dim, d.dtype, m, lay.tpw, lay.wins, sm, wpx, hdr,
+      const int64_t items = (int64_t)((lay.wins + 7) / 8) * ((u1 - u0 + 3) / 4);   // of the XCD with most windows
+      hipLaunchKernelGGL(residual_kernel<T>, dim3(8 * (int)std::min<int64_t>(items, kResWorkgroups / 8)), dim3(256), 0, s, K, V, st,
+                         u0, u1, n, r, d.head_dim, d.dtype, m, lay.tpw, lay.wins, sm, hdr,
                          reinterpret_cast<const _Float16*>(base + lay.winv),
                          reinterpret_cast<const int*>(base + lay.k0), grid, scores, epart, um);
     }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  return energy_reduce_launch(epart, lay.wins, units, energy, um, s);
+  return energy_reduce_launch(epart, lay.wins * lay.wpu, units, energy, um, s);
 }
 
 hipError_t resample_score(const void* K, const void* V, const fc_kv_desc& d, int32_t r, const ResampleLayout& lay,
