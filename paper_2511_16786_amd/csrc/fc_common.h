@@ -24,6 +24,7 @@ static_assert(sizeof(WsHeader) == 256, "header is one 256-byte slot");
 struct KvStrides {
   int64_t sb, sl, sh, sn;  // elements
   int32_t L, H;
+  int32_t even;            // unit u starts at u * sh (no gaps between heads, layers, sequences)
 };
 
 // Offsets (bytes from the workspace base) of the regions of the dense realisation.
@@ -119,7 +120,9 @@ class ProfileScope {
 };
 
 inline KvStrides strides_of(const fc_kv_desc& d) {
-  return KvStrides{d.stride_b, d.stride_l, d.stride_h, d.stride_n, d.layers, d.kv_heads};
+  const bool even = (d.layers == 1 || d.stride_l == d.kv_heads * d.stride_h) &&
+                    (d.batch <= 1 || d.stride_b == (int64_t)d.layers * d.kv_heads * d.stride_h);
+  return KvStrides{d.stride_b, d.stride_l, d.stride_h, d.stride_n, d.layers, d.kv_heads, even ? 1 : 0};
 }
 
 #if defined(__HIPCC__)
@@ -127,14 +130,18 @@ __device__ __forceinline__ float bf16_to_f32(uint32_t bits16) { return __uint_as
 
 // True (and raises the flag once) if the workspace was not prepared for these arguments.
 __device__ __forceinline__ bool ws_mismatch(WsHeader* h, int path, int n, int r, int d, int dtype) {
-  bool bad = h->magic != kWsMagic || h->path != path || h->n != n || h->r != r || h->d != d ||
-             h->dtype != dtype;
+  // (read at once and compared without branches: one wait for memory at the start of a kernel, not six)
+  const int4 a = reinterpret_cast<const int4*>(h)[0];
+  const int2 b = reinterpret_cast<const int2*>(h)[2];
+  const bool bad = (((uint32_t)a.x ^ kWsMagic) | (uint32_t)((a.y ^ path) | (a.z ^ n) | (a.w ^ r) | (b.x ^ d) |
+                                                            (b.y ^ dtype))) != 0;
   if (bad && threadIdx.x == 0) h->error = 1;
   return bad;
 }
 
 // Base element offset of unit u = (b*L + l)*H + h.
 __device__ __forceinline__ int64_t unit_offset(const KvStrides& st, int u) {
+  if (st.even) return (int64_t)u * st.sh;
   int h = u % st.H;
   int bl = u / st.H;
   int l = bl % st.L;

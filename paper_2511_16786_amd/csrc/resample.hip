@@ -82,22 +82,47 @@ struct TablePtrs {
   float2* twid;      // see GridFft
 };
 
-// Passes of the grid transform: M = R0 R1 R2 by M / P threads that keep P points each.  Three passes at every
-// length; short lengths take small radices, so that a pair is spread over more threads (a short grid usually comes
-// with few pairs).  Twiddle table: powers 1..7 and 8, 16, .. (below R) of w_{R NS}^j for the second pass (NS = R0,
-// j < NS) and for the last (NS = R0 R1, j < threads), then e^{i pi t / M}.
-__host__ __device__ constexpr int grid_points_per_thread(int m) {
-  return m % 3 == 0 ? (m <= 1536 ? 24 : 48) : (m <= 2048 ? 16 : 32);
+// Passes of the grid transform: M = R0 R1 R2 R3 (a radix 1 is no pass) by M / P threads that keep P points each.
+// Twiddle table: for every pass after the first, powers 1..7 and 8, 16, .. (below R) of w_{R NS}^j, NS the product of
+// the radices before it, j < NS, or j < threads for the last pass; then e^{i pi t / M}.
+struct GridRadices {
+  int p, r[4];
+};
+__host__ __device__ constexpr GridRadices grid_radices(int m) {
+  switch (m) {
+    case 64: return {8, {8, 8, 1, 1}};
+    case 96: return {24, {8, 12, 1, 1}};
+    case 128: return {16, {8, 16, 1, 1}};
+    case 192: return {24, {8, 24, 1, 1}};
+    case 256: return {16, {16, 16, 1, 1}};
+    case 384: return {24, {8, 8, 6, 1}};
+    case 512: return {16, {8, 8, 8, 1}};
+    case 768: return {24, {8, 8, 12, 1}};
+    case 1024: return {16, {8, 8, 16, 1}};
+    case 1536: return {24, {8, 8, 24, 1}};
+    case 2048: return {16, {8, 16, 16, 1}};
+    case 3072: return {48, {16, 16, 12, 1}};
+    case 4096: return {32, {16, 16, 16, 1}};
+    case 6144: return {48, {16, 16, 24, 1}};
+    case 8192: return {32, {16, 16, 32, 1}};
+    case 12288: return {48, {16, 16, 48, 1}};
+    default: return {32, {32, 32, 16, 1}};         // 16384
+  }
 }
-__host__ __device__ constexpr int grid_radix0(int m) { return m == 16384 ? 32 : (m <= 2048 ? 8 : 16); }
-__host__ __device__ constexpr int grid_radix1(int m) { return m == 16384 ? 32 : (m <= 1536 ? 8 : 16); }
-__host__ __device__ constexpr int grid_radix2(int m) { return m / (grid_radix0(m) * grid_radix1(m)); }
+__host__ __device__ constexpr int grid_threads(int m) { return m / grid_radices(m).p; }
 __host__ __device__ constexpr int twid_powers(int r) { return (r < 8 ? r : 8) - 1 + (r - 1) / 8; }
-__host__ __device__ constexpr int twid_last_off(int m) { return twid_powers(grid_radix1(m)) * grid_radix0(m); }
-__host__ __device__ constexpr int twid_phase_off(int m) {
-  return twid_last_off(m) + twid_powers(grid_radix2(m)) * (m / grid_points_per_thread(m));
+// first entry of the factors of pass k (k = 1, 2, 3), and of the phases for the first k that is no pass
+__host__ __device__ constexpr int twid_off(int m, int k) {
+  const GridRadices g = grid_radices(m);
+  int off = 0, ns = g.r[0];
+  for (int i = 1; i < k && i < 4 && ns < m; ++i) {
+    off += twid_powers(g.r[i]) * (ns * g.r[i] == m ? m / g.p : ns);
+    ns *= g.r[i];
+  }
+  return off;
 }
-__host__ __device__ constexpr int twid_size(int m) { return twid_phase_off(m) + m / grid_points_per_thread(m); }
+__host__ __device__ constexpr int twid_phase_off(int m) { return twid_off(m, 4); }
+__host__ __device__ constexpr int twid_size(int m) { return twid_phase_off(m) + grid_threads(m); }
 
 __device__ float2 unit_root(double frac) {        // e^{-2 pi i frac}
   double s, c;
@@ -166,19 +191,16 @@ __global__ __launch_bounds__(256) void resample_table_kernel(TablePtrs tp, int n
   }
   id -= m;
   if (id >= twid_size(m)) return;
-  const int r0 = grid_radix0(m), threads = m / grid_points_per_thread(m);
-  auto power = [](int slot, int radix) {
-    const int low = (radix < 8 ? radix : 8) - 1;
-    return slot < low ? slot + 1 : 8 * (slot - low + 1);
-  };
   float2 v;
-  if (id < twid_last_off(m)) {
-    v = unit_root((double)(power(id / r0, grid_radix1(m)) * (id % r0)) / (double)(r0 * grid_radix1(m)));
-  } else if (id < twid_phase_off(m)) {
-    const int j = id - twid_last_off(m);
-    v = unit_root((double)(power(j / threads, grid_radix2(m)) * (j % threads)) / (double)m);
-  } else {
+  if (id >= twid_phase_off(m)) {
     v = unit_root(-0.5 * (double)(id - twid_phase_off(m)) / (double)m);
+  } else {
+    const GridRadices gr = grid_radices(m);
+    int k = 1, ns = gr.r[0];
+    while (id >= twid_off(m, k + 1)) ns *= gr.r[k++];
+    const int stride = ns * gr.r[k] == m ? grid_threads(m) : ns, j = id - twid_off(m, k), slot = j / stride;
+    const int low = (gr.r[k] < 8 ? gr.r[k] : 8) - 1, power = slot < low ? slot + 1 : 8 * (slot - low + 1);
+    v = unit_root((double)(power * (j % stride)) / (double)(ns * gr.r[k]));
   }
   tp.twid[id] = v;
 }
@@ -270,7 +292,6 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
   constexpr int kTerms = sizeof(T) == 2 ? 1 : 3;
   constexpr int kBuf = sizeof(T) == 2 ? 2 : 1;    // steps of rows under way (a step's registers are refilled in place)
   extern __shared__ f32x4 wlds[];                 // [GT][steps][2][64]
-  if (ws_mismatch(hdr, kPathResample, n, r, d, dtype)) return;
   const int xcd = blockIdx.x & 7, slot_id = blockIdx.x >> 3;
   const int super = xcd * supers_per_xcd + slot_id % supers_per_xcd;
   if (super >= (m / 16 + GT - 1) / GT) return;
@@ -285,6 +306,7 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
   int first[GT];                                  // a tile's first step
 #pragma unroll
   for (int q = 0; q < GT; ++q) first[q] = s0s[tile0 + min(q, n_tiles - 1)];
+  if (ws_mismatch(hdr, kPathResample, n, r, d, dtype)) return;     // (waits for memory together with the above)
   const int s_end = first[GT - 1] + steps;
   const T* p = (second ? V : K) + unit_offset(st, mine ? unit : u0) + (slot - (second ? sm.nb : 0)) * 8 +
                (int64_t)(8 * (lane >> 4)) * st.sn;
@@ -355,10 +377,8 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
 
 __device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
-template <bool INV>
-__device__ __forceinline__ float2 cmul(float2 a, float2 w) {      // a * w, or a * conj(w)
-  return INV ? make_float2(fmaf(a.x, w.x, a.y * w.y), fmaf(a.y, w.x, -a.x * w.y))
-             : make_float2(fmaf(a.x, w.x, -a.y * w.y), fmaf(a.y, w.x, a.x * w.y));
+__device__ __forceinline__ float2 cmul(float2 a, float2 w) {
+  return make_float2(fmaf(a.x, w.x, -a.y * w.y), fmaf(a.y, w.x, a.x * w.y));
 }
 
 // cos(2 pi k / 192) of the first quadrant; every constant root the transforms use is on this circle
@@ -384,40 +404,37 @@ __device__ __forceinline__ constexpr float2 root(int k, int n) {
   return float2{cos192(k * (192 / n)), cos192(k * (192 / n) + 48)};
 }
 
-template <bool INV>
 __device__ __forceinline__ void dft2(float2 (&v)[2]) {
   const float2 a = v[0], b = v[1];
   v[0] = cadd(a, b);
   v[1] = csub(a, b);
 }
-template <bool INV>
 __device__ __forceinline__ void dft3(float2 (&v)[3]) {
   const float2 t = cadd(v[1], v[2]), d = csub(v[1], v[2]);
-  const float k = INV ? -0.86602540378443865f : 0.86602540378443865f;
+  const float k = 0.86602540378443865f;
   const float2 m = make_float2(fmaf(-0.5f, t.x, v[0].x), fmaf(-0.5f, t.y, v[0].y));
   v[0] = cadd(v[0], t);
   v[1] = make_float2(fmaf(k, d.y, m.x), fmaf(-k, d.x, m.y));
   v[2] = make_float2(fmaf(-k, d.y, m.x), fmaf(k, d.x, m.y));
 }
-template <bool INV>
 __device__ __forceinline__ void dft4(float2 (&v)[4]) {
   const float2 s = cadd(v[0], v[2]), t = csub(v[0], v[2]), u = cadd(v[1], v[3]), w = csub(v[1], v[3]);
   const float2 p = make_float2(t.x + w.y, t.y - w.x), q = make_float2(t.x - w.y, t.y + w.x);
   v[0] = cadd(s, u);
-  v[1] = INV ? q : p;
+  v[1] = p;
   v[2] = csub(s, u);
-  v[3] = INV ? p : q;
+  v[3] = q;
 }
 
 // Transform of R points in registers, natural order on both sides: R = A * B with A-point transforms
 // over the strided points, constant factors, B-point transforms.
 template <int R>
 constexpr int first_factor() { return R == 2 || R == 3 || R == 4 ? R : (R % 4 == 0 ? 4 : 2); }
-template <int R, bool INV>
+template <int R>
 __device__ __forceinline__ void dft(float2 (&v)[R]) {
-  if constexpr (R == 2) dft2<INV>(v);
-  else if constexpr (R == 3) dft3<INV>(v);
-  else if constexpr (R == 4) dft4<INV>(v);
+  if constexpr (R == 2) dft2(v);
+  else if constexpr (R == 3) dft3(v);
+  else if constexpr (R == 4) dft4(v);
   else {
     constexpr int A = first_factor<R>(), B = R / A;
     float2 y[A][B];
@@ -426,17 +443,17 @@ __device__ __forceinline__ void dft(float2 (&v)[R]) {
       float2 u[A];
 #pragma unroll
       for (int a = 0; a < A; ++a) u[a] = v[B * a + b];
-      dft<A, INV>(u);
+      dft<A>(u);
 #pragma unroll
       for (int a = 0; a < A; ++a) {
         if (a * b == 0) y[a][b] = u[a];
-        else if (4 * a * b == R) y[a][b] = INV ? make_float2(-u[a].y, u[a].x) : make_float2(u[a].y, -u[a].x);
-        else y[a][b] = cmul<INV>(u[a], root(a * b, R));
+        else if (4 * a * b == R) y[a][b] = make_float2(u[a].y, -u[a].x);
+        else y[a][b] = cmul(u[a], root(a * b, R));
       }
     }
 #pragma unroll
     for (int a = 0; a < A; ++a) {
-      dft<B, INV>(y[a]);
+      dft<B>(y[a]);
 #pragma unroll
       for (int b = 0; b < B; ++b) v[a + A * b] = y[a][b];
     }
@@ -445,50 +462,63 @@ __device__ __forceinline__ void dft(float2 (&v)[R]) {
 
 template <int M>
 struct GridPlan {
-  static constexpr int P = grid_points_per_thread(M), T = M / P;
-  static constexpr int R0 = grid_radix0(M), R1 = grid_radix1(M), R2 = grid_radix2(M);
-  static constexpr int kPadShift = R0 == 8 ? 3 : (R0 == 16 ? 4 : 5);   // one slot of padding per R0: the strided
-  static constexpr int kLds = M + (M >> kPadShift) + 1;                // writes of a pass fall on distinct banks
+  static constexpr GridRadices G = grid_radices(M);
+  static constexpr int P = G.p, T = M / P, R0 = G.r[0], R1 = G.r[1], R2 = G.r[2], R3 = G.r[3];
+  // One slot of padding per R0 (or T, where fewer): the strided writes of a pass fall on distinct banks.
+  static constexpr int log2(int v) { return v <= 1 ? 0 : 1 + log2(v / 2); }
+  static constexpr int kPadShift = log2(R0 < T ? R0 : T);
+  static constexpr int kLds = M + (M >> kPadShift) + 1;
+  static_assert(R0 * R1 * R2 * R3 == M && T % (1 << kPadShift) == 0, "radices of the grid transform");
 };
 
 // element i + k of a table: uniform base and constant part, 32-bit part of the lane
-__device__ __forceinline__ float2 at(const float2* __restrict__ base, int k, uint32_t i) {
-  return *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(base + k) + i * (uint32_t)sizeof(float2));
+__device__ __forceinline__ float2 at(const float2* base, int k, uint32_t i) {
+  // (said to be global memory: a pointer that went through an asm statement has lost that)
+  typedef const __attribute__((address_space(1))) f32x2* Global;
+  const f32x2 v = *(Global)(reinterpret_cast<const char*>(base + k) + i * (uint32_t)sizeof(float2));
+  return make_float2(v.x, v.y);
 }
 
 // Length-M complex transform of one column pair; natural order before and after, exchanges through LDS.
-template <int M, bool INV>
+template <int M>
 struct GridFft {
   using G = GridPlan<M>;
   static constexpr int P = G::P, T = G::T;
   // slot of point i; T and NS * R are multiples of 2^kPadShift, so that pad(i + T q) = pad(i) + pad(T q)
   static __device__ __forceinline__ constexpr int pad(int i) { return i + (i >> G::kPadShift); }
 
-  // Pass of radix R after NS-point transforms are done: butterfly j = t + T c takes the points j + (M/R) q,
-  // which are this thread's own, times w_{R NS}^{(j mod NS) q}.
+  // Factors w_{R NS}^{(j mod NS) q} of a pass, q = lo + 8 hi from stored powers 1..7 and 8 hi.
   template <int R, int NS>
-  static __device__ __forceinline__ void pass(float2 (&x)[P], float* lds, const float2* __restrict__ tw, int t) {
-    constexpr int C = P / R;
-    float re[P];
-    constexpr bool kLast = R * NS == M;
-    if constexpr (NS > 1) {
-      // factors q = lo + 8 hi from stored powers lo = 1..7 and 8 hi; butterflies of one thread differ by a
-      // constant factor in the last pass, and by none before
-      constexpr int HI = (R - 1) / 8;
-      const int j = kLast ? t : t & (NS - 1);
+  struct Factors {
+    static constexpr int HI = (R - 1) / 8;
+    float2 lo[8], hi[HI + 1];
+    __device__ __forceinline__ void load(const float2* __restrict__ tw, int t) {
+      constexpr bool kLast = R * NS == M;
       constexpr int stride = kLast ? T : NS;
-      float2 lo[8], hi[HI + 1];
+      const int j = kLast ? t : t & (NS - 1);
 #pragma unroll
       for (int q = 1; q < 8; ++q)
         if (q < R) lo[q] = at(tw, (q - 1) * stride, j);
 #pragma unroll
       for (int q = 1; q <= HI; ++q) hi[q] = at(tw, ((R < 8 ? R : 8) - 1 + q - 1) * stride, j);
+    }
+    __device__ __forceinline__ float2 get(int q) const {
+      return q < 8 ? lo[q] : (q % 8 == 0 ? hi[q / 8] : cmul(lo[q % 8], hi[q / 8]));
+    }
+  };
+
+  // Pass of radix R after NS-point transforms are done: butterfly j = t + T c takes the points j + (M/R) q,
+  // which are this thread's own; the butterflies of a thread share the factors, in the last pass up to a constant.
+  template <int R, int NS>
+  static __device__ __forceinline__ void butterflies(float2 (&x)[P], const Factors<R, NS>& f) {
+    constexpr int C = P / R;
+    constexpr bool kLast = R * NS == M;
+    if constexpr (NS > 1) {
 #pragma unroll
       for (int q = 1; q < R; ++q) {
-        const float2 w = q < 8 ? lo[q] : (q % 8 == 0 ? hi[q / 8] : cmul<false>(lo[q % 8], hi[q / 8]));
+        const float2 w = f.get(q);
 #pragma unroll
-        for (int c = 0; c < C; ++c)
-          x[c + C * q] = cmul<INV>(x[c + C * q], kLast && c > 0 ? cmul<false>(w, root(c * q, P)) : w);
+        for (int c = 0; c < C; ++c) x[c + C * q] = cmul(x[c + C * q], kLast && c > 0 ? cmul(w, root(c * q, P)) : w);
         if (q % 8 == 7) __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -498,39 +528,58 @@ struct GridFft {
 #pragma unroll
       for (int q = 0; q < R; ++q) v[q] = x[c + C * q];
       __builtin_amdgcn_sched_barrier(0);
-      dft<R, INV>(v);
+      dft<R>(v);
 #pragma unroll
       for (int q = 0; q < R; ++q) x[c + C * q] = v[q];
     }
-    if constexpr (!kLast) {
-      // Real parts, then imaginary parts, through the same half: half the LDS keeps twice the waves resident.
-      // Point (j / NS) NS R + j % NS + q NS of butterfly j = t + T c (T is a multiple of NS).
-      float* o = lds + pad((t / NS) * (NS * R) + (t & (NS - 1)));
-      const float* in = lds + pad(t);
-#pragma unroll
-      for (int c = 0; c < C; ++c)
-#pragma unroll
-        for (int q = 0; q < R; ++q) o[pad(T * c * R) + (NS == 1 ? q : pad(q * NS))] = x[c + C * q].x;
-      __syncthreads();
-#pragma unroll
-      for (int q = 0; q < P; ++q) re[q] = in[pad(T * q)];
-      __syncthreads();
-#pragma unroll
-      for (int c = 0; c < C; ++c)
-#pragma unroll
-        for (int q = 0; q < R; ++q) o[pad(T * c * R) + (NS == 1 ? q : pad(q * NS))] = x[c + C * q].y;
-      __syncthreads();
-#pragma unroll
-      for (int q = 0; q < P; ++q) x[q] = make_float2(re[q], in[pad(T * q)]);
-      __syncthreads();
-      // (table loads of the next pass stay behind the exchange: hoisted, they cost the registers of a pass)
-      __builtin_amdgcn_sched_barrier(0);
-    }
   }
+  // Results of a pass to where the next one takes them: real parts, then imaginary parts, through the same half
+  // (half the LDS keeps twice the waves resident).  Point (j / NS) NS R + j % NS + q NS of butterfly j = t + T c.
+  template <int R, int NS>
+  static __device__ __forceinline__ void exchange(float2 (&x)[P], float* lds, int t) {
+    constexpr int C = P / R;
+    float* o = lds + pad((t / NS) * (NS * R) + (t & (NS - 1)));
+    const float* in = lds + pad(t);
+    float re[P];
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+      for (int q = 0; q < R; ++q) o[pad(T * c * R) + pad(q * NS)] = x[c + C * q].x;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < P; ++q) re[q] = in[pad(T * q)];
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+      for (int q = 0; q < R; ++q) o[pad(T * c * R) + pad(q * NS)] = x[c + C * q].y;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < P; ++q) x[q] = make_float2(re[q], in[pad(T * q)]);
+    __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  // (a pass's factors are requested before the exchange that precedes it)
   static __device__ __forceinline__ void run(float2 (&x)[P], float* lds, const float2* __restrict__ twid, int t) {
-    pass<G::R0, 1>(x, lds, twid, t);
-    pass<G::R1, G::R0>(x, lds, twid, t);
-    pass<G::R2, G::R0 * G::R1>(x, lds, twid + twid_last_off(M), t);
+    constexpr int N1 = G::R0, N2 = N1 * G::R1, N3 = N2 * G::R2;
+    Factors<G::R0, 1> f0;
+    Factors<G::R1, N1> f1;
+    butterflies<G::R0, 1>(x, f0);
+    f1.load(twid, t);
+    exchange<G::R0, 1>(x, lds, t);
+    butterflies<G::R1, N1>(x, f1);
+    if constexpr (G::R2 > 1) {
+      Factors<G::R2, N2> f2;
+      f2.load(twid + twid_off(M, 2), t);
+      exchange<G::R1, N1>(x, lds, t);
+      butterflies<G::R2, N2>(x, f2);
+    }
+    if constexpr (G::R3 > 1) {
+      Factors<G::R3, N3> f3;
+      f3.load(twid + twid_off(M, 3), t);
+      exchange<G::R2, N2>(x, lds, t);
+      butterflies<G::R3, N3>(x, f3);
+    }
   }
 };
 
@@ -538,17 +587,19 @@ struct GridFft {
 // modes below the cut-off, transform back.  With the permuted input order the DFT carries DCT modes m and
 // M-m in the pair of bins (m, M-m):
 //     W'[m] = (f[m] + f[M-m])/2 W[m] + (f[m] - f[M-m])/2 e^{i pi m/M} W[M-m].
-// sum_m Re(conj(W) W') is the kept energy of both columns (the operator is symmetric).
+// sum_m Re(conj(W) W') is the kept energy of both columns (the operator is symmetric).  The way back is the same
+// transform with real and imaginary parts exchanged.  Short lengths (few workgroups) run it in the same code, since
+// such a launch would wait for the instructions of a second copy to be fetched (768 points: 13 instead of 16 us); the
+// lengths whose points fill the registers are better off with two copies (3072 points: 180 instead of 220 us).
 template <int M>
-__global__ __launch_bounds__(GridPlan<M>::T < 64 ? 64 : GridPlan<M>::T, 2) void grid_filter_kernel(
+__global__ __launch_bounds__(GridPlan<M>::T < 64 ? 64 : GridPlan<M>::T, GridPlan<M>::P <= 16 ? 4 : (GridPlan<M>::P == 24 ? 3 : 2)) void grid_filter_kernel(
     float2* __restrict__ grid, int pairs, int n, int r, int d, int dtype, WsHeader* hdr,
     const float2* __restrict__ filt, const float2* __restrict__ twid, double* __restrict__ elow) {
   using G = GridPlan<M>;
-  using F = GridFft<M, false>;
+  using F = GridFft<M>;
   constexpr int P = G::P, T = G::T, PB = T < 64 ? 64 / T : 1;
   extern __shared__ float lds_all[];
   __shared__ double wsum[T < 64 ? 1 : T / 64];
-  if (ws_mismatch(hdr, kPathResample, n, r, d, dtype)) return;
   const int t = threadIdx.x % T, pb = threadIdx.x / T;
   float* lds = lds_all + pb * G::kLds;
   const int pair = min(blockIdx.x * PB + pb, pairs - 1);   // (surplus lanes repeat the last pair)
@@ -557,39 +608,44 @@ __global__ __launch_bounds__(GridPlan<M>::T < 64 ? 64 : GridPlan<M>::T, 2) void 
   float2 x[P];
 #pragma unroll
   for (int q = 0; q < P; ++q) x[q] = at(g, T * q, lane_at);
-  F::run(x, lds, twid, t);
-
-  // each bin's mirror, W[M - m] (with W[M] = W[0])
-  float2 o[P];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-#pragma unroll
-    for (int q = 0; q < P; ++q) lds[F::pad(t) + F::pad(T * q)] = h ? x[q].y : x[q].x;
-    if (t == 0) lds[F::pad(M)] = h ? x[0].y : x[0].x;
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < P; ++q) (h ? o[q].y : o[q].x) = lds[F::pad(M - T * q) + F::pad(-t)];
-    __syncthreads();
-  }
-  const float2 ph = at(twid, twid_phase_off(M), t);
+  float2 ph = at(twid, twid_phase_off(M), t);
+  if (ws_mismatch(hdr, kPathResample, n, r, d, dtype)) return;
   float e = 0.f;
+#pragma unroll(P <= 24 ? 1 : 2)
+  for (int way = 0; way < 2; ++way) {
+    // (what the tables give is loaded and derived anew: kept from one way to the next it would fill the registers)
+    asm volatile("" : "+s"(twid), "+s"(filt), "+v"(ph.x), "+v"(ph.y));
+    F::run(x, lds, twid, t);
+    if (way == 1) break;
+    // each bin's mirror, W[M - m] (with W[M] = W[0])
+    float2 o[P];
 #pragma unroll
-  for (int q = 0; q < P; ++q) {
-    if (q % 8 == 0) __builtin_amdgcn_sched_barrier(0);
-    const float2 f = at(filt, T * q, t);
-    const float2 z = cmul<false>(o[q], cmul<true>(ph, root(q, 2 * P)));    // e^{i pi (t + T q) / M}
-    const float2 y = make_float2(fmaf(f.y, z.x, f.x * x[q].x), fmaf(f.y, z.y, f.x * x[q].y));
-    e = fmaf(x[q].x, y.x, fmaf(x[q].y, y.y, e));
-    x[q] = y;
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int q = 0; q < P; ++q) lds[F::pad(t) + F::pad(T * q)] = h ? x[q].y : x[q].x;
+      if (t == 0) lds[F::pad(M)] = h ? x[0].y : x[0].x;
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < P; ++q) (h ? o[q].y : o[q].x) = lds[F::pad(M - T * q) + F::pad(-t)];
+      __syncthreads();
+    }
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+      if (q % 8 == 0) __builtin_amdgcn_sched_barrier(0);
+      const float2 f = at(filt, T * q, t);
+      const float2 c = root(q, 2 * P);
+      const float2 z = cmul(o[q], cmul(ph, make_float2(c.x, -c.y)));         // e^{i pi (t + T q) / M}
+      const float2 y = make_float2(fmaf(f.y, z.x, f.x * x[q].x), fmaf(f.y, z.y, f.x * x[q].y));
+      e = fmaf(x[q].x, y.x, fmaf(x[q].y, y.y, e));
+      x[q] = make_float2(y.y, y.x);
+    }
+    __builtin_amdgcn_sched_barrier(0);
   }
-  __builtin_amdgcn_sched_barrier(0);
-  // the way back loads its factors again: kept from the way there they would cost 100 registers
-  asm volatile("" : "+s"(twid));
-  GridFft<M, true>::run(x, lds, twid, t);
-  asm volatile("" : "+v"(lane_at));                        // (nor are the load addresses worth keeping)
+  asm volatile("" : "+v"(lane_at));                        // (the load addresses are not worth keeping)
 #pragma unroll
   for (int q = 0; q < P; ++q)
-    *reinterpret_cast<float2*>(reinterpret_cast<char*>(g + T * q) + lane_at * (uint32_t)sizeof(float2)) = x[q];
+    *reinterpret_cast<float2*>(reinterpret_cast<char*>(g + T * q) + lane_at * (uint32_t)sizeof(float2)) =
+        make_float2(x[q].y, x[q].x);
 
   double es = (double)e;
 #pragma unroll
@@ -637,6 +693,32 @@ template <int CTRL>
 __device__ __forceinline__ float dpp(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
 }
+__device__ __forceinline__ float lane_of(float v, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+// Over the whole wave, in the vector and scalar pipes (a reduction by LDS permutes waits for LDS at every step).
+__device__ __forceinline__ float wave_max(float v) {
+  v = fmaxf(v, dpp<0x121>(v));
+  v = fmaxf(v, dpp<0x122>(v));
+  v = fmaxf(v, dpp<0x124>(v));
+  v = fmaxf(v, dpp<0x128>(v));
+  return fmaxf(fmaxf(lane_of(v, 0), lane_of(v, 16)), fmaxf(lane_of(v, 32), lane_of(v, 48)));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, true);
+  return v + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  v = dpp_add<0x128>(dpp_add<0x124>(dpp_add<0x122>(dpp_add<0x121>(v))));
+  double s = 0.0;
+#pragma unroll
+  for (int l = 0; l < 64; l += 16)
+    s += __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+  return s;
+}
 // Sums of v[0..3] over the 16 lanes of a row; a lane returns the sum of v[lane & 3].
 __device__ __forceinline__ float row_sums(const float (&v)[4], int lane) {
   const bool b0 = lane & 1, b1 = lane & 2;
@@ -652,7 +734,8 @@ constexpr int kResWorkgroups = 512;   // residual kernel: two for each compute u
 
 // One wave applies windows (32 grid points each) to the 16-token tiles they cover, 16 slots at a time.  Its work
 // is a list of segments: a window, a unit (four units at a time, one for each wave of a workgroup), a part of the
-// unit's slots.  Rows are requested two tiles ahead and grid values one window ahead, across segments.
+// unit's slots; with few segments (split) a workgroup's waves take the parts of a unit side by side instead of one
+// after the other.  Rows are requested two tiles ahead and grid values one window ahead, across segments.
 // Neighbouring windows read the same lines of the grid: an XCD takes a contiguous range of windows and its
 // workgroups walk (units, window) side by side, window fastest, so that its L2 serves what they share.
 // A lane holds slot lane & 15 throughout: columns 8 slot + j of tokens 4 (lane >> 4) + i, so that a load reads whole
@@ -660,7 +743,7 @@ constexpr int kResWorkgroups = 512;   // residual kernel: two for each compute u
 template <typename T>
 __global__ __launch_bounds__(256, 2) void residual_kernel(
     const T* __restrict__ K, const T* __restrict__ V, KvStrides st, int u0, int u1, int n, int r, int d, int dtype,
-    int m, int tpw, int wins, SlotMap sm, WsHeader* hdr, const _Float16* __restrict__ winv,
+    int m, int tpw, int wins, SlotMap sm, bool split, WsHeader* hdr, const _Float16* __restrict__ winv,
     const int* __restrict__ k0s, const float2* __restrict__ grid, float* __restrict__ scores,
     double* __restrict__ epart, UnitMap um) {
   constexpr int kBuf = sizeof(T) == 2 ? 2 : 1;             // tiles of rows under way
@@ -668,26 +751,30 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
   if (ws_mismatch(hdr, kPathResample, n, r, d, dtype)) return;
   const int lane = threadIdx.x & 63, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int quads = (u1 - u0 + 3) >> 2, tok_tiles = (n + 15) >> 4;
+  // units worked on side by side: one for each wave, or (split) as many as have a wave for every part
+  const int abreast = split ? 4 / sm.wpu : 4, parts = split ? 1 : sm.wpu;
+  const int my_unit = split ? wave / sm.wpu : wave, my_part = split ? wave % sm.wpu : 0;
+  const int sets = (u1 - u0 + abreast - 1) / abreast, tok_tiles = (n + 15) >> 4;
   const int xcd = blockIdx.x & 7, peers = gridDim.x >> 3;
   const int w_first = (int)((int64_t)wins * xcd >> 3), w_count = (int)((int64_t)wins * (xcd + 1) >> 3) - w_first;
-  const int items = w_count * quads;
+  const int items = w_count * sets;
   int item = blockIdx.x >> 3, part = 0;                    // segment under way
   if (item >= items) return;
 
   struct Seg {
-    int win, unit, part, tiles;
+    int win, unit, part, tiles, n0;                        // n0: position of the window's first even grid point
     const T* rows;                                         // this lane's columns of token 4 g
     const float2* gp;                                      // this lane's first column pair on the grid
   };
   auto segment = [&](int it, int pt) {
     Seg s;
-    s.part = pt;
-    const int quad = it / w_count;
-    s.win = w_first + it - quad * w_count;
-    s.unit = min(u0 + 4 * quad + wave, u1 - 1);            // (a surplus wave repeats the last unit)
+    s.part = my_part + pt;
+    const int set = (unsigned)it / (unsigned)w_count;
+    s.win = w_first + it - set * w_count;
+    s.n0 = k0s[s.win] >> 1;
+    s.unit = min(u0 + abreast * set + my_unit, u1 - 1);    // (a surplus wave repeats the last unit)
     s.tiles = max(min(tpw, tok_tiles - s.win * tpw), kBuf);   // (a tile too many is worked on and dropped)
-    const int mine = pt * 16 + (lane & 15), slot = mine < 2 * sm.nb ? mine : 0;
+    const int mine = s.part * 16 + (lane & 15), slot = mine < 2 * sm.nb ? mine : 0;
     const bool second = slot >= sm.nb;
     s.rows = (second ? V : K) + unit_offset(st, s.unit) + (slot - (second ? sm.nb : 0)) * 8 + (int64_t)(4 * g) * st.sn;
     s.gp = grid + ((size_t)(s.unit - u0) * 2 * sm.nb + slot) * 4 * m + 2 * g;
@@ -695,17 +782,16 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
   };
   auto following = [&](const Seg& s) {                     // (the last segment follows itself)
     int it = item, pt = part + 1;
-    if (pt == sm.wpu) { pt = 0; it += peers; }
+    if (pt == parts) { pt = 0; it += peers; }
     return it < items ? segment(it, pt) : s;
   };
   f32x4 v[4][4];
   auto load_window = [&](const Seg& s) {
-    const int n0 = k0s[s.win] >> 1;
 #pragma unroll
     for (int jp = 0; jp < 4; ++jp)
 #pragma unroll
       for (int c = 0; c < 4; ++c)
-        v[jp][c] = *reinterpret_cast<const f32x4*>(s.gp + (size_t)jp * m + (c < 2 ? n0 + 8 * c : m - 32 - n0 + 8 * c));
+        v[jp][c] = *reinterpret_cast<const f32x4*>(s.gp + (size_t)jp * m + (c < 2 ? s.n0 + 8 * c : m - 32 - s.n0 + 8 * c));
   };
   auto load_rows = [&](RowPiece<T> (&x)[4], const Seg& s, int tl) {
     const int t = (s.win * tpw + tl) * 16;
@@ -744,8 +830,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
       for (int c = 0; c < 4; ++c)
 #pragma unroll
         for (int q = 0; q < 4; ++q) mx = fmaxf(mx, fabsf(v[jp][c][q]));
-#pragma unroll
-    for (int s = 1; s < 64; s <<= 1) mx = fmaxf(mx, __shfl_xor(mx, s, 64));
+    mx = wave_max(mx);
     // largest magnitude of the window into [2^14, 2^15); powers of two, so nothing is rounded
     const int eb = max(14, min((int)(__float_as_uint(mx) >> 23), 254));
     const float scale = __uint_as_float((uint32_t)(268 - eb) << 23);
@@ -775,11 +860,8 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
                     use && !second ? (double)tot : 0.0, use && second ? (double)tot : 0.0};
     double* e = epart + (((size_t)cur.unit * wins + cur.win) * sm.wpu + cur.part) * 4;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-#pragma unroll
-      for (int s = 1; s < 64; s <<= 1) ev[k] += __shfl_xor(ev[k], s, 64);
-      if (lane == 0) e[k] = ev[k];
-    }
+    for (int k = 0; k < 4; ++k) ev[k] = wave_sum(ev[k]);
+    if (lane == 0) { e[0] = ev[0]; e[1] = ev[1]; e[2] = ev[2]; e[3] = ev[3]; }
   };
   auto step = [&](RowPiece<T> (&xb)[4]) {
     if (tl == 0) take_window();
@@ -810,8 +892,8 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     float sum = row_sums(h, lane);
     if ((lane & 15) < 4) {
       const int k = 4 * g + (lane & 3), token = t0 + k;
-      if (cur.part > 0) sum += part_sum[wave][16 * tl + k];
-      if (cur.part + 1 < sm.wpu) part_sum[wave][16 * tl + k] = sum;
+      if (part > 0) sum += part_sum[wave][16 * tl + k];
+      if (split || part + 1 < parts) part_sum[wave][16 * tl + k] = sum;
       else if (token < n && tl < tpw) scores[(size_t)out_unit(um, cur.unit) * n + token] = sum / (float)d;
     }
     if (tl + kBuf < cur.tiles) load_rows(xb, cur, tl + kBuf);
@@ -820,7 +902,18 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     if (last) {
       asm volatile("");                                    // (keeps what follows out of every tile's path)
       record();
-      if (++part == sm.wpu) { part = 0; item += peers; }
+      if (split) {                                         // (segments are the same for all waves of a workgroup)
+        __syncthreads();
+        if (my_part == 0)
+          for (int k = lane; k < 16 * cur.tiles; k += 64) {
+            const int token = cur.win * tpw * 16 + k;
+            float s = part_sum[wave][k];
+            for (int p = 1; p < sm.wpu; ++p) s += part_sum[wave + p][k];
+            if (token < n && k < 16 * tpw) scores[(size_t)out_unit(um, cur.unit) * n + token] = s / (float)d;
+          }
+        __syncthreads();
+      }
+      if (++part == parts) { part = 0; item += peers; }
       more = item < items;
       cur = nxt;
       nxt = following(cur);
@@ -872,7 +965,7 @@ static size_t resample_chunk_bytes() {
 // Grid length for this shape and cut-off, 0 if the realisation does not apply.
 static int grid_length(const fc_kv_desc& d, int32_t r) {
   if (d.head_dim % 8 != 0 || d.head_dim > 256 || r < 1 || 2 * (int64_t)r > d.n_tokens) return 0;
-  for (int m2 = 512; m2 <= 16384; m2 *= 2)
+  for (int m2 = 64; m2 <= 16384; m2 *= 2)
     for (int m = m2; m <= 16384 && m <= m2 + m2 / 2; m += m2 / 2)   // 2^k and 3 2^(k-1)
       if (4 * (int64_t)m >= 7 * (int64_t)r && 16 * (int64_t)m >= d.n_tokens)   // M >= 1.75 r: the accuracy above
         return 5 * (int64_t)d.n_tokens >= 4 * (int64_t)m ? m : 0;   // a 16-token tile and its windows fit 32 points
@@ -1002,7 +1095,7 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
     const int pairs = (u1 - u0) * 2 * lay.nb * 4;
 #define FC_FILTER(MV) case MV: e = launch_filter<MV>(grid, pairs, n, r, d.head_dim, d.dtype, hdr, filt, twid, elow, s); break;
     switch (m) {
-      FC_FILTER(512) FC_FILTER(768) FC_FILTER(1024) FC_FILTER(1536) FC_FILTER(2048) FC_FILTER(3072) FC_FILTER(4096)
+      FC_FILTER(64) FC_FILTER(96) FC_FILTER(128) FC_FILTER(192) FC_FILTER(256) FC_FILTER(384) FC_FILTER(512) FC_FILTER(768) FC_FILTER(1024) FC_FILTER(1536) FC_FILTER(2048) FC_FILTER(3072) FC_FILTER(4096)
       FC_FILTER(6144) FC_FILTER(8192) FC_FILTER(12288) FC_FILTER(16384)
       default: e = hipErrorInvalidValue;
     }
@@ -1010,9 +1103,12 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
     if (e != hipSuccess) return e;
     {
       ProfileScope ps("residual_kernel", s);
-      const int64_t items = (int64_t)((lay.wins + 7) / 8) * ((u1 - u0 + 3) / 4);   // of the XCD with most windows
-      hipLaunchKernelGGL(residual_kernel<T>, dim3(8 * (int)std::min<int64_t>(items, kResWorkgroups / 8)), dim3(256), 0, s, K, V, st,
-                         u0, u1, n, r, d.head_dim, d.dtype, m, lay.tpw, lay.wins, sm, hdr,
+      const int64_t per_xcd = (lay.wins + 7) / 8;          // windows of the XCD with most
+      const bool split = lay.wpu > 1 && per_xcd * ((u1 - u0 + 3) / 4) < kResWorkgroups / 8;
+      const int abreast = split ? 4 / lay.wpu : 4;
+      const int64_t items = per_xcd * ((u1 - u0 + abreast - 1) / abreast);
+      hipLaunchKernelGGL(residual_kernel<T>, dim3(8 * (int)std::min<int64_t>(items, kResWorkgroups / 8)), dim3(256), 0,
+                         s, K, V, st, u0, u1, n, r, d.head_dim, d.dtype, m, lay.tpw, lay.wins, sm, split, hdr,
                          reinterpret_cast<const _Float16*>(base + lay.winv),
                          reinterpret_cast<const int*>(base + lay.k0), grid, scores, epart, um);
     }
