@@ -1,11 +1,11 @@
 // Selection of the b_l highest-scoring KV pairs of every unit and the packed gather (the rule in
 // the sentence after Eq. 10: per layer, the pairs that deviate most, as many as the budget allows).
 //
-// select_kernel / select_large_kernel: one workgroup per unit.  A four-pass 8-bit radix select
-//   over the fp32 bit patterns finds the k-th largest key and how many keys equal to it are
-//   still needed; a compaction in token order (prefix counts) then writes the kept indices, which
-//   yields them ascending and gives ties to the lower index without any sort.  Up to 65536
-//   tokens the keys stay in registers between the passes; beyond that they are re-read from L2.
+// select_kernel / select_large_kernel: one workgroup per unit.  Counting passes over the fp32 bit
+//   patterns (a narrowing key range, or 8-bit digits) find the k-th largest key and how many keys
+//   equal to it are still needed; a compaction in token order (prefix counts) then writes the kept
+//   indices, which yields them ascending and gives ties to the lower index without any sort.  Up to
+//   65536 tokens the keys stay in registers between the passes; beyond that they are re-read from L2.
 //   Only integer atomics are used (LDS histogram), so the result is deterministic.
 // gather_kernel: one 16-byte vector per thread; rows are bit copies.
 #include "fc_common.h"
@@ -130,31 +130,42 @@ __global__ __launch_bounds__(kSelThreads) void select_large_kernel(
   }
 }
 
-// Register-resident variant for n <= 64*1024: thread t keeps tokens [t*chunk, (t+1)*chunk) in
-// registers (at most MAXC = 32 or 64 of them), so the scores are read once; the ordered compaction
-// is one block-wide scan of the per-thread counts followed by sequential writes.
+// Register-resident variant for n <= 64*1024.  A wave keeps 64 * MAXC consecutive tokens, lane l the tokens
+// 256 j + 4 l + e of them (coalesced 16-byte loads).  The k-th largest key is found by narrowing a key range:
+// 2048 equal bins between the lowest and the highest key in question, counted in LDS, take a range of any width
+// to a single key in three passes, usually in two (the search ends when a bin is kept whole); bins of equal width
+// between the extremes spread the keys over many counters, where digits of the key put nearly all of them on a few.
+// Latency-bound: one workgroup per unit, a barrier per step (32768 tokens, 112 units: 35 -> 20 us; 512 tokens:
+// 22 -> 8 us against four passes of 8-bit digits, which also ran over MAXC = 32 keys whatever n was).
 constexpr int kSelMaxChunk = 64;
+constexpr int kSelBins = 2048;
 
-__device__ __forceinline__ unsigned wave_excl_scan(unsigned v, unsigned& total) {
-  const int lane = threadIdx.x & 63;
-  unsigned incl = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    unsigned o = __shfl_up(incl, d, 64);
-    if (lane >= d) incl += o;
-  }
-  total = __shfl(incl, 63, 64);
-  return incl - v;
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned dpp_u32(unsigned v) {       // 0 where there is no source lane
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ unsigned wave_incl_scan(unsigned v) {
+  v += dpp_u32<0x111, 0xF>(v);      // row_shr:1, 2, 4, 8
+  v += dpp_u32<0x112, 0xF>(v);
+  v += dpp_u32<0x114, 0xF>(v);
+  v += dpp_u32<0x118, 0xF>(v);
+  v += dpp_u32<0x142, 0xA>(v);      // row_bcast:15 into rows 1 and 3
+  v += dpp_u32<0x143, 0xC>(v);      // row_bcast:31 into rows 2 and 3
+  return v;
+}
+__device__ __forceinline__ unsigned below_me(unsigned long long mask, unsigned add) {   // set bits of lower lanes
+  return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, add));
 }
 
-template <bool SHARED, int MAXC>
-__global__ __launch_bounds__(kSelThreads) void select_kernel(
+template <bool SHARED, int NT, int MAXC>
+__global__ __launch_bounds__(NT) void select_kernel(
     const float* __restrict__ scores, const int* __restrict__ budgets,
-    const long long* __restrict__ layer_offsets, int L, int H, int n, int chunk, long long rows_per_seq,
+    const long long* __restrict__ layer_offsets, int L, int H, int n, long long rows_per_seq,
     int* __restrict__ idx_out) {
-  __shared__ unsigned hist[256];
-  __shared__ unsigned wave_gt[kSelThreads / 64], wave_eq[kSelThreads / 64];
-  __shared__ unsigned sh_bucket, sh_need;
+  constexpr int kWaves = NT / 64, kPer = kSelBins / NT;
+  __shared__ unsigned hist[kSelBins];
+  __shared__ unsigned wave_a[kWaves], wave_b[kWaves];
+  __shared__ unsigned sh_bin, sh_need, sh_count;
 
   // per-head mode: one workgroup per (b,l,h); layer-shared mode: one per (b,l), writing H copies
   const int unit = SHARED ? blockIdx.x * H : blockIdx.x;
@@ -162,105 +173,131 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
   const int k = budgets[(size_t)b * L + l];
   const int copies = SHARED ? H : 1;
   const long long off = layer_offsets[(size_t)b * (L + 1) + l] + (long long)h * k;
-  if (k <= 0 || k > n || off < 0 || off + (long long)copies * k > rows_per_seq) return;   // bad budgets
   const float* s = scores + (size_t)unit * n;
-  int* out = idx_out + (size_t)b * rows_per_seq + off;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int i0 = tid * chunk;
+  const int i0 = wave * 64 * MAXC + lane * 4;
 
-  // keys of this thread's chunk; positions past n get key 0, below every real key (real keys of
-  // non-negative floats have the top bit set, of negative floats are >= 1 unless the score is NaN)
+  // tokens past n get key 0, below every real key (non-negative floats have the top bit set, negative ones are
+  // >= 1 unless the score is NaN)
   uint32_t key[MAXC];
-  if (!SHARED && (chunk & 3) == 0 && (n & 3) == 0 && (reinterpret_cast<uintptr_t>(s) & 15u) == 0) {
+  if (!SHARED && (n & 3) == 0 && (reinterpret_cast<uintptr_t>(s) & 15u) == 0) {
 #pragma unroll
     for (int j = 0; j < MAXC; j += 4) {
+      const int i = i0 + j * 64;
       float4 f = make_float4(0.f, 0.f, 0.f, 0.f);
-      const bool in = j < chunk && i0 + j < n;
-      if (in) f = *reinterpret_cast<const float4*>(s + i0 + j);
+      const bool in = i < n;
+      if (in) f = *reinterpret_cast<const float4*>(s + i);
       key[j] = in ? order_key(f.x) : 0u; key[j + 1] = in ? order_key(f.y) : 0u;
       key[j + 2] = in ? order_key(f.z) : 0u; key[j + 3] = in ? order_key(f.w) : 0u;
     }
   } else {
 #pragma unroll
     for (int j = 0; j < MAXC; ++j) {
-      const bool in = j < chunk && i0 + j < n;
-      key[j] = in ? order_key(score_at<SHARED>(s, i0 + j, n, H)) : 0u;
+      const int i = i0 + (j >> 2) * 256 + (j & 3);
+      key[j] = i < n ? order_key(score_at<SHARED>(s, i, n, H)) : 0u;
     }
   }
-  const int mine = max(0, min(chunk, n - i0));     // valid keys of this thread
+  if (k <= 0 || k > n || off < 0 || off + (long long)copies * k > rows_per_seq) return;   // bad budgets
+  int* out = idx_out + (size_t)b * rows_per_seq + off;
 
-  uint32_t prefix = 0, mask = 0;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) hist[tid * kPer + q] = 0;
+  uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+#pragma unroll
+  for (int j = 0; j < MAXC; ++j) {
+    lo = min(lo, key[j] - 1u);                 // (key 0 wraps to the top and does not count)
+    hi = max(hi, key[j]);
+  }
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    lo = min(lo, (uint32_t)__shfl_xor((int)lo, d, 64));
+    hi = max(hi, (uint32_t)__shfl_xor((int)hi, d, 64));
+  }
+  if (lane == 0) { wave_a[wave] = lo; wave_b[wave] = hi; }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) { lo = min(lo, wave_a[w]); hi = max(hi, wave_b[w]); }
+  lo += 1u;
+
+  // the k-th largest key is the need-th largest of the keys in [lo, hi]; `whole`: all of [lo, hi] is kept
   unsigned need = (unsigned)k;
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    if (tid < 256) hist[tid] = 0;
-    __syncthreads();
-    unsigned run_dig = 0, run_cnt = 0;
+  bool whole = false;
+  while (hi > lo) {
+    const uint32_t width = hi - lo;
+    const int shift = max(0, 21 - __clz((int)width));          // width >> shift < 2048
 #pragma unroll
     for (int j = 0; j < MAXC; ++j) {
-      // neighbouring keys mostly share their leading digits, so runs of equal digits are counted
-      // in a register and flushed with one atomic (integer adds: the histogram is the same)
-      const bool in = j < mine && (key[j] & mask) == prefix;
-      const unsigned dig = (key[j] >> shift) & 255u;
-      if (in && run_cnt > 0 && dig == run_dig) {
-        ++run_cnt;
-      } else {
-        if (run_cnt > 0) atomicAdd(&hist[run_dig], run_cnt);
-        run_dig = dig;
-        run_cnt = in ? 1u : 0u;
-      }
+      const uint32_t rel = key[j] - lo;
+      if (rel <= width) atomicAdd(&hist[rel >> shift], 1u);
     }
-    if (run_cnt > 0) atomicAdd(&hist[run_dig], run_cnt);
     __syncthreads();
-    if (wave == 0) {
-      unsigned c0 = hist[lane * 4 + 0], c1 = hist[lane * 4 + 1], c2 = hist[lane * 4 + 2],
-               c3 = hist[lane * 4 + 3];
-      unsigned mine4 = c0 + c1 + c2 + c3;
-      unsigned run = mine4;
+    // counts from the top: thread t has the kPer bins from 2047 - t kPer downwards
+    unsigned c[kPer], mine = 0;
 #pragma unroll
-      for (int d = 1; d < 64; d <<= 1) {
-        unsigned v = __shfl_down(run, d, 64);
-        if (lane + d < 64) run += v;
-      }
-      const unsigned above = run - mine4;
-      if (above < need && need <= above + mine4) {
-        unsigned a = above, bucket;
-        if (a + c3 >= need) bucket = 3;
-        else { a += c3; if (a + c2 >= need) bucket = 2;
-        else { a += c2; if (a + c1 >= need) bucket = 1;
-        else { a += c1; bucket = 0; } } }
-        sh_bucket = lane * 4 + bucket;
-        sh_need = need - a;
+    for (int q = 0; q < kPer; ++q) {
+      c[q] = hist[kSelBins - 1 - tid * kPer - q];
+      hist[kSelBins - 1 - tid * kPer - q] = 0;
+      mine += c[q];
+    }
+    const unsigned incl = wave_incl_scan(mine);
+    if (lane == 63) wave_a[wave] = incl;
+    __syncthreads();
+    unsigned above = incl - mine;
+    for (int w = 0; w < wave; ++w) above += wave_a[w];
+    if (above < need && need <= above + mine) {
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) {
+        if (above < need && need <= above + c[q]) {
+          sh_bin = kSelBins - 1 - tid * kPer - q;
+          sh_need = need - above;
+          sh_count = c[q];
+        }
+        above += c[q];
       }
     }
     __syncthreads();
-    prefix |= sh_bucket << shift;
-    mask |= 255u << shift;
+    lo += sh_bin << shift;
+    hi = min(hi, lo + ((1u << shift) - 1u));
     need = sh_need;
+    if (sh_count == need) { whole = true; break; }
   }
-  const uint32_t tau = prefix;
-
-  unsigned cg = 0, ce = 0;
+  const uint32_t tau = lo;
+  // kept: keys above tau, and of those equal to it the `need` with the lowest token indices (keys >= tau, if `whole`)
+  uint32_t count_gt = 0, count_eq = 0;         // of this wave
 #pragma unroll
   for (int j = 0; j < MAXC; ++j) {
-    cg += (j < mine && key[j] > tau) ? 1u : 0u;
-    ce += (j < mine && key[j] == tau) ? 1u : 0u;
+    count_gt += __popcll(__ballot(whole ? key[j] >= tau : key[j] > tau));
+    if (!whole) count_eq += __popcll(__ballot(key[j] == tau));
   }
-  unsigned tg, te;
-  unsigned pg = wave_excl_scan(cg, tg), pe = wave_excl_scan(ce, te);
-  if (lane == 0) { wave_gt[wave] = tg; wave_eq[wave] = te; }
+  __syncthreads();                              // (wave_a is still being read above)
+  if (lane == 0) { wave_a[wave] = count_gt; wave_b[wave] = count_eq; }
   __syncthreads();
-  for (int w = 0; w < wave; ++w) { pg += wave_gt[w]; pe += wave_eq[w]; }
-  // pg / pe = kept-candidates strictly before this thread's chunk (greater / equal to tau)
+  unsigned pg = 0, pe = 0;                      // kept by lower waves: above tau; equal to it (capped later)
+  for (int w = 0; w < wave; ++w) { pg += wave_a[w]; pe += wave_b[w]; }
 #pragma unroll
-  for (int j = 0; j < MAXC; ++j) {
-    if (j < mine) {
-      const bool gt = key[j] > tau, eq = key[j] == tau;
-      if (gt || (eq && pe < need)) {
-        const unsigned pos = pg + min(pe, need);
-        for (int c = 0; c < copies; ++c) out[(size_t)c * k + pos] = i0 + j;
+  for (int j = 0; j < MAXC; j += 4) {
+    const int i = i0 + j * 64;
+    unsigned long long mg[4], me[4] = {0, 0, 0, 0};
+    unsigned my_g = pg, my_e = pe;              // before this lane's first token of the group
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      mg[e] = __ballot(whole ? key[j + e] >= tau : key[j + e] > tau);
+      my_g = below_me(mg[e], my_g);
+      if (!whole) {
+        me[e] = __ballot(key[j + e] == tau);
+        my_e = below_me(me[e], my_e);
       }
-      pg += gt ? 1u : 0u;
-      pe += eq ? 1u : 0u;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool gt = whole ? key[j + e] >= tau : key[j + e] > tau, eq = !whole && key[j + e] == tau;
+      const unsigned pos = my_g + min(my_e, need);
+      if ((gt || (eq && my_e < need)) && pos < (unsigned)k && i + e < n)
+        for (int c = 0; c < copies; ++c) out[(size_t)c * k + pos] = i + e;
+      my_g += gt ? 1u : 0u;
+      my_e += eq ? 1u : 0u;
+      pg += __popcll(mg[e]);
+      pe += __popcll(me[e]);
     }
   }
 }
@@ -337,26 +374,31 @@ hipError_t select_gather_launch(const void* K, const void* V, const fc_kv_desc& 
   const long long* offs = reinterpret_cast<const long long*>(layer_offsets);
   {
     ProfileScope ps(shared ? "select_shared_kernel" : "select_kernel", s);
-    const int chunk = (d.n_tokens + kSelThreads - 1) / kSelThreads;
-    const dim3 grid(shared ? units / d.kv_heads : units), block(kSelThreads);
+    const dim3 grid(shared ? units / d.kv_heads : units);
     const long long rows = (long long)rows_per_seq;
-    if (chunk <= 32) {
-      if (shared)
-        hipLaunchKernelGGL((select_kernel<true, 32>), grid, block, 0, s, scores, budgets, offs, d.layers,
-                           d.kv_heads, d.n_tokens, (chunk + 3) & ~3, rows, idx_out);
-      else
-        hipLaunchKernelGGL((select_kernel<false, 32>), grid, block, 0, s, scores, budgets, offs, d.layers,
-                           d.kv_heads, d.n_tokens, (chunk + 3) & ~3, rows, idx_out);
-    } else if (chunk <= kSelMaxChunk && !shared) {   // (the layer-shared keys need too many registers)
-      hipLaunchKernelGGL((select_kernel<false, 64>), grid, block, 0, s, scores, budgets, offs, d.layers,
-                         d.kv_heads, d.n_tokens, (chunk + 3) & ~3, rows, idx_out);
+    const int n = d.n_tokens;
+#define FC_SELECT(SH, NT, MAXC)                                                                               \
+  hipLaunchKernelGGL((select_kernel<SH, NT, MAXC>), grid, dim3(NT), 0, s, scores, budgets, offs, d.layers,     \
+                     d.kv_heads, n, rows, idx_out)
+    // the fewest keys per thread that cover n; four waves while each has at most 16 (their barriers are cheaper)
+#define FC_SELECT_N(SH)                                                                                        \
+  if (n <= 1024) FC_SELECT(SH, 256, 4);                                                                        \
+  else if (n <= 4096) FC_SELECT(SH, 256, 16);                                                                  \
+  else if (n <= 8192) FC_SELECT(SH, 1024, 8);                                                                  \
+  else if (n <= 16384) FC_SELECT(SH, 1024, 16);                                                                \
+  else FC_SELECT(SH, 1024, 32)
+    if (n <= 32 * kSelThreads) {
+      if (shared) { FC_SELECT_N(true); } else { FC_SELECT_N(false); }
+    } else if (n <= kSelMaxChunk * kSelThreads) {
+      if (shared) FC_SELECT(true, 1024, 64); else FC_SELECT(false, 1024, 64);
+#undef FC_SELECT_N
+#undef FC_SELECT
+    } else if (shared) {
+      hipLaunchKernelGGL(select_large_kernel<true>, grid, dim3(kSelThreads), 0, s, scores, budgets, offs, d.layers,
+                         d.kv_heads, n, rows, idx_out);
     } else {
-      if (shared)
-        hipLaunchKernelGGL(select_large_kernel<true>, grid, block, 0, s, scores, budgets, offs, d.layers,
-                           d.kv_heads, d.n_tokens, rows, idx_out);
-      else
-        hipLaunchKernelGGL(select_large_kernel<false>, grid, block, 0, s, scores, budgets, offs, d.layers,
-                           d.kv_heads, d.n_tokens, rows, idx_out);
+      hipLaunchKernelGGL(select_large_kernel<false>, grid, dim3(kSelThreads), 0, s, scores, budgets, offs, d.layers,
+                         d.kv_heads, n, rows, idx_out);
     }
   }
   hipError_t e = hipGetLastError();
