@@ -52,7 +52,7 @@ typedef enum { FC_F32 = 0, FC_BF16 = 1 } fc_dtype;
 typedef enum {
   FC_PATH_AUTO = 0,  /* FC_PATH_FFT where it applies, else FC_PATH_DENSE */
   FC_PATH_DENSE = 1, /* products with stored bases on the matrix cores; any N, head_dim <= 256.  Short
-                        token axes use the basis itself (C = B^T X, base = B C); from about 400 tokens on
+                        token axes use the basis itself (C = B^T X, base = B C); from 256 tokens on
                         and for cut-offs up to N/2 the banded factors of the resampled transform, whose
                         cost does not grow with r * N */
   FC_PATH_FFT = 2    /* fast cosine transform on the vector ALUs: N a multiple of 1024 (up to

@@ -972,7 +972,8 @@ static int grid_length(const fc_kv_desc& d, int32_t r) {
   return 0;
 }
 
-bool resample_supported(const fc_kv_desc& d, int32_t r) { return grid_length(d, r) != 0; }
+// (below 256 tokens the products with the basis itself are as quick and need no plan worth speaking of)
+bool resample_supported(const fc_kv_desc& d, int32_t r) { return d.n_tokens >= 256 && grid_length(d, r) != 0; }
 
 ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
   ResampleLayout lay{};
