@@ -242,7 +242,7 @@ __device__ __forceinline__ uint32_t bf16_rne(float f) {
 //   output:  A = P (head c16, rows 4*g4+i: exactly the layout the scores come out in), B = V (rows
 //            4*g4+i, dim (D/16)*c16 + t for output tile t)  ->  lane holds out[head 4*g4+i][that dim]
 template <int D, bool PAGED>
-__global__ __launch_bounds__(kDecThreads) void decode_mfma_partial_kernel(
+__global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_partial_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kc, const uint16_t* __restrict__ Vc,
     const int* __restrict__ budgets, const long long* __restrict__ layer_offsets, int L, int H, int G,
     long long rows_per_seq, float scale_log2e, int splits, float* __restrict__ partial, PagedSrc pg) {
@@ -252,6 +252,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_mfma_partial_kernel(
   constexpr int VW = VT / 2;            // dwords of a V row per lane
   constexpr int NW = kDecThreads / 64;
   constexpr int GP = 16;                // query heads per tile
+  constexpr int kStepRows = 16 * kTilesPerStep;
   __shared__ float sm_m[NW][GP], sm_l[NW][GP];
   __shared__ float sm_o[NW][GP][D];
   const int split = blockIdx.x, unit = blockIdx.y;
@@ -261,8 +262,9 @@ __global__ __launch_bounds__(kDecThreads) void decode_mfma_partial_kernel(
   float* rec = partial + ((size_t)unit * splits + split) * partial_floats(G, D);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c16 = lane & 15, g4 = lane >> 4;
   const bool bad = k < 0 || (!PAGED && (off < 0 || off + k > rows_per_seq));
-  const int chunk = bad ? 0 : (k + splits - 1) / splits;
-  const int r0 = min(k, split * chunk), r1 = bad ? 0 : min(k, r0 + chunk);
+  // the unit's steps of 32 rows, shared out evenly over the waves of its workgroups
+  const int steps = bad ? 0 : (k + kStepRows - 1) / kStepRows, share = splits * NW, w_id = split * NW + wave;
+  const int s0 = (int)((int64_t)steps * w_id / share), s1 = (int)((int64_t)steps * (w_id + 1) / share);
 
   // B operand of the score product: query head c16 (zeros beyond G), dims (D/4)*g4 ..
   uint32_t qw[KW];
@@ -285,46 +287,63 @@ __global__ __launch_bounds__(kDecThreads) void decode_mfma_partial_kernel(
   const long long packed_base = PAGED ? 0 : (long long)b * rows_per_seq + off;
   const uint16_t* kbase = Kc + (D / 4) * g4;
   const uint16_t* vbase = Vc + VT * c16;
-  constexpr int kStepRows = 16 * kTilesPerStep;
-  // loads of one step: K rows rb+16*tt+c16, V rows rb+16*tt+4*g4+i (clamped to the chunk; masked later)
-  uint32_t kw[kTilesPerStep][KW], vw[kTilesPerStep][4][VW], kwn[kTilesPerStep][KW], vwn[kTilesPerStep][4][VW];
-  // vok: bit 4*tt+i set if row rb+16*tt+4*g4+i of the step has a page (always, in the packed layout)
-  unsigned vok = ~0u, vokn = ~0u;
-  auto load_step = [&](int rb, uint32_t (&kd)[kTilesPerStep][KW], uint32_t (&vd)[kTilesPerStep][4][VW],
-                       unsigned& okbits) {
-    okbits = 0u;
+  // Loads of one step: K rows 16*tt+c16, V rows 16*tt+4*g4+i of it (clamped to the unit's last row; masked later).
+  // vok: bit 4*tt+i set if V row i of tile tt has a page (always, in the packed layout).  In the paged layout
+  // lane r looks up row r % 32 of the step, one step before the step's rows are requested, and the others take the
+  // result from it: one lookup per lane and step, and no load waits for the block table.
+  struct Rows {
+    uint32_t kw[kTilesPerStep][KW], vw[kTilesPerStep][4][VW];
+    unsigned vok;
+  };
+  constexpr uint32_t kNoRow = 0xFFFFFFFFu;
+  auto lookup = [&](int st) -> uint32_t {
+    bool ok;
+    const long long ci = cache_row<true>(pg, 0, unit, min(st * kStepRows + (lane & (kStepRows - 1)), k - 1), ok);
+    return ok ? (uint32_t)ci : kNoRow;
+  };
+  auto load_step = [&](int st, uint32_t where, Rows& x) {
+    x.vok = PAGED ? 0u : ~0u;
 #pragma unroll
     for (int tt = 0; tt < kTilesPerStep; ++tt) {
-      const int kr = min(rb + 16 * tt + c16, r1 - 1);
-      bool kok;
-      const uint16_t* kp = kbase + (size_t)cache_row<PAGED>(pg, packed_base, unit, kr, kok) * D;
+      long long kr, vr[4];
+      if constexpr (PAGED) {
+        const uint32_t c = (uint32_t)__shfl((int)where, 16 * tt + c16, 64);
+        kr = c == kNoRow ? 0u : c;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t v = (uint32_t)__shfl((int)where, 16 * tt + 4 * g4 + i, 64);
+          x.vok |= (v != kNoRow ? 1u : 0u) << (4 * tt + i);
+          vr[i] = v == kNoRow ? 0u : v;
+        }
+      } else {
+        kr = packed_base + min(st * kStepRows + 16 * tt + c16, k - 1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) vr[i] = packed_base + min(st * kStepRows + 16 * tt + 4 * g4 + i, k - 1);
+      }
+      const uint16_t* kp = kbase + kr * D;
 #pragma unroll
       for (int i = 0; i < KW / 4; ++i) {
         const uint4 u = *reinterpret_cast<const uint4*>(kp + 8 * i);
-        kd[tt][4 * i] = u.x; kd[tt][4 * i + 1] = u.y; kd[tt][4 * i + 2] = u.z; kd[tt][4 * i + 3] = u.w;
+        x.kw[tt][4 * i] = u.x; x.kw[tt][4 * i + 1] = u.y; x.kw[tt][4 * i + 2] = u.z; x.kw[tt][4 * i + 3] = u.w;
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int vr = min(rb + 16 * tt + 4 * g4 + i, r1 - 1);
-        bool ok;
-        const uint16_t* vp = vbase + (size_t)cache_row<PAGED>(pg, packed_base, unit, vr, ok) * D;
-        okbits |= (ok ? 1u : 0u) << (4 * tt + i);
+        const uint16_t* vp = vbase + vr[i] * D;
         if constexpr (VW == 4) {
           const uint4 u = *reinterpret_cast<const uint4*>(vp);
-          vd[tt][i][0] = u.x; vd[tt][i][1] = u.y; vd[tt][i][2] = u.z; vd[tt][i][3] = u.w;
+          x.vw[tt][i][0] = u.x; x.vw[tt][i][1] = u.y; x.vw[tt][i][2] = u.z; x.vw[tt][i][3] = u.w;
         } else {
           const uint2 u = *reinterpret_cast<const uint2*>(vp);
-          vd[tt][i][0] = u.x; vd[tt][i][1] = u.y;
+          x.vw[tt][i][0] = u.x; x.vw[tt][i][1] = u.y;
         }
       }
     }
   };
-  const int rb0 = r0 + wave * kStepRows;
-  if (rb0 < r1) load_step(rb0, kw, vw, vok);
-  for (int rb = rb0; rb < r1; rb += NW * kStepRows) {
-    // the next step's rows travel while this step is computed
-    const int rbn = rb + NW * kStepRows;
-    if (rbn < r1) load_step(rbn, kwn, vwn, vokn);
+  auto work = [&](int st, const Rows& x) {
+    const auto& kw = x.kw;
+    const auto& vw = x.vw;
+    const unsigned vok = x.vok;
+    const int rb = st * kStepRows;
     // scores of the step, in log2 units
     float sc[kTilesPerStep][4];
     float mx = -INFINITY;
@@ -337,7 +356,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_mfma_partial_kernel(
                                                         as_short4(qw[2 * s], qw[2 * s + 1]), acc, 0, 0, 0);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const bool valid = rb + 16 * tt + 4 * g4 + i < r1 && ((vok >> (4 * tt + i)) & 1u);
+        const bool valid = rb + 16 * tt + 4 * g4 + i < k && ((vok >> (4 * tt + i)) & 1u);
         sc[tt][i] = valid ? acc[i] * scale_log2e : -INFINITY;
         mx = fmaxf(mx, sc[tt][i]);
       }
@@ -386,16 +405,27 @@ __global__ __launch_bounds__(kDecThreads) void decode_mfma_partial_kernel(
         out[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(plo[tt], vb, out[t], 0, 0, 0);
       }
     }
-#pragma unroll
-    for (int tt = 0; tt < kTilesPerStep; ++tt) {
-#pragma unroll
-      for (int i = 0; i < KW; ++i) kw[tt][i] = kwn[tt][i];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < VW; ++j) vw[tt][i][j] = vwn[tt][i][j];
+  };
+  // two steps of rows under way; a step's registers are filled again in place
+  Rows xa, xb;
+  uint32_t where = 0;
+  if (s0 < s1) {
+    if (PAGED) where = lookup(s0);
+    load_step(s0, where, xa);
+    if (s0 + 1 < s1) {
+      if (PAGED) where = lookup(s0 + 1);
+      load_step(s0 + 1, where, xb);
+      if (PAGED && s0 + 2 < s1) where = lookup(s0 + 2);
     }
-    vok = vokn;
+  }
+  auto turn = [&](int st, Rows& x) {
+    work(st, x);
+    if (st + 2 < s1) load_step(st + 2, where, x);
+    if (PAGED && st + 3 < s1) where = lookup(st + 3);
+  };
+  for (int st = s0; st < s1; st += 2) {
+    turn(st, xa);
+    if (st + 1 < s1) turn(st + 1, xb);
   }
 
   // the 4 lanes of a head add their sums; then the waves merge through LDS in a fixed order
@@ -426,35 +456,69 @@ __global__ __launch_bounds__(kDecThreads) void decode_mfma_partial_kernel(
 
 // out[unit][g][:] = sum_s o_s w_s / sum_s l_s w_s with w_s = exp2(m_s - max m); zeros if no rows.
 // grid = (G, units), one thread per feature.
+template <int kAtOnce>
 __global__ void decode_merge_kernel(const float* __restrict__ partial, int G, int d, int splits,
                                     float* __restrict__ out) {
   const int g = blockIdx.x, unit = blockIdx.y, dim = threadIdx.x;
   const size_t stride = partial_floats(G, d);
   const float* base = partial + (size_t)unit * splits * stride;
-  float M = -INFINITY;
-  for (int s = 0; s < splits; ++s) M = fmaxf(M, base[(size_t)s * stride + g]);
-  float acc = 0.f, lt = 0.f;
-  if (M > -INFINITY) {
-    for (int s = 0; s < splits; ++s) {
-      const float* rec = base + (size_t)s * stride;
-      const float w = exp2f(rec[g] - M);
-      acc = fmaf(rec[2 * G + (size_t)g * d + dim], w, acc);
-      lt = fmaf(rec[G + g], w, lt);
+  // kAtOnce records at a time: their loads are under way together (one by one each waits for memory; 112 units of
+  // 9 records: 7.2 -> 4.8 us)
+  float M = -INFINITY, acc = 0.f, lt = 0.f;
+  for (int s0 = 0; s0 < splits; s0 += kAtOnce) {
+    float m[kAtOnce], l[kAtOnce], o[kAtOnce];
+#pragma unroll
+    for (int k = 0; k < kAtOnce; ++k) {
+      const float* rec = base + (size_t)min(s0 + k, splits - 1) * stride;
+      m[k] = s0 + k < splits ? rec[g] : -INFINITY;
+      l[k] = rec[G + g];
+      o[k] = rec[2 * G + (size_t)g * d + dim];
+    }
+    float top = M;
+#pragma unroll
+    for (int k = 0; k < kAtOnce; ++k) top = fmaxf(top, m[k]);
+    if (top == -INFINITY) continue;
+    const float before = exp2f(M - top);
+    acc *= before;
+    lt *= before;
+    M = top;
+#pragma unroll
+    for (int k = 0; k < kAtOnce; ++k) {
+      const float w = exp2f(m[k] - top);
+      acc = fmaf(o[k], w, acc);
+      lt = fmaf(l[k], w, lt);
     }
   }
   out[((size_t)unit * G + g) * d + dim] = lt > 0.f ? acc / lt : 0.f;
 }
 
+// Workgroups per unit.  A compute unit holds two, so the launch fills whole rounds of 512: two rounds for few
+// units, four for many (their budgets differ, and shorter pieces even that out).
 int pick_splits(int units) {
-  int s = (1024 + units - 1) / units;
-  return s < 1 ? 1 : (s > 32 ? 32 : s);
+  const int s = (units > 256 ? 2048 : 1024) / units;
+  return s < 1 ? 1 : (s > 64 ? 64 : s);
+}
+
+hipError_t launch_merge(const float* ws, int G, int d, int splits, int units, float* out, hipStream_t s) {
+  ProfileScope ps("decode_merge_kernel", s);
+  auto kern = splits <= 2 ? decode_merge_kernel<2> : (splits <= 4 ? decode_merge_kernel<4> : decode_merge_kernel<8>);
+  hipLaunchKernelGGL(kern, dim3(G, units), dim3(d), 0, s, ws, G, d, splits, out);
+  return hipGetLastError();
+}
+
+// The pieces a launch really makes: none shorter than 128 rows (a step for each wave) where the mean budget, or in
+// the paged layout the table's reach, says so.
+int cut_splits(int splits, int L, int H, int64_t rows_per_seq, const PagedSrc& pg) {
+  const int64_t rows = pg.table ? (int64_t)pg.max_pages * pg.page_size : rows_per_seq / ((int64_t)L * H);
+  const int64_t most = (rows + 127) / 128;
+  return most < 1 ? 1 : (most < splits ? (int)most : splits);
 }
 
 template <typename T, int G, int LPR>
 hipError_t decode_t(const void* Q, const void* Kc, const void* Vc, int B, int L, int H, const int32_t* budgets,
                     const int64_t* offs, int64_t rows_per_seq, float scale, float* out, float* ws,
                     const PagedSrc& pg, hipStream_t s) {
-  const int units = B * L * H, splits = pick_splits(units), d = LPR * 8;
+  const int units = B * L * H, splits = cut_splits(pick_splits(units), L, H, rows_per_seq, pg), d = LPR * 8;
   {
     ProfileScope ps("decode_partial_kernel", s);
     auto launch = [&](auto kern) {
@@ -468,16 +532,14 @@ hipError_t decode_t(const void* Q, const void* Kc, const void* Vc, int B, int L,
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  ProfileScope ps("decode_merge_kernel", s);
-  hipLaunchKernelGGL(decode_merge_kernel, dim3(G, units), dim3(d), 0, s, ws, G, d, splits, out);
-  return hipGetLastError();
+  return launch_merge(ws, G, d, splits, units, out, s);
 }
 
 template <int D>
 hipError_t decode_mfma_t(const void* Q, const void* Kc, const void* Vc, int B, int L, int H, int G,
                          const int32_t* budgets, const int64_t* offs, int64_t rows_per_seq, float scale,
                          float* out, float* ws, const PagedSrc& pg, hipStream_t s) {
-  const int units = B * L * H, splits = pick_splits(units);
+  const int units = B * L * H, splits = cut_splits(pick_splits(units), L, H, rows_per_seq, pg);
   {
     ProfileScope ps("decode_mfma_partial_kernel", s);
     auto launch = [&](auto kern) {
@@ -491,9 +553,7 @@ hipError_t decode_mfma_t(const void* Q, const void* Kc, const void* Vc, int B, i
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  ProfileScope ps("decode_merge_kernel", s);
-  hipLaunchKernelGGL(decode_merge_kernel, dim3(G, units), dim3(D), 0, s, ws, G, D, splits, out);
-  return hipGetLastError();
+  return launch_merge(ws, G, D, splits, units, out, s);
 }
 
 }  // namespace
