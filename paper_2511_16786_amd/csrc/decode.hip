@@ -16,6 +16,7 @@
 //    in fp32), probabilities in fp32, then P V with P split into two bf16 terms (hi + lo, 16
 //    significant bits) so that the weighted sum keeps fp32-grade accuracy.
 //  * fp32 caches: vector ALUs, d/8 lanes per row, one online-softmax state per lane group.
+#include <algorithm>
 #include <mutex>
 
 #include "fc_common.h"
@@ -493,10 +494,13 @@ __global__ void decode_merge_kernel(const float* __restrict__ partial, int G, in
 }
 
 // Workgroups per unit.  A compute unit holds two, so the launch fills whole rounds of 512: two rounds for few
-// units, four for many (their budgets differ, and shorter pieces even that out).
-int pick_splits(int units) {
-  const int s = (units > 256 ? 2048 : 1024) / units;
-  return s < 1 ? 1 : (s > 64 ? 64 : s);
+// units, four for many (their budgets differ, and shorter pieces even that out).  Where that many records would not
+// fit the static array, one round of 1024 shared out among the units, which bounds what the array has to hold; the
+// rule is the same for both kinds of scratch, so that their results agree to the bit.
+int pick_splits(int units, int group, int d) {
+  const int fine = std::min(64, (units > 256 ? 2048 : 1024) / units);
+  if (fine >= 1 && (size_t)units * fine * partial_floats(group, d) * sizeof(float) <= kStaticScratchBytes) return fine;
+  return std::max(1, std::min(32, (1024 + units - 1) / units));
 }
 
 hipError_t launch_merge(const float* ws, int G, int d, int splits, int units, float* out, hipStream_t s) {
@@ -518,7 +522,7 @@ template <typename T, int G, int LPR>
 hipError_t decode_t(const void* Q, const void* Kc, const void* Vc, int B, int L, int H, const int32_t* budgets,
                     const int64_t* offs, int64_t rows_per_seq, float scale, float* out, float* ws,
                     const PagedSrc& pg, hipStream_t s) {
-  const int units = B * L * H, splits = cut_splits(pick_splits(units), L, H, rows_per_seq, pg), d = LPR * 8;
+  const int units = B * L * H, splits = cut_splits(pick_splits(units, G, LPR * 8), L, H, rows_per_seq, pg), d = LPR * 8;
   {
     ProfileScope ps("decode_partial_kernel", s);
     auto launch = [&](auto kern) {
@@ -539,7 +543,7 @@ template <int D>
 hipError_t decode_mfma_t(const void* Q, const void* Kc, const void* Vc, int B, int L, int H, int G,
                          const int32_t* budgets, const int64_t* offs, int64_t rows_per_seq, float scale,
                          float* out, float* ws, const PagedSrc& pg, hipStream_t s) {
-  const int units = B * L * H, splits = cut_splits(pick_splits(units), L, H, rows_per_seq, pg);
+  const int units = B * L * H, splits = cut_splits(pick_splits(units, G, D), L, H, rows_per_seq, pg);
   {
     ProfileScope ps("decode_mfma_partial_kernel", s);
     auto launch = [&](auto kern) {
@@ -590,7 +594,7 @@ hipError_t decode_static_scratch(void** ptr) {
 
 size_t decode_workspace_bytes(int B, int L, int H, int group, int d) {
   const int units = B * L * H;
-  return units == 0 ? 0 : (size_t)units * pick_splits(units) * partial_floats(group, d) * sizeof(float);
+  return units == 0 ? 0 : (size_t)units * pick_splits(units, group, d) * partial_floats(group, d) * sizeof(float);
 }
 
 hipError_t decode_launch(const void* Q, const void* Kc, const void* Vc, int B, int L, int H, int group, int d,

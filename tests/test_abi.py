@@ -123,3 +123,16 @@ def test_validation_errors_before_any_launch():
     assert lib.flashcache_score(None, None, ref(empty), 7, 1, None, None, None, 0, None) == b.FC_OK
     assert lib.flashcache_allocate(None, 0, 4, 2, 64, 40, 1, 64, None, None, None) == b.FC_OK
     assert b.status_string(b.FC_EBUDGET).startswith("FC_EBUDGET")
+
+
+def test_static_decode_scratch_holds_what_one_round_of_pieces_needs():
+    """Shapes whose records at 1024 pieces shared out among the units fit the static array are taken by the static
+    entry point, however finely other shapes are cut."""
+    from paper_2511_16786_amd import binding as b
+    lib = b._lib
+    for units in (1, 3, 31, 100, 256, 257, 300, 512, 896, 1023, 1024, 1500, 2048, 4000):
+        for group, d in ((1, 64), (7, 128), (16, 128)):
+            records = units * max(1, min(32, -(-1024 // units))) * group * (d + 2) * 4
+            need = lib.flashcache_decode_workspace_bytes(1, 1, units, units * group, d)
+            assert need > 0
+            assert (need <= lib.flashcache_decode_static_scratch_bytes()) == (records <= 16 << 20), (units, group, d)

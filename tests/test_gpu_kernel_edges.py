@@ -1,0 +1,205 @@
+"""The kernels at the sizes where their tiles, windows and size rules end, against the oracle.
+
+Scores follow the tolerance of parity_util; selection and allocation are bit-exact; decode attention
+follows |err| <= 5e-5 max|V| (fp32 exp2 and sums over up to N rows).
+"""
+import numpy as np
+import pytest
+
+import kvsynth
+from oracle import flashcache_ref as ref
+
+import parity_util as pu
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _smooth_plus_noise(rng, shape, dtype):
+    """[..., N, d]: a few low cosine modes, noise a tenth as strong, strongly deviating tokens."""
+    n, d = shape[-2:]
+    u = (np.arange(n) + 0.5) / n
+    modes = np.cos(np.pi * u[:, None] * np.arange(6))
+    x = modes @ rng.standard_normal(shape[:-2] + (6, d)) + 0.1 * rng.standard_normal(shape)
+    x[..., rng.choice(n, max(1, n // 50), replace=False), :] += 3.0 * rng.standard_normal(d)
+    x = x.astype(np.float32)
+    return kvsynth.f32_to_bf16_bits(x) if dtype == "bf16" else x
+
+
+# (tokens, kept modes, head_dim, dtype, heads).  The grid is the shortest of 2^k and 3 * 2^k points, from 64 to
+# 16384, with 1.75 r points and N/16 points: every length once, at cut-offs that just fit it or are just above the
+# shorter one, token counts one off a multiple of the 16-token tiles and 32-token steps, the fewest (256) and most
+# tokens per grid point (16), and 1, 2 and 4 waves per unit (head_dim up to 64, 128, 256)
+GRIDS = [(256, 1, 64, "f32", 2), (1024, 36, 8, "bf16", 3), (999, 54, 128, "bf16", 2), (2048, 73, 72, "f32", 1),
+         (1025, 109, 136, "bf16", 2), (257, 128, 128, "bf16", 5), (513, 146, 256, "bf16", 1), (777, 219, 64, "bf16", 2),
+         (1111, 292, 128, "f32", 1), (1533, 438, 40, "bf16", 2), (2047, 585, 128, "bf16", 9), (3001, 877, 128, "bf16", 2),
+         (3333, 1170, 16, "f32", 2), (4099, 1755, 64, "bf16", 1), (9001, 2340, 24, "bf16", 2), (7023, 3510, 8, "bf16", 2),
+         (9401, 4680, 16, "f32", 1), (14055, 7022, 8, "bf16", 1), (18749, 9362, 16, "bf16", 1),
+         (100003, 100, 8, "bf16", 1), (262144, 40, 8, "bf16", 1)]
+
+
+@pytest.mark.parametrize("n,r,d,dtype,heads", GRIDS)
+def test_scores_at_every_grid_length(n, r, d, dtype, heads):
+    import paper_2511_16786_amd as fc
+    rng = np.random.default_rng(n + r)
+    K = _smooth_plus_noise(rng, (1, 1, heads, n, d), dtype)
+    V = _smooth_plus_noise(rng, (1, 1, heads, n, d), dtype)
+    want = ref.score(K, V, dtype, r, route="fast")
+    Kt, Vt = pu.to_torch(K, dtype), pu.to_torch(V, dtype)
+    comp = fc.Compressor(Kt, r, ref.total_budget(1, n, 0.2))
+    comp.run(Kt, Vt)
+    torch.cuda.synchronize()
+    assert fc.workspace_error(comp.workspace) == 0
+    pu.check_scores(comp.scores.cpu().numpy(), want["score"], pu.unit_power(ref.widen(K, dtype), ref.widen(V, dtype)))
+    e = comp.energy.cpu().numpy()
+    assert np.allclose(e[..., 2:], want["energy"][..., 2:], rtol=1e-5)
+    assert np.all(np.abs(e[..., :2] - want["energy"][..., :2]) <= 1e-4 * want["energy"][..., :2]
+                  + 1e-7 * want["energy"][..., 2:])
+
+
+@pytest.mark.parametrize("layout", ["token_major", "padded_rows", "heads_last"])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_scores_do_not_depend_on_strides(layout, dtype):
+    """The same values behind other strides give the same bits (odd token count, batch and layers)."""
+    import paper_2511_16786_amd as fc
+    rng = np.random.default_rng(5)
+    B, L, H, n, d = 2, 2, 3, 1237, 64
+    dense = [pu.to_torch(_smooth_plus_noise(rng, (B, L, H, n, d), dtype), dtype) for _ in range(2)]
+
+    def lay(x):
+        if layout == "token_major":
+            return x.permute(0, 1, 3, 2, 4).contiguous().permute(0, 1, 3, 2, 4)
+        if layout == "padded_rows":
+            wide = torch.zeros((B, L, H, n + 3, d + 8), dtype=x.dtype, device=x.device)
+            wide[:, :, :, :n, :d] = x
+            return wide[:, :, :, :n, :d]
+        return x.permute(2, 1, 0, 3, 4).contiguous().permute(2, 1, 0, 3, 4)
+    got = []
+    for K, V in (dense, [lay(x) for x in dense]):
+        comp = fc.Compressor(K, 124, ref.total_budget(L, n, 0.2))
+        comp.run(K, V)
+        torch.cuda.synchronize()
+        got.append((comp.scores.cpu(), comp.energy.cpu(), comp.idx.cpu()))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_a_value_that_is_not_finite_spoils_its_own_unit_only(bad):
+    """Base KV of a column that holds it is not finite anywhere; other units' scores keep their bits."""
+    import paper_2511_16786_amd as fc
+    rng = np.random.default_rng(8)
+    n = 1500
+    K, V = (pu.to_torch(_smooth_plus_noise(rng, (1, 2, 4, n, 64), "bf16"), "bf16") for _ in range(2))
+    comp = fc.Compressor(K, 150, ref.total_budget(2, n, 0.2))
+    comp.run_score(K, V)
+    clean = comp.scores.clone()
+    K[0, 1, 2, 700, 5] = bad
+    comp.run_score(K, V)
+    torch.cuda.synchronize()
+    same = torch.ones((2, 4), dtype=torch.bool)
+    same[1, 2] = False
+    for l in range(2):
+        for h in range(4):
+            if same[l, h]:
+                assert torch.equal(comp.scores[0, l, h], clean[0, l, h])
+            else:
+                assert not torch.isfinite(comp.scores[0, l, h]).any()
+
+
+# one key, and both sides of every size at which the selection kernel changes
+@pytest.mark.parametrize("n", [1, 63, 1024, 1025, 4096, 4097, 8192, 8193, 16385, 32768, 32769, 65536, 65537])
+@pytest.mark.parametrize("shared", [False, True])
+def test_selection_of_uneven_key_ranges(n, shared):
+    """Scores that fill the search's bins unevenly: equal ones, two values, one far above the others, many
+    magnitudes, both signs, infinities, and a NaN of all set bits beside others."""
+    import paper_2511_16786_amd as fc
+    rng = np.random.default_rng(n)
+    L, d = 6, 8
+    s = np.empty((1, L, 1, n), np.float32)
+    s[0, 0] = 0.5
+    s[0, 1] = np.where(rng.uniform(size=n) < 0.3, np.float32(1.0), np.nextafter(np.float32(1.0), np.float32(2.0)))
+    s[0, 2] = rng.uniform(0.01, 0.02, n)
+    s[0, 2, 0, n // 2] = 3e38
+    s[0, 3] = np.exp(rng.uniform(-80, 80, n))
+    s[0, 4] = rng.standard_normal(n)
+    s[0, 4, 0, n // 3] = np.inf
+    s[0, 5] = rng.gamma(2.0, 1.0, n)
+    s[0, 5, 0, n // 4] = np.array(0xFFFFFFFF, np.uint32).view(np.float32)
+    K = rng.standard_normal((1, L, 1, n, d)).astype(np.float32)
+    Kt = torch.from_numpy(K).cuda()
+    s_t = torch.from_numpy(s).cuda()
+    bits = s.view(np.uint32)
+    key = np.where(bits >> 31, ~bits, bits | np.uint32(1 << 31))
+    if shared:                           # (the head mean's division may give the NaN another payload)
+        key[np.isnan(s)] = 0
+    for k in sorted({1, (n + 1) // 2, max(1, n - 1), n}):
+        budgets = np.full((1, L), k, np.int64)
+        offs = ref.layer_offsets(budgets[0], 1)
+        rows = int(offs[-1])
+        idx = torch.full((1, rows), -1, dtype=torch.int32, device="cuda")
+        Ko = torch.zeros((1, rows, d), device="cuda")
+        Vo = torch.zeros_like(Ko)
+        fc.select_gather(Kt, Kt, fc.describe(Kt), s_t, torch.from_numpy(budgets.astype(np.int32)).cuda(),
+                         torch.from_numpy(offs[None]).cuda(), rows, idx, Ko, Vo, shared=shared)
+        got = idx.cpu().numpy()[0]
+        for l in range(5 if shared else L):
+            order = np.lexsort((np.arange(n), -key[0, l, 0].astype(np.int64)))
+            assert np.array_equal(got[l * k:(l + 1) * k], np.sort(order[:k])), (l, k)
+
+
+@pytest.mark.parametrize("L", [63, 64, 65])
+def test_allocation_on_both_sides_of_one_wave(L):
+    import paper_2511_16786_amd as fc
+    rng = np.random.default_rng(L)
+    B, H, N = 40, 2, 300
+    energy = np.empty((B, L, H, 4))
+    energy[..., 2:] = rng.uniform(1.0, 100.0, (B, L, H, 2))
+    energy[..., :2] = energy[..., 2:] * rng.uniform(0.0, 1.0, (B, L, H, 2)) ** 4
+    energy[:, ::7, :, :2] = 0.0
+    e_t = torch.from_numpy(energy).cuda()
+    for T, lo, hi in ((L * 60, 1, N), (L * 60, 20, 90), (L * 90 - 1, 5, 90), (L, 1, N)):
+        budgets = torch.empty((B, L), dtype=torch.int32, device="cuda")
+        offs = torch.empty((B, L + 1), dtype=torch.int64, device="cuda")
+        fc.allocate(e_t, B, L, H, N, T, lo, hi, budgets, offs)
+        bg, og = budgets.cpu().numpy(), offs.cpu().numpy()
+        for b in range(B):
+            want, _ = ref.allocate(ref.layer_ratios(energy[b]), T, lo, hi)
+            assert np.array_equal(bg[b], want)
+            assert np.array_equal(og[b], ref.layer_offsets(want, H))
+
+
+# budgets on both sides of a step (32 rows a wave) and of a 128-row piece; page sizes that do and do not divide a step
+@pytest.mark.parametrize("page", [0, 1, 7, 16, 64, 200])
+@pytest.mark.parametrize("dtype,d,group", [("bf16", 128, 7), ("bf16", 64, 16), ("f32", 128, 4)])
+def test_decode_rows_that_end_inside_a_step(dtype, d, group, page):
+    import paper_2511_16786_amd as fc
+    rng = np.random.default_rng(17 * group + page)
+    B, L, H = 1, 8, 2
+    budgets = np.array([[1, 31, 32, 33, 127, 129, 640, 2049]], dtype=np.int64)
+    offs = ref.layer_offsets(budgets[0], H)
+    rows = int(offs[-1])
+
+    def make(shape, sigma=1.0):
+        x = (sigma * rng.standard_normal(shape)).astype(np.float32)
+        return kvsynth.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    Kr, Vr, Q = make((B, rows, d)), make((B, rows, d), 2.0), make((B, L, H * group, d))
+    scale = float(1.0 / np.sqrt(d))
+    b_t = torch.from_numpy(budgets.astype(np.int32)).cuda()
+    want = ref.decode_attention(Q[0], Kr[0], Vr[0], dtype, budgets[0], H, scale)
+    if page == 0:
+        out = fc.decode_attention(pu.to_torch(Q, dtype), pu.to_torch(Kr, dtype), pu.to_torch(Vr, dtype), H, b_t,
+                                  torch.from_numpy(offs[None]).cuda(), rows, scale)
+    else:
+        reach = -(-int(budgets.max()) // page)
+        pages = B * L * H * reach
+        table = rng.permutation(pages).astype(np.int32).reshape(B, L, H, reach)
+        Kc = np.zeros((pages, page, d), dtype=Kr.dtype)
+        Vc = np.zeros_like(Kc)
+        ref.scatter_paged(Kr[0], budgets[0], H, table[0], page, Kc)
+        ref.scatter_paged(Vr[0], budgets[0], H, table[0], page, Vc)
+        out = fc.decode_attention_paged(pu.to_torch(Q, dtype), pu.to_torch(Kc, dtype), pu.to_torch(Vc, dtype), H, b_t,
+                                        torch.from_numpy(table).cuda(), scale)
+    err = np.abs(out.cpu().numpy()[0] - want).max()
+    assert err <= 5e-5 * float(np.abs(ref.widen(Vr, dtype)).max())
