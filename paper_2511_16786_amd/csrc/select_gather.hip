@@ -177,8 +177,8 @@ __global__ __launch_bounds__(NT) void select_kernel(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int i0 = wave * 64 * MAXC + lane * 4;
 
-  // tokens past n get key 0, below every real key (non-negative floats have the top bit set, negative ones are
-  // >= 1 unless the score is NaN)
+  // tokens past n get key 0, which no score has but the NaN of all set bits; equal keys are kept lowest token first
+  // and k <= n, so that the surplus tokens, which come last, are never among the kept
   uint32_t key[MAXC];
   if (!SHARED && (n & 3) == 0 && (reinterpret_cast<uintptr_t>(s) & 15u) == 0) {
 #pragma unroll
@@ -205,7 +205,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
   uint32_t lo = 0xFFFFFFFFu, hi = 0u;
 #pragma unroll
   for (int j = 0; j < MAXC; ++j) {
-    lo = min(lo, key[j] - 1u);                 // (key 0 wraps to the top and does not count)
+    lo = min(lo, i0 + (j >> 2) * 256 + (j & 3) < n ? key[j] : 0xFFFFFFFFu);
     hi = max(hi, key[j]);
   }
 #pragma unroll
@@ -217,7 +217,6 @@ __global__ __launch_bounds__(NT) void select_kernel(
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) { lo = min(lo, wave_a[w]); hi = max(hi, wave_b[w]); }
-  lo += 1u;
 
   // the k-th largest key is the need-th largest of the keys in [lo, hi]; `whole`: all of [lo, hi] is kept
   unsigned need = (unsigned)k;
