@@ -45,27 +45,41 @@ union Frag {
 
 // ---------------------------------------------------------------------------- tables
 
-__device__ double bessel_i0(double x) {          // power series, all terms positive
-  const double q = 0.25 * x * x;
-  double term = 1.0, sum = 1.0;
-  for (int k = 1; k < 200; ++k) {
-    term *= q / ((double)k * (double)k);
-    sum += term;
-    if (term < sum * 1e-18) break;
+// I0 by its power series in q = x^2/4 (all terms positive); the arguments stay below 9 pi = 28.3, where the 48th
+// term is 1e-22 of the sum.
+struct I0Series {
+  double c[48];
+  constexpr I0Series() : c{} {
+    double f = 1.0;
+    for (int k = 0; k < 48; ++k) { c[k] = f; f /= (double)(k + 1) * (double)(k + 1); }
   }
+};
+__host__ __device__ __forceinline__ double bessel_i0(double q) {
+  constexpr I0Series t;
+  double sum = t.c[47];
+#pragma unroll
+  for (int k = 46; k >= 0; --k) sum = fma(sum, q, t.c[k]);
   return sum;
 }
 
-__device__ double window(double s, double beta, double inv_i0) {
-  const double z = s * (2.0 / kW);
-  const double t = 1.0 - z * z;
-  return t >= 0.0 ? bessel_i0(beta * sqrt(t)) * inv_i0 : 0.0;
+struct Window {
+  double beta, inv_i0;
+};
+Window make_window(int r, int m) {
+  const double beta = M_PI * kW * (1.0 - 0.5 * (double)r / (double)m);
+  return {beta, 1.0 / bessel_i0(0.25 * beta * beta)};
 }
 
 // weight between token position u and grid point k, images of the even extension included
-__device__ double weight_at(double u, int k, int m, double beta, double inv_i0) {
-  return window(u - k, beta, inv_i0) + window(u + 1.0 + k, beta, inv_i0) +
-         window(2.0 * m - 1.0 - k - u, beta, inv_i0);
+__device__ double weight_at(double u, int k, int m, const Window& w) {
+  double sum = 0.0;
+#pragma unroll 1
+  for (int image = 0; image < 3; ++image) {
+    const double s = image == 0 ? u - k : (image == 1 ? u + 1.0 + k : 2.0 * m - 1.0 - k - u);
+    const double z = s * (2.0 / kW), t = 1.0 - z * z;
+    if (t >= 0.0) sum += bessel_i0(0.25 * w.beta * w.beta * t) * w.inv_i0;
+  }
+  return sum;
 }
 
 // position of grid point k in the order the transform takes its input (even points ascending, then
@@ -130,50 +144,47 @@ __device__ float2 unit_root(double frac) {        // e^{-2 pi i frac}
   return make_float2((float)c, (float)-s);
 }
 
-// One thread per 8-weight fragment piece and per table entry; runs once per plan.
+// One thread per weight and per table entry; runs once per plan, and a prompt of a new length waits for it.  The
+// weights' series are the work: as fused multiply-adds with constant factors, one weight a thread and the window's
+// own constants from the host, 12 us at 7321 tokens where a thread of eight weights, each with a division per term,
+// took 52 us.
 __global__ __launch_bounds__(256) void resample_table_kernel(TablePtrs tp, int n, int r, int m, int d, int dtype,
-                                                             int steps, int tpw, int n_wfwd, int n_winv) {
+                                                             int steps, int tpw, int n_wfwd, int n_winv, Window win) {
   int id = blockIdx.x * blockDim.x + threadIdx.x;
   const double dd = (double)n / (double)m;        // tokens per grid point
   const double inv_dd = (double)m / (double)n;
-  const double beta = M_PI * kW * (1.0 - 0.5 * (double)r / (double)m);
-  const double inv_i0 = 1.0 / bessel_i0(beta);
   if (id == 0) {
     WsHeader h{};
     h.magic = kWsMagic; h.path = kPathResample; h.n = n; h.r = r; h.d = d; h.dtype = dtype;
     *tp.hdr = h;
   }
   if (id < n_wfwd) {
-    const int lane = id & 63, step = (id >> 6) % steps, tile = (id >> 6) / steps;
+    const int o = id & 511, lane = (o >> 2) & 63, e = (o >> 8) * 4 + (o & 3);
+    const int step = (id >> 9) % steps, tile = (id >> 9) / steps;
     int s0 = max(0, (int)ceil(dd * (16.0 * tile - 0.5 * kW + 0.5) - 0.5)) / 32;
     s0 = min(s0, (n + 31) / 32 - steps);
-    if (lane == 0 && step == 0) tp.s0[tile] = s0;
-    const int k = 16 * tile + (lane & 15);
+    if (o == 0 && step == 0) tp.s0[tile] = s0;
     // the last step slides back to end with the last token and takes only what earlier steps have not
-    const int i0 = min(32 * (s0 + step), n - 32) + 8 * (lane >> 4);
-    float* w = tp.wfwd + (size_t)(tile * steps + step) * 512 + lane * 4;
-    for (int e = 0; e < 8; ++e)
-      w[(e >> 2) * 256 + (e & 3)] =
-          i0 + e >= 32 * (s0 + step) ? (float)weight_at((i0 + e + 0.5) * inv_dd - 0.5, k, m, beta, inv_i0) : 0.0f;
+    const int i = min(32 * (s0 + step), n - 32) + 8 * (lane >> 4) + e;
+    tp.wfwd[id] =
+        i >= 32 * (s0 + step) ? (float)weight_at((i + 0.5) * inv_dd - 0.5, 16 * tile + (lane & 15), m, win) : 0.0f;
     return;
   }
   id -= n_wfwd;
   if (id < n_winv) {
-    const int lane = id & 63, tile = id >> 6, win = tile / tpw;
-    const double uf = (16.0 * tpw * win + 0.5) * inv_dd - 0.5;
+    const int o = id & 511, lane = o >> 3, e = o & 7, tile = id >> 9, g = lane >> 4, first = tile / tpw * tpw;
+    const double uf = (16.0 * first + 0.5) * inv_dd - 0.5;
     int k0 = (int)ceil(uf - 0.5 * kW);
     k0 = max(0, min(k0, m - 32)) & ~3;
-    if (lane == 0 && tile == win * tpw) tp.k0[win] = k0;
-    const int i = 16 * tile + (lane & 15), g = lane >> 4;
-    const double u = (i + 0.5) * inv_dd - 0.5;
-    for (int e = 0; e < 8; ++e) {
-      // the order in which the residual kernel's loads deliver the window's grid points
-      const int k = e < 4 ? k0 + 2 * (8 * (e >> 1) + 2 * g + (e & 1)) : k0 + 2 * (31 - 8 * (e >> 1) - 2 * g - (e & 1)) + 1;
-      const double w = i < n ? kInvWeightScale * weight_at(u, k, m, beta, inv_i0) : 0.0;
-      const _Float16 hi = (_Float16)(float)w;
-      tp.winv[(size_t)tile * 1024 + lane * 8 + e] = hi;
-      tp.winv[(size_t)tile * 1024 + 512 + lane * 8 + e] = (_Float16)(float)(w - (double)hi);
-    }
+    if (o == 0 && tile == first) tp.k0[tile / tpw] = k0;
+    const int i = 16 * tile + (lane & 15);
+    // the order in which the residual kernel's loads deliver the window's grid points
+    const int k = e < 4 ? k0 + 2 * (8 * (e >> 1) + 2 * g + (e & 1)) : k0 + 2 * (31 - 8 * (e >> 1) - 2 * g - (e & 1)) + 1;
+    const double w = i < n ? kInvWeightScale * weight_at((i + 0.5) * inv_dd - 0.5, k, m, win) : 0.0;
+    const _Float16 hi = (_Float16)(float)w;
+    _Float16* p = tp.winv + (size_t)tile * 1024 + o;
+    p[0] = hi;
+    p[512] = (_Float16)(float)(w - (double)hi);
     return;
   }
   id -= n_winv;
@@ -181,8 +192,8 @@ __global__ __launch_bounds__(256) void resample_table_kernel(TablePtrs tp, int n
     auto f = [&](int q) -> double {
       if (q >= r) return 0.0;
       const double a = 0.5 * M_PI * kW * q / m;
-      const double s = sqrt(beta * beta - a * a);
-      const double ph = kW * sinh(s) / s * inv_i0;
+      const double s = sqrt(win.beta * win.beta - a * a);
+      const double ph = kW * sinh(s) / s * win.inv_i0;
       return 1.0 / ((double)n * ph * ph);
     };
     const double fa = f(id), fb = f(m - id);
@@ -1029,11 +1040,12 @@ hipError_t resample_prepare(const fc_kv_desc& d, int32_t r, const ResampleLayout
                reinterpret_cast<_Float16*>(base + lay.winv), reinterpret_cast<int*>(base + lay.s0),
                reinterpret_cast<int*>(base + lay.k0), reinterpret_cast<float2*>(base + lay.filt),
                reinterpret_cast<float2*>(base + lay.twid)};
-  const int n_wfwd = lay.m / 16 * lay.steps * 64, n_winv = lay.wins * lay.tpw * 64;
+  const int n_wfwd = lay.m / 16 * lay.steps * 512, n_winv = lay.wins * lay.tpw * 512;
   const int total = n_wfwd + n_winv + lay.m + twid_size(lay.m);
   ProfileScope ps("resample_table_kernel", s);
   hipLaunchKernelGGL(resample_table_kernel, dim3((total + 255) / 256), dim3(256), 0, s, tp, d.n_tokens, r, lay.m,
-                     d.head_dim, d.dtype, lay.steps, lay.tpw, n_wfwd, n_winv);
+                     d.head_dim, d.dtype, lay.steps, lay.tpw, n_wfwd, n_winv,
+                     make_window(r, lay.m));
   return hipGetLastError();
 }
 
