@@ -153,6 +153,14 @@ __device__ __forceinline__ unsigned wave_incl_scan(unsigned v) {
   v += dpp_u32<0x143, 0xC>(v);      // row_bcast:31 into rows 2 and 3
   return v;
 }
+__device__ __forceinline__ unsigned wave_max_u32(unsigned v) {  // valid in lane 63
+  v = max(v, dpp_u32<0x111, 0xF>(v));
+  v = max(v, dpp_u32<0x112, 0xF>(v));
+  v = max(v, dpp_u32<0x114, 0xF>(v));
+  v = max(v, dpp_u32<0x118, 0xF>(v));
+  v = max(v, dpp_u32<0x142, 0xA>(v));
+  return max(v, dpp_u32<0x143, 0xC>(v));
+}
 __device__ __forceinline__ unsigned below_me(unsigned long long mask, unsigned add) {   // set bits of lower lanes
   return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, add));
 }
@@ -208,12 +216,10 @@ __global__ __launch_bounds__(NT) void select_kernel(
     lo = min(lo, i0 + (j >> 2) * 256 + (j & 3) < n ? key[j] : 0xFFFFFFFFu);
     hi = max(hi, key[j]);
   }
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    lo = min(lo, (uint32_t)__shfl_xor((int)lo, d, 64));
-    hi = max(hi, (uint32_t)__shfl_xor((int)hi, d, 64));
-  }
-  if (lane == 0) { wave_a[wave] = lo; wave_b[wave] = hi; }
+  lo = wave_max_u32(~lo);                      // (~ of the lowest)
+  hi = wave_max_u32(hi);
+  if (lane == 63) { wave_a[wave] = ~lo; wave_b[wave] = hi; }
+  lo = ~0u;
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) { lo = min(lo, wave_a[w]); hi = max(hi, wave_b[w]); }
@@ -379,10 +385,14 @@ hipError_t select_gather_launch(const void* K, const void* V, const fc_kv_desc& 
 #define FC_SELECT(SH, NT, MAXC)                                                                               \
   hipLaunchKernelGGL((select_kernel<SH, NT, MAXC>), grid, dim3(NT), 0, s, scores, budgets, offs, d.layers,     \
                      d.kv_heads, n, rows, idx_out)
-    // the fewest keys per thread that cover n; four waves while each has at most 16 (their barriers are cheaper)
+    // The fewest keys per thread that cover n, and more waves while the barriers they wait at cost less than the keys
+    // they share out (us at 16 and at 896 units): 2048 tokens, 512 threads of 4 keys 7.8 / 12.2, 256 of 16 11.2 / 15.5;
+    // 4096 tokens, 512 threads of 8 9.4 / 15.6, 1024 of 4 8.9 / 19.8; 8192 tokens, 1024 of 8 11.4 / 26.6, 512 of 16
+    // 12.1 / 25.9; 16384 tokens, 1024 of 16 15.3 / 52.6, 512 of 32 19.2 / 48.7.
 #define FC_SELECT_N(SH)                                                                                        \
   if (n <= 1024) FC_SELECT(SH, 256, 4);                                                                        \
-  else if (n <= 4096) FC_SELECT(SH, 256, 16);                                                                  \
+  else if (n <= 2048) FC_SELECT(SH, 512, 4);                                                                   \
+  else if (n <= 4096) FC_SELECT(SH, 512, 8);                                                                   \
   else if (n <= 8192) FC_SELECT(SH, 1024, 8);                                                                  \
   else if (n <= 16384) FC_SELECT(SH, 1024, 16);                                                                \
   else FC_SELECT(SH, 1024, 32)
