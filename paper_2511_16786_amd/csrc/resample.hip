@@ -224,20 +224,28 @@ struct SlotMap {
   int wpu;       // waves per unit: 1, 2 or 4
 };
 
+// 8 columns of one row, read with (KEEP) or without a claim on the last-level cache (see keep_rows).
+template <bool KEEP, typename V>
+__device__ __forceinline__ V load_piece(const void* p) {
+  if constexpr (KEEP) return *static_cast<const V*>(p);
+  return __builtin_nontemporal_load(static_cast<const V*>(p));
+}
 template <typename T>
-struct RowPiece;                                   // 8 columns of one row
+struct RowPiece;
 
 template <>
 struct RowPiece<uint16_t> {
   u32x4 v;
-  __device__ __forceinline__ void load(const uint16_t* p) { v = *reinterpret_cast<const u32x4*>(p); }
+  template <bool KEEP>
+  __device__ __forceinline__ void load(const uint16_t* p) { v = load_piece<KEEP, u32x4>(p); }
 };
 template <>
 struct RowPiece<float> {
   f32x4 a, b;
+  template <bool KEEP>
   __device__ __forceinline__ void load(const float* p) {
-    a = *reinterpret_cast<const f32x4*>(p);
-    b = *reinterpret_cast<const f32x4*>(p + 4);
+    a = load_piece<KEEP, f32x4>(p);
+    b = load_piece<KEEP, f32x4>(p + 4);
   }
 };
 
@@ -295,7 +303,7 @@ constexpr int kDecWaves = 4;          // waves of a workgroup: 4 slots' worth of
 // The tiles' weights are in LDS as fp32 and are split in three bf16 terms when a step uses them.
 // Bound by the rows' way through the fabric: 16 tiles apart, rows under the seams are read twice, so GT is
 // as large as registers allow; results do not depend on it (a tile's steps and their order are its own).
-template <typename T, int GT>
+template <typename T, int GT, bool KEEP>
 __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
     const T* __restrict__ K, const T* __restrict__ V, KvStrides st, int u0, int u1, int n, int r, int d, int dtype,
     int m, int steps, SlotMap sm, int supers_per_xcd, WsHeader* hdr, const float* __restrict__ wfwd,
@@ -325,7 +333,7 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
   auto load = [&](RowPiece<T> (&v)[8], int s) {
     const T* ps = p + min(32 * s, n - 32) * st.sn;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e].load(ps + e * st.sn);
+    for (int e = 0; e < 8; ++e) v[e].template load<KEEP>(ps + e * st.sn);
   };
 #pragma unroll
   for (int b = 0; b < kBuf; ++b)
@@ -751,7 +759,7 @@ constexpr int kResWorkgroups = 512;   // residual kernel: two for each compute u
 // workgroups walk (units, window) side by side, window fastest, so that its L2 serves what they share.
 // A lane holds slot lane & 15 throughout: columns 8 slot + j of tokens 4 (lane >> 4) + i, so that a load reads whole
 // rows, and of a window the points that its loads deliver in 64-byte pieces (see resample_table_kernel).
-template <typename T>
+template <typename T, bool KEEP>
 __global__ __launch_bounds__(256, 2) void residual_kernel(
     const T* __restrict__ K, const T* __restrict__ V, KvStrides st, int u0, int u1, int n, int r, int d, int dtype,
     int m, int tpw, int wins, SlotMap sm, bool split, WsHeader* hdr, const _Float16* __restrict__ winv,
@@ -809,10 +817,10 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     if (t + 16 <= n) {
       const T* p = s.rows + t * st.sn;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) x[i].load(p + i * st.sn);
+      for (int i = 0; i < 4; ++i) x[i].template load<KEEP>(p + i * st.sn);
     } else {                                               // rows past the end repeat the last one
 #pragma unroll
-      for (int i = 0; i < 4; ++i) x[i].load(s.rows + (int64_t)(min(t + 4 * g + i, n - 1) - 4 * g) * st.sn);
+      for (int i = 0; i < 4; ++i) x[i].template load<KEEP>(s.rows + (int64_t)(min(t + 4 * g + i, n - 1) - 4 * g) * st.sn);
     }
   };
   Frag wn[2];
@@ -968,10 +976,12 @@ hipError_t launch_filter(float2* grid, int pairs, int n, int r, int d, int dtype
 
 }  // namespace
 
-// Bytes of input rows and grid one round of the three kernels works on (see resample_layout).
-static size_t resample_chunk_bytes() {
-  return (size_t)4 << 30;
-}
+// Bytes of grid one round of the three kernels works on.  They are written, read, written and read again: below the
+// last-level cache's 256 MB, and with the rows kept out of it (keep_rows), three of the four ways stay on the chip, while smaller
+// rounds leave the launches too little to work on.  Scoring 112 units of 32768 tokens (336 MB of grid at r = 1639,
+// 1344 MB at r = 6554): one round 1184 / 2513 us, 200 MB 1106 / 2344, 140 MB 1139 / 2624, 80 MB 1319 / 3164; with
+// ordinary loads one round 1218 / 2450, and smaller ones slower.
+constexpr size_t kRoundGridBytes = (size_t)200 << 20;
 
 // Grid length for this shape and cut-off, 0 if the realisation does not apply.
 static int grid_length(const fc_kv_desc& d, int32_t r) {
@@ -1001,11 +1011,10 @@ ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
   lay.nb = d.head_dim / 8;
   const int waves = (2 * lay.nb + 15) / 16;
   lay.wpu = waves <= 2 ? waves : 4;
-  // units per round of the three kernels (bounds the memory the grid takes; measured, smaller rounds
-  // gain less from the last-level cache than their launches cost)
-  const size_t eb = d.dtype == FC_BF16 ? 2 : 4;
-  const size_t unit_bytes = 2 * (size_t)n * d.head_dim * eb + 2 * (size_t)m * d.head_dim * 4;
-  lay.chunk = (int)std::max<size_t>(1, std::min(std::max<size_t>(units, 1), resample_chunk_bytes() / unit_bytes));
+  // units per round of the three kernels, the rounds alike
+  const size_t most = std::max<size_t>(1, kRoundGridBytes / (2 * (size_t)m * d.head_dim * sizeof(float)));
+  const size_t rounds = std::max<size_t>(1, (units + most - 1) / most);
+  lay.chunk = (int)std::max<size_t>(1, (units + rounds - 1) / rounds);
   auto up = [](size_t x) { return (x + kWsAlign - 1) / kWsAlign * kWsAlign; };
   size_t off = sizeof(WsHeader);
   lay.wfwd = off; off = up(off + (size_t)(m / 16) * lay.steps * 512 * sizeof(float));
@@ -1028,7 +1037,7 @@ size_t resample_reserve(const fc_kv_desc& d) {
   const size_t m = std::min<size_t>(16384, n * 5 / 4);
   const size_t tables = 232 * n + 280 * m + (256 << 10);
   const size_t records = units * (64 * nb + 2 * n * (nb <= 8 ? 1 : (nb <= 16 ? 2 : 4)) + 64 * 4);
-  const size_t grid = std::max<size_t>(resample_chunk_bytes(), 64 * nb * m);
+  const size_t grid = std::max<size_t>(kRoundGridBytes, 64 * nb * m);
   const size_t need = tables + records + std::min<size_t>(grid, units * 64 * nb * m);
   const size_t have = units * 2 * (nb / 2) * n * sizeof(float);
   return need > have ? (need - have + kWsAlign - 1) / kWsAlign * kWsAlign : 0;
@@ -1049,11 +1058,11 @@ hipError_t resample_prepare(const fc_kv_desc& d, int32_t r, const ResampleLayout
   return hipGetLastError();
 }
 
-template <typename T, int GT>
+template <typename T, int GT, bool KEEP>
 static hipError_t launch_decimate_gt(const T* K, const T* V, KvStrides st, int u0, int u1, int n, int r,
                                      const fc_kv_desc& d, int m, const ResampleLayout& lay, SlotMap sm, WsHeader* hdr,
                                      const float* wfwd, const int* s0, float2* grid, hipStream_t s) {
-  auto kern = decimate_kernel<T, GT>;
+  auto kern = decimate_kernel<T, GT, KEEP>;
   const size_t lds = (size_t)GT * lay.steps * 2048;
   if (lds > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -1070,7 +1079,7 @@ static hipError_t launch_decimate_gt(const T* K, const T* V, KvStrides st, int u
 
 // Tiles per wave: four while two workgroups' weights fit a compute unit's LDS (N/M up to 11) and the launch
 // still has several workgroups for each of them, else two or one.  fp32 rows leave registers for two.
-template <typename T>
+template <typename T, bool KEEP>
 static hipError_t launch_decimate(const T* K, const T* V, KvStrides st, int u0, int u1, int n, int r,
                                   const fc_kv_desc& d, int m, const ResampleLayout& lay, SlotMap sm, WsHeader* hdr,
                                   const float* wfwd, const int* s0, float2* grid, hipStream_t s) {
@@ -1079,12 +1088,12 @@ static hipError_t launch_decimate(const T* K, const T* V, KvStrides st, int u0, 
     return gt * lay.steps * 2048 <= 78 * 1024 && (int64_t)(m / 16 / gt) * groups >= kMinWorkgroups;
   };
   if constexpr (sizeof(T) == 2)
-    if (fits(4)) return launch_decimate_gt<T, 4>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, s0, grid, s);
-  if (fits(2)) return launch_decimate_gt<T, 2>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, s0, grid, s);
-  return launch_decimate_gt<T, 1>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, s0, grid, s);
+    if (fits(4)) return launch_decimate_gt<T, 4, KEEP>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, s0, grid, s);
+  if (fits(2)) return launch_decimate_gt<T, 2, KEEP>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, s0, grid, s);
+  return launch_decimate_gt<T, 1, KEEP>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, s0, grid, s);
 }
 
-template <typename T>
+template <typename T, bool KEEP>
 static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, int32_t r, const ResampleLayout& lay,
                                    float* scores, double* energy, void* ws, UnitMap um, hipStream_t s) {
   char* base = static_cast<char*>(ws);
@@ -1100,7 +1109,7 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
   // and the rows neighbouring tiles share
   for (int u0 = 0; u0 < units; u0 += lay.chunk) {
     const int u1 = std::min(units, u0 + lay.chunk);
-    hipError_t e = launch_decimate<T>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr,
+    hipError_t e = launch_decimate<T, KEEP>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr,
                                       reinterpret_cast<const float*>(base + lay.wfwd),
                                       reinterpret_cast<const int*>(base + lay.s0), grid, s);
     if (e != hipSuccess) return e;
@@ -1120,7 +1129,7 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
       const bool split = lay.wpu > 1 && per_xcd * ((u1 - u0 + 3) / 4) < kResWorkgroups / 8;
       const int abreast = split ? 4 / lay.wpu : 4;
       const int64_t items = per_xcd * ((u1 - u0 + abreast - 1) / abreast);
-      hipLaunchKernelGGL(residual_kernel<T>, dim3(8 * (int)std::min<int64_t>(items, kResWorkgroups / 8)), dim3(256), 0,
+      hipLaunchKernelGGL((residual_kernel<T, KEEP>), dim3(8 * (int)std::min<int64_t>(items, kResWorkgroups / 8)), dim3(256), 0,
                          s, K, V, st, u0, u1, n, r, d.head_dim, d.dtype, m, lay.tpw, lay.wins, sm, split, hdr,
                          reinterpret_cast<const _Float16*>(base + lay.winv),
                          reinterpret_cast<const int*>(base + lay.k0), grid, scores, epart, um);
@@ -1131,13 +1140,22 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
   return energy_reduce_launch(epart, lay.wins * lay.wpu, units, energy, um, s);
 }
 
+// Whether a round's bf16 rows fit the last-level cache, to be found there on their second reading; else they are read
+// without a claim on it, which leaves it to the grid.  Scoring, kept / not kept: 246 MB of rows 168 / 182 us, 268 MB
+// 234 / 232, 470 MB 413 / 377, 738 MB 516 / 457; 34 MB 50 / 60.  (fp32 rows are read in half lines, which do not
+// survive until the other half is asked for: 604 MB 390 / 424.)
+static bool keep_rows(const fc_kv_desc& d, const ResampleLayout& lay) {
+  return (size_t)lay.chunk * 2 * d.n_tokens * d.head_dim * sizeof(uint16_t) <= (size_t)256 * 1000 * 1000;
+}
+
 hipError_t resample_score(const void* K, const void* V, const fc_kv_desc& d, int32_t r, const ResampleLayout& lay,
                           float* scores, double* energy, void* ws, UnitMap um, hipStream_t s) {
-  return d.dtype == FC_BF16
-             ? resample_score_t(static_cast<const uint16_t*>(K), static_cast<const uint16_t*>(V), d, r, lay, scores,
-                                energy, ws, um, s)
-             : resample_score_t(static_cast<const float*>(K), static_cast<const float*>(V), d, r, lay, scores, energy,
-                                ws, um, s);
+  auto run = [&](auto score, const auto* k, const auto* v) { return score(k, v, d, r, lay, scores, energy, ws, um, s); };
+  if (d.dtype == FC_BF16) {
+    const uint16_t *k = static_cast<const uint16_t*>(K), *v = static_cast<const uint16_t*>(V);
+    return keep_rows(d, lay) ? run(resample_score_t<uint16_t, true>, k, v) : run(resample_score_t<uint16_t, false>, k, v);
+  }
+  return run(resample_score_t<float, true>, static_cast<const float*>(K), static_cast<const float*>(V));
 }
 
 hipError_t resample_lowpass(const fc_kv_desc& d, const ResampleLayout& lay, void* ws, double* lowpass, hipStream_t s) {
