@@ -335,6 +335,17 @@ def main():
         # the same launch against the HBM roof: read K and V once, write one fp32 score per token
         gbs = ab["score"] / (dom_ms * 1e-3) / 1e9
         roofline["hbm"] = {"achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS}
+    elif dom in ("decimate_kernel", "residual_kernel", "grid_filter_kernel"):
+        # the resampled transform, in rounds: a pass of it reads K and V once in each of the first two kernels, and
+        # the grid (the shortest of 2^k and 3 * 2^k points that holds 1.75 r and N/16) twice in the third
+        launches = kern[dom][0] / max(1, args.profile_steps)
+        if dom == "grid_filter_kernel":
+            m = min(q << k for q in (2, 3) for k in range(5, 14) if 4 * (q << k) >= 7 * r and 16 * (q << k) >= n)
+            moved = 2 * 2.0 * units * m * d * 4
+        else:
+            moved = ab["score"]
+        roofline = {"kernel": dom, "bound": "hbm", "achieved": moved / (launches * dom_ms * 1e-3) / 1e9,
+                    "peak": HBM_PEAK_GBS, "unit": "GB/s", "launches_per_pass": launches}
     else:
         roofline = {"kernel": dom, "bound": "hbm", "achieved": ab["select_gather"] / (dom_ms * 1e-3) / 1e9,
                     "peak": HBM_PEAK_GBS, "unit": "GB/s"}

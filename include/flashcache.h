@@ -55,7 +55,8 @@ typedef enum {
                         token axes use the basis itself (C = B^T X, base = B C); from 256 tokens on
                         and for cut-offs up to N/2 the banded factors of the resampled transform, whose
                         cost does not grow with r * N */
-  FC_PATH_FFT = 2    /* fast cosine transform on the vector ALUs: N a multiple of 1024 (up to
+  FC_PATH_FFT = 2    /* fast cosine transform on the vector ALUs (cut-offs up to N/2 and 9362 modes with
+                        head_dim <= 256: the resampled transform as above): N a multiple of 1024 (up to
                         132 * 1024), or of 256 (up to 64 * 1024, head_dim a multiple of 16);
                         head_dim a multiple of 8; any cut-off 1 <= r <= N */
 } fc_path;

@@ -135,8 +135,8 @@ __global__ __launch_bounds__(kSelThreads) void select_large_kernel(
 // 2048 equal bins between the lowest and the highest key in question, counted in LDS, take a range of any width
 // to a single key in three passes, usually in two (the search ends when a bin is kept whole); bins of equal width
 // between the extremes spread the keys over many counters, where digits of the key put nearly all of them on a few.
-// Latency-bound: one workgroup per unit, a barrier per step (32768 tokens, 112 units: 35 -> 20 us; 512 tokens:
-// 22 -> 8 us against four passes of 8-bit digits, which also ran over MAXC = 32 keys whatever n was).
+// Latency-bound: one workgroup per unit, a barrier per step (32768 tokens, 112 units: 35 -> 26 us; 4096 tokens:
+// 24 -> 8.4; 512 tokens: 22 -> 4.5 against four passes of 8-bit digits, which ran over 32 keys whatever n was).
 constexpr int kSelMaxChunk = 64;
 constexpr int kSelBins = 2048;
 
