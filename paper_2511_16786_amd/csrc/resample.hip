@@ -97,6 +97,8 @@ struct TablePtrs {
 };
 
 // Passes of the grid transform: M = R0 R1 R2 R3 (a radix 1 is no pass) by M / P threads that keep P points each.
+// More points a thread mean fewer passes and exchanges, fewer points more waves: 8192 transforms of 6144 and of 12288
+// points take 258 and 530 us with 48 a thread in three passes, 269 and 807 with 24 in four.
 // Twiddle table: for every pass after the first, powers 1..7 and 8, 16, .. (below R) of w_{R NS}^j, NS the product of
 // the radices before it, j < NS, or j < threads for the last pass; then e^{i pi t / M}.
 struct GridRadices {
@@ -489,6 +491,8 @@ struct GridPlan {
   static constexpr int log2(int v) { return v <= 1 ? 0 : 1 + log2(v / 2); }
   static constexpr int kPadShift = log2(R0 < T ? R0 : T);
   static constexpr int kLds = M + (M >> kPadShift) + 1;
+  // (a pass's exchange takes a thread's butterflies to be T apart in whole groups of the transforms done before it)
+  static_assert((R2 == 1 || R0 <= T) && (R3 == 1 || R0 * R1 <= T), "groups of the grid transform");
   static_assert(R0 * R1 * R2 * R3 == M && T % (1 << kPadShift) == 0, "radices of the grid transform");
 };
 
