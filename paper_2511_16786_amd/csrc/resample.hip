@@ -13,8 +13,8 @@
 //
 // The banded products run on the matrix cores with their operands split so that fp32 accuracy is kept:
 // bf16 inputs are exact and meet weights split in three bf16 terms; grid values, scaled to a common
-// exponent per window, and weights are split in two fp16 terms each (22 bits and the rounding of the
-// second term) and the product of the two second terms, 2^-24 of the whole, is left out.
+// exponent per window and 8 columns, and weights are split in two fp16 terms each (22 bits and the rounding
+// of the second term) and the product of the two second terms, 2^-24 of the whole, is left out.
 #include <algorithm>
 
 #include "fc_common.h"
@@ -718,16 +718,10 @@ template <int CTRL>
 __device__ __forceinline__ float dpp(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
 }
-__device__ __forceinline__ float lane_of(float v, int l) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
-// Over the whole wave, in the vector and scalar pipes (a reduction by LDS permutes waits for LDS at every step).
-__device__ __forceinline__ float wave_max(float v) {
-  v = fmaxf(v, dpp<0x121>(v));
-  v = fmaxf(v, dpp<0x122>(v));
-  v = fmaxf(v, dpp<0x124>(v));
-  v = fmaxf(v, dpp<0x128>(v));
-  return fmaxf(fmaxf(lane_of(v, 0), lane_of(v, 16)), fmaxf(lane_of(v, 32), lane_of(v, 48)));
+// Over the four lanes that hold one slot.
+__device__ __forceinline__ float slot_max(float v) {
+  v = fmaxf(v, __shfl_xor(v, 16, 64));
+  return fmaxf(v, __shfl_xor(v, 32, 64));
 }
 template <int CTRL>
 __device__ __forceinline__ double dpp_add(double v) {
@@ -856,8 +850,10 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
       for (int c = 0; c < 4; ++c)
 #pragma unroll
         for (int q = 0; q < 4; ++q) mx = fmaxf(mx, fabsf(v[jp][c][q]));
-    mx = wave_max(mx);
-    // largest magnitude of the window into [2^14, 2^15); powers of two, so nothing is rounded
+    // Largest magnitude of the slot's window into [2^14, 2^15); powers of two, so nothing is rounded.  The exponent is
+    // the slot's own: columns of K and V, which one wave may hold, can lie any number of octaves apart, and with a
+    // common one the smaller tensor's values would run out of bits (2^-30 below: a thousandth of Ehp, 2^-40: all).
+    mx = slot_max(mx);
     const int eb = max(14, min((int)(__float_as_uint(mx) >> 23), 254));
     const float scale = __uint_as_float((uint32_t)(268 - eb) << 23);
     inv = ldexpf(1.0f / kInvWeightScale, eb - 141);

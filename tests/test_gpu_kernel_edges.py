@@ -58,6 +58,33 @@ def test_scores_at_every_grid_length(n, r, d, dtype, heads):
                   + 1e-7 * want["energy"][..., 2:])
 
 
+# One wave of the residual kernel holds columns of both tensors (64: all of them, 72 and 136: across the seam; 128: none)
+@pytest.mark.parametrize("d", [64, 72, 128, 136])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_energies_of_tensors_many_octaves_apart(d, dtype):
+    """K and V are scored by themselves: each energy keeps its accuracy however small its tensor is beside the other
+    (multiplied by powers of two, which round nothing)."""
+    import paper_2511_16786_amd as fc
+    rng = np.random.default_rng(d)
+    n, r = 1024, 52
+    X = _smooth_plus_noise(rng, (2, 1, 1, 1, n, d), "f32")
+    if dtype == "bf16":
+        X = ref.widen(kvsynth.f32_to_bf16_bits(X), "bf16").astype(np.float32)
+
+    def stored(x):
+        return kvsynth.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    for k in (12, 24, 30, 34, 40, 50):
+        for small in (0, 1):
+            K, V = (stored(x * np.float32(2.0 ** -k if t == small else 1.0)) for t, x in enumerate(X))
+            want = ref.score(K, V, dtype, r, route="fast")["energy"]
+            Kt, Vt = pu.to_torch(K, dtype), pu.to_torch(V, dtype)
+            comp = fc.Compressor(Kt, r, ref.total_budget(1, n, 0.2))
+            comp.run_score(Kt, Vt)
+            e = comp.energy.cpu().numpy()
+            assert np.all(np.abs(e[..., :2] - want[..., :2]) <= 1e-4 * want[..., :2] + 1e-7 * want[..., 2:]), (k, small)
+            assert np.allclose(e[..., 2:], want[..., 2:], rtol=1e-5), (k, small)
+
+
 @pytest.mark.parametrize("layout", ["token_major", "padded_rows", "heads_last"])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_scores_do_not_depend_on_strides(layout, dtype):
