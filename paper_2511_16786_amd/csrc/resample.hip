@@ -12,9 +12,10 @@
 // same operator serves every N, since the token positions enter through the window weights alone.
 //
 // The banded products run on the matrix cores with their operands split so that fp32 accuracy is kept:
-// bf16 inputs are exact and meet weights split in three bf16 terms; grid values, scaled to a common
-// exponent per window and 8 columns, and weights are split in two fp16 terms each (22 bits and the rounding
-// of the second term) and the product of the two second terms, 2^-24 of the whole, is left out.
+// bf16 inputs are exact and meet weights split in three bf16 terms; on the way back weights are three fp16
+// terms (more than fp32 holds) and grid values, scaled to a common exponent per window and 8 columns, two
+// (23 bits: they come out of a transform in fp32), and only products below 2^-33 of the whole are left out.
+// Sums over columns and tokens are in 64 bits from 32 squares on.
 #include <algorithm>
 
 #include "fc_common.h"
@@ -89,7 +90,7 @@ __device__ __forceinline__ int grid_pos(int k, int m) { return (k & 1) ? m - 1 -
 struct TablePtrs {
   WsHeader* hdr;
   float* wfwd;       // [M/16][steps][2][64][4]
-  _Float16* winv;    // [tokens/16][2][64][8] fp16
+  _Float16* winv;    // [tokens/16][3][64][8] fp16
   int* s0;           // [M/16] first 32-token step of a grid tile
   int* k0;           // [windows] first grid point of a window
   float2* filt;      // [M] (f[m] + f[M-m]) / 2, (f[m] - f[M-m]) / 2
@@ -183,10 +184,13 @@ __global__ __launch_bounds__(256) void resample_table_kernel(TablePtrs tp, int n
     // the order in which the residual kernel's loads deliver the window's grid points
     const int k = e < 4 ? k0 + 2 * (8 * (e >> 1) + 2 * g + (e & 1)) : k0 + 2 * (31 - 8 * (e >> 1) - 2 * g - (e & 1)) + 1;
     const double w = i < n ? kInvWeightScale * weight_at((i + 0.5) * inv_dd - 0.5, k, m, win) : 0.0;
-    const _Float16 hi = (_Float16)(float)w;
-    _Float16* p = tp.winv + (size_t)tile * 1024 + o;
-    p[0] = hi;
-    p[512] = (_Float16)(float)(w - (double)hi);
+    _Float16* p = tp.winv + (size_t)tile * 1536 + o;
+    double rest = w;
+    for (int q = 0; q < 3; ++q) {
+      const _Float16 t = (_Float16)(float)rest;
+      p[512 * q] = t;
+      rest -= (double)t;
+    }
     return;
   }
   id -= n_winv;
@@ -738,15 +742,13 @@ __device__ __forceinline__ double wave_sum(double v) {
                           __builtin_amdgcn_readlane(__double2loint(v), l));
   return s;
 }
-// Sums of v[0..3] over the 16 lanes of a row; a lane returns the sum of v[lane & 3].
-__device__ __forceinline__ float row_sums(const float (&v)[4], int lane) {
+// Sums of v[0..3] over the 16 lanes of a row, from four lanes' sums on in 64 bits; a lane returns the sum of v[lane & 3].
+__device__ __forceinline__ double row_sums(const float (&v)[4], int lane) {
   const bool b0 = lane & 1, b1 = lane & 2;
   const float s01 = (b0 ? v[1] : v[0]) + dpp<0xB1>(b0 ? v[0] : v[1]);      // quad_perm 1,0,3,2
   const float s23 = (b0 ? v[3] : v[2]) + dpp<0xB1>(b0 ? v[2] : v[3]);
-  float s = (b1 ? s23 : s01) + dpp<0x4E>(b1 ? s01 : s23);                  // quad_perm 2,3,0,1
-  s += dpp<0x124>(s);                                                      // row_ror:4
-  s += dpp<0x128>(s);                                                      // row_ror:8
-  return s;
+  const float s = (b1 ? s23 : s01) + dpp<0x4E>(b1 ? s01 : s23);            // quad_perm 2,3,0,1
+  return dpp_add<0x128>(dpp_add<0x124>((double)s));                        // row_ror:4, row_ror:8
 }
 
 constexpr int kResWorkgroups = 512;   // residual kernel: two for each compute unit, all resident
@@ -767,7 +769,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     const int* __restrict__ k0s, const float2* __restrict__ grid, float* __restrict__ scores,
     double* __restrict__ epart, UnitMap um) {
   constexpr int kBuf = sizeof(T) == 2 ? 2 : 1;             // tiles of rows under way
-  __shared__ float part_sum[4][16 * kMaxTilesPerWin];
+  __shared__ double part_sum[4][16 * kMaxTilesPerWin];
   if (ws_mismatch(hdr, kPathResample, n, r, d, dtype)) return;
   const int lane = threadIdx.x & 63, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -805,6 +807,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     if (pt == parts) { pt = 0; it += peers; }
     return it < items ? segment(it, pt) : s;
   };
+  const double inv_d = 1.0 / (double)d;
   f32x4 v[4][4];
   auto load_window = [&](const Seg& s) {
 #pragma unroll
@@ -824,11 +827,11 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
       for (int i = 0; i < 4; ++i) x[i].template load<KEEP>(s.rows + (int64_t)(min(t + 4 * g + i, n - 1) - 4 * g) * st.sn);
     }
   };
-  Frag wn[2];
+  Frag wn[3];
   auto load_weights = [&](const Seg& s, int tl) {
-    const u32x4* p = reinterpret_cast<const u32x4*>(winv) + (size_t)(s.win * tpw + min(tl, tpw - 1)) * 128 + lane;
-    wn[0].u = p[0];
-    wn[1].u = p[64];
+    const u32x4* p = reinterpret_cast<const u32x4*>(winv) + (size_t)(s.win * tpw + min(tl, tpw - 1)) * 192 + lane;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) wn[q].u = p[64 * q];
   };
 
   Seg cur = segment(item, part), nxt = following(cur);
@@ -840,7 +843,8 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
   int tl = 0;
   bool more = true;
   Frag bh[8], bl[8];
-  float inv = 0.f, hp = 0.f, tot = 0.f;
+  float inv = 0.f;
+  double hp = 0.0, tot = 0.0;
 
   auto take_window = [&]() {
     float mx = 0.f;
@@ -871,15 +875,15 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     // (the operands are made here, before their sources' registers are loaded again)
 #pragma unroll
     for (int j = 0; j < 8; ++j) asm volatile("" : "+v"(bh[j].u), "+v"(bl[j].u));
-    hp = tot = 0.f;
+    hp = tot = 0.0;
     load_window(nxt);
   };
   // energies of the segment: Ehp_k, Ehp_v, Etot_k, Etot_v
   auto record = [&]() {
     const int mine = cur.part * 16 + (lane & 15);
     const bool use = mine < 2 * sm.nb, second = mine >= sm.nb;
-    double ev[4] = {use && !second ? (double)hp : 0.0, use && second ? (double)hp : 0.0,
-                    use && !second ? (double)tot : 0.0, use && second ? (double)tot : 0.0};
+    double ev[4] = {use && !second ? hp : 0.0, use && second ? hp : 0.0, use && !second ? tot : 0.0,
+                    use && second ? tot : 0.0};
     double* e = epart + (((size_t)cur.unit * wins + cur.win) * sm.wpu + cur.part) * 4;
 #pragma unroll
     for (int k = 0; k < 4; ++k) ev[k] = wave_sum(ev[k]);
@@ -887,20 +891,21 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
   };
   auto step = [&](RowPiece<T> (&xb)[4]) {
     if (tl == 0) take_window();
-    const Frag wh = wn[0], wl = wn[1];
     f32x4 acc[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      acc[j] = mfma_f16(wh, bl[j], f32x4{0.f, 0.f, 0.f, 0.f});
-      acc[j] = mfma_f16(wl, bh[j], acc[j]);
-      acc[j] = mfma_f16(wh, bh[j], acc[j]);
+      acc[j] = mfma_f16(wn[1], bl[j], f32x4{0.f, 0.f, 0.f, 0.f});
+      acc[j] = mfma_f16(wn[2], bh[j], acc[j]);
+      acc[j] = mfma_f16(wn[0], bl[j], acc[j]);
+      acc[j] = mfma_f16(wn[1], bh[j], acc[j]);
+      acc[j] = mfma_f16(wn[0], bh[j], acc[j]);
     }
     const bool last = tl + 1 == cur.tiles;
     if (!last) load_weights(cur, tl + 1);
     else load_weights(nxt, 0);
     const int t0 = (cur.win * tpw + tl) * 16;
     const bool slot_used = cur.part * 16 + (lane & 15) < 2 * sm.nb;
-    float h[4];
+    float h[4], t_sum = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       float h1 = 0.f, t1 = 0.f;
@@ -908,15 +913,16 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
       // tokens past the end, tiles past the window's own (they are the next window's) and slots past the last
       const uint32_t use = slot_used && t0 + 4 * g + i < n && tl < tpw ? ~0u : 0u;
       h[i] = __uint_as_float(__float_as_uint(h1) & use);
-      hp += h[i];
-      tot += __uint_as_float(__float_as_uint(t1) & use);
+      t_sum += __uint_as_float(__float_as_uint(t1) & use);
     }
-    float sum = row_sums(h, lane);
+    hp += (double)((h[0] + h[1]) + (h[2] + h[3]));
+    tot += (double)t_sum;
+    double sum = row_sums(h, lane);
     if ((lane & 15) < 4) {
       const int k = 4 * g + (lane & 3), token = t0 + k;
       if (part > 0) sum += part_sum[wave][16 * tl + k];
       if (split || part + 1 < parts) part_sum[wave][16 * tl + k] = sum;
-      else if (token < n && tl < tpw) scores[(size_t)out_unit(um, cur.unit) * n + token] = sum / (float)d;
+      else if (token < n && tl < tpw) scores[(size_t)out_unit(um, cur.unit) * n + token] = (float)(sum * inv_d);
     }
     if (tl + kBuf < cur.tiles) load_rows(xb, cur, tl + kBuf);
     else load_rows(xb, nxt, tl + kBuf - cur.tiles);
@@ -929,9 +935,9 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
         if (my_part == 0)
           for (int k = lane; k < 16 * cur.tiles; k += 64) {
             const int token = cur.win * tpw * 16 + k;
-            float s = part_sum[wave][k];
+            double s = part_sum[wave][k];
             for (int p = 1; p < sm.wpu; ++p) s += part_sum[wave + p][k];
-            if (token < n && k < 16 * tpw) scores[(size_t)out_unit(um, cur.unit) * n + token] = s / (float)d;
+            if (token < n && k < 16 * tpw) scores[(size_t)out_unit(um, cur.unit) * n + token] = (float)(s * inv_d);
           }
         __syncthreads();
       }
@@ -1021,7 +1027,7 @@ ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
   auto up = [](size_t x) { return (x + kWsAlign - 1) / kWsAlign * kWsAlign; };
   size_t off = sizeof(WsHeader);
   lay.wfwd = off; off = up(off + (size_t)(m / 16) * lay.steps * 512 * sizeof(float));
-  lay.winv = off; off = up(off + (size_t)lay.wins * lay.tpw * 1024 * 2);
+  lay.winv = off; off = up(off + (size_t)lay.wins * lay.tpw * 1536 * 2);
   lay.s0 = off; off = up(off + (size_t)(m / 16) * 4);
   lay.k0 = off; off = up(off + (size_t)lay.wins * 4);
   lay.filt = off; off = up(off + (size_t)m * sizeof(float2));
@@ -1038,7 +1044,7 @@ ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
 size_t resample_reserve(const fc_kv_desc& d) {
   const size_t n = d.n_tokens, nb = d.head_dim / 8, units = (size_t)d.batch * d.layers * d.kv_heads;
   const size_t m = std::min<size_t>(16384, n * 5 / 4);
-  const size_t tables = 232 * n + 280 * m + (256 << 10);
+  const size_t tables = 296 * n + 288 * m + (256 << 10);
   const size_t records = units * (64 * nb + 2 * n * (nb <= 8 ? 1 : (nb <= 16 ? 2 : 4)) + 64 * 4);
   const size_t grid = std::max<size_t>(kRoundGridBytes, 64 * nb * m);
   const size_t need = tables + records + std::min<size_t>(grid, units * 64 * nb * m);

@@ -85,6 +85,46 @@ def test_energies_of_tensors_many_octaves_apart(d, dtype):
             assert np.allclose(e[..., 2:], want[..., 2:], rtol=1e-5), (k, small)
 
 
+def _residual64(X, r):
+    """K or V [.., N, d] on the GPU without its r lowest modes, in 64 bits from the basis itself."""
+    n, d = X.shape[-2:]
+    x = X.double().reshape(-1, n, d)
+    i = torch.arange(n, device="cuda", dtype=torch.float64) + 0.5
+    base = torch.zeros_like(x)
+    for a in range(0, r, 1024):
+        m = torch.arange(a, min(r, a + 1024), device="cuda", dtype=torch.float64)
+        basis = torch.cos(np.pi / n * m[:, None] * i) * np.sqrt(2.0 / n)
+        if a == 0:
+            basis[0] *= np.sqrt(0.5)
+        for u in range(x.shape[0]):
+            base[u] += basis.t().contiguous() @ (basis @ x[u])
+    return (x - base).reshape(X.shape)
+
+
+# 1, 2 and 4 waves per unit, with waves that take the parts of a unit in turn and side by side
+@pytest.mark.parametrize("n,r,d,units", [(1000, 50, 64, 8), (4096, 205, 128, 8), (4096, 64, 256, 8), (512, 20, 128, 900)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_sums_of_noise_are_as_good_as_64_bits(n, r, d, units, dtype):
+    """White columns leave the sums themselves as the error.  Energies: up to 32 squares are added in fp32 and the rest
+    in fp64, at most 32 * 2^-24 and by chance 1e-7 / sqrt(n d / 32) < 1e-8; scores: one rounding to fp32, 2.5e-8 in
+    the mean, beside sums over 8 columns and 4 lanes of 1.9e-8 (d = 64: 4 of its 8 slots at once, 2.7e-8)."""
+    import paper_2511_16786_amd as fc
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n + d)
+    K, V = (torch.randn((1, 1, units, n, d), generator=gen, device="cuda").to(
+        torch.bfloat16 if dtype == "bf16" else torch.float32) for _ in range(2))
+    comp = fc.Compressor(K, r, ref.total_budget(1, n, 0.2))
+    comp.run_score(K, V)
+    hp = [_residual64(X, r) for X in (K, V)]
+    want = torch.stack([x.pow(2).sum((-1, -2)) for x in (hp[0], hp[1], K.double(), V.double())], -1)
+    off = (comp.energy / want - 1.0).abs().amax((0, 1, 2)).tolist()
+    assert max(off[:2]) <= 4e-9
+    # (bf16 squares of Etot go through a dot product that truncates its sums: 2^-24 low at most, half of it in the mean)
+    assert max(off[2:]) <= (2.0 ** -25 if dtype == "bf16" else 4e-9)
+    s = (hp[0].pow(2).sum(-1) + hp[1].pow(2).sum(-1)) / d
+    assert float((comp.scores.double() - s).norm() / s.norm()) <= (4.0e-8 if d == 64 else 3.6e-8)
+
+
 @pytest.mark.parametrize("layout", ["token_major", "padded_rows", "heads_last"])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_scores_do_not_depend_on_strides(layout, dtype):
