@@ -17,6 +17,7 @@
 // (23 bits: they come out of a transform in fp32), and only products below 2^-33 of the whole are left out.
 // Sums over columns and tokens are in 64 bits from 32 squares on.
 #include <algorithm>
+#include <type_traits>
 
 #include "fc_common.h"
 
@@ -94,7 +95,7 @@ struct TablePtrs {
   int* s0;           // [M/16] first 32-token step of a grid tile
   int* k0;           // [windows] first grid point of a window
   float2* filt;      // [M] (f[m] + f[M-m]) / 2, (f[m] - f[M-m]) / 2
-  float2* twid;      // see GridFft
+  void* twid;        // see GridFft: float2, or double2 for a wide transform
 };
 
 // Passes of the grid transform: M = R0 R1 R2 R3 (a radix 1 is no pass) by M / P threads that keep P points each.
@@ -102,10 +103,18 @@ struct TablePtrs {
 // points take 258 and 530 us with 48 a thread in three passes, 269 and 807 with 24 in four.
 // Twiddle table: for every pass after the first, powers 1..7 and 8, 16, .. (below R) of w_{R NS}^j, NS the product of
 // the radices before it, j < NS, or j < threads for the last pass; then e^{i pi t / M}.
+// A wide transform (see wide_transform) has twice the registers per point under work, so that three lengths whose
+// last pass would not fit them take four passes: 1606 instead of 3074 us at 12288 points, 637 / 1134 at 6144 and
+// 294 / 366 at 3072 (14336 columns pairs; spilled registers in the longer times).
 struct GridRadices {
   int p, r[4];
 };
-__host__ __device__ constexpr GridRadices grid_radices(int m) {
+__host__ __device__ constexpr GridRadices grid_radices(int m, bool wide) {
+  if (wide) switch (m) {
+    case 3072: return {24, {8, 8, 8, 6}};
+    case 6144: return {24, {8, 8, 8, 12}};
+    case 12288: return {48, {8, 8, 16, 12}};
+  }
   switch (m) {
     case 64: return {8, {8, 8, 1, 1}};
     case 96: return {24, {8, 12, 1, 1}};
@@ -126,11 +135,11 @@ __host__ __device__ constexpr GridRadices grid_radices(int m) {
     default: return {32, {32, 32, 16, 1}};         // 16384
   }
 }
-__host__ __device__ constexpr int grid_threads(int m) { return m / grid_radices(m).p; }
+__host__ __device__ constexpr int grid_threads(int m, bool wide) { return m / grid_radices(m, wide).p; }
 __host__ __device__ constexpr int twid_powers(int r) { return (r < 8 ? r : 8) - 1 + (r - 1) / 8; }
 // first entry of the factors of pass k (k = 1, 2, 3), and of the phases for the first k that is no pass
-__host__ __device__ constexpr int twid_off(int m, int k) {
-  const GridRadices g = grid_radices(m);
+__host__ __device__ constexpr int twid_off(int m, bool wide, int k) {
+  const GridRadices g = grid_radices(m, wide);
   int off = 0, ns = g.r[0];
   for (int i = 1; i < k && i < 4 && ns < m; ++i) {
     off += twid_powers(g.r[i]) * (ns * g.r[i] == m ? m / g.p : ns);
@@ -138,13 +147,13 @@ __host__ __device__ constexpr int twid_off(int m, int k) {
   }
   return off;
 }
-__host__ __device__ constexpr int twid_phase_off(int m) { return twid_off(m, 4); }
-__host__ __device__ constexpr int twid_size(int m) { return twid_phase_off(m) + grid_threads(m); }
+__host__ __device__ constexpr int twid_phase_off(int m, bool wide) { return twid_off(m, wide, 4); }
+__host__ __device__ constexpr int twid_size(int m, bool wide) { return twid_phase_off(m, wide) + grid_threads(m, wide); }
 
-__device__ float2 unit_root(double frac) {        // e^{-2 pi i frac}
+__device__ double2 unit_root(double frac) {       // e^{-2 pi i frac}
   double s, c;
   sincospi(2.0 * frac, &s, &c);
-  return make_float2((float)c, (float)-s);
+  return make_double2(c, -s);
 }
 
 // One thread per weight and per table entry; runs once per plan, and a prompt of a new length waits for it.  The
@@ -152,7 +161,7 @@ __device__ float2 unit_root(double frac) {        // e^{-2 pi i frac}
 // own constants from the host, 12 us at 7321 tokens where a thread of eight weights, each with a division per term,
 // took 52 us.
 __global__ __launch_bounds__(256) void resample_table_kernel(TablePtrs tp, int n, int r, int m, int d, int dtype,
-                                                             int steps, int tpw, int n_wfwd, int n_winv, Window win) {
+                                                             int steps, int tpw, int n_wfwd, int n_winv, bool wide, Window win) {
   int id = blockIdx.x * blockDim.x + threadIdx.x;
   const double dd = (double)n / (double)m;        // tokens per grid point
   const double inv_dd = (double)m / (double)n;
@@ -207,19 +216,20 @@ __global__ __launch_bounds__(256) void resample_table_kernel(TablePtrs tp, int n
     return;
   }
   id -= m;
-  if (id >= twid_size(m)) return;
-  float2 v;
-  if (id >= twid_phase_off(m)) {
-    v = unit_root(-0.5 * (double)(id - twid_phase_off(m)) / (double)m);
+  if (id >= twid_size(m, wide)) return;
+  double2 v;
+  if (id >= twid_phase_off(m, wide)) {
+    v = unit_root(-0.5 * (double)(id - twid_phase_off(m, wide)) / (double)m);
   } else {
-    const GridRadices gr = grid_radices(m);
+    const GridRadices gr = grid_radices(m, wide);
     int k = 1, ns = gr.r[0];
-    while (id >= twid_off(m, k + 1)) ns *= gr.r[k++];
-    const int stride = ns * gr.r[k] == m ? grid_threads(m) : ns, j = id - twid_off(m, k), slot = j / stride;
+    while (id >= twid_off(m, wide, k + 1)) ns *= gr.r[k++];
+    const int stride = ns * gr.r[k] == m ? grid_threads(m, wide) : ns, j = id - twid_off(m, wide, k), slot = j / stride;
     const int low = (gr.r[k] < 8 ? gr.r[k] : 8) - 1, power = slot < low ? slot + 1 : 8 * (slot - low + 1);
     v = unit_root((double)(power * (j % stride)) / (double)(ns * gr.r[k]));
   }
-  tp.twid[id] = v;
+  if (wide) static_cast<double2*>(tp.twid)[id] = v;
+  else static_cast<float2*>(tp.twid)[id] = make_float2((float)v.x, (float)v.y);
 }
 
 // ---------------------------------------------------------------------------- decimation
@@ -402,51 +412,64 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
 
 // ---------------------------------------------------------------------------- filter on the grid
 
-__device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
-__device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
-__device__ __forceinline__ float2 cmul(float2 a, float2 w) {
-  return make_float2(fmaf(a.x, w.x, -a.y * w.y), fmaf(a.y, w.x, a.x * w.y));
+// Complex numbers of 32 and of 64 bits (C = float2, double2).
+template <typename C>
+__device__ __forceinline__ constexpr C cpair(decltype(C::x) re, decltype(C::x) im) { return C{re, im}; }
+__device__ __forceinline__ float mad(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double mad(double a, double b, double c) { return fma(a, b, c); }
+template <typename C>
+__device__ __forceinline__ C cadd(C a, C b) { return cpair<C>(a.x + b.x, a.y + b.y); }
+template <typename C>
+__device__ __forceinline__ C csub(C a, C b) { return cpair<C>(a.x - b.x, a.y - b.y); }
+template <typename C>
+__device__ __forceinline__ C cmul(C a, C w) {
+  return cpair<C>(mad(a.x, w.x, -a.y * w.y), mad(a.y, w.x, a.x * w.y));
 }
 
 // cos(2 pi k / 192) of the first quadrant; every constant root the transforms use is on this circle
-__device__ constexpr float kCos192[49] = {
-    1.f, 0.99946458747636568f, 0.99785892323860348f, 0.99518472667219693f, 0.99144486137381038f,
-    0.98664333208487898f, 0.98078528040323043f, 0.97387697927733363f, 0.96592582628906831f,
-    0.95694033573220882f, 0.94693012949510569f, 0.93590592675732576f, 0.92387953251128674f,
-    0.91086382492117579f, 0.89687274153268837f, 0.88192126434835505f, 0.86602540378443871f,
-    0.84920218152657889f, 0.83146961230254524f, 0.81284668459161524f, 0.79335334029123517f,
-    0.77301045336273699f, 0.75183980747897738f, 0.72986407269783571f, 0.70710678118654757f,
-    0.68359230202287125f, 0.65934581510006884f, 0.63439328416364549f, 0.60876142900872066f,
-    0.58247769686780215f, 0.5555702330196024f, 0.5280678506503681f, 0.50000000000000011f, 0.47139673682599759f,
-    0.44228869021900125f, 0.41270702980439472f, 0.38268343236508984f, 0.3522500479212336f, 0.3214394653031617f,
-    0.2902846772544625f, 0.25881904510252074f, 0.22707626303437345f, 0.19509032201612833f, 0.16289547339458882f,
-    0.13052619222005171f, 0.098017140329560548f, 0.06540312923014327f, 0.032719082821776165f, 0.f};
-__device__ constexpr float cos192(int k) {
+__device__ constexpr double kCos192[49] = {
+    1.0, 0.9994645874763657, 0.9978589232386035, 0.9951847266721969, 0.9914448613738104, 0.986643332084879,
+    0.9807852804032304, 0.9738769792773336, 0.9659258262890683, 0.9569403357322088, 0.9469301294951057,
+    0.9359059267573258, 0.9238795325112867, 0.9108638249211758, 0.8968727415326884, 0.881921264348355,
+    0.8660254037844387, 0.8492021815265789, 0.8314696123025452, 0.8128466845916152, 0.7933533402912352,
+    0.773010453362737, 0.7518398074789774, 0.7298640726978357, 0.7071067811865476, 0.6835923020228712,
+    0.6593458151000688, 0.6343932841636455, 0.6087614290087207, 0.5824776968678022, 0.5555702330196024,
+    0.5280678506503681, 0.5, 0.4713967368259976, 0.44228869021900125, 0.4127070298043947, 0.38268343236508984,
+    0.3522500479212336, 0.3214394653031617, 0.2902846772544625, 0.25881904510252074, 0.22707626303437345,
+    0.19509032201612833, 0.16289547339458882, 0.1305261922200517, 0.09801714032956055, 0.06540312923014327,
+    0.032719082821776165, 0.0};
+__device__ constexpr double cos192(int k) {
   k %= 192;
   if (k > 96) k = 192 - k;
   return k <= 48 ? kCos192[k] : -kCos192[96 - k];
 }
 // e^{-2 pi i k / n}, n a divisor of 192
-__device__ __forceinline__ constexpr float2 root(int k, int n) {
-  return float2{cos192(k * (192 / n)), cos192(k * (192 / n) + 48)};
+template <typename C>
+__device__ __forceinline__ constexpr C root(int k, int n) {
+  typedef decltype(C::x) R;
+  return C{(R)cos192(k * (192 / n)), (R)cos192(k * (192 / n) + 48)};
 }
 
-__device__ __forceinline__ void dft2(float2 (&v)[2]) {
-  const float2 a = v[0], b = v[1];
+template <typename C>
+__device__ __forceinline__ void dft2(C (&v)[2]) {
+  const C a = v[0], b = v[1];
   v[0] = cadd(a, b);
   v[1] = csub(a, b);
 }
-__device__ __forceinline__ void dft3(float2 (&v)[3]) {
-  const float2 t = cadd(v[1], v[2]), d = csub(v[1], v[2]);
-  const float k = 0.86602540378443865f;
-  const float2 m = make_float2(fmaf(-0.5f, t.x, v[0].x), fmaf(-0.5f, t.y, v[0].y));
+template <typename C>
+__device__ __forceinline__ void dft3(C (&v)[3]) {
+  typedef decltype(C::x) R;
+  const C t = cadd(v[1], v[2]), d = csub(v[1], v[2]);
+  const R k = (R)0.86602540378443865, h = (R)-0.5;
+  const C m = cpair<C>(mad(h, t.x, v[0].x), mad(h, t.y, v[0].y));
   v[0] = cadd(v[0], t);
-  v[1] = make_float2(fmaf(k, d.y, m.x), fmaf(-k, d.x, m.y));
-  v[2] = make_float2(fmaf(-k, d.y, m.x), fmaf(k, d.x, m.y));
+  v[1] = cpair<C>(mad(k, d.y, m.x), mad(-k, d.x, m.y));
+  v[2] = cpair<C>(mad(-k, d.y, m.x), mad(k, d.x, m.y));
 }
-__device__ __forceinline__ void dft4(float2 (&v)[4]) {
-  const float2 s = cadd(v[0], v[2]), t = csub(v[0], v[2]), u = cadd(v[1], v[3]), w = csub(v[1], v[3]);
-  const float2 p = make_float2(t.x + w.y, t.y - w.x), q = make_float2(t.x - w.y, t.y + w.x);
+template <typename C>
+__device__ __forceinline__ void dft4(C (&v)[4]) {
+  const C s = cadd(v[0], v[2]), t = csub(v[0], v[2]), u = cadd(v[1], v[3]), w = csub(v[1], v[3]);
+  const C p = cpair<C>(t.x + w.y, t.y - w.x), q = cpair<C>(t.x - w.y, t.y + w.x);
   v[0] = cadd(s, u);
   v[1] = p;
   v[2] = csub(s, u);
@@ -457,25 +480,25 @@ __device__ __forceinline__ void dft4(float2 (&v)[4]) {
 // over the strided points, constant factors, B-point transforms.
 template <int R>
 constexpr int first_factor() { return R == 2 || R == 3 || R == 4 ? R : (R % 4 == 0 ? 4 : 2); }
-template <int R>
-__device__ __forceinline__ void dft(float2 (&v)[R]) {
+template <int R, typename C>
+__device__ __forceinline__ void dft(C (&v)[R]) {
   if constexpr (R == 2) dft2(v);
   else if constexpr (R == 3) dft3(v);
   else if constexpr (R == 4) dft4(v);
   else {
     constexpr int A = first_factor<R>(), B = R / A;
-    float2 y[A][B];
+    C y[A][B];
 #pragma unroll
     for (int b = 0; b < B; ++b) {
-      float2 u[A];
+      C u[A];
 #pragma unroll
       for (int a = 0; a < A; ++a) u[a] = v[B * a + b];
       dft<A>(u);
 #pragma unroll
       for (int a = 0; a < A; ++a) {
         if (a * b == 0) y[a][b] = u[a];
-        else if (4 * a * b == R) y[a][b] = make_float2(u[a].y, -u[a].x);
-        else y[a][b] = cmul(u[a], root(a * b, R));
+        else if (4 * a * b == R) y[a][b] = cpair<C>(u[a].y, -u[a].x);
+        else y[a][b] = cmul(u[a], root<C>(a * b, R));
       }
     }
 #pragma unroll
@@ -487,9 +510,9 @@ __device__ __forceinline__ void dft(float2 (&v)[R]) {
   }
 }
 
-template <int M>
+template <int M, bool WIDE>
 struct GridPlan {
-  static constexpr GridRadices G = grid_radices(M);
+  static constexpr GridRadices G = grid_radices(M, WIDE);
   static constexpr int P = G.p, T = M / P, R0 = G.r[0], R1 = G.r[1], R2 = G.r[2], R3 = G.r[3];
   // One slot of padding per R0 (or T, where fewer): the strided writes of a pass fall on distinct banks.
   static constexpr int log2(int v) { return v <= 1 ? 0 : 1 + log2(v / 2); }
@@ -501,17 +524,22 @@ struct GridPlan {
 };
 
 // element i + k of a table: uniform base and constant part, 32-bit part of the lane
-__device__ __forceinline__ float2 at(const float2* base, int k, uint32_t i) {
-  // (said to be global memory: a pointer that went through an asm statement has lost that)
-  typedef const __attribute__((address_space(1))) f32x2* Global;
-  const f32x2 v = *(Global)(reinterpret_cast<const char*>(base + k) + i * (uint32_t)sizeof(float2));
-  return make_float2(v.x, v.y);
+// (said to be global memory: a pointer that went through an asm statement has lost that)
+template <typename C>
+__device__ __forceinline__ C at(const C* base, int k, uint32_t i) {
+  typedef decltype(C::x) V2 __attribute__((ext_vector_type(2)));
+  typedef const __attribute__((address_space(1))) V2* Global;
+  const V2 v = *(Global)(reinterpret_cast<const char*>(base + k) + i * (uint32_t)sizeof(C));
+  return cpair<C>(v.x, v.y);
 }
 
 // Length-M complex transform of one column pair; natural order before and after, exchanges through LDS.
-template <int M>
+// Points are held in 32 bits; a wide transform takes each pass's factors and arithmetic in 64, so that its results are
+// rounded once a pass.
+template <int M, bool WIDE>
 struct GridFft {
-  using G = GridPlan<M>;
+  using G = GridPlan<M, WIDE>;
+  using C = typename std::conditional<WIDE, double2, float2>::type;
   static constexpr int P = G::P, T = G::T;
   // slot of point i; T and NS * R are multiples of 2^kPadShift, so that pad(i + T q) = pad(i) + pad(T q)
   static __device__ __forceinline__ constexpr int pad(int i) { return i + (i >> G::kPadShift); }
@@ -520,8 +548,8 @@ struct GridFft {
   template <int R, int NS>
   struct Factors {
     static constexpr int HI = (R - 1) / 8;
-    float2 lo[8], hi[HI + 1];
-    __device__ __forceinline__ void load(const float2* __restrict__ tw, int t) {
+    C lo[8], hi[HI + 1];
+    __device__ __forceinline__ void load(const C* __restrict__ tw, int t) {
       constexpr bool kLast = R * NS == M;
       constexpr int stride = kLast ? T : NS;
       const int j = kLast ? t : t & (NS - 1);
@@ -531,7 +559,7 @@ struct GridFft {
 #pragma unroll
       for (int q = 1; q <= HI; ++q) hi[q] = at(tw, ((R < 8 ? R : 8) - 1 + q - 1) * stride, j);
     }
-    __device__ __forceinline__ float2 get(int q) const {
+    __device__ __forceinline__ C get(int q) const {
       return q < 8 ? lo[q] : (q % 8 == 0 ? hi[q / 8] : cmul(lo[q % 8], hi[q / 8]));
     }
   };
@@ -540,48 +568,56 @@ struct GridFft {
   // which are this thread's own; the butterflies of a thread share the factors, in the last pass up to a constant.
   template <int R, int NS>
   static __device__ __forceinline__ void butterflies(float2 (&x)[P], const Factors<R, NS>& f) {
-    constexpr int C = P / R;
+    constexpr int N = P / R;
     constexpr bool kLast = R * NS == M;
-    if constexpr (NS > 1) {
+    // (the factors first, shared by the thread's butterflies, where the points are multiplied in place)
+    if constexpr (NS > 1 && !WIDE) {
 #pragma unroll
       for (int q = 1; q < R; ++q) {
-        const float2 w = f.get(q);
+        const C w = f.get(q);
 #pragma unroll
-        for (int c = 0; c < C; ++c) x[c + C * q] = cmul(x[c + C * q], kLast && c > 0 ? cmul(w, root(c * q, P)) : w);
+        for (int c = 0; c < N; ++c) x[c + N * q] = cmul(x[c + N * q], kLast && c > 0 ? cmul(w, root<C>(c * q, P)) : w);
         if (q % 8 == 7) __builtin_amdgcn_sched_barrier(0);
       }
     }
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-      float2 v[R];
+    for (int c = 0; c < N; ++c) {
+      C v[R];
 #pragma unroll
-      for (int q = 0; q < R; ++q) v[q] = x[c + C * q];
+      for (int q = 0; q < R; ++q) {
+        v[q] = cpair<C>(x[c + N * q].x, x[c + N * q].y);
+        if constexpr (NS > 1 && WIDE) {
+          if (q > 0) v[q] = cmul(v[q], kLast && c > 0 ? cmul(f.get(q), root<C>(c * q, P)) : f.get(q));
+          if (q % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+        }
+      }
       __builtin_amdgcn_sched_barrier(0);
       dft<R>(v);
 #pragma unroll
-      for (int q = 0; q < R; ++q) x[c + C * q] = v[q];
+      for (int q = 0; q < R; ++q) x[c + N * q] = make_float2((float)v[q].x, (float)v[q].y);
+      if (WIDE) __builtin_amdgcn_sched_barrier(0);
     }
   }
   // Results of a pass to where the next one takes them: real parts, then imaginary parts, through the same half
   // (half the LDS keeps twice the waves resident).  Point (j / NS) NS R + j % NS + q NS of butterfly j = t + T c.
   template <int R, int NS>
   static __device__ __forceinline__ void exchange(float2 (&x)[P], float* lds, int t) {
-    constexpr int C = P / R;
+    constexpr int N = P / R;
     float* o = lds + pad((t / NS) * (NS * R) + (t & (NS - 1)));
     const float* in = lds + pad(t);
     float re[P];
 #pragma unroll
-    for (int c = 0; c < C; ++c)
+    for (int c = 0; c < N; ++c)
 #pragma unroll
-      for (int q = 0; q < R; ++q) o[pad(T * c * R) + pad(q * NS)] = x[c + C * q].x;
+      for (int q = 0; q < R; ++q) o[pad(T * c * R) + pad(q * NS)] = x[c + N * q].x;
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < P; ++q) re[q] = in[pad(T * q)];
     __syncthreads();
 #pragma unroll
-    for (int c = 0; c < C; ++c)
+    for (int c = 0; c < N; ++c)
 #pragma unroll
-      for (int q = 0; q < R; ++q) o[pad(T * c * R) + pad(q * NS)] = x[c + C * q].y;
+      for (int q = 0; q < R; ++q) o[pad(T * c * R) + pad(q * NS)] = x[c + N * q].y;
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < P; ++q) x[q] = make_float2(re[q], in[pad(T * q)]);
@@ -589,7 +625,7 @@ struct GridFft {
     __builtin_amdgcn_sched_barrier(0);
   }
   // (a pass's factors are requested before the exchange that precedes it)
-  static __device__ __forceinline__ void run(float2 (&x)[P], float* lds, const float2* __restrict__ twid, int t) {
+  static __device__ __forceinline__ void run(float2 (&x)[P], float* lds, const C* __restrict__ twid, int t) {
     constexpr int N1 = G::R0, N2 = N1 * G::R1, N3 = N2 * G::R2;
     Factors<G::R0, 1> f0;
     Factors<G::R1, N1> f1;
@@ -599,13 +635,13 @@ struct GridFft {
     butterflies<G::R1, N1>(x, f1);
     if constexpr (G::R2 > 1) {
       Factors<G::R2, N2> f2;
-      f2.load(twid + twid_off(M, 2), t);
+      f2.load(twid + twid_off(M, WIDE, 2), t);
       exchange<G::R1, N1>(x, lds, t);
       butterflies<G::R2, N2>(x, f2);
     }
     if constexpr (G::R3 > 1) {
       Factors<G::R3, N3> f3;
-      f3.load(twid + twid_off(M, 3), t);
+      f3.load(twid + twid_off(M, WIDE, 3), t);
       exchange<G::R2, N2>(x, lds, t);
       butterflies<G::R3, N3>(x, f3);
     }
@@ -620,12 +656,11 @@ struct GridFft {
 // transform with real and imaginary parts exchanged.  Short lengths (few workgroups) run it in the same code, since
 // such a launch would wait for the instructions of a second copy to be fetched (768 points: 13 instead of 16 us); the
 // lengths whose points fill the registers are better off with two copies (3072 points: 180 instead of 220 us).
-template <int M>
-__global__ __launch_bounds__(GridPlan<M>::T < 64 ? 64 : GridPlan<M>::T, GridPlan<M>::P <= 16 ? 4 : (GridPlan<M>::P == 24 ? 3 : 2)) void grid_filter_kernel(
+template <int M, bool WIDE, typename G = GridPlan<M, WIDE>, typename F = GridFft<M, WIDE>>
+__global__ __launch_bounds__(G::T < 64 ? 64 : G::T, G::P <= 16 ? 4 : (G::P == 24 ? 3 : 2)) void grid_filter_kernel(
     float2* __restrict__ grid, int pairs, int n, int r, int d, int dtype, WsHeader* hdr,
-    const float2* __restrict__ filt, const float2* __restrict__ twid, double* __restrict__ elow) {
-  using G = GridPlan<M>;
-  using F = GridFft<M>;
+    const float2* __restrict__ filt, const typename F::C* __restrict__ twid, double* __restrict__ elow) {
+  using C = typename F::C;
   constexpr int P = G::P, T = G::T, PB = T < 64 ? 64 / T : 1;
   extern __shared__ float lds_all[];
   __shared__ double wsum[T < 64 ? 1 : T / 64];
@@ -637,9 +672,9 @@ __global__ __launch_bounds__(GridPlan<M>::T < 64 ? 64 : GridPlan<M>::T, GridPlan
   float2 x[P];
 #pragma unroll
   for (int q = 0; q < P; ++q) x[q] = at(g, T * q, lane_at);
-  float2 ph = at(twid, twid_phase_off(M), t);
+  C ph = at(twid, twid_phase_off(M, WIDE), t);
   if (ws_mismatch(hdr, kPathResample, n, r, d, dtype)) return;
-  float e = 0.f;
+  decltype(C::x) e = 0;
 #pragma unroll(P <= 24 ? 1 : 2)
   for (int way = 0; way < 2; ++way) {
     // (what the tables give is loaded and derived anew: kept from one way to the next it would fill the registers)
@@ -661,12 +696,13 @@ __global__ __launch_bounds__(GridPlan<M>::T < 64 ? 64 : GridPlan<M>::T, GridPlan
 #pragma unroll
     for (int q = 0; q < P; ++q) {
       if (q % 8 == 0) __builtin_amdgcn_sched_barrier(0);
-      const float2 f = at(filt, T * q, t);
-      const float2 c = root(q, 2 * P);
-      const float2 z = cmul(o[q], cmul(ph, make_float2(c.x, -c.y)));         // e^{i pi (t + T q) / M}
-      const float2 y = make_float2(fmaf(f.y, z.x, f.x * x[q].x), fmaf(f.y, z.y, f.x * x[q].y));
-      e = fmaf(x[q].x, y.x, fmaf(x[q].y, y.y, e));
-      x[q] = make_float2(y.y, y.x);
+      const float2 fq = at(filt, T * q, t);
+      const C f = cpair<C>(fq.x, fq.y);
+      const C c = root<C>(q, 2 * P), w = cpair<C>(x[q].x, x[q].y);
+      const C z = cmul(cpair<C>(o[q].x, o[q].y), cmul(ph, cpair<C>(c.x, -c.y)));   // e^{i pi (t + T q) / M}
+      const C y = cpair<C>(mad(f.y, z.x, f.x * w.x), mad(f.y, z.y, f.x * w.y));
+      e = mad(w.x, y.x, mad(w.y, y.y, e));
+      x[q] = make_float2((float)y.y, (float)y.x);
     }
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -771,6 +807,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
   constexpr int kBuf = sizeof(T) == 2 ? 2 : 1;             // tiles of rows under way
   __shared__ double part_sum[4][16 * kMaxTilesPerWin];
   if (ws_mismatch(hdr, kPathResample, n, r, d, dtype)) return;
+  const double inv_d = 1.0 / (double)d;
   const int lane = threadIdx.x & 63, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // units worked on side by side: one for each wave, or (split) as many as have a wave for every part
@@ -807,7 +844,6 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     if (pt == parts) { pt = 0; it += peers; }
     return it < items ? segment(it, pt) : s;
   };
-  const double inv_d = 1.0 / (double)d;
   f32x4 v[4][4];
   auto load_window = [&](const Seg& s) {
 #pragma unroll
@@ -965,12 +1001,12 @@ __global__ void resample_lowpass_kernel(const double* __restrict__ elow, int pai
   lowpass[ut] = s;
 }
 
-template <int M>
+template <int M, bool WIDE>
 hipError_t launch_filter(float2* grid, int pairs, int n, int r, int d, int dtype, WsHeader* hdr, const float2* filt,
-                         const float2* twid, double* elow, hipStream_t s) {
-  constexpr int T = GridPlan<M>::T, PB = T < 64 ? 64 / T : 1;
-  const size_t lds = (size_t)PB * GridPlan<M>::kLds * sizeof(float);
-  auto kern = grid_filter_kernel<M>;
+                         const void* twid, double* elow, hipStream_t s) {
+  constexpr int T = GridPlan<M, WIDE>::T, PB = T < 64 ? 64 / T : 1;
+  const size_t lds = (size_t)PB * GridPlan<M, WIDE>::kLds * sizeof(float);
+  auto kern = grid_filter_kernel<M, WIDE>;
   if (lds > 64 * 1024) {
     // raising the dynamic LDS limit is per kernel and per device, and idempotent
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -979,7 +1015,7 @@ hipError_t launch_filter(float2* grid, int pairs, int n, int r, int d, int dtype
   }
   ProfileScope ps("grid_filter_kernel", s);
   hipLaunchKernelGGL(kern, dim3((pairs + PB - 1) / PB), dim3(T < 64 ? 64 : T), lds, s, grid, pairs, n, r, d, dtype,
-                     hdr, filt, twid, elow);
+                     hdr, filt, static_cast<const typename GridFft<M, WIDE>::C*>(twid), elow);
   return hipGetLastError();
 }
 
@@ -1002,6 +1038,19 @@ static int grid_length(const fc_kv_desc& d, int32_t r) {
   return 0;
 }
 
+// Whether the grid transform is computed in 64 bits.  Rounding in 32 (the same for every column where a factor is
+// rounded) comes back from modes near the cut-off multiplied by 1 / phihat there, and counts against a residual that
+// shrinks as the cut-off rises.  Error of the scores against 64 bits (2-norm, 1e-8): streaming transform or explicit
+// basis / this realisation in 32 bits / in 64 bits:
+//   N, r, M             32768, 1639, 3072   4864, 674, 1536   3001, 991, 2048   7680, 2305, 4096   8192, 2049, 4096
+//                       5.1 / 3.7 / -       5.1 / 4.5 / -     6.9 / 11.3 / 3.9  6.4 / 11.4 / 3.9   10.8 / 8.4 / 3.2
+//   N, r, M             16384, 3277, 6144   32768, 6554, 12288   10562, 2968, 6144   32768, 9176, 16384
+//                       10.1 / 8.4 / -      11.4 / 8.2 / -       10.5 / 11.6 / 3.4   11.2 / 12.0 / 3.2
+// So it is taken where 32 bits are worse than the other realisations: above r = 3/16 N, and above N/4 for grids of
+// more than 4096 points (where those take several passes over an fp32 residual, or sums of 10000 products).  The
+// filter takes 1.2 to 1.75 times as long (14336 column pairs of 4096 points 240 / 330 us, 16384 points 795 / 950).
+static bool wide_transform(int64_t n, int64_t r, int64_t m) { return m <= 4096 ? 16 * r > 3 * n : 4 * r > n; }
+
 // (below 256 tokens the products with the basis itself are as quick and need no plan worth speaking of)
 bool resample_supported(const fc_kv_desc& d, int32_t r) { return d.n_tokens >= 256 && grid_length(d, r) != 0; }
 
@@ -1010,6 +1059,7 @@ ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
   const int64_t n = d.n_tokens, m = grid_length(d, r);
   const size_t units = (size_t)d.batch * d.layers * d.kv_heads;
   lay.m = (int)m;
+  lay.wide = wide_transform(n, r, m);
   // tokens under a tile of 16 grid points: at most (15 + W) N/M + 1, and the 32-token steps they lie in
   lay.steps = (int)std::min(((15 + kW) * n / m + 31) / 32 + 1, (n + 31) / 32);
   // tiles whose windows fit 32 grid points when the first point is rounded down to a multiple of 4
@@ -1031,7 +1081,7 @@ ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
   lay.s0 = off; off = up(off + (size_t)(m / 16) * 4);
   lay.k0 = off; off = up(off + (size_t)lay.wins * 4);
   lay.filt = off; off = up(off + (size_t)m * sizeof(float2));
-  lay.twid = off; off = up(off + (size_t)twid_size((int)m) * sizeof(float2));
+  lay.twid = off; off = up(off + (size_t)twid_size((int)m, lay.wide) * (lay.wide ? sizeof(double2) : sizeof(float2)));
   lay.elow = off; off = up(off + units * 2 * lay.nb * 4 * sizeof(double));
   lay.epart = off; off = up(off + units * lay.wins * lay.wpu * 4 * sizeof(double));
   lay.grid = off; off = up(off + (size_t)lay.chunk * 2 * lay.nb * 4 * m * sizeof(float2));
@@ -1057,12 +1107,12 @@ hipError_t resample_prepare(const fc_kv_desc& d, int32_t r, const ResampleLayout
   TablePtrs tp{reinterpret_cast<WsHeader*>(base), reinterpret_cast<float*>(base + lay.wfwd),
                reinterpret_cast<_Float16*>(base + lay.winv), reinterpret_cast<int*>(base + lay.s0),
                reinterpret_cast<int*>(base + lay.k0), reinterpret_cast<float2*>(base + lay.filt),
-               reinterpret_cast<float2*>(base + lay.twid)};
+               base + lay.twid};
   const int n_wfwd = lay.m / 16 * lay.steps * 512, n_winv = lay.wins * lay.tpw * 512;
-  const int total = n_wfwd + n_winv + lay.m + twid_size(lay.m);
+  const int total = n_wfwd + n_winv + lay.m + twid_size(lay.m, lay.wide);
   ProfileScope ps("resample_table_kernel", s);
   hipLaunchKernelGGL(resample_table_kernel, dim3((total + 255) / 256), dim3(256), 0, s, tp, d.n_tokens, r, lay.m,
-                     d.head_dim, d.dtype, lay.steps, lay.tpw, n_wfwd, n_winv,
+                     d.head_dim, d.dtype, lay.steps, lay.tpw, n_wfwd, n_winv, lay.wide,
                      make_window(r, lay.m));
   return hipGetLastError();
 }
@@ -1110,7 +1160,7 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
   const int units = d.batch * d.layers * d.kv_heads, n = d.n_tokens, m = lay.m;
   float2* grid = reinterpret_cast<float2*>(base + lay.grid);
   const float2* filt = reinterpret_cast<const float2*>(base + lay.filt);
-  const float2* twid = reinterpret_cast<const float2*>(base + lay.twid);
+  const void* twid = base + lay.twid;
   double* epart = reinterpret_cast<double*>(base + lay.epart);
   const SlotMap sm{lay.nb, lay.wpu};
   const KvStrides st = strides_of(d);
@@ -1124,10 +1174,15 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
     if (e != hipSuccess) return e;
     double* elow = reinterpret_cast<double*>(base + lay.elow) + (size_t)u0 * 2 * lay.nb * 4;
     const int pairs = (u1 - u0) * 2 * lay.nb * 4;
-#define FC_FILTER(MV) case MV: e = launch_filter<MV>(grid, pairs, n, r, d.head_dim, d.dtype, hdr, filt, twid, elow, s); break;
+    auto filter = [&](auto narrow, auto wide) {
+      return (lay.wide ? wide : narrow)(grid, pairs, n, r, d.head_dim, d.dtype, hdr, filt, twid, elow, s);
+    };
+#define FC_FILTER(MV) case MV: e = filter(launch_filter<MV, false>, launch_filter<MV, true>); break;
     switch (m) {
-      FC_FILTER(64) FC_FILTER(96) FC_FILTER(128) FC_FILTER(192) FC_FILTER(256) FC_FILTER(384) FC_FILTER(512) FC_FILTER(768) FC_FILTER(1024) FC_FILTER(1536) FC_FILTER(2048) FC_FILTER(3072) FC_FILTER(4096)
-      FC_FILTER(6144) FC_FILTER(8192) FC_FILTER(12288) FC_FILTER(16384)
+      case 64: e = launch_filter<64, false>(grid, pairs, n, r, d.head_dim, d.dtype, hdr, filt, twid, elow, s); break;
+      FC_FILTER(96) FC_FILTER(128) FC_FILTER(192) FC_FILTER(256) FC_FILTER(384) FC_FILTER(512) FC_FILTER(768)
+      FC_FILTER(1024) FC_FILTER(1536) FC_FILTER(2048) FC_FILTER(3072) FC_FILTER(4096) FC_FILTER(6144) FC_FILTER(8192)
+      FC_FILTER(12288) FC_FILTER(16384)
       default: e = hipErrorInvalidValue;
     }
 #undef FC_FILTER
