@@ -8,8 +8,9 @@
 //     b       = DCT^-1( f . DCT(g) )               grid_filter_kernel  length M, f[m] = 1 / (N phihat(m)^2), m < r
 //     base[i] = sum_k phi(u_i - k) b[k]            residual_kernel     M -> N, banded product, fused with the score
 // phihat is phi's Fourier transform; what the window lets through beyond the grid's own modes is the
-// only approximation, below 1e-8 of the signal for M >= 1.75 r and W = 9 (fp32 rounding is 1e-7).  The
-// same operator serves every N, since the token positions enter through the window weights alone.
+// only approximation.  It is largest for the mode just below the cut-off, and kept below fp32's rounding of
+// that mode, 6e-8, by the choice of W, see window_points.  The same operator serves every N, since the token
+// positions enter through the window weights alone.
 //
 // The banded products run on the matrix cores with their operands split so that fp32 accuracy is kept:
 // bf16 inputs are exact and meet weights split in three bf16 terms; on the way back weights are three fp16
@@ -25,7 +26,6 @@ namespace fc {
 
 namespace {
 
-constexpr int kW = 9;                  // grid points a token's window reaches
 constexpr int kPathResample = 3;       // header tag of a workspace prepared for this realisation
 constexpr int kMaxTilesPerWin = 16;    // 16-token tiles one wave of the residual kernel walks
 constexpr float kInvWeightScale = 4096.0f;   // fp16 weights are stored times 2^12 (their tails stay normal numbers)
@@ -47,8 +47,8 @@ union Frag {
 
 // ---------------------------------------------------------------------------- tables
 
-// I0 by its power series in q = x^2/4 (all terms positive); the arguments stay below 9 pi = 28.3, where the 48th
-// term is 1e-22 of the sum.
+// I0 by its power series in q = x^2/4 (all terms positive); the arguments stay below 10 pi 5/6 = 26.2 (9 pi = 28.3
+// for 9 points), where the 48th term is 1e-22 of the sum.
 struct I0Series {
   double c[48];
   constexpr I0Series() : c{} {
@@ -64,12 +64,24 @@ __host__ __device__ __forceinline__ double bessel_i0(double q) {
   return sum;
 }
 
+// Grid points a token's window reaches (W), by the grid points per kept mode.  Error of the projection of mode r - 1
+// in 64 bits, the largest over N / M from 1 to 11 (white columns: a tenth of it):
+//   M / r     1.75     1.87     2.0      2.25     2.5      3.0      5.0
+//   W =  9    3.5e-7   1.6e-7   1.7e-7   6e-8     2.8e-8   8.4e-9   1.0e-9
+//   W = 10    4.6e-8   2.0e-8   2.0e-8   6e-9     2.7e-9   7.6e-10
+//   W = 11    6.6e-9   2.6e-9   2.3e-9   6e-10
+// A wider window also multiplies the rounding of the grid's points by more (1 / phihat at the cut-off: 5.5, 6.6 and 8 at
+// 1.75), and what comes out for that mode on the device, 2048 tokens, r = 585, is 3.6e-7, 2.0e-7 and 2.5e-7.
+__host__ __device__ constexpr int window_points(int r, int m) { return m < 3 * (int64_t)r ? 10 : 9; }
+
 struct Window {
+  int w;
   double beta, inv_i0;
 };
 Window make_window(int r, int m) {
-  const double beta = M_PI * kW * (1.0 - 0.5 * (double)r / (double)m);
-  return {beta, 1.0 / bessel_i0(0.25 * beta * beta)};
+  const int w = window_points(r, m);
+  const double beta = M_PI * w * (1.0 - 0.5 * (double)r / (double)m);
+  return {w, beta, 1.0 / bessel_i0(0.25 * beta * beta)};
 }
 
 // weight between token position u and grid point k, images of the even extension included
@@ -78,7 +90,7 @@ __device__ double weight_at(double u, int k, int m, const Window& w) {
 #pragma unroll 1
   for (int image = 0; image < 3; ++image) {
     const double s = image == 0 ? u - k : (image == 1 ? u + 1.0 + k : 2.0 * m - 1.0 - k - u);
-    const double z = s * (2.0 / kW), t = 1.0 - z * z;
+    const double z = s * (2.0 / w.w), t = 1.0 - z * z;
     if (t >= 0.0) sum += bessel_i0(0.25 * w.beta * w.beta * t) * w.inv_i0;
   }
   return sum;
@@ -173,7 +185,7 @@ __global__ __launch_bounds__(256) void resample_table_kernel(TablePtrs tp, int n
   if (id < n_wfwd) {
     const int o = id & 511, lane = (o >> 2) & 63, e = (o >> 8) * 4 + (o & 3);
     const int step = (id >> 9) % steps, tile = (id >> 9) / steps;
-    int s0 = max(0, (int)ceil(dd * (16.0 * tile - 0.5 * kW + 0.5) - 0.5)) / 32;
+    int s0 = max(0, (int)ceil(dd * (16.0 * tile - 0.5 * win.w + 0.5) - 0.5)) / 32;
     s0 = min(s0, (n + 31) / 32 - steps);
     if (o == 0 && step == 0) tp.s0[tile] = s0;
     // the last step slides back to end with the last token and takes only what earlier steps have not
@@ -186,7 +198,7 @@ __global__ __launch_bounds__(256) void resample_table_kernel(TablePtrs tp, int n
   if (id < n_winv) {
     const int o = id & 511, lane = o >> 3, e = o & 7, tile = id >> 9, g = lane >> 4, first = tile / tpw * tpw;
     const double uf = (16.0 * first + 0.5) * inv_dd - 0.5;
-    int k0 = (int)ceil(uf - 0.5 * kW);
+    int k0 = (int)ceil(uf - 0.5 * win.w);
     k0 = max(0, min(k0, m - 32)) & ~3;
     if (o == 0 && tile == first) tp.k0[tile / tpw] = k0;
     const int i = 16 * tile + (lane & 15);
@@ -206,9 +218,9 @@ __global__ __launch_bounds__(256) void resample_table_kernel(TablePtrs tp, int n
   if (id < m) {
     auto f = [&](int q) -> double {
       if (q >= r) return 0.0;
-      const double a = 0.5 * M_PI * kW * q / m;
+      const double a = 0.5 * M_PI * win.w * q / m;
       const double s = sqrt(win.beta * win.beta - a * a);
-      const double ph = kW * sinh(s) / s * win.inv_i0;
+      const double ph = win.w * sinh(s) / s * win.inv_i0;
       return 1.0 / ((double)n * ph * ph);
     };
     const double fa = f(id), fb = f(m - id);
@@ -1033,8 +1045,9 @@ static int grid_length(const fc_kv_desc& d, int32_t r) {
   if (d.head_dim % 8 != 0 || d.head_dim > 256 || r < 1 || 2 * (int64_t)r > d.n_tokens) return 0;
   for (int m2 = 64; m2 <= 16384; m2 *= 2)
     for (int m = m2; m <= 16384 && m <= m2 + m2 / 2; m += m2 / 2)   // 2^k and 3 2^(k-1)
-      if (4 * (int64_t)m >= 7 * (int64_t)r && 16 * (int64_t)m >= d.n_tokens)   // M >= 1.75 r: the accuracy above
-        return 5 * (int64_t)d.n_tokens >= 4 * (int64_t)m ? m : 0;   // a 16-token tile and its windows fit 32 points
+      if (4 * (int64_t)m >= 7 * (int64_t)r && 16 * (int64_t)m >= d.n_tokens)   // M >= 1.75 r: see window_points
+        // a 16-token tile and its windows fit 32 points: 15 M/N + W < 29
+        return 5 * (int64_t)d.n_tokens >= 4 * (int64_t)m ? m : 0;
   return 0;
 }
 
@@ -1061,10 +1074,11 @@ ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
   lay.m = (int)m;
   lay.wide = wide_transform(n, r, m);
   // tokens under a tile of 16 grid points: at most (15 + W) N/M + 1, and the 32-token steps they lie in
-  lay.steps = (int)std::min(((15 + kW) * n / m + 31) / 32 + 1, (n + 31) / 32);
-  // tiles whose windows fit 32 grid points when the first point is rounded down to a multiple of 4
-  lay.tpw = (int)std::min<int64_t>(kMaxTilesPerWin, ((28 - kW) * n / m + 1) / 16);
-  if (lay.tpw < 1) lay.tpw = 1;
+  const int w = window_points(r, (int)m);
+  lay.steps = (int)std::min(((15 + w) * n / m + 31) / 32 + 1, (n + 31) / 32);
+  // tiles whose windows fit 32 grid points when the first point is rounded down to a multiple of 4: the positions of
+  // 16 tpw tokens span (16 tpw - 1) M/N, and together with W that has to be less than 29
+  lay.tpw = (int)std::min<int64_t>(kMaxTilesPerWin, (((29 - w) * n - 1) / m + 1) / 16);
   const int tok_tiles = (int)((n + 15) / 16);
   lay.wins = (tok_tiles + lay.tpw - 1) / lay.tpw;
   lay.nb = d.head_dim / 8;

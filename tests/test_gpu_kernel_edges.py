@@ -143,6 +143,24 @@ def test_scores_at_high_cutoffs_are_as_good_as_64_bits(n, r, dtype):
     assert float((comp.scores.double() - s).norm() / s.norm()) <= 1e-7
 
 
+@pytest.mark.parametrize("n,r", [(1024, 292), (2048, 585), (3072, 877), (7680, 2305)])
+def test_modes_just_below_the_cutoff_are_kept(n, r):
+    """Few grid points per mode (1.75): the last kept mode is what the window and the rounding of the grid's points,
+    which comes back 1 / phihat(r) = 6.6 times as large, reproduce worst: window 4.6e-8, points 6.6 * 2.5e-8, the rest
+    of the way 1e-7, together 2e-7 of the mode, by chance a third more."""
+    import paper_2511_16786_amd as fc
+    lost = []
+    for m in (r - 1, r - 2):
+        x = np.cos(np.pi * m * (np.arange(n) + 0.5) / n)
+        for scale in (1.0, 1.17, 1.34, 1.51):
+            X = torch.from_numpy(np.repeat(scale * x[:, None], 8, 1).astype(np.float32)[None, None, None]).cuda()
+            comp = fc.Compressor(X, r, ref.total_budget(1, n, 0.2))
+            comp.run_score(X, X)
+            e = comp.energy[0, 0, 0]
+            lost.append(float(e[0] / e[2]))
+    assert np.sqrt(np.mean(lost)) <= 2.7e-7
+
+
 @pytest.mark.parametrize("layout", ["token_major", "padded_rows", "heads_last"])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_scores_do_not_depend_on_strides(layout, dtype):
