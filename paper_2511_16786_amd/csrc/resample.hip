@@ -104,7 +104,7 @@ struct TablePtrs {
   WsHeader* hdr;
   float* wfwd;       // [M/16][steps][2][64][4]
   _Float16* winv;    // [tokens/16][3][64][8] fp16
-  int* s0;           // [M/16] first 32-token step of a grid tile
+  int2* s0;          // [M/16] first 32-token step of a grid tile, and the steps its windows reach into
   int* k0;           // [windows] first grid point of a window
   float2* filt;      // [M] (f[m] + f[M-m]) / 2, (f[m] - f[M-m]) / 2
   void* twid;        // see GridFft: float2, or double2 for a wide transform
@@ -187,7 +187,10 @@ __global__ __launch_bounds__(256) void resample_table_kernel(TablePtrs tp, int n
     const int step = (id >> 9) % steps, tile = (id >> 9) / steps;
     int s0 = max(0, (int)ceil(dd * (16.0 * tile - 0.5 * win.w + 0.5) - 0.5)) / 32;
     s0 = min(s0, (n + 31) / 32 - steps);
-    if (o == 0 && step == 0) tp.s0[tile] = s0;
+    if (o == 0 && step == 0) {
+      const int last = min(n - 1, (int)floor(dd * (16.0 * tile + 15.5 + 0.5 * win.w) - 0.5));
+      tp.s0[tile] = make_int2(s0, min(last / 32 + 1 - s0, steps));
+    }
     // the last step slides back to end with the last token and takes only what earlier steps have not
     const int i = min(32 * (s0 + step), n - 32) + 8 * (lane >> 4) + e;
     tp.wfwd[id] =
@@ -330,14 +333,16 @@ constexpr int kDecWaves = 4;          // waves of a workgroup: 4 slots' worth of
 // consecutive rows and swaps the halves of the words in registers (the order of the contraction is free).
 // The tiles' weights are in LDS as fp32 and are split in three bf16 terms when a step uses them.
 // Bound by the rows' way through the fabric: 16 tiles apart, rows under the seams are read twice, so GT is
-// as large as registers allow; results do not depend on it (a tile's steps and their order are its own).
+// as large as registers allow; results do not depend on it (a tile's steps and their order are its own).  A tile walks
+// the steps that its windows reach into, one fewer than the most any tile has for two tiles in three (12288 points
+// for 32768 tokens: 757 instead of 800 us for 112 units).
 // 56 units of 32768 tokens, M = 3072: 232 us, 0.94 GB of rows and 0.18 GB of grid at 4.8 TB/s (one tile a wave read
 // the rows 1.75 instead of 1.14 times).
 template <typename T, int GT, bool KEEP>
 __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
     const T* __restrict__ K, const T* __restrict__ V, KvStrides st, int u0, int u1, int n, int r, int d, int dtype,
     int m, int steps, SlotMap sm, int supers_per_xcd, WsHeader* hdr, const float* __restrict__ wfwd,
-    const int* __restrict__ s0s, float2* __restrict__ grid) {
+    const int2* __restrict__ s0s, float2* __restrict__ grid) {
   constexpr int kTerms = sizeof(T) == 2 ? 1 : 3;
   constexpr int kBuf = sizeof(T) == 2 ? 2 : 1;    // steps of rows under way (a step's registers are refilled in place)
   extern __shared__ f32x4 wlds[];                 // [GT][steps][2][64]
@@ -352,11 +357,15 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
   const int s_mine = part * 16 + (lane & 15);
   const int slot = s_mine < 2 * sm.nb ? s_mine : 0;
   const bool second = slot >= sm.nb;
-  int first[GT];                                  // a tile's first step
+  int first[GT], count[GT], s_end = 0;            // a tile's first step, and how many it has
 #pragma unroll
-  for (int q = 0; q < GT; ++q) first[q] = s0s[tile0 + min(q, n_tiles - 1)];
+  for (int q = 0; q < GT; ++q) {
+    const int2 s = s0s[tile0 + min(q, n_tiles - 1)];
+    first[q] = s.x;
+    count[q] = q < n_tiles ? s.y : 0;
+    s_end = s.x + s.y;
+  }
   if (ws_mismatch(hdr, kPathResample, n, r, d, dtype)) return;     // (waits for memory together with the above)
-  const int s_end = first[GT - 1] + steps;
   const T* p = (second ? V : K) + unit_offset(st, mine ? unit : u0) + (slot - (second ? sm.nb : 0)) * 8 +
                (int64_t)(8 * (lane >> 4)) * st.sn;
   RowPiece<T> x[kBuf][8];
@@ -384,7 +393,7 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
 #pragma unroll
     for (int q = 0; q < GT; ++q) {
       const int k = s - first[q];
-      if (k >= 0 && k < steps && q < n_tiles) {
+      if (k >= 0 && k < count[q]) {
         const f32x4* wp = wlds + (q * steps + k) * 128 + lane;
         const f32x4 wa = wp[0], wb = wp[64];
         Frag w[3];
@@ -1092,7 +1101,7 @@ ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
   size_t off = sizeof(WsHeader);
   lay.wfwd = off; off = up(off + (size_t)(m / 16) * lay.steps * 512 * sizeof(float));
   lay.winv = off; off = up(off + (size_t)lay.wins * lay.tpw * 1536 * 2);
-  lay.s0 = off; off = up(off + (size_t)(m / 16) * 4);
+  lay.s0 = off; off = up(off + (size_t)(m / 16) * 8);
   lay.k0 = off; off = up(off + (size_t)lay.wins * 4);
   lay.filt = off; off = up(off + (size_t)m * sizeof(float2));
   lay.twid = off; off = up(off + (size_t)twid_size((int)m, lay.wide) * (lay.wide ? sizeof(double2) : sizeof(float2)));
@@ -1119,7 +1128,7 @@ size_t resample_reserve(const fc_kv_desc& d) {
 hipError_t resample_prepare(const fc_kv_desc& d, int32_t r, const ResampleLayout& lay, void* ws, hipStream_t s) {
   char* base = static_cast<char*>(ws);
   TablePtrs tp{reinterpret_cast<WsHeader*>(base), reinterpret_cast<float*>(base + lay.wfwd),
-               reinterpret_cast<_Float16*>(base + lay.winv), reinterpret_cast<int*>(base + lay.s0),
+               reinterpret_cast<_Float16*>(base + lay.winv), reinterpret_cast<int2*>(base + lay.s0),
                reinterpret_cast<int*>(base + lay.k0), reinterpret_cast<float2*>(base + lay.filt),
                base + lay.twid};
   const int n_wfwd = lay.m / 16 * lay.steps * 512, n_winv = lay.wins * lay.tpw * 512;
@@ -1134,7 +1143,7 @@ hipError_t resample_prepare(const fc_kv_desc& d, int32_t r, const ResampleLayout
 template <typename T, int GT, bool KEEP>
 static hipError_t launch_decimate_gt(const T* K, const T* V, KvStrides st, int u0, int u1, int n, int r,
                                      const fc_kv_desc& d, int m, const ResampleLayout& lay, SlotMap sm, WsHeader* hdr,
-                                     const float* wfwd, const int* s0, float2* grid, hipStream_t s) {
+                                     const float* wfwd, const int2* s0, float2* grid, hipStream_t s) {
   auto kern = decimate_kernel<T, GT, KEEP>;
   const size_t lds = (size_t)GT * lay.steps * 2048;
   if (lds > 64 * 1024) {
@@ -1150,15 +1159,16 @@ static hipError_t launch_decimate_gt(const T* K, const T* V, KvStrides st, int u
   return hipGetLastError();
 }
 
-// Tiles per wave: four while two workgroups' weights fit a compute unit's LDS (N/M up to 11) and the launch
-// still has several workgroups for each of them, else two or one.  fp32 rows leave registers for two.
+// Tiles per wave: four while two workgroups' weights fit a compute unit's 160 KB of LDS (10 steps, N/M up to 11; two
+// tiles there: 519 instead of 473 us at 32768 tokens, M = 3072) and the launch still has several workgroups for each
+// of them, else two or one.  fp32 rows leave registers for two.
 template <typename T, bool KEEP>
 static hipError_t launch_decimate(const T* K, const T* V, KvStrides st, int u0, int u1, int n, int r,
                                   const fc_kv_desc& d, int m, const ResampleLayout& lay, SlotMap sm, WsHeader* hdr,
-                                  const float* wfwd, const int* s0, float2* grid, hipStream_t s) {
+                                  const float* wfwd, const int2* s0, float2* grid, hipStream_t s) {
   const int groups = ((u1 - u0) * sm.wpu + kDecWaves - 1) / kDecWaves;
   auto fits = [&](int gt) {
-    return gt * lay.steps * 2048 <= 78 * 1024 && (int64_t)(m / 16 / gt) * groups >= kMinWorkgroups;
+    return gt * lay.steps * 2048 <= 80 * 1024 && (int64_t)(m / 16 / gt) * groups >= kMinWorkgroups;
   };
   if constexpr (sizeof(T) == 2)
     if (fits(4)) return launch_decimate_gt<T, 4, KEEP>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, s0, grid, s);
@@ -1184,7 +1194,7 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
     const int u1 = std::min(units, u0 + lay.chunk);
     hipError_t e = launch_decimate<T, KEEP>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr,
                                       reinterpret_cast<const float*>(base + lay.wfwd),
-                                      reinterpret_cast<const int*>(base + lay.s0), grid, s);
+                                      reinterpret_cast<const int2*>(base + lay.s0), grid, s);
     if (e != hipSuccess) return e;
     double* elow = reinterpret_cast<double*>(base + lay.elow) + (size_t)u0 * 2 * lay.nb * 4;
     const int pairs = (u1 - u0) * 2 * lay.nb * 4;
