@@ -34,7 +34,7 @@ def algorithmic_bytes(cfg, T):
     return {"score": score, "select_gather": select + gather, "total": score + select + gather}
 
 
-def read_traffic(kernel, workload, path):
+def read_traffic(kernel, workload, realisation):
     """HBM bytes per launch of `kernel` as measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE
     (two runs of this script, scaled by the counters' reading for a plain copy of known size);
     taken from the committed summary of those runs, None if there is none for this kernel."""
@@ -47,7 +47,7 @@ def read_traffic(kernel, workload, path):
             if "=" in ln and not ln.startswith("#"):
                 k, v = ln.split("=", 1)
                 vals[k.strip()] = v.strip()
-    if vals.get("path") != path:
+    if vals.get("realisation") != realisation:
         return None
     try:
         return {"read_bytes": float(vals["read_bytes_per_launch"]),
@@ -180,7 +180,7 @@ def main():
     ap.add_argument("--steps", type=int, default=20)
     ap.add_argument("--warmup", type=int, default=3)
     ap.add_argument("--config", default="long_32k")
-    ap.add_argument("--path", default="auto", choices=["auto", "dense", "fft"])
+    ap.add_argument("--path", default="auto", choices=["auto", "dense", "fft", "basis", "stream", "resample"])
     ap.add_argument("--gamma", type=float, default=None, help="override the config's cut-off factor")
     ap.add_argument("--rho", type=float, default=None, help="override the config's retention ratio")
     ap.add_argument("--n-tokens", type=int, default=None,
@@ -250,7 +250,8 @@ def main():
     comp = fc.Compressor(Kt, r, T, path=args.path)      # includes the one-time table build (A1)
     torch.cuda.synchronize()
     t_prepare = time.time() - t0
-    path_name = {binding.FC_PATH_DENSE: "dense", binding.FC_PATH_FFT: "fft"}[comp.path]
+    path_names = {v: k for k, v in binding.PATHS.items()}
+    path_name, real_name = path_names[comp.path], path_names[fc.realisation(comp.desc, r, comp.path)]
 
     if args.copy_calibration:
         # one elementwise copy kernel that reads 1 GiB and writes 1 GiB: what FETCH_SIZE and
@@ -354,7 +355,7 @@ def main():
     # the stored traffic figures belong to the named workload as configured, not to overridden ones
     overridden = (args.gamma is not None or args.rho is not None or args.n_tokens is not None or
                   args.storage is not None or args.library is not None)
-    roofline["traffic"] = None if overridden else read_traffic(dom, args.config, path_name)
+    roofline["traffic"] = None if overridden else read_traffic(dom, args.config, real_name)
     roofline["kernels_ms"] = {k: round(v[1], 4) for k, v in kern.items()}
 
     overlap = overlap_record(torch, fc, cfg, Kt, Vt, r, comp) if args.overlap else None
@@ -431,7 +432,7 @@ def main():
         "config": {"workload": args.config, "batch": cfg.batch, "layers": cfg.layers,
                    "kv_heads": cfg.kv_heads, "n_tokens": cfg.n_tokens, "head_dim": cfg.head_dim,
                    "storage": cfg.dtype, "gamma": cfg.gamma, "rho": cfg.rho, "r": r,
-                   "total_budget": T, "path": path_name, "seed": cfg.seed,
+                   "total_budget": T, "path": path_name, "realisation": real_name, "seed": cfg.seed,
                    "launch": "direct" if graph is None else "hip_graph_replay"},
         "sequence_tokens_per_s": cfg.batch * cfg.n_tokens / (ms_per_step * 1e-3),
         "hbm_frac_whole_path": ab["total"] / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS,

@@ -48,17 +48,23 @@ typedef enum {
 
 typedef enum { FC_F32 = 0, FC_BF16 = 1 } fc_dtype;
 
-/* Realisation of the low-pass projection (all compute the same Base KV). */
+/* How the low-pass projection is realised (all compute the same Base KV).  The first three leave the choice
+ * to the library, the others name one realisation, which then is the one that runs (a cross-check of another,
+ * for instance); flashcache_realisation says which one a path stands for. */
 typedef enum {
   FC_PATH_AUTO = 0,  /* FC_PATH_FFT where it applies, else FC_PATH_DENSE */
   FC_PATH_DENSE = 1, /* products with stored bases on the matrix cores; any N, head_dim <= 256.  Short
                         token axes use the basis itself (C = B^T X, base = B C); from 256 tokens on
                         and for cut-offs up to N/2 the banded factors of the resampled transform, whose
                         cost does not grow with r * N */
-  FC_PATH_FFT = 2    /* fast cosine transform on the vector ALUs (cut-offs up to N/2 and 9362 modes with
+  FC_PATH_FFT = 2,   /* fast cosine transform on the vector ALUs (cut-offs up to N/2 and 9362 modes with
                         head_dim <= 256: the resampled transform as above): N a multiple of 1024 (up to
                         132 * 1024), or of 256 (up to 64 * 1024, head_dim a multiple of 16);
                         head_dim a multiple of 8; any cut-off 1 <= r <= N */
+  FC_PATH_BASIS = 3,   /* products with the stored basis itself: any N and r, head_dim <= 256 */
+  FC_PATH_STREAM = 4,  /* the streaming transform on the vector ALUs: shapes of FC_PATH_FFT */
+  FC_PATH_RESAMPLE = 5 /* the resampled transform: N >= 256, cut-offs up to N/2 and 9362 modes for which a grid of
+                          at most 1.25 N points serves, head_dim a multiple of 8 up to 256 */
 } fc_path;
 
 /* Layout of K and of V (one descriptor serves both): element (b,l,h,n,c) lives at
@@ -81,12 +87,16 @@ int32_t flashcache_cutoff_r(int32_t n_tokens, double gamma);
  * Eq. 12): floor(rho*L*N) clamped to [L, L*N].  Returns 0 if L < 1 or N < 1. */
 int64_t flashcache_total_budget(int32_t layers, int32_t n_tokens, double rho);
 
-/* The realisation FC_PATH_AUTO resolves to for this shape (FC_PATH_DENSE or FC_PATH_FFT),
- * or 0 if the shape is invalid or unsupported. */
+/* The path FC_PATH_AUTO resolves to for this shape (FC_PATH_DENSE or FC_PATH_FFT); any other path
+ * resolves to itself.  0 if the shape is invalid or unsupported. */
 int32_t flashcache_resolve_path(const fc_kv_desc* desc, int32_t r, int32_t path);
 
+/* The realisation that runs behind a path (FC_PATH_BASIS, FC_PATH_STREAM or FC_PATH_RESAMPLE), or 0 if
+ * the shape is invalid or unsupported. */
+int32_t flashcache_realisation(const fc_kv_desc* desc, int32_t r, int32_t path);
+
 /* Bytes of device workspace flashcache_prepare/flashcache_score need for this shape, cut-off
- * and realisation; 0 if the request is invalid or unsupported. */
+ * and path; 0 if the request is invalid or unsupported. */
 size_t flashcache_workspace_bytes(const fc_kv_desc* desc, int32_t r, int32_t path);
 
 /* Bytes of device workspace the flashcache_select_gather* entry points need.  The selection kernels
@@ -97,7 +107,7 @@ size_t flashcache_workspace_bytes(const fc_kv_desc* desc, int32_t r, int32_t pat
 size_t flashcache_select_workspace_bytes(const fc_kv_desc* desc);
 
 /* One-time table construction for (N, r, path): the explicit basis alpha[m]*phi_N(m,i) of
- * Eq. 7 for the dense realisation, or the twiddle tables of the fast transform.  Writes only
+ * Eq. 7, the twiddle tables of the streaming transform, or the window weights and factors of the resampled one.  Writes only
  * into `workspace` (device, 256-byte aligned, at least flashcache_workspace_bytes()).  The
  * same workspace, shape, r and path must then be passed to flashcache_score; a workspace that
  * was prepared for something else makes the score kernels write nothing and raise the error

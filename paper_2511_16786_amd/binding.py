@@ -19,11 +19,12 @@ _LIB_PATH = os.environ.get("FLASHCACHE_LIBRARY") or os.path.join(
 
 FC_OK, FC_EINVAL, FC_EUNSUPPORTED, FC_EWORKSPACE, FC_EBUDGET, FC_EHIP = range(6)
 FC_F32, FC_BF16 = 0, 1
-FC_PATH_AUTO, FC_PATH_DENSE, FC_PATH_FFT = 0, 1, 2
-PATHS = {"auto": FC_PATH_AUTO, "dense": FC_PATH_DENSE, "fft": FC_PATH_FFT}
+FC_PATH_AUTO, FC_PATH_DENSE, FC_PATH_FFT, FC_PATH_BASIS, FC_PATH_STREAM, FC_PATH_RESAMPLE = range(6)
+PATHS = {"auto": FC_PATH_AUTO, "dense": FC_PATH_DENSE, "fft": FC_PATH_FFT,
+         "basis": FC_PATH_BASIS, "stream": FC_PATH_STREAM, "resample": FC_PATH_RESAMPLE}
 
 EXPORTED_SYMBOLS = (
-    "flashcache_cutoff_r", "flashcache_total_budget", "flashcache_resolve_path",
+    "flashcache_cutoff_r", "flashcache_total_budget", "flashcache_resolve_path", "flashcache_realisation",
     "flashcache_workspace_bytes", "flashcache_select_workspace_bytes", "flashcache_prepare",
     "flashcache_workspace_error", "flashcache_score", "flashcache_score_layer", "flashcache_lowpass_energy",
     "flashcache_allocate",
@@ -61,6 +62,7 @@ def _load() -> ctypes.CDLL:
     lib.flashcache_cutoff_r.argtypes, lib.flashcache_cutoff_r.restype = [i32, dbl], i32
     lib.flashcache_total_budget.argtypes, lib.flashcache_total_budget.restype = [i32, i32, dbl], i64
     lib.flashcache_resolve_path.argtypes, lib.flashcache_resolve_path.restype = [c_desc_p, i32, i32], i32
+    lib.flashcache_realisation.argtypes, lib.flashcache_realisation.restype = [c_desc_p, i32, i32], i32
     lib.flashcache_workspace_bytes.argtypes, lib.flashcache_workspace_bytes.restype = [c_desc_p, i32, i32], sz
     lib.flashcache_select_workspace_bytes.argtypes = [c_desc_p]
     lib.flashcache_select_workspace_bytes.restype = sz
@@ -154,6 +156,11 @@ def total_budget(layers: int, n_tokens: int, rho: float) -> int:
 
 def resolve_path(desc: FcKvDesc, r: int, path: int = FC_PATH_AUTO) -> int:
     return int(_lib.flashcache_resolve_path(ctypes.byref(desc), r, path))
+
+
+def realisation(desc: FcKvDesc, r: int, path: int = FC_PATH_AUTO) -> int:
+    """What runs behind `path`: FC_PATH_BASIS, FC_PATH_STREAM or FC_PATH_RESAMPLE (0: unsupported)."""
+    return int(_lib.flashcache_realisation(ctypes.byref(desc), r, path))
 
 
 def workspace_bytes(desc: FcKvDesc, r: int, path: int = FC_PATH_AUTO) -> int:

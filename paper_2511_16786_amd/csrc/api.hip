@@ -28,33 +28,33 @@ fc_status check_desc(const fc_kv_desc* d) {
   return FC_OK;
 }
 
-// FC_PATH_DENSE / FC_PATH_FFT, or 0 if unsupported
+bool basis_supported(const fc_kv_desc& d) { return d.head_dim <= 256; }   // (the kernels pad rows to 64 columns)
+
+// What FC_PATH_AUTO resolves to; every other path that applies stays as it is; 0 if unsupported
 int32_t resolve(const fc_kv_desc& d, int32_t r, int32_t path) {
-  const bool dense_ok = d.head_dim <= 256;     // (rows are multiples of 16 bytes; the kernels pad to 64 columns)
-  const bool fft_ok = fft_supported(d, r);
   switch (path) {
-    case FC_PATH_AUTO: return fft_ok ? FC_PATH_FFT : (dense_ok ? FC_PATH_DENSE : 0);
-    case FC_PATH_DENSE: return dense_ok ? FC_PATH_DENSE : 0;
-    case FC_PATH_FFT: return fft_ok ? FC_PATH_FFT : 0;
+    case FC_PATH_AUTO: return fft_supported(d, r) ? FC_PATH_FFT : (basis_supported(d) ? FC_PATH_DENSE : 0);
+    case FC_PATH_DENSE: case FC_PATH_BASIS: return basis_supported(d) ? path : 0;
+    case FC_PATH_FFT: case FC_PATH_STREAM: return fft_supported(d, r) ? path : 0;
+    case FC_PATH_RESAMPLE: return resample_supported(d, r) ? path : 0;
     default: return 0;
   }
 }
 
-// What runs behind a path: the explicit basis, the streaming transform or the resampled transform.
-enum class Real { kNone, kDense, kFft, kResample };
-
-Real realisation(const fc_kv_desc& d, int32_t r, int32_t path) {
+// The realisation behind a path: FC_PATH_BASIS, FC_PATH_STREAM, FC_PATH_RESAMPLE, or 0
+int32_t realisation(const fc_kv_desc& d, int32_t r, int32_t path) {
   const int32_t p = resolve(d, r, path);
-  if (!p) return Real::kNone;
-  if (resample_supported(d, r)) return Real::kResample;
-  return p == FC_PATH_FFT ? Real::kFft : Real::kDense;
+  if (p != FC_PATH_DENSE && p != FC_PATH_FFT) return p;
+  if (resample_supported(d, r)) return FC_PATH_RESAMPLE;
+  return p == FC_PATH_FFT ? FC_PATH_STREAM : FC_PATH_BASIS;
 }
 
 size_t score_workspace(const fc_kv_desc& d, int32_t r, int32_t path) {
   if (resolve(d, r, path) == FC_PATH_FFT) return fft_layout(d, r).total + resample_reserve(d);
   switch (realisation(d, r, path)) {
-    case Real::kDense: return dense_layout(d, r).total;
-    case Real::kResample: return resample_layout(d, r).total;
+    case FC_PATH_BASIS: return dense_layout(d, r).total;
+    case FC_PATH_STREAM: return fft_layout(d, r).total;
+    case FC_PATH_RESAMPLE: return resample_layout(d, r).total;
     default: return 0;
   }
 }
@@ -87,6 +87,11 @@ int32_t flashcache_resolve_path(const fc_kv_desc* desc, int32_t r, int32_t path)
   return resolve(*desc, r, path);
 }
 
+int32_t flashcache_realisation(const fc_kv_desc* desc, int32_t r, int32_t path) {
+  if (check_desc(desc) != FC_OK || r < 1 || r > desc->n_tokens) return 0;
+  return realisation(*desc, r, path);
+}
+
 size_t flashcache_workspace_bytes(const fc_kv_desc* desc, int32_t r, int32_t path) {
   if (check_desc(desc) != FC_OK || r < 1 || r > desc->n_tokens) return 0;
   return score_workspace(*desc, r, path);
@@ -102,16 +107,16 @@ fc_status flashcache_prepare(const fc_kv_desc* desc, int32_t r, int32_t path, vo
   fc_status st = check_desc(desc);
   if (st != FC_OK) return st;
   if (r < 1 || r > desc->n_tokens) return FC_EINVAL;
-  const Real real = realisation(*desc, r, path);
-  if (real == Real::kNone) return FC_EUNSUPPORTED;
+  const int32_t real = realisation(*desc, r, path);
+  if (real == 0) return FC_EUNSUPPORTED;
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) % kWsAlign) != 0) return FC_EWORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   hipError_t e;
-  if (real == Real::kDense) {
+  if (real == FC_PATH_BASIS) {
     DenseLayout lay = dense_layout(*desc, r);
     if (workspace_bytes < lay.total) return FC_EWORKSPACE;
     e = dense_prepare(*desc, r, lay, workspace, s);
-  } else if (real == Real::kResample) {
+  } else if (real == FC_PATH_RESAMPLE) {
     ResampleLayout lay = resample_layout(*desc, r);
     if (workspace_bytes < lay.total) return FC_EWORKSPACE;
     e = resample_prepare(*desc, r, lay, workspace, s);
@@ -139,19 +144,19 @@ static fc_status score_common(const void* K, const void* V, const fc_kv_desc* de
   fc_status st = check_desc(desc);
   if (st != FC_OK) return st;
   if (r < 1 || r > desc->n_tokens) return FC_EINVAL;
-  const Real real = realisation(*desc, r, path);
-  if (real == Real::kNone) return FC_EUNSUPPORTED;
+  const int32_t real = realisation(*desc, r, path);
+  if (real == 0) return FC_EUNSUPPORTED;
   if (desc->batch == 0) return FC_OK;
   if (!K || !V || !scores || !energy) return FC_EINVAL;
   if (!aligned16(K) || !aligned16(V) || !aligned16(scores) || !aligned16(energy)) return FC_EINVAL;
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) % kWsAlign) != 0) return FC_EWORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   hipError_t e;
-  if (real == Real::kDense) {
+  if (real == FC_PATH_BASIS) {
     DenseLayout lay = dense_layout(*desc, r);
     if (workspace_bytes < lay.total) return FC_EWORKSPACE;
     e = dense_score(K, V, *desc, r, lay, scores, energy, workspace, um, s);
-  } else if (real == Real::kResample) {
+  } else if (real == FC_PATH_RESAMPLE) {
     ResampleLayout lay = resample_layout(*desc, r);
     if (workspace_bytes < lay.total) return FC_EWORKSPACE;
     e = resample_score(K, V, *desc, r, lay, scores, energy, workspace, um, s);
@@ -184,18 +189,18 @@ fc_status flashcache_lowpass_energy(const fc_kv_desc* desc, int32_t r, int32_t p
   fc_status st = check_desc(desc);
   if (st != FC_OK) return st;
   if (r < 1 || r > desc->n_tokens) return FC_EINVAL;
-  const Real real = realisation(*desc, r, path);
-  if (real == Real::kNone) return FC_EUNSUPPORTED;
+  const int32_t real = realisation(*desc, r, path);
+  if (real == 0) return FC_EUNSUPPORTED;
   if (desc->batch == 0) return FC_OK;
   if (!lowpass_energy || (reinterpret_cast<uintptr_t>(lowpass_energy) & 7u)) return FC_EINVAL;
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) % kWsAlign) != 0) return FC_EWORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   hipError_t e;
-  if (real == Real::kDense) {
+  if (real == FC_PATH_BASIS) {
     DenseLayout lay = dense_layout(*desc, r);
     if (workspace_bytes < lay.total) return FC_EWORKSPACE;
     e = dense_lowpass(*desc, lay, workspace, lowpass_energy, s);
-  } else if (real == Real::kResample) {
+  } else if (real == FC_PATH_RESAMPLE) {
     ResampleLayout lay = resample_layout(*desc, r);
     if (workspace_bytes < lay.total) return FC_EWORKSPACE;
     e = resample_lowpass(*desc, lay, workspace, lowpass_energy, s);

@@ -26,7 +26,6 @@ namespace fc {
 
 namespace {
 
-constexpr int kPathResample = 3;       // header tag of a workspace prepared for this realisation
 constexpr int kMaxTilesPerWin = 16;    // 16-token tiles one wave of the residual kernel walks
 constexpr float kInvWeightScale = 4096.0f;   // fp16 weights are stored times 2^12 (their tails stay normal numbers)
 
@@ -179,7 +178,7 @@ __global__ __launch_bounds__(256) void resample_table_kernel(TablePtrs tp, int n
   const double inv_dd = (double)m / (double)n;
   if (id == 0) {
     WsHeader h{};
-    h.magic = kWsMagic; h.path = kPathResample; h.n = n; h.r = r; h.d = d; h.dtype = dtype;
+    h.magic = kWsMagic; h.path = FC_PATH_RESAMPLE; h.n = n; h.r = r; h.d = d; h.dtype = dtype;
     *tp.hdr = h;
   }
   if (id < n_wfwd) {
@@ -365,7 +364,7 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
     count[q] = q < n_tiles ? s.y : 0;
     s_end = s.x + s.y;
   }
-  if (ws_mismatch(hdr, kPathResample, n, r, d, dtype)) return;     // (waits for memory together with the above)
+  if (ws_mismatch(hdr, FC_PATH_RESAMPLE, n, r, d, dtype)) return;     // (waits for memory together with the above)
   const T* p = (second ? V : K) + unit_offset(st, mine ? unit : u0) + (slot - (second ? sm.nb : 0)) * 8 +
                (int64_t)(8 * (lane >> 4)) * st.sn;
   RowPiece<T> x[kBuf][8];
@@ -694,7 +693,7 @@ __global__ __launch_bounds__(G::T < 64 ? 64 : G::T, G::P <= 16 ? 4 : (G::P == 24
 #pragma unroll
   for (int q = 0; q < P; ++q) x[q] = at(g, T * q, lane_at);
   C ph = at(twid, twid_phase_off(M, WIDE), t);
-  if (ws_mismatch(hdr, kPathResample, n, r, d, dtype)) return;
+  if (ws_mismatch(hdr, FC_PATH_RESAMPLE, n, r, d, dtype)) return;
   decltype(C::x) e = 0;
 #pragma unroll(P <= 24 ? 1 : 2)
   for (int way = 0; way < 2; ++way) {
@@ -827,7 +826,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     double* __restrict__ epart, UnitMap um) {
   constexpr int kBuf = sizeof(T) == 2 ? 2 : 1;             // tiles of rows under way
   __shared__ double part_sum[4][16 * kMaxTilesPerWin];
-  if (ws_mismatch(hdr, kPathResample, n, r, d, dtype)) return;
+  if (ws_mismatch(hdr, FC_PATH_RESAMPLE, n, r, d, dtype)) return;
   const double inv_d = 1.0 / (double)d;
   const int lane = threadIdx.x & 63, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

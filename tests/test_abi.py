@@ -136,3 +136,26 @@ def test_static_decode_scratch_holds_what_one_round_of_pieces_needs():
             need = lib.flashcache_decode_workspace_bytes(1, 1, units, units * group, d)
             assert need > 0
             assert (need <= lib.flashcache_decode_static_scratch_bytes()) == (records <= 16 << 20), (units, group, d)
+
+
+def test_every_path_stands_for_the_realisation_it_names():
+    import paper_2511_16786_amd as fc
+    from paper_2511_16786_amd import binding as b
+
+    def real(N, r, d=128, dtype=1, path=b.FC_PATH_AUTO):
+        return fc.realisation(_desc(fc, L=1, H=1, N=N, d=d, dtype=dtype), r, path)
+    # forced: itself wherever its kernels apply, also where the library would choose another
+    for N, r in ((8192, 820), (8192, 4096), (65536, 9362)):
+        for path in (b.FC_PATH_BASIS, b.FC_PATH_STREAM, b.FC_PATH_RESAMPLE):
+            assert real(N, r, path=path) == path
+            assert fc.resolve_path(_desc(fc, L=1, H=1, N=N, d=128, dtype=1), r, path) == path
+        for path in (b.FC_PATH_AUTO, b.FC_PATH_DENSE, b.FC_PATH_FFT):
+            assert real(N, r, path=path) == b.FC_PATH_RESAMPLE
+    # chosen: the resampled transform ends at N/2, at 9362 modes, at head_dim 256 and below 256 tokens
+    for N, r, d in ((8192, 4097, 128), (65536, 9363, 128), (8192, 820, 264)):
+        assert real(N, r, d) == b.FC_PATH_STREAM and real(N, r, d, path=b.FC_PATH_RESAMPLE) == 0
+    for N, r in ((30011, 9363), (8191, 4096), (255, 20)):
+        assert real(N, r) == b.FC_PATH_BASIS and real(N, r, path=b.FC_PATH_RESAMPLE) == 0
+        assert real(N, r, path=b.FC_PATH_STREAM) == 0
+    assert real(8192, 820, path=6) == 0 and real(8192, 820, path=-1) == 0
+    assert real(8191, 4096, 264) == 0                           # no kernel at all

@@ -161,6 +161,29 @@ def test_modes_just_below_the_cutoff_are_kept(n, r):
     assert np.sqrt(np.mean(lost)) <= 2.7e-7
 
 
+# Where the resampled transform ends (9362 modes, N/2, head_dim 256) and the other two go on
+@pytest.mark.parametrize("path,n,r,d", [("basis", 20011, 9363, 16), ("basis", 20011, 9900, 64), ("basis", 20011, 10100, 64),
+                                        ("stream", 20480, 9363, 16), ("stream", 20480, 9900, 64),
+                                        ("stream", 20480, 10241, 8), ("stream", 2048, 200, 264), ("stream", 2560, 600, 272)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_shapes_left_to_the_basis_and_the_streaming_transform(path, n, r, d, dtype):
+    import paper_2511_16786_amd as fc
+    rng = np.random.default_rng(n + r)
+    K = _smooth_plus_noise(rng, (1, 1, 2, n, d), dtype)
+    V = _smooth_plus_noise(rng, (1, 1, 2, n, d), dtype)
+    Kt, Vt = pu.to_torch(K, dtype), pu.to_torch(V, dtype)
+    comp = fc.Compressor(Kt, r, ref.total_budget(1, n, 0.2))
+    assert fc.realisation(comp.desc, r) == fc.binding.PATHS[path]
+    comp.run(Kt, Vt)
+    assert fc.workspace_error(comp.workspace) == 0
+    want = ref.score(K, V, dtype, r, route="fast")
+    pu.check_scores(comp.scores.cpu().numpy(), want["score"], pu.unit_power(ref.widen(K, dtype), ref.widen(V, dtype)))
+    e = comp.energy.cpu().numpy()
+    assert np.allclose(e[..., 2:], want["energy"][..., 2:], rtol=1e-5)
+    assert np.all(np.abs(e[..., :2] - want["energy"][..., :2]) <= 1e-4 * want["energy"][..., :2]
+                  + 1e-7 * want["energy"][..., 2:])
+
+
 @pytest.mark.parametrize("layout", ["token_major", "padded_rows", "heads_last"])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_scores_do_not_depend_on_strides(layout, dtype):

@@ -30,35 +30,39 @@ def _case(name, **kw):
 
 
 CASES = {
-    # name: (config, paths to test)
-    "tiny": (_case("tiny"), ["dense"]),
-    "tiny_ragged": (_case("tiny", n_tokens=500, kv_heads=3), ["dense"]),
+    # name: (config, paths to test).  "dense" and "fft" are what a program asks for, and run the resampled transform for
+    # cut-offs up to N/2 from 256 tokens on; "basis" and "stream" are the realisations that run elsewhere, whose own
+    # cases (folds, passes, blocks, buffers) are the ones described below
+    "tiny": (_case("tiny"), ["dense", "basis"]),
+    "tiny_ragged": (_case("tiny", n_tokens=500, kv_heads=3), ["dense", "basis"]),
     "tiny_n1": (_case("tiny", n_tokens=1, outlier_frac=0.0), ["dense"]),
     "tiny_n70_d128": (_case("tiny", n_tokens=70, head_dim=128, gamma=0.3), ["dense"]),
-    "mid_small": (_case("mid", n_tokens=1024, layers=3, kv_heads=2), ["dense", "fft"]),
-    "mid_half": (_case("mid", n_tokens=3072, layers=1, kv_heads=2, gamma=0.4999), ["fft"]),   # r = N/2
-    "mid": (_case("mid"), ["dense", "fft"]),
+    "mid_small": (_case("mid", n_tokens=1024, layers=3, kv_heads=2), ["dense", "fft", "basis", "stream"]),
+    "mid_half": (_case("mid", n_tokens=3072, layers=1, kv_heads=2, gamma=0.4999), ["fft", "stream"]),   # r = N/2
+    "mid": (_case("mid"), ["dense", "fft", "basis", "stream"]),
     # two full low blocks in one pass (r = 2008 of N = 4096), both realisations
-    "n4k_g49": (_case("mid", n_tokens=4096, layers=1, kv_heads=2, gamma=0.49), ["fft", "dense"]),
+    "n4k_g49": (_case("mid", n_tokens=4096, layers=1, kv_heads=2, gamma=0.49), ["fft", "dense", "stream", "basis"]),
     # odd token count with a middle token (the dense path folds rows i and N-1-i)
-    "odd_n777": (_case("mid", n_tokens=777, layers=2, kv_heads=2, head_dim=64, gamma=0.3), ["dense"]),
-    "qwen_2l": (_case("qwen_8k", layers=2), ["fft"]),
-    "long_1l": (_case("long_32k", layers=1, kv_heads=2), ["fft"]),
-    "batch_16k": (_case("batch8_16k", batch=2, layers=2, kv_heads=1), ["fft"]),
+    "odd_n777": (_case("mid", n_tokens=777, layers=2, kv_heads=2, head_dim=64, gamma=0.3), ["dense", "basis"]),
+    "qwen_2l": (_case("qwen_8k", layers=2), ["fft", "stream"]),
+    "long_1l": (_case("long_32k", layers=1, kv_heads=2), ["fft", "stream"]),
+    "batch_16k": (_case("batch8_16k", batch=2, layers=2, kv_heads=1), ["fft", "stream"]),
     # other storage types and head dims on the fast path
-    "mid_f32_d64": (_case("mid", dtype="f32", head_dim=64, n_tokens=2048, layers=2), ["fft", "dense"]),
-    "mid_d24": (_case("mid", head_dim=24, n_tokens=3072, layers=1, kv_heads=2), ["fft", "dense"]),
-    "mid_f32_d8": (_case("mid", dtype="f32", head_dim=8, n_tokens=2048, layers=1, gamma=0.4), ["fft", "dense"]),
+    "mid_f32_d64": (_case("mid", dtype="f32", head_dim=64, n_tokens=2048, layers=2),
+                    ["fft", "dense", "stream", "basis"]),
+    "mid_d24": (_case("mid", head_dim=24, n_tokens=3072, layers=1, kv_heads=2), ["fft", "dense", "stream", "basis"]),
+    "mid_f32_d8": (_case("mid", dtype="f32", head_dim=8, n_tokens=2048, layers=1, gamma=0.4),
+                   ["fft", "dense", "stream", "basis"]),
     # head dims that are not multiples of 64 on the dense path (padded to 64 inside the kernels), with
     # token counts the fast path does not take
-    "d40_n1000": (_case("mid", head_dim=40, n_tokens=1000, layers=2, kv_heads=2), ["dense"]),
-    "d96_n777": (_case("mid", head_dim=96, n_tokens=777, layers=1, kv_heads=3, gamma=0.3), ["dense"]),
+    "d40_n1000": (_case("mid", head_dim=40, n_tokens=1000, layers=2, kv_heads=2), ["dense", "basis"]),
+    "d96_n777": (_case("mid", head_dim=96, n_tokens=777, layers=1, kv_heads=3, gamma=0.3), ["dense", "basis"]),
     "f32_d12_n333": (_case("mid", dtype="f32", head_dim=12, n_tokens=333, layers=2, kv_heads=1), ["dense"]),
-    "d160_n1500": (_case("mid", head_dim=160, n_tokens=1500, layers=1, kv_heads=2), ["dense"]),
+    "d160_n1500": (_case("mid", head_dim=160, n_tokens=1500, layers=1, kv_heads=2), ["dense", "basis"]),
     # cut-offs above 2048 modes: the fast path runs several passes over an fp32 residual
-    "qwen_g30": (_case("qwen_8k", layers=2, gamma=0.3), ["fft"]),
-    "batch_g25": (_case("batch8_16k", batch=1, layers=1, kv_heads=2, gamma=0.25), ["fft"]),
-    "long_g10": (_case("long_32k", layers=1, kv_heads=1, gamma=0.1), ["fft"]),
+    "qwen_g30": (_case("qwen_8k", layers=2, gamma=0.3), ["fft", "stream"]),
+    "batch_g25": (_case("batch8_16k", batch=1, layers=1, kv_heads=2, gamma=0.25), ["fft", "stream"]),
+    "long_g10": (_case("long_32k", layers=1, kv_heads=1, gamma=0.1), ["fft", "stream"]),
     # cut-offs above N/2: the fast path computes the dropped part (complement mode); one block, two
     # blocks in one pass, several passes (buffer ends as Base KV), everything kept, one 1024-block
     "qwen_g90": (_case("qwen_8k", layers=2, gamma=0.9), ["fft"]),
@@ -69,16 +73,17 @@ CASES = {
                        ["fft", "dense"]),
     # token counts that are multiples of 512 or of 256 only: the fast path with a 512- or 256-point
     # register transform (more passes per cut-off), also in complement mode
-    "n1536": (_case("mid", n_tokens=1536, layers=2, kv_heads=2), ["fft", "dense"]),
-    "n2816_f32": (_case("mid", n_tokens=2816, layers=1, kv_heads=2, dtype="f32", head_dim=64), ["fft", "dense"]),
-    "n7680_g30": (_case("qwen_8k", n_tokens=7680, n_blocks=7, layers=2, kv_heads=2, gamma=0.3), ["fft"]),
+    "n1536": (_case("mid", n_tokens=1536, layers=2, kv_heads=2), ["fft", "dense", "stream", "basis"]),
+    "n2816_f32": (_case("mid", n_tokens=2816, layers=1, kv_heads=2, dtype="f32", head_dim=64),
+                  ["fft", "dense", "stream", "basis"]),
+    "n7680_g30": (_case("qwen_8k", n_tokens=7680, n_blocks=7, layers=2, kv_heads=2, gamma=0.3), ["fft", "stream"]),
     "n7936_g85": (_case("qwen_8k", n_tokens=7936, n_blocks=7, layers=1, kv_heads=2, gamma=0.85), ["fft"]),
-    "n32000": (_case("long_32k", n_tokens=32000, n_blocks=31, layers=1, kv_heads=1), ["fft"]),
+    "n32000": (_case("long_32k", n_tokens=32000, n_blocks=31, layers=1, kv_heads=1), ["fft", "stream"]),
     # above 32768 tokens (single exchange buffer) and a token count with an odd number of 1024-blocks
-    "n64k": (_case("long_32k", n_tokens=65536, n_blocks=64, layers=1, kv_heads=1, gamma=0.02), ["fft"]),
-    "n31k": (_case("long_32k", n_tokens=31744, n_blocks=30, layers=1, kv_heads=2), ["fft"]),
-    "n128k": (_case("long_32k", n_tokens=131072, n_blocks=128, layers=1, kv_heads=1, gamma=0.012), ["fft"]),
-    "blocks_ragged": (_case("qwen_8k", layers=2, kv_heads=2, n_tokens=3000, block_len=360), ["dense"]),
+    "n64k": (_case("long_32k", n_tokens=65536, n_blocks=64, layers=1, kv_heads=1, gamma=0.02), ["fft", "stream"]),
+    "n31k": (_case("long_32k", n_tokens=31744, n_blocks=30, layers=1, kv_heads=2), ["fft", "stream"]),
+    "n128k": (_case("long_32k", n_tokens=131072, n_blocks=128, layers=1, kv_heads=1, gamma=0.012), ["fft", "stream"]),
+    "blocks_ragged": (_case("qwen_8k", layers=2, kv_heads=2, n_tokens=3000, block_len=360), ["dense", "basis"]),
 }
 
 
@@ -176,6 +181,8 @@ def test_end_to_end_matches_oracle(case, path):
         pytest.skip(f"path {path} does not cover this shape")
     assert fc.cutoff_r(cfg.n_tokens, cfg.gamma) == r and fc.total_budget(cfg.layers, cfg.n_tokens, cfg.rho) == T
     comp = fc.Compressor(Kt, r, T, path=path)
+    if path in ("basis", "stream"):
+        assert fc.realisation(comp.desc, r, comp.path) == comp.path
     comp.run(Kt, Vt)
     torch.cuda.synchronize()
     assert fc.workspace_error(comp.workspace) == 0
@@ -439,7 +446,7 @@ def test_strided_layout_token_major():
     Kp = Kt.permute(0, 3, 1, 2, 4).contiguous().permute(0, 2, 3, 1, 4)
     Vp = Vt.permute(0, 3, 1, 2, 4).contiguous().permute(0, 2, 3, 1, 4)
     assert not Kp.is_contiguous()
-    for path in ("dense", "fft"):
+    for path in ("dense", "fft", "basis", "stream", "resample"):
         a = fc.Compressor(Kt, r, T, path=path)
         a.run(Kt, Vt)
         b = fc.Compressor(Kp, r, T, path=path)
@@ -455,7 +462,7 @@ def test_deterministic_and_workspace_guard():
     K, V = generate(cfg, workers=4)
     r, T = ref.cutoff_r(2048, cfg.gamma), ref.total_budget(2, 2048, cfg.rho)
     Kt, Vt = pu.to_torch(K, cfg.dtype), pu.to_torch(V, cfg.dtype)
-    for path in ("dense", "fft"):
+    for path in ("dense", "fft", "basis", "stream", "resample"):
         if not _supported(fc, Kt, r, path):
             continue
         comp = fc.Compressor(Kt, r, T, path=path)
@@ -570,7 +577,8 @@ def test_layer_streamed_scoring_matches_oracle_and_batched():
         assert torch.equal(a, b)
 
 
-@pytest.mark.parametrize("path,n", [("fft", 2048), ("dense", 700), ("fft", 8192)])
+@pytest.mark.parametrize("path,n", [("fft", 2048), ("dense", 700), ("fft", 8192), ("stream", 2048), ("basis", 700),
+                                    ("stream", 8192)])
 def test_layer_streamed_scoring_of_a_batch(path, n):
     """flashcache_score_layer: one call per layer covers every sequence of a batch and writes that
     layer of the full-size outputs; compared with the oracle, and bit-equal to one call over all layers."""
@@ -700,7 +708,8 @@ def test_decode_attention_over_paged_cache(dtype, d, Hq, H, N, page):
 
 
 @pytest.mark.parametrize("case,path", [("mid_small", "dense"), ("mid", "fft"), ("qwen_g30", "fft"),
-                                       ("qwen_g80", "fft"), ("qwen_g60", "fft")])
+                                       ("qwen_g80", "fft"), ("qwen_g60", "fft"), ("mid_small", "basis"),
+                                       ("mid", "stream"), ("qwen_g30", "stream")])
 def test_spectrum_side_energy_cross_check(case, path):
     """Eq. 11-12 as written (energies from the DCT coefficients) against the residual route."""
     fc = _fc()
