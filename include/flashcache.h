@@ -95,8 +95,11 @@ int32_t flashcache_resolve_path(const fc_kv_desc* desc, int32_t r, int32_t path)
  * the shape is invalid or unsupported. */
 int32_t flashcache_realisation(const fc_kv_desc* desc, int32_t r, int32_t path);
 
-/* Bytes of device workspace flashcache_prepare/flashcache_score need for this shape, cut-off
- * and path; 0 if the request is invalid or unsupported. */
+/* Bytes of device workspace for this shape, cut-off and path; 0 if the request is invalid or unsupported.
+ * FC_PATH_FFT (and FC_PATH_AUTO where it resolves to it) asks for the streaming transform's buffers and an
+ * allowance for the resampled transform that does not depend on r.  The path that flashcache_realisation
+ * returns asks for what that realisation needs, which is all that flashcache_prepare and flashcache_score
+ * check, whichever path names it. */
 size_t flashcache_workspace_bytes(const fc_kv_desc* desc, int32_t r, int32_t path);
 
 /* Bytes of device workspace the flashcache_select_gather* entry points need.  The selection kernels

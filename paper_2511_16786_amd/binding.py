@@ -334,7 +334,7 @@ class Compressor:
         if self.path == 0:
             raise FlashCacheError(FC_EUNSUPPORTED, "resolve_path")
         dev = K.device
-        nbytes = workspace_bytes(self.desc, self.r, self.path)
+        nbytes = workspace_bytes(self.desc, self.r, realisation(self.desc, self.r, self.path))
         self.workspace = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=dev)
         self.scores = torch.empty((B, L, H, N), dtype=torch.float32, device=dev)
         self.energy = torch.empty((B, L, H, 4), dtype=torch.float64, device=dev)

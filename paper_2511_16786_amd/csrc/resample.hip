@@ -1106,7 +1106,8 @@ ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
   lay.twid = off; off = up(off + (size_t)twid_size((int)m, lay.wide) * (lay.wide ? sizeof(double2) : sizeof(float2)));
   lay.elow = off; off = up(off + units * 2 * lay.nb * 4 * sizeof(double));
   lay.epart = off; off = up(off + units * lay.wins * lay.wpu * 4 * sizeof(double));
-  lay.grid = off; off = up(off + (size_t)lay.chunk * 2 * lay.nb * 4 * m * sizeof(float2));
+  // (room for the most units of a round: fewer units than these may make a round longer than theirs)
+  lay.grid = off; off = up(off + std::min(units, most) * 2 * lay.nb * 4 * m * sizeof(float2));
   lay.total = off;
   return lay;
 }
@@ -1114,6 +1115,7 @@ ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
 // Upper bound, over all cut-offs, of what this realisation needs beyond the streaming transform's
 // partial sums: one workspace size per shape and cut-off serves both.
 size_t resample_reserve(const fc_kv_desc& d) {
+  if (d.head_dim > 256 || d.n_tokens < 256) return 0;
   const size_t n = d.n_tokens, nb = d.head_dim / 8, units = (size_t)d.batch * d.layers * d.kv_heads;
   const size_t m = std::min<size_t>(16384, n * 5 / 4);
   const size_t tables = 296 * n + 288 * m + (256 << 10);

@@ -159,3 +159,28 @@ def test_every_path_stands_for_the_realisation_it_names():
         assert real(N, r, path=b.FC_PATH_STREAM) == 0
     assert real(8192, 820, path=6) == 0 and real(8192, 820, path=-1) == 0
     assert real(8191, 4096, 264) == 0                           # no kernel at all
+
+
+def test_workspace_sizes_cover_what_runs():
+    """The size for a path is enough for the realisation behind it (score and prepare check the latter), and a
+    workspace of the transforms for more units is enough for fewer."""
+    import random
+    import paper_2511_16786_amd as fc
+    from paper_2511_16786_amd import binding as b
+    rng = random.Random(11)
+    for _ in range(20000):
+        N = int(256 * 2.0 ** rng.uniform(0, 9))
+        if rng.random() < 0.6:
+            N = N // 256 * 256
+        r = max(1, min(N, int(N * 2.0 ** rng.uniform(-9, -0.5))))
+        L, H, d, dtype = rng.choice((1, 2, 7, 28, 60)), rng.choice((1, 4, 8)), 8 * rng.randint(1, 33), rng.randint(0, 1)
+        desc = _desc(fc, L=L, H=H, N=N, d=d, dtype=dtype)
+        fewer = _desc(fc, L=rng.randint(1, L), H=H, N=N, d=d, dtype=dtype)
+        for path in (b.FC_PATH_AUTO, b.FC_PATH_DENSE, b.FC_PATH_FFT):
+            real = fc.realisation(desc, r, path)
+            assert (real == 0) == (fc.resolve_path(desc, r, path) == 0)
+            if real:
+                need = fc.workspace_bytes(desc, r, real)
+                assert 0 < need <= fc.workspace_bytes(desc, r, path), (N, r, d, L, H, path, real)
+                if real != b.FC_PATH_BASIS:                     # (its sums are split the finer the fewer units there are)
+                    assert fc.workspace_bytes(fewer, r, real) <= need, (N, r, d, L, H, path, real)
