@@ -65,6 +65,15 @@ template <> __device__ __forceinline__ void load8<float>(const float* p, float (
 // partial record of one (unit, split): m[G], l[G], o[G][d]  (floats)
 __host__ __device__ inline size_t partial_floats(int G, int d) { return (size_t)G * (d + 2); }
 
+// Pieces that a unit's k rows make of the `splits` that a launch has for every unit: none shorter than 128 rows, a step
+// for each wave.  Budgets are on the device and differ from layer to layer, so that the cut is made there; workgroups
+// beyond it end at once.  28 layers of 4 heads, 7 query heads each, one layer with 2048 rows and 27 with 57: 12.7 us,
+// and 12.7 with 128 rows in every layer (cut on the host by the mean budget, which makes one workgroup of each unit: 26.8
+// and 12.5; every unit in 10 pieces: 20.1 and 20.0).
+__device__ __forceinline__ int pieces_of(int k, int splits) {
+  return min(splits, k > 0 ? (k - 1) / 128 + 1 : 1);
+}
+
 // Paged source: row j of unit (b,l,h) sits in slot j % page_size of page
 // block_table[unit][j / page_size] of caches laid out [num_pages][page_size][d].  table == nullptr
 // means the packed layout.  Rows of a page entry that is missing or out of range are not read.
@@ -103,7 +112,8 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(
   float* rec = partial + ((size_t)unit * splits + split) * partial_floats(G, D);
   const int tid = threadIdx.x, grp = tid / LPR, sub = tid % LPR;
   const bool bad = k < 0 || (!PAGED && (off < 0 || off + k > rows_per_seq));
-  const int chunk = bad ? 0 : (k + splits - 1) / splits;
+  const int pieces = pieces_of(k, splits), chunk = bad ? 0 : (k + pieces - 1) / pieces;
+  if (split >= pieces) return;
   const int r0 = min(k, split * chunk), r1 = bad ? 0 : min(k, r0 + chunk);
 
   // this lane's 8 dims of the G query vectors, pre-multiplied by scale*log2(e)
@@ -264,7 +274,9 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_partial_kernel(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c16 = lane & 15, g4 = lane >> 4;
   const bool bad = k < 0 || (!PAGED && (off < 0 || off + k > rows_per_seq));
   // the unit's steps of 32 rows, shared out evenly over the waves of its workgroups
-  const int steps = bad ? 0 : (k + kStepRows - 1) / kStepRows, share = splits * NW, w_id = split * NW + wave;
+  const int pieces = pieces_of(k, splits);
+  if (split >= pieces) return;
+  const int steps = bad ? 0 : (k + kStepRows - 1) / kStepRows, share = pieces * NW, w_id = split * NW + wave;
   const int s0 = (int)((int64_t)steps * w_id / share), s1 = (int)((int64_t)steps * (w_id + 1) / share);
 
   // B operand of the score product: query head c16 (zeros beyond G), dims (D/4)*g4 ..
@@ -458,20 +470,21 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_partial_kernel(
 // out[unit][g][:] = sum_s o_s w_s / sum_s l_s w_s with w_s = exp2(m_s - max m); zeros if no rows.
 // grid = (G, units), one thread per feature.
 template <int kAtOnce>
-__global__ void decode_merge_kernel(const float* __restrict__ partial, int G, int d, int splits,
-                                    float* __restrict__ out) {
+__global__ void decode_merge_kernel(const float* __restrict__ partial, const int* __restrict__ budgets, int H, int G,
+                                    int d, int splits, float* __restrict__ out) {
   const int g = blockIdx.x, unit = blockIdx.y, dim = threadIdx.x;
+  const int pieces = pieces_of(budgets[unit / H], splits);
   const size_t stride = partial_floats(G, d);
   const float* base = partial + (size_t)unit * splits * stride;
   // kAtOnce records at a time: their loads are under way together (one by one each waits for memory; 112 units of
   // 9 records: 7.2 -> 4.8 us)
   float M = -INFINITY, acc = 0.f, lt = 0.f;
-  for (int s0 = 0; s0 < splits; s0 += kAtOnce) {
+  for (int s0 = 0; s0 < pieces; s0 += kAtOnce) {
     float m[kAtOnce], l[kAtOnce], o[kAtOnce];
 #pragma unroll
     for (int k = 0; k < kAtOnce; ++k) {
-      const float* rec = base + (size_t)min(s0 + k, splits - 1) * stride;
-      m[k] = s0 + k < splits ? rec[g] : -INFINITY;
+      const float* rec = base + (size_t)min(s0 + k, pieces - 1) * stride;
+      m[k] = s0 + k < pieces ? rec[g] : -INFINITY;
       l[k] = rec[G + g];
       o[k] = rec[2 * G + (size_t)g * d + dim];
     }
@@ -503,17 +516,18 @@ int pick_splits(int units, int group, int d) {
   return std::max(1, std::min(32, (1024 + units - 1) / units));
 }
 
-hipError_t launch_merge(const float* ws, int G, int d, int splits, int units, float* out, hipStream_t s) {
+hipError_t launch_merge(const float* ws, const int32_t* budgets, int H, int G, int d, int splits, int units, float* out,
+                        hipStream_t s) {
   ProfileScope ps("decode_merge_kernel", s);
   auto kern = splits <= 2 ? decode_merge_kernel<2> : (splits <= 4 ? decode_merge_kernel<4> : decode_merge_kernel<8>);
-  hipLaunchKernelGGL(kern, dim3(G, units), dim3(d), 0, s, ws, G, d, splits, out);
+  hipLaunchKernelGGL(kern, dim3(G, units), dim3(d), 0, s, ws, budgets, H, G, d, splits, out);
   return hipGetLastError();
 }
 
-// The pieces a launch really makes: none shorter than 128 rows (a step for each wave) where the mean budget, or in
-// the paged layout the table's reach, says so.
-int cut_splits(int splits, int L, int H, int64_t rows_per_seq, const PagedSrc& pg) {
-  const int64_t rows = pg.table ? (int64_t)pg.max_pages * pg.page_size : rows_per_seq / ((int64_t)L * H);
+// The pieces a launch provides for: what the largest budget there can be makes, one layer's heads keeping every row of
+// the sequence or, in the paged layout, a unit as many as its part of the table reaches.
+int cut_splits(int splits, int H, int64_t rows_per_seq, const PagedSrc& pg) {
+  const int64_t rows = pg.table ? (int64_t)pg.max_pages * pg.page_size : rows_per_seq / H;
   const int64_t most = (rows + 127) / 128;
   return most < 1 ? 1 : (most < splits ? (int)most : splits);
 }
@@ -522,7 +536,7 @@ template <typename T, int G, int LPR>
 hipError_t decode_t(const void* Q, const void* Kc, const void* Vc, int B, int L, int H, const int32_t* budgets,
                     const int64_t* offs, int64_t rows_per_seq, float scale, float* out, float* ws,
                     const PagedSrc& pg, hipStream_t s) {
-  const int units = B * L * H, splits = cut_splits(pick_splits(units, G, LPR * 8), L, H, rows_per_seq, pg), d = LPR * 8;
+  const int units = B * L * H, splits = cut_splits(pick_splits(units, G, LPR * 8), H, rows_per_seq, pg), d = LPR * 8;
   {
     ProfileScope ps("decode_partial_kernel", s);
     auto launch = [&](auto kern) {
@@ -536,14 +550,14 @@ hipError_t decode_t(const void* Q, const void* Kc, const void* Vc, int B, int L,
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_merge(ws, G, d, splits, units, out, s);
+  return launch_merge(ws, budgets, H, G, d, splits, units, out, s);
 }
 
 template <int D>
 hipError_t decode_mfma_t(const void* Q, const void* Kc, const void* Vc, int B, int L, int H, int G,
                          const int32_t* budgets, const int64_t* offs, int64_t rows_per_seq, float scale,
                          float* out, float* ws, const PagedSrc& pg, hipStream_t s) {
-  const int units = B * L * H, splits = cut_splits(pick_splits(units, G, D), L, H, rows_per_seq, pg);
+  const int units = B * L * H, splits = cut_splits(pick_splits(units, G, D), H, rows_per_seq, pg);
   {
     ProfileScope ps("decode_mfma_partial_kernel", s);
     auto launch = [&](auto kern) {
@@ -557,7 +571,7 @@ hipError_t decode_mfma_t(const void* Q, const void* Kc, const void* Vc, int B, i
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_merge(ws, G, D, splits, units, out, s);
+  return launch_merge(ws, budgets, H, G, D, splits, units, out, s);
 }
 
 }  // namespace

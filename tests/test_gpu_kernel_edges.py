@@ -329,3 +329,36 @@ def test_decode_rows_that_end_inside_a_step(dtype, d, group, page):
                                         torch.from_numpy(table).cuda(), scale)
     err = np.abs(out.cpu().numpy()[0] - want).max()
     assert err <= 5e-5 * float(np.abs(ref.widen(Vr, dtype)).max())
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_decode_cuts_every_unit_by_its_own_budget(dtype):
+    """Pieces of 128 rows and more, up to the launch's number for a unit, whatever the other layers keep: a record per
+    piece is written, and no other.  The result is the same as for the unit by itself up to the order of the sums."""
+    import paper_2511_16786_amd as fc
+    rng = np.random.default_rng(3)
+    L, H, group, d = 28, 4, 7, 128
+    budgets = np.full(L, 57, np.int64)
+    budgets[[3, 11, 20, 27]] = 2048, 0, 129, 1000
+    offs = ref.layer_offsets(budgets, H)
+    rows = int(offs[-1])
+
+    def make(shape, sigma=1.0):
+        x = (sigma * rng.standard_normal(shape)).astype(np.float32)
+        return kvsynth.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    K, V, Q = make((1, rows, d)), make((1, rows, d), 2.0), make((1, L, H * group, d))
+    record = group * (d + 2)
+    workspace = torch.full((L * H * 64 * record,), float("nan"), device="cuda")
+    scale = float(1.0 / np.sqrt(d))
+    out = fc.decode_attention(pu.to_torch(Q, dtype), pu.to_torch(K, dtype), pu.to_torch(V, dtype), H,
+                              torch.from_numpy(budgets.astype(np.int32)[None]).cuda(),
+                              torch.from_numpy(offs[None]).cuda(), rows, scale, workspace=workspace.view(torch.uint8))
+    splits = 1024 // (L * H)
+    written = ~torch.isnan(workspace.view(-1, record)[:, 0]).cpu().numpy()
+    for u in range(L * H):
+        pieces = min(splits, max(1, -(-int(budgets[u // H]) // 128)))
+        assert np.array_equal(written[u * splits:(u + 1) * splits], np.arange(splits) < pieces), u
+    assert not written[L * H * splits:].any()
+    want = ref.decode_attention(Q[0], K[0], V[0], dtype, budgets, H, scale)
+    err = np.abs(out.cpu().numpy()[0] - want).max()
+    assert err <= 5e-5 * float(np.abs(ref.widen(V, dtype)).max())
