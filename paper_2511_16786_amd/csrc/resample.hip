@@ -114,18 +114,12 @@ struct TablePtrs {
 // points take 258 and 530 us with 48 a thread in three passes, 269 and 807 with 24 in four.
 // Twiddle table: for every pass after the first, powers 1..7 and 8, 16, .. (below R) of w_{R NS}^j, NS the product of
 // the radices before it, j < NS, or j < threads for the last pass; then e^{i pi t / M}.
-// A wide transform (see wide_transform) has twice the registers per point under work, so that three lengths whose
-// last pass would not fit them take four passes: 1606 instead of 3074 us at 12288 points, 637 / 1134 at 6144 and
-// 294 / 366 at 3072 (14336 columns pairs; spilled registers in the longer times).
+// A wide transform (see wide_transform, lengths from 128 to 4096) has twice the registers per point under work: 3072
+// points take four passes, 294 us for 14336 column pairs, instead of three with spilled registers, 366.
 struct GridRadices {
   int p, r[4];
 };
 __host__ __device__ constexpr GridRadices grid_radices(int m, bool wide) {
-  if (wide) switch (m) {
-    case 3072: return {24, {8, 8, 8, 6}};
-    case 6144: return {24, {8, 8, 8, 12}};
-    case 12288: return {48, {8, 8, 16, 12}};
-  }
   switch (m) {
     case 64: return {8, {8, 8, 1, 1}};
     case 96: return {24, {8, 12, 1, 1}};
@@ -138,7 +132,7 @@ __host__ __device__ constexpr GridRadices grid_radices(int m, bool wide) {
     case 1024: return {16, {8, 8, 16, 1}};
     case 1536: return {24, {8, 8, 24, 1}};
     case 2048: return {16, {8, 16, 16, 1}};
-    case 3072: return {48, {16, 16, 12, 1}};
+    case 3072: return wide ? GridRadices{24, {8, 8, 8, 6}} : GridRadices{48, {16, 16, 12, 1}};
     case 4096: return {32, {16, 16, 16, 1}};
     case 6144: return {48, {16, 16, 24, 1}};
     case 8192: return {32, {16, 16, 32, 1}};
@@ -470,6 +464,20 @@ __device__ __forceinline__ constexpr C root(int k, int n) {
   return C{(R)cos192(k * (192 / n)), (R)cos192(k * (192 / n) + 48)};
 }
 
+// What 32 bits leave of a constant, for products that take both parts.  A constant's error is the same in every
+// column's transform and does not average out over them as that of rounded points does: with constants of 32 bits the
+// scores at 7680 tokens, r = 2305, are 1.1e-7 from 64 bits instead of 7e-8, at 32768 tokens, r = 6554, 7.2e-8 instead
+// of 4.1e-8.  The filter takes 2 to 5 % longer for it (14336 column pairs of 3072 points: 199 / 207 us).
+__device__ __forceinline__ constexpr float rest_of(double c) { return (float)(c - (double)(float)c); }
+// a * e^{-2 pi i k / n}
+__device__ __forceinline__ double2 turn(double2 a, int k, int n) { return cmul(a, root<double2>(k, n)); }
+__device__ __forceinline__ float2 turn(float2 a, int k, int n) {
+  const double c = cos192(k * (192 / n)), s = cos192(k * (192 / n) + 48);
+  const float cl = rest_of(c), sl = rest_of(s);
+  return make_float2(fmaf(a.x, (float)c, fmaf(-a.y, (float)s, fmaf(a.x, cl, -a.y * sl))),
+                     fmaf(a.y, (float)c, fmaf(a.x, (float)s, fmaf(a.y, cl, a.x * sl))));
+}
+
 template <typename C>
 __device__ __forceinline__ void dft2(C (&v)[2]) {
   const C a = v[0], b = v[1];
@@ -480,11 +488,18 @@ template <typename C>
 __device__ __forceinline__ void dft3(C (&v)[3]) {
   typedef decltype(C::x) R;
   const C t = cadd(v[1], v[2]), d = csub(v[1], v[2]);
-  const R k = (R)0.86602540378443865, h = (R)-0.5;
+  constexpr double sin60 = 0.86602540378443865;
+  const R k = (R)sin60, h = (R)-0.5;
   const C m = cpair<C>(mad(h, t.x, v[0].x), mad(h, t.y, v[0].y));
   v[0] = cadd(v[0], t);
-  v[1] = cpair<C>(mad(k, d.y, m.x), mad(-k, d.x, m.y));
-  v[2] = cpair<C>(mad(-k, d.y, m.x), mad(k, d.x, m.y));
+  C p = m, q = m;
+  if constexpr (sizeof(R) == 4) {
+    const R l = rest_of(sin60);
+    p = cpair<C>(mad(l, d.y, m.x), mad(-l, d.x, m.y));
+    q = cpair<C>(mad(-l, d.y, m.x), mad(l, d.x, m.y));
+  }
+  v[1] = cpair<C>(mad(k, d.y, p.x), mad(-k, d.x, p.y));
+  v[2] = cpair<C>(mad(-k, d.y, q.x), mad(k, d.x, q.y));
 }
 template <typename C>
 __device__ __forceinline__ void dft4(C (&v)[4]) {
@@ -518,7 +533,7 @@ __device__ __forceinline__ void dft(C (&v)[R]) {
       for (int a = 0; a < A; ++a) {
         if (a * b == 0) y[a][b] = u[a];
         else if (4 * a * b == R) y[a][b] = cpair<C>(u[a].y, -u[a].x);
-        else y[a][b] = cmul(u[a], root<C>(a * b, R));
+        else y[a][b] = turn(u[a], a * b, R);
       }
     }
 #pragma unroll
@@ -1059,18 +1074,17 @@ static int grid_length(const fc_kv_desc& d, int32_t r) {
   return 0;
 }
 
-// Whether the grid transform is computed in 64 bits.  Rounding in 32 (the same for every column where a factor is
-// rounded) comes back from modes near the cut-off multiplied by 1 / phihat there, and counts against a residual that
-// shrinks as the cut-off rises.  Error of the scores against 64 bits (2-norm, 1e-8): streaming transform or explicit
-// basis / this realisation in 32 bits / in 64 bits:
-//   N, r, M             32768, 1639, 3072   4864, 674, 1536   3001, 991, 2048   7680, 2305, 4096   8192, 2049, 4096
-//                       5.1 / 3.7 / -       5.1 / 4.5 / -     6.9 / 11.3 / 3.9  6.4 / 11.4 / 3.9   10.8 / 8.4 / 3.2
+// Whether the grid transform is computed in 64 bits.  Its rounding in 32 comes back from modes near the cut-off
+// multiplied by 1 / phihat there, and counts against a residual that shrinks as the cut-off rises.  Error of the scores
+// against 64 bits (2-norm, 1e-8): streaming transform or explicit basis / this realisation in 32 bits / in 64 bits:
+//   N, r, M             32768, 1639, 3072   4864, 674, 1536   3001, 991, 2048   7680, 2305, 4096   1111, 293, 768
+//                       5.1 / 3.3 / -       5.1 / 3.7 / -     6.9 / 6.0 / 4.0   6.4 / 7.2 / 4.4    5.4 / 6.1 / 3.4
 //   N, r, M             16384, 3277, 6144   32768, 6554, 12288   10562, 2968, 6144   32768, 9176, 16384
-//                       10.1 / 8.4 / -      11.4 / 8.2 / -       10.5 / 11.6 / 3.4   11.2 / 12.0 / 3.2
-// So it is taken where 32 bits are worse than the other realisations: above r = 3/16 N, and above N/4 for grids of
-// more than 4096 points (where those take several passes over an fp32 residual, or sums of 10000 products).  The
-// filter takes 1.2 to 1.75 times as long (14336 column pairs of 4096 points 240 / 330 us, 16384 points 795 / 950).
-static bool wide_transform(int64_t n, int64_t r, int64_t m) { return m <= 4096 ? 16 * r > 3 * n : 4 * r > n; }
+//                       10.1 / 4.2 / -      11.4 / 4.1 / -       10.5 / 5.8 / 3.4    11.2 / 3.9 / 3.2
+// So it is taken where 32 bits are worse than the other realisations: above r = N/4 for grids of up to 4096 points (the
+// longer ones' shapes take those several passes over an fp32 residual, or sums of 10000 products).  The filter takes
+// 1.4 times as long (14336 column pairs of 4096 points: 240 / 330 us).
+static bool wide_transform(int64_t n, int64_t r, int64_t m) { return m <= 4096 && 4 * r > n; }
 
 // (below 256 tokens the products with the basis itself are as quick and need no plan worth speaking of)
 bool resample_supported(const fc_kv_desc& d, int32_t r) { return d.n_tokens >= 256 && grid_length(d, r) != 0; }
@@ -1199,17 +1213,18 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
     if (e != hipSuccess) return e;
     double* elow = reinterpret_cast<double*>(base + lay.elow) + (size_t)u0 * 2 * lay.nb * 4;
     const int pairs = (u1 - u0) * 2 * lay.nb * 4;
-    auto filter = [&](auto narrow, auto wide) {
-      return (lay.wide ? wide : narrow)(grid, pairs, n, r, d.head_dim, d.dtype, hdr, filt, twid, elow, s);
-    };
-#define FC_FILTER(MV) case MV: e = filter(launch_filter<MV, false>, launch_filter<MV, true>); break;
+#define FC_FILTER(MV, WIDE) launch_filter<MV, WIDE>(grid, pairs, n, r, d.head_dim, d.dtype, hdr, filt, twid, elow, s)
+#define FC_NARROW(MV) case MV: e = FC_FILTER(MV, false); break;
+#define FC_EITHER(MV) case MV: e = lay.wide ? FC_FILTER(MV, true) : FC_FILTER(MV, false); break;
     switch (m) {
-      case 64: e = launch_filter<64, false>(grid, pairs, n, r, d.head_dim, d.dtype, hdr, filt, twid, elow, s); break;
-      FC_FILTER(96) FC_FILTER(128) FC_FILTER(192) FC_FILTER(256) FC_FILTER(384) FC_FILTER(512) FC_FILTER(768)
-      FC_FILTER(1024) FC_FILTER(1536) FC_FILTER(2048) FC_FILTER(3072) FC_FILTER(4096) FC_FILTER(6144) FC_FILTER(8192)
-      FC_FILTER(12288) FC_FILTER(16384)
+      FC_NARROW(64) FC_NARROW(96)
+      FC_EITHER(128) FC_EITHER(192) FC_EITHER(256) FC_EITHER(384) FC_EITHER(512) FC_EITHER(768) FC_EITHER(1024)
+      FC_EITHER(1536) FC_EITHER(2048) FC_EITHER(3072) FC_EITHER(4096)
+      FC_NARROW(6144) FC_NARROW(8192) FC_NARROW(12288) FC_NARROW(16384)
       default: e = hipErrorInvalidValue;
     }
+#undef FC_EITHER
+#undef FC_NARROW
 #undef FC_FILTER
     if (e != hipSuccess) return e;
     {

@@ -125,14 +125,16 @@ def test_sums_of_noise_are_as_good_as_64_bits(n, r, d, units, dtype):
     assert float((comp.scores.double() - s).norm() / s.norm()) <= (4.0e-8 if d == 64 else 3.6e-8)
 
 
-# Every grid length at a cut-off where its transform is computed in 64 bits, from where that rule begins (3/16 N, N/4)
-@pytest.mark.parametrize("n,r", [(260, 52), (300, 70), (420, 100), (600, 140), (777, 219), (512, 231), (1111, 293),
-                                 (2048, 585), (3072, 877), (3001, 991), (4099, 1755), (7680, 2305), (7023, 3400),
-                                 (9401, 4680), (12544, 5645), (18749, 9362), (2048, 383), (2048, 385), (10562, 2641)])
+# Every grid length from 128 points on at cut-offs near N/4, from where on grids of up to 4096 points are transformed in
+# 64 bits, and near N/2
+@pytest.mark.parametrize("n,r", [(260, 64), (260, 66), (300, 76), (420, 106), (600, 151), (777, 219), (512, 231),
+                                 (1111, 293), (2048, 512), (2048, 513), (3072, 877), (3001, 991), (4099, 1755),
+                                 (7680, 2305), (4000, 990), (7023, 3400), (9401, 4680), (12544, 5645), (18749, 9362)])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_scores_at_high_cutoffs_are_as_good_as_64_bits(n, r, dtype):
     """What remains above a high cut-off is small beside the columns, and their transform's rounding counts.  Allowed
-    are four times the 2.5e-8 of one rounding to fp32: of the score, its sums, the weights and the grid values."""
+    are four times the 2.5e-8 of one rounding to fp32 (of the score, its sums, the weights and the grid values), and
+    1.7e-7 for grids of more than 4096 points, whose transform adds sqrt(2 log2 M) roundings of 2.5e-8, 1.3e-7."""
     import paper_2511_16786_amd as fc
     rng = np.random.default_rng(n + r)
     K, V = (pu.to_torch(_smooth_plus_noise(rng, (1, 1, 2, n, 64), dtype), dtype) for _ in range(2))
@@ -140,7 +142,7 @@ def test_scores_at_high_cutoffs_are_as_good_as_64_bits(n, r, dtype):
     comp.run_score(K, V)
     hp = [_residual64(X, r) for X in (K, V)]
     s = (hp[0].pow(2).sum(-1) + hp[1].pow(2).sum(-1)) / 64
-    assert float((comp.scores.double() - s).norm() / s.norm()) <= 1e-7
+    assert float((comp.scores.double() - s).norm() / s.norm()) <= (1e-7 if 7 * r <= 4 * 4096 else 1.7e-7)
 
 
 @pytest.mark.parametrize("n,r", [(1024, 292), (2048, 585), (3072, 877), (7680, 2305)])
