@@ -169,9 +169,8 @@ def overlap_record(torch, fc, cfg, Kt, Vt, r, comp, reps=3, producer_mb=512):
             "serial_sum_ms": t_p + t_c, "hidden_fraction_of_scoring": (t_p + t_c - t_b) / t_c,
             "scores_equal_batched_run": same,
             "producer": f"per layer: one elementwise pass over {producer_mb} MB, then the copies of the layer's K and V",
-            "note": "one layer occupies B*H*2*(d/16) workgroups of the transform kernel (64 of 256 compute "
-                    "units for one sequence), so layer-by-layer scoring alone is slower than the batched "
-                    "call; beside a producer its time is hidden"}
+            "note": "the launches of one layer leave most of the chip idle, so layer-by-layer scoring alone is "
+                    "slower than the batched call; beside a producer part of its time is hidden"}
 
 
 def main():

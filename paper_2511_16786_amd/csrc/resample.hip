@@ -329,8 +329,8 @@ constexpr int kDecWaves = 4;          // waves of a workgroup: 4 slots' worth of
 // as large as registers allow; results do not depend on it (a tile's steps and their order are its own).  A tile walks
 // the steps that its windows reach into, one fewer than the most any tile has for two tiles in three (12288 points
 // for 32768 tokens: 757 instead of 800 us for 112 units).
-// 56 units of 32768 tokens, M = 3072: 232 us, 0.94 GB of rows and 0.18 GB of grid at 4.8 TB/s (one tile a wave read
-// the rows 1.75 instead of 1.14 times).
+// 56 units of 32768 tokens, M = 3072: 236 us, 1.11 GB read for 0.94 GB of rows and 0.19 GB written, 5.5 TB/s (one tile a
+// wave read the rows 1.75 times).
 template <typename T, int GT, bool KEEP>
 __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
     const T* __restrict__ K, const T* __restrict__ V, KvStrides st, int u0, int u1, int n, int r, int d, int dtype,
@@ -830,7 +830,8 @@ constexpr int kResWorkgroups = 512;   // residual kernel: two for each compute u
 // after the other.  Rows are requested two tiles ahead and grid values one window ahead, across segments.
 // Neighbouring windows read the same lines of the grid: an XCD takes a contiguous range of windows and its
 // workgroups walk (units, window) side by side, window fastest, so that its L2 serves what they share.
-// Bound by the rows: 56 units of 32768 tokens, M = 3072: 234 us, 0.94 GB of rows at 4.0 TB/s beside the grid's reads.
+// Bound by the rows: 56 units of 32768 tokens, M = 3072: 248 us, 1.18 GB read for 0.94 GB of rows and 0.18 of grid, 4.8
+// TB/s.  112 units: 432 us with three of the five products and sums in 32 bits, 455 with sums as they are, 474 with all.
 // A lane holds slot lane & 15 throughout: columns 8 slot + j of tokens 4 (lane >> 4) + i, so that a load reads whole
 // rows, and of a window the points that its loads deliver in 64-byte pieces (see resample_table_kernel).
 template <typename T, bool KEEP>
