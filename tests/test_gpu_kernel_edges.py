@@ -119,8 +119,8 @@ def test_sums_of_noise_are_as_good_as_64_bits(n, r, d, units, dtype):
     want = torch.stack([x.pow(2).sum((-1, -2)) for x in (hp[0], hp[1], K.double(), V.double())], -1)
     off = (comp.energy / want - 1.0).abs().amax((0, 1, 2)).tolist()
     assert max(off[:2]) <= 4e-9
-    # (bf16 squares have 16 bits, and 32 of them added in fp32, rounded to nearest, come out 1.2e-8 low in the mean)
-    assert max(off[2:]) <= (2.0 ** -25 if dtype == "bf16" else 4e-9)
+    # (bf16 squares have 16 bits, and 8 of them added in fp32, rounded to nearest, come out 6.5e-9 low in the mean)
+    assert max(off[2:]) <= (1e-8 if dtype == "bf16" else 4e-9)
     s = (hp[0].pow(2).sum(-1) + hp[1].pow(2).sum(-1)) / d
     assert float((comp.scores.double() - s).norm() / s.norm()) <= (4.0e-8 if d == 64 else 3.6e-8)
 
