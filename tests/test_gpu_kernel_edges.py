@@ -333,14 +333,16 @@ def test_decode_rows_that_end_inside_a_step(dtype, d, group, page):
     assert err <= 5e-5 * float(np.abs(ref.widen(Vr, dtype)).max())
 
 
+# most layers keep less than the launch's pieces (units first), or more (a unit's pieces first)
+@pytest.mark.parametrize("most", [57, 1300])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-def test_decode_cuts_every_unit_by_its_own_budget(dtype):
+def test_decode_cuts_every_unit_by_its_own_budget(dtype, most):
     """Pieces of 128 rows and more, up to the launch's number for a unit, whatever the other layers keep: a record per
     piece is written, and no other.  The result is the same as for the unit by itself up to the order of the sums."""
     import paper_2511_16786_amd as fc
     rng = np.random.default_rng(3)
     L, H, group, d = 28, 4, 7, 128
-    budgets = np.full(L, 57, np.int64)
+    budgets = np.full(L, most, np.int64)
     budgets[[3, 11, 20, 27]] = 2048, 0, 129, 1000
     offs = ref.layer_offsets(budgets, H)
     rows = int(offs[-1])
