@@ -577,6 +577,9 @@ struct GridFft {
   using G = GridPlan<M, WIDE>;
   using C = typename std::conditional<WIDE, double2, float2>::type;
   static constexpr int P = G::P, T = G::T;
+  // (constants of their own: as a call in the kernel the phases' offset was computed at its start, by a loop over the
+  // radices in scratch memory, three waits in turn: 112 units of 32768 tokens, M = 3072: 207 / 181 us of filter, M = 12288: 964 / 911)
+  static constexpr int kOff2 = twid_off(M, WIDE, 2), kOff3 = twid_off(M, WIDE, 3), kPhaseOff = twid_phase_off(M, WIDE);
   // slot of point i; T and NS * R are multiples of 2^kPadShift, so that pad(i + T q) = pad(i) + pad(T q)
   static __device__ __forceinline__ constexpr int pad(int i) { return i + (i >> G::kPadShift); }
 
@@ -671,13 +674,13 @@ struct GridFft {
     butterflies<G::R1, N1>(x, f1);
     if constexpr (G::R2 > 1) {
       Factors<G::R2, N2> f2;
-      f2.load(twid + twid_off(M, WIDE, 2), t);
+      f2.load(twid + kOff2, t);
       exchange<G::R1, N1>(x, lds, t);
       butterflies<G::R2, N2>(x, f2);
     }
     if constexpr (G::R3 > 1) {
       Factors<G::R3, N3> f3;
-      f3.load(twid + twid_off(M, WIDE, 3), t);
+      f3.load(twid + kOff3, t);
       exchange<G::R2, N2>(x, lds, t);
       butterflies<G::R3, N3>(x, f3);
     }
@@ -702,13 +705,13 @@ __global__ __launch_bounds__(G::T < 64 ? 64 : G::T, G::P <= 16 ? 4 : (G::P == 24
   __shared__ double wsum[T < 64 ? 1 : T / 64];
   const int t = threadIdx.x % T, pb = threadIdx.x / T;
   float* lds = lds_all + pb * G::kLds;
-  const int pair = min(blockIdx.x * PB + pb, pairs - 1);   // (surplus lanes repeat the last pair)
+  const int pair = min((int)blockIdx.x * PB + pb, pairs - 1);   // (surplus lanes repeat the last pair)
   float2* g = grid + (size_t)blockIdx.x * PB * M;
-  uint32_t lane_at = (uint32_t)((pair - blockIdx.x * PB) * M + t);
+  uint32_t lane_at = (uint32_t)((pair - (int)blockIdx.x * PB) * M + t);
   float2 x[P];
 #pragma unroll
   for (int q = 0; q < P; ++q) x[q] = at(g, T * q, lane_at);
-  C ph = at(twid, twid_phase_off(M, WIDE), t);
+  C ph = at(twid, F::kPhaseOff, t);
   if (ws_mismatch(hdr, FC_PATH_RESAMPLE, n, r, d, dtype)) return;
   decltype(C::x) e = 0;
 #pragma unroll(P <= 24 ? 1 : 2)
