@@ -475,6 +475,12 @@ __device__ __forceinline__ double2 turn(double2 a, int k, int n) { return cmul(a
 __device__ __forceinline__ float2 turn(float2 a, int k, int n) {
   const double c = cos192(k * (192 / n)), s = cos192(k * (192 / n) + 48);
   const float cl = rest_of(c), sl = rest_of(s);
+  if (s == 0.0) return c > 0.0 ? a : make_float2(-a.x, -a.y);
+  if (c == 0.0) return s > 0.0 ? make_float2(-a.y, a.x) : make_float2(a.y, -a.x);
+  if (cl == 0.f)                                           // (a half: its product is not rounded)
+    return make_float2(fmaf(a.x, (float)c, fmaf(-a.y, (float)s, -a.y * sl)), fmaf(a.y, (float)c, fmaf(a.x, (float)s, a.x * sl)));
+  if (sl == 0.f)
+    return make_float2(fmaf(-a.y, (float)s, fmaf(a.x, (float)c, a.x * cl)), fmaf(a.x, (float)s, fmaf(a.y, (float)c, a.y * cl)));
   return make_float2(fmaf(a.x, (float)c, fmaf(-a.y, (float)s, fmaf(a.x, cl, -a.y * sl))),
                      fmaf(a.y, (float)c, fmaf(a.x, (float)s, fmaf(a.y, cl, a.x * sl))));
 }
@@ -529,6 +535,7 @@ __device__ __forceinline__ void dft(C (&v)[R]) {
       C u[A];
 #pragma unroll
       for (int a = 0; a < A; ++a) u[a] = v[B * a + b];
+      if (R >= 24 && b % 4 == 0) __builtin_amdgcn_sched_barrier(0);
       dft<A>(u);
 #pragma unroll
       for (int a = 0; a < A; ++a) {
@@ -539,6 +546,7 @@ __device__ __forceinline__ void dft(C (&v)[R]) {
     }
 #pragma unroll
     for (int a = 0; a < A; ++a) {
+      if (R >= 24) __builtin_amdgcn_sched_barrier(0);
       dft<B>(y[a]);
 #pragma unroll
       for (int b = 0; b < B; ++b) v[a + A * b] = y[a][b];
@@ -553,10 +561,21 @@ struct GridPlan {
   // One slot of padding per R0 (or T, where fewer): the strided writes of a pass fall on distinct banks.
   static constexpr int log2(int v) { return v <= 1 ? 0 : 1 + log2(v / 2); }
   static constexpr int kPadShift = log2(R0 < T ? R0 : T);
-  static constexpr int kLds = M + (M >> kPadShift) + 1;
+  static constexpr int kLds = M + (M >> kPadShift) + 2;       // (even: blocks are read as pairs)
+  // Bins from each end of a thread's points that meet their mirrors at a time, 0: all bins at once, real parts, then
+  // imaginary parts.  Blocks need the registers of one block's mirrors instead of all bins', and with them and each
+  // pass's points pinned (see the kernel) a SIMD holds the waves of kWaves without spilling: 48 points a thread three
+  // instead of two, 32 points four instead of three (and 16384 points two workgroups a compute unit instead of one), 64-bit
+  // ones three (16 points; 32: two).  Filter of 112 units, us before / after: 32768 tokens M = 3072 184 / 167, M = 12288
+  // 902 / 778, 30011 tokens M = 6144 401 / 355, 50000 tokens M = 16384 (36 units) 496 / 338; in 64 bits 1500 tokens M = 768
+  // (32 units) 27.0 / 23.0.  The short narrow ones have the registers as they are, and are slower with blocks and more
+  // waves (M = 1536: 84 / 103).
+  static constexpr int kBlock = !WIDE && P < 32 ? 0 : (P == 48 && T == 64 ? 4 : P / 8);
   // (a pass's exchange takes a thread's butterflies to be T apart in whole groups of the transforms done before it)
   static_assert((R2 == 1 || R0 <= T) && (R3 == 1 || R0 * R1 <= T), "groups of the grid transform");
-  static_assert(R0 * R1 * R2 * R3 == M && T % (1 << kPadShift) == 0, "radices of the grid transform");
+  static_assert(R0 * R1 * R2 * R3 == M && T % (1 << kPadShift) == 0 && kLds % 2 == 0, "radices of the grid transform");
+  static_assert(kBlock == 0 || ((P / 2) % kBlock == 0 && 8 * kBlock * T + 8 <= kLds), "blocks of bins fit the exchange's LDS");
+  static constexpr int kWaves = WIDE ? (P <= 16 ? 3 : 2) : (P <= 16 || P == 32 ? 4 : 3);   // a SIMD's
 };
 
 // element i + k of a table: uniform base and constant part, 32-bit part of the lane
@@ -642,6 +661,7 @@ struct GridFft {
   template <int R, int NS>
   static __device__ __forceinline__ void exchange(float2 (&x)[P], float* lds, int t) {
     constexpr int N = P / R;
+    asm volatile("" : "+v"(t));                            // (addresses are not worth keeping from one exchange to the next)
     float* o = lds + pad((t / NS) * (NS * R) + (t & (NS - 1)));
     const float* in = lds + pad(t);
     float re[P];
@@ -694,9 +714,9 @@ struct GridFft {
 // sum_m Re(conj(W) W') is the kept energy of both columns (the operator is symmetric).  The way back is the same
 // transform with real and imaginary parts exchanged.  Short lengths (few workgroups) run it in the same code, since
 // such a launch would wait for the instructions of a second copy to be fetched (768 points: 13 instead of 16 us); the
-// lengths whose points fill the registers are better off with two copies (3072 points: 180 instead of 220 us).
+// lengths with 32 and 48 points a thread are better off with two copies (3072 points: 180 instead of 220 us).
 template <int M, bool WIDE, typename G = GridPlan<M, WIDE>, typename F = GridFft<M, WIDE>>
-__global__ __launch_bounds__(G::T < 64 ? 64 : G::T, G::P <= 16 ? 4 : (G::P == 24 ? 3 : 2)) void grid_filter_kernel(
+__global__ __launch_bounds__(G::T < 64 ? 64 : G::T, G::kWaves) void grid_filter_kernel(
     float2* __restrict__ grid, int pairs, int n, int r, int d, int dtype, WsHeader* hdr,
     const float2* __restrict__ filt, const typename F::C* __restrict__ twid, double* __restrict__ elow) {
   using C = typename F::C;
@@ -707,7 +727,7 @@ __global__ __launch_bounds__(G::T < 64 ? 64 : G::T, G::P <= 16 ? 4 : (G::P == 24
   float* lds = lds_all + pb * G::kLds;
   const int pair = min((int)blockIdx.x * PB + pb, pairs - 1);   // (surplus lanes repeat the last pair)
   float2* g = grid + (size_t)blockIdx.x * PB * M;
-  uint32_t lane_at = (uint32_t)((pair - (int)blockIdx.x * PB) * M + t);
+  uint32_t lane_at = (uint32_t)(T < 64 ? (pair - (int)blockIdx.x * PB) * M + t : t);
   float2 x[P];
 #pragma unroll
   for (int q = 0; q < P; ++q) x[q] = at(g, T * q, lane_at);
@@ -719,29 +739,68 @@ __global__ __launch_bounds__(G::T < 64 ? 64 : G::T, G::P <= 16 ? 4 : (G::P == 24
     // (what the tables give is loaded and derived anew: kept from one way to the next it would fill the registers)
     asm volatile("" : "+s"(twid), "+s"(filt), "+v"(ph.x), "+v"(ph.y));
     F::run(x, lds, twid, t);
+    // (the points are made here: moved down to where a block takes them, the last pass would keep more operands than results)
+    if constexpr (G::kBlock > 0)
+#pragma unroll
+      for (int q = 0; q < P; ++q) asm volatile("" : "+v"(x[q].x), "+v"(x[q].y));
     if (way == 1) break;
-    // each bin's mirror, W[M - m] (with W[M] = W[0])
-    float2 o[P];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-#pragma unroll
-      for (int q = 0; q < P; ++q) lds[F::pad(t) + F::pad(T * q)] = h ? x[q].y : x[q].x;
-      if (t == 0) lds[F::pad(M)] = h ? x[0].y : x[0].x;
-      __syncthreads();
-#pragma unroll
-      for (int q = 0; q < P; ++q) (h ? o[q].y : o[q].x) = lds[F::pad(M - T * q) + F::pad(-t)];
-      __syncthreads();
-    }
-#pragma unroll
-    for (int q = 0; q < P; ++q) {
-      if (q % 8 == 0) __builtin_amdgcn_sched_barrier(0);
+    auto bin = [&](int q, float2 mirror) {
       const float2 fq = at(filt, T * q, t);
       const C f = cpair<C>(fq.x, fq.y);
       const C c = root<C>(q, 2 * P), w = cpair<C>(x[q].x, x[q].y);
-      const C z = cmul(cpair<C>(o[q].x, o[q].y), cmul(ph, cpair<C>(c.x, -c.y)));   // e^{i pi (t + T q) / M}
+      const C z = cmul(cpair<C>(mirror.x, mirror.y), cmul(ph, cpair<C>(c.x, -c.y)));   // e^{i pi (t + T q) / M}
       const C y = cpair<C>(mad(f.y, z.x, f.x * w.x), mad(f.y, z.y, f.x * w.y));
       e = mad(w.x, y.x, mad(w.y, y.y, e));
       x[q] = make_float2((float)y.y, (float)y.x);
+    };
+    // each bin's mirror, W[M - m] (with W[M] = W[0])
+    if constexpr (G::kBlock > 0) {
+      // a block of bins from each end, which are each other's mirrors
+      constexpr int H = G::kBlock;
+      float2 edge = x[0];
+#pragma unroll
+      for (int q0 = 0; q0 < P / 2; q0 += H) {
+        // (blocks take turns with the two halves of the buffer, so that one wait a block will do)
+        float2 *lo = reinterpret_cast<float2*>(lds) + (q0 / H & 1) * (2 * H * T + 2), *hi = lo + H * T + 1;
+#pragma unroll
+        for (int j = 0; j < H; ++j) lo[T * j + t] = x[q0 + j];
+#pragma unroll
+        for (int j = 0; j < H; ++j) hi[T * j + t] = x[P - q0 - H + j];
+        if (t == 0) {
+          lo[T * H] = x[q0 + H];
+          hi[T * H] = edge;
+        }
+        edge = x[P - q0 - H];
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {
+          float2 o[H];
+#pragma unroll
+          for (int j = 0; j < H; ++j) o[j] = (side ? lo : hi)[T * (H - j) - t];
+#pragma unroll
+          for (int j = 0; j < H; ++j) bin(side ? P - q0 - H + j : q0 + j, o[j]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      __syncthreads();
+    } else {
+      float2 o[P];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int q = 0; q < P; ++q) lds[F::pad(t) + F::pad(T * q)] = h ? x[q].y : x[q].x;
+        if (t == 0) lds[F::pad(M)] = h ? x[0].y : x[0].x;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < P; ++q) (h ? o[q].y : o[q].x) = lds[F::pad(M - T * q) + F::pad(-t)];
+        __syncthreads();
+      }
+#pragma unroll
+      for (int q = 0; q < P; ++q) {
+        if (q % 8 == 0) __builtin_amdgcn_sched_barrier(0);
+        bin(q, o[q]);
+      }
     }
     __builtin_amdgcn_sched_barrier(0);
   }
