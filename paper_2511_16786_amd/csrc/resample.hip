@@ -274,6 +274,11 @@ struct RowPiece<float> {
   }
 };
 
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+
 __device__ __forceinline__ f32x4 mfma_bf16(const Frag& a, const Frag& b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.b, b.b, c, 0, 0, 0);
 }
@@ -330,8 +335,11 @@ constexpr int kDecWaves = 4;          // waves of a workgroup: 4 slots' worth of
 // as large as registers allow; results do not depend on it (a tile's steps and their order are its own).  A tile walks
 // the steps that its windows reach into, one fewer than the most any tile has for two tiles in three (12288 points
 // for 32768 tokens: 757 instead of 800 us for 112 units).
-// 56 units of 32768 tokens, M = 3072: 236 us, 1.11 GB read for 0.94 GB of rows and 0.19 GB written, 5.5 TB/s (one tile a
-// wave read the rows 1.75 times).
+// (one tile a wave reads the rows 1.75 times).  Every other group of four tiles is walked from its end, so that neighbours
+// are at the rows they share together.  Results leave in 16 bytes and whole 128-byte lines, two tiles side by side: the
+// writes, a seventh of the traffic, cost a quarter of the time as half lines of 8 bytes a lane.  112 units, us before both /
+// walked both ways / now: 32768 tokens M = 3072 472 / 470 / 457 (1.09 GB read a round for 0.94 GB of rows, was 1.11; 0.19
+// written), M = 12288 750 / 717 / 671, 30011 tokens 541 / 535 / 503, 8192 tokens 146 / 144 / 136.
 template <typename T, int GT, bool KEEP>
 __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
     const T* __restrict__ K, const T* __restrict__ V, KvStrides st, int u0, int u1, int n, int r, int d, int dtype,
@@ -368,9 +376,11 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e].template load<KEEP>(ps + e * st.sn);
   };
+  // (every other group of four tiles is walked from its end, so that neighbours come to the rows they share together)
+  const int steps_all = s_end - first[0], dir = (tile0 >> 2) & 1 ? -1 : 1, s_from = dir > 0 ? first[0] : s_end - 1;
 #pragma unroll
   for (int b = 0; b < kBuf; ++b)
-    if (b == 0 || first[0] + b < s_end) load(x[b], first[0] + b);
+    if (b == 0 || b < steps_all) load(x[b], s_from + dir * b);
   {
     const f32x4* src = reinterpret_cast<const f32x4*>(wfwd) + (size_t)tile0 * steps * 128;
     for (int i = threadIdx.x; i < n_tiles * steps * 128; i += 64 * kDecWaves) wlds[i] = src[i];
@@ -383,7 +393,8 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
   for (int q = 0; q < GT; ++q)
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[q][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto step = [&](RowPiece<T> (&v)[8], int s) {
+  auto step = [&](RowPiece<T> (&v)[8], int i) {
+    const int s = s_from + dir * i;
 #pragma unroll
     for (int q = 0; q < GT; ++q) {
       const int k = s - first[q];
@@ -402,24 +413,47 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
         }
       }
     }
-    if (s + kBuf < s_end) load(v, s + kBuf);
+    if (i + kBuf < steps_all) load(v, s + dir * kBuf);
   };
-  for (int s = first[0]; s < s_end; s += kBuf)
+  for (int i = 0; i < steps_all; i += kBuf)
 #pragma unroll
     for (int b = 0; b < kBuf; ++b)
-      if (s + b < s_end) step(x[b], s + b);
+      if (i + b < steps_all) step(x[b], i + b);
 
+  // Out in 16 bytes, two neighbours of the transform's order: of two points two lanes apart one lane of the two takes
+  // what belongs to the first tile (or column pair), the other what belongs to the second.
+  const bool up = lane & 2, swap = ((lane >> 1) ^ lane) & 1;
+  auto both = [&](float2 a, float2 b) {
+    const float2 own = up ? b : a, give = up ? a : b;
+    const float2 got = make_float2(dpp<0x4E>(give.x), dpp<0x4E>(give.y));          // quad_perm 2,3,0,1
+    return swap ? f32x4{got.x, got.y, own.x, own.y} : f32x4{own.x, own.y, got.x, got.y};
+  };
+  // where the lane's two points go: those of lanes l & ~2 and l | 2, the lower one in the transform's order first
+  const int kl = lane & 13, k0 = 16 * tile0 + ((lane & 1) ? kl | 2 : kl);
 #pragma unroll
-  for (int q = 0; q < GT; ++q) {
+  for (int q = 0; q < GT; q += 2) {
     if (q >= n_tiles) break;
-    const int pos = grid_pos(16 * (tile0 + q) + (lane & 15), m);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int s_out = part * 16 + 4 * (lane >> 4) + i;
-      if (s_out < 2 * sm.nb) {
-        float2* o = grid + ((size_t)(unit - u0) * 2 * sm.nb + s_out) * 4 * m + pos;
+      float2* o = grid + ((size_t)(unit - u0) * 2 * sm.nb + s_out) * 4 * m;
+      if constexpr (GT > 1) {
+        const bool there = s_out < 2 * sm.nb && (!up || q + 1 < n_tiles);
+        float2* t = o + grid_pos(k0 + 16 * (q + (up ? 1 : 0)), m);
 #pragma unroll
-        for (int jp = 0; jp < 4; ++jp) o[(size_t)jp * m] = make_float2(acc[q][2 * jp][i], acc[q][2 * jp + 1][i]);
+        for (int jp = 0; jp < 4; ++jp) {
+          const f32x4 w = both(make_float2(acc[q][2 * jp][i], acc[q][2 * jp + 1][i]),
+                               make_float2(acc[q + 1][2 * jp][i], acc[q + 1][2 * jp + 1][i]));
+          if (there) *reinterpret_cast<f32x4*>(t + (size_t)jp * m) = w;
+        }
+      } else {
+        float2* t = o + grid_pos(k0, m) + (up ? m : 0);
+#pragma unroll
+        for (int jp = 0; jp < 4; jp += 2) {
+          const f32x4 w = both(make_float2(acc[q][2 * jp][i], acc[q][2 * jp + 1][i]),
+                               make_float2(acc[q][2 * jp + 2][i], acc[q][2 * jp + 3][i]));
+          if (s_out < 2 * sm.nb) *reinterpret_cast<f32x4*>(t + (size_t)jp * m) = w;
+        }
       }
     }
   }
@@ -852,10 +886,6 @@ __device__ __forceinline__ void residual8(const RowPiece<float>& x, const f32x4 
   }
 }
 
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
-}
 // Over the four lanes that hold one slot.
 __device__ __forceinline__ float slot_max(float v) {
   v = fmaxf(v, __shfl_xor(v, 16, 64));
