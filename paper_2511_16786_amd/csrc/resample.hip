@@ -1150,11 +1150,12 @@ hipError_t launch_filter(float2* grid, int pairs, int n, int r, int d, int dtype
 }  // namespace
 
 // Bytes of grid one round of the three kernels works on.  They are written, read, written and read again: below the
-// last-level cache's 256 MB, and with the rows kept out of it (keep_rows), three of the four ways stay on the chip, while smaller
-// rounds leave the launches too little to work on.  Scoring 112 units of 32768 tokens (336 MB of grid at r = 1639,
-// 1344 MB at r = 6554): one round 1184 / 2513 us, 200 MB 1106 / 2344, 140 MB 1139 / 2624, 80 MB 1319 / 3164; with
-// ordinary loads one round 1218 / 2450, and smaller ones slower.
-constexpr size_t kRoundGridBytes = (size_t)200 << 20;
+// last-level cache's 256 MB, and with the rows kept out of it (keep_rows), three of the four ways stay on the chip, while
+// smaller rounds leave the launches too little to work on.  Scoring 112 units of 30011 tokens, M = 6144, rounds of 176,
+// 201, 251 and 302 MB: 1394, 1376, 1337, 1452 us; with ordinary loads of the rows larger rounds are better.  Where the rows are less
+// than twice the grid, rounds of 201 MB are (8000 tokens, M = 4096: 168 MB 749 us, 251 MB 766; 32768 tokens, M = 12288: 201
+// MB 2122, 251 MB 2141).
+constexpr size_t kRoundGridBytes = (size_t)240 << 20;
 
 // Grid length for this shape and cut-off, 0 if the realisation does not apply.
 static int grid_length(const fc_kv_desc& d, int32_t r) {
@@ -1182,6 +1183,18 @@ static bool wide_transform(int64_t n, int64_t r, int64_t m) { return m <= 4096 &
 // (below 256 tokens the products with the basis itself are as quick and need no plan worth speaking of)
 bool resample_supported(const fc_kv_desc& d, int32_t r) { return d.n_tokens >= 256 && grid_length(d, r) != 0; }
 
+// Units of a round, of at most `most`: as few rounds as that takes, whole sets of four units (the residual kernel's waves),
+// the last round a little shorter than the others.  Scoring 112 units, us by units of a round:
+//   32768 tokens, M = 3072:  52 1093, 56 1095, 60 1063, 64 1065, 72 1069, 80 1102   M = 12288:  14 2395, 16 2142, 19 2197, 20 2152
+//   30011 tokens, M = 6144:  28 1394, 32 1376, 38 1357, 40 1337
+//   16384 tokens (224 units), M = 3072:  56 1428, 60 1427, 76 1380, 80 1372
+static int round_units(int units, int most) {
+  if (units <= most) return units;
+  if (most < 4) return most;
+  const int rounds = (units + most - 1) / most;
+  return std::min(most / 4, (107 * units + 400 * rounds - 1) / (400 * rounds)) * 4;
+}
+
 ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
   ResampleLayout lay{};
   const int64_t n = d.n_tokens, m = grid_length(d, r);
@@ -1199,10 +1212,11 @@ ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
   lay.nb = d.head_dim / 8;
   const int waves = (2 * lay.nb + 15) / 16;
   lay.wpu = waves <= 2 ? waves : 4;
-  // units per round of the three kernels, the rounds alike
-  const size_t most = std::max<size_t>(1, kRoundGridBytes / (2 * (size_t)m * d.head_dim * sizeof(float)));
-  const size_t rounds = std::max<size_t>(1, (units + most - 1) / most);
-  lay.chunk = (int)std::max<size_t>(1, (units + rounds - 1) / rounds);
+  // units per round of the three kernels
+  const size_t unit_grid = 2 * (size_t)m * d.head_dim * sizeof(float);
+  const bool much_grid = (size_t)n * (d.dtype == FC_BF16 ? 2 : 4) < 2 * (size_t)m * sizeof(float);
+  const int most = (int)std::max<size_t>(1, (much_grid ? kRoundGridBytes / 6 * 5 : kRoundGridBytes) / unit_grid);
+  lay.chunk = round_units((int)units, most);
   auto up = [](size_t x) { return (x + kWsAlign - 1) / kWsAlign * kWsAlign; };
   size_t off = sizeof(WsHeader);
   lay.wfwd = off; off = up(off + (size_t)(m / 16) * lay.steps * 512 * sizeof(float));
@@ -1214,7 +1228,7 @@ ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
   lay.elow = off; off = up(off + units * 2 * lay.nb * 4 * sizeof(double));
   lay.epart = off; off = up(off + units * lay.wins * lay.wpu * 4 * sizeof(double));
   // (room for the most units of a round: fewer units than these may make a round longer than theirs)
-  lay.grid = off; off = up(off + std::min(units, most) * 2 * lay.nb * 4 * m * sizeof(float2));
+  lay.grid = off; off = up(off + std::min<size_t>(units, most) * 2 * lay.nb * 4 * m * sizeof(float2));
   lay.total = off;
   return lay;
 }
