@@ -467,7 +467,7 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_partial_kernel(
 // out[unit][g][:] = sum_s o_s w_s / sum_s l_s w_s with w_s = exp2(m_s - max m); zeros if no rows.
 // grid = (G, units), one thread per feature and group of pieces, groups merged in order.  Bound by waiting for memory: a
 // group takes kAtOnce records at a time, whose loads are under way together, and a launch has groups for all but the longest lists to be
-// one turn (8 units of 64 records: 11.0 -> 6.9 us with event timing, 112 units of 9 records: 6.8 -> 6.3).
+// one turn (8 units of 64 records: 10.9 -> 6.2 us, 112 units of 9 records: 6.8 -> 6.2, with events; an empty launch 6.1).
 template <int kAtOnce, int kGroups>
 __global__ void decode_merge_kernel(const float* __restrict__ partial, const int* __restrict__ budgets, int H, int G,
                                     int d, int splits, float* __restrict__ out) {
