@@ -44,7 +44,7 @@ struct ResampleLayout {
   int32_t m, steps, tpw, wins;    // grid points; 32-token steps per grid tile; 16-token tiles per window; windows
   int32_t nb, wpu, chunk;         // 8-column blocks per tensor; waves per unit; units per round
   bool wide;                      // grid transform in 64 bits
-  size_t wfwd, winv, s0, k0, filt, twid, elow, epart, grid, total;
+  size_t wfwd, winv, filt, twid, elow, epart, grid, total;
 };
 
 DenseLayout dense_layout(const fc_kv_desc& d, int32_t r);

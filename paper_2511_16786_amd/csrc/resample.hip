@@ -96,6 +96,22 @@ __device__ double weight_at(double u, int k, int m, const Window& w) {
   return sum;
 }
 
+// First 32-token step under a tile of 16 grid points, and first grid point (a multiple of four) of a window that begins with
+// token `first`: the tables are made for them and the kernels derive them anew, which is quicker than to read them.
+__host__ __device__ __forceinline__ int first_step(int tile, int n, int steps, double dd, int w) {
+  const int t = (int)ceil(fma(dd, 16.0 * tile - 0.5 * w + 0.5, -0.5));
+  return min(max(0, t) / 32, (n + 31) / 32 - steps);
+}
+__host__ __device__ __forceinline__ int first_point(int first, int m, double inv_dd, int w) {
+  const int k0 = (int)ceil(fma(first + 0.5, inv_dd, -0.5) - 0.5 * w);
+  return max(0, min(k0, m - 32)) & ~3;
+}
+// steps that the tile's windows reach into
+__host__ __device__ __forceinline__ int step_count(int tile, int s0, int n, int steps, double dd, int w) {
+  const int last = min(n - 1, (int)floor(fma(dd, 16.0 * tile + 15.5 + 0.5 * w, -0.5)));
+  return min(last / 32 + 1 - s0, steps);
+}
+
 // position of grid point k in the order the transform takes its input (even points ascending, then
 // odd points descending)
 __device__ __forceinline__ int grid_pos(int k, int m) { return (k & 1) ? m - 1 - (k >> 1) : k >> 1; }
@@ -104,8 +120,6 @@ struct TablePtrs {
   WsHeader* hdr;
   float* wfwd;       // [M/16][steps][2][64][4]
   _Float16* winv;    // [tokens/16][3][64][8] fp16
-  int2* s0;          // [M/16] first 32-token step of a grid tile, and the steps its windows reach into
-  int* k0;           // [windows] first grid point of a window
   float2* filt;      // [M] (f[m] + f[M-m]) / 2, (f[m] - f[M-m]) / 2
   void* twid;        // see GridFft: float2, or double2 for a wide transform
 };
@@ -179,12 +193,7 @@ __global__ __launch_bounds__(256) void resample_table_kernel(TablePtrs tp, int n
   if (id < n_wfwd) {
     const int o = id & 511, lane = (o >> 2) & 63, e = (o >> 8) * 4 + (o & 3);
     const int step = (id >> 9) % steps, tile = (id >> 9) / steps;
-    int s0 = max(0, (int)ceil(dd * (16.0 * tile - 0.5 * win.w + 0.5) - 0.5)) / 32;
-    s0 = min(s0, (n + 31) / 32 - steps);
-    if (o == 0 && step == 0) {
-      const int last = min(n - 1, (int)floor(dd * (16.0 * tile + 15.5 + 0.5 * win.w) - 0.5));
-      tp.s0[tile] = make_int2(s0, min(last / 32 + 1 - s0, steps));
-    }
+    const int s0 = first_step(tile, n, steps, dd, win.w);
     // the last step slides back to end with the last token and takes only what earlier steps have not
     const int i = min(32 * (s0 + step), n - 32) + 8 * (lane >> 4) + e;
     tp.wfwd[id] =
@@ -194,10 +203,7 @@ __global__ __launch_bounds__(256) void resample_table_kernel(TablePtrs tp, int n
   id -= n_wfwd;
   if (id < n_winv) {
     const int o = id & 511, lane = o >> 3, e = o & 7, tile = id >> 9, g = lane >> 4, first = tile / tpw * tpw;
-    const double uf = (16.0 * first + 0.5) * inv_dd - 0.5;
-    int k0 = (int)ceil(uf - 0.5 * win.w);
-    k0 = max(0, min(k0, m - 32)) & ~3;
-    if (o == 0 && tile == first) tp.k0[tile / tpw] = k0;
+    const int k0 = first_point(16 * first, m, inv_dd, win.w);
     const int i = 16 * tile + (lane & 15);
     // the order in which the residual kernel's loads deliver the window's grid points
     const int k = e < 4 ? k0 + 2 * (8 * (e >> 1) + 2 * g + (e & 1)) : k0 + 2 * (31 - 8 * (e >> 1) - 2 * g - (e & 1)) + 1;
@@ -344,7 +350,7 @@ template <typename T, int GT, bool KEEP>
 __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
     const T* __restrict__ K, const T* __restrict__ V, KvStrides st, int u0, int u1, int n, int r, int d, int dtype,
     int m, int steps, SlotMap sm, int supers_per_xcd, WsHeader* hdr, const float* __restrict__ wfwd,
-    const int2* __restrict__ s0s, float2* __restrict__ grid) {
+    float2* __restrict__ grid) {
   constexpr int kTerms = sizeof(T) == 2 ? 1 : 3;
   constexpr int kBuf = sizeof(T) == 2 ? 2 : 1;    // steps of rows under way (a step's registers are refilled in place)
   extern __shared__ f32x4 wlds[];                 // [GT][steps][2][64]
@@ -359,15 +365,16 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
   const int s_mine = part * 16 + (lane & 15);
   const int slot = s_mine < 2 * sm.nb ? s_mine : 0;
   const bool second = slot >= sm.nb;
+  const double dd = (double)n / (double)m;        // tokens per grid point
   int first[GT], count[GT], s_end = 0;            // a tile's first step, and how many it has
 #pragma unroll
   for (int q = 0; q < GT; ++q) {
-    const int2 s = s0s[tile0 + min(q, n_tiles - 1)];
-    first[q] = s.x;
-    count[q] = q < n_tiles ? s.y : 0;
-    s_end = s.x + s.y;
+    const int tile = tile0 + min(q, n_tiles - 1), w = window_points(r, m);
+    first[q] = __builtin_amdgcn_readfirstlane(first_step(tile, n, steps, dd, w));
+    const int c = __builtin_amdgcn_readfirstlane(step_count(tile, first[q], n, steps, dd, w));
+    count[q] = q < n_tiles ? c : 0;
+    s_end = first[q] + c;
   }
-  if (ws_mismatch(hdr, FC_PATH_RESAMPLE, n, r, d, dtype)) return;     // (waits for memory together with the above)
   const T* p = (second ? V : K) + unit_offset(st, mine ? unit : u0) + (slot - (second ? sm.nb : 0)) * 8 +
                (int64_t)(8 * (lane >> 4)) * st.sn;
   RowPiece<T> x[kBuf][8];
@@ -381,6 +388,7 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
 #pragma unroll
   for (int b = 0; b < kBuf; ++b)
     if (b == 0 || b < steps_all) load(x[b], s_from + dir * b);
+  if (ws_mismatch(hdr, FC_PATH_RESAMPLE, n, r, d, dtype)) return;     // (while the rows are on their way)
   {
     const f32x4* src = reinterpret_cast<const f32x4*>(wfwd) + (size_t)tile0 * steps * 128;
     for (int i = threadIdx.x; i < n_tiles * steps * 128; i += 64 * kDecWaves) wlds[i] = src[i];
@@ -931,12 +939,11 @@ template <typename T, bool KEEP>
 __global__ __launch_bounds__(256, 2) void residual_kernel(
     const T* __restrict__ K, const T* __restrict__ V, KvStrides st, int u0, int u1, int n, int r, int d, int dtype,
     int m, int tpw, int wins, SlotMap sm, bool split, WsHeader* hdr, const _Float16* __restrict__ winv,
-    const int* __restrict__ k0s, const float2* __restrict__ grid, float* __restrict__ scores,
+    const float2* __restrict__ grid, float* __restrict__ scores,
     double* __restrict__ epart, UnitMap um) {
   constexpr int kBuf = sizeof(T) == 2 ? 2 : 1;             // tiles of rows under way
   __shared__ double part_sum[4][16 * kMaxTilesPerWin];
-  if (ws_mismatch(hdr, FC_PATH_RESAMPLE, n, r, d, dtype)) return;
-  const double inv_d = 1.0 / (double)d;
+  const double inv_d = 1.0 / (double)d, inv_dd = (double)m / (double)n;
   const int lane = threadIdx.x & 63, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // units worked on side by side: one for each wave, or (split) as many as have a wave for every part
@@ -959,7 +966,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     s.part = my_part + pt;
     const int set = (unsigned)it / (unsigned)w_count;
     s.win = w_first + it - set * w_count;
-    s.n0 = k0s[s.win] >> 1;
+    s.n0 = __builtin_amdgcn_readfirstlane(first_point(16 * tpw * s.win, m, inv_dd, window_points(r, m))) >> 1;
     s.unit = min(u0 + abreast * set + my_unit, u1 - 1);    // (a surplus wave repeats the last unit)
     s.tiles = max(min(tpw, tok_tiles - s.win * tpw), kBuf);   // (a tile too many is worked on and dropped)
     const int mine = s.part * 16 + (lane & 15), slot = mine < 2 * sm.nb ? mine : 0;
@@ -999,12 +1006,14 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     for (int q = 0; q < 3; ++q) wn[q].u = p[64 * q];
   };
 
-  Seg cur = segment(item, part), nxt = following(cur);
+  Seg cur = segment(item, part);
   RowPiece<T> x[kBuf][4];
   load_window(cur);
   load_weights(cur, 0);
 #pragma unroll
   for (int k = 0; k < kBuf; ++k) load_rows(x[k], cur, k);
+  if (ws_mismatch(hdr, FC_PATH_RESAMPLE, n, r, d, dtype)) return;     // (while the above is on its way)
+  Seg nxt = following(cur);
   int tl = 0;
   bool more = true;
   Frag bh[8], bl[8];
@@ -1221,8 +1230,6 @@ ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
   size_t off = sizeof(WsHeader);
   lay.wfwd = off; off = up(off + (size_t)(m / 16) * lay.steps * 512 * sizeof(float));
   lay.winv = off; off = up(off + (size_t)lay.wins * lay.tpw * 1536 * 2);
-  lay.s0 = off; off = up(off + (size_t)(m / 16) * 8);
-  lay.k0 = off; off = up(off + (size_t)lay.wins * 4);
   lay.filt = off; off = up(off + (size_t)m * sizeof(float2));
   lay.twid = off; off = up(off + (size_t)twid_size((int)m, lay.wide) * (lay.wide ? sizeof(double2) : sizeof(float2)));
   lay.elow = off; off = up(off + units * 2 * lay.nb * 4 * sizeof(double));
@@ -1250,9 +1257,7 @@ size_t resample_reserve(const fc_kv_desc& d) {
 hipError_t resample_prepare(const fc_kv_desc& d, int32_t r, const ResampleLayout& lay, void* ws, hipStream_t s) {
   char* base = static_cast<char*>(ws);
   TablePtrs tp{reinterpret_cast<WsHeader*>(base), reinterpret_cast<float*>(base + lay.wfwd),
-               reinterpret_cast<_Float16*>(base + lay.winv), reinterpret_cast<int2*>(base + lay.s0),
-               reinterpret_cast<int*>(base + lay.k0), reinterpret_cast<float2*>(base + lay.filt),
-               base + lay.twid};
+               reinterpret_cast<_Float16*>(base + lay.winv), reinterpret_cast<float2*>(base + lay.filt), base + lay.twid};
   const int n_wfwd = lay.m / 16 * lay.steps * 512, n_winv = lay.wins * lay.tpw * 512;
   const int total = n_wfwd + n_winv + lay.m + twid_size(lay.m, lay.wide);
   ProfileScope ps("resample_table_kernel", s);
@@ -1265,7 +1270,7 @@ hipError_t resample_prepare(const fc_kv_desc& d, int32_t r, const ResampleLayout
 template <typename T, int GT, bool KEEP>
 static hipError_t launch_decimate_gt(const T* K, const T* V, KvStrides st, int u0, int u1, int n, int r,
                                      const fc_kv_desc& d, int m, const ResampleLayout& lay, SlotMap sm, WsHeader* hdr,
-                                     const float* wfwd, const int2* s0, float2* grid, hipStream_t s) {
+                                     const float* wfwd, float2* grid, hipStream_t s) {
   auto kern = decimate_kernel<T, GT, KEEP>;
   const size_t lds = (size_t)GT * lay.steps * 2048;
   if (lds > 64 * 1024) {
@@ -1277,7 +1282,7 @@ static hipError_t launch_decimate_gt(const T* K, const T* V, KvStrides st, int u
   const int groups = ((u1 - u0) * sm.wpu + kDecWaves - 1) / kDecWaves;
   ProfileScope ps("decimate_kernel", s);
   hipLaunchKernelGGL(kern, dim3(8 * spx * groups), dim3(64 * kDecWaves), lds, s, K, V, st, u0, u1, n, r, d.head_dim,
-                     d.dtype, m, lay.steps, sm, spx, hdr, wfwd, s0, grid);
+                     d.dtype, m, lay.steps, sm, spx, hdr, wfwd, grid);
   return hipGetLastError();
 }
 
@@ -1287,15 +1292,15 @@ static hipError_t launch_decimate_gt(const T* K, const T* V, KvStrides st, int u
 template <typename T, bool KEEP>
 static hipError_t launch_decimate(const T* K, const T* V, KvStrides st, int u0, int u1, int n, int r,
                                   const fc_kv_desc& d, int m, const ResampleLayout& lay, SlotMap sm, WsHeader* hdr,
-                                  const float* wfwd, const int2* s0, float2* grid, hipStream_t s) {
+                                  const float* wfwd, float2* grid, hipStream_t s) {
   const int groups = ((u1 - u0) * sm.wpu + kDecWaves - 1) / kDecWaves;
   auto fits = [&](int gt) {
     return gt * lay.steps * 2048 <= 80 * 1024 && (int64_t)(m / 16 / gt) * groups >= kMinWorkgroups;
   };
   if constexpr (sizeof(T) == 2)
-    if (fits(4)) return launch_decimate_gt<T, 4, KEEP>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, s0, grid, s);
-  if (fits(2)) return launch_decimate_gt<T, 2, KEEP>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, s0, grid, s);
-  return launch_decimate_gt<T, 1, KEEP>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, s0, grid, s);
+    if (fits(4)) return launch_decimate_gt<T, 4, KEEP>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, grid, s);
+  if (fits(2)) return launch_decimate_gt<T, 2, KEEP>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, grid, s);
+  return launch_decimate_gt<T, 1, KEEP>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, grid, s);
 }
 
 template <typename T, bool KEEP>
@@ -1315,8 +1320,7 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
   for (int u0 = 0; u0 < units; u0 += lay.chunk) {
     const int u1 = std::min(units, u0 + lay.chunk);
     hipError_t e = launch_decimate<T, KEEP>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr,
-                                      reinterpret_cast<const float*>(base + lay.wfwd),
-                                      reinterpret_cast<const int2*>(base + lay.s0), grid, s);
+                                      reinterpret_cast<const float*>(base + lay.wfwd), grid, s);
     if (e != hipSuccess) return e;
     double* elow = reinterpret_cast<double*>(base + lay.elow) + (size_t)u0 * 2 * lay.nb * 4;
     const int pairs = (u1 - u0) * 2 * lay.nb * 4;
@@ -1343,7 +1347,7 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
       hipLaunchKernelGGL((residual_kernel<T, KEEP>), dim3(8 * (int)std::min<int64_t>(items, kResWorkgroups / 8)), dim3(256), 0,
                          s, K, V, st, u0, u1, n, r, d.head_dim, d.dtype, m, lay.tpw, lay.wins, sm, split, hdr,
                          reinterpret_cast<const _Float16*>(base + lay.winv),
-                         reinterpret_cast<const int*>(base + lay.k0), grid, scores, epart, um);
+                         grid, scores, epart, um);
     }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
