@@ -932,9 +932,13 @@ constexpr int kResWorkgroups = 512;   // residual kernel: two for each compute u
 // Neighbouring windows read the same lines of the grid: an XCD takes a contiguous range of windows and its
 // workgroups walk (units, window) side by side, window fastest, so that its L2 serves what they share.
 // Bound by the rows: 56 units of 32768 tokens, M = 3072: 248 us, 1.18 GB read for 0.94 GB of rows and 0.18 of grid, 4.8
-// TB/s.  112 units: 432 us with three of the five products and sums in 32 bits, 455 with sums as they are, 474 with all.
+// TB/s, with the grid's loads as they first were.  112 units: 432 us with three of the five products and sums in 32 bits, 455 with sums as they are, 474 with all.
 // A lane holds slot lane & 15 throughout: columns 8 slot + j of tokens 4 (lane >> 4) + i, so that a load reads whole
-// rows, and of a window the points that its loads deliver in 64-byte pieces (see resample_table_kernel).
+// rows, and of a window the points that loads of 64-byte pieces deliver (see resample_table_kernel).  Those loads are made
+// by four lanes next to each other and turned over to the operands' lanes through LDS (a swizzle keeps them on distinct
+// banks): by the operands' lanes, 16 slots apart in memory, they took the address unit four times as long.  112 units, us
+// before / after: 32768 tokens M = 3072 460 / 448, M = 12288 729 / 683, 30011 tokens 526 / 507; one layer of 16384 21.5 / 18.0,
+// of which 1.6 for not loading a window after the last segment.
 template <typename T, bool KEEP>
 __global__ __launch_bounds__(256, 2) void residual_kernel(
     const T* __restrict__ K, const T* __restrict__ V, KvStrides st, int u0, int u1, int n, int r, int d, int dtype,
@@ -943,6 +947,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     double* __restrict__ epart, UnitMap um) {
   constexpr int kBuf = sizeof(T) == 2 ? 2 : 1;             // tiles of rows under way
   __shared__ double part_sum[4][16 * kMaxTilesPerWin];
+  __shared__ f32x4 turn_lds[4][4][64];                     // a wave's window on its way from loading to operand lanes
   const double inv_d = 1.0 / (double)d, inv_dd = (double)m / (double)n;
   const int lane = threadIdx.x & 63, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -959,7 +964,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
   struct Seg {
     int win, unit, part, tiles, n0;                        // n0: position of the window's first even grid point
     const T* rows;                                         // this lane's columns of token 4 g
-    const float2* gp;                                      // this lane's first column pair on the grid
+    const float2* gp;                                      // the first column pair that this lane loads on the grid
   };
   auto segment = [&](int it, int pt) {
     Seg s;
@@ -972,13 +977,16 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     const int mine = s.part * 16 + (lane & 15), slot = mine < 2 * sm.nb ? mine : 0;
     const bool second = slot >= sm.nb;
     s.rows = (second ? V : K) + unit_offset(st, s.unit) + (slot - (second ? sm.nb : 0)) * 8 + (int64_t)(4 * g) * st.sn;
-    s.gp = grid + ((size_t)(s.unit - u0) * 2 * sm.nb + slot) * 4 * m + 2 * g;
+    const int loaded = s.part * 16 + (lane >> 2);
+    s.gp = grid + ((size_t)(s.unit - u0) * 2 * sm.nb + (loaded < 2 * sm.nb ? loaded : 0)) * 4 * m + 2 * ((lane ^ (lane >> 3)) & 3);
     return s;
   };
-  auto following = [&](const Seg& s) {                     // (the last segment follows itself)
+  bool follows;                                            // whether there is a segment after the one under way
+  auto following = [&](const Seg& s) {
     int it = item, pt = part + 1;
     if (pt == parts) { pt = 0; it += peers; }
-    return it < items ? segment(it, pt) : s;
+    follows = it < items;
+    return follows ? segment(it, pt) : s;
   };
   f32x4 v[4][4];
   auto load_window = [&](const Seg& s) {
@@ -1020,7 +1028,15 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
   float inv = 0.f;
   double hp = 0.0, tot = 0.0;
 
+  const int operand_at = 4 * (lane & 15) + (g ^ ((lane >> 1) & 3));
   auto take_window = [&]() {
+#pragma unroll
+    for (int jp = 0; jp < 4; ++jp) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) turn_lds[wave][c][lane] = v[jp][c];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) v[jp][c] = turn_lds[wave][c][operand_at];
+    }
     float mx = 0.f;
 #pragma unroll
     for (int jp = 0; jp < 4; ++jp)
@@ -1050,7 +1066,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
 #pragma unroll
     for (int j = 0; j < 8; ++j) asm volatile("" : "+v"(bh[j].u), "+v"(bl[j].u));
     hp = tot = 0.0;
-    load_window(nxt);
+    if (follows) load_window(nxt);
   };
   // energies of the segment: Ehp_k, Ehp_v, Etot_k, Etot_v
   auto record = [&]() {
