@@ -112,6 +112,12 @@ __host__ __device__ __forceinline__ int step_count(int tile, int s0, int n, int 
   return min(last / 32 + 1 - s0, steps);
 }
 
+// Grid point of a tile that lane & 15 = l of the decimation holds: even points in lanes 0 to 7, odd ones in 8 to 15, of
+// each the first half ascending, the second descending, so that lanes that mirror each other hold neighbours.
+__host__ __device__ __forceinline__ int lane_point(int l) {
+  return (l & 4 ? 4 * (3 - (l & 3)) + 2 : 4 * (l & 3)) + (l >> 3);
+}
+
 // position of grid point k in the order the transform takes its input (even points ascending, then
 // odd points descending)
 __device__ __forceinline__ int grid_pos(int k, int m) { return (k & 1) ? m - 1 - (k >> 1) : k >> 1; }
@@ -197,7 +203,7 @@ __global__ __launch_bounds__(256) void resample_table_kernel(TablePtrs tp, int n
     // the last step slides back to end with the last token and takes only what earlier steps have not
     const int i = min(32 * (s0 + step), n - 32) + 8 * (lane >> 4) + e;
     tp.wfwd[id] =
-        i >= 32 * (s0 + step) ? (float)weight_at((i + 0.5) * inv_dd - 0.5, 16 * tile + (lane & 15), m, win) : 0.0f;
+        i >= 32 * (s0 + step) ? (float)weight_at((i + 0.5) * inv_dd - 0.5, 16 * tile + lane_point(lane & 15), m, win) : 0.0f;
     return;
   }
   id -= n_wfwd;
@@ -428,16 +434,16 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
     for (int b = 0; b < kBuf; ++b)
       if (i + b < steps_all) step(x[b], i + b);
 
-  // Out in 16 bytes, two neighbours of the transform's order: of two points two lanes apart one lane of the two takes
-  // what belongs to the first tile (or column pair), the other what belongs to the second.
-  const bool up = lane & 2, swap = ((lane >> 1) ^ lane) & 1;
+  // Out in 16 bytes, two neighbours of the transform's order: of the two lanes that hold them one takes what belongs to the
+  // first tile (or column pair), the other what belongs to the second, and four lanes side by side write 64 bytes.
+  const bool up = lane & 4, swap = ((lane >> 2) ^ (lane >> 3)) & 1;
   auto both = [&](float2 a, float2 b) {
     const float2 own = up ? b : a, give = up ? a : b;
-    const float2 got = make_float2(dpp<0x4E>(give.x), dpp<0x4E>(give.y));          // quad_perm 2,3,0,1
+    const float2 got = make_float2(dpp<0x141>(give.x), dpp<0x141>(give.y));        // row_half_mirror
     return swap ? f32x4{got.x, got.y, own.x, own.y} : f32x4{own.x, own.y, got.x, got.y};
   };
-  // where the lane's two points go: those of lanes l & ~2 and l | 2, the lower one in the transform's order first
-  const int kl = lane & 13, k0 = 16 * tile0 + ((lane & 1) ? kl | 2 : kl);
+  // the one of the lane's two points that is first in the transform's order
+  const int k0 = 16 * tile0 + (lane_point(lane & 15) & ~2) + ((lane >> 2) & 2);
 #pragma unroll
   for (int q = 0; q < GT; q += 2) {
     if (q >= n_tiles) break;
@@ -630,6 +636,14 @@ __device__ __forceinline__ C at(const C* base, int k, uint32_t i) {
   return cpair<C>(v.x, v.y);
 }
 
+// Element k of a grid's column pair as a scalar base and the part of k that a load's 12-bit offset holds.  (Left to the compiler each
+// load of the longer grids makes a 64-bit address of its own on the vector units.)
+__device__ __forceinline__ float2* element(float2* base, int k) {
+  char* b = reinterpret_cast<char*>(base) + ((k * (int)sizeof(float2)) & ~4095);
+  asm volatile("" : "+s"(b));
+  return reinterpret_cast<float2*>(b + ((k * (int)sizeof(float2)) & 4095));
+}
+
 // Length-M complex transform of one column pair; natural order before and after, exchanges through LDS.
 // Points are held in 32 bits; a wide transform takes each pass's factors and arithmetic in 64, so that its results are
 // rounded once a pass.
@@ -772,7 +786,7 @@ __global__ __launch_bounds__(G::T < 64 ? 64 : G::T, G::kWaves) void grid_filter_
   uint32_t lane_at = (uint32_t)(T < 64 ? (pair - (int)blockIdx.x * PB) * M + t : t);
   float2 x[P];
 #pragma unroll
-  for (int q = 0; q < P; ++q) x[q] = at(g, T * q, lane_at);
+  for (int q = 0; q < P; ++q) x[q] = at(element(g, T * q), 0, lane_at);
   C ph = at(twid, F::kPhaseOff, t);
   if (ws_mismatch(hdr, FC_PATH_RESAMPLE, n, r, d, dtype)) return;
   decltype(C::x) e = 0;
@@ -848,9 +862,11 @@ __global__ __launch_bounds__(G::T < 64 ? 64 : G::T, G::kWaves) void grid_filter_
   }
   asm volatile("" : "+v"(lane_at));                        // (the load addresses are not worth keeping)
 #pragma unroll
-  for (int q = 0; q < P; ++q)
-    *reinterpret_cast<float2*>(reinterpret_cast<char*>(g + T * q) + lane_at * (uint32_t)sizeof(float2)) =
-        make_float2(x[q].y, x[q].x);
+  for (int q = 0; q < P; ++q) {
+    typedef float V2 __attribute__((ext_vector_type(2)));
+    typedef __attribute__((address_space(1))) V2* Global;
+    *(Global)(reinterpret_cast<char*>(element(g, T * q)) + lane_at * (uint32_t)sizeof(float2)) = V2{x[q].y, x[q].x};
+  }
 
   double es = (double)e;
 #pragma unroll
