@@ -946,7 +946,8 @@ constexpr int kResWorkgroups = 512;   // residual kernel: two for each compute u
 // unit's slots; with few segments (split) a workgroup's waves take the parts of a unit side by side instead of one
 // after the other.  Rows are requested two tiles ahead and grid values one window ahead, across segments.
 // Neighbouring windows read the same lines of the grid: an XCD takes a contiguous range of windows and its
-// workgroups walk (units, window) side by side, window fastest, so that its L2 serves what they share.
+// workgroups walk (units, window) side by side, window fastest, so that its L2 serves what they share.  Launches with no
+// more than one segment for a wave (ONCE) ask for nothing ahead of a next one (one layer of 16384 tokens: 19.7 / 19.1 us).
 // Bound by the rows: 56 units of 32768 tokens, M = 3072: 248 us, 1.18 GB read for 0.94 GB of rows and 0.18 of grid, 4.8
 // TB/s, with the grid's loads as they first were.  112 units: 432 us with three of the five products and sums in 32 bits, 455 with sums as they are, 474 with all.
 // A lane holds slot lane & 15 throughout: columns 8 slot + j of tokens 4 (lane >> 4) + i, so that a load reads whole
@@ -955,7 +956,7 @@ constexpr int kResWorkgroups = 512;   // residual kernel: two for each compute u
 // banks): by the operands' lanes, 16 slots apart in memory, they took the address unit four times as long.  112 units, us
 // before / after: 32768 tokens M = 3072 460 / 448, M = 12288 729 / 683, 30011 tokens 526 / 507; one layer of 16384 21.5 / 18.0,
 // of which 1.6 for not loading a window after the last segment.
-template <typename T, bool KEEP>
+template <typename T, bool KEEP, bool ONCE>
 __global__ __launch_bounds__(256, 2) void residual_kernel(
     const T* __restrict__ K, const T* __restrict__ V, KvStrides st, int u0, int u1, int n, int r, int d, int dtype,
     int m, int tpw, int wins, SlotMap sm, bool split, WsHeader* hdr, const _Float16* __restrict__ winv,
@@ -1001,7 +1002,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
   auto following = [&](const Seg& s) {
     int it = item, pt = part + 1;
     if (pt == parts) { pt = 0; it += peers; }
-    follows = it < items;
+    follows = !ONCE && it < items;
     return follows ? segment(it, pt) : s;
   };
   f32x4 v[4][4];
@@ -1082,7 +1083,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
 #pragma unroll
     for (int j = 0; j < 8; ++j) asm volatile("" : "+v"(bh[j].u), "+v"(bl[j].u));
     hp = tot = 0.0;
-    if (follows) load_window(nxt);
+    if (!ONCE && follows) load_window(nxt);
   };
   // energies of the segment: Ehp_k, Ehp_v, Etot_k, Etot_v
   auto record = [&]() {
@@ -1108,7 +1109,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     }
     const bool last = tl + 1 == cur.tiles;
     if (!last) load_weights(cur, tl + 1);
-    else load_weights(nxt, 0);
+    else if (!ONCE) load_weights(nxt, 0);
     const int t0 = (cur.win * tpw + tl) * 16;
     const bool slot_used = cur.part * 16 + (lane & 15) < 2 * sm.nb;
     float h[4];
@@ -1130,7 +1131,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
       else if (token < n && tl < tpw) scores[(size_t)out_unit(um, cur.unit) * n + token] = (float)(sum * inv_d);
     }
     if (tl + kBuf < cur.tiles) load_rows(xb, cur, tl + kBuf);
-    else load_rows(xb, nxt, tl + kBuf - cur.tiles);
+    else if (!ONCE) load_rows(xb, nxt, tl + kBuf - cur.tiles);
     ++tl;
     if (last) {
       asm volatile("");                                    // (keeps what follows out of every tile's path)
@@ -1147,10 +1148,12 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
         __syncthreads();
       }
       if (++part == parts) { part = 0; item += peers; }
-      more = item < items;
-      cur = nxt;
-      nxt = following(cur);
-      tl = 0;
+      more = !ONCE && item < items;
+      if constexpr (!ONCE) {
+        cur = nxt;
+        nxt = following(cur);
+        tl = 0;
+      }
     }
   };
   while (more) {
@@ -1376,9 +1379,10 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
       const bool split = lay.wpu > 1 && per_xcd * ((u1 - u0 + 3) / 4) < kResWorkgroups / 8;
       const int abreast = split ? 4 / lay.wpu : 4;
       const int64_t items = per_xcd * ((u1 - u0 + abreast - 1) / abreast);
-      hipLaunchKernelGGL((residual_kernel<T, KEEP>), dim3(8 * (int)std::min<int64_t>(items, kResWorkgroups / 8)), dim3(256), 0,
-                         s, K, V, st, u0, u1, n, r, d.head_dim, d.dtype, m, lay.tpw, lay.wins, sm, split, hdr,
-                         reinterpret_cast<const _Float16*>(base + lay.winv),
+      const bool once = (split || lay.wpu == 1) && items <= kResWorkgroups / 8;   // one segment for each wave at most
+      auto kern = once ? residual_kernel<T, KEEP, true> : residual_kernel<T, KEEP, false>;
+      hipLaunchKernelGGL(kern, dim3(8 * (int)std::min<int64_t>(items, kResWorkgroups / 8)), dim3(256), 0, s, K, V, st, u0, u1, n, r,
+                         d.head_dim, d.dtype, m, lay.tpw, lay.wins, sm, split, hdr, reinterpret_cast<const _Float16*>(base + lay.winv),
                          grid, scores, epart, um);
     }
     e = hipGetLastError();
