@@ -7,7 +7,9 @@
 //   indices, which yields them ascending and gives ties to the lower index without any sort.  Up to
 //   65536 tokens the keys stay in registers between the passes; beyond that they are re-read from L2.
 //   Only integer atomics are used (LDS histogram), so the result is deterministic.
-// gather_kernel: one 16-byte vector per thread; rows are bit copies.
+// gather_kernel: rows are bit copies, 16 bytes a thread; one lookup a row.
+#include <algorithm>
+
 #include "fc_common.h"
 
 namespace fc {
@@ -315,56 +317,66 @@ struct PagedDst {
   long long num_pages;
 };
 
-// One thread copies one 16-byte vector of a K row and of the matching V row; blockIdx.y is the
-// sequence.  Rows are read once and written once, so both sides bypass the caches' retention
-// (non-temporal): the scores, budgets and indices the other lanes need stay resident instead.
+// A workgroup copies the `rows` kept rows from blockIdx.x * rows on (blockIdx.y is the sequence): a thread looks up where
+// one of them is and goes, then each copies a 16-byte vector of a K row and the matching one of V (more than one vector of a
+// long row).  Rows are read once and written once, so both sides bypass the caches' retention (non-temporal): the scores,
+// budgets and indices the other workgroups need stay resident instead.  Bound by memory: 112 units that keep 6554 rows
+// 128 us, 5.9 TB/s; with a lookup for each vector 152, with two, four or eight vectors of each tensor under way in a thread
+// 133, 137 and 140, with K and V in workgroups of their own 163.
 typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
+constexpr int kGatherThreads = 256;
 
 template <bool PAGED>
-__global__ __launch_bounds__(256) void gather_kernel(
+__global__ __launch_bounds__(kGatherThreads) void gather_kernel(
     const char* __restrict__ K, const char* __restrict__ V, KvStrides st, int n, int elem_bytes,
-    int vec_per_row, int vpr_shift, const int* __restrict__ budgets,
+    int vec_per_row, int vpr_shift, int rows, const int* __restrict__ budgets,
     const long long* __restrict__ layer_offsets, const int* __restrict__ idx, long long rows_per_seq,
     char* __restrict__ K_out, char* __restrict__ V_out, PagedDst pg) {
-  const int b = blockIdx.y;
-  const long long v = (long long)blockIdx.x * blockDim.x + threadIdx.x;     // vector within the sequence
-  const long long j = vpr_shift >= 0 ? (v >> vpr_shift) : v / vec_per_row;   // packed row of the sequence
-  const int part = (int)(vpr_shift >= 0 ? (v & (vec_per_row - 1)) : v % vec_per_row);
-  if (j >= rows_per_seq) return;
-  const long long* offs = layer_offsets + (size_t)b * (st.L + 1);
-  // largest l with offs[l] <= j
-  int lo = 0, hi = st.L;                                // invariant: offs[lo] <= j < offs[hi]
-  if (j >= offs[st.L]) return;                          // rows beyond what the budgets fill
-  while (hi - lo > 1) {
-    int mid = (lo + hi) >> 1;
-    if (offs[mid] <= j) lo = mid; else hi = mid;
-  }
-  const int l = lo;
-  const int k = budgets[(size_t)b * st.L + l];
-  if (k <= 0) return;
-  const long long in_layer = j - offs[l];                // < H * k
-  if (in_layer >= (long long)st.H * k) return;
-  const int h = (int)((unsigned)in_layer / (unsigned)k);
+  __shared__ long long from[kGatherThreads], to[kGatherThreads];
+  extern __shared__ long long offs[];                    // [L + 1]: the sequence's layer_offsets
+  const int b = blockIdx.y, tid = threadIdx.x;
+  const long long j = (long long)blockIdx.x * rows + tid;   // packed row of the sequence
+  const bool mine = tid < rows && j < rows_per_seq;
   const long long grow = (long long)b * rows_per_seq + j;
-  const int token = idx[grow];
-  if (token < 0 || token >= n) return;
-  const long long src = ((long long)b * st.sb + (long long)l * st.sl + (long long)h * st.sh +
-                         (long long)token * st.sn) * elem_bytes + (long long)part * 16;
-  long long dst_row = grow;
-  if (PAGED) {
-    const long long jj = in_layer - (long long)h * k;                // row within the unit
-    const long long slot_page = jj / pg.page_size;
-    if (slot_page >= pg.max_pages) return;
-    const long long unit = ((long long)b * st.L + l) * st.H + h;
-    const long long page = pg.block_table[unit * pg.max_pages + slot_page];
-    if (page < 0 || page >= pg.num_pages) return;                    // not a valid page: row skipped
-    dst_row = page * pg.page_size + jj % pg.page_size;
+  const int token = mine ? idx[grow] : -1;
+  for (int i = tid; i <= st.L; i += kGatherThreads) offs[i] = layer_offsets[(size_t)b * (st.L + 1) + i];
+  __syncthreads();
+  if (tid < rows) {
+    long long src = -1, dst = grow;
+    if (mine && token >= 0 && token < n && j < offs[st.L]) {   // (no rows beyond what the budgets fill)
+      // largest l with offs[l] <= j
+      int lo = 0, hi = st.L;                             // invariant: offs[lo] <= j < offs[hi]
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (offs[mid] <= j) lo = mid; else hi = mid;
+      }
+      const int l = lo, k = budgets[(size_t)b * st.L + l];
+      const long long in_layer = j - offs[l];            // < H * k
+      if (k > 0 && in_layer < (long long)st.H * k) {
+        const int h = (int)((unsigned)in_layer / (unsigned)k);
+        src = ((long long)b * st.sb + (long long)l * st.sl + (long long)h * st.sh + (long long)token * st.sn) * elem_bytes;
+        if (PAGED) {
+          const long long jj = in_layer - (long long)h * k;            // row within the unit
+          const long long slot_page = jj / pg.page_size;
+          const long long unit = ((long long)b * st.L + l) * st.H + h;
+          const long long page = slot_page < pg.max_pages ? pg.block_table[unit * pg.max_pages + slot_page] : -1;
+          if (page < 0 || page >= pg.num_pages) src = -1;              // not a valid page: row skipped
+          dst = page * pg.page_size + jj % pg.page_size;
+        }
+      }
+    }
+    from[tid] = src;
+    to[tid] = dst * vec_per_row * 16;
   }
-  const long long dst = dst_row * (long long)vec_per_row * 16 + (long long)part * 16;
-  const uint4v kv = __builtin_nontemporal_load(reinterpret_cast<const uint4v*>(K + src));
-  const uint4v vv = __builtin_nontemporal_load(reinterpret_cast<const uint4v*>(V + src));
-  __builtin_nontemporal_store(kv, reinterpret_cast<uint4v*>(K_out + dst));
-  __builtin_nontemporal_store(vv, reinterpret_cast<uint4v*>(V_out + dst));
+  __syncthreads();
+  for (int v = tid; v < rows * vec_per_row; v += kGatherThreads) {
+    const int r = vpr_shift >= 0 ? v >> vpr_shift : v / vec_per_row, part = (v - r * vec_per_row) * 16;
+    if (from[r] < 0) continue;
+    const uint4v kv = __builtin_nontemporal_load(reinterpret_cast<const uint4v*>(K + from[r] + part));
+    const uint4v vv = __builtin_nontemporal_load(reinterpret_cast<const uint4v*>(V + from[r] + part));
+    __builtin_nontemporal_store(kv, reinterpret_cast<uint4v*>(K_out + to[r] + part));
+    __builtin_nontemporal_store(vv, reinterpret_cast<uint4v*>(V_out + to[r] + part));
+  }
 }
 
 }  // namespace
@@ -414,8 +426,9 @@ hipError_t select_gather_launch(const void* K, const void* V, const fc_kv_desc& 
   if (e != hipSuccess) return e;
   const int elem_bytes = d.dtype == FC_BF16 ? 2 : 4;
   const int vec_per_row = d.head_dim * elem_bytes / 16;
-  const long long seq_vecs = (long long)rows_per_seq * vec_per_row;
-  const long long blocks = (seq_vecs + 255) / 256;
+  // rows of a workgroup: one turn of its threads' copies, if it has a thread for each of them
+  const int rows = std::min(kGatherThreads, std::max(1, kGatherThreads / vec_per_row));
+  const long long blocks = (rows_per_seq + rows - 1) / rows;
   if (blocks > 0x7FFFFFFFll || d.batch > 65535) return hipErrorInvalidValue;
   int vpr_shift = -1;
   if ((vec_per_row & (vec_per_row - 1)) == 0)
@@ -423,15 +436,16 @@ hipError_t select_gather_launch(const void* K, const void* V, const fc_kv_desc& 
   ProfileScope ps("gather_kernel", s);
   const PagedDst pg{block_table, page_size, max_pages, (long long)num_pages};
   const dim3 grid((unsigned)blocks, (unsigned)d.batch);
+  const size_t lds = (size_t)(d.layers + 1) * sizeof(long long);
   if (block_table)
-    hipLaunchKernelGGL(gather_kernel<true>, grid, dim3(256), 0, s, static_cast<const char*>(K),
+    hipLaunchKernelGGL(gather_kernel<true>, grid, dim3(kGatherThreads), lds, s, static_cast<const char*>(K),
                        static_cast<const char*>(V), strides_of(d), d.n_tokens, elem_bytes, vec_per_row,
-                       vpr_shift, budgets, offs, idx_out, (long long)rows_per_seq, static_cast<char*>(K_out),
+                       vpr_shift, rows, budgets, offs, idx_out, (long long)rows_per_seq, static_cast<char*>(K_out),
                        static_cast<char*>(V_out), pg);
   else
-    hipLaunchKernelGGL(gather_kernel<false>, grid, dim3(256), 0, s, static_cast<const char*>(K),
+    hipLaunchKernelGGL(gather_kernel<false>, grid, dim3(kGatherThreads), lds, s, static_cast<const char*>(K),
                        static_cast<const char*>(V), strides_of(d), d.n_tokens, elem_bytes, vec_per_row,
-                       vpr_shift, budgets, offs, idx_out, (long long)rows_per_seq, static_cast<char*>(K_out),
+                       vpr_shift, rows, budgets, offs, idx_out, (long long)rows_per_seq, static_cast<char*>(K_out),
                        static_cast<char*>(V_out), pg);
   return hipGetLastError();
 }
