@@ -167,6 +167,8 @@ __device__ __forceinline__ unsigned below_me(unsigned long long mask, unsigned a
   return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, add));
 }
 
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+
 template <bool SHARED, int NT, int MAXC>
 __global__ __launch_bounds__(NT) void select_kernel(
     const float* __restrict__ scores, const int* __restrict__ budgets,
@@ -190,21 +192,23 @@ __global__ __launch_bounds__(NT) void select_kernel(
   // tokens past n get key 0, which no score has but the NaN of all set bits; equal keys are kept lowest token first
   // and k <= n, so that the surplus tokens, which come last, are never among the kept
   uint32_t key[MAXC];
-  if (!SHARED && (n & 3) == 0 && (reinterpret_cast<uintptr_t>(s) & 15u) == 0) {
+  // (units of an odd number of tokens begin at any multiple of 4 bytes, which is all that a load of 16 needs; 30011 tokens,
+  // one by one / four at a time: 112 units 30.9 / 26.0 us, 28 layers shared by four heads 52.4 / 34.6)
 #pragma unroll
-    for (int j = 0; j < MAXC; j += 4) {
-      const int i = i0 + j * 64;
-      float4 f = make_float4(0.f, 0.f, 0.f, 0.f);
-      const bool in = i < n;
-      if (in) f = *reinterpret_cast<const float4*>(s + i);
-      key[j] = in ? order_key(f.x) : 0u; key[j + 1] = in ? order_key(f.y) : 0u;
-      key[j + 2] = in ? order_key(f.z) : 0u; key[j + 3] = in ? order_key(f.w) : 0u;
-    }
-  } else {
+  for (int j = 0; j < MAXC; j += 4) {
+    const int i = i0 + j * 64;
+    if (i + 4 <= n) {
+      float4u f = *reinterpret_cast<const float4u*>(s + i);
+      if (SHARED) {
+        for (int hh = 1; hh < H; ++hh) f += *reinterpret_cast<const float4u*>(s + (size_t)hh * n + i);
 #pragma unroll
-    for (int j = 0; j < MAXC; ++j) {
-      const int i = i0 + (j >> 2) * 256 + (j & 3);
-      key[j] = i < n ? order_key(score_at<SHARED>(s, i, n, H)) : 0u;
+        for (int e = 0; e < 4; ++e) f[e] = __fdiv_rn(f[e], (float)H);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) key[j + e] = order_key(f[e]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) key[j + e] = i + e < n ? order_key(score_at<SHARED>(s, i + e, n, H)) : 0u;
     }
   }
   if (k <= 0 || k > n || off < 0 || off + (long long)copies * k > rows_per_seq) return;   // bad budgets
