@@ -982,6 +982,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     int win, unit, part, tiles, n0;                        // n0: position of the window's first even grid point
     const T* rows;                                         // this lane's columns of token 4 g
     const float2* gp;                                      // the first column pair that this lane loads on the grid
+    float* score;                                          // of the unit's first token
   };
   auto segment = [&](int it, int pt) {
     Seg s;
@@ -994,6 +995,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     const int mine = s.part * 16 + (lane & 15), slot = mine < 2 * sm.nb ? mine : 0;
     const bool second = slot >= sm.nb;
     s.rows = (second ? V : K) + unit_offset(st, s.unit) + (slot - (second ? sm.nb : 0)) * 8 + (int64_t)(4 * g) * st.sn;
+    s.score = scores + (size_t)out_unit(um, s.unit) * n;
     const int loaded = s.part * 16 + (lane >> 2);
     s.gp = grid + ((size_t)(s.unit - u0) * 2 * sm.nb + (loaded < 2 * sm.nb ? loaded : 0)) * 4 * m + 2 * ((lane ^ (lane >> 3)) & 3);
     return s;
@@ -1013,16 +1015,23 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
       for (int c = 0; c < 4; ++c)
         v[jp][c] = *reinterpret_cast<const f32x4*>(s.gp + (size_t)jp * m + (c < 2 ? s.n0 + 8 * c : m - 32 - s.n0 + 8 * c));
   };
-  auto load_rows = [&](RowPiece<T> (&x)[4], const Seg& s, int tl) {
-    const int t = (s.win * tpw + tl) * 16;
-    if (t + 16 <= n) {
-      const T* p = s.rows + t * st.sn;
+  const T* ahead;                                          // this lane's columns of token 4 g of the next tile to load
+  int ahead_at;                                            // its first token
+  auto start_rows = [&](const Seg& s) {
+    ahead_at = s.win * tpw * 16;
+    ahead = s.rows + ahead_at * st.sn;
+  };
+  auto load_rows = [&](RowPiece<T> (&x)[4]) {
+    if (ahead_at + 16 <= n) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) x[i].template load<KEEP>(p + i * st.sn);
+      for (int i = 0; i < 4; ++i) x[i].template load<KEEP>(ahead + i * st.sn);
     } else {                                               // rows past the end repeat the last one
 #pragma unroll
-      for (int i = 0; i < 4; ++i) x[i].template load<KEEP>(s.rows + (int64_t)(min(t + 4 * g + i, n - 1) - 4 * g) * st.sn);
+      for (int i = 0; i < 4; ++i)
+        x[i].template load<KEEP>(ahead + (int64_t)(min(ahead_at + 4 * g + i, n - 1) - ahead_at - 4 * g) * st.sn);
     }
+    ahead += 16 * st.sn;
+    ahead_at += 16;
   };
   Frag wn[3];
   auto load_weights = [&](const Seg& s, int tl) {
@@ -1035,8 +1044,9 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
   RowPiece<T> x[kBuf][4];
   load_window(cur);
   load_weights(cur, 0);
+  start_rows(cur);
 #pragma unroll
-  for (int k = 0; k < kBuf; ++k) load_rows(x[k], cur, k);
+  for (int k = 0; k < kBuf; ++k) load_rows(x[k]);
   if (ws_mismatch(hdr, FC_PATH_RESAMPLE, n, r, d, dtype)) return;     // (while the above is on its way)
   Seg nxt = following(cur);
   int tl = 0;
@@ -1111,27 +1121,34 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     if (!last) load_weights(cur, tl + 1);
     else if (!ONCE) load_weights(nxt, 0);
     const int t0 = (cur.win * tpw + tl) * 16;
-    const bool slot_used = cur.part * 16 + (lane & 15) < 2 * sm.nb;
-    float h[4];
+    float h[4], t[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      float h1 = 0.f, t1 = 0.f;
-      residual8(xb[i], acc, i, inv, h1, t1);
-      // tokens past the end, tiles past the window's own (they are the next window's) and slots past the last
-      const uint32_t use = slot_used && t0 + 4 * g + i < n && tl < tpw ? ~0u : 0u;
-      h[i] = __uint_as_float(__float_as_uint(h1) & use);
-      tot += (double)__uint_as_float(__float_as_uint(t1) & use);
+      h[i] = t[i] = 0.f;
+      residual8(xb[i], acc, i, inv, h[i], t[i]);
     }
+    // tokens past the end, tiles past the window's own (they are the next window's) and slots past the last
+    if (t0 + 16 > n || tl >= tpw || cur.part * 16 + 16 > 2 * sm.nb) {
+      const bool slot_used = cur.part * 16 + (lane & 15) < 2 * sm.nb;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t use = slot_used && t0 + 4 * g + i < n && tl < tpw ? ~0u : 0u;
+        h[i] = __uint_as_float(__float_as_uint(h[i]) & use);
+        t[i] = __uint_as_float(__float_as_uint(t[i]) & use);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) tot += (double)t[i];
     hp += (double)((h[0] + h[1]) + (h[2] + h[3]));
     double sum = row_sums(h, lane);
     if ((lane & 15) < 4) {
       const int k = 4 * g + (lane & 3), token = t0 + k;
       if (part > 0) sum += part_sum[wave][16 * tl + k];
       if (split || part + 1 < parts) part_sum[wave][16 * tl + k] = sum;
-      else if (token < n && tl < tpw) scores[(size_t)out_unit(um, cur.unit) * n + token] = (float)(sum * inv_d);
+      else if (token < n && tl < tpw) cur.score[token] = (float)(sum * inv_d);
     }
-    if (tl + kBuf < cur.tiles) load_rows(xb, cur, tl + kBuf);
-    else if (!ONCE) load_rows(xb, nxt, tl + kBuf - cur.tiles);
+    if (!ONCE && tl + kBuf == cur.tiles) start_rows(nxt);
+    if (!ONCE || tl + kBuf < cur.tiles) load_rows(xb);
     ++tl;
     if (last) {
       asm volatile("");                                    // (keeps what follows out of every tile's path)
@@ -1143,7 +1160,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
             const int token = cur.win * tpw * 16 + k;
             double s = part_sum[wave][k];
             for (int p = 1; p < sm.wpu; ++p) s += part_sum[wave + p][k];
-            if (token < n && k < 16 * tpw) scores[(size_t)out_unit(um, cur.unit) * n + token] = (float)(s * inv_d);
+            if (token < n && k < 16 * tpw) cur.score[token] = (float)(s * inv_d);
           }
         __syncthreads();
       }
