@@ -27,6 +27,9 @@ namespace fc {
 
 namespace {
 
+template <int V>
+using Int = std::integral_constant<int, V>;
+
 constexpr int kMaxTilesPerWin = 16;    // 16-token tiles one wave of the residual kernel walks
 constexpr float kInvWeightScale = 4096.0f;   // fp16 weights are stored times 2^12 (their tails stay normal numbers)
 
@@ -174,7 +177,33 @@ __host__ __device__ constexpr int twid_off(int m, bool wide, int k) {
   return off;
 }
 __host__ __device__ constexpr int twid_phase_off(int m, bool wide) { return twid_off(m, wide, 4); }
-__host__ __device__ constexpr int twid_size(int m, bool wide) { return twid_phase_off(m, wide) + grid_threads(m, wide); }
+// ... then e^{-2 pi i k / P} and e^{-pi i k / P}, k < P, which the transform's own code holds as constants
+__host__ __device__ constexpr int twid_root_off(int m, bool wide) { return twid_phase_off(m, wide) + grid_threads(m, wide); }
+__host__ __device__ constexpr int twid_size(int m, bool wide) { return twid_root_off(m, wide) + 2 * grid_radices(m, wide).p; }
+
+// cos(2 pi k / 192) of the first quadrant; every constant root the transforms use is on this circle
+__device__ constexpr double kCos192[49] = {
+    1.0, 0.9994645874763657, 0.9978589232386035, 0.9951847266721969, 0.9914448613738104, 0.986643332084879,
+    0.9807852804032304, 0.9738769792773336, 0.9659258262890683, 0.9569403357322088, 0.9469301294951057,
+    0.9359059267573258, 0.9238795325112867, 0.9108638249211758, 0.8968727415326884, 0.881921264348355,
+    0.8660254037844387, 0.8492021815265789, 0.8314696123025452, 0.8128466845916152, 0.7933533402912352,
+    0.773010453362737, 0.7518398074789774, 0.7298640726978357, 0.7071067811865476, 0.6835923020228712,
+    0.6593458151000688, 0.6343932841636455, 0.6087614290087207, 0.5824776968678022, 0.5555702330196024,
+    0.5280678506503681, 0.5, 0.4713967368259976, 0.44228869021900125, 0.4127070298043947, 0.38268343236508984,
+    0.3522500479212336, 0.3214394653031617, 0.2902846772544625, 0.25881904510252074, 0.22707626303437345,
+    0.19509032201612833, 0.16289547339458882, 0.1305261922200517, 0.09801714032956055, 0.06540312923014327,
+    0.032719082821776165, 0.0};
+__device__ constexpr double cos192(int k) {
+  k %= 192;
+  if (k > 96) k = 192 - k;
+  return k <= 48 ? kCos192[k] : -kCos192[96 - k];
+}
+// e^{-2 pi i k / n}, n a divisor of 192
+template <typename C>
+__device__ __forceinline__ constexpr C root(int k, int n) {
+  typedef decltype(C::x) R;
+  return C{(R)cos192(k * (192 / n)), (R)cos192(k * (192 / n) + 48)};
+}
 
 __device__ double2 unit_root(double frac) {       // e^{-2 pi i frac}
   double s, c;
@@ -239,7 +268,10 @@ __global__ __launch_bounds__(256) void resample_table_kernel(TablePtrs tp, int n
   id -= m;
   if (id >= twid_size(m, wide)) return;
   double2 v;
-  if (id >= twid_phase_off(m, wide)) {
+  if (id >= twid_root_off(m, wide)) {
+    const int k = id - twid_root_off(m, wide), p = grid_radices(m, wide).p;
+    v = k < p ? root<double2>(k, p) : root<double2>(k - p, 2 * p);
+  } else if (id >= twid_phase_off(m, wide)) {
     v = unit_root(-0.5 * (double)(id - twid_phase_off(m, wide)) / (double)m);
   } else {
     const GridRadices gr = grid_radices(m, wide);
@@ -487,30 +519,6 @@ __device__ __forceinline__ C csub(C a, C b) { return cpair<C>(a.x - b.x, a.y - b
 template <typename C>
 __device__ __forceinline__ C cmul(C a, C w) {
   return cpair<C>(mad(a.x, w.x, -a.y * w.y), mad(a.y, w.x, a.x * w.y));
-}
-
-// cos(2 pi k / 192) of the first quadrant; every constant root the transforms use is on this circle
-__device__ constexpr double kCos192[49] = {
-    1.0, 0.9994645874763657, 0.9978589232386035, 0.9951847266721969, 0.9914448613738104, 0.986643332084879,
-    0.9807852804032304, 0.9738769792773336, 0.9659258262890683, 0.9569403357322088, 0.9469301294951057,
-    0.9359059267573258, 0.9238795325112867, 0.9108638249211758, 0.8968727415326884, 0.881921264348355,
-    0.8660254037844387, 0.8492021815265789, 0.8314696123025452, 0.8128466845916152, 0.7933533402912352,
-    0.773010453362737, 0.7518398074789774, 0.7298640726978357, 0.7071067811865476, 0.6835923020228712,
-    0.6593458151000688, 0.6343932841636455, 0.6087614290087207, 0.5824776968678022, 0.5555702330196024,
-    0.5280678506503681, 0.5, 0.4713967368259976, 0.44228869021900125, 0.4127070298043947, 0.38268343236508984,
-    0.3522500479212336, 0.3214394653031617, 0.2902846772544625, 0.25881904510252074, 0.22707626303437345,
-    0.19509032201612833, 0.16289547339458882, 0.1305261922200517, 0.09801714032956055, 0.06540312923014327,
-    0.032719082821776165, 0.0};
-__device__ constexpr double cos192(int k) {
-  k %= 192;
-  if (k > 96) k = 192 - k;
-  return k <= 48 ? kCos192[k] : -kCos192[96 - k];
-}
-// e^{-2 pi i k / n}, n a divisor of 192
-template <typename C>
-__device__ __forceinline__ constexpr C root(int k, int n) {
-  typedef decltype(C::x) R;
-  return C{(R)cos192(k * (192 / n)), (R)cos192(k * (192 / n) + 48)};
 }
 
 // What 32 bits leave of a constant, for products that take both parts.  A constant's error is the same in every
@@ -884,6 +892,148 @@ __global__ __launch_bounds__(G::T < 64 ? 64 : G::T, G::kWaves) void grid_filter_
   }
 }
 
+// The same transform (in 32 bits) spread over one thread for each butterfly of its widest pass, every pass through LDS.
+// Points meet the same factors in the same order as in grid_filter_kernel, so that results are the same bits (the kept
+// energy's sum aside).  It takes more instructions in all, and is for launches that leave half of the chip or more without a
+// wave, whose time is that of one wave's instructions one after the other: up to 512 column pairs of transforms with 24
+// points a thread and more.  Before / after, us with events (an empty launch: 6): 512 pairs of 3072 points 21.8 / 17.6, of
+// 384 10.6 / 7.3, 256 of 96 8.2 / 6.8, of 4096 16.8 / 14.7; 1024 pairs of 3072 26.6 / 27.9, of 768 11.9 / 12.0, 2048 of 768
+// 15.0 / 17.0; 256 of 2048, which have 16 points a thread, 11.1 / 12.2; 512 of 6144 26.3 / 41.6.
+template <int M>
+struct SpreadPlan {
+  using G = GridPlan<M, false>;
+  static constexpr bool kUse = G::P >= 24 && M <= 4096;
+  static constexpr int kMostPairs = 512;
+  static constexpr int least(int a, int b) { return a < b ? a : b; }
+  static constexpr int kRadix = least(least(G::R0, G::R1), least(G::R2 > 1 ? G::R2 : M, G::R3 > 1 ? G::R3 : M));
+  static constexpr int NT = (M / kRadix + 63) / 64 * 64;
+};
+template <int M, typename G = GridPlan<M, false>, typename F = GridFft<M, false>>
+__global__ __launch_bounds__(SpreadPlan<M>::NT) void grid_spread_kernel(
+    float2* __restrict__ grid, int n, int r, int d, int dtype, WsHeader* hdr, const float2* __restrict__ filt,
+    const float2* __restrict__ twid, double* __restrict__ elow) {
+  using C = float2;
+  constexpr int P = G::P, T = G::T, NT = SpreadPlan<M>::NT;
+  constexpr int kRoots = twid_root_off(M, false), kPhases = twid_phase_off(M, false);
+  static_assert(NT % T == 0, "a thread's bins share a phase");
+  extern __shared__ float lds_all[];
+  __shared__ double wsum[NT / 64];
+  float *re = lds_all, *im = lds_all + G::kLds;
+  const int tid = threadIdx.x;
+  float2* g = grid + (size_t)blockIdx.x * M;
+  // what the tables give, requested at once with the points
+  constexpr int N1 = G::R0, N2 = N1 * G::R1, N3 = N2 * G::R2;
+  constexpr int kPasses = G::R3 > 1 ? 4 : (G::R2 > 1 ? 3 : 2), RL = kPasses == 4 ? G::R3 : (kPasses == 3 ? G::R2 : G::R1);
+  constexpr bool kTurns = T < M / RL;                      // butterflies of the last pass share T threads' factors
+  typename F::template Factors<G::R0, 1> f0;
+  typename F::template Factors<G::R1, N1> f1;
+  typename F::template Factors<(kPasses > 2 ? G::R2 : 2), (kPasses > 2 ? N2 : 1)> f2;
+  typename F::template Factors<(kPasses > 3 ? G::R3 : 2), (kPasses > 3 ? N3 : 1)> f3;
+  const int t = tid & (T - 1);
+  float2 x0[G::R0];
+#pragma unroll
+  for (int q = 0; q < G::R0; ++q)
+    if (M / G::R0 >= NT || tid < M / G::R0) x0[q] = g[tid + M / G::R0 * q];
+  f1.load(twid, kPasses == 2 ? t : tid);
+  if constexpr (kPasses > 2) f2.load(twid + F::kOff2, kPasses == 3 ? t : tid);
+  if constexpr (kPasses > 3) f3.load(twid + F::kOff3, t);
+  C turn_by[kTurns ? RL : 1];
+  if constexpr (kTurns)
+#pragma unroll
+    for (int q = 1; q < RL; ++q) turn_by[q] = twid[kRoots + (tid / T) * q % P];
+  constexpr int kBins = (M + NT - 1) / NT;
+  float2 fq[kBins];
+  C phase[kBins];
+  const C ph = twid[kPhases + t];
+#pragma unroll
+  for (int k = 0; k < kBins; ++k) {
+    const int m = min(tid + NT * k, M - 1);
+    fq[k] = filt[m];
+    phase[k] = twid[kRoots + P + m / T];
+  }
+  // butterfly tid of a pass of radix R after NS-point transforms: from registers (x) or LDS to LDS or the grid (STORE)
+  auto pass = [&](auto radix, auto done, auto first, auto store, const auto& f) {
+    constexpr int R = decltype(radix)::value, NS = decltype(done)::value, B = M / R;
+    constexpr bool kLast = R * NS == M;
+    const bool mine = B >= NT || tid < B;
+    C v[R];
+    if (mine)
+#pragma unroll
+      for (int q = 0; q < R; ++q) {
+        const int at = F::pad(tid + B * q);
+        if constexpr (first) v[q] = cpair<C>(x0[q].x, x0[q].y);
+        else v[q] = cpair<C>(re[at], im[at]);
+      }
+    if (!first) __syncthreads();
+    if (mine) {
+      if constexpr (NS > 1) {
+#pragma unroll
+        for (int q = 1; q < R; ++q) {
+          C w = f.get(q);
+          if constexpr (kLast && kTurns) w = cmul(w, turn_by[q]);
+          v[q] = cmul(v[q], w);
+        }
+      }
+      dft<R>(v);
+#pragma unroll
+      for (int q = 0; q < R; ++q) {
+        const int at = kLast ? tid + B * q : tid / NS * (NS * R) + (tid & (NS - 1)) + q * NS;
+        const float2 x = make_float2((float)v[q].x, (float)v[q].y);
+        if (store) g[at] = make_float2(x.y, x.x);
+        else { re[F::pad(at)] = x.x; im[F::pad(at)] = x.y; }
+      }
+    }
+    if (!store) __syncthreads();
+  };
+  auto transform = [&](auto first, auto store) {
+    std::false_type no;
+    pass(Int<G::R0>{}, Int<1>{}, first, no, f0);
+    if constexpr (kPasses == 2) pass(Int<G::R1>{}, Int<N1>{}, no, store, f1);
+    else {
+      pass(Int<G::R1>{}, Int<N1>{}, no, no, f1);
+      if constexpr (kPasses == 3) pass(Int<G::R2>{}, Int<N2>{}, no, store, f2);
+      else {
+        pass(Int<G::R2>{}, Int<N2>{}, no, no, f2);
+        pass(Int<G::R3>{}, Int<N3>{}, no, store, f3);
+      }
+    }
+  };
+  if (ws_mismatch(hdr, FC_PATH_RESAMPLE, n, r, d, dtype)) return;
+  transform(std::true_type{}, std::false_type{});
+  decltype(C::x) e = 0;
+  C y[kBins];
+#pragma unroll
+  for (int k = 0; k < kBins; ++k) {
+    const int m = tid + NT * k;
+    if (M % NT == 0 || m < M) {
+      const int o = m ? M - m : 0;
+      const C w = cpair<C>(re[F::pad(m)], im[F::pad(m)]), mirror = cpair<C>(re[F::pad(o)], im[F::pad(o)]);
+      const C f = cpair<C>(fq[k].x, fq[k].y), z = cmul(mirror, cmul(ph, cpair<C>(phase[k].x, -phase[k].y)));
+      y[k] = cpair<C>(mad(f.y, z.x, f.x * w.x), mad(f.y, z.y, f.x * w.y));
+      e = mad(w.x, y[k].x, mad(w.y, y[k].y, e));
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kBins; ++k) {
+    const int m = tid + NT * k;
+    if (M % NT == 0 || m < M) { re[F::pad(m)] = (float)y[k].y; im[F::pad(m)] = (float)y[k].x; }
+  }
+  __syncthreads();
+  transform(std::false_type{}, std::true_type{});
+
+  double es = (double)e;
+#pragma unroll
+  for (int s = 1; s < 64; s <<= 1) es += __shfl_xor(es, s, 64);
+  if ((tid & 63) == 0) wsum[tid >> 6] = es;
+  __syncthreads();
+  if (tid == 0) {
+    double a = 0.0;
+    for (int k = 0; k < NT / 64; ++k) a += wsum[k];
+    elow[blockIdx.x] = a;
+  }
+}
+
 // ---------------------------------------------------------------------------- residual and score
 
 // squares of (row - inv * base) and of the row, 8 columns of token i of the tile
@@ -1203,6 +1353,17 @@ hipError_t launch_filter(float2* grid, int pairs, int n, int r, int d, int dtype
     if (e != hipSuccess) return e;
   }
   ProfileScope ps("grid_filter_kernel", s);
+  if constexpr (!WIDE && SpreadPlan<M>::kUse) {
+    if (pairs <= SpreadPlan<M>::kMostPairs) {
+      auto spread = grid_spread_kernel<M>;
+      constexpr int kThreads = SpreadPlan<M>::NT;
+      constexpr size_t kBytes = 2 * GridPlan<M, WIDE>::kLds * sizeof(float);
+      static_assert(kBytes <= 64 * 1024, "a kernel's dynamic LDS without asking for more");
+      hipLaunchKernelGGL(spread, dim3(pairs), dim3(kThreads), kBytes, s, grid, n, r, d, dtype, hdr, filt,
+                         static_cast<const float2*>(twid), elow);
+      return hipGetLastError();
+    }
+  }
   hipLaunchKernelGGL(kern, dim3((pairs + PB - 1) / PB), dim3(T < 64 ? 64 : T), lds, s, grid, pairs, n, r, d, dtype,
                      hdr, filt, static_cast<const typename GridFft<M, WIDE>::C*>(twid), elow);
   return hipGetLastError();

@@ -366,3 +366,24 @@ def test_decode_cuts_every_unit_by_its_own_budget(dtype, most):
     want = ref.decode_attention(Q[0], K[0], V[0], dtype, budgets, H, scale)
     err = np.abs(out.cpu().numpy()[0] - want).max()
     assert err <= 5e-5 * float(np.abs(ref.widen(V, dtype)).max())
+
+
+# A launch of up to 512 column pairs spreads each grid transform over more threads (lengths 96 to 1536 with a factor of 3,
+# 3072 and 4096); the layers' units together make more than that
+@pytest.mark.parametrize("n,r,dtype", [(512, 52, "f32"), (1023, 109, "bf16"), (2048, 210, "bf16"), (4099, 410, "bf16"), (8191, 820, "bf16"),
+                                       (16384, 1639, "bf16"), (20001, 2300, "bf16")])
+def test_scores_of_small_launches_are_the_same_bits(n, r, dtype):
+    import paper_2511_16786_amd as fc
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    L, H, d = 5, 1, 128
+    K, V = (torch.randn((1, L, H, n, d), generator=gen, device="cuda").to(torch.float32 if dtype == "f32" else torch.bfloat16)
+            for _ in range(2))
+    all_at_once = fc.Compressor(K, r, fc.total_budget(L, n, 0.2))
+    all_at_once.run_score(K, V)
+    one = fc.Compressor(K[:, :1], r, fc.total_budget(1, n, 0.2))
+    for _ in range(2):                                           # (nothing is left behind for the next call)
+        for l in range(L):
+            one.run_score(K[:, l:l + 1], V[:, l:l + 1])
+            assert torch.equal(one.scores[:, 0], all_at_once.scores[:, l])
+            assert torch.equal(one.energy[:, 0], all_at_once.energy[:, l])
+    assert fc.workspace_error(one.workspace) == 0
