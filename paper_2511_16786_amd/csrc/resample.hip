@@ -211,12 +211,38 @@ __device__ double2 unit_root(double frac) {       // e^{-2 pi i frac}
   return make_double2(c, -s);
 }
 
+// What the table kernel has to know of a plan's twiddle factors, made on the host: looked up on the device, the radices
+// are an array under a running index, for which all of the kernel's threads had scratch memory and 20 KiB of LDS: 11.7 us
+// instead of 7.6 at 7321 tokens.
+struct TwidPlan {
+  int off[4];                                      // factors of passes 1, 2 and 3 (a pass that is none: empty), phases
+  int stride[3], low[3], len[3];
+  int p, roots, size;
+};
+TwidPlan make_twid_plan(int m, bool wide) {
+  const GridRadices g = grid_radices(m, wide);
+  TwidPlan t{};
+  int ns = g.r[0];
+  for (int k = 1; k < 4; ++k) {
+    const int len = ns * g.r[k];
+    t.off[k - 1] = twid_off(m, wide, k);
+    t.stride[k - 1] = len == m ? m / g.p : ns;
+    t.low[k - 1] = std::min(g.r[k], 8) - 1;
+    t.len[k - 1] = len;
+    ns = len;
+  }
+  t.off[3] = twid_phase_off(m, wide);
+  t.p = g.p; t.roots = twid_root_off(m, wide); t.size = twid_size(m, wide);
+  return t;
+}
+
 // One thread per weight and per table entry; runs once per plan, and a prompt of a new length waits for it.  The
 // weights' series are the work: as fused multiply-adds with constant factors, one weight a thread and the window's
 // own constants from the host, 12 us at 7321 tokens where a thread of eight weights, each with a division per term,
-// took 52 us.
+// took 52 us; 7.6 us since the twiddle factors' radices come from the host as well.
 __global__ __launch_bounds__(256) void resample_table_kernel(TablePtrs tp, int n, int r, int m, int d, int dtype,
-                                                             int steps, int tpw, int n_wfwd, int n_winv, bool wide, Window win) {
+                                                             int steps, int tpw, int n_wfwd, int n_winv, bool wide, Window win,
+                                                             TwidPlan plan) {
   int id = blockIdx.x * blockDim.x + threadIdx.x;
   const double dd = (double)n / (double)m;        // tokens per grid point
   const double inv_dd = (double)m / (double)n;
@@ -266,20 +292,25 @@ __global__ __launch_bounds__(256) void resample_table_kernel(TablePtrs tp, int n
     return;
   }
   id -= m;
-  if (id >= twid_size(m, wide)) return;
+  if (id >= plan.size) return;
   double2 v;
-  if (id >= twid_root_off(m, wide)) {
-    const int k = id - twid_root_off(m, wide), p = grid_radices(m, wide).p;
-    v = k < p ? root<double2>(k, p) : root<double2>(k - p, 2 * p);
-  } else if (id >= twid_phase_off(m, wide)) {
-    v = unit_root(-0.5 * (double)(id - twid_phase_off(m, wide)) / (double)m);
+  if (id >= plan.roots) {
+    const int k = id - plan.roots;
+    v = k < plan.p ? root<double2>(k, plan.p) : root<double2>(k - plan.p, 2 * plan.p);
   } else {
-    const GridRadices gr = grid_radices(m, wide);
-    int k = 1, ns = gr.r[0];
-    while (id >= twid_off(m, wide, k + 1)) ns *= gr.r[k++];
-    const int stride = ns * gr.r[k] == m ? grid_threads(m, wide) : ns, j = id - twid_off(m, wide, k), slot = j / stride;
-    const int low = (gr.r[k] < 8 ? gr.r[k] : 8) - 1, power = slot < low ? slot + 1 : 8 * (slot - low + 1);
-    v = unit_root((double)(power * (j % stride)) / (double)(ns * gr.r[k]));
+    double frac = 0.5 * (double)(id - plan.off[3]) / (double)m;
+    if (id >= plan.off[3]) {
+      frac = -frac;
+    } else {
+      const int k = id >= plan.off[2] ? 2 : (id >= plan.off[1] ? 1 : 0);
+      const int off = k == 2 ? plan.off[2] : (k == 1 ? plan.off[1] : plan.off[0]);
+      const int stride = k == 2 ? plan.stride[2] : (k == 1 ? plan.stride[1] : plan.stride[0]);
+      const int low = k == 2 ? plan.low[2] : (k == 1 ? plan.low[1] : plan.low[0]);
+      const int len = k == 2 ? plan.len[2] : (k == 1 ? plan.len[1] : plan.len[0]);
+      const int j = id - off, slot = j / stride, power = slot < low ? slot + 1 : 8 * (slot - low + 1);
+      frac = (double)(power * (j - slot * stride)) / (double)len;
+    }
+    v = unit_root(frac);
   }
   if (wide) static_cast<double2*>(tp.twid)[id] = v;
   else static_cast<float2*>(tp.twid)[id] = make_float2((float)v.x, (float)v.y);
@@ -1475,11 +1506,12 @@ hipError_t resample_prepare(const fc_kv_desc& d, int32_t r, const ResampleLayout
   TablePtrs tp{reinterpret_cast<WsHeader*>(base), reinterpret_cast<float*>(base + lay.wfwd),
                reinterpret_cast<_Float16*>(base + lay.winv), reinterpret_cast<float2*>(base + lay.filt), base + lay.twid};
   const int n_wfwd = lay.m / 16 * lay.steps * 512, n_winv = lay.wins * lay.tpw * 512;
-  const int total = n_wfwd + n_winv + lay.m + twid_size(lay.m, lay.wide);
+  const TwidPlan plan = make_twid_plan(lay.m, lay.wide);
+  const int total = n_wfwd + n_winv + lay.m + plan.size;
   ProfileScope ps("resample_table_kernel", s);
   hipLaunchKernelGGL(resample_table_kernel, dim3((total + 255) / 256), dim3(256), 0, s, tp, d.n_tokens, r, lay.m,
                      d.head_dim, d.dtype, lay.steps, lay.tpw, n_wfwd, n_winv, lay.wide,
-                     make_window(r, lay.m));
+                     make_window(r, lay.m), plan);
   return hipGetLastError();
 }
 
