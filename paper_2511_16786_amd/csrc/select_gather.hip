@@ -137,8 +137,10 @@ __global__ __launch_bounds__(kSelThreads) void select_large_kernel(
 // 2048 equal bins between the lowest and the highest key in question, counted in LDS, take a range of any width
 // to a single key in three passes, usually in two (the search ends when a bin is kept whole); bins of equal width
 // between the extremes spread the keys over many counters, where digits of the key put nearly all of them on a few.
-// Latency-bound: one workgroup per unit, a barrier per step (32768 tokens, 112 units: 35 -> 26 us; 4096 tokens:
-// 24 -> 8.4; 512 tokens: 22 -> 4.5 against four passes of 8-bit digits, which ran over 32 keys whatever n was).
+// One workgroup per unit, a barrier per step: bound by latency and by how fast one CU's SIMDs issue the work on its keys
+// (32768 tokens, 112 units: 19.7 us; 8192: 9.1; 4 units of 512: 7.1, 6 of them an empty launch).  Kept tokens are gathered
+// in LDS and written as whole lines: stored from where they were found, with the loads one after another, it took 26.3 and
+// 11.1 us (16384 tokens, 896 units: 52.4 / 26.5; 60000, 80 units: 62.6 / 29.4).
 constexpr int kSelMaxChunk = 64;
 constexpr int kSelBins = 2048;
 
@@ -167,6 +169,9 @@ __device__ __forceinline__ unsigned below_me(unsigned long long mask, unsigned a
   return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, add));
 }
 
+// a value that all lanes of the wave hold, in a scalar register
+__device__ __forceinline__ unsigned uniform(unsigned v) { return (unsigned)__builtin_amdgcn_readfirstlane((int)v); }
+
 typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
 
 template <bool SHARED, int NT, int MAXC>
@@ -175,7 +180,9 @@ __global__ __launch_bounds__(NT) void select_kernel(
     const long long* __restrict__ layer_offsets, int L, int H, int n, long long rows_per_seq,
     int* __restrict__ idx_out) {
   constexpr int kWaves = NT / 64, kPer = kSelBins / NT;
-  __shared__ unsigned hist[kSelBins];
+  __shared__ union { unsigned hist[kSelBins]; unsigned short stage[NT * MAXC]; } lds;
+  unsigned* const hist = lds.hist;
+  unsigned short* const stage = lds.stage;
   __shared__ unsigned wave_a[kWaves], wave_b[kWaves];
   __shared__ unsigned sh_bin, sh_need, sh_count;
 
@@ -186,29 +193,52 @@ __global__ __launch_bounds__(NT) void select_kernel(
   const int copies = SHARED ? H : 1;
   const long long off = layer_offsets[(size_t)b * (L + 1) + l] + (long long)h * k;
   const float* s = scores + (size_t)unit * n;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
   const int i0 = wave * 64 * MAXC + lane * 4;
 
   // tokens past n get key 0, which no score has but the NaN of all set bits; equal keys are kept lowest token first
   // and k <= n, so that the surplus tokens, which come last, are never among the kept
   uint32_t key[MAXC];
-  // (units of an odd number of tokens begin at any multiple of 4 bytes, which is all that a load of 16 needs; 30011 tokens,
-  // one by one / four at a time: 112 units 30.9 / 26.0 us, 28 layers shared by four heads 52.4 / 34.6)
+  // All loads are under way before the first is looked at.  Lanes whose four tokens are not all there load the unit's last
+  // four and move them down.  (Units of an odd number of tokens begin at any multiple of 4 bytes, which is all that a load
+  // of 16 needs.)
+  constexpr int kAhead = SHARED && MAXC > 16 ? 16 : MAXC;
 #pragma unroll
-  for (int j = 0; j < MAXC; j += 4) {
-    const int i = i0 + j * 64;
-    if (i + 4 <= n) {
-      float4u f = *reinterpret_cast<const float4u*>(s + i);
+  for (int j0 = 0; j0 < MAXC; j0 += kAhead) {
+    float4u f[kAhead / 4];
+    if (n >= 4) {
+#pragma unroll
+      for (int q = 0; q < kAhead / 4; ++q)
+        f[q] = *reinterpret_cast<const float4u*>(s + min(i0 + (j0 + 4 * q) * 64, n - 4));
       if (SHARED) {
-        for (int hh = 1; hh < H; ++hh) f += *reinterpret_cast<const float4u*>(s + (size_t)hh * n + i);
+        for (int hh = 1; hh < H; ++hh) {
+          const float* sh = s + (size_t)hh * n;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) f[e] = __fdiv_rn(f[e], (float)H);
+          for (int q = 0; q < kAhead / 4; ++q)
+            f[q] += *reinterpret_cast<const float4u*>(sh + min(i0 + (j0 + 4 * q) * 64, n - 4));
+        }
+#pragma unroll
+        for (int q = 0; q < kAhead / 4; ++q)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) f[q][e] = __fdiv_rn(f[q][e], (float)H);
       }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) key[j + e] = order_key(f[e]);
     } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) key[j + e] = i + e < n ? order_key(score_at<SHARED>(s, i + e, n, H)) : 0u;
+      for (int e = 0; e < 4; ++e) f[0][e] = score_at<SHARED>(s, max(n - 4 + e, 0), n, H);
+#pragma unroll
+      for (int q = 1; q < kAhead / 4; ++q) f[q] = f[0];
+    }
+#pragma unroll
+    for (int q = 0; q < kAhead / 4; ++q) {
+      uint32_t* g = key + j0 + 4 * q;
+      const int past = i0 + (j0 + 4 * q) * 64 + 4 - n;     // tokens of the four that are past the last
+#pragma unroll
+      for (int e = 0; e < 4; ++e) g[e] = order_key(f[q][e]);
+      if (past > 0) {
+        if (past & 1) { g[0] = g[1]; g[1] = g[2]; g[2] = g[3]; g[3] = 0u; }
+        if (past & 2) { g[0] = g[2]; g[1] = g[3]; g[2] = g[3] = 0u; }
+        if (past > 3) { g[0] = g[1] = g[2] = g[3] = 0u; }
+      }
     }
   }
   if (k <= 0 || k > n || off < 0 || off + (long long)copies * k > rows_per_seq) return;   // bad budgets
@@ -229,6 +259,8 @@ __global__ __launch_bounds__(NT) void select_kernel(
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) { lo = min(lo, wave_a[w]); hi = max(hi, wave_b[w]); }
+  lo = uniform(lo);
+  hi = uniform(hi);
 
   // the k-th largest key is the need-th largest of the keys in [lo, hi]; `whole`: all of [lo, hi] is kept
   unsigned need = (unsigned)k;
@@ -267,49 +299,71 @@ __global__ __launch_bounds__(NT) void select_kernel(
       }
     }
     __syncthreads();
-    lo += sh_bin << shift;
+    lo += uniform(sh_bin) << shift;
     hi = min(hi, lo + ((1u << shift) - 1u));
-    need = sh_need;
-    if (sh_count == need) { whole = true; break; }
+    need = uniform(sh_need);
+    if (uniform(sh_count) == need) { whole = true; break; }
   }
-  const uint32_t tau = lo;
-  // kept: keys above tau, and of those equal to it the `need` with the lowest token indices (keys >= tau, if `whole`)
-  uint32_t count_gt = 0, count_eq = 0;         // of this wave
+  // kept: all keys from tau upwards
+  uint32_t tau = lo;
+  __syncthreads();                              // (wave_a and wave_b are still being read above)
+  if (!whole) {
+    // of the keys equal to tau only the `need` with the lowest token indices: keys are marked as kept or not
+    uint32_t equal = 0;                         // of this wave
 #pragma unroll
-  for (int j = 0; j < MAXC; ++j) {
-    count_gt += __popcll(__ballot(whole ? key[j] >= tau : key[j] > tau));
-    if (!whole) count_eq += __popcll(__ballot(key[j] == tau));
-  }
-  __syncthreads();                              // (wave_a is still being read above)
-  if (lane == 0) { wave_a[wave] = count_gt; wave_b[wave] = count_eq; }
-  __syncthreads();
-  unsigned pg = 0, pe = 0;                      // kept by lower waves: above tau; equal to it (capped later)
-  for (int w = 0; w < wave; ++w) { pg += wave_a[w]; pe += wave_b[w]; }
+    for (int j = 0; j < MAXC; ++j) equal += __popcll(__ballot(key[j] == tau));
+    if (lane == 0) wave_b[wave] = equal;
+    __syncthreads();
+    unsigned before = 0;
+    for (int w = 0; w < wave; ++w) before += wave_b[w];
+    before = uniform(before);
 #pragma unroll
-  for (int j = 0; j < MAXC; j += 4) {
-    const int i = i0 + j * 64;
-    unsigned long long mg[4], me[4] = {0, 0, 0, 0};
-    unsigned my_g = pg, my_e = pe;              // before this lane's first token of the group
+    for (int j = 0; j < MAXC; j += 4) {
+      asm volatile("" : "+s"(tau));             // (or all groups' masks are made at once, in registers a second workgroup needs)
+      unsigned mine = before;                   // before this lane's first token of the group
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      mg[e] = __ballot(whole ? key[j + e] >= tau : key[j + e] > tau);
-      my_g = below_me(mg[e], my_g);
-      if (!whole) {
-        me[e] = __ballot(key[j + e] == tau);
-        my_e = below_me(me[e], my_e);
+      for (int e = 0; e < 4; ++e) {
+        const unsigned long long me = __ballot(key[j + e] == tau);
+        mine = below_me(me, mine);
+        before += __popcll(me);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool eq = key[j + e] == tau;
+        key[j + e] = key[j + e] > tau || (eq && mine < need) ? 1u : 0u;
+        mine += eq ? 1u : 0u;
       }
     }
+    tau = 1u;
+  }
+  unsigned short* mine = stage + wave * 64 * MAXC;
+  unsigned held = 0;                            // kept tokens of this wave, in `mine`
+#pragma unroll
+  for (int j = 0; j < MAXC; j += 4) {
+    asm volatile("" : "+s"(tau));
+    unsigned at = held;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const bool gt = whole ? key[j + e] >= tau : key[j + e] > tau, eq = !whole && key[j + e] == tau;
-      const unsigned pos = my_g + min(my_e, need);
-      if ((gt || (eq && my_e < need)) && pos < (unsigned)k && i + e < n)
-        for (int c = 0; c < copies; ++c) out[(size_t)c * k + pos] = i + e;
-      my_g += gt ? 1u : 0u;
-      my_e += eq ? 1u : 0u;
-      pg += __popcll(mg[e]);
-      pe += __popcll(me[e]);
+      const unsigned long long mk = __ballot(key[j + e] >= tau);
+      at = below_me(mk, at);
+      held += __popcll(mk);
     }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool keep = key[j + e] >= tau;
+      if (keep) mine[at] = (unsigned short)(i0 + j * 64 + e);
+      at += keep ? 1u : 0u;
+    }
+  }
+  if (lane == 0) wave_a[wave] = held;
+  __syncthreads();
+  unsigned pos = 0;                             // kept by lower waves
+  for (int w = 0; w < wave; ++w) pos += wave_a[w];
+  pos = uniform(pos);
+  for (unsigned t = lane; t < held; t += 64) {
+    const int token = mine[t];
+    if (pos + t < (unsigned)k)
+      for (int c = 0; c < copies; ++c) out[(size_t)c * k + pos + t] = token;
   }
 }
 

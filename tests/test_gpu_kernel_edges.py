@@ -277,6 +277,44 @@ def test_selection_of_uneven_key_ranges(n, shared):
             assert np.array_equal(got[l * k:(l + 1) * k], np.sort(order[:k])), (l, k)
 
 
+# every remainder of the four scores a lane loads, units that begin at any multiple of 4 bytes, ties within and across waves;
+# rows of 1, 3, 9, 32 and 257 vectors of 16 bytes, fewer kept rows than a workgroup takes, and many layers
+@pytest.mark.parametrize("n,L,H,d,dtype", [(1, 70, 1, 8, "bf16"), (2, 70, 3, 24, "bf16"), (3, 9, 2, 72, "bf16"), (5, 3, 3, 128, "f32"),
+                                           (6, 2, 1, 2056, "bf16"), (1021, 70, 3, 8, "bf16"), (2046, 3, 2, 72, "bf16"),
+                                           (4095, 2, 3, 128, "f32"), (16381, 2, 3, 24, "bf16"), (40002, 2, 1, 8, "bf16")])
+@pytest.mark.parametrize("shared", [False, True])
+def test_selection_and_gather_of_odd_sizes(n, L, H, d, dtype, shared):
+    import paper_2511_16786_amd as fc
+    rng = np.random.default_rng(n + L)
+    K, V = (rng.integers(0, 0x7F80, (L, H, n, d)).astype(np.uint16) if dtype == "bf16" else
+            rng.standard_normal((L, H, n, d)).astype(np.float32) for _ in range(2))
+    scores = rng.integers(0, 3 + n // 4, (L, H, n)).astype(np.float32)
+    scores[::2] += rng.uniform(0.0, 0.5, (len(scores[::2]), H, n)).astype(np.float32)
+    budgets = rng.integers(1, n + 1, L)
+    budgets[0] = n
+    want = ref.select_gather(K, V, scores, budgets, shared=shared)
+    offs = ref.layer_offsets(budgets, H)
+    rows = int(offs[-1])
+    Kt, Vt = pu.to_torch(K[None], dtype), pu.to_torch(V[None], dtype)
+    s_t, b_t, o_t = (torch.from_numpy(x[None]).cuda() for x in (scores, budgets.astype(np.int32), offs))
+    idx = torch.full((1, rows), -1, dtype=torch.int32, device="cuda")
+    Ko, Vo = (torch.zeros((1, rows, d), dtype=Kt.dtype, device="cuda") for _ in range(2))
+    fc.select_gather(Kt, Vt, fc.describe(Kt), s_t, b_t, o_t, rows, idx, Ko, Vo, shared=shared)
+    assert np.array_equal(idx.cpu().numpy()[0], want["idx"])
+    assert np.array_equal(pu.rows_to_numpy(Ko, dtype)[0], want["K_out"])
+    assert np.array_equal(pu.rows_to_numpy(Vo, dtype)[0], want["V_out"])
+    page = 3
+    reach = -(-n // page)
+    table = rng.permutation(L * H * reach).astype(np.int32).reshape(L, H, reach)
+    Kc, Vc = (torch.zeros((L * H * reach, page, d), dtype=Kt.dtype, device="cuda") for _ in range(2))
+    fc.select_gather_paged(Kt, Vt, fc.describe(Kt), s_t, b_t, o_t, rows, idx, torch.from_numpy(table[None]).cuda(), page, Kc, Vc,
+                           shared=shared)
+    for got, packed in ((Kc, want["K_out"]), (Vc, want["V_out"])):
+        paged = np.zeros(got.shape, dtype=K.dtype)
+        ref.scatter_paged(packed, budgets, H, table, page, paged)
+        assert np.array_equal(pu.rows_to_numpy(got, dtype), paged)
+
+
 @pytest.mark.parametrize("L", [63, 64, 65])
 def test_allocation_on_both_sides_of_one_wave(L):
     import paper_2511_16786_amd as fc
