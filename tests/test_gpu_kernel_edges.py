@@ -371,6 +371,43 @@ def test_decode_rows_that_end_inside_a_step(dtype, d, group, page):
     assert err <= 5e-5 * float(np.abs(ref.widen(Vr, dtype)).max())
 
 
+# caches of more than 256 MB, whose rows are read past the last-level cache, and the same rows in small ones
+@pytest.mark.parametrize("page", [0, 16])
+@pytest.mark.parametrize("dtype,d,group", [("bf16", 128, 7), ("bf16", 64, 4), ("f32", 64, 2)])
+def test_decode_of_large_caches_is_the_same_bits(dtype, d, group, page):
+    import paper_2511_16786_amd as fc
+    gen = torch.Generator(device="cuda").manual_seed(d + group)
+    L, H = 4, 2
+    budgets = [1, 200, 1025, 2047]
+    offs = torch.tensor([[0] + [H * sum(budgets[:l + 1]) for l in range(L)]], device="cuda")
+    rows = int(offs[0, -1])
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    Q = torch.randn((1, L, H * group, d), generator=gen, device="cuda").to(dt)
+    b_t = torch.tensor([budgets], dtype=torch.int32, device="cuda")
+    large = -(-(1 << 28) // (2 * d * Q.element_size()) // 16) * 16
+    assert 2 * large * d * Q.element_size() >= 1 << 28 > 2 * 2 * rows * d * Q.element_size()
+    K, V = (torch.randn((rows, d), generator=gen, device="cuda").to(dt) for _ in range(2))
+    out = []
+    for held in (-(-rows // 16) * 16 + 16 * L * H, large):
+        Kc, Vc = (torch.zeros((held, d), dtype=dt, device="cuda") for _ in range(2))
+        if page == 0:
+            Kc[:rows], Vc[:rows] = K, V
+            out.append(fc.decode_attention(Q, Kc[None], Vc[None], H, b_t, offs, held, 0.1))
+            continue
+        reach = max(160, held // (page * L * H))         # (both launches for more than 16 pieces: one order of the sums)
+        table = (torch.arange(L * H * reach, dtype=torch.int32, device="cuda") % (held // page)).reshape(1, L, H, reach)
+        first = 0
+        for l in range(L):
+            for h in range(H):
+                need = -(-budgets[l] // page)
+                table[0, l, h, :need] = torch.arange(first // page, first // page + need, dtype=torch.int32, device="cuda")
+                at = int(offs[0, l]) + h * budgets[l]
+                Kc[first:first + budgets[l]], Vc[first:first + budgets[l]] = K[at:at + budgets[l]], V[at:at + budgets[l]]
+                first += need * page
+        out.append(fc.decode_attention_paged(Q, Kc.view(-1, page, d), Vc.view(-1, page, d), H, b_t, table, 0.1))
+    assert torch.equal(out[0], out[1])
+
+
 # most layers keep less than the launch's pieces (units first), or more (a unit's pieces first)
 @pytest.mark.parametrize("most", [57, 1300])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
