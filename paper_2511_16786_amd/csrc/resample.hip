@@ -454,13 +454,26 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
   };
   // (every other group of four tiles is walked from its end, so that neighbours come to the rows they share together)
   const int steps_all = s_end - first[0], dir = (tile0 >> 2) & 1 ? -1 : 1, s_from = dir > 0 ? first[0] : s_end - 1;
+  // The weights, four loads at a time and the first ahead of the rows, for which they would wait otherwise (one at a time
+  // behind the rows, 28 layers: 32768 tokens 445 us, 436 now; 8192 tokens 134.5, 131.4; one layer of these 11.6, 11.0).
+  const f32x4* w_src = reinterpret_cast<const f32x4*>(wfwd) + (size_t)tile0 * steps * 128;
+  const int w_last = n_tiles * steps * 128 - 1;
+  f32x4 wt[4];
+  auto load_weights = [&](int i) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) wt[k] = w_src[min(i + k * 64 * kDecWaves, w_last)];
+  };
+  load_weights(threadIdx.x);
 #pragma unroll
   for (int b = 0; b < kBuf; ++b)
     if (b == 0 || b < steps_all) load(x[b], s_from + dir * b);
-  if (ws_mismatch(hdr, FC_PATH_RESAMPLE, n, r, d, dtype)) return;     // (while the rows are on their way)
-  {
-    const f32x4* src = reinterpret_cast<const f32x4*>(wfwd) + (size_t)tile0 * steps * 128;
-    for (int i = threadIdx.x; i < n_tiles * steps * 128; i += 64 * kDecWaves) wlds[i] = src[i];
+  if (ws_mismatch(hdr, FC_PATH_RESAMPLE, n, r, d, dtype)) return;     // (while all that is on its way)
+  for (int i = threadIdx.x;;) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) wlds[min(i + k * 64 * kDecWaves, w_last)] = wt[k];
+    i += 4 * 64 * kDecWaves;
+    if (i > w_last) break;
+    load_weights(i);
   }
   __syncthreads();
   if (!mine) return;
