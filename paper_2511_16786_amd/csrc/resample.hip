@@ -414,7 +414,8 @@ constexpr int kDecWaves = 4;          // waves of a workgroup: 4 slots' worth of
 // are at the rows they share together.  Results leave in 16 bytes and whole 128-byte lines, two tiles side by side: the
 // writes, a seventh of the traffic, cost a quarter of the time as half lines of 8 bytes a lane.  112 units, us before both /
 // walked both ways / now: 32768 tokens M = 3072 472 / 470 / 457 (1.09 GB read a round for 0.94 GB of rows, was 1.11; 0.19
-// written), M = 12288 750 / 717 / 671, 30011 tokens 541 / 535 / 503, 8192 tokens 146 / 144 / 136.
+// written), M = 12288 750 / 717 / 671, 30011 tokens 541 / 535 / 503, 8192 tokens 146 / 144 / 136; with the weights ahead of
+// the rows 436, 653, 470 and 131 (5.8 TB/s).  Three to five steps of rows under way in the one-tile variant are no quicker.
 template <typename T, int GT, bool KEEP>
 __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
     const T* __restrict__ K, const T* __restrict__ V, KvStrides st, int u0, int u1, int n, int r, int d, int dtype,
@@ -1142,8 +1143,10 @@ constexpr int kResWorkgroups = 512;   // residual kernel: two for each compute u
 // Neighbouring windows read the same lines of the grid: an XCD takes a contiguous range of windows and its
 // workgroups walk (units, window) side by side, window fastest, so that its L2 serves what they share.  Launches with no
 // more than one segment for a wave (ONCE) ask for nothing ahead of a next one (one layer of 16384 tokens: 19.7 / 19.1 us).
-// Bound by the rows: 56 units of 32768 tokens, M = 3072: 248 us, 1.18 GB read for 0.94 GB of rows and 0.18 of grid, 4.8
-// TB/s, with the grid's loads as they first were.  112 units: 432 us with three of the five products and sums in 32 bits, 455 with sums as they are, 474 with all.
+// Bound by the memory path: 56 units of 32768 tokens, M = 3072: 238 us, 1.18 GB read for 0.94 GB of rows and 0.18 of
+// grid, 5.0 TB/s.  Rows three or four tiles ahead, with their weights, or windows not asked for ahead leave it there (112
+// units, us: 452 as it is, 453, 454, 457).  Sums: 432 us with three of the five products and sums in 32 bits where 455 were
+// taken with sums as they are and 474 with all in 64.
 // A lane holds slot lane & 15 throughout: columns 8 slot + j of tokens 4 (lane >> 4) + i, so that a load reads whole
 // rows, and of a window the points that loads of 64-byte pieces deliver (see resample_table_kernel).  Those loads are made
 // by four lanes next to each other and turned over to the operands' lanes through LDS (a swizzle keeps them on distinct
