@@ -96,20 +96,56 @@ __device__ __forceinline__ long long cache_row(const PagedSrc& pg, long long pac
   return ok ? page * pg.page_size + (row - p * pg.page_size) : 0;
 }
 
+// Which unit a workgroup works on, its budget and (packed) first row.  `by_budget` = B: the units in the launch's order are
+// layers by falling budget (ties by layer), of each all sequences and heads, else 0: units as they are numbered.  Every wave ranks
+// the layers by itself, a lane each, from the loads that it would wait for anyway.
+struct Place {
+  int unit, b, l, h, k;
+  long long off;
+};
+template <bool PAGED>
+__device__ __forceinline__ Place place_of(int at, const int* __restrict__ budgets, const long long* __restrict__ layer_offsets,
+                                          int L, int H, int by_budget) {
+  Place p;
+  p.h = at % H;
+  if (by_budget == 0) {
+    p.unit = at;
+    p.l = at / H % L;
+    p.b = at / H / L;
+    p.k = budgets[(size_t)p.b * L + p.l];
+    p.off = PAGED ? 0 : layer_offsets[(size_t)p.b * (L + 1) + p.l] + (long long)p.h * p.k;
+    return p;
+  }
+  const int lane = threadIdx.x & 63, mine = min(lane, L - 1), rank = at / H / by_budget;
+  p.b = at / H % by_budget;
+  const int k = budgets[(size_t)p.b * L + mine];
+  const long long off = PAGED ? 0 : layer_offsets[(size_t)p.b * (L + 1) + mine];
+  const int key = min(max(k, 0), (1 << 25) - 1) * 64 + 63 - mine;           // (no two alike)
+  int above = 0;
+#pragma unroll 4
+  for (int j = 0; j < L; ++j) above += __builtin_amdgcn_readlane(key, j) > key ? 1 : 0;
+  p.l = __builtin_ctzll(__ballot(lane < L && above == rank));
+  p.k = __builtin_amdgcn_readlane(k, p.l);
+  const unsigned lo = __builtin_amdgcn_readlane((int)off, p.l), hi = __builtin_amdgcn_readlane((int)(off >> 32), p.l);
+  p.off = PAGED ? 0 : (long long)((unsigned long long)hi << 32 | lo) + (long long)p.h * p.k;
+  p.unit = (p.b * L + p.l) * H + p.h;
+  return p;
+}
+
 template <typename T, int G, int LPR, bool PAGED, bool KEEP>
 __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(
     const T* __restrict__ Q, const T* __restrict__ Kc, const T* __restrict__ Vc,
     const int* __restrict__ budgets, const long long* __restrict__ layer_offsets, int L, int H,
-    long long rows_per_seq, float scale_log2e, int splits, bool spread, float* __restrict__ partial, PagedSrc pg) {
+    long long rows_per_seq, float scale_log2e, int splits, bool spread, int by_budget, float* __restrict__ partial, PagedSrc pg) {
   constexpr int D = LPR * 8;
   constexpr int NG = kDecThreads / LPR;                 // lane groups (rows in flight per step / unroll)
   constexpr int NW = kDecThreads / 64;                  // waves; their lane groups merge in registers
   __shared__ float sm_m[NW][G], sm_l[NW][G];
   __shared__ float sm_o[NW][G][D];
-  const int split = spread ? blockIdx.y : blockIdx.x, unit = spread ? blockIdx.x : blockIdx.y;
-  const int h = unit % H, bl = unit / H, l = bl % L, b = bl / L;
-  const int k = budgets[(size_t)b * L + l];
-  const long long off = PAGED ? 0 : layer_offsets[(size_t)b * (L + 1) + l] + (long long)h * k;
+  const int split = spread ? blockIdx.y : blockIdx.x;
+  const Place at = place_of<PAGED>(spread ? blockIdx.x : blockIdx.y, budgets, layer_offsets, L, H, by_budget);
+  const int unit = at.unit, h = at.h, l = at.l, b = at.b, k = at.k;
+  const long long off = at.off;
   float* rec = partial + ((size_t)unit * splits + split) * partial_floats(G, D);
   const int tid = threadIdx.x, grp = tid / LPR, sub = tid % LPR;
   const bool bad = k < 0 || (!PAGED && (off < 0 || off + k > rows_per_seq));
@@ -249,12 +285,13 @@ __device__ __forceinline__ bf16x8 as_bf16x8(uint32_t a, uint32_t b, uint32_t c, 
 //            same rows, dim (D/16)*c16 + t for output tile t)  ->  lane holds out[head 4*g4+i][that dim]
 // Bound by memory and by what a launch cannot overlap, its first loads and last merges.  112 units of 6554 rows, 7 query
 // heads (0.38 GB): 79.2 us as long as rows claimed the last-level cache, a load took 16 bytes in four places of a K row and
-// products were of 16; 74.0 now, all but 1 us of it for the loads past the cache; 896 units of 1638 rows, paged: 156 / 144.
+// products were of 16; 74.1 with these changed, all but 1 us of it for the loads past the cache, and 66.3 in order of the
+// layers' budgets (see Cut); 896 units of 1638 rows, paged: 156 / 144 / 135.
 template <int D, bool PAGED, bool KEEP>
 __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_partial_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kc, const uint16_t* __restrict__ Vc,
     const int* __restrict__ budgets, const long long* __restrict__ layer_offsets, int L, int H, int G,
-    long long rows_per_seq, float scale_log2e, int splits, bool spread, float* __restrict__ partial, PagedSrc pg) {
+    long long rows_per_seq, float scale_log2e, int splits, bool spread, int by_budget, float* __restrict__ partial, PagedSrc pg) {
   constexpr int KS = D / 32;            // k-steps of the score product
   constexpr int KW = D / 8;             // dwords of a K row (and of a Q row) per lane: D/4 dims
   constexpr int VT = D / 16;            // output tiles = dims of a V row per lane
@@ -264,10 +301,10 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_partial_kernel(
   constexpr int kStepRows = 16 * kTilesPerStep;
   __shared__ float sm_m[NW][GP], sm_l[NW][GP];
   __shared__ float sm_o[NW][GP][D];
-  const int split = spread ? blockIdx.y : blockIdx.x, unit = spread ? blockIdx.x : blockIdx.y;
-  const int h = unit % H, bl = unit / H, l = bl % L, b = bl / L;
-  const int k = budgets[(size_t)b * L + l];
-  const long long off = PAGED ? 0 : layer_offsets[(size_t)b * (L + 1) + l] + (long long)h * k;
+  const int split = spread ? blockIdx.y : blockIdx.x;
+  const Place at = place_of<PAGED>(spread ? blockIdx.x : blockIdx.y, budgets, layer_offsets, L, H, by_budget);
+  const int unit = at.unit, h = at.h, l = at.l, b = at.b, k = at.k;
+  const long long off = at.off;
   float* rec = partial + ((size_t)unit * splits + split) * partial_floats(G, D);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c16 = lane & 15, g4 = lane >> 4;
   const bool bad = k < 0 || (!PAGED && (off < 0 || off + k > rows_per_seq));
@@ -554,16 +591,22 @@ hipError_t launch_merge(const float* ws, const int32_t* budgets, int H, int G, i
 // fewer, surplus workgroups are among them, and the units' first pieces are launched before their second ones, so that
 // those with rows spread over the compute units (fp32, 3 layers of 4 heads that keep 1463 rows, 8 query heads each: 17.3 ->
 // 13.5 us; a unit's pieces side by side are better where all have rows: 18 layers of 8 heads, 1827 rows: 83 / 88).
+// Where pieces have 256 rows and more by the mean budget and the launch is more than the 512 workgroups that are resident,
+// layers come by falling budget, so that the last workgroups to begin are the shortest (of all layers alike the launch
+// below takes 64 us).  As numbered / by budget, us: 28 layers of 4 heads that keep 6554 rows, bf16 74.1 / 66.3, fp32
+// 143.7 / 134.7; 12 layers 38.3 / 36.8; eight sequences that keep 1638, paged 144.1 / 134.9.  With shorter pieces the ranking is
+// what counts: 19 layers that keep 548 rows 10.7 / 11.3, eight sequences of 28 layers that keep 300 35.5 / 39.6.
 struct Cut {
   int splits;
-  bool spread;
+  bool spread, long_pieces;
   dim3 grid(int units) const { return spread ? dim3(units, splits) : dim3(splits, units); }
+  int by_budget(int B, int L, int units) const { return long_pieces && L > 1 && L <= 64 && (int64_t)units * splits > 512 ? B : 0; }
 };
 Cut cut_splits(int splits, int L, int H, int64_t rows_per_seq, const PagedSrc& pg) {
   const int64_t rows = pg.table ? (int64_t)pg.max_pages * pg.page_size : rows_per_seq / H;
   const int64_t most = (rows + 127) / 128, mean = pg.table ? rows : rows / L;
   const int cut = most < 1 ? 1 : (most < splits ? (int)most : splits);
-  return {cut, mean < 128 * (int64_t)cut};
+  return {cut, mean < 128 * (int64_t)cut, mean >= 256 * (int64_t)cut};
 }
 
 // Whether the rows fit the last-level cache (256 MB) from one step to the next; else they are read without a claim on it.
@@ -586,7 +629,7 @@ hipError_t decode_t(const void* Q, const void* Kc, const void* Vc, int B, int L,
       hipLaunchKernelGGL(kern, cut.grid(units), dim3(kDecThreads), 0, s, static_cast<const T*>(Q),
                          static_cast<const T*>(Kc), static_cast<const T*>(Vc), budgets,
                          reinterpret_cast<const long long*>(offs), L, H, (long long)rows_per_seq,
-                         scale * 1.4426950408889634f, cut.splits, cut.spread, ws, pg);
+                         scale * 1.4426950408889634f, cut.splits, cut.spread, cut.by_budget(B, L, units), ws, pg);
     };
     const bool keep = keep_rows(B, L, H, rows_per_seq, d * sizeof(T), pg);
     if (pg.table) keep ? launch(decode_partial_kernel<T, G, LPR, true, true>) : launch(decode_partial_kernel<T, G, LPR, true, false>);
@@ -609,7 +652,7 @@ hipError_t decode_mfma_t(const void* Q, const void* Kc, const void* Vc, int B, i
       hipLaunchKernelGGL(kern, cut.grid(units), dim3(kDecThreads), 0, s, static_cast<const uint16_t*>(Q),
                          static_cast<const uint16_t*>(Kc), static_cast<const uint16_t*>(Vc), budgets,
                          reinterpret_cast<const long long*>(offs), L, H, G, (long long)rows_per_seq,
-                         scale * 1.4426950408889634f, cut.splits, cut.spread, ws, pg);
+                         scale * 1.4426950408889634f, cut.splits, cut.spread, cut.by_budget(B, L, units), ws, pg);
     };
     const bool keep = keep_rows(B, L, H, rows_per_seq, D * sizeof(uint16_t), pg);
     if (pg.table) keep ? launch(decode_mfma_partial_kernel<D, true, true>) : launch(decode_mfma_partial_kernel<D, true, false>);

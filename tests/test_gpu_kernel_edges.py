@@ -371,6 +371,48 @@ def test_decode_rows_that_end_inside_a_step(dtype, d, group, page):
     assert err <= 5e-5 * float(np.abs(ref.widen(Vr, dtype)).max())
 
 
+# launches whose workgroups take the layers by falling budget (2 to 64 of them), and one layer too many for that: layers
+# with the same budget, with one row and with none, and sequences whose orders differ
+@pytest.mark.parametrize("B,L,H", [(8, 2, 16), (2, 64, 2), (2, 65, 2)])
+@pytest.mark.parametrize("dtype,group,page", [("bf16", 4, 0), ("bf16", 16, 16), ("f32", 2, 0), ("f32", 1, 48)])
+def test_decode_of_many_long_pieces(B, L, H, dtype, group, page):
+    import paper_2511_16786_amd as fc
+    rng = np.random.default_rng(L + group)
+    d, mean = 64, 1100
+    budgets = np.empty((B, L), np.int64)
+    for b in range(B):
+        half = rng.integers(0, 2 * mean, L // 2)
+        budgets[b] = rng.permutation(np.concatenate([half, 2 * mean - half, np.full(L % 2, mean)]))
+    if L > 2:
+        budgets[0, :6] = 1, 0, 1700, 1700, 2 * mean, 3 * mean - 1
+    rows = max(H * mean * L, int(H * budgets.sum(axis=1).max()))
+    offs = np.stack([ref.layer_offsets(k, H) for k in budgets])
+
+    def make(shape, sigma=1.0):
+        x = (sigma * rng.standard_normal(shape, dtype=np.float32)).astype(np.float32)
+        return kvsynth.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    K, V, Q = make((B, rows, d)), make((B, rows, d), 2.0), make((B, L, H * group, d))
+    scale = float(1.0 / np.sqrt(d))
+    b_t = torch.from_numpy(budgets.astype(np.int32)).cuda()
+    if page == 0:
+        out = fc.decode_attention(pu.to_torch(Q, dtype), pu.to_torch(K, dtype), pu.to_torch(V, dtype), H, b_t,
+                                  torch.from_numpy(offs).cuda(), rows, scale)
+    else:
+        reach = -(-int(budgets.max()) // page)
+        table = rng.permutation(B * L * H * reach).astype(np.int32).reshape(B, L, H, reach)
+        Kc = np.zeros((B * L * H * reach, page, d), dtype=K.dtype)
+        Vc = np.zeros_like(Kc)
+        for b in range(B):
+            ref.scatter_paged(K[b], budgets[b], H, table[b], page, Kc)
+            ref.scatter_paged(V[b], budgets[b], H, table[b], page, Vc)
+        out = fc.decode_attention_paged(pu.to_torch(Q, dtype), pu.to_torch(Kc, dtype), pu.to_torch(Vc, dtype), H, b_t,
+                                        torch.from_numpy(table).cuda(), scale)
+    out = out.cpu().numpy()
+    for b in range(B):
+        want = ref.decode_attention(Q[b], K[b], V[b], dtype, budgets[b], H, scale)
+        assert np.abs(out[b] - want).max() <= 5e-5 * float(np.abs(ref.widen(V[b], dtype)).max()), b
+
+
 # caches of more than 256 MB, whose rows are read past the last-level cache, and the same rows in small ones
 @pytest.mark.parametrize("page", [0, 16])
 @pytest.mark.parametrize("dtype,d,group", [("bf16", 128, 7), ("bf16", 64, 4), ("f32", 64, 2)])
