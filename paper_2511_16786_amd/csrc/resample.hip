@@ -1143,8 +1143,8 @@ constexpr int kResWorkgroups = 512;   // residual kernel: two for each compute u
 // Neighbouring windows read the same lines of the grid: an XCD takes a contiguous range of windows and its
 // workgroups walk (units, window) side by side, window fastest, so that its L2 serves what they share.  Launches with no
 // more than one segment for a wave (ONCE) ask for nothing ahead of a next one (one layer of 16384 tokens: 19.7 / 19.1 us).
-// Bound by the memory path: 56 units of 32768 tokens, M = 3072: 238 us, 1.18 GB read for 0.94 GB of rows and 0.18 of
-// grid, 5.0 TB/s.  Rows three or four tiles ahead, with their weights, or windows not asked for ahead leave it there (112
+// Bound by the memory path: 56 units of 32768 tokens, M = 3072: 238 to 245 us by card, 1.18 GB read for 0.94 GB of rows and
+// 0.18 of grid, 5.0 to 4.8 TB/s.  Rows three or four tiles ahead, with their weights, or windows not asked for ahead leave it there (112
 // units, us: 452 as it is, 453, 454, 457).  Sums: 432 us with three of the five products and sums in 32 bits where 455 were
 // taken with sums as they are and 474 with all in 64.
 // A lane holds slot lane & 15 throughout: columns 8 slot + j of tokens 4 (lane >> 4) + i, so that a load reads whole
