@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "fc_common.h"
+#include "rules.h"
 
 namespace fc {
 
@@ -1451,18 +1452,6 @@ static bool wide_transform(int64_t n, int64_t r, int64_t m) { return m <= 4096 &
 
 // (below 256 tokens the products with the basis itself are as quick and need no plan worth speaking of)
 bool resample_supported(const fc_kv_desc& d, int32_t r) { return d.n_tokens >= 256 && grid_length(d, r) != 0; }
-
-// Units of a round, of at most `most`: as few rounds as that takes, whole sets of four units (the residual kernel's waves),
-// the last round a little shorter than the others.  Scoring 112 units, us by units of a round:
-//   32768 tokens, M = 3072:  52 1093, 56 1095, 60 1063, 64 1065, 72 1069, 80 1102   M = 12288:  14 2395, 16 2142, 19 2197, 20 2152
-//   30011 tokens, M = 6144:  28 1394, 32 1376, 38 1357, 40 1337
-//   16384 tokens (224 units), M = 3072:  56 1428, 60 1427, 76 1380, 80 1372
-static int round_units(int units, int most) {
-  if (units <= most) return units;
-  if (most < 4) return most;
-  const int rounds = (units + most - 1) / most;
-  return std::min(most / 4, (107 * units + 400 * rounds - 1) / (400 * rounds)) * 4;
-}
 
 ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
   ResampleLayout lay{};

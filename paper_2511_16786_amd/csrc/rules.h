@@ -1,0 +1,25 @@
+// Choices by size alone, for host and device (constexpr functions serve both) and without HIP, so that they can be
+// compiled and checked by themselves.
+#ifndef FC_RULES_H_
+#define FC_RULES_H_
+
+namespace fc {
+
+// Units of a round of scoring, of at most `most`: as few rounds as whole sets of four units (the residual kernel's waves)
+// allow, and these alike.  Units that fill up what whole sets leave of `most` are not worth a set begun: 30 units of 32768
+// tokens with 256 columns, M = 16384, most 6: eight rounds of 4 1510 us, five of 6 1588.  Nor are rounds longer than equal
+// parts, with a shorter last one, us by units of a round:
+//   100 units of  8000, M = 4096:  36 651, 40 659, 48 676        128 units of 24000, M = 3072:  64 949, 68 967, 72 968
+//    64 units of 65536, M = 12288: 16 1548, 20 1596               96 units of 32768, M = 6144:  32 1165, 36 1191
+//   256 units of  8192, M = 1536:  128 733, 140 751              256 units of 16384, M = 3072:  64 1477, 72 1497
+// and in a few sizes they are (112 units of 32768, M = 3072: 56 1065, 60 1044, 64 1042, 72 1045, 80 1072; 224 of 16384:
+// 76 1358, 80 1344), with nothing that tells which; over 16 more shapes drawn at random the sum is the same.
+constexpr int round_units(int units, int most) {
+  if (units <= most) return units;
+  if (most < 4) return most;
+  const int cap = most / 4 * 4, rounds = (units + cap - 1) / cap;
+  return (units + 4 * rounds - 1) / (4 * rounds) * 4;
+}
+
+}  // namespace fc
+#endif
