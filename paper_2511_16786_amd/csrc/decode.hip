@@ -20,6 +20,7 @@
 #include <mutex>
 
 #include "fc_common.h"
+#include "rules.h"
 
 namespace fc {
 
@@ -96,19 +97,32 @@ __device__ __forceinline__ long long cache_row(const PagedSrc& pg, long long pac
   return ok ? page * pg.page_size + (row - p * pg.page_size) : 0;
 }
 
-// Which unit a workgroup works on, its budget and (packed) first row.  `by_budget` = B: the units in the launch's order are
-// layers by falling budget (ties by layer), of each all sequences and heads, else 0: units as they are numbered.  Every wave ranks
-// the layers by itself, a lane each, from the loads that it would wait for anyway.
+// The sum of every lane's value, in a scalar register.
+template <int CTRL> __device__ __forceinline__ int dpp_add_int(int v) {
+  return v + __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true);
+}
+__device__ __forceinline__ int wave_total(int v) {
+  v = dpp_add_int<kRowMirror>(dpp_add_int<kRowHalfMirror>(dpp_add_int<kQuadXor2>(dpp_add_int<kQuadXor1>(v))));
+  int sum = 0;
+#pragma unroll
+  for (int row = 0; row < 64; row += 16) sum += __builtin_amdgcn_readlane(v, row);
+  return sum;
+}
+
+// Which unit a workgroup works on, its budget and (packed) first row.  `may_rank`: the launch's order is layer by layer, of
+// each all sequences and heads, and where a sequence's pieces are long (ranks_by_budget) its layers come by falling budget, ties
+// by layer; else units as they are numbered.  Every wave sums up and ranks the layers by itself, a lane each, from the
+// loads that it would wait for anyway.
 struct Place {
   int unit, b, l, h, k;
   long long off;
 };
 template <bool PAGED>
 __device__ __forceinline__ Place place_of(int at, const int* __restrict__ budgets, const long long* __restrict__ layer_offsets,
-                                          int L, int H, int by_budget) {
+                                          int B, int L, int H, int splits, bool may_rank, int row_bytes) {
   Place p;
   p.h = at % H;
-  if (by_budget == 0) {
+  if (!may_rank) {
     p.unit = at;
     p.l = at / H % L;
     p.b = at / H / L;
@@ -116,15 +130,19 @@ __device__ __forceinline__ Place place_of(int at, const int* __restrict__ budget
     p.off = PAGED ? 0 : layer_offsets[(size_t)p.b * (L + 1) + p.l] + (long long)p.h * p.k;
     return p;
   }
-  const int lane = threadIdx.x & 63, mine = min(lane, L - 1), rank = at / H / by_budget;
-  p.b = at / H % by_budget;
+  const int lane = threadIdx.x & 63, mine = min(lane, L - 1), rank = at / H / B;
+  p.b = at / H % B;
   const int k = budgets[(size_t)p.b * L + mine];
   const long long off = PAGED ? 0 : layer_offsets[(size_t)p.b * (L + 1) + mine];
-  const int key = min(max(k, 0), (1 << 25) - 1) * 64 + 63 - mine;           // (no two alike)
-  int above = 0;
+  const int rows = min(max(k, 0), (1 << 25) - 1);          // (64 of them, and 64 times one, are 31 bits)
+  p.l = rank;
+  if (ranks_by_budget(wave_total(lane < L ? rows : 0), L, splits, row_bytes)) {
+    const int key = rows * 64 + 63 - mine;                 // (no two alike)
+    int above = 0;
 #pragma unroll 4
-  for (int j = 0; j < L; ++j) above += __builtin_amdgcn_readlane(key, j) > key ? 1 : 0;
-  p.l = __builtin_ctzll(__ballot(lane < L && above == rank));
+    for (int j = 0; j < L; ++j) above += __builtin_amdgcn_readlane(key, j) > key ? 1 : 0;
+    p.l = __builtin_ctzll(__ballot(lane < L && above == rank));
+  }
   p.k = __builtin_amdgcn_readlane(k, p.l);
   const unsigned lo = __builtin_amdgcn_readlane((int)off, p.l), hi = __builtin_amdgcn_readlane((int)(off >> 32), p.l);
   p.off = PAGED ? 0 : (long long)((unsigned long long)hi << 32 | lo) + (long long)p.h * p.k;
@@ -135,15 +153,17 @@ __device__ __forceinline__ Place place_of(int at, const int* __restrict__ budget
 template <typename T, int G, int LPR, bool PAGED, bool KEEP>
 __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(
     const T* __restrict__ Q, const T* __restrict__ Kc, const T* __restrict__ Vc,
-    const int* __restrict__ budgets, const long long* __restrict__ layer_offsets, int L, int H,
-    long long rows_per_seq, float scale_log2e, int splits, bool spread, int by_budget, float* __restrict__ partial, PagedSrc pg) {
+    const int* __restrict__ budgets, const long long* __restrict__ layer_offsets, int B, int L, int H,
+    long long rows_per_seq, float scale_log2e, int splits, bool spread, bool may_rank, float* __restrict__ partial,
+    PagedSrc pg) {
   constexpr int D = LPR * 8;
   constexpr int NG = kDecThreads / LPR;                 // lane groups (rows in flight per step / unroll)
   constexpr int NW = kDecThreads / 64;                  // waves; their lane groups merge in registers
   __shared__ float sm_m[NW][G], sm_l[NW][G];
   __shared__ float sm_o[NW][G][D];
   const int split = spread ? blockIdx.y : blockIdx.x;
-  const Place at = place_of<PAGED>(spread ? blockIdx.x : blockIdx.y, budgets, layer_offsets, L, H, by_budget);
+  const Place at = place_of<PAGED>(spread ? blockIdx.x : blockIdx.y, budgets, layer_offsets, B, L, H, splits, may_rank,
+                                   D * (int)sizeof(*Kc));
   const int unit = at.unit, h = at.h, l = at.l, b = at.b, k = at.k;
   const long long off = at.off;
   float* rec = partial + ((size_t)unit * splits + split) * partial_floats(G, D);
@@ -286,12 +306,13 @@ __device__ __forceinline__ bf16x8 as_bf16x8(uint32_t a, uint32_t b, uint32_t c, 
 // Bound by memory and by what a launch cannot overlap, its first loads and last merges.  112 units of 6554 rows, 7 query
 // heads (0.38 GB): 79.2 us as long as rows claimed the last-level cache, a load took 16 bytes in four places of a K row and
 // products were of 16; 74.1 with these changed, all but 1 us of it for the loads past the cache, and 66.3 in order of the
-// layers' budgets (see Cut); 896 units of 1638 rows, paged: 156 / 144 / 135.
+// layers' budgets (see place_of); 896 units of 1638 rows, paged: 156 / 144 / 135.
 template <int D, bool PAGED, bool KEEP>
 __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_partial_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kc, const uint16_t* __restrict__ Vc,
-    const int* __restrict__ budgets, const long long* __restrict__ layer_offsets, int L, int H, int G,
-    long long rows_per_seq, float scale_log2e, int splits, bool spread, int by_budget, float* __restrict__ partial, PagedSrc pg) {
+    const int* __restrict__ budgets, const long long* __restrict__ layer_offsets, int B, int L, int H, int G,
+    long long rows_per_seq, float scale_log2e, int splits, bool spread, bool may_rank, float* __restrict__ partial,
+    PagedSrc pg) {
   constexpr int KS = D / 32;            // k-steps of the score product
   constexpr int KW = D / 8;             // dwords of a K row (and of a Q row) per lane: D/4 dims
   constexpr int VT = D / 16;            // output tiles = dims of a V row per lane
@@ -302,7 +323,8 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_partial_kernel(
   __shared__ float sm_m[NW][GP], sm_l[NW][GP];
   __shared__ float sm_o[NW][GP][D];
   const int split = spread ? blockIdx.y : blockIdx.x;
-  const Place at = place_of<PAGED>(spread ? blockIdx.x : blockIdx.y, budgets, layer_offsets, L, H, by_budget);
+  const Place at = place_of<PAGED>(spread ? blockIdx.x : blockIdx.y, budgets, layer_offsets, B, L, H, splits, may_rank,
+                                   D * (int)sizeof(*Kc));
   const int unit = at.unit, h = at.h, l = at.l, b = at.b, k = at.k;
   const long long off = at.off;
   float* rec = partial + ((size_t)unit * splits + split) * partial_floats(G, D);
@@ -591,22 +613,21 @@ hipError_t launch_merge(const float* ws, const int32_t* budgets, int H, int G, i
 // fewer, surplus workgroups are among them, and the units' first pieces are launched before their second ones, so that
 // those with rows spread over the compute units (fp32, 3 layers of 4 heads that keep 1463 rows, 8 query heads each: 17.3 ->
 // 13.5 us; a unit's pieces side by side are better where all have rows: 18 layers of 8 heads, 1827 rows: 83 / 88).
-// Where pieces have 256 rows and more by the mean budget and the launch is more than the 512 workgroups that are resident,
-// layers come by falling budget, so that the last workgroups to begin are the shortest (of all layers alike the launch
-// below takes 64 us).  As numbered / by budget, us: 28 layers of 4 heads that keep 6554 rows, bf16 74.1 / 66.3, fp32
-// 143.7 / 134.7; 12 layers 38.3 / 36.8; eight sequences that keep 1638, paged 144.1 / 134.9.  With shorter pieces the ranking is
-// what counts: 19 layers that keep 548 rows 10.7 / 11.3, eight sequences of 28 layers that keep 300 35.5 / 39.6.
+// Layers may come by falling budget (see place_of) in launches of more than the 512 workgroups that are resident, so
+// that the last to begin are the shortest (28 layers of 4 heads that keep 6554 rows: 66.3 us, as numbered 74.1, all layers
+// alike 64).  The host knows what a budget can be, a table's reach for instance; what the budgets are is decided by on the
+// device (by the reach alone eight sequences that keep 300 rows were ranked whatever their table: 41.3 us instead of 37.5).
 struct Cut {
   int splits;
   bool spread, long_pieces;
   dim3 grid(int units) const { return spread ? dim3(units, splits) : dim3(splits, units); }
-  int by_budget(int B, int L, int units) const { return long_pieces && L > 1 && L <= 64 && (int64_t)units * splits > 512 ? B : 0; }
+  bool may_rank(int L, int units) const { return long_pieces && L > 1 && L <= 64 && (int64_t)units * splits > 512; }
 };
-Cut cut_splits(int splits, int L, int H, int64_t rows_per_seq, const PagedSrc& pg) {
+Cut cut_splits(int splits, int L, int H, int64_t rows_per_seq, int row_bytes, const PagedSrc& pg) {
   const int64_t rows = pg.table ? (int64_t)pg.max_pages * pg.page_size : rows_per_seq / H;
   const int64_t most = (rows + 127) / 128, mean = pg.table ? rows : rows / L;
   const int cut = most < 1 ? 1 : (most < splits ? (int)most : splits);
-  return {cut, mean < 128 * (int64_t)cut, mean >= 256 * (int64_t)cut};
+  return {cut, mean < 128 * (int64_t)cut, ranks_by_budget(mean, 1, cut, row_bytes)};
 }
 
 // Whether the rows fit the last-level cache (256 MB) from one step to the next; else they are read without a claim on it.
@@ -622,14 +643,14 @@ hipError_t decode_t(const void* Q, const void* Kc, const void* Vc, int B, int L,
                     const int64_t* offs, int64_t rows_per_seq, float scale, float* out, float* ws,
                     const PagedSrc& pg, hipStream_t s) {
   const int units = B * L * H, d = LPR * 8;
-  const Cut cut = cut_splits(pick_splits(units, G, d), L, H, rows_per_seq, pg);
+  const Cut cut = cut_splits(pick_splits(units, G, d), L, H, rows_per_seq, d * (int)sizeof(T), pg);
   {
     ProfileScope ps("decode_partial_kernel", s);
     auto launch = [&](auto kern) {
       hipLaunchKernelGGL(kern, cut.grid(units), dim3(kDecThreads), 0, s, static_cast<const T*>(Q),
                          static_cast<const T*>(Kc), static_cast<const T*>(Vc), budgets,
-                         reinterpret_cast<const long long*>(offs), L, H, (long long)rows_per_seq,
-                         scale * 1.4426950408889634f, cut.splits, cut.spread, cut.by_budget(B, L, units), ws, pg);
+                         reinterpret_cast<const long long*>(offs), B, L, H, (long long)rows_per_seq,
+                         scale * 1.4426950408889634f, cut.splits, cut.spread, cut.may_rank(L, units), ws, pg);
     };
     const bool keep = keep_rows(B, L, H, rows_per_seq, d * sizeof(T), pg);
     if (pg.table) keep ? launch(decode_partial_kernel<T, G, LPR, true, true>) : launch(decode_partial_kernel<T, G, LPR, true, false>);
@@ -645,14 +666,14 @@ hipError_t decode_mfma_t(const void* Q, const void* Kc, const void* Vc, int B, i
                          const int32_t* budgets, const int64_t* offs, int64_t rows_per_seq, float scale,
                          float* out, float* ws, const PagedSrc& pg, hipStream_t s) {
   const int units = B * L * H;
-  const Cut cut = cut_splits(pick_splits(units, G, D), L, H, rows_per_seq, pg);
+  const Cut cut = cut_splits(pick_splits(units, G, D), L, H, rows_per_seq, D * (int)sizeof(uint16_t), pg);
   {
     ProfileScope ps("decode_mfma_partial_kernel", s);
     auto launch = [&](auto kern) {
       hipLaunchKernelGGL(kern, cut.grid(units), dim3(kDecThreads), 0, s, static_cast<const uint16_t*>(Q),
                          static_cast<const uint16_t*>(Kc), static_cast<const uint16_t*>(Vc), budgets,
-                         reinterpret_cast<const long long*>(offs), L, H, G, (long long)rows_per_seq,
-                         scale * 1.4426950408889634f, cut.splits, cut.spread, cut.by_budget(B, L, units), ws, pg);
+                         reinterpret_cast<const long long*>(offs), B, L, H, G, (long long)rows_per_seq,
+                         scale * 1.4426950408889634f, cut.splits, cut.spread, cut.may_rank(L, units), ws, pg);
     };
     const bool keep = keep_rows(B, L, H, rows_per_seq, D * sizeof(uint16_t), pg);
     if (pg.table) keep ? launch(decode_mfma_partial_kernel<D, true, true>) : launch(decode_mfma_partial_kernel<D, true, false>);

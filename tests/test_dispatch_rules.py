@@ -13,6 +13,7 @@ _WRAPPERS = """
 #include "rules.h"
 extern "C" {
 int round_units(int units, int most) { return fc::round_units(units, most); }
+bool ranks_by_budget(long long rows, int layers, int splits, int row_bytes) { return fc::ranks_by_budget(rows, layers, splits, row_bytes); }
 }
 """
 
@@ -41,3 +42,14 @@ def test_rounds_are_as_few_and_as_equal_as_whole_sets_allow(rules):
             assert -(-units // got) == rounds, (units, most, got)       # (no round for what is left over)
             assert (got - 4) * rounds < units, (units, most, got)       # (a set less in each would not do)
     assert [rules.round_units(*x) for x in ((100, 50), (112, 80), (132, 66), (26, 15), (30, 6))] == [36, 56, 44, 12, 4]
+
+
+def test_layers_are_ranked_where_pieces_are_long(rules):
+    fn = rules.ranks_by_budget
+    fn.restype, fn.argtypes = ctypes.c_bool, [ctypes.c_longlong, ctypes.c_int, ctypes.c_int, ctypes.c_int]
+    for layers, splits, row_bytes in ((28, 2, 256), (64, 64, 256), (2, 9, 128), (28, 18, 512), (64, 1, 256)):
+        at = -(-72 * 1024 * layers * splits // row_bytes)                # the sum of the budgets from which they are
+        assert not fn(at - 1, layers, splits, row_bytes) and fn(at, layers, splits, row_bytes)
+    assert not fn(0, 2, 1, 256) and fn(64 * ((1 << 25) - 1), 64, 64, 512)
+    # budgets count, not what a table reaches: eight sequences that keep 300 rows of 128 bf16 columns through any table
+    assert not fn(28 * 300, 28, 2, 256) and fn(28 * 1638, 28, 2, 256)

@@ -413,6 +413,49 @@ def test_decode_of_many_long_pieces(B, L, H, dtype, group, page):
         assert np.abs(out[b] - want).max() <= 5e-5 * float(np.abs(ref.widen(V[b], dtype)).max()), b
 
 
+# sequences of one launch with long pieces, whose layers come by falling budget, and with short ones, whose layers do not; a table
+# that reaches further than any budget
+@pytest.mark.parametrize("dtype,d,group,page", [("bf16", 128, 4, 64), ("bf16", 64, 7, 16), ("f32", 64, 2, 0), ("bf16", 128, 2, 0), ("f32", 128, 1, 48)])
+def test_decode_of_sequences_with_long_and_short_pieces(dtype, d, group, page):
+    import paper_2511_16786_amd as fc
+    rng = np.random.default_rng(d + group)
+    B, L, H = 3, 44, 8                                           # (1056 units: one piece each)
+    long = 88 * 1024 // (d * (2 if dtype == "bf16" else 4))      # rows of 88 KiB, on average
+    budgets = np.stack([rng.permutation(np.linspace(lo, hi, L).astype(np.int64)) for lo, hi in ((0, 2 * long), (0, 180), (1, 1))])
+    offs = np.stack([ref.layer_offsets(k, H) for k in budgets])
+    rows = int(offs[0, -1])
+
+    def make(shape, sigma=1.0):
+        x = (sigma * rng.standard_normal(shape, dtype=np.float32)).astype(np.float32)
+        return kvsynth.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    K, V, Q = make((B, rows, d)), make((B, rows, d), 2.0), make((B, L, H * group, d))
+    scale = float(1.0 / np.sqrt(d))
+    b_t = torch.from_numpy(budgets.astype(np.int32)).cuda()
+    if page == 0:
+        out = fc.decode_attention(pu.to_torch(Q, dtype), pu.to_torch(K, dtype), pu.to_torch(V, dtype), H, b_t,
+                                  torch.from_numpy(offs).cuda(), rows, scale)
+    else:
+        reach = 8192 // page
+        need = -(-budgets // page)
+        table = np.full((B, L, H, reach), -1, np.int32)
+        at = 0
+        for b in range(B):
+            for l in range(L):
+                for h in range(H):
+                    table[b, l, h, :need[b, l]] = np.arange(at, at + need[b, l])
+                    at += int(need[b, l])
+        Kc, Vc = np.zeros((at, page, d), dtype=K.dtype), np.zeros((at, page, d), dtype=K.dtype)
+        for b in range(B):
+            ref.scatter_paged(K[b], budgets[b], H, table[b], page, Kc)
+            ref.scatter_paged(V[b], budgets[b], H, table[b], page, Vc)
+        out = fc.decode_attention_paged(pu.to_torch(Q, dtype), pu.to_torch(Kc, dtype), pu.to_torch(Vc, dtype), H, b_t,
+                                        torch.from_numpy(table).cuda(), scale)
+    out = out.cpu().numpy()
+    for b in range(B):
+        want = ref.decode_attention(Q[b], K[b], V[b], dtype, budgets[b], H, scale)
+        assert np.abs(out[b] - want).max() <= 5e-5 * float(np.abs(ref.widen(V[b], dtype)).max()), b
+
+
 # caches of more than 256 MB, whose rows are read past the last-level cache, and the same rows in small ones
 @pytest.mark.parametrize("page", [0, 16])
 @pytest.mark.parametrize("dtype,d,group", [("bf16", 128, 7), ("bf16", 64, 4), ("f32", 64, 2)])
