@@ -18,6 +18,7 @@
 //  * fp32 caches: vector ALUs, d/8 lanes per row, one online-softmax state per lane group.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "fc_common.h"
 #include "rules.h"
@@ -109,6 +110,9 @@ __device__ __forceinline__ int wave_total(int v) {
   return sum;
 }
 
+constexpr int kMostRows = (1 << 25) - 1;                   // (64 of them, and 64 times one, are 31 bits)
+__device__ __forceinline__ int rows_in(int budget) { return min(max(budget, 0), kMostRows); }
+
 // Which unit a workgroup works on, its budget and (packed) first row.  `may_rank`: the launch's order is layer by layer, of
 // each all sequences and heads, and where a sequence's pieces are long (ranks_by_budget) its layers come by falling budget, ties
 // by layer; else units as they are numbered.  Every wave sums up and ranks the layers by itself, a lane each, from the
@@ -116,27 +120,36 @@ __device__ __forceinline__ int wave_total(int v) {
 struct Place {
   int unit, b, l, h, k;
   long long off;
+  long long rows;                                          // of the sequence; paged: this lane's part of its budgets' sum
 };
-template <bool PAGED>
+template <bool PAGED, bool FITS>
 __device__ __forceinline__ Place place_of(int at, const int* __restrict__ budgets, const long long* __restrict__ layer_offsets,
                                           int B, int L, int H, int splits, bool may_rank, int row_bytes) {
   Place p;
   p.h = at % H;
+  const int lane = threadIdx.x & 63;
   if (!may_rank) {
     p.unit = at;
     p.l = at / H % L;
     p.b = at / H / L;
     p.k = budgets[(size_t)p.b * L + p.l];
     p.off = PAGED ? 0 : layer_offsets[(size_t)p.b * (L + 1) + p.l] + (long long)p.h * p.k;
+    int rows = lane ? 0 : rows_in(p.k);
+    if (PAGED && !FITS && L > 1) {
+      rows = 0;
+      for (int l = lane; l < L; l += 64) rows = min(rows + rows_in(budgets[(size_t)p.b * L + l]), kMostRows);
+    }
+    p.rows = PAGED ? rows : (FITS ? 0 : layer_offsets[(size_t)p.b * (L + 1) + L]);
     return p;
   }
-  const int lane = threadIdx.x & 63, mine = min(lane, L - 1), rank = at / H / B;
+  const int mine = min(lane, L - 1), rank = at / H / B;
   p.b = at / H % B;
   const int k = budgets[(size_t)p.b * L + mine];
   const long long off = PAGED ? 0 : layer_offsets[(size_t)p.b * (L + 1) + mine];
-  const int rows = min(max(k, 0), (1 << 25) - 1);          // (64 of them, and 64 times one, are 31 bits)
+  const int rows = rows_in(k), part = lane < L ? rows : 0;
+  p.rows = PAGED ? part : (FITS ? 0 : layer_offsets[(size_t)p.b * (L + 1) + L]);
   p.l = rank;
-  if (ranks_by_budget(wave_total(lane < L ? rows : 0), L, splits, row_bytes)) {
+  if (ranks_by_budget(wave_total(part), L, splits, row_bytes)) {
     const int key = rows * 64 + 63 - mine;                 // (no two alike)
     int above = 0;
 #pragma unroll 4
@@ -150,7 +163,17 @@ __device__ __forceinline__ Place place_of(int at, const int* __restrict__ budget
   return p;
 }
 
-template <typename T, int G, int LPR, bool PAGED, bool KEEP>
+// Whether rows claim the last-level cache (keeps_rows), by what the launch reads if all sequences keep as many as this one.
+// What a table or a buffer has room for does not tell.  By the room / by the budgets, us: through tables that reach 32768 rows four
+// sequences of 28 layers of 4 heads that keep 300 rows 32.9 / 28.3, one that keeps 1638 30.2 / 27.9, 80 layers of 8 heads
+// that keep 400 42.0 / 36.5; packed, a buffer for eight times the 1638 rows 27.5 / 25.4; where rows exceed the cache the same (137.2 /
+// 137.8, 108.3 / 109.5, packed 68.0 / 67.7).  Two loops, since a branch at each step's loads costs 3 %.
+template <bool PAGED>
+__device__ __forceinline__ bool keep_rows(const Place& p, int B, int H, int row_bytes) {
+  return keeps_rows((PAGED ? (long long)wave_total((int)p.rows) * H : p.rows) * B, row_bytes);
+}
+
+template <typename T, int G, int LPR, bool PAGED, bool FITS>
 __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(
     const T* __restrict__ Q, const T* __restrict__ Kc, const T* __restrict__ Vc,
     const int* __restrict__ budgets, const long long* __restrict__ layer_offsets, int B, int L, int H,
@@ -162,7 +185,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(
   __shared__ float sm_m[NW][G], sm_l[NW][G];
   __shared__ float sm_o[NW][G][D];
   const int split = spread ? blockIdx.y : blockIdx.x;
-  const Place at = place_of<PAGED>(spread ? blockIdx.x : blockIdx.y, budgets, layer_offsets, B, L, H, splits, may_rank,
+  const Place at = place_of<PAGED, FITS>(spread ? blockIdx.x : blockIdx.y, budgets, layer_offsets, B, L, H, splits, may_rank,
                                    D * (int)sizeof(*Kc));
   const int unit = at.unit, h = at.h, l = at.l, b = at.b, k = at.k;
   const long long off = at.off;
@@ -192,51 +215,55 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(
   const long long packed_base = PAGED ? 0 : (long long)b * rows_per_seq + off;
   const T* kbase = Kc + sub * 4;
   const T* vbase = Vc + sub * 4;
-  for (int row = r0 + grp; row < r1; row += NG * kDecUnroll) {
-    float kv[kDecUnroll][8], vv[kDecUnroll][8];
-    bool valid[kDecUnroll];
-#pragma unroll
-    for (int u = 0; u < kDecUnroll; ++u) {
-      const int rr = row + u * NG;
-      valid[u] = rr < r1;
-      const int rc = valid[u] ? rr : row;               // row itself is always in range
-      bool ok;
-      const long long ci = cache_row<PAGED>(pg, packed_base, unit, rc, ok);
-      valid[u] = valid[u] && ok;
-      load8<D, KEEP>(kbase + (size_t)ci * D, kv[u]);
-      load8<D, KEEP>(vbase + (size_t)ci * D, vv[u]);
-    }
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      float s[kDecUnroll];
-      float mx = m[g];
+  auto walk = [&](auto keep) {
+    for (int row = r0 + grp; row < r1; row += NG * kDecUnroll) {
+      float kv[kDecUnroll][8], vv[kDecUnroll][8];
+      bool valid[kDecUnroll];
 #pragma unroll
       for (int u = 0; u < kDecUnroll; ++u) {
-        float acc = 0.f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc = fmaf(q[g][i], kv[u][i], acc);
-        acc = row_sum<LPR>(acc);
-        s[u] = valid[u] ? acc : -INFINITY;
-        mx = fmaxf(mx, s[u]);
+        const int rr = row + u * NG;
+        valid[u] = rr < r1;
+        const int rc = valid[u] ? rr : row;               // row itself is always in range
+        bool ok;
+        const long long ci = cache_row<PAGED>(pg, packed_base, unit, rc, ok);
+        valid[u] = valid[u] && ok;
+        load8<D, keep>(kbase + (size_t)ci * D, kv[u]);
+        load8<D, keep>(vbase + (size_t)ci * D, vv[u]);
       }
-      // mx is finite as soon as one row was valid (packed layout: row `row` always is); while no
-      // row has been seen the state stays empty
-      if (mx == -INFINITY) continue;
-      const float alpha = exp2f(m[g] - mx);             // exp2(-inf) = 0 on the first step
-      float psum = 0.f;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) o[g][i] *= alpha;
+      for (int g = 0; g < G; ++g) {
+        float s[kDecUnroll];
+        float mx = m[g];
 #pragma unroll
-      for (int u = 0; u < kDecUnroll; ++u) {
-        const float p = exp2f(s[u] - mx);
-        psum += p;
+        for (int u = 0; u < kDecUnroll; ++u) {
+          float acc = 0.f;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) o[g][i] = fmaf(p, vv[u][i], o[g][i]);
+          for (int i = 0; i < 8; ++i) acc = fmaf(q[g][i], kv[u][i], acc);
+          acc = row_sum<LPR>(acc);
+          s[u] = valid[u] ? acc : -INFINITY;
+          mx = fmaxf(mx, s[u]);
+        }
+        // mx is finite as soon as one row was valid (packed layout: row `row` always is); while no
+        // row has been seen the state stays empty
+        if (mx == -INFINITY) continue;
+        const float alpha = exp2f(m[g] - mx);             // exp2(-inf) = 0 on the first step
+        float psum = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) o[g][i] *= alpha;
+#pragma unroll
+        for (int u = 0; u < kDecUnroll; ++u) {
+          const float p = exp2f(s[u] - mx);
+          psum += p;
+#pragma unroll
+          for (int i = 0; i < 8; ++i) o[g][i] = fmaf(p, vv[u][i], o[g][i]);
+        }
+        ls[g] = fmaf(ls[g], alpha, psum);
+        m[g] = mx;
       }
-      ls[g] = fmaf(ls[g], alpha, psum);
-      m[g] = mx;
     }
-  }
+  };
+  if (FITS || keep_rows<PAGED>(at, B, H, D * (int)sizeof(*Kc))) walk(std::true_type{});
+  else walk(std::false_type{});
 
   // merge the lane groups of a wave (lanes that hold the same dims of different rows), then the
   // waves through LDS; the order of the merges is fixed
@@ -307,7 +334,7 @@ __device__ __forceinline__ bf16x8 as_bf16x8(uint32_t a, uint32_t b, uint32_t c, 
 // heads (0.38 GB): 79.2 us as long as rows claimed the last-level cache, a load took 16 bytes in four places of a K row and
 // products were of 16; 74.1 with these changed, all but 1 us of it for the loads past the cache, and 66.3 in order of the
 // layers' budgets (see place_of); 896 units of 1638 rows, paged: 156 / 144 / 135.
-template <int D, bool PAGED, bool KEEP>
+template <int D, bool PAGED, bool FITS>
 __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_partial_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kc, const uint16_t* __restrict__ Vc,
     const int* __restrict__ budgets, const long long* __restrict__ layer_offsets, int B, int L, int H, int G,
@@ -323,7 +350,7 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_partial_kernel(
   __shared__ float sm_m[NW][GP], sm_l[NW][GP];
   __shared__ float sm_o[NW][GP][D];
   const int split = spread ? blockIdx.y : blockIdx.x;
-  const Place at = place_of<PAGED>(spread ? blockIdx.x : blockIdx.y, budgets, layer_offsets, B, L, H, splits, may_rank,
+  const Place at = place_of<PAGED, FITS>(spread ? blockIdx.x : blockIdx.y, budgets, layer_offsets, B, L, H, splits, may_rank,
                                    D * (int)sizeof(*Kc));
   const int unit = at.unit, h = at.h, l = at.l, b = at.b, k = at.k;
   const long long off = at.off;
@@ -371,7 +398,7 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_partial_kernel(
     const long long ci = cache_row<true>(pg, 0, unit, min(st * kStepRows + (lane & (kStepRows - 1)), k - 1), ok);
     return ok ? (uint32_t)ci : kNoRow;
   };
-  auto load_step = [&](int st, uint32_t where, Rows& x) {
+  auto load_step = [&](auto keep, int st, uint32_t where, Rows& x) {
     x.vok = PAGED ? 0u : ~0u;
 #pragma unroll
     for (int tt = 0; tt < kTilesPerStep; ++tt) {
@@ -393,17 +420,17 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_partial_kernel(
       const uint16_t* kp = kbase + kr * D;
 #pragma unroll
       for (int i = 0; i < KW / 4; ++i) {
-        const u32x4 u = load_vec<KEEP, u32x4>(kp + 32 * i);
+        const u32x4 u = load_vec<keep, u32x4>(kp + 32 * i);
         x.kw[tt][4 * i] = u.x; x.kw[tt][4 * i + 1] = u.y; x.kw[tt][4 * i + 2] = u.z; x.kw[tt][4 * i + 3] = u.w;
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const uint16_t* vp = vbase + vr[i] * D;
         if constexpr (VW == 4) {
-          const u32x4 u = load_vec<KEEP, u32x4>(vp);
+          const u32x4 u = load_vec<keep, u32x4>(vp);
           x.vw[tt][i][0] = u.x; x.vw[tt][i][1] = u.y; x.vw[tt][i][2] = u.z; x.vw[tt][i][3] = u.w;
         } else {
-          const u32x2 u = load_vec<KEEP, u32x2>(vp);
+          const u32x2 u = load_vec<keep, u32x2>(vp);
           x.vw[tt][i][0] = u.x; x.vw[tt][i][1] = u.y;
         }
       }
@@ -476,26 +503,30 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_partial_kernel(
     }
   };
   // two steps of rows under way; a step's registers are filled again in place
-  Rows xa, xb;
-  uint32_t where = 0;
-  if (s0 < s1) {
-    if (PAGED) where = lookup(s0);
-    load_step(s0, where, xa);
-    if (s0 + 1 < s1) {
-      if (PAGED) where = lookup(s0 + 1);
-      load_step(s0 + 1, where, xb);
-      if (PAGED && s0 + 2 < s1) where = lookup(s0 + 2);
+  auto walk = [&](auto keep) {
+    Rows xa, xb;
+    uint32_t where = 0;
+    if (s0 < s1) {
+      if (PAGED) where = lookup(s0);
+      load_step(keep, s0, where, xa);
+      if (s0 + 1 < s1) {
+        if (PAGED) where = lookup(s0 + 1);
+        load_step(keep, s0 + 1, where, xb);
+        if (PAGED && s0 + 2 < s1) where = lookup(s0 + 2);
+      }
     }
-  }
-  auto turn = [&](int st, Rows& x) {
-    work(st, x);
-    if (st + 2 < s1) load_step(st + 2, where, x);
-    if (PAGED && st + 3 < s1) where = lookup(st + 3);
+    auto turn = [&](int st, Rows& x) {
+      work(st, x);
+      if (st + 2 < s1) load_step(keep, st + 2, where, x);
+      if (PAGED && st + 3 < s1) where = lookup(st + 3);
+    };
+    for (int st = s0; st < s1; st += 2) {
+      turn(st, xa);
+      if (st + 1 < s1) turn(st + 1, xb);
+    }
   };
-  for (int st = s0; st < s1; st += 2) {
-    turn(st, xa);
-    if (st + 1 < s1) turn(st + 1, xb);
-  }
+  if (FITS || keep_rows<PAGED>(at, B, H, D * (int)sizeof(*Kc))) walk(std::true_type{});
+  else walk(std::false_type{});
 
   // the 4 lanes of a head add their sums; then the waves merge through LDS in a fixed order
   ls += __shfl_xor(ls, 16, 64);
@@ -630,12 +661,11 @@ Cut cut_splits(int splits, int L, int H, int64_t rows_per_seq, int row_bytes, co
   return {cut, mean < 128 * (int64_t)cut, ranks_by_budget(mean, 1, cut, row_bytes)};
 }
 
-// Whether the rows fit the last-level cache (256 MB) from one step to the next; else they are read without a claim on it.
-// Kept / not kept: 1.5 GB of fp32 280 / 252 us, 0.75 GB 158 / 143, 0.38 GB of bf16 78 / 74; 26 MB from step to step 16.1 / 17.6.
-bool keep_rows(int B, int L, int H, int64_t rows_per_seq, size_t row_bytes, const PagedSrc& pg) {
+// Whether the rows fit the last-level cache whatever the budgets are; else the kernels look at these (see keep_rows).
+bool surely_fits(int B, int L, int H, int64_t rows_per_seq, int row_bytes, const PagedSrc& pg) {
   const int64_t rows = pg.table ? std::min<int64_t>(pg.num_pages, (int64_t)B * L * H * pg.max_pages) * pg.page_size
                                 : B * rows_per_seq;
-  return 2.0 * (double)rows * (double)row_bytes <= 256e6;
+  return keeps_rows(rows, row_bytes);
 }
 
 template <typename T, int G, int LPR>
@@ -652,9 +682,9 @@ hipError_t decode_t(const void* Q, const void* Kc, const void* Vc, int B, int L,
                          reinterpret_cast<const long long*>(offs), B, L, H, (long long)rows_per_seq,
                          scale * 1.4426950408889634f, cut.splits, cut.spread, cut.may_rank(L, units), ws, pg);
     };
-    const bool keep = keep_rows(B, L, H, rows_per_seq, d * sizeof(T), pg);
-    if (pg.table) keep ? launch(decode_partial_kernel<T, G, LPR, true, true>) : launch(decode_partial_kernel<T, G, LPR, true, false>);
-    else keep ? launch(decode_partial_kernel<T, G, LPR, false, true>) : launch(decode_partial_kernel<T, G, LPR, false, false>);
+    const bool fits = surely_fits(B, L, H, rows_per_seq, d * (int)sizeof(T), pg);
+    if (pg.table) fits ? launch(decode_partial_kernel<T, G, LPR, true, true>) : launch(decode_partial_kernel<T, G, LPR, true, false>);
+    else fits ? launch(decode_partial_kernel<T, G, LPR, false, true>) : launch(decode_partial_kernel<T, G, LPR, false, false>);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -675,9 +705,9 @@ hipError_t decode_mfma_t(const void* Q, const void* Kc, const void* Vc, int B, i
                          reinterpret_cast<const long long*>(offs), B, L, H, G, (long long)rows_per_seq,
                          scale * 1.4426950408889634f, cut.splits, cut.spread, cut.may_rank(L, units), ws, pg);
     };
-    const bool keep = keep_rows(B, L, H, rows_per_seq, D * sizeof(uint16_t), pg);
-    if (pg.table) keep ? launch(decode_mfma_partial_kernel<D, true, true>) : launch(decode_mfma_partial_kernel<D, true, false>);
-    else keep ? launch(decode_mfma_partial_kernel<D, false, true>) : launch(decode_mfma_partial_kernel<D, false, false>);
+    const bool fits = surely_fits(B, L, H, rows_per_seq, D * (int)sizeof(uint16_t), pg);
+    if (pg.table) fits ? launch(decode_mfma_partial_kernel<D, true, true>) : launch(decode_mfma_partial_kernel<D, true, false>);
+    else fits ? launch(decode_mfma_partial_kernel<D, false, true>) : launch(decode_mfma_partial_kernel<D, false, false>);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

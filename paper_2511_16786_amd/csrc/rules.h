@@ -32,5 +32,10 @@ constexpr bool ranks_by_budget(long long rows, int layers, int splits, int row_b
   return rows * row_bytes >= (72LL << 10) * layers * splits;
 }
 
+// Decode: whether a launch's rows, of K and as many of V, fit the last-level cache (256 MB) from one step to the next and claim it;
+// else they are read past it.  Kept / not kept, us: 1.5 GB of fp32 280 / 252, 0.75 GB 158 / 143, 0.38 GB of bf16 78 / 74; 26 MB from
+// step to step 16.1 / 17.6.
+constexpr bool keeps_rows(long long rows, int row_bytes) { return 2 * rows * row_bytes <= 256000000; }
+
 }  // namespace fc
 #endif

@@ -13,6 +13,7 @@ _WRAPPERS = """
 #include "rules.h"
 extern "C" {
 int round_units(int units, int most) { return fc::round_units(units, most); }
+bool keeps_rows(long long rows, int row_bytes) { return fc::keeps_rows(rows, row_bytes); }
 bool ranks_by_budget(long long rows, int layers, int splits, int row_bytes) { return fc::ranks_by_budget(rows, layers, splits, row_bytes); }
 }
 """
@@ -53,3 +54,13 @@ def test_layers_are_ranked_where_pieces_are_long(rules):
     assert not fn(0, 2, 1, 256) and fn(64 * ((1 << 25) - 1), 64, 64, 512)
     # budgets count, not what a table reaches: eight sequences that keep 300 rows of 128 bf16 columns through any table
     assert not fn(28 * 300, 28, 2, 256) and fn(28 * 1638, 28, 2, 256)
+
+
+def test_rows_claim_the_cache_where_they_fit_it(rules):
+    fn = rules.keeps_rows
+    fn.restype, fn.argtypes = ctypes.c_bool, [ctypes.c_longlong, ctypes.c_int]
+    for row_bytes in (128, 256, 512):
+        assert fn(128_000_000 // row_bytes, row_bytes) and not fn(128_000_000 // row_bytes + 1, row_bytes)
+    assert fn(0, 512) and not fn(64 * ((1 << 25) - 1) * 32767, 512)      # (the most that a launch can hand it)
+    # 28 layers of 4 heads that keep 1638 rows, whatever a table reaches, and 6554
+    assert fn(28 * 4 * 1638, 256) and not fn(28 * 4 * 6554, 256)

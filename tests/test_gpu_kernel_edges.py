@@ -493,6 +493,53 @@ def test_decode_of_large_caches_is_the_same_bits(dtype, d, group, page):
     assert torch.equal(out[0], out[1])
 
 
+# one sequence whose rows are read past the last-level cache, by what the launch reads if all are like it, and one whose rows are
+# not, of one layer, of layers that may come by falling budget, and of more layers than a wave has lanes
+@pytest.mark.parametrize("L,H", [(1, 8), (2, 8), (70, 2)])
+@pytest.mark.parametrize("dtype,d,group,page", [("bf16", 128, 4, 0), ("bf16", 64, 7, 64), ("f32", 64, 2, 16), ("f32", 128, 8, 0)])
+def test_decode_of_rows_past_the_cache_and_in_it(L, H, dtype, d, group, page):
+    import paper_2511_16786_amd as fc
+    gen = torch.Generator(device="cuda").manual_seed(L + d + group)
+    B, scale = 2, 0.1
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    row_bytes = d * dt.itemsize
+    many = -(-256_000_000 // (2 * row_bytes * B * L * H)) + 1
+    budgets = torch.tensor([[many + 7 * (l % 3) for l in range(L)], [1 + 37 * l % 200 for l in range(L)]])
+    assert 2 * row_bytes * B * H * int(budgets[0].sum()) > 256_000_000 > 2 * row_bytes * B * H * int(budgets[1].sum())
+    offs = torch.zeros((B, L + 1), dtype=torch.int64)
+    offs[:, 1:] = torch.cumsum(H * budgets, 1)
+    rows = int(offs[:, -1].max())
+    Q = torch.randn((B, L, H * group, d), generator=gen, device="cuda").to(dt)
+    K, V = (torch.randn((B, rows, d), generator=gen, device="cuda").to(dt) for _ in range(2))
+    b_t = budgets.to(torch.int32).cuda()
+    if page == 0:
+        out = fc.decode_attention(Q, K, V, H, b_t, offs.cuda(), rows, scale)
+    else:
+        need = -(-budgets // page)
+        pages, reach = H * int(need.sum()), int(need.max()) + 3
+        table = torch.full((B, L, H, reach), -1, dtype=torch.int32)
+        Kc, Vc = (torch.zeros((pages, page, d), dtype=dt, device="cuda") for _ in range(2))
+        at = 0
+        for b in range(B):
+            for l in range(L):
+                for h in range(H):
+                    k, first = int(budgets[b, l]), int(offs[b, l]) + h * int(budgets[b, l])
+                    table[b, l, h, :need[b, l]] = torch.arange(at, at + int(need[b, l]), dtype=torch.int32)
+                    for full, cache in ((K, Kc), (V, Vc)):
+                        cache.view(-1, d)[at * page:at * page + k] = full[b, first:first + k]
+                    at += int(need[b, l])
+        out = fc.decode_attention_paged(Q, Kc, Vc, H, b_t, table.cuda(), scale)
+    for b in range(B):
+        for l in range(L):
+            for h in range(H):
+                k, first = int(budgets[b, l]), int(offs[b, l]) + h * int(budgets[b, l])
+                q = Q[b, l, h * group:(h + 1) * group].double()
+                p = torch.softmax(scale * (K[b, first:first + k].double() @ q.T), 0)
+                want = p.T.contiguous() @ V[b, first:first + k].double()
+                err = (out[b, l, h * group:(h + 1) * group].double() - want).abs().max()
+                assert float(err) <= 5e-5 * float(V[b, first:first + k].abs().max()), (b, l, h)
+
+
 # most layers keep less than the launch's pieces (units first), or more (a unit's pieces first)
 @pytest.mark.parametrize("most", [57, 1300])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
