@@ -1254,13 +1254,21 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
   double hp = 0.0, tot = 0.0;
 
   const int operand_at = 4 * (lane & 15) + (g ^ ((lane >> 1) & 3));
+  // What other lanes of the wave wrote to LDS is there, and what they read of it has been read.  (No instruction: a wave's LDS
+  // operations are in order; the compiler, which sees one lane, has to keep them so.)
+  auto turned = [] {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+  };
   auto take_window = [&]() {
 #pragma unroll
     for (int jp = 0; jp < 4; ++jp) {
 #pragma unroll
       for (int c = 0; c < 4; ++c) turn_lds[wave][c][lane] = v[jp][c];
+      turned();
 #pragma unroll
       for (int c = 0; c < 4; ++c) v[jp][c] = turn_lds[wave][c][operand_at];
+      turned();
     }
     float mx = 0.f;
 #pragma unroll
