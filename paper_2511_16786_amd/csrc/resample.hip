@@ -1492,10 +1492,7 @@ ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
   lay.elow = off; off = up(off + units * 2 * lay.nb * 4 * sizeof(double));
   lay.epart = off; off = up(off + units * lay.wins * lay.wpu * 4 * sizeof(double));
   // (room for the most units of a round: fewer units than these may make a round longer than theirs)
-  // (a grid that begins at a multiple of 512 bytes costs the residual kernel a tenth where M is a power of two: 28 layers of
-  // 4096 tokens, M = 4096: 182 us at 128, 256, 768, 1280 and 2304 bytes past a multiple of 4096, 204 at 0 and 512)
-  off = (off + 255) / 512 * 512 + 256;
-  lay.grid = off; off = up(off + std::min<size_t>(units, most) * 2 * lay.nb * 4 * m * sizeof(float2));
+  lay.grid = off; off = up(off + kGridSlack + std::min<size_t>(units, most) * 2 * lay.nb * 4 * m * sizeof(float2));
   lay.total = off;
   return lay;
 }
@@ -1570,7 +1567,7 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
   char* base = static_cast<char*>(ws);
   WsHeader* hdr = reinterpret_cast<WsHeader*>(base);
   const int units = d.batch * d.layers * d.kv_heads, n = d.n_tokens, m = lay.m;
-  float2* grid = reinterpret_cast<float2*>(base + lay.grid);
+  float2* grid = reinterpret_cast<float2*>(grid_start(reinterpret_cast<uintptr_t>(base) + lay.grid));
   const float2* filt = reinterpret_cast<const float2*>(base + lay.filt);
   const void* twid = base + lay.twid;
   double* epart = reinterpret_cast<double*>(base + lay.epart);

@@ -13,6 +13,8 @@ _WRAPPERS = """
 #include "rules.h"
 extern "C" {
 int round_units(int units, int most) { return fc::round_units(units, most); }
+unsigned long long grid_start(unsigned long long at) { return fc::grid_start(at); }
+unsigned long long grid_slack() { return fc::kGridSlack; }
 bool keeps_rows(long long rows, int row_bytes) { return fc::keeps_rows(rows, row_bytes); }
 bool ranks_by_budget(long long rows, int layers, int splits, int row_bytes) { return fc::ranks_by_budget(rows, layers, splits, row_bytes); }
 }
@@ -64,3 +66,12 @@ def test_rows_claim_the_cache_where_they_fit_it(rules):
     assert fn(0, 512) and not fn(64 * ((1 << 25) - 1) * 32767, 512)      # (the most that a launch can hand it)
     # 28 layers of 4 heads that keep 1638 rows, whatever a table reaches, and 6554
     assert fn(28 * 4 * 1638, 256) and not fn(28 * 4 * 6554, 256)
+
+
+def test_grids_begin_at_odd_multiples_of_256_wherever_a_workspace_begins(rules):
+    rules.grid_start.restype, rules.grid_start.argtypes = ctypes.c_ulonglong, [ctypes.c_ulonglong]
+    rules.grid_slack.restype = ctypes.c_ulonglong
+    for base in (0, 256, 512, 4096, (1 << 47) + 256, (1 << 47) + 3840):
+        for region in range(0, 2048, 256):
+            at = rules.grid_start(base + region)
+            assert at % 512 == 256 and 0 <= at - base - region <= rules.grid_slack()
