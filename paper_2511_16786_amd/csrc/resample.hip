@@ -1482,7 +1482,7 @@ ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
   const size_t unit_grid = 2 * (size_t)m * d.head_dim * sizeof(float);
   const bool much_grid = (size_t)n * (d.dtype == FC_BF16 ? 2 : 4) < 2 * (size_t)m * sizeof(float);
   const int most = (int)std::max<size_t>(1, (much_grid ? kRoundGridBytes / 6 * 5 : kRoundGridBytes) / unit_grid);
-  lay.chunk = round_units((int)units, most);
+  lay.chunk = round_units((int)units, most, (lay.wins + 7) / 8);
   auto up = [](size_t x) { return (x + kWsAlign - 1) / kWsAlign * kWsAlign; };
   size_t off = sizeof(WsHeader);
   lay.wfwd = off; off = up(off + (size_t)(m / 16) * lay.steps * 512 * sizeof(float));

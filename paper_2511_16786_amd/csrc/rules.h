@@ -5,20 +5,36 @@
 
 namespace fc {
 
-// Units of a round of scoring, of at most `most`: as few rounds as whole sets of four units (the residual kernel's waves)
-// allow, and these alike.  Units that fill up what whole sets leave of `most` are not worth a set begun: 30 units of 32768
-// tokens with 256 columns, M = 16384, most 6: eight rounds of 4 1510 us, five of 6 1588.  Nor are rounds longer than equal
-// parts, with a shorter last one, us by units of a round:
-//   100 units of  8000, M = 4096:  36 651, 40 659, 48 676        128 units of 24000, M = 3072:  64 949, 68 967, 72 968
-//    64 units of 65536, M = 12288: 16 1548, 20 1596               96 units of 32768, M = 6144:  32 1165, 36 1191
-//   256 units of  8192, M = 1536:  128 733, 140 751              256 units of 16384, M = 3072:  64 1477, 72 1497
-// and in a few sizes they are (112 units of 32768, M = 3072: 56 1065, 60 1044, 64 1042, 72 1045, 80 1072; 224 of 16384:
-// 76 1358, 80 1344), with nothing that tells which; over 16 more shapes drawn at random the sum is the same.
-constexpr int round_units(int units, int most) {
+// Half turns of the residual kernel's workgroups in a round of `units` units: two for each of an XCD's 32 compute units take
+// its items, `windows` for each four units, one after the other.  The last turn of no more than 32 workgroups has a compute unit for
+// each and is over in half the time.  Rounds of 28, 32, ... 76 units of 32768 tokens, M = 3072 (22 windows for an XCD):
+// 124, 143, 158, 163, 187, 202, 207, 233, 246, 250, 279, 292, 318 us, all of them 22.4 to 23.3 us for a half turn but the first two
+// and the more the even: in 33rds of a half turn 32 for an odd number, 33 for an even one.
+constexpr long long residual_cost(int units, int windows) {
+  const long long halves = ((units + 3) / 4 * (long long)windows + 31) / 32;
+  return halves * (halves % 2 ? 32 : 33);
+}
+
+// Units of a round of scoring, of at most `most`, `windows` as above: as few rounds as whole sets of four units (the
+// residual kernel's waves) allow, alike or, where that makes the residual's turns fewer or their ends shorter, the last one
+// shorter than the others.  Scoring, us by units of a round, equal ones first, the rule's choice marked:
+//   112 units of 32768, M = 3072: 56 1074, *60 1051, 64 1049, 72 1054, 76 1092    128 of 24000, M = 3072: *64 960, 68 975, 72 977, 80 980
+//   224 units of 16384, M = 3072: 76 1366, *80 1348           256 of 16384, M = 3072: *64 1536, 68 1573, 72 1557, 76 1585, 80 1573
+//   100 units of  8000, M = 4096: *36 664, 40 671, 48 685      96 of 32768, M = 6144: *32 1170, 36 1194, 40 1204
+// Units that fill up what whole sets leave of `most` are not worth a set begun: 30 units of 32768 tokens with 256 columns,
+// M = 16384, most 6: eight rounds of 4 1510 us, five of 6 1588.
+constexpr int round_units(int units, int most, int windows) {
   if (units <= most) return units;
   if (most < 4) return most;
-  const int cap = most / 4 * 4, rounds = (units + cap - 1) / cap;
-  return (units + 4 * rounds - 1) / (4 * rounds) * 4;
+  const int cap = most / 4 * 4, rounds = (units + cap - 1) / cap, equal = (units + 4 * rounds - 1) / (4 * rounds) * 4;
+  int best = equal;
+  long long least = 0;
+  for (int c = equal; c <= cap && c < equal + 64; c += 4) {
+    const int full = (units - 1) / c;                      // (rounds before the last: no more than as many as there have to be)
+    const long long cost = full * residual_cost(c, windows) + residual_cost(units - full * c, windows);
+    if (c == equal || cost < least) { best = c; least = cost; }
+  }
+  return best;
 }
 
 // Where the grid begins in its region of a workspace, both at multiples of 256 bytes: an odd multiple, whatever the

@@ -12,7 +12,8 @@ CSRC = os.path.join(ROOT, "paper_2511_16786_amd", "csrc")
 _WRAPPERS = """
 #include "rules.h"
 extern "C" {
-int round_units(int units, int most) { return fc::round_units(units, most); }
+int round_units(int units, int most, int windows) { return fc::round_units(units, most, windows); }
+long long residual_cost(int units, int windows) { return fc::residual_cost(units, windows); }
 unsigned long long grid_start(unsigned long long at) { return fc::grid_start(at); }
 unsigned long long grid_slack() { return fc::kGridSlack; }
 bool keeps_rows(long long rows, int row_bytes) { return fc::keeps_rows(rows, row_bytes); }
@@ -32,19 +33,29 @@ def rules(tmp_path_factory):
     return ctypes.CDLL(lib)
 
 
-def test_rounds_are_as_few_and_as_equal_as_whole_sets_allow(rules):
-    for most in list(range(1, 200)) + [480, 1000]:
-        for units in list(range(1, 400)) + [896, 4000, 32767]:
-            got = rules.round_units(units, most)
-            if units <= most or most < 4:
-                assert got == min(units, most)
-                continue
-            cap = most // 4 * 4
-            rounds = -(-units // cap)
-            assert 4 <= got <= cap and got % 4 == 0, (units, most, got)
-            assert -(-units // got) == rounds, (units, most, got)       # (no round for what is left over)
-            assert (got - 4) * rounds < units, (units, most, got)       # (a set less in each would not do)
-    assert [rules.round_units(*x) for x in ((100, 50), (112, 80), (132, 66), (26, 15), (30, 6))] == [36, 56, 44, 12, 4]
+def test_rounds_are_as_few_as_whole_sets_allow_and_end_with_the_workgroups_turns(rules):
+    rules.residual_cost.restype, rules.residual_cost.argtypes = ctypes.c_longlong, [ctypes.c_int, ctypes.c_int]
+    cost = rules.residual_cost
+    assert [cost(u, 22) for u in (4, 8, 40, 44, 52, 56, 64)] == [1 * 32, 2 * 33, 7 * 32, 8 * 33, 9 * 32, 10 * 33, 11 * 32]
+    for windows in (1, 5, 22, 86, 1024):
+        for most in list(range(1, 90)) + [200, 480, 1000]:
+            for units in list(range(1, 260)) + [896, 4000, 32767]:
+                got = rules.round_units(units, most, windows)
+                if units <= most or most < 4:
+                    assert got == min(units, most)
+                    continue
+                cap = most // 4 * 4
+                rounds = -(-units // cap)
+                assert 4 <= got <= cap and got % 4 == 0, (units, most, windows, got)
+                assert -(-units // got) == rounds, (units, most, windows, got)       # (no round for what is left over)
+
+                def of(c):
+                    return sum(cost(min(c, units - u), windows) for u in range(0, units, c))
+                equal = -(-units // (4 * rounds)) * 4
+                if units < 260:
+                    assert of(got) == min(of(c) for c in range(equal, min(cap, equal + 63) + 1, 4)), (units, most, windows, got)
+    want = {(100, 50, 32): 36, (112, 80, 22): 60, (224, 80, 22): 80, (256, 80, 22): 64, (128, 80, 21): 64, (96, 40, 43): 32, (30, 6, 86): 4}
+    assert {k: rules.round_units(*k) for k in want} == want
 
 
 def test_layers_are_ranked_where_pieces_are_long(rules):

@@ -594,3 +594,51 @@ def test_scores_of_small_launches_are_the_same_bits(n, r, dtype):
             assert torch.equal(one.scores[:, 0], all_at_once.scores[:, l])
             assert torch.equal(one.energy[:, 0], all_at_once.energy[:, l])
     assert fc.workspace_error(one.workspace) == 0
+
+
+# The kept energy is added up per thread of the transform in 32 bits, of at most 48 points with two products each, and differently by
+# the launch that spreads a transform over more threads; then in 64 bits.  The points are the same bits.
+@pytest.mark.parametrize("n,r,dtype", [(512, 52, "f32"), (1023, 109, "bf16"), (2048, 210, "bf16"), (4099, 410, "bf16"), (8191, 820, "bf16"),
+                                       (16384, 1639, "bf16"), (20001, 2300, "bf16")])
+def test_kept_energies_of_small_launches(n, r, dtype):
+    import paper_2511_16786_amd as fc
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    L, H, d = 5, 1, 128
+    K, V = (torch.randn((1, L, H, n, d), generator=gen, device="cuda").to(torch.float32 if dtype == "f32" else torch.bfloat16)
+            for _ in range(2))
+    kept = []
+    for part in (L, 1):
+        comp = fc.Compressor(K[:, :part], r, fc.total_budget(part, n, 0.2))
+        for l in range(0, L, part):
+            comp.run_score(K[:, l:l + part], V[:, l:l + part])
+            low = torch.empty((1, part, H, 2), dtype=torch.float64, device="cuda")
+            fc.lowpass_energy(comp.desc, r, comp.path, comp.workspace, low)
+            kept.append(low)
+            # total less kept is what was removed (Parseval)
+            total, removed = comp.energy[..., 2:], comp.energy[..., :2]
+            assert bool(((total - low - removed).abs() <= 2e-5 * total).all())
+    assert float(((torch.cat(kept[1:], 1) - kept[0]).abs() / kept[0]).max()) <= 2 * 96 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("n,r,d", [(300, 33, 64), (4096, 1639, 128)])
+def test_workspaces_at_any_multiple_of_256(n, r, d):
+    import paper_2511_16786_amd as fc
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    K, V = (torch.randn((1, 3, 2, n, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    desc = fc.describe(K)
+    path = fc.resolve_path(desc, r)
+    size = fc.workspace_bytes(desc, r, fc.realisation(desc, r, path))
+    out = []
+    for at in (0, 256, 512, 768):
+        held = torch.full((size + 1024 + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+        at += -held.data_ptr() % 512
+        workspace = held[at:at + size]
+        fc.prepare(desc, r, path, workspace)
+        scores = torch.empty((1, 3, 2, n), device="cuda")
+        energy = torch.empty((1, 3, 2, 4), dtype=torch.float64, device="cuda")
+        fc.score(K, V, desc, r, path, scores, energy, workspace)
+        assert fc.workspace_error(workspace) == 0
+        assert bool((held[:at] == 0x5A).all()) and bool((held[at + size:] == 0x5A).all())     # (nothing beyond its size)
+        out.append((scores, energy))
+    for scores, energy in out[1:]:
+        assert torch.equal(scores, out[0][0]) and torch.equal(energy, out[0][1])
