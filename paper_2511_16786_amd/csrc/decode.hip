@@ -120,7 +120,7 @@ __device__ __forceinline__ int rows_in(int budget) { return min(max(budget, 0), 
 struct Place {
   int unit, b, l, h, k;
   long long off;
-  long long rows;                                          // of the sequence; paged: this lane's part of its budgets' sum
+  long long rows;                                          // of the sequence; paged: its budgets' sum (may_rank), or this lane's part of it
 };
 template <bool PAGED, bool FITS>
 __device__ __forceinline__ Place place_of(int at, const int* __restrict__ budgets, const long long* __restrict__ layer_offsets,
@@ -146,10 +146,10 @@ __device__ __forceinline__ Place place_of(int at, const int* __restrict__ budget
   p.b = at / H % B;
   const int k = budgets[(size_t)p.b * L + mine];
   const long long off = PAGED ? 0 : layer_offsets[(size_t)p.b * (L + 1) + mine];
-  const int rows = rows_in(k), part = lane < L ? rows : 0;
-  p.rows = PAGED ? part : (FITS ? 0 : layer_offsets[(size_t)p.b * (L + 1) + L]);
+  const int rows = rows_in(k), total = wave_total(lane < L ? rows : 0);
+  p.rows = PAGED ? total : (FITS ? 0 : layer_offsets[(size_t)p.b * (L + 1) + L]);
   p.l = rank;
-  if (ranks_by_budget(wave_total(part), L, splits, row_bytes)) {
+  if (ranks_by_budget(total, L, splits, row_bytes)) {
     const int key = rows * 64 + 63 - mine;                 // (no two alike)
     int above = 0;
 #pragma unroll 4
@@ -169,8 +169,8 @@ __device__ __forceinline__ Place place_of(int at, const int* __restrict__ budget
 // that keep 400 42.0 / 36.5; packed, a buffer for eight times the 1638 rows 27.5 / 25.4; where rows exceed the cache the same (137.2 /
 // 137.8, 108.3 / 109.5, packed 68.0 / 67.7).  Two loops, since a branch at each step's loads costs 3 %.
 template <bool PAGED>
-__device__ __forceinline__ bool keep_rows(const Place& p, int B, int H, int row_bytes) {
-  return keeps_rows((PAGED ? (long long)wave_total((int)p.rows) * H : p.rows) * B, row_bytes);
+__device__ __forceinline__ bool keep_rows(const Place& p, bool may_rank, int B, int H, int row_bytes) {
+  return keeps_rows((PAGED ? (long long)(may_rank ? (int)p.rows : wave_total((int)p.rows)) * H : p.rows) * B, row_bytes);
 }
 
 template <typename T, int G, int LPR, bool PAGED, bool FITS>
@@ -262,7 +262,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(
       }
     }
   };
-  if (FITS || keep_rows<PAGED>(at, B, H, D * (int)sizeof(*Kc))) walk(std::true_type{});
+  if (FITS || keep_rows<PAGED>(at, may_rank, B, H, D * (int)sizeof(*Kc))) walk(std::true_type{});
   else walk(std::false_type{});
 
   // merge the lane groups of a wave (lanes that hold the same dims of different rows), then the
@@ -525,7 +525,7 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_partial_kernel(
       if (st + 1 < s1) turn(st + 1, xb);
     }
   };
-  if (FITS || keep_rows<PAGED>(at, B, H, D * (int)sizeof(*Kc))) walk(std::true_type{});
+  if (FITS || keep_rows<PAGED>(at, may_rank, B, H, D * (int)sizeof(*Kc))) walk(std::true_type{});
   else walk(std::false_type{});
 
   // the 4 lanes of a head add their sums; then the waves merge through LDS in a fixed order
