@@ -120,7 +120,7 @@ __device__ __forceinline__ int rows_in(int budget) { return min(max(budget, 0), 
 struct Place {
   int unit, b, l, h, k;
   long long off;
-  long long rows;                                          // of the sequence; paged: its budgets' sum (may_rank), or this lane's part of it
+  long long rows;                                          // of the sequence; paged: its budgets' sum, or (no may_rank) a lane's part of it
 };
 template <bool PAGED, bool FITS>
 __device__ __forceinline__ Place place_of(int at, const int* __restrict__ budgets, const long long* __restrict__ layer_offsets,
@@ -269,9 +269,10 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(
   const long long packed_base = PAGED ? 0 : (long long)b * rows_per_seq + off;
   const T* kbase = Kc + sub * 4;
   const T* vbase = Vc + sub * 4;
-  if constexpr (FITS) walk_rows<T, G, LPR, PAGED, true>(kbase, vbase, pg, packed_base, unit, r0 + grp, r1, q, m, ls, o);
-  else if (keep_rows<PAGED>(at, may_rank, B, H, D * (int)sizeof(*Kc))) walk_rows<T, G, LPR, PAGED, true>(kbase, vbase, pg, packed_base, unit, r0 + grp, r1, q, m, ls, o);
-  else walk_rows<T, G, LPR, PAGED, false>(kbase, vbase, pg, packed_base, unit, r0 + grp, r1, q, m, ls, o);
+  if (FITS || keep_rows<PAGED>(at, may_rank, B, H, D * (int)sizeof(*Kc)))
+    walk_rows<T, G, LPR, PAGED, true>(kbase, vbase, pg, packed_base, unit, r0 + grp, r1, q, m, ls, o);
+  else
+    walk_rows<T, G, LPR, PAGED, false>(kbase, vbase, pg, packed_base, unit, r0 + grp, r1, q, m, ls, o);
 
   // merge the lane groups of a wave (lanes that hold the same dims of different rows), then the
   // waves through LDS; the order of the merges is fixed
@@ -371,7 +372,7 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_partial_kernel(
   const int steps = bad ? 0 : (k + kStepRows - 1) / kStepRows, share = pieces * NW, w_id = split * NW + wave;
   const int s0 = (int)((int64_t)steps * w_id / share), s1 = (int)((int64_t)steps * (w_id + 1) / share);
 
-  // B operand of the score product: query head c16 (zeros beyond G), dims (D/4)*g4 ..
+  // B operand of the score product: query head c16 (zeros beyond G), dims 32 i + 8 g4 .. + 7
   uint32_t qw[KW];
 #pragma unroll
   for (int i = 0; i < KW; ++i) qw[i] = 0u;
@@ -564,9 +565,12 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_partial_kernel(
 }
 
 // out[unit][g][:] = sum_s o_s w_s / sum_s l_s w_s with w_s = exp2(m_s - max m); zeros if no rows.
-// grid = (G, units), one thread per feature and group of pieces, groups merged in order.  Bound by waiting for memory: a
-// group takes kAtOnce records at a time, whose loads are under way together, and a launch has groups for all but the longest lists to be
-// one turn (8 units of 64 records: 10.9 -> 6.2 us, 112 units of 9 records: 6.8 -> 6.2, with events; an empty launch 6.1).
+// grid = (G, units), one thread per feature and group of up to kAtOnce pieces, groups merged in order.  Bound by waiting for
+// memory: a launch has groups for all pieces that its units may have, whose loads are under way together (8 units of 64 records:
+// 10.9 -> 6.2 us, 112 units of 9 records: 6.8 -> 6.2, with events; an empty launch 6.1).  A unit whose budget makes no more than one
+// group's pieces is done without LDS (28 units that keep 277 rows in a buffer for four times as many, both kernels: 8.1 -> 7.5).
+constexpr int kMostPieces = 64;        // of a unit (see pick_splits)
+
 template <int kAtOnce, int kGroups>
 __global__ void decode_merge_kernel(const float* __restrict__ partial, const int* __restrict__ budgets, int H, int G,
                                     int d, int splits, float* __restrict__ out) {
@@ -575,7 +579,8 @@ __global__ void decode_merge_kernel(const float* __restrict__ partial, const int
   const size_t stride = partial_floats(G, d);
   const float* base = partial + (size_t)unit * splits * stride;
   float M = -INFINITY, acc = 0.f, lt = 0.f;
-  for (int s0 = group * kAtOnce; s0 < pieces; s0 += kGroups * kAtOnce) {
+  const int s0 = group * kAtOnce;
+  if (s0 < pieces) {
     float m[kAtOnce], l[kAtOnce], o[kAtOnce];
 #pragma unroll
     for (int k = 0; k < kAtOnce; ++k) {
@@ -584,22 +589,17 @@ __global__ void decode_merge_kernel(const float* __restrict__ partial, const int
       l[k] = rec[G + g];
       o[k] = rec[2 * G + (size_t)g * d + dim];
     }
-    float top = M;
 #pragma unroll
-    for (int k = 0; k < kAtOnce; ++k) top = fmaxf(top, m[k]);
-    if (top == -INFINITY) continue;
-    const float before = exp2f(M - top);
-    acc *= before;
-    lt *= before;
-    M = top;
+    for (int k = 0; k < kAtOnce; ++k) M = fmaxf(M, m[k]);
+    if (M > -INFINITY)
 #pragma unroll
-    for (int k = 0; k < kAtOnce; ++k) {
-      const float w = exp2f(m[k] - top);
-      acc = fmaf(o[k], w, acc);
-      lt = fmaf(l[k], w, lt);
-    }
+      for (int k = 0; k < kAtOnce; ++k) {
+        const float w = exp2f(m[k] - M);
+        acc = fmaf(o[k], w, acc);
+        lt = fmaf(l[k], w, lt);
+      }
   }
-  if constexpr (kGroups > 1) {
+  if (kGroups > 1 && pieces > kAtOnce) {
     extern __shared__ float group_sums[];                  // [kGroups][3][d]: largest logit, sum, weighted sum
     float* mine = group_sums + (size_t)group * 3 * d + dim;
     mine[0] = M; mine[d] = lt; mine[2 * d] = acc;
@@ -620,7 +620,7 @@ __global__ void decode_merge_kernel(const float* __restrict__ partial, const int
       }
     }
   }
-  out[((size_t)unit * G + g) * d + dim] = lt > 0.f ? acc / lt : 0.f;
+  if (group == 0) out[((size_t)unit * G + g) * d + dim] = lt > 0.f ? acc / lt : 0.f;
 }
 
 // Workgroups per unit.  A compute unit holds two, so the launch fills whole rounds of 512: two rounds for few
@@ -628,7 +628,7 @@ __global__ void decode_merge_kernel(const float* __restrict__ partial, const int
 // fit the static array, one round of 1024 shared out among the units, which bounds what the array has to hold; the
 // rule is the same for both kinds of scratch, so that their results agree to the bit.
 int pick_splits(int units, int group, int d) {
-  const int fine = std::min(64, (units > 256 ? 2048 : 1024) / units);
+  const int fine = std::min(kMostPieces, (units > 256 ? 2048 : 1024) / units);
   if (fine >= 1 && (size_t)units * fine * partial_floats(group, d) * sizeof(float) <= kStaticScratchBytes) return fine;
   return std::max(1, std::min(32, (1024 + units - 1) / units));
 }
@@ -640,6 +640,7 @@ hipError_t launch_merge(const float* ws, const int32_t* budgets, int H, int G, i
     hipLaunchKernelGGL(kern, dim3(G, units), dim3(groups * d), groups > 1 ? (size_t)groups * 3 * d * sizeof(float) : 0, s, ws,
                        budgets, H, G, d, splits, out);
   };
+  static_assert(kMostPieces <= 8 * 8, "a group for all pieces of a unit");
   if (splits <= 2) launch(decode_merge_kernel<2, 1>, 1);
   else if (splits <= 4) launch(decode_merge_kernel<4, 1>, 1);
   else if (splits <= 8) launch(decode_merge_kernel<8, 1>, 1);
