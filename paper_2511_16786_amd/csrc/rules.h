@@ -7,9 +7,9 @@ namespace fc {
 
 // Half turns of the residual kernel's workgroups in a round of `units` units: two for each of an XCD's 32 compute units take
 // its items, `windows` for each four units, one after the other.  The last turn of no more than 32 workgroups has a compute unit for
-// each and is over in half the time.  Rounds of 28, 32, ... 76 units of 32768 tokens, M = 3072 (22 windows for an XCD):
-// 124, 143, 158, 163, 187, 202, 207, 233, 246, 250, 279, 292, 318 us, all of them 22.4 to 23.3 us for a half turn but the first two
-// and the more the even: in 33rds of a half turn 32 for an odd number, 33 for an even one.
+// each and is over in half the time.  Rounds of 36, 40, ... 76 units of 32768 tokens, M = 3072 (22 windows for an XCD):
+// 158, 163, 187, 202, 207, 233, 246, 250, 279, 292, 318 us, 22.4 to 23.4 for each half turn.  An even number of them costs a
+// little more, since the last ones share compute units: 33 against 32.
 constexpr long long residual_cost(int units, int windows) {
   const long long halves = ((units + 3) / 4 * (long long)windows + 31) / 32;
   return halves * (halves % 2 ? 32 : 33);
