@@ -111,7 +111,8 @@ size_t flashcache_select_workspace_bytes(const fc_kv_desc* desc);
 
 /* One-time table construction for (N, r, path): the explicit basis alpha[m]*phi_N(m,i) of
  * Eq. 7, the twiddle tables of the streaming transform, or the window weights and factors of the resampled one.  Writes only
- * into `workspace` (device, 256-byte aligned, at least flashcache_workspace_bytes()).  The
+ * into `workspace` (device, 256-byte aligned, at least flashcache_workspace_bytes(), of which the
+ * resampled transform's grid, the points of one round of units, takes up to 240 MiB).  The
  * same workspace, shape, r and path must then be passed to flashcache_score; a workspace that
  * was prepared for something else makes the score kernels write nothing and raise the error
  * flag that flashcache_workspace_error() reports. */
@@ -154,7 +155,8 @@ fc_status flashcache_score_layer(const void* K, const void* V, const fc_kv_desc*
  * with Ehp.  Valid after flashcache_score on the same workspace with the same desc, r and path,
  * and before the workspace is used again.  (For r > N/2 the fast transform works on the dropped
  * modes; it then sums |C[m]|^2 over m >= r, Eq. 12's numerator as written, and returns the total
- * energy minus that sum.)
+ * energy minus that sum.)  It is added up in 32 bits by thread before it goes to 64: its last bits
+ * depend on how many units the call scored, unlike those of scores and energies.
  *   lowpass_energy  device out, double [B][L][H][2] = (K, V) */
 fc_status flashcache_lowpass_energy(const fc_kv_desc* desc, int32_t r, int32_t path, void* workspace,
                                     size_t workspace_bytes, double* lowpass_energy, void* hip_stream);

@@ -201,9 +201,9 @@ __global__ __launch_bounds__(kAllocThreads) void allocate_kernel(
 
 // The same rule for up to 64 layers, one wave per sequence and one layer per lane: no LDS and no barrier, and the
 // sums whose order is part of the definition take a layer's value from its lane's registers (a chain of additions,
-// where the kernel above waits for LDS at every term; 28 layers: 14 -> 4 us, all latency).  Lanes outside a sum add a zero, so that
-// its terms are fetched four at a time ahead of the additions, and the loads of four heads are under way together: with
-// events, an empty launch 6, 28 layers 8.2 / 7.0 us.
+// where the kernel above waits for LDS at every term; by the profile, 28 layers: 14 -> 5 to 7 us, 4 layers 5.4 -> 3.4, all
+// latency).  Lanes outside a sum add a zero, so that its terms are fetched four at a time ahead of the additions, and the loads
+// of four heads are under way together: 1.2 us less at 28 layers, 0.2 more at one or two.
 __device__ __forceinline__ double lane_value(double v, int l) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
                           __builtin_amdgcn_readlane(__double2loint(v), l));
