@@ -456,7 +456,8 @@ def test_decode_of_sequences_with_long_and_short_pieces(dtype, d, group, page):
         assert np.abs(out[b] - want).max() <= 5e-5 * float(np.abs(ref.widen(V[b], dtype)).max()), b
 
 
-# caches of more than 256 MB, whose rows are read past the last-level cache, and the same rows in small ones
+# few rows in buffers and pools of more than 256 MB, whose launches look at the budgets before they read past the last-level cache,
+# and the same rows in small ones
 @pytest.mark.parametrize("page", [0, 16])
 @pytest.mark.parametrize("dtype,d,group", [("bf16", 128, 7), ("bf16", 64, 4), ("f32", 64, 2)])
 def test_decode_of_large_caches_is_the_same_bits(dtype, d, group, page):
