@@ -643,3 +643,11 @@ def test_workspaces_at_any_multiple_of_256(n, r, d):
         out.append((scores, energy))
     for scores, energy in out[1:]:
         assert torch.equal(scores, out[0][0]) and torch.equal(energy, out[0][1])
+
+
+def test_calls_go_to_the_current_stream():
+    from paper_2511_16786_amd import binding
+    side = torch.cuda.Stream()
+    for stream in (torch.cuda.default_stream(), side, torch.cuda.default_stream()):
+        with torch.cuda.stream(stream):
+            assert binding._stream() == torch.cuda.current_stream().cuda_stream == stream.cuda_stream
