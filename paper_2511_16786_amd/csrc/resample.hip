@@ -1154,13 +1154,13 @@ constexpr int kResWorkgroups = 512;   // residual kernel: two for each compute u
 // banks): by the operands' lanes, 16 slots apart in memory, they took the address unit four times as long.  112 units, us
 // before / after: 32768 tokens M = 3072 460 / 448, M = 12288 729 / 683, 30011 tokens 526 / 507; one layer of 16384 21.5 / 18.0,
 // of which 1.6 for not loading a window after the last segment.
-template <typename T, bool KEEP, bool ONCE>
+template <typename T, bool KEEP, bool ONCE, int BUF>
 __global__ __launch_bounds__(256, 2) void residual_kernel(
     const T* __restrict__ K, const T* __restrict__ V, KvStrides st, int u0, int u1, int n, int r, int d, int dtype,
     int m, int tpw, int wins, SlotMap sm, bool split, WsHeader* hdr, const _Float16* __restrict__ winv,
     const float2* __restrict__ grid, float* __restrict__ scores,
     double* __restrict__ epart, UnitMap um) {
-  constexpr int kBuf = sizeof(T) == 2 ? 2 : 1;             // tiles of rows under way
+  constexpr int kBuf = sizeof(T) == 2 ? BUF : 1;           // tiles of rows under way
   __shared__ double part_sum[4][16 * kMaxTilesPerWin];
   __shared__ f32x4 turn_lds[4][4][64];                     // a wave's window on its way from loading to operand lanes
   const double inv_d = 1.0 / (double)d, inv_dd = (double)m / (double)n;
@@ -1189,7 +1189,8 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     s.win = w_first + it - set * w_count;
     s.n0 = __builtin_amdgcn_readfirstlane(first_point(16 * tpw * s.win, m, inv_dd, window_points(r, m))) >> 1;
     s.unit = min(u0 + abreast * set + my_unit, u1 - 1);    // (a surplus wave repeats the last unit)
-    s.tiles = max(min(tpw, tok_tiles - s.win * tpw), kBuf);   // (a tile too many is worked on and dropped)
+    s.tiles = min(tpw, tok_tiles - s.win * tpw);
+    if (!ONCE) s.tiles = max(s.tiles, kBuf);               // (a tile too many is worked on and dropped)
     const int mine = s.part * 16 + (lane & 15), slot = mine < 2 * sm.nb ? mine : 0;
     const bool second = slot >= sm.nb;
     s.rows = (second ? V : K) + unit_offset(st, s.unit) + (slot - (second ? sm.nb : 0)) * 8 + (int64_t)(4 * g) * st.sn;
@@ -1244,7 +1245,8 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
   load_weights(cur, 0);
   start_rows(cur);
 #pragma unroll
-  for (int k = 0; k < kBuf; ++k) load_rows(x[k]);
+  for (int k = 0; k < kBuf; ++k)
+    if (!ONCE || k < cur.tiles) load_rows(x[k]);
   if (ws_mismatch(hdr, FC_PATH_RESAMPLE, n, r, d, dtype)) return;     // (while the above is on its way)
   Seg nxt = following(cur);
   int tl = 0;
@@ -1603,7 +1605,11 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
       const int abreast = split ? 4 / lay.wpu : 4;
       const int64_t items = per_xcd * ((u1 - u0 + abreast - 1) / abreast);
       const bool once = (split || lay.wpu == 1) && items <= kResWorkgroups / 8;   // one segment for each wave at most
-      auto kern = once ? residual_kernel<T, KEEP, true> : residual_kernel<T, KEEP, false>;
+      // Windows of a single tile (token counts below 1.7 times the grid's): with a second tile under way each would be worked on
+      // twice.  Residual, two tiles / one under way: 28 layers of 8192 tokens, M = 6144 390 / 342 us, 4 layers 54 / 45, 28 of 4096,
+      // M = 3072 201 / 179.
+      auto kern = once ? residual_kernel<T, KEEP, true, 2>
+                       : (lay.tpw > 1 ? residual_kernel<T, KEEP, false, 2> : residual_kernel<T, KEEP, false, 1>);
       hipLaunchKernelGGL(kern, dim3(8 * (int)std::min<int64_t>(items, kResWorkgroups / 8)), dim3(256), 0, s, K, V, st, u0, u1, n, r,
                          d.head_dim, d.dtype, m, lay.tpw, lay.wins, sm, split, hdr, reinterpret_cast<const _Float16*>(base + lay.winv),
                          grid, scores, epart, um);

@@ -651,3 +651,26 @@ def test_calls_go_to_the_current_stream():
     for stream in (torch.cuda.default_stream(), side, torch.cuda.default_stream()):
         with torch.cuda.stream(stream):
             assert binding._stream() == torch.cuda.current_stream().cuda_stream == stream.cuda_stream
+
+
+def _scores_and_energies_follow_the_oracle(n, r, d, dtype, heads):
+    import paper_2511_16786_amd as fc
+    rng = np.random.default_rng(n + r + d)
+    K, V = (_smooth_plus_noise(rng, (1, 1, heads, n, d), dtype) for _ in range(2))
+    want = ref.score(K, V, dtype, r, route="fast")
+    comp = fc.Compressor(pu.to_torch(K, dtype), r, ref.total_budget(1, n, 0.2))
+    comp.run_score(pu.to_torch(K, dtype), pu.to_torch(V, dtype))
+    torch.cuda.synchronize()
+    assert fc.workspace_error(comp.workspace) == 0
+    pu.check_scores(comp.scores.cpu().numpy(), want["score"], pu.unit_power(ref.widen(K, dtype), ref.widen(V, dtype)))
+    e = comp.energy.cpu().numpy()
+    assert np.allclose(e[..., 2:], want["energy"][..., 2:], rtol=1e-5)
+    assert np.all(np.abs(e[..., :2] - want["energy"][..., :2]) <= 1e-4 * want["energy"][..., :2] + 1e-7 * want["energy"][..., 2:])
+
+
+# Windows of the residual kernel that hold a single tile (fewer than 1.7 tokens for each grid point), with more of them than
+# workgroups, the last unit's set not full and the last tile not whole
+@pytest.mark.parametrize("n,r,d,heads", [(4000, 1400, 64, 14), (2047, 1000, 128, 21), (2050, 880, 256, 18)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_windows_of_a_single_tile(n, r, d, heads, dtype):
+    _scores_and_energies_follow_the_oracle(n, r, d, dtype, heads)
