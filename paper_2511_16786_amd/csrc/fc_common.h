@@ -42,7 +42,7 @@ struct FftLayout {
 // ... and of the resampled realisation.
 struct ResampleLayout {
   int32_t m, steps, tpw, wins;    // grid points; 32-token steps per grid tile; 16-token tiles per window; windows
-  int32_t nb, wpu, chunk;         // 8-column blocks per tensor; waves per unit; units per round
+  int32_t pairs, nb, wpu, chunk;  // column pairs and 16-byte pieces of a row per tensor; waves per unit; units per round
   bool wide;                      // grid transform in 64 bits
   size_t wfwd, winv, filt, twid, elow, epart, grid, total;
 };

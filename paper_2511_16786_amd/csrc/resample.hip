@@ -319,13 +319,18 @@ __global__ __launch_bounds__(256) void resample_table_kernel(TablePtrs tp, int n
 
 // ---------------------------------------------------------------------------- decimation
 
-// The 2*nb column blocks (8 columns each) of a unit's K and V rows are dealt out to waves of 16 slots.
+// A lane's piece of a row is 16 bytes, so that a load takes whole lines; the 2*nb pieces of a unit's K and V rows are dealt out
+// to waves of 16 slots.  (With pieces of 8 columns for fp32 too, each load took every other 16 bytes of its lines, rows could not be read past
+// the cache, and a wave had twice the work: scoring, us, with 8 columns / with 4: 28 layers of 8192 tokens 582 / 551, 16 of
+// 20000, r = 4001 1126 / 1027, one layer of 13648, 64 columns 49.6 / 37.5, two heads of 512 27.3 / 22.3.)
+template <typename T>
+constexpr int kCols = 16 / (int)sizeof(T);
 struct SlotMap {
-  int nb;        // blocks per tensor (head_dim / 8)
-  int wpu;       // waves per unit: 1, 2 or 4
+  int nb;        // pieces per tensor (head_dim / kCols)
+  int wpu;       // waves per unit: 1, 2, 4 or 8
 };
 
-// 8 columns of one row, read with (KEEP) or without a claim on the last-level cache (see keep_rows).
+// A piece of one row, read with (KEEP) or without a claim on the last-level cache (see keep_rows).
 template <bool KEEP, typename V>
 __device__ __forceinline__ V load_piece(const void* p) {
   if constexpr (KEEP) return *static_cast<const V*>(p);
@@ -342,12 +347,9 @@ struct RowPiece<uint16_t> {
 };
 template <>
 struct RowPiece<float> {
-  f32x4 a, b;
+  f32x4 v;
   template <bool KEEP>
-  __device__ __forceinline__ void load(const float* p) {
-    a = load_piece<KEEP, f32x4>(p);
-    b = load_piece<KEEP, f32x4>(p + 4);
-  }
+  __device__ __forceinline__ void load(const float* p) { v = load_piece<KEEP, f32x4>(p); }
 };
 
 template <int CTRL>
@@ -381,9 +383,7 @@ __device__ __forceinline__ void bf16_terms(float a, float b, Frag (&t)[3], int h
 }
 __device__ __forceinline__ void column_frag(const RowPiece<float> (&x)[8], int j, Frag (&a)[3]) {
 #pragma unroll
-  for (int p = 0; p < 4; ++p)
-    bf16_terms(j < 4 ? x[2 * p].a[j & 3] : x[2 * p].b[j & 3], j < 4 ? x[2 * p + 1].a[j & 3] : x[2 * p + 1].b[j & 3],
-               a, p);
+  for (int p = 0; p < 4; ++p) bf16_terms(x[2 * p].v[j], x[2 * p + 1].v[j], a, p);
 }
 __device__ __forceinline__ f32x4 fold_column(const Frag (&a)[1], const Frag (&w)[3], f32x4 acc) {
 #pragma unroll
@@ -423,7 +423,8 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
     int m, int steps, SlotMap sm, int supers_per_xcd, WsHeader* hdr, const float* __restrict__ wfwd,
     float2* __restrict__ grid) {
   constexpr int kTerms = sizeof(T) == 2 ? 1 : 3;
-  constexpr int kBuf = sizeof(T) == 2 ? 2 : 1;    // steps of rows under way (a step's registers are refilled in place)
+  constexpr int C = kCols<T>;
+  constexpr int kBuf = 2;                         // steps of rows under way (a step's registers are refilled in place)
   extern __shared__ f32x4 wlds[];                 // [GT][steps][2][64]
   const int xcd = blockIdx.x & 7, slot_id = blockIdx.x >> 3;
   const int super = xcd * supers_per_xcd + slot_id % supers_per_xcd;
@@ -446,7 +447,7 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
     count[q] = q < n_tiles ? c : 0;
     s_end = first[q] + c;
   }
-  const T* p = (second ? V : K) + unit_offset(st, mine ? unit : u0) + (slot - (second ? sm.nb : 0)) * 8 +
+  const T* p = (second ? V : K) + unit_offset(st, mine ? unit : u0) + (slot - (second ? sm.nb : 0)) * C +
                (int64_t)(8 * (lane >> 4)) * st.sn;
   RowPiece<T> x[kBuf][8];
   auto load = [&](RowPiece<T> (&v)[8], int s) {
@@ -480,11 +481,11 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
   __syncthreads();
   if (!mine) return;
 
-  f32x4 acc[GT][8];
+  f32x4 acc[GT][C];
 #pragma unroll
   for (int q = 0; q < GT; ++q)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc[q][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < C; ++j) acc[q][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   auto step = [&](RowPiece<T> (&v)[8], int i) {
     const int s = s_from + dir * i;
 #pragma unroll
@@ -498,7 +499,7 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
         for (int h = 0; h < 4; ++h)
           bf16_terms(h < 2 ? wa[2 * h] : wb[2 * h - 4], h < 2 ? wa[2 * h + 1] : wb[2 * h - 3], w, h);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
+        for (int j = 0; j < C; ++j) {
           Frag a[kTerms];
           column_frag(v, j, a);
           acc[q][j] = fold_column(a, w, acc[q][j]);
@@ -528,12 +529,12 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int s_out = part * 16 + 4 * (lane >> 4) + i;
-      float2* o = grid + ((size_t)(unit - u0) * 2 * sm.nb + s_out) * 4 * m;
+      float2* o = grid + ((size_t)(unit - u0) * 2 * sm.nb + s_out) * (C / 2) * m;
       if constexpr (GT > 1) {
         const bool there = s_out < 2 * sm.nb && (!up || q + 1 < n_tiles);
         float2* t = o + grid_pos(k0 + 16 * (q + (up ? 1 : 0)), m);
 #pragma unroll
-        for (int jp = 0; jp < 4; ++jp) {
+        for (int jp = 0; jp < C / 2; ++jp) {
           const f32x4 w = both(make_float2(acc[q][2 * jp][i], acc[q][2 * jp + 1][i]),
                                make_float2(acc[q + 1][2 * jp][i], acc[q + 1][2 * jp + 1][i]));
           if (there) *reinterpret_cast<f32x4*>(t + (size_t)jp * m) = w;
@@ -541,7 +542,7 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
       } else {
         float2* t = o + grid_pos(k0, m) + (up ? m : 0);
 #pragma unroll
-        for (int jp = 0; jp < 4; jp += 2) {
+        for (int jp = 0; jp < C / 2; jp += 2) {
           const f32x4 w = both(make_float2(acc[q][2 * jp][i], acc[q][2 * jp + 1][i]),
                                make_float2(acc[q][2 * jp + 2][i], acc[q][2 * jp + 3][i]));
           if (s_out < 2 * sm.nb) *reinterpret_cast<f32x4*>(t + (size_t)jp * m) = w;
@@ -1082,9 +1083,9 @@ __global__ __launch_bounds__(SpreadPlan<M>::NT) void grid_spread_kernel(
 
 // ---------------------------------------------------------------------------- residual and score
 
-// squares of (row - inv * base) and of the row, 8 columns of token i of the tile
-__device__ __forceinline__ void residual8(const RowPiece<uint16_t>& x, const f32x4 (&acc)[8], int i, float inv,
-                                          float& hp, float& tot) {
+// squares of (row - inv * base) and of the row, a piece of token i of the tile
+__device__ __forceinline__ void residual_piece(const RowPiece<uint16_t>& x, const f32x4 (&acc)[8], int i, float inv,
+                                               float& hp, float& tot) {
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     const uint32_t w = x.v[c];
@@ -1095,14 +1096,13 @@ __device__ __forceinline__ void residual8(const RowPiece<uint16_t>& x, const f32
     tot = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(s16x2, w), __builtin_bit_cast(s16x2, w), tot, false);
   }
 }
-__device__ __forceinline__ void residual8(const RowPiece<float>& x, const f32x4 (&acc)[8], int i, float inv,
-                                          float& hp, float& tot) {
+__device__ __forceinline__ void residual_piece(const RowPiece<float>& x, const f32x4 (&acc)[4], int i, float inv,
+                                               float& hp, float& tot) {
 #pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    const float v = c < 4 ? x.a[c & 3] : x.b[c & 3];
-    const float dv = fmaf(-inv, acc[c][i], v);
+  for (int c = 0; c < 4; ++c) {
+    const float dv = fmaf(-inv, acc[c][i], x.v[c]);
     hp = fmaf(dv, dv, hp);
-    tot = fmaf(v, v, tot);
+    tot = fmaf(x.v[c], x.v[c], tot);
   }
 }
 
@@ -1160,7 +1160,8 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     int m, int tpw, int wins, SlotMap sm, bool split, WsHeader* hdr, const _Float16* __restrict__ winv,
     const float2* __restrict__ grid, float* __restrict__ scores,
     double* __restrict__ epart, UnitMap um) {
-  constexpr int kBuf = sizeof(T) == 2 ? BUF : 1;           // tiles of rows under way
+  constexpr int C = kCols<T>;
+  constexpr int kBuf = BUF;                                // tiles of rows under way
   __shared__ double part_sum[4][16 * kMaxTilesPerWin];
   __shared__ f32x4 turn_lds[4][4][64];                     // a wave's window on its way from loading to operand lanes
   const double inv_d = 1.0 / (double)d, inv_dd = (double)m / (double)n;
@@ -1193,10 +1194,10 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     if (!ONCE) s.tiles = max(s.tiles, kBuf);               // (a tile too many is worked on and dropped)
     const int mine = s.part * 16 + (lane & 15), slot = mine < 2 * sm.nb ? mine : 0;
     const bool second = slot >= sm.nb;
-    s.rows = (second ? V : K) + unit_offset(st, s.unit) + (slot - (second ? sm.nb : 0)) * 8 + (int64_t)(4 * g) * st.sn;
+    s.rows = (second ? V : K) + unit_offset(st, s.unit) + (slot - (second ? sm.nb : 0)) * C + (int64_t)(4 * g) * st.sn;
     s.score = scores + (size_t)out_unit(um, s.unit) * n;
     const int loaded = s.part * 16 + (lane >> 2);
-    s.gp = grid + ((size_t)(s.unit - u0) * 2 * sm.nb + (loaded < 2 * sm.nb ? loaded : 0)) * 4 * m + 2 * ((lane ^ (lane >> 3)) & 3);
+    s.gp = grid + ((size_t)(s.unit - u0) * 2 * sm.nb + (loaded < 2 * sm.nb ? loaded : 0)) * (C / 2) * m + 2 * ((lane ^ (lane >> 3)) & 3);
     return s;
   };
   bool follows;                                            // whether there is a segment after the one under way
@@ -1206,10 +1207,10 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     follows = !ONCE && it < items;
     return follows ? segment(it, pt) : s;
   };
-  f32x4 v[4][4];
+  f32x4 v[C / 2][4];
   auto load_window = [&](const Seg& s) {
 #pragma unroll
-    for (int jp = 0; jp < 4; ++jp)
+    for (int jp = 0; jp < C / 2; ++jp)
 #pragma unroll
       for (int c = 0; c < 4; ++c)
         v[jp][c] = *reinterpret_cast<const f32x4*>(s.gp + (size_t)jp * m + (c < 2 ? s.n0 + 8 * c : m - 32 - s.n0 + 8 * c));
@@ -1251,7 +1252,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
   Seg nxt = following(cur);
   int tl = 0;
   bool more = true;
-  Frag bh[8], bl[8];
+  Frag bh[C], bl[C];
   float inv = 0.f;
   double hp = 0.0, tot = 0.0;
 
@@ -1264,7 +1265,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
   };
   auto take_window = [&]() {
 #pragma unroll
-    for (int jp = 0; jp < 4; ++jp) {
+    for (int jp = 0; jp < C / 2; ++jp) {
 #pragma unroll
       for (int c = 0; c < 4; ++c) turn_lds[wave][c][lane] = v[jp][c];
       turned();
@@ -1274,7 +1275,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     }
     float mx = 0.f;
 #pragma unroll
-    for (int jp = 0; jp < 4; ++jp)
+    for (int jp = 0; jp < C / 2; ++jp)
 #pragma unroll
       for (int c = 0; c < 4; ++c)
 #pragma unroll
@@ -1287,7 +1288,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     const float scale = __uint_as_float((uint32_t)(268 - eb) << 23);
     inv = ldexpf(1.0f / kInvWeightScale, eb - 141);
 #pragma unroll
-    for (int jp = 0; jp < 4; ++jp)
+    for (int jp = 0; jp < C / 2; ++jp)
 #pragma unroll
       for (int c = 0; c < 4; ++c)
 #pragma unroll
@@ -1299,7 +1300,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
         }
     // (the operands are made here, before their sources' registers are loaded again)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) asm volatile("" : "+v"(bh[j].u), "+v"(bl[j].u));
+    for (int j = 0; j < C; ++j) asm volatile("" : "+v"(bh[j].u), "+v"(bl[j].u));
     hp = tot = 0.0;
     if (!ONCE && follows) load_window(nxt);
   };
@@ -1316,9 +1317,9 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
   };
   auto step = [&](RowPiece<T> (&xb)[4]) {
     if (tl == 0) take_window();
-    f32x4 acc[8];
+    f32x4 acc[C];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < C; ++j) {
       acc[j] = mfma_f16(wn[1], bl[j], f32x4{0.f, 0.f, 0.f, 0.f});
       acc[j] = mfma_f16(wn[2], bh[j], acc[j]);
       acc[j] = mfma_f16(wn[0], bl[j], acc[j]);
@@ -1333,7 +1334,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       h[i] = t[i] = 0.f;
-      residual8(xb[i], acc, i, inv, h[i], t[i]);
+      residual_piece(xb[i], acc, i, inv, h[i], t[i]);
     }
     // tokens past the end, tiles past the window's own (they are the next window's) and slots past the last
     if (t0 + 16 > n || tl >= tpw || cur.part * 16 + 16 > 2 * sm.nb) {
@@ -1463,6 +1464,8 @@ static bool wide_transform(int64_t n, int64_t r, int64_t m) { return m <= 4096 &
 // (below 256 tokens the products with the basis itself are as quick and need no plan worth speaking of)
 bool resample_supported(const fc_kv_desc& d, int32_t r) { return d.n_tokens >= 256 && grid_length(d, r) != 0; }
 
+static int waves_per_unit(int nb) { return nb <= 8 ? 1 : (nb <= 16 ? 2 : (nb <= 32 ? 4 : 8)); }
+
 ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
   ResampleLayout lay{};
   const int64_t n = d.n_tokens, m = grid_length(d, r);
@@ -1477,9 +1480,9 @@ ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
   lay.tpw = (int)std::min<int64_t>(kMaxTilesPerWin, (((29 - w) * n - 1) / m + 1) / 16);
   const int tok_tiles = (int)((n + 15) / 16);
   lay.wins = (tok_tiles + lay.tpw - 1) / lay.tpw;
-  lay.nb = d.head_dim / 8;
-  const int waves = (2 * lay.nb + 15) / 16;
-  lay.wpu = waves <= 2 ? waves : 4;
+  lay.pairs = d.head_dim / 2;
+  lay.nb = d.head_dim * (d.dtype == FC_BF16 ? 2 : 4) / 16;
+  lay.wpu = waves_per_unit(lay.nb);
   // units per round of the three kernels
   const size_t unit_grid = 2 * (size_t)m * d.head_dim * sizeof(float);
   const bool much_grid = (size_t)n * (d.dtype == FC_BF16 ? 2 : 4) < 2 * (size_t)m * sizeof(float);
@@ -1491,10 +1494,10 @@ ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
   lay.winv = off; off = up(off + (size_t)lay.wins * lay.tpw * 1536 * 2);
   lay.filt = off; off = up(off + (size_t)m * sizeof(float2));
   lay.twid = off; off = up(off + (size_t)twid_size((int)m, lay.wide) * (lay.wide ? sizeof(double2) : sizeof(float2)));
-  lay.elow = off; off = up(off + units * 2 * lay.nb * 4 * sizeof(double));
+  lay.elow = off; off = up(off + units * 2 * lay.pairs * sizeof(double));
   lay.epart = off; off = up(off + units * lay.wins * lay.wpu * 4 * sizeof(double));
   // (room for the most units of a round: fewer units than these may make a round longer than theirs)
-  lay.grid = off; off = up(off + kGridSlack + std::min<size_t>(units, most) * 2 * lay.nb * 4 * m * sizeof(float2));
+  lay.grid = off; off = up(off + kGridSlack + std::min<size_t>(units, most) * 2 * lay.pairs * m * sizeof(float2));
   lay.total = off;
   return lay;
 }
@@ -1506,7 +1509,7 @@ size_t resample_reserve(const fc_kv_desc& d) {
   const size_t n = d.n_tokens, nb = d.head_dim / 8, units = (size_t)d.batch * d.layers * d.kv_heads;
   const size_t m = std::min<size_t>(16384, n * 5 / 4);
   const size_t tables = 296 * n + 288 * m + (256 << 10);
-  const size_t records = units * (64 * nb + 2 * n * (nb <= 8 ? 1 : (nb <= 16 ? 2 : 4)) + 64 * 4);
+  const size_t records = units * (64 * nb + 2 * n * waves_per_unit((int)nb * (d.dtype == FC_BF16 ? 1 : 2)) + 64 * 8);
   const size_t grid = std::max<size_t>(kRoundGridBytes, 64 * nb * m);
   const size_t need = tables + records + std::min<size_t>(grid, units * 64 * nb * m);
   const size_t have = units * 2 * (nb / 2) * n * sizeof(float);
@@ -1548,7 +1551,7 @@ static hipError_t launch_decimate_gt(const T* K, const T* V, KvStrides st, int u
 
 // Tiles per wave: four while two workgroups' weights fit a compute unit's 160 KB of LDS (10 steps, N/M up to 11; two
 // tiles there: 519 instead of 473 us at 32768 tokens, M = 3072) and the launch still has several workgroups for each
-// of them, else two or one.  fp32 rows leave registers for two.
+// of them, else two or one.
 template <typename T, bool KEEP>
 static hipError_t launch_decimate(const T* K, const T* V, KvStrides st, int u0, int u1, int n, int r,
                                   const fc_kv_desc& d, int m, const ResampleLayout& lay, SlotMap sm, WsHeader* hdr,
@@ -1557,8 +1560,7 @@ static hipError_t launch_decimate(const T* K, const T* V, KvStrides st, int u0, 
   auto fits = [&](int gt) {
     return gt * lay.steps * 2048 <= 80 * 1024 && (int64_t)(m / 16 / gt) * groups >= kMinWorkgroups;
   };
-  if constexpr (sizeof(T) == 2)
-    if (fits(4)) return launch_decimate_gt<T, 4, KEEP>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, grid, s);
+  if (fits(4)) return launch_decimate_gt<T, 4, KEEP>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, grid, s);
   if (fits(2)) return launch_decimate_gt<T, 2, KEEP>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, grid, s);
   return launch_decimate_gt<T, 1, KEEP>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, grid, s);
 }
@@ -1582,8 +1584,8 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
     hipError_t e = launch_decimate<T, KEEP>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr,
                                       reinterpret_cast<const float*>(base + lay.wfwd), grid, s);
     if (e != hipSuccess) return e;
-    double* elow = reinterpret_cast<double*>(base + lay.elow) + (size_t)u0 * 2 * lay.nb * 4;
-    const int pairs = (u1 - u0) * 2 * lay.nb * 4;
+    double* elow = reinterpret_cast<double*>(base + lay.elow) + (size_t)u0 * 2 * lay.pairs;
+    const int pairs = (u1 - u0) * 2 * lay.pairs;
 #define FC_FILTER(MV, WIDE) launch_filter<MV, WIDE>(grid, pairs, n, r, d.head_dim, d.dtype, hdr, filt, twid, elow, s)
 #define FC_NARROW(MV) case MV: e = FC_FILTER(MV, false); break;
 #define FC_EITHER(MV) case MV: e = lay.wide ? FC_FILTER(MV, true) : FC_FILTER(MV, false); break;
@@ -1601,7 +1603,7 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
     {
       ProfileScope ps("residual_kernel", s);
       const int64_t per_xcd = (lay.wins + 7) / 8;          // windows of the XCD with most
-      const bool split = lay.wpu > 1 && per_xcd * ((u1 - u0 + 3) / 4) < kResWorkgroups / 8;
+      const bool split = lay.wpu > 1 && lay.wpu <= 4 && per_xcd * ((u1 - u0 + 3) / 4) < kResWorkgroups / 8;
       const int abreast = split ? 4 / lay.wpu : 4;
       const int64_t items = per_xcd * ((u1 - u0 + abreast - 1) / abreast);
       const bool once = (split || lay.wpu == 1) && items <= kResWorkgroups / 8;   // one segment for each wave at most
@@ -1620,12 +1622,12 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
   return energy_reduce_launch(epart, lay.wins * lay.wpu, units, energy, um, s);
 }
 
-// Whether a round's bf16 rows fit the last-level cache, to be found there on their second reading; else they are read
+// Whether a round's rows fit the last-level cache, to be found there on their second reading; else they are read
 // without a claim on it, which leaves it to the grid.  Scoring, kept / not kept: 246 MB of rows 168 / 182 us, 268 MB
-// 234 / 232, 470 MB 413 / 377, 738 MB 516 / 457; 34 MB 50 / 60.  (fp32 rows are read in half lines, which do not
-// survive until the other half is asked for: 604 MB 390 / 424.)
+// 234 / 232, 470 MB 413 / 377, 738 MB 516 / 457; 34 MB 50 / 60.  fp32: 940 MB 575 / 558, 560 MB 1093 / 1040 (in rounds), 34 MB
+// 114 / 126, 7 MB 38 / 44.
 static bool keep_rows(const fc_kv_desc& d, const ResampleLayout& lay) {
-  return (size_t)lay.chunk * 2 * d.n_tokens * d.head_dim * sizeof(uint16_t) <= (size_t)256 * 1000 * 1000;
+  return (size_t)lay.chunk * 2 * d.n_tokens * d.head_dim * (d.dtype == FC_BF16 ? 2 : 4) <= (size_t)256 * 1000 * 1000;
 }
 
 hipError_t resample_score(const void* K, const void* V, const fc_kv_desc& d, int32_t r, const ResampleLayout& lay,
@@ -1635,14 +1637,15 @@ hipError_t resample_score(const void* K, const void* V, const fc_kv_desc& d, int
     const uint16_t *k = static_cast<const uint16_t*>(K), *v = static_cast<const uint16_t*>(V);
     return keep_rows(d, lay) ? run(resample_score_t<uint16_t, true>, k, v) : run(resample_score_t<uint16_t, false>, k, v);
   }
-  return run(resample_score_t<float, true>, static_cast<const float*>(K), static_cast<const float*>(V));
+  const float *k = static_cast<const float*>(K), *v = static_cast<const float*>(V);
+  return keep_rows(d, lay) ? run(resample_score_t<float, true>, k, v) : run(resample_score_t<float, false>, k, v);
 }
 
 hipError_t resample_lowpass(const fc_kv_desc& d, const ResampleLayout& lay, void* ws, double* lowpass, hipStream_t s) {
   const int n_ut = d.batch * d.layers * d.kv_heads * 2;
   ProfileScope ps("resample_lowpass_kernel", s);
   hipLaunchKernelGGL(resample_lowpass_kernel, dim3((n_ut + 255) / 256), dim3(256), 0, s,
-                     reinterpret_cast<const double*>(static_cast<char*>(ws) + lay.elow), lay.nb * 4, n_ut, lowpass);
+                     reinterpret_cast<const double*>(static_cast<char*>(ws) + lay.elow), lay.pairs, n_ut, lowpass);
   return hipGetLastError();
 }
 

@@ -674,3 +674,11 @@ def _scores_and_energies_follow_the_oracle(n, r, d, dtype, heads):
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_windows_of_a_single_tile(n, r, d, heads, dtype):
     _scores_and_energies_follow_the_oracle(n, r, d, dtype, heads)
+
+
+# fp32 rows come in pieces of four columns: 1, 2, 4 and 8 waves per unit, whole and partly filled, tensors that meet inside a
+# wave and between two; few units (a workgroup's waves take a unit's parts side by side) and more
+@pytest.mark.parametrize("d", [8, 32, 40, 64, 104, 128, 136, 248, 256])
+@pytest.mark.parametrize("n,r,heads", [(1500, 150, 3), (3100, 150, 37)])
+def test_fp32_rows_of_every_width(d, n, r, heads):
+    _scores_and_energies_follow_the_oracle(n, r, d, "f32", heads)
