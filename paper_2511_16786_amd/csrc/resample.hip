@@ -420,18 +420,20 @@ constexpr int kDecWaves = 4;          // waves of a workgroup: 4 slots' worth of
 template <typename T, int GT, bool KEEP>
 __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
     const T* __restrict__ K, const T* __restrict__ V, KvStrides st, int u0, int u1, int n, int r, int d, int dtype,
-    int m, int steps, SlotMap sm, int supers_per_xcd, WsHeader* hdr, const float* __restrict__ wfwd,
+    int m, int steps, SlotMap sm, int groups, int along, WsHeader* hdr, const float* __restrict__ wfwd,
     float2* __restrict__ grid) {
   constexpr int kTerms = sizeof(T) == 2 ? 1 : 3;
   constexpr int C = kCols<T>;
   constexpr int kBuf = 2;                         // steps of rows under way (a step's registers are refilled in place)
   extern __shared__ f32x4 wlds[];                 // [GT][steps][2][64]
-  const int xcd = blockIdx.x & 7, slot_id = blockIdx.x >> 3;
-  const int super = xcd * supers_per_xcd + slot_id % supers_per_xcd;
-  if (super >= (m / 16 + GT - 1) / GT) return;
+  const int slot_id = blockIdx.x >> 3;
+  const Span mine_t = xcd_first(blockIdx.x & 7, along, (m / 16 + GT - 1) / GT), mine_g = xcd_second(blockIdx.x & 7, along, groups);
+  if (slot_id >= mine_t.count * mine_g.count) return;
+  const int row = (unsigned)slot_id / (unsigned)mine_t.count;
+  const int group = mine_g.from + row, super = mine_t.from + slot_id - row * mine_t.count;
   const int tile0 = super * GT, n_tiles = min(GT, m / 16 - tile0);
   const int lane = threadIdx.x & 63;
-  const int gw = (slot_id / supers_per_xcd) * kDecWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int gw = group * kDecWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int unit = u0 + gw / sm.wpu, part = gw % sm.wpu;
   const bool mine = unit < u1;
   const int s_mine = part * 16 + (lane & 15);
@@ -1157,7 +1159,7 @@ constexpr int kResWorkgroups = 512;   // residual kernel: two for each compute u
 template <typename T, bool KEEP, bool ONCE, int BUF>
 __global__ __launch_bounds__(256, 2) void residual_kernel(
     const T* __restrict__ K, const T* __restrict__ V, KvStrides st, int u0, int u1, int n, int r, int d, int dtype,
-    int m, int tpw, int wins, SlotMap sm, bool split, WsHeader* hdr, const _Float16* __restrict__ winv,
+    int m, int tpw, int wins, SlotMap sm, bool split, int along, WsHeader* hdr, const _Float16* __restrict__ winv,
     const float2* __restrict__ grid, float* __restrict__ scores,
     double* __restrict__ epart, UnitMap um) {
   constexpr int C = kCols<T>;
@@ -1171,9 +1173,9 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
   const int abreast = split ? 4 / sm.wpu : 4, parts = split ? 1 : sm.wpu;
   const int my_unit = split ? wave / sm.wpu : wave, my_part = split ? wave % sm.wpu : 0;
   const int sets = (u1 - u0 + abreast - 1) / abreast, tok_tiles = (n + 15) >> 4;
-  const int xcd = blockIdx.x & 7, peers = gridDim.x >> 3;
-  const int w_first = (int)((int64_t)wins * xcd >> 3), w_count = (int)((int64_t)wins * (xcd + 1) >> 3) - w_first;
-  const int items = w_count * sets;
+  const int peers = gridDim.x >> 3;
+  const Span mine_w = xcd_first(blockIdx.x & 7, along, wins), mine_s = xcd_second(blockIdx.x & 7, along, sets);
+  const int items = mine_w.count * mine_s.count;
   int item = blockIdx.x >> 3, part = 0;                    // segment under way
   if (item >= items) return;
 
@@ -1186,8 +1188,8 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
   auto segment = [&](int it, int pt) {
     Seg s;
     s.part = my_part + pt;
-    const int set = (unsigned)it / (unsigned)w_count;
-    s.win = w_first + it - set * w_count;
+    const int row = (unsigned)it / (unsigned)mine_w.count, set = mine_s.from + row;
+    s.win = mine_w.from + it - row * mine_w.count;
     s.n0 = __builtin_amdgcn_readfirstlane(first_point(16 * tpw * s.win, m, inv_dd, window_points(r, m))) >> 1;
     s.unit = min(u0 + abreast * set + my_unit, u1 - 1);    // (a surplus wave repeats the last unit)
     s.tiles = min(tpw, tok_tiles - s.win * tpw);
@@ -1532,8 +1534,8 @@ hipError_t resample_prepare(const fc_kv_desc& d, int32_t r, const ResampleLayout
 
 template <typename T, int GT, bool KEEP>
 static hipError_t launch_decimate_gt(const T* K, const T* V, KvStrides st, int u0, int u1, int n, int r,
-                                     const fc_kv_desc& d, int m, const ResampleLayout& lay, SlotMap sm, WsHeader* hdr,
-                                     const float* wfwd, float2* grid, hipStream_t s) {
+                                     const fc_kv_desc& d, int m, const ResampleLayout& lay, SlotMap sm, Sides sides, int along,
+                                     WsHeader* hdr, const float* wfwd, float2* grid, hipStream_t s) {
   auto kern = decimate_kernel<T, GT, KEEP>;
   const size_t lds = (size_t)GT * lay.steps * 2048;
   if (lds > 64 * 1024) {
@@ -1541,28 +1543,20 @@ static hipError_t launch_decimate_gt(const T* K, const T* V, KvStrides st, int u
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  const int supers = (m / 16 + GT - 1) / GT, spx = (supers + 7) / 8;
-  const int groups = ((u1 - u0) * sm.wpu + kDecWaves - 1) / kDecWaves;
   ProfileScope ps("decimate_kernel", s);
-  hipLaunchKernelGGL(kern, dim3(8 * spx * groups), dim3(64 * kDecWaves), lds, s, K, V, st, u0, u1, n, r, d.head_dim,
-                     d.dtype, m, lay.steps, sm, spx, hdr, wfwd, grid);
+  hipLaunchKernelGGL(kern, dim3(8 * xcd_items(along, sides)), dim3(64 * kDecWaves), lds, s, K, V, st, u0, u1, n, r, d.head_dim,
+                     d.dtype, m, lay.steps, sm, sides.second, along, hdr, wfwd, grid);
   return hipGetLastError();
 }
 
 // Tiles per wave: four while two workgroups' weights fit a compute unit's 160 KB of LDS (10 steps, N/M up to 11; two
 // tiles there: 519 instead of 473 us at 32768 tokens, M = 3072) and the launch still has several workgroups for each
 // of them, else two or one.
-template <typename T, bool KEEP>
-static hipError_t launch_decimate(const T* K, const T* V, KvStrides st, int u0, int u1, int n, int r,
-                                  const fc_kv_desc& d, int m, const ResampleLayout& lay, SlotMap sm, WsHeader* hdr,
-                                  const float* wfwd, float2* grid, hipStream_t s) {
-  const int groups = ((u1 - u0) * sm.wpu + kDecWaves - 1) / kDecWaves;
+static int decimate_tiles(int m, int groups, int steps) {
   auto fits = [&](int gt) {
-    return gt * lay.steps * 2048 <= 80 * 1024 && (int64_t)(m / 16 / gt) * groups >= kMinWorkgroups;
+    return gt * steps * 2048 <= 80 * 1024 && (int64_t)(m / 16 / gt) * groups >= kMinWorkgroups;
   };
-  if (fits(4)) return launch_decimate_gt<T, 4, KEEP>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, grid, s);
-  if (fits(2)) return launch_decimate_gt<T, 2, KEEP>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, grid, s);
-  return launch_decimate_gt<T, 1, KEEP>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr, wfwd, grid, s);
+  return fits(4) ? 4 : (fits(2) ? 2 : 1);
 }
 
 template <typename T, bool KEEP>
@@ -1581,8 +1575,16 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
   // and the rows neighbouring tiles share
   for (int u0 = 0; u0 < units; u0 += lay.chunk) {
     const int u1 = std::min(units, u0 + lay.chunk);
-    hipError_t e = launch_decimate<T, KEEP>(K, V, st, u0, u1, n, r, d, m, lay, sm, hdr,
-                                      reinterpret_cast<const float*>(base + lay.wfwd), grid, s);
+    // the residual's waves take the parts of a unit side by side, where workgroups of four units' windows leave an XCD's without work
+    const int groups = ((u1 - u0) * sm.wpu + kDecWaves - 1) / kDecWaves, gt = decimate_tiles(m, groups, lay.steps);
+    const Sides dec{(m / 16 + gt - 1) / gt, groups}, fours{lay.wins, (u1 - u0 + 3) / 4};
+    const bool split = lay.wpu > 1 && lay.wpu <= 4 && xcd_items(xcds_along(dec, fours), fours) < kResWorkgroups / 8;
+    const int abreast = split ? 4 / lay.wpu : 4;
+    const Sides res{lay.wins, (u1 - u0 + abreast - 1) / abreast};
+    const int along = xcds_along(dec, res);
+    const float* wfwd = reinterpret_cast<const float*>(base + lay.wfwd);
+    auto decimate = gt == 4 ? launch_decimate_gt<T, 4, KEEP> : (gt == 2 ? launch_decimate_gt<T, 2, KEEP> : launch_decimate_gt<T, 1, KEEP>);
+    hipError_t e = decimate(K, V, st, u0, u1, n, r, d, m, lay, sm, dec, along, hdr, wfwd, grid, s);
     if (e != hipSuccess) return e;
     double* elow = reinterpret_cast<double*>(base + lay.elow) + (size_t)u0 * 2 * lay.pairs;
     const int pairs = (u1 - u0) * 2 * lay.pairs;
@@ -1602,18 +1604,15 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
     if (e != hipSuccess) return e;
     {
       ProfileScope ps("residual_kernel", s);
-      const int64_t per_xcd = (lay.wins + 7) / 8;          // windows of the XCD with most
-      const bool split = lay.wpu > 1 && lay.wpu <= 4 && per_xcd * ((u1 - u0 + 3) / 4) < kResWorkgroups / 8;
-      const int abreast = split ? 4 / lay.wpu : 4;
-      const int64_t items = per_xcd * ((u1 - u0 + abreast - 1) / abreast);
+      const int items = xcd_items(along, res);
       const bool once = (split || lay.wpu == 1) && items <= kResWorkgroups / 8;   // one segment for each wave at most
       // Windows of a single tile (token counts below 1.7 times the grid's): with a second tile under way each would be worked on
       // twice.  Residual, two tiles / one under way: 28 layers of 8192 tokens, M = 6144 390 / 342 us, 4 layers 54 / 45, 28 of 4096,
       // M = 3072 201 / 179.
       auto kern = once ? residual_kernel<T, KEEP, true, 2>
                        : (lay.tpw > 1 ? residual_kernel<T, KEEP, false, 2> : residual_kernel<T, KEEP, false, 1>);
-      hipLaunchKernelGGL(kern, dim3(8 * (int)std::min<int64_t>(items, kResWorkgroups / 8)), dim3(256), 0, s, K, V, st, u0, u1, n, r,
-                         d.head_dim, d.dtype, m, lay.tpw, lay.wins, sm, split, hdr, reinterpret_cast<const _Float16*>(base + lay.winv),
+      hipLaunchKernelGGL(kern, dim3(8 * std::min(items, kResWorkgroups / 8)), dim3(256), 0, s, K, V, st, u0, u1, n, r,
+                         d.head_dim, d.dtype, m, lay.tpw, lay.wins, sm, split, along, hdr, reinterpret_cast<const _Float16*>(base + lay.winv),
                          grid, scores, epart, um);
     }
     e = hipGetLastError();

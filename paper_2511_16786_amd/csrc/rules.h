@@ -37,6 +37,37 @@ constexpr int round_units(int units, int most, int windows) {
   return best;
 }
 
+// The row kernels' work are rectangles, tiles or windows along one side and groups of units along the other.  Each of the 8 XCDs takes a
+// rectangle of its own: neighbours along the first side share rows, weights and lines of the grid, which its L2 then holds.  The first
+// side is cut for 2^xcds_along XCDs, all 8 if it can be, fewer where that makes the two kernels' largest rectangles smaller by
+// more than a sixteenth: a short sequence has fewer tiles or windows than XCDs, or a few more.  The cut is the same for both, so that
+// an XCD's L2 has the second kernel's rows where they fit (4 layers of 4096 tokens, cut for 8 and for 4: 43 us, both for 8 42).
+// Scoring, us, cut for 8 always / now: 720 units of 1024 tokens, 64 columns 215 / 145, 128 of 512, 128 columns 51 / 40, 112 of 4096 205 /
+// 184, 248 of 1938 219 / 204.
+struct Sides { int first, second; };
+constexpr int xcd_items(int along, Sides r) {               // of the largest rectangle
+  return ((r.first + (1 << along) - 1) >> along) * ((r.second + (8 >> along) - 1) >> (3 - along));
+}
+constexpr int xcds_along(Sides a, Sides b) {
+  const long long all_a = (long long)a.first * a.second, all_b = (long long)b.first * b.second;
+  int best = 3;
+  long long least = xcd_items(3, a) * all_b + xcd_items(3, b) * all_a;
+  for (int along = 2; along >= 0; --along) {
+    const long long cost = xcd_items(along, a) * all_b + xcd_items(along, b) * all_a;
+    if (16 * cost < 15 * least) { best = along; least = cost; }
+  }
+  return best;
+}
+struct Span { int from, count; };
+constexpr Span xcd_first(int xcd, int along, int first) {
+  const int a = xcd & ((1 << along) - 1), from = first * a >> along;
+  return {from, (first * (a + 1) >> along) - from};
+}
+constexpr Span xcd_second(int xcd, int along, int second) {
+  const int b = xcd >> along, from = second * b >> (3 - along);
+  return {from, (second * (b + 1) >> (3 - along)) - from};
+}
+
 // Where the grid begins in its region of a workspace, both at multiples of 256 bytes: an odd multiple, whatever the
 // workspace's own address is.  A grid at a multiple of 512 costs the residual kernel a tenth where M is a power of two (28 layers of
 // 4096 tokens, M = 4096: 182 us at 128, 256, 768, 1280 and 2304 bytes past a multiple of 4096, 204 at 0 and 512).

@@ -16,6 +16,12 @@ int round_units(int units, int most, int windows) { return fc::round_units(units
 long long residual_cost(int units, int windows) { return fc::residual_cost(units, windows); }
 unsigned long long grid_start(unsigned long long at) { return fc::grid_start(at); }
 unsigned long long grid_slack() { return fc::kGridSlack; }
+int xcd_items(int along, int first, int second) { return fc::xcd_items(along, {first, second}); }
+int xcds_along(int f1, int s1, int f2, int s2) { return fc::xcds_along({f1, s1}, {f2, s2}); }
+void xcd_rectangle(int xcd, int along, int first, int second, int* out) {
+  const fc::Span a = fc::xcd_first(xcd, along, first), b = fc::xcd_second(xcd, along, second);
+  out[0] = a.from; out[1] = a.count; out[2] = b.from; out[3] = b.count;
+}
 bool keeps_rows(long long rows, int row_bytes) { return fc::keeps_rows(rows, row_bytes); }
 bool ranks_by_budget(long long rows, int layers, int splits, int row_bytes) { return fc::ranks_by_budget(rows, layers, splits, row_bytes); }
 }
@@ -86,3 +92,24 @@ def test_grids_begin_at_odd_multiples_of_256_wherever_a_workspace_begins(rules):
         for region in range(0, 2048, 256):
             at = rules.grid_start(base + region)
             assert at % 512 == 256 and 0 <= at - base - region <= rules.grid_slack()
+
+
+def test_xcds_take_rectangles_that_cover_the_work(rules):
+    out = (ctypes.c_int * 4)()
+    for first, second in ((1, 1), (3, 180), (5, 1), (7, 9), (11, 23), (48, 30), (86, 28), (158, 15), (16384, 1), (1, 8192)):
+        for along in range(4):
+            at, most = [], 0
+            for xcd in range(8):
+                rules.xcd_rectangle(xcd, along, first, second, out)
+                f, nf, s, ns = out
+                assert nf >= 0 and ns >= 0 and f + nf <= first and s + ns <= second
+                most = max(most, nf * ns)
+                at.append((f, nf, s, ns))
+            assert most == rules.xcd_items(along, first, second)          # (what a launch has workgroups for)
+            assert sum(nf * ns for _, nf, _, ns in at) == first * second
+            for i, (f, nf, s, ns) in enumerate(at):                       # (no two meet)
+                for g, ng, t, nt in at[:i]:
+                    assert f + nf <= g or g + ng <= f or s + ns <= t or t + nt <= s or not nf * ns * ng * nt
+    # long sequences are cut along the tokens for all XCDs, short ones along the units as well
+    assert [rules.xcds_along(*x) for x in ((48, 30, 158, 15), (96, 20, 376, 10), (24, 56, 86, 28), (48, 8, 43, 8))] == [3, 3, 3, 3]
+    assert [rules.xcds_along(*x) for x in ((3, 180, 11, 180), (2, 32, 6, 32), (12, 56, 43, 28))] == [0, 1, 2]

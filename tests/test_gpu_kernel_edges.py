@@ -682,3 +682,11 @@ def test_windows_of_a_single_tile(n, r, d, heads, dtype):
 @pytest.mark.parametrize("n,r,heads", [(1500, 150, 3), (3100, 150, 37)])
 def test_fp32_rows_of_every_width(d, n, r, heads):
     _scores_and_energies_follow_the_oracle(n, r, d, "f32", heads)
+
+
+# Short sequences, whose tiles and windows are fewer than XCDs or a few more, of few units and of many
+@pytest.mark.parametrize("n,r,d,heads", [(300, 20, 64, 3), (512, 50, 128, 33), (700, 70, 64, 90), (1024, 91, 64, 140), (1938, 220, 128, 31),
+                                         (4096, 410, 32, 60)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_short_sequences(n, r, d, heads, dtype):
+    _scores_and_energies_follow_the_oracle(n, r, d, dtype, heads)
