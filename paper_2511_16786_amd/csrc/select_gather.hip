@@ -6,7 +6,7 @@
 //   equal to it are still needed; a compaction in token order (prefix counts) then writes the kept
 //   indices, which yields them ascending and gives ties to the lower index without any sort.  Up to
 //   65536 tokens the keys stay in registers between the passes; beyond that they are re-read from L2.
-//   Only integer atomics are used (LDS histogram), so the result is deterministic.
+//   Only integer atomics are used (LDS histogram), so the result is deterministic.  Small launches copy the rows as well.
 // gather_kernel: rows are bit copies, 16 bytes a thread; one lookup a row.
 #include <algorithm>
 
@@ -173,21 +173,63 @@ __device__ __forceinline__ unsigned below_me(unsigned long long mask, unsigned a
 __device__ __forceinline__ unsigned uniform(unsigned v) { return (unsigned)__builtin_amdgcn_readfirstlane((int)v); }
 
 typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
 
-template <bool SHARED, int NT, int MAXC>
+// Destination of the paged variant: kept row j of unit (b,l,h) goes to slot j % page_size of page
+// block_table[b][l][h][j / page_size] of caches laid out [num_pages][page_size][d].
+struct PagedDst {
+  const int* block_table;
+  int page_size, max_pages;
+  long long num_pages;
+};
+
+// What the selection needs to copy the rows as well.
+struct CopyArgs {
+  const char *K, *V;
+  KvStrides st;
+  int lists, elem_bytes, vec_per_row, vpr_shift;
+  char *K_out, *V_out;
+  PagedDst pg;
+};
+
+// The index set that a workgroup works on, and which of how many shares of its kept rows.  A set has as many workgroups as
+// its budget takes of equal shares of all sets' rows (one layer: budgets are alike); there are no more than 64 sets, a
+// lane each.
+struct Share {
+  int list, at, of;
+};
+__device__ __forceinline__ Share share_of(int g, int all, int lists, int L, int sets_per_budget, int n, const int* __restrict__ budgets) {
+  if (L == 1) return {g % lists, g / lists, all / lists};
+  const int lane = threadIdx.x & 63;
+  const unsigned k = lane < lists ? (unsigned)min(max(budgets[lane / sets_per_budget], 0), n) : 0u;
+  const unsigned total = (unsigned)__builtin_amdgcn_readlane((int)wave_incl_scan(k), 63), spare = (unsigned)(all - lists);
+  const unsigned rows = max(1u, (total + spare - 1) / spare), mine = (k + rows - 1) / rows, upto = wave_incl_scan(mine);
+  const unsigned long long behind = __ballot(upto > (unsigned)g);
+  if (!behind) return {0, 0, 0};
+  const int list = __builtin_ctzll(behind), of = __builtin_amdgcn_readlane((int)mine, list);
+  return {list, g - __builtin_amdgcn_readlane((int)upto, list) + of, of};
+}
+
+// COPY: workgroups that have a set in common make the same selection, and each writes the indices of its share of the kept rows and copies
+// these.  For launches that leave most compute units idle, whose time is that of the launches themselves.
+template <bool SHARED, int NT, int MAXC, bool COPY>
 __global__ __launch_bounds__(NT) void select_kernel(
     const float* __restrict__ scores, const int* __restrict__ budgets,
     const long long* __restrict__ layer_offsets, int L, int H, int n, long long rows_per_seq,
-    int* __restrict__ idx_out) {
+    int* __restrict__ idx_out, CopyArgs cp) {
   constexpr int kWaves = NT / 64, kPer = kSelBins / NT;
   __shared__ union { unsigned hist[kSelBins]; unsigned short stage[NT * MAXC]; } lds;
   unsigned* const hist = lds.hist;
   unsigned short* const stage = lds.stage;
+  __shared__ unsigned short list[COPY ? NT * MAXC : 1];    // this workgroup's share of the kept tokens
   __shared__ unsigned wave_a[kWaves], wave_b[kWaves];
   __shared__ unsigned sh_bin, sh_need, sh_count;
 
   // per-head mode: one workgroup per (b,l,h); layer-shared mode: one per (b,l), writing H copies
-  const int unit = SHARED ? blockIdx.x * H : blockIdx.x;
+  Share share{(int)blockIdx.x, 0, 1};
+  if (COPY) share = share_of(blockIdx.x, gridDim.x, cp.lists, L, SHARED ? 1 : H, n, budgets);
+  if (share.of == 0) return;
+  const int unit = SHARED ? share.list * H : share.list;
   const int h = unit % H, bl = unit / H, l = bl % L, b = bl / L;
   const int k = budgets[(size_t)b * L + l];
   const int copies = SHARED ? H : 1;
@@ -360,20 +402,40 @@ __global__ __launch_bounds__(NT) void select_kernel(
   unsigned pos = 0;                             // kept by lower waves
   for (int w = 0; w < wave; ++w) pos += wave_a[w];
   pos = uniform(pos);
+  const unsigned r0 = COPY ? (unsigned)k * share.at / share.of : 0u, r1 = COPY ? (unsigned)k * (share.at + 1) / share.of : (unsigned)k;
   for (unsigned t = lane; t < held; t += 64) {
     const int token = mine[t];
-    if (pos + t < (unsigned)k)
+    if (pos + t >= r0 && pos + t < r1) {
+      if (COPY) list[pos + t - r0] = (unsigned short)token;
       for (int c = 0; c < copies; ++c) out[(size_t)c * k + pos + t] = token;
+    }
+  }
+  if constexpr (COPY) {
+    __syncthreads();
+    const long long filled = layer_offsets[(size_t)b * (L + 1) + L];       // (no rows beyond what the budgets fill)
+    const unsigned rows = r1 - r0, all = rows * (unsigned)copies * (unsigned)cp.vec_per_row;
+    for (unsigned v = tid; v < all; v += NT) {
+      const unsigned at = cp.vpr_shift >= 0 ? v >> cp.vpr_shift : v / (unsigned)cp.vec_per_row, part = (v - at * cp.vec_per_row) * 16;
+      const unsigned c = SHARED ? at / rows : 0, i = at - c * rows;
+      const int j = (int)(r0 + i), token = list[i];                        // kept row j of head h + c
+      const long long packed = off + (long long)c * k + j;
+      if (packed >= filled) continue;
+      const long long src = (long long)b * cp.st.sb + (long long)l * cp.st.sl + (long long)(h + (int)c) * cp.st.sh + (long long)token * cp.st.sn;
+      long long dst = (long long)b * rows_per_seq + packed;
+      if (cp.pg.block_table) {
+        const int slot_page = j / cp.pg.page_size;
+        const long long page = slot_page < cp.pg.max_pages ? cp.pg.block_table[(long long)(unit + (int)c) * cp.pg.max_pages + slot_page] : -1;
+        if (page < 0 || page >= cp.pg.num_pages) continue;                 // not a valid page: row skipped
+        dst = page * cp.pg.page_size + (j - slot_page * cp.pg.page_size);
+      }
+      const size_t from = (size_t)src * cp.elem_bytes + part, to = (size_t)dst * cp.vec_per_row * 16 + part;
+      const uint4v kv = __builtin_nontemporal_load(reinterpret_cast<const uint4v*>(cp.K + from));
+      const uint4v vv = __builtin_nontemporal_load(reinterpret_cast<const uint4v*>(cp.V + from));
+      __builtin_nontemporal_store(kv, reinterpret_cast<uint4v*>(cp.K_out + to));
+      __builtin_nontemporal_store(vv, reinterpret_cast<uint4v*>(cp.V_out + to));
+    }
   }
 }
-
-// Destination of the paged variant: kept row j of unit (b,l,h) goes to slot j % page_size of page
-// block_table[b][l][h][j / page_size] of caches laid out [num_pages][page_size][d].
-struct PagedDst {
-  const int* block_table;
-  int page_size, max_pages;
-  long long num_pages;
-};
 
 // A workgroup copies the `rows` kept rows from blockIdx.x * rows on (blockIdx.y is the sequence): a thread looks up where
 // one of them is and goes, then each copies a 16-byte vector of a K row and the matching one of V (more than one vector of a
@@ -381,7 +443,6 @@ struct PagedDst {
 // budgets and indices the other workgroups need stay resident instead.  Bound by memory: 112 units that keep 6554 rows
 // 128 us, 5.9 TB/s; with a lookup for each vector 152, with two, four or eight vectors of each tensor under way in a thread
 // 133, 137 and 140, with K and V in workgroups of their own 163.
-typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
 constexpr int kGatherThreads = 256;
 
 template <bool PAGED>
@@ -439,6 +500,17 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(
 
 }  // namespace
 
+// Workgroups of a selection that copies the rows as well, 0: the copying is a launch of its own.  Those with an index set in common all make
+// the selection, so that there must be compute units to spare, and their own share of rows has to be short, since a workgroup copies it
+// alone.  Two launches / one, us, with the bytes that a workgroup copies: 2 sets of 512 tokens (6 KB) 8.3 / 5.8, 16 of 4096 (52) 10.2 /
+// 8.5, 16 of 1280 (28) 8.7 / 6.5, 64 of 2048 (52) 9.6 / 7.8, 4 of 16384 (105) 11.6 / 11.0, 32 of 8192 (105) 13.2 / 12.4; 4 of 4096, heads'
+// rows alike (209) 10.8 / 13.1, 8 of 16384 (315) 17.3 / 19.3; 128 of 512 (92) 11.3 / 12.3.
+static int copy_groups(int lists, int layers, int n, long long rows, int row_bytes) {
+  if (n > 16384 || lists > 64) return 0;
+  const int groups = lists * std::min(16, 256 / lists), sharing = layers == 1 ? groups : groups - lists;
+  return 4 * rows * row_bytes <= (long long)sharing * (112 << 10) ? groups : 0;
+}
+
 hipError_t select_gather_launch(const void* K, const void* V, const fc_kv_desc& d, const float* scores,
                                 const int32_t* budgets, const int64_t* layer_offsets,
                                 int64_t rows_per_seq, bool shared, int32_t* idx_out, void* K_out,
@@ -447,30 +519,46 @@ hipError_t select_gather_launch(const void* K, const void* V, const fc_kv_desc& 
   const int units = d.batch * d.layers * d.kv_heads;
   if (units == 0 || rows_per_seq == 0) return hipSuccess;
   const long long* offs = reinterpret_cast<const long long*>(layer_offsets);
+  const int elem_bytes = d.dtype == FC_BF16 ? 2 : 4;
+  const int vec_per_row = d.head_dim * elem_bytes / 16;
+  int vpr_shift = -1;
+  if ((vec_per_row & (vec_per_row - 1)) == 0)
+    for (vpr_shift = 0; (1 << vpr_shift) < vec_per_row; ++vpr_shift) {}
+  const PagedDst pg{block_table, page_size, max_pages, (long long)num_pages};
+  const int lists = shared ? units / d.kv_heads : units;           // index sets to be found
+  const int groups = copy_groups(lists, d.layers, d.n_tokens, (long long)rows_per_seq * d.batch, vec_per_row * 16);
   {
     ProfileScope ps(shared ? "select_shared_kernel" : "select_kernel", s);
-    const dim3 grid(shared ? units / d.kv_heads : units);
+    const dim3 grid(groups ? groups : lists);
+    const CopyArgs cp{static_cast<const char*>(K), static_cast<const char*>(V), strides_of(d), lists, elem_bytes, vec_per_row, vpr_shift,
+                      static_cast<char*>(K_out), static_cast<char*>(V_out), pg};
     const long long rows = (long long)rows_per_seq;
     const int n = d.n_tokens;
 #define FC_SELECT(SH, NT, MAXC)                                                                               \
-  hipLaunchKernelGGL((select_kernel<SH, NT, MAXC>), grid, dim3(NT), 0, s, scores, budgets, offs, d.layers,     \
-                     d.kv_heads, n, rows, idx_out)
+  hipLaunchKernelGGL((select_kernel<SH, NT, MAXC, false>), grid, dim3(NT), 0, s, scores, budgets, offs,        \
+                     d.layers, d.kv_heads, n, rows, idx_out, cp)
+#define FC_SELECT_COPY(SH, NT, MAXC)                                                                          \
+  if (groups)                                                                                                 \
+    hipLaunchKernelGGL((select_kernel<SH, NT, MAXC, true>), grid, dim3(NT), 0, s, scores, budgets, offs,       \
+                       d.layers, d.kv_heads, n, rows, idx_out, cp);                                           \
+  else FC_SELECT(SH, NT, MAXC)
     // The fewest keys per thread that cover n, and more waves while the barriers they wait at cost less than the keys
     // they share out (us at 16 and at 896 units): 2048 tokens, 512 threads of 4 keys 7.8 / 12.2, 256 of 16 11.2 / 15.5;
     // 4096 tokens, 512 threads of 8 9.4 / 15.6, 1024 of 4 8.9 / 19.8; 8192 tokens, 1024 of 8 11.4 / 26.6, 512 of 16
     // 12.1 / 25.9; 16384 tokens, 1024 of 16 15.3 / 52.6, 512 of 32 19.2 / 48.7.
 #define FC_SELECT_N(SH)                                                                                        \
-  if (n <= 1024) FC_SELECT(SH, 256, 4);                                                                        \
-  else if (n <= 2048) FC_SELECT(SH, 512, 4);                                                                   \
-  else if (n <= 4096) FC_SELECT(SH, 512, 8);                                                                   \
-  else if (n <= 8192) FC_SELECT(SH, 1024, 8);                                                                  \
-  else if (n <= 16384) FC_SELECT(SH, 1024, 16);                                                                \
+  if (n <= 1024) { FC_SELECT_COPY(SH, 256, 4); }                                                               \
+  else if (n <= 2048) { FC_SELECT_COPY(SH, 512, 4); }                                                          \
+  else if (n <= 4096) { FC_SELECT_COPY(SH, 512, 8); }                                                          \
+  else if (n <= 8192) { FC_SELECT_COPY(SH, 1024, 8); }                                                         \
+  else if (n <= 16384) { FC_SELECT_COPY(SH, 1024, 16); }                                                       \
   else FC_SELECT(SH, 1024, 32)
     if (n <= 32 * kSelThreads) {
       if (shared) { FC_SELECT_N(true); } else { FC_SELECT_N(false); }
     } else if (n <= kSelMaxChunk * kSelThreads) {
       if (shared) FC_SELECT(true, 1024, 64); else FC_SELECT(false, 1024, 64);
 #undef FC_SELECT_N
+#undef FC_SELECT_COPY
 #undef FC_SELECT
     } else if (shared) {
       hipLaunchKernelGGL(select_large_kernel<true>, grid, dim3(kSelThreads), 0, s, scores, budgets, offs, d.layers,
@@ -481,18 +569,12 @@ hipError_t select_gather_launch(const void* K, const void* V, const fc_kv_desc& 
     }
   }
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int elem_bytes = d.dtype == FC_BF16 ? 2 : 4;
-  const int vec_per_row = d.head_dim * elem_bytes / 16;
+  if (e != hipSuccess || groups) return e;
   // rows of a workgroup: one turn of its threads' copies, if it has a thread for each of them
   const int rows = std::min(kGatherThreads, std::max(1, kGatherThreads / vec_per_row));
   const long long blocks = (rows_per_seq + rows - 1) / rows;
   if (blocks > 0x7FFFFFFFll || d.batch > 65535) return hipErrorInvalidValue;
-  int vpr_shift = -1;
-  if ((vec_per_row & (vec_per_row - 1)) == 0)
-    for (vpr_shift = 0; (1 << vpr_shift) < vec_per_row; ++vpr_shift) {}
   ProfileScope ps("gather_kernel", s);
-  const PagedDst pg{block_table, page_size, max_pages, (long long)num_pages};
   const dim3 grid((unsigned)blocks, (unsigned)d.batch);
   const size_t lds = (size_t)(d.layers + 1) * sizeof(long long);
   if (block_table)

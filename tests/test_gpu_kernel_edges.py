@@ -690,3 +690,46 @@ def test_fp32_rows_of_every_width(d, n, r, heads):
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_short_sequences(n, r, d, heads, dtype):
     _scores_and_energies_follow_the_oracle(n, r, d, dtype, heads)
+
+
+# Small launches copy the rows in the selection's workgroups: as many for an index set as its budget takes of them, at the sizes of
+# every such kernel, for 1 to 64 sets, budgets of one row beside whole layers, and one set more than that
+@pytest.mark.parametrize("n,B,L,H", [(1024, 1, 1, 1), (513, 3, 1, 5), (1025, 2, 4, 8), (4096, 2, 7, 2), (2047, 1, 64, 1), (2050, 1, 13, 5),
+                                     (5000, 1, 3, 2), (16384, 2, 2, 3)])
+@pytest.mark.parametrize("shared", [False, True])
+def test_rows_copied_by_the_selection(n, B, L, H, shared):
+    import paper_2511_16786_amd as fc
+    d, page = 24, 64
+    rng = np.random.default_rng(n + L)
+    K, V = (rng.integers(0, 0x7F80, (B, L, H, n, d)).astype(np.uint16) for _ in range(2))
+    scores = rng.integers(0, 3 + n // 4, (B, L, H, n)).astype(np.float32)
+    budgets = rng.integers(1, max(2, n // 16), (B, L))
+    if L > 1:
+        budgets[:, 0], budgets[:, -1] = n // 2, 1
+    budgets[1:, 0] += budgets[0].sum() - budgets[1:].sum(1)               # (sequences keep as many rows)
+    assert budgets.min() >= 1 and budgets.max() <= n
+    offs = np.stack([ref.layer_offsets(x, H) for x in budgets])
+    rows = int(offs[0, -1])
+    Kt, Vt = pu.to_torch(K, "bf16"), pu.to_torch(V, "bf16")
+    s_t, b_t, o_t = (torch.from_numpy(x).cuda() for x in (scores, budgets.astype(np.int32), offs))
+    idx = torch.full((B, rows), -1, dtype=torch.int32, device="cuda")
+    Ko, Vo = (torch.zeros((B, rows, d), dtype=Kt.dtype, device="cuda") for _ in range(2))
+    desc = fc.describe(Kt)
+    fc.select_gather(Kt, Vt, desc, s_t, b_t, o_t, rows, idx, Ko, Vo, shared=shared)
+    reach = -(-n // page) - 1                                             # (rows of a last page that is not there are left out)
+    table = rng.permutation(B * L * H * reach).astype(np.int32).reshape(B, L, H, reach)
+    Kc, Vc = (torch.zeros((B * L * H * reach, page, d), dtype=Kt.dtype, device="cuda") for _ in range(2))
+    fc.select_gather_paged(Kt, Vt, desc, s_t, b_t, o_t, rows, torch.empty_like(idx), torch.from_numpy(table).cuda(), page, Kc, Vc,
+                           shared=shared)
+    paged = [np.zeros(Kc.shape, dtype=K.dtype) for _ in range(2)]
+    for b in range(B):
+        want = ref.select_gather(K[b], V[b], scores[b], budgets[b], shared=shared)
+        assert np.array_equal(idx[b].cpu().numpy(), want["idx"])
+        for got, name, out in ((Ko, "K_out", paged[0]), (Vo, "V_out", paged[1])):
+            assert np.array_equal(pu.rows_to_numpy(got, "bf16")[b], want[name])
+            for l in range(L):
+                for h in range(H):
+                    at = offs[b, l] + h * budgets[b, l]
+                    for j in range(min(int(budgets[b, l]), reach * page)):
+                        out[table[b, l, h, j // page], j % page] = want[name][at + j]
+    assert np.array_equal(pu.rows_to_numpy(Kc, "bf16"), paged[0]) and np.array_equal(pu.rows_to_numpy(Vc, "bf16"), paged[1])
