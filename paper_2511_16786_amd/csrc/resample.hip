@@ -943,16 +943,18 @@ __global__ __launch_bounds__(G::T < 64 ? 64 : G::T, G::kWaves) void grid_filter_
 
 // The same transform (in 32 bits) spread over one thread for each butterfly of its widest pass, every pass through LDS.
 // Points meet the same factors in the same order as in grid_filter_kernel, so that results are the same bits (the kept
-// energy's sum aside).  It takes more instructions in all, and is for launches that leave half of the chip or more without a
+// energy's sum aside).  It takes more instructions in all, and is for launches that leave much of the chip without a
 // wave, whose time is that of one wave's instructions one after the other: up to 512 column pairs of transforms with 24
-// points a thread and more.  Before / after, us with events (an empty launch: 6): 512 pairs of 3072 points 21.8 / 17.6, of
-// 384 10.6 / 7.3, 256 of 96 8.2 / 6.8, of 4096 16.8 / 14.7; 1024 pairs of 3072 26.6 / 27.9, of 768 11.9 / 12.0, 2048 of 768
-// 15.0 / 17.0; 256 of 2048, which have 16 points a thread, 11.1 / 12.2; 512 of 6144 26.3 / 41.6.
+// points a thread and more, more where it was found the quicker one.  One wave for each transform / spread, us with events (an empty
+// launch: 6): 512 pairs of 3072 points 21.8 / 16.9, of 1536 14.9 / 13.2, of 4096 16.8 / 14.7, 256 of 96 8.2 / 6.4; 1024 pairs of 3072
+// 25.5 / 23.8, of 1536 14.9 / 17.6, of 768 12.2 / 11.5, of 384 10.9 / 8.3, of 192 8.8 / 9.5; 2048 of 3072 35.7 / 37.4, of 768 14.6 /
+// 15.2, of 384 12.0 / 9.8; 256 of 2048, which have 16 points a thread, 11.1 / 12.2; 512 of 6144 26.3 / 41.6.  (Addresses of LDS as a part of the
+// thread's own and constants: a seventh of the instructions, 512 pairs of 3072 points 17.5 / 16.9, of 384 7.4 / 7.0.)
 template <int M>
 struct SpreadPlan {
   using G = GridPlan<M, false>;
   static constexpr bool kUse = G::P >= 24 && M <= 4096;
-  static constexpr int kMostPairs = 512;
+  static constexpr int kMostPairs = M == 384 ? 2048 : (M == 768 || M == 3072 ? 1024 : 512);
   static constexpr int least(int a, int b) { return a < b ? a : b; }
   static constexpr int kRadix = least(least(G::R0, G::R1), least(G::R2 > 1 ? G::R2 : M, G::R3 > 1 ? G::R3 : M));
   static constexpr int NT = (M / kRadix + 63) / 64 * 64;
@@ -1005,13 +1007,16 @@ __global__ __launch_bounds__(SpreadPlan<M>::NT) void grid_spread_kernel(
     constexpr int R = decltype(radix)::value, NS = decltype(done)::value, B = M / R;
     constexpr bool kLast = R * NS == M;
     const bool mine = B >= NT || tid < B;
+    // (addresses are a part of the thread's own and a constant: B q, and q NS or q of a group of NS R, are made of whole groups of
+    // 2^kPadShift, or do not leave one)
+    static_assert(B % (1 << G::kPadShift) == 0 && (NS == 1 ? R <= (1 << G::kPadShift) || R % (1 << G::kPadShift) == 0
+                                                           : NS % (1 << G::kPadShift) == 0), "padding of a pass");
     C v[R];
     if (mine)
 #pragma unroll
       for (int q = 0; q < R; ++q) {
-        const int at = F::pad(tid + B * q);
         if constexpr (first) v[q] = cpair<C>(x0[q].x, x0[q].y);
-        else v[q] = cpair<C>(re[at], im[at]);
+        else v[q] = cpair<C>(re[F::pad(tid) + F::pad(B * q)], im[F::pad(tid) + F::pad(B * q)]);
       }
     if (!first) __syncthreads();
     if (mine) {
@@ -1024,12 +1029,13 @@ __global__ __launch_bounds__(SpreadPlan<M>::NT) void grid_spread_kernel(
         }
       }
       dft<R>(v);
+      const int to = kLast ? tid : tid / NS * (NS * R) + (tid & (NS - 1));
 #pragma unroll
       for (int q = 0; q < R; ++q) {
-        const int at = kLast ? tid + B * q : tid / NS * (NS * R) + (tid & (NS - 1)) + q * NS;
         const float2 x = make_float2((float)v[q].x, (float)v[q].y);
-        if (store) g[at] = make_float2(x.y, x.x);
-        else { re[F::pad(at)] = x.x; im[F::pad(at)] = x.y; }
+        const int at = F::pad(to) + F::pad(kLast ? B * q : q * NS);
+        if (store) g[to + B * q] = make_float2(x.y, x.x);
+        else { re[at] = x.x; im[at] = x.y; }
       }
     }
     if (!store) __syncthreads();
@@ -1055,8 +1061,8 @@ __global__ __launch_bounds__(SpreadPlan<M>::NT) void grid_spread_kernel(
   for (int k = 0; k < kBins; ++k) {
     const int m = tid + NT * k;
     if (M % NT == 0 || m < M) {
-      const int o = m ? M - m : 0;
-      const C w = cpair<C>(re[F::pad(m)], im[F::pad(m)]), mirror = cpair<C>(re[F::pad(o)], im[F::pad(o)]);
+      const int at = F::pad(tid) + F::pad(NT * k), o = k == 0 && tid == 0 ? 0 : F::pad(M - NT * k) + F::pad(-tid);
+      const C w = cpair<C>(re[at], im[at]), mirror = cpair<C>(re[o], im[o]);
       const C f = cpair<C>(fq[k].x, fq[k].y), z = cmul(mirror, cmul(ph, cpair<C>(phase[k].x, -phase[k].y)));
       y[k] = cpair<C>(mad(f.y, z.x, f.x * w.x), mad(f.y, z.y, f.x * w.y));
       e = mad(w.x, y[k].x, mad(w.y, y[k].y, e));
@@ -1066,7 +1072,8 @@ __global__ __launch_bounds__(SpreadPlan<M>::NT) void grid_spread_kernel(
 #pragma unroll
   for (int k = 0; k < kBins; ++k) {
     const int m = tid + NT * k;
-    if (M % NT == 0 || m < M) { re[F::pad(m)] = (float)y[k].y; im[F::pad(m)] = (float)y[k].x; }
+    const int at = F::pad(tid) + F::pad(NT * k);
+    if (M % NT == 0 || m < M) { re[at] = (float)y[k].y; im[at] = (float)y[k].x; }
   }
   __syncthreads();
   transform(std::false_type{}, std::true_type{});

@@ -733,3 +733,19 @@ def test_rows_copied_by_the_selection(n, B, L, H, shared):
                     for j in range(min(int(budgets[b, l]), reach * page)):
                         out[table[b, l, h, j // page], j % page] = want[name][at + j]
     assert np.array_equal(pu.rows_to_numpy(Kc, "bf16"), paged[0]) and np.array_equal(pu.rows_to_numpy(Vc, "bf16"), paged[1])
+
+
+# ... and of launches on both sides of the most column pairs that are spread: 512, 1024 (768 and 3072 points) and 2048 (384), by
+# units of 32 pairs
+@pytest.mark.parametrize("n,r,most", [(8191, 820, 512), (4099, 410, 1024), (16384, 1639, 1024), (2048, 210, 2048)])
+def test_scores_on_both_sides_of_the_spread_launches(n, r, most):
+    import paper_2511_16786_amd as fc
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    units, d = most // 32 + 1, 32
+    K, V = (torch.randn((1, units, 1, n, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    every = fc.Compressor(K, r, fc.total_budget(units, n, 0.2))
+    every.run_score(K, V)
+    fewer = fc.Compressor(K[:, :-1], r, fc.total_budget(units - 1, n, 0.2))
+    fewer.run_score(K[:, :-1], V[:, :-1])
+    assert torch.equal(fewer.scores, every.scores[:, :-1]) and torch.equal(fewer.energy, every.energy[:, :-1])
+    assert fc.workspace_error(every.workspace) == 0 and fc.workspace_error(fewer.workspace) == 0
