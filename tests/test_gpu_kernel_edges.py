@@ -749,3 +749,30 @@ def test_scores_on_both_sides_of_the_spread_launches(n, r, most):
     fewer.run_score(K[:, :-1], V[:, :-1])
     assert torch.equal(fewer.scores, every.scores[:, :-1]) and torch.equal(fewer.energy, every.energy[:, :-1])
     assert fc.workspace_error(every.workspace) == 0 and fc.workspace_error(fewer.workspace) == 0
+
+
+# Tables that reach 128 rows make one piece of every unit, which needs no merge; tables that reach further make the same pieces of the
+# same budgets, and merge them
+@pytest.mark.parametrize("d,group", [(64, 4), (128, 7)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_decode_of_single_pieces_is_the_merged_one(dtype, d, group):
+    import paper_2511_16786_amd as fc
+    B, L, H, page = 2, 3, 2, 64
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    Q = torch.randn((B, L, H * group, d), generator=gen, device="cuda").to(dt)
+    units = B * L * H
+    K, V = (torch.randn((units * 2, page, d), generator=gen, device="cuda").to(dt) for _ in range(2))
+    budgets = torch.tensor([[128, 1, 77], [64, 0, 33]], dtype=torch.int32, device="cuda")
+    short = torch.randperm(units * 2, generator=gen, device="cuda").to(torch.int32).view(B, L, H, 2)
+    long = torch.cat((short, torch.full((B, L, H, 3), -1, dtype=torch.int32, device="cuda")), 3).contiguous()
+    out = [fc.decode_attention_paged(Q, K, V, H, budgets, t, d ** -0.5) for t in (short, long)]
+    assert torch.equal(out[0], out[1]) and bool((out[0][1, 1] == 0).all()) and bool(torch.isfinite(out[0]).all())
+    for b in range(B):
+        for l in range(L):
+            k = int(budgets[b, l])
+            for h in range(H if k else 0):
+                rows = [x[short[b, l, h].long()].reshape(-1, d)[:k].double() for x in (K, V)]
+                p = torch.softmax(Q[b, l, h * group:(h + 1) * group].double() @ rows[0].T * d ** -0.5, -1)
+                want = p @ rows[1]
+                assert float((out[0][b, l, h * group:(h + 1) * group] - want).abs().max()) <= 5e-5 * float(rows[1].abs().max())
