@@ -38,6 +38,7 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef short s16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16v8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -335,6 +336,12 @@ template <bool KEEP, typename V>
 __device__ __forceinline__ V load_piece(const void* p) {
   if constexpr (KEEP) return *static_cast<const V*>(p);
   return __builtin_nontemporal_load(static_cast<const V*>(p));
+}
+// From a uniform address and 32 bits of the lane's own.
+template <typename V>
+__device__ __forceinline__ V lane_load(const void* base, uint32_t at) {
+  typedef const __attribute__((address_space(1))) V* Global;
+  return *(Global)(static_cast<const char*>(base) + at);
 }
 template <typename T>
 struct RowPiece;
@@ -1115,6 +1122,16 @@ __device__ __forceinline__ void residual_piece(const RowPiece<float>& x, const f
   }
 }
 
+// a and b times scale, a power of two, in two terms of 16 bits each: rounded, and what that leaves.  (Scaling, rounding and difference
+// are one instruction for each of the four: the sums are fused multiply-adds, and the first terms are pinned as a word, else the
+// compiler makes them twice, 192 instructions more for a window.)
+__device__ __forceinline__ void halves(float a, float b, float scale, Frag& high, Frag& low, int word) {
+  f16x2 h = {(_Float16)fmaf(a, scale, 0.f), (_Float16)fmaf(b, scale, 0.f)};
+  asm volatile("" : "+v"(h));
+  const f16x2 l = {(_Float16)fmaf(a, scale, -(float)h[0]), (_Float16)fmaf(b, scale, -(float)h[1])};
+  high.u[word] = __builtin_bit_cast(uint32_t, h);
+  low.u[word] = __builtin_bit_cast(uint32_t, l);
+}
 // Over the four lanes that hold one slot.
 __device__ __forceinline__ float slot_max(float v) {
   v = fmaxf(v, __shfl_xor(v, 16, 64));
@@ -1126,14 +1143,13 @@ __device__ __forceinline__ double dpp_add(double v) {
   const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, true);
   return v + __hiloint2double(hi, lo);
 }
-__device__ __forceinline__ double wave_sum(double v) {
+// Sums over the wave: of a in lanes 16 to 31, of b in lanes 48 to 63.
+__device__ __forceinline__ double wave_sums(double a, double b) {
+  const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+  double v = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
   v = dpp_add<0x128>(dpp_add<0x124>(dpp_add<0x122>(dpp_add<0x121>(v))));
-  double s = 0.0;
-#pragma unroll
-  for (int l = 0; l < 64; l += 16)
-    s += __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
-                          __builtin_amdgcn_readlane(__double2loint(v), l));
-  return s;
+  return dpp_add<0x142>(v);                                // row_bcast:15
 }
 // Sums of v[0..3] over the 16 lanes of a row, from four lanes' sums on in 64 bits; a lane returns the sum of v[lane & 3].
 __device__ __forceinline__ double row_sums(const float (&v)[4], int lane) {
@@ -1163,6 +1179,10 @@ constexpr int kResWorkgroups = 512;   // residual kernel: two for each compute u
 // banks): by the operands' lanes, 16 slots apart in memory, they took the address unit four times as long.  112 units, us
 // before / after: 32768 tokens M = 3072 460 / 448, M = 12288 729 / 683, 30011 tokens 526 / 507; one layer of 16384 21.5 / 18.0,
 // of which 1.6 for not loading a window after the last segment.
+// What a segment takes besides its tiles weighs where those are few (three at M = 12288): of 600 vector and 500 scalar
+// instructions 350 and 300 are left, since a window's values are scaled and split in one instruction a term, energies of one
+// tensor's slots take one pair of sums over the wave, items follow one another without a division and loads have scalar bases.
+// Residual of 112 units, us: M = 12288 681 / 654, 16384 tokens, M = 12288 715 / 680, 30011 tokens 505 / 490, M = 3072 449 / 443.
 template <typename T, bool KEEP, bool ONCE, int BUF>
 __global__ __launch_bounds__(256, 2) void residual_kernel(
     const T* __restrict__ K, const T* __restrict__ V, KvStrides st, int u0, int u1, int n, int r, int d, int dtype,
@@ -1185,18 +1205,21 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
   const int items = mine_w.count * mine_s.count;
   int item = blockIdx.x >> 3, part = 0;                    // segment under way
   if (item >= items) return;
+  // (a workgroup's next item is as many rows and columns of the XCD's rectangle further on: no division for each)
+  const int peer_rows = (unsigned)peers / (unsigned)mine_w.count, peer_cols = peers - peer_rows * mine_w.count;
 
   struct Seg {
-    int win, unit, part, tiles, n0;                        // n0: position of the window's first even grid point
+    int row, col, win, unit, part, tiles, n0;              // n0: position of the window's first even grid point
     const T* rows;                                         // this lane's columns of token 4 g
-    const float2* gp;                                      // the first column pair that this lane loads on the grid
     float* score;                                          // of the unit's first token
   };
-  auto segment = [&](int it, int pt) {
+  auto segment = [&](int row, int col, int pt) {
     Seg s;
     s.part = my_part + pt;
-    const int row = (unsigned)it / (unsigned)mine_w.count, set = mine_s.from + row;
-    s.win = mine_w.from + it - row * mine_w.count;
+    s.row = row;
+    s.col = col;
+    const int set = mine_s.from + row;
+    s.win = mine_w.from + col;
     s.n0 = __builtin_amdgcn_readfirstlane(first_point(16 * tpw * s.win, m, inv_dd, window_points(r, m))) >> 1;
     s.unit = min(u0 + abreast * set + my_unit, u1 - 1);    // (a surplus wave repeats the last unit)
     s.tiles = min(tpw, tok_tiles - s.win * tpw);
@@ -1205,24 +1228,31 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     const bool second = slot >= sm.nb;
     s.rows = (second ? V : K) + unit_offset(st, s.unit) + (slot - (second ? sm.nb : 0)) * C + (int64_t)(4 * g) * st.sn;
     s.score = scores + (size_t)out_unit(um, s.unit) * n;
-    const int loaded = s.part * 16 + (lane >> 2);
-    s.gp = grid + ((size_t)(s.unit - u0) * 2 * sm.nb + (loaded < 2 * sm.nb ? loaded : 0)) * (C / 2) * m + 2 * ((lane ^ (lane >> 3)) & 3);
     return s;
   };
   bool follows;                                            // whether there is a segment after the one under way
   auto following = [&](const Seg& s) {
-    int it = item, pt = part + 1;
-    if (pt == parts) { pt = 0; it += peers; }
+    int it = item, pt = part + 1, row = s.row, col = s.col;
+    if (pt == parts) {
+      pt = 0;
+      it += peers;
+      row += peer_rows;
+      col += peer_cols;
+      if (col >= mine_w.count) { col -= mine_w.count; ++row; }
+    }
     follows = !ONCE && it < items;
-    return follows ? segment(it, pt) : s;
+    return follows ? segment(row, col, pt) : s;
   };
   f32x4 v[C / 2][4];
   auto load_window = [&](const Seg& s) {
+    // (a slot past the last loads the part's first, a part past the last the unit's; addresses are a scalar base and 32 bits of the lane's)
+    const int slots = 2 * sm.nb - s.part * 16, slot = (lane >> 2) < slots ? lane >> 2 : 0, first = slots > 0 ? s.part * 16 : 0;
+    const uint32_t at = ((uint32_t)(slot * (C / 2) * m) + 2 * ((lane ^ (lane >> 3)) & 3)) * (uint32_t)sizeof(float2);
+    const float2* base = grid + ((size_t)(s.unit - u0) * 2 * sm.nb + first) * (C / 2) * m;
 #pragma unroll
     for (int jp = 0; jp < C / 2; ++jp)
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
-        v[jp][c] = *reinterpret_cast<const f32x4*>(s.gp + (size_t)jp * m + (c < 2 ? s.n0 + 8 * c : m - 32 - s.n0 + 8 * c));
+      for (int c = 0; c < 4; ++c) v[jp][c] = lane_load<f32x4>(base + (size_t)jp * m + (c < 2 ? s.n0 : m - 32 - s.n0) + 8 * c, at);
   };
   const T* ahead;                                          // this lane's columns of token 4 g of the next tile to load
   int ahead_at;                                            // its first token
@@ -1244,12 +1274,13 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
   };
   Frag wn[3];
   auto load_weights = [&](const Seg& s, int tl) {
-    const u32x4* p = reinterpret_cast<const u32x4*>(winv) + (size_t)(s.win * tpw + min(tl, tpw - 1)) * 192 + lane;
+    const u32x4* p = reinterpret_cast<const u32x4*>(winv) + (size_t)(s.win * tpw + min(tl, tpw - 1)) * 192;
 #pragma unroll
-    for (int q = 0; q < 3; ++q) wn[q].u = p[64 * q];
+    for (int q = 0; q < 3; ++q) wn[q].u = lane_load<u32x4>(p + 64 * q, lane * (uint32_t)sizeof(u32x4));
   };
 
-  Seg cur = segment(item, part);
+  const int first_row = (unsigned)item / (unsigned)mine_w.count;
+  Seg cur = segment(first_row, item - first_row * mine_w.count, part);
   RowPiece<T> x[kBuf][4];
   load_window(cur);
   load_weights(cur, 0);
@@ -1301,28 +1332,23 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
 #pragma unroll
       for (int c = 0; c < 4; ++c)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float b = v[jp][c][q] * scale;
-          const _Float16 h = (_Float16)b;
-          bh[2 * jp + (q & 1)].hs[2 * c + (q >> 1)] = h;
-          bl[2 * jp + (q & 1)].hs[2 * c + (q >> 1)] = (_Float16)(b - (float)h);
-        }
+        for (int q = 0; q < 2; ++q) halves(v[jp][c][q], v[jp][c][q + 2], scale, bh[2 * jp + q], bl[2 * jp + q], c);
     // (the operands are made here, before their sources' registers are loaded again)
 #pragma unroll
     for (int j = 0; j < C; ++j) asm volatile("" : "+v"(bh[j].u), "+v"(bl[j].u));
     hp = tot = 0.0;
     if (!ONCE && follows) load_window(nxt);
   };
-  // energies of the segment: Ehp_k, Ehp_v, Etot_k, Etot_v
+  // Energies of the segment: Ehp_k, Ehp_v, Etot_k, Etot_v.  (Slots past the last have sums of 0; a part of one tensor's slots alone,
+  // the usual one, takes one pair of sums over the wave, not two.)
   auto record = [&]() {
-    const int mine = cur.part * 16 + (lane & 15);
-    const bool use = mine < 2 * sm.nb, second = mine >= sm.nb;
-    double ev[4] = {use && !second ? hp : 0.0, use && second ? hp : 0.0, use && !second ? tot : 0.0,
-                    use && second ? tot : 0.0};
+    const bool second = cur.part * 16 + (lane & 15) >= sm.nb;
+    const bool has_k = cur.part * 16 < sm.nb, has_v = cur.part * 16 + 16 > sm.nb;
+    double ek = 0.0, ev = 0.0;
+    if (has_k) ek = wave_sums(has_v && second ? 0.0 : hp, has_v && second ? 0.0 : tot);
+    if (has_v) ev = wave_sums(has_k && !second ? 0.0 : hp, has_k && !second ? 0.0 : tot);
     double* e = epart + (((size_t)cur.unit * wins + cur.win) * sm.wpu + cur.part) * 4;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) ev[k] = wave_sum(ev[k]);
-    if (lane == 0) { e[0] = ev[0]; e[1] = ev[1]; e[2] = ev[2]; e[3] = ev[3]; }
+    if ((lane & 30) == 16) e[(lane >> 5) * 2 + (lane & 1)] = lane & 1 ? ev : ek;
   };
   auto step = [&](RowPiece<T> (&xb)[4]) {
     if (tl == 0) take_window();

@@ -684,6 +684,14 @@ def test_fp32_rows_of_every_width(d, n, r, heads):
     _scores_and_energies_follow_the_oracle(n, r, d, "f32", heads)
 
 
+# The residual kernel's sums over a wave that holds K alone, V alone, both or some of either, and its next segments: an XCD's
+# rectangle narrower and wider than its workgroups are many
+@pytest.mark.parametrize("d", [16, 72, 96, 128, 200])
+@pytest.mark.parametrize("n,r,heads", [(3100, 150, 70), (16000, 3000, 11)])
+def test_bf16_segments_of_every_width(d, n, r, heads):
+    _scores_and_energies_follow_the_oracle(n, r, d, "bf16", heads)
+
+
 # Short sequences, whose tiles and windows are fewer than XCDs or a few more, of few units and of many
 @pytest.mark.parametrize("n,r,d,heads", [(300, 20, 64, 3), (512, 50, 128, 33), (700, 70, 64, 90), (1024, 91, 64, 140), (1938, 220, 128, 31),
                                          (4096, 410, 32, 60)])
