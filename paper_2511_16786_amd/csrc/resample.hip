@@ -407,6 +407,18 @@ __device__ __forceinline__ f32x4 fold_column(const Frag (&a)[3], const Frag (&w)
   return mfma_bf16(a[0], w[0], acc);
 }
 
+// The order of the steps of a wave that walks tiles of one group of four (for each tile the same, whether by itself or with others
+// of its group in a wave): odd groups are walked from their end; even ones take the steps that they share with the group
+// before from the last to the first, then the others from the first to the last, then the ones shared with the next group from
+// the last again.  So neighbours take what they share in the same order and, where they begin together, at the same time.
+struct StepOrder {
+  int first, low, high, end;          // steps below low, and those from high on, in descending order
+  __device__ __forceinline__ int at(int i) const {
+    const int s = first + i;
+    return s < low ? low - 1 - i : (s < high ? s : end - 1 - (s - high));
+  }
+};
+
 constexpr int kMinWorkgroups = 512;   // two for each compute unit
 constexpr int kDecWaves = 4;          // waves of a workgroup: 4 slots' worth of rows under the same tiles
 
@@ -418,8 +430,10 @@ constexpr int kDecWaves = 4;          // waves of a workgroup: 4 slots' worth of
 // as large as registers allow; results do not depend on it (a tile's steps and their order are its own).  A tile walks
 // the steps that its windows reach into, one fewer than the most any tile has for two tiles in three (12288 points
 // for 32768 tokens: 757 instead of 800 us for 112 units).
-// (one tile a wave reads the rows 1.75 times).  Every other group of four tiles is walked from its end, so that neighbours
-// are at the rows they share together.  Results leave in 16 bytes and whole 128-byte lines, two tiles side by side: the
+// (one tile a wave reads the rows 1.75 times).  Neighbours take the rows they share in the same order (StepOrder), so that those
+// that begin together find them in the L2, which holds some 5 us of what passes through it: 32768 tokens M = 3072 438 / 424 us, 8192 130 /
+// 127, M = 12288 656 / 643, fp32 8192 228 / 221 (before: both towards the seam or away from it, a step apart at its middle alone).
+// Results leave in 16 bytes and whole 128-byte lines, two tiles side by side: the
 // writes, a seventh of the traffic, cost a quarter of the time as half lines of 8 bytes a lane.  112 units, us before both /
 // walked both ways / now: 32768 tokens M = 3072 472 / 470 / 457 (1.09 GB read a round for 0.94 GB of rows, was 1.11; 0.19
 // written), M = 12288 750 / 717 / 671, 30011 tokens 541 / 535 / 503, 8192 tokens 146 / 144 / 136; with the weights ahead of
@@ -448,13 +462,25 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
   const bool second = slot >= sm.nb;
   const double dd = (double)n / (double)m;        // tokens per grid point
   int first[GT], count[GT], s_end = 0;            // a tile's first step, and how many it has
+  // (a lane works out a tile: the one before the group of four, its own four, the one after)
+  const int before = (tile0 & ~3) - 1, tiles = m / 16, lanes_tile = min(max(before + min(lane, 5), 0), tiles - 1);
+  const int lanes_first = first_step(lanes_tile, n, steps, dd, window_points(r, m));
+  const int lanes_count = step_count(lanes_tile, lanes_first, n, steps, dd, window_points(r, m));
 #pragma unroll
   for (int q = 0; q < GT; ++q) {
-    const int tile = tile0 + min(q, n_tiles - 1), w = window_points(r, m);
-    first[q] = __builtin_amdgcn_readfirstlane(first_step(tile, n, steps, dd, w));
-    const int c = __builtin_amdgcn_readfirstlane(step_count(tile, first[q], n, steps, dd, w));
+    const int from = tile0 - before + min(q, n_tiles - 1);
+    first[q] = __builtin_amdgcn_readlane(lanes_first, from);
+    const int c = __builtin_amdgcn_readlane(lanes_count, from);
     count[q] = q < n_tiles ? c : 0;
     s_end = first[q] + c;
+  }
+  StepOrder order{first[0], first[0], first[0], s_end};
+  if (!(tile0 & 4)) {
+    // (with fewer than two tokens for each grid point nearly all steps are shared, and even groups are walked from the first)
+    const bool meets = n >= 2 * m;
+    if (meets && before >= 0)
+      order.low = min(max(__builtin_amdgcn_readlane(lanes_first, 0) + __builtin_amdgcn_readlane(lanes_count, 0), first[0]), s_end);
+    order.high = meets && before + 5 < tiles ? min(max(__builtin_amdgcn_readlane(lanes_first, 5), order.low), s_end) : s_end;
   }
   const T* p = (second ? V : K) + unit_offset(st, mine ? unit : u0) + (slot - (second ? sm.nb : 0)) * C +
                (int64_t)(8 * (lane >> 4)) * st.sn;
@@ -464,8 +490,7 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e].template load<KEEP>(ps + e * st.sn);
   };
-  // (every other group of four tiles is walked from its end, so that neighbours come to the rows they share together)
-  const int steps_all = s_end - first[0], dir = (tile0 >> 2) & 1 ? -1 : 1, s_from = dir > 0 ? first[0] : s_end - 1;
+  const int steps_all = s_end - first[0];
   // The weights, four loads at a time and the first ahead of the rows, for which they would wait otherwise (one at a time
   // behind the rows, 28 layers: 32768 tokens 445 us, 436 now; 8192 tokens 134.5, 131.4; one layer of these 11.6, 11.0).
   const f32x4* w_src = reinterpret_cast<const f32x4*>(wfwd) + (size_t)tile0 * steps * 128;
@@ -478,7 +503,7 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
   load_weights(threadIdx.x);
 #pragma unroll
   for (int b = 0; b < kBuf; ++b)
-    if (b == 0 || b < steps_all) load(x[b], s_from + dir * b);
+    if (b == 0 || b < steps_all) load(x[b], order.at(b));
   if (ws_mismatch(hdr, FC_PATH_RESAMPLE, n, r, d, dtype)) return;     // (while all that is on its way)
   for (int i = threadIdx.x;;) {
 #pragma unroll
@@ -496,7 +521,7 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
 #pragma unroll
     for (int j = 0; j < C; ++j) acc[q][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   auto step = [&](RowPiece<T> (&v)[8], int i) {
-    const int s = s_from + dir * i;
+    const int s = order.at(i);
 #pragma unroll
     for (int q = 0; q < GT; ++q) {
       const int k = s - first[q];
@@ -515,7 +540,7 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
         }
       }
     }
-    if (i + kBuf < steps_all) load(v, s + dir * kBuf);
+    if (i + kBuf < steps_all) load(v, order.at(i + kBuf));
   };
   for (int i = 0; i < steps_all; i += kBuf)
 #pragma unroll

@@ -597,6 +597,24 @@ def test_scores_of_small_launches_are_the_same_bits(n, r, dtype):
     assert fc.workspace_error(one.workspace) == 0
 
 
+# One, two or four tiles of the grid to a wave by the launch's size: a tile takes its steps in an order of its own, that of its
+# group of four, with fewer and with more than two tokens for each grid point and a last group that is not full
+@pytest.mark.parametrize("n,r,heads", [(4099, 410, 24), (4099, 410, 90), (3001, 700, 90), (1000, 54, 300), (20001, 1000, 60)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_scores_by_the_tiles_of_a_wave_are_the_same_bits(n, r, heads, dtype):
+    import paper_2511_16786_amd as fc
+    gen = torch.Generator(device="cuda").manual_seed(n + heads)
+    K, V = (torch.randn((1, 1, heads, n, 128), generator=gen, device="cuda").to(torch.float32 if dtype == "f32" else torch.bfloat16)
+            for _ in range(2))
+    comp = fc.Compressor(K, r, fc.total_budget(1, n, 0.2))
+    comp.run_score(K, V)
+    one = fc.Compressor(K[:, :, :1], r, fc.total_budget(1, n, 0.2))
+    for h in (0, heads // 2, heads - 1):
+        one.run_score(K[:, :, h:h + 1], V[:, :, h:h + 1])
+        assert torch.equal(one.scores[:, :, 0], comp.scores[:, :, h])
+        assert torch.equal(one.energy[:, :, 0], comp.energy[:, :, h])
+
+
 # The kept energy is added up per thread of the transform in 32 bits, of at most 48 points with two products each, and differently by
 # the launch that spreads a transform over more threads; then in 64 bits.  The points are the same bits.
 @pytest.mark.parametrize("n,r,dtype", [(512, 52, "f32"), (1023, 109, "bf16"), (2048, 210, "bf16"), (4099, 410, "bf16"), (8191, 820, "bf16"),
