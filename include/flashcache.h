@@ -57,14 +57,15 @@ typedef enum {
                         token axes use the basis itself (C = B^T X, base = B C); from 256 tokens on
                         and for cut-offs up to N/2 the banded factors of the resampled transform, whose
                         cost does not grow with r * N */
-  FC_PATH_FFT = 2,   /* fast cosine transform on the vector ALUs (cut-offs up to N/2 and 9362 modes with
-                        head_dim <= 256: the resampled transform as above): N a multiple of 1024 (up to
+  FC_PATH_FFT = 2,   /* fast cosine transform on the vector ALUs (cut-offs that the resampled transform takes, with
+                        head_dim <= 256: that one, as above): N a multiple of 1024 (up to
                         132 * 1024), or of 256 (up to 64 * 1024, head_dim a multiple of 16);
                         head_dim a multiple of 8; any cut-off 1 <= r <= N */
   FC_PATH_BASIS = 3,   /* products with the stored basis itself: any N and r, head_dim <= 256 */
   FC_PATH_STREAM = 4,  /* the streaming transform on the vector ALUs: shapes of FC_PATH_FFT */
-  FC_PATH_RESAMPLE = 5 /* the resampled transform: N >= 256, cut-offs up to N/2 and 9362 modes for which a grid of
-                          at most 1.25 N points serves, head_dim a multiple of 8 up to 256 */
+  FC_PATH_RESAMPLE = 5 /* the resampled transform: N >= 256, cut-offs up to N/2 for which a grid of at most 1.25 N
+                          points serves: up to 9362 modes, and 10240 (9453 from 24576 tokens on) to 21065;
+                          head_dim a multiple of 8 up to 256 */
 } fc_path;
 
 /* Layout of K and of V (one descriptor serves both): element (b,l,h,n,c) lives at

@@ -163,7 +163,10 @@ __host__ __device__ constexpr GridRadices grid_radices(int m, bool wide) {
     case 6144: return {48, {16, 16, 24, 1}};
     case 8192: return {32, {16, 16, 32, 1}};
     case 12288: return {48, {16, 16, 48, 1}};
-    default: return {32, {32, 32, 16, 1}};         // 16384
+    case 16384: return {32, {32, 32, 16, 1}};
+    case 24576: return {48, {16, 16, 16, 6}};
+    case 32768: return {32, {32, 32, 32, 1}};
+    default: return {48, {16, 48, 48, 1}};         // 36864
   }
 }
 __host__ __device__ constexpr int grid_threads(int m, bool wide) { return m / grid_radices(m, wide).p; }
@@ -712,7 +715,8 @@ struct GridPlan {
   static_assert((R2 == 1 || R0 <= T) && (R3 == 1 || R0 * R1 <= T), "groups of the grid transform");
   static_assert(R0 * R1 * R2 * R3 == M && T % (1 << kPadShift) == 0 && kLds % 2 == 0, "radices of the grid transform");
   static_assert(kBlock == 0 || ((P / 2) % kBlock == 0 && 8 * kBlock * T + 8 <= kLds), "blocks of bins fit the exchange's LDS");
-  static constexpr int kWaves = WIDE ? (P <= 16 ? 3 : 2) : (P <= 16 || P == 32 ? 4 : 3);   // a SIMD's
+  // (24576 points have a compute unit's LDS to themselves, eight waves' worth)
+  static constexpr int kWaves = WIDE ? (P <= 16 ? 3 : 2) : (P <= 16 || P == 32 ? 4 : (T == 512 ? 2 : 3));   // a SIMD's
 };
 
 // element i + k of a table: uniform base and constant part, 32-bit part of the lane
@@ -1497,16 +1501,30 @@ hipError_t launch_filter(float2* grid, int pairs, int n, int r, int d, int dtype
 // than twice the grid, rounds of 201 MB are (8000 tokens, M = 4096: 168 MB 749 us, 251 MB 766; 32768 tokens, M = 12288: 201
 // MB 2122, 251 MB 2141).
 constexpr size_t kRoundGridBytes = (size_t)240 << 20;
+constexpr int kMaxGrid = 36864;       // points
 
-// Grid length for this shape and cut-off, 0 if the realisation does not apply.
+// The grid lengths are 2^k and 3 2^k points from 64 on, and the longest of which a compute unit's LDS holds one part (real or
+// imaginary) of a column pair.
+static int next_grid(int m) { return m == 32768 ? kMaxGrid : ((m & (m - 1)) == 0 ? m + m / 2 : m / 3 * 4); }
+
+// Grid length for this shape and cut-off, 0 if the realisation does not apply.  Above 9362 modes (16384 points) it starts again
+// where a cut-off takes the next grid whole, with 2.6 points a mode or fewer (9453 modes on; 2.4 where tokens are fewer than points):
+// the few before that keep the realisation that FC_PATH_RESAMPLE has always left them to.
+// Scoring by that realisation / this one, us (bf16, 128 columns): basis 12 units of 47568 tokens, r = 10894 34113 / 565, 8 of 44736,
+// r = 17649 34666 / 419, 8 of 50000, r = 20501 46754 / 528, 2 of 24600, r = 11071 2585 / 76; streaming 16 of 42752, r = 10415 18677 / 726,
+// 32 of 32768, r = 13108 2508 / 1451, 4 of 65536, r = 19661 728 / 148.  Error of the scores against 64 bits, white columns:
+// 29435 tokens, r = 10759 2.3e-7 (basis) / 4.5e-8, 30720, r = 14300 6.5e-8 (streaming) / 5.0e-8, 37449, r = 18724 4.3e-7 / 6.2e-8.
 static int grid_length(const fc_kv_desc& d, int32_t r) {
-  if (d.head_dim % 8 != 0 || d.head_dim > 256 || r < 1 || 2 * (int64_t)r > d.n_tokens) return 0;
-  for (int m2 = 64; m2 <= 16384; m2 *= 2)
-    for (int m = m2; m <= 16384 && m <= m2 + m2 / 2; m += m2 / 2)   // 2^k and 3 2^(k-1)
-      if (4 * (int64_t)m >= 7 * (int64_t)r && 16 * (int64_t)m >= d.n_tokens)   // M >= 1.75 r: see window_points
-        // a 16-token tile and its windows fit 32 points: 15 M/N + W < 29
-        return 5 * (int64_t)d.n_tokens >= 4 * (int64_t)m ? m : 0;
-  return 0;
+  const int64_t n = d.n_tokens;
+  if (d.head_dim % 8 != 0 || d.head_dim > 256 || r < 1 || 2 * (int64_t)r > n) return 0;
+  int64_t m = 64;
+  while (4 * m < 7 * (int64_t)r || 16 * m < n) {           // M >= 1.75 r: see window_points
+    if (m >= (r > 9362 ? kMaxGrid : 16384)) return 0;
+    m = next_grid((int)m);
+  }
+  if (m > 16384 && 5 * m > (n >= m ? 13 : 12) * (int64_t)r) return 0;
+  // a 16-token tile and its windows fit 32 points: 15 M/N + W < 29
+  return 5 * n >= 4 * m ? (int)m : 0;
 }
 
 // Whether the grid transform is computed in 64 bits.  Its rounding in 32 comes back from modes near the cut-off
@@ -1567,7 +1585,7 @@ ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
 size_t resample_reserve(const fc_kv_desc& d) {
   if (d.head_dim > 256 || d.n_tokens < 256) return 0;
   const size_t n = d.n_tokens, nb = d.head_dim / 8, units = (size_t)d.batch * d.layers * d.kv_heads;
-  const size_t m = std::min<size_t>(16384, n * 5 / 4);
+  const size_t m = std::min<size_t>(kMaxGrid, n * 5 / 4);
   const size_t tables = 296 * n + 288 * m + (256 << 10);
   const size_t records = units * (64 * nb + 2 * n * waves_per_unit((int)nb * (d.dtype == FC_BF16 ? 1 : 2)) + 64 * 8);
   const size_t grid = std::max<size_t>(kRoundGridBytes, 64 * nb * m);
@@ -1653,7 +1671,8 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
       FC_NARROW(64) FC_NARROW(96)
       FC_EITHER(128) FC_EITHER(192) FC_EITHER(256) FC_EITHER(384) FC_EITHER(512) FC_EITHER(768) FC_EITHER(1024)
       FC_EITHER(1536) FC_EITHER(2048) FC_EITHER(3072) FC_EITHER(4096)
-      FC_NARROW(6144) FC_NARROW(8192) FC_NARROW(12288) FC_NARROW(16384)
+      FC_NARROW(6144) FC_NARROW(8192) FC_NARROW(12288) FC_NARROW(16384) FC_NARROW(24576) FC_NARROW(32768)
+      FC_NARROW(36864)
       default: e = hipErrorInvalidValue;
     }
 #undef FC_EITHER

@@ -710,6 +710,35 @@ def test_bf16_segments_of_every_width(d, n, r, heads):
     _scores_and_energies_follow_the_oracle(n, r, d, "bf16", heads)
 
 
+# The grids of 24576, 32768 and 36864 points at the fewest and most modes and tokens they take, and just beyond
+@pytest.mark.parametrize("n,r,d,heads", [(20480, 10240, 16, 2), (20483, 10241, 64, 1), (47568, 10894, 8, 3), (28087, 14043, 24, 1),
+                                         (28088, 14044, 16, 2), (66001, 14100, 64, 1), (37449, 18724, 8, 3), (65536, 18725, 16, 1),
+                                         (42130, 21065, 8, 3), (66001, 21065, 8, 1), (65536, 21066, 16, 1), (24576, 9453, 16, 2),
+                                         (24575, 9453, 8, 1), (30000, 9452, 8, 1)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_scores_at_the_longest_grids(n, r, d, heads, dtype):
+    import paper_2511_16786_amd as fc
+    desc = fc.describe(torch.empty((1, 1, heads, n, d), dtype=torch.bfloat16 if dtype == "bf16" else torch.float32))
+    assert (fc.realisation(desc, r) == fc.binding.PATHS["resample"]) == ((r, n) not in ((21066, 65536), (9453, 24575), (9452, 30000)))
+    _scores_and_energies_follow_the_oracle(n, r, d, dtype, heads)
+
+
+# What they replace is 2.3e-7 to 4.3e-7 (the basis) and 6.2e-8 to 6.5e-8 (the streaming transform) from 64 bits
+@pytest.mark.parametrize("n,r", [(20490, 10240), (29435, 10759), (30720, 14300), (37449, 18724), (60000, 14044), (42131, 21065)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_scores_at_the_longest_grids_are_as_good_as_64_bits(n, r, dtype):
+    """White columns: a transform's sqrt(2 log2 M) roundings of 2.5e-8 count by what the removed modes keep of them, at most
+    half here; with the scores' own rounding and the sums' 7.8e-8 at the highest cut-off, for which a quarter more is left."""
+    import paper_2511_16786_amd as fc
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    K, V = (torch.randn((1, 1, 1, n, 64), generator=gen, device="cuda").to(
+        torch.bfloat16 if dtype == "bf16" else torch.float32) for _ in range(2))
+    comp = fc.Compressor(K, r, ref.total_budget(1, n, 0.2))
+    comp.run_score(K, V)
+    s = sum(_residual64(X, r).pow(2).sum(-1) for X in (K, V)) / 64
+    assert float((comp.scores.double() - s).norm() / s.norm()) <= 1e-7
+
+
 # Short sequences, whose tiles and windows are fewer than XCDs or a few more, of few units and of many
 @pytest.mark.parametrize("n,r,d,heads", [(300, 20, 64, 3), (512, 50, 128, 33), (700, 70, 64, 90), (1024, 91, 64, 140), (1938, 220, 128, 31),
                                          (4096, 410, 32, 60)])
