@@ -127,6 +127,10 @@ __host__ __device__ __forceinline__ int lane_point(int l) {
 // odd points descending)
 __device__ __forceinline__ int grid_pos(int k, int m) { return (k & 1) ? m - 1 - (k >> 1) : k >> 1; }
 
+// Launches that leave room for it give each block of a window's tiles a wave of its own (see residual_kernel).
+__host__ __device__ constexpr int window_blocks(int tpw) { return tpw > 8 ? 4 : (tpw > 4 ? 2 : 1); }
+__host__ __device__ constexpr int window_block(int tpw) { return (tpw + window_blocks(tpw) - 1) / window_blocks(tpw); }
+
 struct TablePtrs {
   WsHeader* hdr;
   float* wfwd;       // [M/16][steps][2][64][4]
@@ -1212,22 +1216,30 @@ constexpr int kResWorkgroups = 512;   // residual kernel: two for each compute u
 // instructions 350 and 300 are left, since a window's values are scaled and split in one instruction a term, energies of one
 // tensor's slots take one pair of sums over the wave, items follow one another without a division and loads have scalar bases.
 // Residual of 112 units, us: M = 12288 681 / 654, 16384 tokens, M = 12288 715 / 680, 30011 tokens 505 / 490, M = 3072 449 / 443.
-template <typename T, bool KEEP, bool ONCE, int BUF>
-__global__ __launch_bounds__(256, 2) void residual_kernel(
+template <typename T, bool KEEP, bool ONCE, bool BLOCKS, int BUF, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 2) void residual_kernel(
     const T* __restrict__ K, const T* __restrict__ V, KvStrides st, int u0, int u1, int n, int r, int d, int dtype,
-    int m, int tpw, int wins, SlotMap sm, bool split, int along, WsHeader* hdr, const _Float16* __restrict__ winv,
+    int m, int tpw, int wins, SlotMap sm, bool split, int blocks, int along, WsHeader* hdr, const _Float16* __restrict__ winv,
     const float2* __restrict__ grid, float* __restrict__ scores,
     double* __restrict__ epart, UnitMap um) {
   constexpr int C = kCols<T>;
   constexpr int kBuf = BUF;                                // tiles of rows under way
-  __shared__ double part_sum[4][16 * kMaxTilesPerWin];
-  __shared__ f32x4 turn_lds[4][4][64];                     // a wave's window on its way from loading to operand lanes
+  __shared__ double part_sum[WAVES][16 * kMaxTilesPerWin];
+  // a wave's window on its way from loading to operand lanes; then (BLOCKS) what each of its tiles adds to the energies
+  constexpr int kMostBlockTiles = window_block(kMaxTilesPerWin);
+  __shared__ f32x4 turn_lds[WAVES][BLOCKS ? 5 : 4][64];
+  static_assert(!BLOCKS || ONCE, "blocks of a window's tiles are worked on side by side");
+  static_assert(!BLOCKS || kMostBlockTiles * 5 * 64 * sizeof(float) <= sizeof(turn_lds[0]), "a block's energies by tile and lane");
   const double inv_d = 1.0 / (double)d, inv_dd = (double)m / (double)n;
   const int lane = threadIdx.x & 63, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // units worked on side by side: one for each wave, or (split) as many as have a wave for every part
-  const int abreast = split ? 4 / sm.wpu : 4, parts = split ? 1 : sm.wpu;
-  const int my_unit = split ? wave / sm.wpu : wave, my_part = split ? wave % sm.wpu : 0;
+  // and (BLOCKS) with a wave for every block of a window's tiles
+  // (all powers of two)
+  const int side_parts = split ? sm.wpu : 1, parts = split ? 1 : sm.wpu, log_parts = __builtin_ctz(side_parts);
+  const int log_unit = log_parts + (BLOCKS ? __builtin_ctz(blocks) : 0), abreast = WAVES >> log_unit;
+  const int my_unit = wave >> log_unit, my_part = wave & (side_parts - 1);
+  const int block_tiles = window_block(tpw), my_tile = BLOCKS ? ((wave >> log_parts) & (blocks - 1)) * block_tiles : 0;
   const int sets = (u1 - u0 + abreast - 1) / abreast, tok_tiles = (n + 15) >> 4;
   const int peers = gridDim.x >> 3;
   const Span mine_w = xcd_first(blockIdx.x & 7, along, wins), mine_s = xcd_second(blockIdx.x & 7, along, sets);
@@ -1252,6 +1264,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     s.n0 = __builtin_amdgcn_readfirstlane(first_point(16 * tpw * s.win, m, inv_dd, window_points(r, m))) >> 1;
     s.unit = min(u0 + abreast * set + my_unit, u1 - 1);    // (a surplus wave repeats the last unit)
     s.tiles = min(tpw, tok_tiles - s.win * tpw);
+    if (BLOCKS) s.tiles = max(0, min(block_tiles, s.tiles - my_tile));
     if (!ONCE) s.tiles = max(s.tiles, kBuf);               // (a tile too many is worked on and dropped)
     const int mine = s.part * 16 + (lane & 15), slot = mine < 2 * sm.nb ? mine : 0;
     const bool second = slot >= sm.nb;
@@ -1286,7 +1299,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
   const T* ahead;                                          // this lane's columns of token 4 g of the next tile to load
   int ahead_at;                                            // its first token
   auto start_rows = [&](const Seg& s) {
-    ahead_at = s.win * tpw * 16;
+    ahead_at = (s.win * tpw + my_tile) * 16;
     ahead = s.rows + ahead_at * st.sn;
   };
   auto load_rows = [&](RowPiece<T> (&x)[4]) {
@@ -1303,7 +1316,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
   };
   Frag wn[3];
   auto load_weights = [&](const Seg& s, int tl) {
-    const u32x4* p = reinterpret_cast<const u32x4*>(winv) + (size_t)(s.win * tpw + min(tl, tpw - 1)) * 192;
+    const u32x4* p = reinterpret_cast<const u32x4*>(winv) + (size_t)(s.win * tpw + min(my_tile + tl, tpw - 1)) * 192;
 #pragma unroll
     for (int q = 0; q < 3; ++q) wn[q].u = lane_load<u32x4>(p + 64 * q, lane * (uint32_t)sizeof(u32x4));
   };
@@ -1379,6 +1392,18 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     double* e = epart + (((size_t)cur.unit * wins + cur.win) * sm.wpu + cur.part) * 4;
     if ((lane & 30) == 16) e[(lane >> 5) * 2 + (lane & 1)] = lane & 1 ? ev : ek;
   };
+  // Scores of a window (or block) whose unit's parts the workgroup's waves took side by side.
+  auto add_parts = [&]() {                                 // (segments are the same for all waves of a workgroup)
+    __syncthreads();
+    if (my_part == 0)
+      for (int k = lane; k < 16 * cur.tiles; k += 64) {
+        const int token = (cur.win * tpw + my_tile) * 16 + k;
+        double s = part_sum[wave][k];
+        for (int p = 1; p < sm.wpu; ++p) s += part_sum[wave + p][k];
+        if (token < n && k < 16 * tpw) cur.score[token] = (float)(s * inv_d);
+      }
+    __syncthreads();
+  };
   auto step = [&](RowPiece<T> (&xb)[4]) {
     if (tl == 0) take_window();
     f32x4 acc[C];
@@ -1393,7 +1418,7 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     const bool last = tl + 1 == cur.tiles;
     if (!last) load_weights(cur, tl + 1);
     else if (!ONCE) load_weights(nxt, 0);
-    const int t0 = (cur.win * tpw + tl) * 16;
+    const int t0 = (cur.win * tpw + my_tile + tl) * 16;
     float h[4], t[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -1410,9 +1435,17 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
         t[i] = __uint_as_float(__float_as_uint(t[i]) & use);
       }
     }
+    const float hs = (h[0] + h[1]) + (h[2] + h[3]);
+    if constexpr (BLOCKS) {
+      float* e = reinterpret_cast<float*>(turn_lds[wave]) + tl * 320 + lane;
+      e[0] = hs;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) tot += (double)t[i];
-    hp += (double)((h[0] + h[1]) + (h[2] + h[3]));
+      for (int i = 0; i < 4; ++i) e[64 * (i + 1)] = t[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) tot += (double)t[i];
+      hp += (double)hs;
+    }
     double sum = row_sums(h, lane);
     if ((lane & 15) < 4) {
       const int k = 4 * g + (lane & 3), token = t0 + k;
@@ -1424,32 +1457,53 @@ __global__ __launch_bounds__(256, 2) void residual_kernel(
     if (!ONCE || tl + kBuf < cur.tiles) load_rows(xb);
     ++tl;
     if (last) {
-      asm volatile("");                                    // (keeps what follows out of every tile's path)
-      record();
-      if (split) {                                         // (segments are the same for all waves of a workgroup)
-        __syncthreads();
-        if (my_part == 0)
-          for (int k = lane; k < 16 * cur.tiles; k += 64) {
-            const int token = cur.win * tpw * 16 + k;
-            double s = part_sum[wave][k];
-            for (int p = 1; p < sm.wpu; ++p) s += part_sum[wave + p][k];
-            if (token < n && k < 16 * tpw) cur.score[token] = (float)(s * inv_d);
-          }
-        __syncthreads();
-      }
-      if (++part == parts) { part = 0; item += peers; }
-      more = !ONCE && item < items;
-      if constexpr (!ONCE) {
+      if constexpr (ONCE) {
+        more = false;
+      } else {
+        asm volatile("");                                  // (keeps what follows out of every tile's path)
+        record();
+        if (split) add_parts();
+        if (++part == parts) { part = 0; item += peers; }
+        more = item < items;
         cur = nxt;
         nxt = following(cur);
         tl = 0;
       }
     }
   };
+  if (BLOCKS) more = cur.tiles > 0;
   while (more) {
 #pragma unroll
     for (int k = 0; k < kBuf; ++k)
       if (more) step(x[k]);
+  }
+  if constexpr (ONCE) {
+    if constexpr (BLOCKS) {
+      // the tiles' energies in the order in which a wave that takes all of the window's adds them up
+      __syncthreads();
+      if (my_tile == 0) {
+        hp = tot = 0.0;
+        const int tiles = min(tpw, tok_tiles - cur.win * tpw);
+        for (int b = 0; b < blocks; ++b) {
+          const float* e = reinterpret_cast<const float*>(turn_lds[wave + (b << log_parts)]) + lane;
+          float add[kMostBlockTiles][5];
+#pragma unroll
+          for (int k = 0; k < kMostBlockTiles; ++k)
+#pragma unroll
+            for (int i = 0; i < 5; ++i) add[k][i] = e[k * 320 + 64 * i];
+          const int left = min(block_tiles, tiles - b * block_tiles);
+#pragma unroll
+          for (int k = 0; k < kMostBlockTiles; ++k)
+            if (k < left) {
+#pragma unroll
+              for (int i = 1; i < 5; ++i) tot += (double)add[k][i];
+              hp += (double)add[k][0];
+            }
+        }
+      }
+    }
+    if (my_tile == 0) record();
+    if (split) add_parts();
   }
 }
 
@@ -1654,9 +1708,18 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
     // the residual's waves take the parts of a unit side by side, where workgroups of four units' windows leave an XCD's without work
     const int groups = ((u1 - u0) * sm.wpu + kDecWaves - 1) / kDecWaves, gt = decimate_tiles(m, groups, lay.steps);
     const Sides dec{(m / 16 + gt - 1) / gt, groups}, fours{lay.wins, (u1 - u0 + 3) / 4};
-    const bool split = lay.wpu > 1 && lay.wpu <= 4 && xcd_items(xcds_along(dec, fours), fours) < kResWorkgroups / 8;
+    // In launches that leave room for it each block of a window's tiles, of each part, has a wave of its own: all of them resident at
+    // once (eight waves a compute unit), as workgroups of four or eight.  Scoring, us, a wave for a window / for a block: 8 units of 1381 tokens,
+    // 64 columns (13 tiles) 30.4 / 23.1, 16 of 3697 38.7 / 28.4, 20 of 2304 38.5 / 33.3, 8 of 1024 27.3 / 24.8, 2 of 512 in fp32
+    // (6 tiles) 21.3 / 20.0; windows of three tiles cut in two 26.7 / 27.4, so four are left whole.
+    const int unit_waves = lay.wpu * window_blocks(lay.tpw), block_waves = std::max(unit_waves, 4);
+    const int block_units = block_waves / unit_waves;
+    const Sides small{lay.wins, (u1 - u0 + block_units - 1) / block_units};
+    const bool by_block = unit_waves > lay.wpu && unit_waves <= 8 &&
+                          xcd_items(xcds_along(dec, small), small) * block_waves <= kResWorkgroups / 8 * 4;
+    const bool split = lay.wpu > 1 && lay.wpu <= 4 && (by_block || xcd_items(xcds_along(dec, fours), fours) < kResWorkgroups / 8);
     const int abreast = split ? 4 / lay.wpu : 4;
-    const Sides res{lay.wins, (u1 - u0 + abreast - 1) / abreast};
+    const Sides res = by_block ? small : Sides{lay.wins, (u1 - u0 + abreast - 1) / abreast};
     const int along = xcds_along(dec, res);
     const float* wfwd = reinterpret_cast<const float*>(base + lay.wfwd);
     auto decimate = gt == 4 ? launch_decimate_gt<T, 4, KEEP> : (gt == 2 ? launch_decimate_gt<T, 2, KEEP> : launch_decimate_gt<T, 1, KEEP>);
@@ -1682,14 +1745,15 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
     {
       ProfileScope ps("residual_kernel", s);
       const int items = xcd_items(along, res);
-      const bool once = (split || lay.wpu == 1) && items <= kResWorkgroups / 8;   // one segment for each wave at most
+      const bool once = by_block || ((split || lay.wpu == 1) && items <= kResWorkgroups / 8);   // one segment for each wave at most
       // Windows of a single tile (token counts below 1.7 times the grid's): with a second tile under way each would be worked on
       // twice.  Residual, two tiles / one under way: 28 layers of 8192 tokens, M = 6144 390 / 342 us, 4 layers 54 / 45, 28 of 4096,
       // M = 3072 201 / 179.
-      auto kern = once ? residual_kernel<T, KEEP, true, 2>
-                       : (lay.tpw > 1 ? residual_kernel<T, KEEP, false, 2> : residual_kernel<T, KEEP, false, 1>);
-      hipLaunchKernelGGL(kern, dim3(8 * std::min(items, kResWorkgroups / 8)), dim3(256), 0, s, K, V, st, u0, u1, n, r,
-                         d.head_dim, d.dtype, m, lay.tpw, lay.wins, sm, split, along, hdr, reinterpret_cast<const _Float16*>(base + lay.winv),
+      auto kern = by_block ? (block_waves == 8 ? residual_kernel<T, KEEP, true, true, 2, 8> : residual_kernel<T, KEEP, true, true, 2, 4>)
+                  : once   ? residual_kernel<T, KEEP, true, false, 2, 4>
+                           : (lay.tpw > 1 ? residual_kernel<T, KEEP, false, false, 2, 4> : residual_kernel<T, KEEP, false, false, 1, 4>);
+      hipLaunchKernelGGL(kern, dim3(8 * std::min(items, kResWorkgroups / 8)), dim3(by_block ? 64 * block_waves : 256), 0, s, K, V, st, u0, u1, n, r,
+                         d.head_dim, d.dtype, m, lay.tpw, lay.wins, sm, split, by_block ? window_blocks(lay.tpw) : 1, along, hdr, reinterpret_cast<const _Float16*>(base + lay.winv),
                          grid, scores, epart, um);
     }
     e = hipGetLastError();

@@ -615,6 +615,28 @@ def test_scores_by_the_tiles_of_a_wave_are_the_same_bits(n, r, heads, dtype):
         assert torch.equal(one.energy[:, :, 0], comp.energy[:, :, h])
 
 
+# Blocks of a window's tiles with a wave each (16, 13, 9, 6, 3 and 1 tiles to a window, last windows of every length) for 1, 2 and 4
+# waves a unit, one unit, a few and more than fit; together the units make launches of whole windows
+@pytest.mark.parametrize("n,r", [(1600, 40), (1381, 65), (1000, 85), (700, 66), (690, 130), (2310, 140), (600, 260)])
+@pytest.mark.parametrize("d,dtype", [(64, "bf16"), (128, "bf16"), (256, "bf16"), (72, "f32"), (32, "f32")])
+def test_blocks_of_a_windows_tiles_are_the_same_bits(n, r, d, dtype):
+    import paper_2511_16786_amd as fc
+    _scores_and_energies_follow_the_oracle(n, r, d, dtype, 3)
+    gen = torch.Generator(device="cuda").manual_seed(n + d)
+    heads = 170
+    K, V = (torch.randn((1, 1, heads, n, d), generator=gen, device="cuda").to(torch.float32 if dtype == "f32" else torch.bfloat16)
+            for _ in range(2))
+    scale = 2.0 ** torch.randint(-12, 12, (n, 1), generator=gen, device="cuda")   # (sums that no order leaves exact)
+    K, V = K * scale.to(K.dtype), V * scale.flip(0).to(V.dtype)
+    comp = fc.Compressor(K, r, fc.total_budget(1, n, 0.2))
+    comp.run_score(K, V)
+    for first, count in ((0, 1), (5, 7), (33, 40)):
+        part = fc.Compressor(K[:, :, :count], r, fc.total_budget(1, n, 0.2))
+        part.run_score(K[:, :, first:first + count], V[:, :, first:first + count])
+        assert torch.equal(part.scores, comp.scores[:, :, first:first + count])
+        assert torch.equal(part.energy, comp.energy[:, :, first:first + count])
+
+
 # The kept energy is added up per thread of the transform in 32 bits, of at most 48 points with two products each, and differently by
 # the launch that spreads a transform over more threads; then in 64 bits.  The points are the same bits.
 @pytest.mark.parametrize("n,r,dtype", [(512, 52, "f32"), (1023, 109, "bf16"), (2048, 210, "bf16"), (4099, 410, "bf16"), (8191, 820, "bf16"),
