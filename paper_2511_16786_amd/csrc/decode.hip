@@ -227,7 +227,7 @@ __device__ __forceinline__ void walk_rows(const T* __restrict__ kbase, const T* 
   }
 }
 
-template <typename T, int G, int LPR, bool PAGED, bool FITS>
+template <typename T, int G, int LPR, bool PAGED, bool FITS, bool WHOLE>
 __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(
     const T* __restrict__ Q, const T* __restrict__ Kc, const T* __restrict__ Vc,
     const int* __restrict__ budgets, const long long* __restrict__ layer_offsets, int B, int L, int H,
@@ -314,7 +314,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(
         lt = fmaf(sm_l[s2][g], w, lt);
       }
     }
-    if (whole) {                                            // (what the merge makes of a single record)
+    if constexpr (WHOLE) {                                  // (what the merge makes of a single record)
       whole[((size_t)unit * G + g) * D + dim] = lt > 0.f ? acc / lt : 0.f;
     } else {
       rec[2 * G + (size_t)g * D + dim] = acc;
@@ -347,7 +347,7 @@ __device__ __forceinline__ bf16x8 as_bf16x8(uint32_t a, uint32_t b, uint32_t c, 
 // heads (0.38 GB): 79.2 us as long as rows claimed the last-level cache, a load took 16 bytes in four places of a K row and
 // products were of 16; 74.1 with these changed, all but 1 us of it for the loads past the cache, and 66.3 in order of the
 // layers' budgets (see place_of); 896 units of 1638 rows, paged: 156 / 144 / 135.
-template <int D, bool PAGED, bool FITS>
+template <int D, bool PAGED, bool FITS, bool WHOLE>
 __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_partial_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kc, const uint16_t* __restrict__ Vc,
     const int* __restrict__ budgets, const long long* __restrict__ layer_offsets, int B, int L, int H, int G,
@@ -563,7 +563,7 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_partial_kernel(
         lt = fmaf(sm_l[s2][g], w, lt);
       }
     }
-    if (whole) {                                            // (what the merge makes of a single record)
+    if constexpr (WHOLE) {                                  // (what the merge makes of a single record)
       whole[((size_t)unit * G + g) * D + dim] = lt > 0.f ? acc / lt : 0.f;
     } else {
       rec[2 * G + (size_t)g * D + dim] = acc;
@@ -668,7 +668,7 @@ hipError_t launch_merge(const float* ws, const int32_t* budgets, int H, int G, i
 // device (by the reach alone eight sequences that keep 300 rows were ranked whatever their table: 41.3 us instead of 37.5).
 // Launches of a single piece for each unit (budgets that cannot exceed 128 rows, or more than 1024 units) write the results themselves and
 // need no merge: 13 layers of 2 heads that keep 73 rows, through tables that reach 128, 10.9 us with it, 8.0 without; 1280 units that keep 100
-// 21.9 / 17.6, of fp32 31.5 / 27.1.
+// 21.9 / 17.6, of fp32 31.5 / 27.1.  (Kernels of their own: asked at run time the others took 1 % longer.)
 struct Cut {
   int splits;
   bool spread, long_pieces;
@@ -704,8 +704,12 @@ hipError_t decode_t(const void* Q, const void* Kc, const void* Vc, int B, int L,
                          scale * 1.4426950408889634f, cut.splits, cut.spread, cut.may_rank(L, units), ws, cut.splits == 1 ? out : nullptr, pg);
     };
     const bool fits = surely_fits(B, L, H, rows_per_seq, d * (int)sizeof(T), pg);
-    if (pg.table) fits ? launch(decode_partial_kernel<T, G, LPR, true, true>) : launch(decode_partial_kernel<T, G, LPR, true, false>);
-    else fits ? launch(decode_partial_kernel<T, G, LPR, false, true>) : launch(decode_partial_kernel<T, G, LPR, false, false>);
+    auto choose = [&](auto single) {
+      constexpr bool kWhole = decltype(single)::value;
+      if (pg.table) fits ? launch(decode_partial_kernel<T, G, LPR, true, true, kWhole>) : launch(decode_partial_kernel<T, G, LPR, true, false, kWhole>);
+      else fits ? launch(decode_partial_kernel<T, G, LPR, false, true, kWhole>) : launch(decode_partial_kernel<T, G, LPR, false, false, kWhole>);
+    };
+    cut.splits == 1 ? choose(std::true_type{}) : choose(std::false_type{});
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || cut.splits == 1) return e;
@@ -727,8 +731,12 @@ hipError_t decode_mfma_t(const void* Q, const void* Kc, const void* Vc, int B, i
                          scale * 1.4426950408889634f, cut.splits, cut.spread, cut.may_rank(L, units), ws, cut.splits == 1 ? out : nullptr, pg);
     };
     const bool fits = surely_fits(B, L, H, rows_per_seq, D * (int)sizeof(uint16_t), pg);
-    if (pg.table) fits ? launch(decode_mfma_partial_kernel<D, true, true>) : launch(decode_mfma_partial_kernel<D, true, false>);
-    else fits ? launch(decode_mfma_partial_kernel<D, false, true>) : launch(decode_mfma_partial_kernel<D, false, false>);
+    auto choose = [&](auto single) {
+      constexpr bool kWhole = decltype(single)::value;
+      if (pg.table) fits ? launch(decode_mfma_partial_kernel<D, true, true, kWhole>) : launch(decode_mfma_partial_kernel<D, true, false, kWhole>);
+      else fits ? launch(decode_mfma_partial_kernel<D, false, true, kWhole>) : launch(decode_mfma_partial_kernel<D, false, false, kWhole>);
+    };
+    cut.splits == 1 ? choose(std::true_type{}) : choose(std::false_type{});
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || cut.splits == 1) return e;
