@@ -335,7 +335,7 @@ template <typename T>
 constexpr int kCols = 16 / (int)sizeof(T);
 struct SlotMap {
   int nb;        // pieces per tensor (head_dim / kCols)
-  int wpu;       // waves per unit: 1, 2, 4 or 8
+  int wpu;       // waves per unit
 };
 
 // A piece of one row, read with (KEEP) or without a claim on the last-level cache (see keep_rows).
@@ -463,8 +463,7 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decimate_kernel(
   const int gw = group * kDecWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int unit = u0 + gw / sm.wpu, part = gw % sm.wpu;
   const bool mine = unit < u1;
-  const int s_mine = part * 16 + (lane & 15);
-  const int slot = s_mine < 2 * sm.nb ? s_mine : 0;
+  const int slot = lane_slot(part, lane & 15, 2 * sm.nb);
   const bool second = slot >= sm.nb;
   const double dd = (double)n / (double)m;        // tokens per grid point
   int first[GT], count[GT], s_end = 0;            // a tile's first step, and how many it has
@@ -1192,6 +1191,15 @@ __device__ __forceinline__ double row_sums(const float (&v)[4], int lane) {
   return dpp_add<0x128>(dpp_add<0x124>((double)s));                        // row_ror:4, row_ror:8
 }
 
+// What a residual workgroup's waves take side by side: units, and of each the blocks of a window's tiles, and of each the parts.
+// (Divisors as factors: a wave's number divided by waves is one multiplication, and not the first tenth of a us of a small launch.)
+struct SideBySide {
+  int units, parts;
+  int per_unit, per_block;    // side_factor of the waves of a unit and of a block
+};
+constexpr int side_factor(int waves) { return 256 / waves + 1; }
+__device__ __forceinline__ int side_div(int wave, int factor) { return wave * factor >> 8; }   // (exact up to 8 waves)
+
 constexpr int kResWorkgroups = 512;   // residual kernel: two for each compute unit, all resident
 
 // One wave applies windows (32 grid points each) to the 16-token tiles they cover, 16 slots at a time.  Its work
@@ -1218,7 +1226,7 @@ constexpr int kResWorkgroups = 512;   // residual kernel: two for each compute u
 template <typename T, bool KEEP, bool ONCE, bool BLOCKS, int BUF, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, 2) void residual_kernel(
     const T* __restrict__ K, const T* __restrict__ V, KvStrides st, int u0, int u1, int n, int r, int d, int dtype,
-    int m, int tpw, int wins, SlotMap sm, bool split, int blocks, int along, WsHeader* hdr, const _Float16* __restrict__ winv,
+    int m, int tpw, int wins, SlotMap sm, bool split, int blocks, SideBySide side, int along, WsHeader* hdr, const _Float16* __restrict__ winv,
     const float2* __restrict__ grid, float* __restrict__ scores,
     double* __restrict__ epart, UnitMap um) {
   constexpr int C = kCols<T>;
@@ -1234,11 +1242,10 @@ __global__ __launch_bounds__(64 * WAVES, 2) void residual_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // units worked on side by side: one for each wave, or (split) as many as have a wave for every part
   // and (BLOCKS) with a wave for every block of a window's tiles
-  // (all powers of two)
-  const int side_parts = split ? sm.wpu : 1, parts = split ? 1 : sm.wpu, log_parts = __builtin_ctz(side_parts);
-  const int log_unit = log_parts + (BLOCKS ? __builtin_ctz(blocks) : 0), abreast = WAVES >> log_unit;
-  const int my_unit = wave >> log_unit, my_part = wave & (side_parts - 1);
-  const int block_tiles = window_block(tpw), my_tile = BLOCKS ? ((wave >> log_parts) & (blocks - 1)) * block_tiles : 0;
+  const int side_parts = side.parts, parts = split ? 1 : sm.wpu, abreast = side.units;
+  const int my_unit = side_div(wave, side.per_unit), of_unit = wave - my_unit * (BLOCKS ? side_parts * blocks : side_parts);
+  const int my_block = BLOCKS ? side_div(of_unit, side.per_block) : 0, my_part = of_unit - my_block * side_parts;
+  const int block_tiles = window_block(tpw), my_tile = my_block * block_tiles;
   const int sets = (u1 - u0 + abreast - 1) / abreast, tok_tiles = (n + 15) >> 4;
   const int peers = gridDim.x >> 3;
   const Span mine_w = xcd_first(blockIdx.x & 7, along, wins), mine_s = xcd_second(blockIdx.x & 7, along, sets);
@@ -1265,7 +1272,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void residual_kernel(
     s.tiles = min(tpw, tok_tiles - s.win * tpw);
     if (BLOCKS) s.tiles = max(0, min(block_tiles, s.tiles - my_tile));
     if (!ONCE) s.tiles = max(s.tiles, kBuf);               // (a tile too many is worked on and dropped)
-    const int mine = s.part * 16 + (lane & 15), slot = mine < 2 * sm.nb ? mine : 0;
+    const int slot = lane_slot(s.part, lane & 15, 2 * sm.nb);
     const bool second = slot >= sm.nb;
     s.rows = (second ? V : K) + unit_offset(st, s.unit) + (slot - (second ? sm.nb : 0)) * C + (int64_t)(4 * g) * st.sn;
     s.score = scores + (size_t)out_unit(um, s.unit) * n;
@@ -1286,8 +1293,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void residual_kernel(
   };
   f32x4 v[C / 2][4];
   auto load_window = [&](const Seg& s) {
-    // (a slot past the last loads the part's first, a part past the last the unit's; addresses are a scalar base and 32 bits of the lane's)
-    const int slots = 2 * sm.nb - s.part * 16, slot = (lane >> 2) < slots ? lane >> 2 : 0, first = slots > 0 ? s.part * 16 : 0;
+    // (addresses are a scalar base and 32 bits of the lane's)
+    const int first = s.part * 16, slot = lane_slot(s.part, lane >> 2, 2 * sm.nb) - first;
     const uint32_t at = ((uint32_t)(slot * (C / 2) * m) + 2 * ((lane ^ (lane >> 3)) & 3)) * (uint32_t)sizeof(float2);
     const float2* base = grid + ((size_t)(s.unit - u0) * 2 * sm.nb + first) * (C / 2) * m;
 #pragma unroll
@@ -1484,7 +1491,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void residual_kernel(
         hp = tot = 0.0;
         const int tiles = min(tpw, tok_tiles - cur.win * tpw);
         for (int b = 0; b < blocks; ++b) {
-          const float* e = reinterpret_cast<const float*>(turn_lds[wave + (b << log_parts)]) + lane;
+          const float* e = reinterpret_cast<const float*>(turn_lds[wave + b * side_parts]) + lane;
           float add[kMostBlockTiles][5];
 #pragma unroll
           for (int k = 0; k < kMostBlockTiles; ++k)
@@ -1595,8 +1602,6 @@ static bool wide_transform(int64_t n, int64_t r, int64_t m) { return m <= 4096 &
 // (below 256 tokens the products with the basis itself are as quick and need no plan worth speaking of)
 bool resample_supported(const fc_kv_desc& d, int32_t r) { return d.n_tokens >= 256 && grid_length(d, r) != 0; }
 
-static int waves_per_unit(int nb) { return nb <= 8 ? 1 : (nb <= 16 ? 2 : (nb <= 32 ? 4 : 8)); }
-
 ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
   ResampleLayout lay{};
   const int64_t n = d.n_tokens, m = grid_length(d, r);
@@ -1613,7 +1618,7 @@ ResampleLayout resample_layout(const fc_kv_desc& d, int32_t r) {
   lay.wins = (tok_tiles + lay.tpw - 1) / lay.tpw;
   lay.pairs = d.head_dim / 2;
   lay.nb = d.head_dim * (d.dtype == FC_BF16 ? 2 : 4) / 16;
-  lay.wpu = waves_per_unit(lay.nb);
+  lay.wpu = slot_waves(2 * lay.nb);
   // units per round of the three kernels
   const size_t unit_grid = 2 * (size_t)m * d.head_dim * sizeof(float);
   const bool much_grid = (size_t)n * (d.dtype == FC_BF16 ? 2 : 4) < 2 * (size_t)m * sizeof(float);
@@ -1640,7 +1645,7 @@ size_t resample_reserve(const fc_kv_desc& d) {
   const size_t n = d.n_tokens, nb = d.head_dim / 8, units = (size_t)d.batch * d.layers * d.kv_heads;
   const size_t m = std::min<size_t>(kMaxGrid, n * 5 / 4);
   const size_t tables = 296 * n + 288 * m + (256 << 10);
-  const size_t records = units * (64 * nb + 2 * n * waves_per_unit((int)nb * (d.dtype == FC_BF16 ? 1 : 2)) + 64 * 8);
+  const size_t records = units * (64 * nb + 2 * n * slot_waves(2 * (int)nb * (d.dtype == FC_BF16 ? 1 : 2)) + 64 * 8);
   const size_t grid = std::max<size_t>(kRoundGridBytes, 64 * nb * m);
   const size_t need = tables + records + std::min<size_t>(grid, units * 64 * nb * m);
   const size_t have = units * 2 * (nb / 2) * n * sizeof(float);
@@ -1713,7 +1718,7 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
     const int groups = ((u1 - u0) * sm.wpu + kDecWaves - 1) / kDecWaves, gt = decimate_tiles(m, groups, lay.steps, sizeof(T) == 2);
     const Sides dec{(m / 16 + gt - 1) / gt, groups}, fours{lay.wins, (u1 - u0 + 3) / 4};
     // In launches that leave room for it each block of a window's tiles, of each part, has a wave of its own: all of them resident at
-    // once (eight waves a compute unit), as workgroups of four or eight.  Scoring, us, a wave for a window / for a block: 8 units of 1381 tokens,
+    // once (eight waves a compute unit), as workgroups of four to eight.  Scoring, us, a wave for a window / for a block: 8 units of 1381 tokens,
     // 64 columns (13 tiles) 30.4 / 23.1, 16 of 3697 38.7 / 28.4, 20 of 2304 38.5 / 33.3, 8 of 1024 27.3 / 24.8, 2 of 512 in fp32
     // (6 tiles) 21.3 / 20.0; windows of three tiles cut in two 26.7 / 27.4, so four are left whole.
     const int unit_waves = lay.wpu * window_blocks(lay.tpw), block_waves = std::max(unit_waves, 4);
@@ -1722,7 +1727,7 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
     const bool by_block = unit_waves > lay.wpu && unit_waves <= 8 &&
                           xcd_items(xcds_along(dec, small), small) * block_waves <= kResWorkgroups / 8 * 4;
     const bool split = lay.wpu > 1 && lay.wpu <= 4 && (by_block || xcd_items(xcds_along(dec, fours), fours) < kResWorkgroups / 8);
-    const int abreast = split ? 4 / lay.wpu : 4;
+    const int abreast = split ? 4 / lay.wpu : 4, res_waves = by_block ? block_waves : (split ? abreast * lay.wpu : 4);
     const Sides res = by_block ? small : Sides{lay.wins, (u1 - u0 + abreast - 1) / abreast};
     const int along = xcds_along(dec, res);
     const float* wfwd = reinterpret_cast<const float*>(base + lay.wfwd);
@@ -1753,11 +1758,13 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
       // Windows of a single tile (token counts below 1.7 times the grid's): with a second tile under way each would be worked on
       // twice.  Residual, two tiles / one under way: 28 layers of 8192 tokens, M = 6144 390 / 342 us, 4 layers 54 / 45, 28 of 4096,
       // M = 3072 201 / 179.
-      auto kern = by_block ? (block_waves == 8 ? residual_kernel<T, KEEP, true, true, 2, 8> : residual_kernel<T, KEEP, true, true, 2, 4>)
+      auto kern = by_block ? (block_waves > 4 ? residual_kernel<T, KEEP, true, true, 2, 8> : residual_kernel<T, KEEP, true, true, 2, 4>)
                   : once   ? residual_kernel<T, KEEP, true, false, 2, 4>
                            : (lay.tpw > 1 ? residual_kernel<T, KEEP, false, false, 2, 4> : residual_kernel<T, KEEP, false, false, 1, 4>);
-      hipLaunchKernelGGL(kern, dim3(8 * std::min(items, kResWorkgroups / 8)), dim3(by_block ? 64 * block_waves : 256), 0, s, K, V, st, u0, u1, n, r,
-                         d.head_dim, d.dtype, m, lay.tpw, lay.wins, sm, split, by_block ? window_blocks(lay.tpw) : 1, along, hdr, reinterpret_cast<const _Float16*>(base + lay.winv),
+      const int side_parts = split ? lay.wpu : 1, blocks = by_block ? window_blocks(lay.tpw) : 1;
+      const SideBySide side{by_block ? block_units : abreast, side_parts, side_factor(side_parts * blocks), side_factor(side_parts)};
+      hipLaunchKernelGGL(kern, dim3(8 * std::min(items, kResWorkgroups / 8)), dim3(64 * res_waves), 0, s, K, V, st, u0, u1, n, r,
+                         d.head_dim, d.dtype, m, lay.tpw, lay.wins, sm, split, blocks, side, along, hdr, reinterpret_cast<const _Float16*>(base + lay.winv),
                          grid, scores, epart, um);
     }
     e = hipGetLastError();

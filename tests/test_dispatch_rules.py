@@ -22,6 +22,8 @@ void xcd_rectangle(int xcd, int along, int first, int second, int* out) {
   const fc::Span a = fc::xcd_first(xcd, along, first), b = fc::xcd_second(xcd, along, second);
   out[0] = a.from; out[1] = a.count; out[2] = b.from; out[3] = b.count;
 }
+int slot_waves(int slots) { return fc::slot_waves(slots); }
+int lane_slot(int part, int lane, int slots) { return fc::lane_slot(part, lane, slots); }
 bool keeps_rows(long long rows, int row_bytes) { return fc::keeps_rows(rows, row_bytes); }
 bool ranks_by_budget(long long rows, int layers, int splits, int row_bytes) { return fc::ranks_by_budget(rows, layers, splits, row_bytes); }
 }
@@ -113,3 +115,13 @@ def test_xcds_take_rectangles_that_cover_the_work(rules):
     # long sequences are cut along the tokens for all XCDs, short ones along the units as well
     assert [rules.xcds_along(*x) for x in ((48, 30, 158, 15), (96, 20, 376, 10), (24, 56, 86, 28), (48, 8, 43, 8))] == [3, 3, 3, 3]
     assert [rules.xcds_along(*x) for x in ((3, 180, 11, 180), (2, 32, 6, 32), (12, 56, 43, 28))] == [0, 1, 2]
+
+
+def test_waves_have_slots_of_their_own_and_lanes_load_what_their_wave_loads(rules):
+    for slots in range(2, 129, 2):
+        waves = rules.slot_waves(slots)
+        loaded = [[rules.lane_slot(part, lane, slots) for lane in range(16)] for part in range(waves)]
+        assert [s for part in range(waves) for s in loaded[part][:slots - 16 * part]] == list(range(slots))
+        for part in range(waves):
+            # (no wave is empty, and what its lanes past the last slot load is one of its own)
+            assert 16 * part < slots and all(16 * part <= s < 16 * part + 16 for s in loaded[part])
