@@ -338,7 +338,7 @@ struct SlotMap {
   int wpu;       // waves per unit
 };
 
-// A piece of one row, read with (KEEP) or without a claim on the last-level cache (see keep_rows).
+// A piece of one row, read with (KEEP) or without a claim on the last-level cache (see round_keeps_rows).
 template <bool KEEP, typename V>
 __device__ __forceinline__ V load_piece(const void* p) {
   if constexpr (KEEP) return *static_cast<const V*>(p);
@@ -1555,7 +1555,7 @@ hipError_t launch_filter(float2* grid, int pairs, int n, int r, int d, int dtype
 }  // namespace
 
 // Bytes of grid one round of the three kernels works on.  They are written, read, written and read again: below the
-// last-level cache's 256 MB, and with the rows kept out of it (keep_rows), three of the four ways stay on the chip, while
+// last-level cache's 256 MB, and with the rows kept out of it (round_keeps_rows), three of the four ways stay on the chip, while
 // smaller rounds leave the launches too little to work on.  Scoring 112 units of 30011 tokens, M = 6144, rounds of 176,
 // 201, 251 and 302 MB: 1394, 1376, 1337, 1452 us; with ordinary loads of the rows larger rounds are better.  Where the rows are less
 // than twice the grid, rounds of 201 MB are (8000 tokens, M = 4096: 168 MB 749 us, 251 MB 766; 32768 tokens, M = 12288: 201
@@ -1773,12 +1773,9 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
   return energy_reduce_launch(epart, lay.wins * lay.wpu, units, energy, um, s);
 }
 
-// Whether a round's rows fit the last-level cache, to be found there on their second reading; else they are read
-// without a claim on it, which leaves it to the grid.  Scoring, kept / not kept: 246 MB of rows 168 / 182 us, 268 MB
-// 234 / 232, 470 MB 413 / 377, 738 MB 516 / 457; 34 MB 50 / 60.  fp32: 940 MB 575 / 558, 560 MB 1093 / 1040 (in rounds), 34 MB
-// 114 / 126, 7 MB 38 / 44.
 static bool keep_rows(const fc_kv_desc& d, const ResampleLayout& lay) {
-  return (size_t)lay.chunk * 2 * d.n_tokens * d.head_dim * (d.dtype == FC_BF16 ? 2 : 4) <= (size_t)256 * 1000 * 1000;
+  const int row_bytes = d.head_dim * (d.dtype == FC_BF16 ? 2 : 4);
+  return round_keeps_rows((long long)lay.chunk * 2 * d.n_tokens * row_bytes, row_bytes);
 }
 
 hipError_t resample_score(const void* K, const void* V, const fc_kv_desc& d, int32_t r, const ResampleLayout& lay,

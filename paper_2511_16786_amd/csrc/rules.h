@@ -75,6 +75,14 @@ constexpr Span xcd_second(int xcd, int along, int second) {
 constexpr int slot_waves(int slots) { return (slots + 15) / 16; }
 constexpr int lane_slot(int part, int lane, int slots) { return part * 16 + lane < slots ? part * 16 + lane : slots - 1; }
 
+// Whether the row kernels read a round's rows with a claim on the last-level cache.  Rows that fit it are found there on their second
+// reading; of others it is left to the grid.  Scoring, us, kept / not kept: 246 MB of rows 168 / 182, 268 MB 234 / 232, 470 MB 413 /
+// 377, 738 MB 516 / 457; 34 MB 50 / 60.  fp32: 940 MB 575 / 558, 560 MB 1093 / 1040 (in rounds), 34 MB 114 / 126, 7 MB 38 / 44.
+// Rows that are not whole lines of 128 bytes are kept whatever their size: a line is asked for by the rows or waves that share it, and read
+// past the cache it is often gone by then.  fp32 rows of 8192 tokens, r = 820, kept / not kept: 8 columns 577 / 607, 24 396 / 436, 40 521 / 559, 248 295 /
+// 314, but 32 504 / 477, 96 370 / 358, 160 395 / 383, 224 430 / 415; bf16: 8 columns 658 / 677, 24 448 / 481, 72 634 / 689, 136 571 / 604.
+constexpr bool round_keeps_rows(long long round_bytes, int row_bytes) { return row_bytes % 128 != 0 || round_bytes <= 256 * 1000 * 1000; }
+
 // Where the grid begins in its region of a workspace, both at multiples of 256 bytes: an odd multiple, whatever the
 // workspace's own address is.  A grid at a multiple of 512 costs the residual kernel a tenth where M is a power of two (28 layers of
 // 4096 tokens, M = 4096: 182 us at 128, 256, 768, 1280 and 2304 bytes past a multiple of 4096, 204 at 0 and 512).

@@ -24,6 +24,7 @@ void xcd_rectangle(int xcd, int along, int first, int second, int* out) {
 }
 int slot_waves(int slots) { return fc::slot_waves(slots); }
 int lane_slot(int part, int lane, int slots) { return fc::lane_slot(part, lane, slots); }
+bool round_keeps_rows(long long bytes, int row_bytes) { return fc::round_keeps_rows(bytes, row_bytes); }
 bool keeps_rows(long long rows, int row_bytes) { return fc::keeps_rows(rows, row_bytes); }
 bool ranks_by_budget(long long rows, int layers, int splits, int row_bytes) { return fc::ranks_by_budget(rows, layers, splits, row_bytes); }
 }
@@ -125,3 +126,12 @@ def test_waves_have_slots_of_their_own_and_lanes_load_what_their_wave_loads(rule
         for part in range(waves):
             # (no wave is empty, and what its lanes past the last slot load is one of its own)
             assert 16 * part < slots and all(16 * part <= s < 16 * part + 16 for s in loaded[part])
+
+
+def test_rows_of_whole_lines_alone_are_read_past_the_cache(rules):
+    keeps = rules.round_keeps_rows
+    keeps.restype, keeps.argtypes = ctypes.c_bool, [ctypes.c_longlong, ctypes.c_int]
+    for row_bytes in range(16, 1040, 16):
+        assert keeps(256_000_000, row_bytes) and keeps(1, row_bytes)
+        for much in (256_000_001, 10 ** 10):
+            assert keeps(much, row_bytes) == (row_bytes % 128 != 0)
