@@ -127,10 +127,6 @@ __host__ __device__ __forceinline__ int lane_point(int l) {
 // odd points descending)
 __device__ __forceinline__ int grid_pos(int k, int m) { return (k & 1) ? m - 1 - (k >> 1) : k >> 1; }
 
-// Launches that leave room for it give each block of a window's tiles a wave of its own (see residual_kernel).
-__host__ __device__ constexpr int window_blocks(int tpw) { return tpw > 8 ? 4 : (tpw > 4 ? 2 : 1); }
-__host__ __device__ constexpr int window_block(int tpw) { return (tpw + window_blocks(tpw) - 1) / window_blocks(tpw); }
-
 struct TablePtrs {
   WsHeader* hdr;
   float* wfwd;       // [M/16][steps][2][64][4]
@@ -1200,12 +1196,10 @@ struct SideBySide {
 constexpr int side_factor(int waves) { return 256 / waves + 1; }
 __device__ __forceinline__ int side_div(int wave, int factor) { return wave * factor >> 8; }   // (exact up to 8 waves)
 
-constexpr int kResWorkgroups = 512;   // residual kernel: two for each compute unit, all resident
-
 // One wave applies windows (32 grid points each) to the 16-token tiles they cover, 16 slots at a time.  Its work
 // is a list of segments: a window, a unit (four units at a time, one for each wave of a workgroup), a part of the
-// unit's slots; with few segments (split) a workgroup's waves take the parts of a unit side by side instead of one
-// after the other.  Rows are requested two tiles ahead and grid values one window ahead, across segments.
+// unit's slots; with few segments, and for fp32 always (split), a workgroup's waves take the parts of a unit side by side
+// instead of one after the other.  Rows are requested two tiles ahead and grid values one window ahead, across segments.
 // Neighbouring windows read the same lines of the grid: an XCD takes a contiguous range of windows and its
 // workgroups walk (units, window) side by side, window fastest, so that its L2 serves what they share.  Launches with no
 // more than one segment for a wave (ONCE) ask for nothing ahead of a next one (one layer of 16384 tokens: 19.7 / 19.1 us).
@@ -1224,7 +1218,7 @@ constexpr int kResWorkgroups = 512;   // residual kernel: two for each compute u
 // tensor's slots take one pair of sums over the wave, items follow one another without a division and loads have scalar bases.
 // Residual of 112 units, us: M = 12288 681 / 654, 16384 tokens, M = 12288 715 / 680, 30011 tokens 505 / 490, M = 3072 449 / 443.
 template <typename T, bool KEEP, bool ONCE, bool BLOCKS, int BUF, int WAVES>
-__global__ __launch_bounds__(64 * WAVES, 2) void residual_kernel(
+__global__ __launch_bounds__(64 * WAVES, residual_waves(sizeof(T) == 2, ONCE) / 4) void residual_kernel(
     const T* __restrict__ K, const T* __restrict__ V, KvStrides st, int u0, int u1, int n, int r, int d, int dtype,
     int m, int tpw, int wins, SlotMap sm, bool split, int blocks, SideBySide side, int along, WsHeader* hdr, const _Float16* __restrict__ winv,
     const float2* __restrict__ grid, float* __restrict__ scores,
@@ -1411,7 +1405,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void residual_kernel(
     __syncthreads();
   };
   auto step = [&](RowPiece<T> (&xb)[4]) {
-    if (tl == 0) take_window();
+    if (!ONCE && tl == 0) take_window();
     f32x4 acc[C];
 #pragma unroll
     for (int j = 0; j < C; ++j) {
@@ -1478,6 +1472,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void residual_kernel(
     }
   };
   if (BLOCKS) more = cur.tiles > 0;
+  if (ONCE && more) take_window();                         // (out of the loop, in which its registers are free: 232 are 161, of fp32 152 are 113)
   while (more) {
 #pragma unroll
     for (int k = 0; k < kBuf; ++k)
@@ -1714,25 +1709,12 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
   // and the rows neighbouring tiles share
   for (int u0 = 0; u0 < units; u0 += lay.chunk) {
     const int u1 = std::min(units, u0 + lay.chunk);
-    // the residual's waves take the parts of a unit side by side, where workgroups of four units' windows leave an XCD's without work
     const int groups = ((u1 - u0) * sm.wpu + kDecWaves - 1) / kDecWaves, gt = decimate_tiles(m, groups, lay.steps, sizeof(T) == 2);
-    const Sides dec{(m / 16 + gt - 1) / gt, groups}, fours{lay.wins, (u1 - u0 + 3) / 4};
-    // In launches that leave room for it each block of a window's tiles, of each part, has a wave of its own: all of them resident at
-    // once (eight waves a compute unit), as workgroups of four to eight.  Scoring, us, a wave for a window / for a block: 8 units of 1381 tokens,
-    // 64 columns (13 tiles) 30.4 / 23.1, 16 of 3697 38.7 / 28.4, 20 of 2304 38.5 / 33.3, 8 of 1024 27.3 / 24.8, 2 of 512 in fp32
-    // (6 tiles) 21.3 / 20.0; windows of three tiles cut in two 26.7 / 27.4, so four are left whole.
-    const int unit_waves = lay.wpu * window_blocks(lay.tpw), block_waves = std::max(unit_waves, 4);
-    const int block_units = block_waves / unit_waves;
-    const Sides small{lay.wins, (u1 - u0 + block_units - 1) / block_units};
-    const bool by_block = unit_waves > lay.wpu && unit_waves <= 8 &&
-                          xcd_items(xcds_along(dec, small), small) * block_waves <= kResWorkgroups / 8 * 4;
-    const bool split = lay.wpu > 1 && lay.wpu <= 4 && (by_block || xcd_items(xcds_along(dec, fours), fours) < kResWorkgroups / 8);
-    const int abreast = split ? 4 / lay.wpu : 4, res_waves = by_block ? block_waves : (split ? abreast * lay.wpu : 4);
-    const Sides res = by_block ? small : Sides{lay.wins, (u1 - u0 + abreast - 1) / abreast};
-    const int along = xcds_along(dec, res);
+    const Sides dec{(m / 16 + gt - 1) / gt, groups};
+    const ResidualPlan res = residual_plan(lay.wins, lay.tpw, lay.wpu, u1 - u0, dec, sizeof(T) == 2);
     const float* wfwd = reinterpret_cast<const float*>(base + lay.wfwd);
     auto decimate = gt == 4 ? launch_decimate_gt<T, 4, KEEP> : (gt == 2 ? launch_decimate_gt<T, 2, KEEP> : launch_decimate_gt<T, 1, KEEP>);
-    hipError_t e = decimate(K, V, st, u0, u1, n, r, d, m, lay, sm, dec, along, hdr, wfwd, grid, s);
+    hipError_t e = decimate(K, V, st, u0, u1, n, r, d, m, lay, sm, dec, res.along, hdr, wfwd, grid, s);
     if (e != hipSuccess) return e;
     double* elow = reinterpret_cast<double*>(base + lay.elow) + (size_t)u0 * 2 * lay.pairs;
     const int pairs = (u1 - u0) * 2 * lay.pairs;
@@ -1753,18 +1735,21 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
     if (e != hipSuccess) return e;
     {
       ProfileScope ps("residual_kernel", s);
-      const int items = xcd_items(along, res);
-      const bool once = by_block || ((split || lay.wpu == 1) && items <= kResWorkgroups / 8);   // one segment for each wave at most
       // Windows of a single tile (token counts below 1.7 times the grid's): with a second tile under way each would be worked on
       // twice.  Residual, two tiles / one under way: 28 layers of 8192 tokens, M = 6144 390 / 342 us, 4 layers 54 / 45, 28 of 4096,
       // M = 3072 201 / 179.
-      auto kern = by_block ? (block_waves > 4 ? residual_kernel<T, KEEP, true, true, 2, 8> : residual_kernel<T, KEEP, true, true, 2, 4>)
-                  : once   ? residual_kernel<T, KEEP, true, false, 2, 4>
-                           : (lay.tpw > 1 ? residual_kernel<T, KEEP, false, false, 2, 4> : residual_kernel<T, KEEP, false, false, 1, 4>);
-      const int side_parts = split ? lay.wpu : 1, blocks = by_block ? window_blocks(lay.tpw) : 1;
-      const SideBySide side{by_block ? block_units : abreast, side_parts, side_factor(side_parts * blocks), side_factor(side_parts)};
-      hipLaunchKernelGGL(kern, dim3(8 * std::min(items, kResWorkgroups / 8)), dim3(64 * res_waves), 0, s, K, V, st, u0, u1, n, r,
-                         d.head_dim, d.dtype, m, lay.tpw, lay.wins, sm, split, blocks, side, along, hdr, reinterpret_cast<const _Float16*>(base + lay.winv),
+      constexpr bool kWide = sizeof(T) == 4;               // (a unit has more than four parts: fp32 rows of more than 128 columns)
+      auto kern = res.blocks > 1 ? (res.waves > 4 ? residual_kernel<T, KEEP, true, true, 2, 8> : residual_kernel<T, KEEP, true, true, 2, 4>)
+                  : res.once     ? residual_kernel<T, KEEP, true, false, 2, 4>
+                  : lay.tpw > 1  ? residual_kernel<T, KEEP, false, false, 2, 4> : residual_kernel<T, KEEP, false, false, 1, 4>;
+      if constexpr (kWide)
+        if (res.blocks == 1 && res.waves > 4)
+          kern = res.once ? residual_kernel<T, KEEP, true, false, 2, 8>
+                 : lay.tpw > 1 ? residual_kernel<T, KEEP, false, false, 2, 8> : residual_kernel<T, KEEP, false, false, 1, 8>;
+      const int side_parts = res.split ? lay.wpu : 1;
+      const SideBySide side{res.abreast, side_parts, side_factor(side_parts * res.blocks), side_factor(side_parts)};
+      hipLaunchKernelGGL(kern, dim3(8 * res.workgroups), dim3(64 * res.waves), 0, s, K, V, st, u0, u1, n, r,
+                         d.head_dim, d.dtype, m, lay.tpw, lay.wins, sm, res.split, res.blocks, side, res.along, hdr, reinterpret_cast<const _Float16*>(base + lay.winv),
                          grid, scores, epart, um);
     }
     e = hipGetLastError();

@@ -75,6 +75,50 @@ constexpr Span xcd_second(int xcd, int along, int second) {
 constexpr int slot_waves(int slots) { return (slots + 15) / 16; }
 constexpr int lane_slot(int part, int lane, int slots) { return part * 16 + lane < slots ? part * 16 + lane : slots - 1; }
 
+// A window's tiles are cut in blocks, with a wave each, in launches that leave room for it.
+constexpr int window_blocks(int tpw) { return tpw > 8 ? 4 : (tpw > 4 ? 2 : 1); }
+constexpr int window_block(int tpw) { return (tpw + window_blocks(tpw) - 1) / window_blocks(tpw); }
+
+// Waves of the residual kernel that a compute unit holds: of bf16 rows eight; a wave of fp32 rows has half the columns and so half the
+// registers, and twelve of them are under way, 16 in launches of one segment for each (ONCE).
+constexpr int residual_waves(bool bf16, bool once) { return bf16 ? 8 : (once ? 16 : 12); }
+
+// Work of a residual launch: windows (wins, of tpw tiles) along one side, units abreast in a workgroup along the other; a unit has as many parts
+// as slot_waves.  Workgroups of four waves take a unit each, or (split) a unit's parts side by side; of five to eight where a unit has
+// that many.
+//   bf16: split where workgroups of four units leave an XCD's compute units without two each.  Else the waves take the parts in turn, which
+//   needs no barriers.
+//   fp32: always split, as many workgroups as are resident.  Scoring, us, pieces of 32 bytes / parts in turn, two workgroups a compute unit / split,
+//   two / split, three: 112 units of 8192 tokens 572 / 526 / 510 / 514, 154 of 12032, 72 columns 643 / 587 / 580 / 558, 36 of 16384, 64 columns 170 / 188 / 165 / 162,
+//   3 of 48283 85 / 91 / 85 / 85, one of 55808 80 / 85 / 63 / 63, 50 of 9000, 256 columns 546 / - / 490 / 485; 80 and 112 workgroups an XCD, which compute units share
+//   unevenly, 534 and 539 where 96 take 514.  More than four parts, in turn / split: one of 512, 256 columns 56 / 23, 4 of 2048,
+//   136 columns 60 / 25, 16 of 4096, 256 columns 94 / 81 (pieces of 32 bytes 28, 32, 89).
+// In launches that leave room for it each block of a window's tiles, of each part, has a wave of its own: all of them resident at
+// once (eight waves a compute unit), as workgroups of four to eight.  Scoring, us, a wave for a window / for a block: 8 units of 1381 tokens,
+// 64 columns (13 tiles) 30.4 / 23.1, 16 of 3697 38.7 / 28.4, 20 of 2304 38.5 / 33.3, 8 of 1024 27.3 / 24.8, 2 of 512 in fp32
+// (6 tiles) 21.3 / 20.0; windows of three tiles cut in two 26.7 / 27.4, so four are left whole.
+struct ResidualPlan {
+  int waves, abreast, blocks;         // of a workgroup; units side by side; of a window's tiles (1: a wave takes them all)
+  bool split, once;                   // parts side by side; no more than one segment for each wave
+  int along, workgroups;              // the XCDs' cut; of an XCD
+};
+constexpr ResidualPlan residual_plan(int wins, int tpw, int parts, int units, Sides dec, bool bf16) {
+  const int blocks = window_blocks(tpw), unit_waves = parts * blocks, block_waves = unit_waves > 4 ? unit_waves : 4;
+  const int block_units = block_waves / unit_waves > 1 ? block_waves / unit_waves : 1;
+  const Sides small{wins, (units + block_units - 1) / block_units}, fours{wins, (units + 3) / 4};
+  if (blocks > 1 && unit_waves <= 8) {
+    const int along = xcds_along(dec, small), items = xcd_items(along, small);
+    if (items * block_waves <= 32 * 8) return {block_waves, block_units, blocks, parts > 1, true, along, items};
+  }
+  const bool split = parts > 1 && (!bf16 || xcd_items(xcds_along(dec, fours), fours) < 64);
+  const int abreast = split ? (parts < 4 ? 4 / parts : 1) : 4, waves = split ? abreast * parts : 4;
+  const Sides all{wins, (units + abreast - 1) / abreast};
+  const int along = xcds_along(dec, all), items = xcd_items(along, all), as_four = waves < 4 ? 4 : waves;
+  const int held = 32 * (residual_waves(bf16, false) / as_four), held_once = 32 * (residual_waves(bf16, true) / as_four);
+  const bool once = (split || parts == 1) && items <= held_once;
+  return {waves, abreast, 1, split, once, along, once || items < held ? items : held};
+}
+
 // Whether the row kernels read a round's rows with a claim on the last-level cache.  Rows that fit it are found there on their second
 // reading; of others it is left to the grid.  Scoring, us, kept / not kept: 246 MB of rows 168 / 182, 268 MB 234 / 232, 470 MB 413 /
 // 377, 738 MB 516 / 457; 34 MB 50 / 60.  fp32: 940 MB 575 / 558, 560 MB 1093 / 1040 (in rounds), 34 MB 114 / 126, 7 MB 38 / 44.

@@ -25,6 +25,11 @@ void xcd_rectangle(int xcd, int along, int first, int second, int* out) {
 int slot_waves(int slots) { return fc::slot_waves(slots); }
 int lane_slot(int part, int lane, int slots) { return fc::lane_slot(part, lane, slots); }
 bool round_keeps_rows(long long bytes, int row_bytes) { return fc::round_keeps_rows(bytes, row_bytes); }
+void residual_plan(int wins, int tpw, int parts, int units, int f, int sec, bool bf16, int* out) {
+  const fc::ResidualPlan p = fc::residual_plan(wins, tpw, parts, units, {f, sec}, bf16);
+  out[0] = p.waves; out[1] = p.abreast; out[2] = p.blocks; out[3] = p.split; out[4] = p.once; out[5] = p.along; out[6] = p.workgroups;
+}
+int residual_waves(bool bf16, bool once) { return fc::residual_waves(bf16, once); }
 bool keeps_rows(long long rows, int row_bytes) { return fc::keeps_rows(rows, row_bytes); }
 bool ranks_by_budget(long long rows, int layers, int splits, int row_bytes) { return fc::ranks_by_budget(rows, layers, splits, row_bytes); }
 }
@@ -135,3 +140,31 @@ def test_rows_of_whole_lines_alone_are_read_past_the_cache(rules):
         assert keeps(256_000_000, row_bytes) and keeps(1, row_bytes)
         for much in (256_000_001, 10 ** 10):
             assert keeps(much, row_bytes) == (row_bytes % 128 != 0)
+
+
+def test_residual_workgroups_take_parts_side_by_side_and_are_resident(rules):
+    out = (ctypes.c_int * 7)()
+
+    def plan(wins, tpw, parts, units, dec, bf16):
+        rules.residual_plan(wins, tpw, parts, units, *dec, bf16, out)
+        return list(out)
+    for bf16 in (False, True):
+        for parts in range(1, 5 if bf16 else 9):
+            for tpw in (1, 2, 3, 5, 9, 16):
+                for wins in (1, 4, 14, 100, 700):
+                    for units in (1, 2, 3, 4, 16, 112, 900):
+                        dec = (max(1, wins // 2), -(-units * parts // 4))
+                        waves, abreast, blocks, split, once, along, workgroups = plan(wins, tpw, parts, units, dec, bf16)
+                        of_unit = (parts if split else 1) * blocks
+                        assert 1 <= waves <= 8 and abreast == waves // of_unit and waves == abreast * of_unit
+                        assert split == (parts > 1) or (bf16 and blocks == 1)
+                        items = rules.xcd_items(along, wins, -(-units // abreast))
+                        held = 32 * (rules.residual_waves(bf16, once) // max(4, waves))
+                        assert workgroups == (items if once else min(items, held)) and workgroups <= max(held, 32 * 8 // waves)
+                        held_once = 32 * (rules.residual_waves(bf16, True) // max(4, waves))
+                        assert blocks > 1 or once == ((split or parts == 1) and items <= held_once)
+    # one layer of a head of 256 fp32 columns and the like: a wave for every part, one turn
+    for parts in (5, 6, 8):
+        for wins, units in ((14, 1), (43, 4), (21, 4)):
+            waves, abreast, _, split, once, _, workgroups = plan(wins, 3, parts, units, (16, units * parts // 4), False)
+            assert (waves, abreast, split, once) == (parts, 1, 1, 1) and workgroups <= 64
