@@ -43,16 +43,20 @@ constexpr int round_units(int units, int most, int windows) {
 // more than a sixteenth: a short sequence has fewer tiles or windows than XCDs, or a few more.  The cut is the same for both, so that
 // an XCD's L2 has the second kernel's rows where they fit (4 layers of 4096 tokens, cut for 8 and for 4: 43 us, both for 8 42).
 // Scoring, us, cut for 8 always / now: 720 units of 1024 tokens, 64 columns 215 / 145, 128 of 512, 128 columns 51 / 40, 112 of 4096 205 /
-// 184, 248 of 1938 219 / 204.
+// 184, 248 of 1938 219 / 204.  Where the second kernel's items, cut along the tokens, are all under way at once (at_once of an XCD), so they are
+// as cut: a rectangle a few items larger costs it a second turn (41 units of 4869 tokens, 63 and 66 items where an XCD holds 64: 67.3 and 76.9 us, 82
+// of 2731, 8 columns 36.4 and 43.3).
 struct Sides { int first, second; };
 constexpr int xcd_items(int along, Sides r) {               // of the largest rectangle
   return ((r.first + (1 << along) - 1) >> along) * ((r.second + (8 >> along) - 1) >> (3 - along));
 }
-constexpr int xcds_along(Sides a, Sides b) {
+constexpr int xcds_along(Sides a, Sides b, int at_once) {
   const long long all_a = (long long)a.first * a.second, all_b = (long long)b.first * b.second;
   int best = 3;
   long long least = xcd_items(3, a) * all_b + xcd_items(3, b) * all_a;
+  const bool one_turn = xcd_items(3, b) <= at_once;
   for (int along = 2; along >= 0; --along) {
+    if (one_turn && xcd_items(along, b) > at_once) continue;
     const long long cost = xcd_items(along, a) * all_b + xcd_items(along, b) * all_a;
     if (16 * cost < 15 * least) { best = along; least = cost; }
   }
@@ -107,14 +111,15 @@ constexpr ResidualPlan residual_plan(int wins, int tpw, int parts, int units, Si
   const int block_units = block_waves / unit_waves > 1 ? block_waves / unit_waves : 1;
   const Sides small{wins, (units + block_units - 1) / block_units}, fours{wins, (units + 3) / 4};
   if (blocks > 1 && unit_waves <= 8) {
-    const int along = xcds_along(dec, small), items = xcd_items(along, small);
-    if (items * block_waves <= 32 * 8) return {block_waves, block_units, blocks, parts > 1, true, along, items};
+    const int at_once = 32 * 8 / block_waves, along = xcds_along(dec, small, at_once), items = xcd_items(along, small);
+    if (items <= at_once) return {block_waves, block_units, blocks, parts > 1, true, along, items};
   }
-  const bool split = parts > 1 && (!bf16 || xcd_items(xcds_along(dec, fours), fours) < 64);
+  const bool split = parts > 1 && (!bf16 || xcd_items(xcds_along(dec, fours, 64), fours) < 64);
   const int abreast = split ? (parts < 4 ? 4 / parts : 1) : 4, waves = split ? abreast * parts : 4;
   const Sides all{wins, (units + abreast - 1) / abreast};
-  const int along = xcds_along(dec, all), items = xcd_items(along, all), as_four = waves < 4 ? 4 : waves;
+  const int as_four = waves < 4 ? 4 : waves;
   const int held = 32 * (residual_waves(bf16, false) / as_four), held_once = 32 * (residual_waves(bf16, true) / as_four);
+  const int along = xcds_along(dec, all, split || parts == 1 ? held_once : held), items = xcd_items(along, all);
   const bool once = (split || parts == 1) && items <= held_once;
   return {waves, abreast, 1, split, once, along, once || items < held ? items : held};
 }

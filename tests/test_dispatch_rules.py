@@ -17,7 +17,8 @@ long long residual_cost(int units, int windows) { return fc::residual_cost(units
 unsigned long long grid_start(unsigned long long at) { return fc::grid_start(at); }
 unsigned long long grid_slack() { return fc::kGridSlack; }
 int xcd_items(int along, int first, int second) { return fc::xcd_items(along, {first, second}); }
-int xcds_along(int f1, int s1, int f2, int s2) { return fc::xcds_along({f1, s1}, {f2, s2}); }
+int xcds_along(int f1, int s1, int f2, int s2) { return fc::xcds_along({f1, s1}, {f2, s2}, 0); }
+int xcds_along_at_once(int f1, int s1, int f2, int s2, int at_once) { return fc::xcds_along({f1, s1}, {f2, s2}, at_once); }
 void xcd_rectangle(int xcd, int along, int first, int second, int* out) {
   const fc::Span a = fc::xcd_first(xcd, along, first), b = fc::xcd_second(xcd, along, second);
   out[0] = a.from; out[1] = a.count; out[2] = b.from; out[3] = b.count;
@@ -168,3 +169,15 @@ def test_residual_workgroups_take_parts_side_by_side_and_are_resident(rules):
         for wins, units in ((14, 1), (43, 4), (21, 4)):
             waves, abreast, _, split, once, _, workgroups = plan(wins, 3, parts, units, (16, units * parts // 4), False)
             assert (waves, abreast, split, once) == (parts, 1, 1, 1) and workgroups <= 64
+
+
+def test_the_cut_leaves_the_residuals_items_one_turn(rules):
+    for dec, res in (((12, 21), (21, 21)), ((12, 21), (22, 21)), ((3, 30), (23, 20)), ((5, 9), (9, 47))):
+        for at_once in (16, 32, 64, 128):
+            along = rules.xcds_along_at_once(*dec, *res, at_once)
+            if rules.xcd_items(3, *res) <= at_once:
+                assert rules.xcd_items(along, *res) <= at_once
+            else:
+                assert along == rules.xcds_along(*dec, *res)
+    # 41 units of 4869 tokens: 66 workgroups an XCD by the smaller rectangles alone
+    assert [rules.xcd_items(f, 21, 21) for f in (rules.xcds_along(12, 21, 21, 21), rules.xcds_along_at_once(12, 21, 21, 21, 64))] == [66, 63]
