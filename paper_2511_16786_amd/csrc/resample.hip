@@ -1678,21 +1678,6 @@ static hipError_t launch_decimate_gt(const T* K, const T* V, KvStrides st, int u
   return hipGetLastError();
 }
 
-// Tiles per wave: four while two workgroups' weights fit a compute unit's 160 KB of LDS (10 steps, N/M up to 11; two
-// tiles there: 519 instead of 473 us at 32768 tokens, M = 3072) and the launch still has a workgroup for each of them, else two while
-// it has nearly that many, or one: the rows under seams are read again, which costs more than compute units that have one workgroup and
-// not two.  fp32 rows, whose waves have twice the products, want half as many more.  Scoring, us, by workgroups of four, two and one tiles a
-// wave (the rule's choice marked): 192, 384, 768: 16 units of 8192 tokens 60.6, *59.3, 63.2, 8 of 32768 88.3, *87.6, 93.8; 240, 480, 960: 40 of
-// 4096 69.4, *70.0, 76.8; 288, 576, 1152: 48 of 4096 *86.1, 89.3, 93.8, fp32 12 of 8192 73.0, *69.1, 73.8; 396, 792, 1584: 132 of 1280 *78.7,
-// 86.7, 88.6; 480, 960, 1920: 80 of 4096 *117.3, 124.7, 136.4; 112, 224, 448: 112 of 700 46.2, *42.4, 47.0; 96, 192, 384: 16 of 4096
-// 48.8, 42.6, *41.0, 4 of 16384 50.5, 44.2, *42.7.
-static int decimate_tiles(int m, int groups, int steps, bool bf16) {
-  auto fits = [&](int gt, int least) {
-    return gt * steps * 2048 <= 80 * 1024 && (int64_t)(m / 16 / gt) * groups >= least;
-  };
-  return fits(4, bf16 ? 256 : 384) ? 4 : (fits(2, bf16 ? 224 : 384) ? 2 : 1);
-}
-
 template <typename T, bool KEEP>
 static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, int32_t r, const ResampleLayout& lay,
                                    float* scores, double* energy, void* ws, UnitMap um, hipStream_t s) {
@@ -1709,7 +1694,8 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
   // and the rows neighbouring tiles share
   for (int u0 = 0; u0 < units; u0 += lay.chunk) {
     const int u1 = std::min(units, u0 + lay.chunk);
-    const int groups = ((u1 - u0) * sm.wpu + kDecWaves - 1) / kDecWaves, gt = decimate_tiles(m, groups, lay.steps, sizeof(T) == 2);
+    const int groups = ((u1 - u0) * sm.wpu + kDecWaves - 1) / kDecWaves;
+    const int gt = decimate_tiles(m, groups, lay.steps, sizeof(T) == 2, 2 * lay.nb, (long long)(u1 - u0) * 2 * n * d.head_dim * (int)sizeof(T));
     const Sides dec{(m / 16 + gt - 1) / gt, groups};
     const ResidualPlan res = residual_plan(lay.wins, lay.tpw, lay.wpu, u1 - u0, dec, sizeof(T) == 2);
     const float* wfwd = reinterpret_cast<const float*>(base + lay.wfwd);

@@ -31,6 +31,9 @@ void residual_plan(int wins, int tpw, int parts, int units, int f, int sec, bool
   out[0] = p.waves; out[1] = p.abreast; out[2] = p.blocks; out[3] = p.split; out[4] = p.once; out[5] = p.along; out[6] = p.workgroups;
 }
 int residual_waves(bool bf16, bool once) { return fc::residual_waves(bf16, once); }
+int decimate_tiles(int m, int groups, int steps, bool bf16, int slots, long long row_bytes) {
+  return fc::decimate_tiles(m, groups, steps, bf16, slots, row_bytes);
+}
 bool keeps_rows(long long rows, int row_bytes) { return fc::keeps_rows(rows, row_bytes); }
 bool ranks_by_budget(long long rows, int layers, int splits, int row_bytes) { return fc::ranks_by_budget(rows, layers, splits, row_bytes); }
 }
@@ -181,3 +184,24 @@ def test_the_cut_leaves_the_residuals_items_one_turn(rules):
                 assert along == rules.xcds_along(*dec, *res)
     # 41 units of 4869 tokens: 66 workgroups an XCD by the smaller rectangles alone
     assert [rules.xcd_items(f, 21, 21) for f in (rules.xcds_along(12, 21, 21, 21), rules.xcds_along_at_once(12, 21, 21, 21, 64))] == [66, 63]
+
+
+def test_decimation_walks_more_tiles_where_the_rows_are_what_it_waits_for(rules):
+    rules.decimate_tiles.argtypes = [ctypes.c_int] * 3 + [ctypes.c_bool, ctypes.c_int, ctypes.c_longlong]
+
+    def tiles(units, n, m, steps, columns, bf16):
+        slots = 2 * columns * (2 if bf16 else 4) // 16
+        groups = -(-units * rules.slot_waves(slots) // 4)
+        return rules.decimate_tiles(m, groups, steps, bf16, slots, units * 2 * n * columns * (2 if bf16 else 4))
+    # large launches, and a chip with few workgroups
+    assert tiles(112, 32768, 3072, 10, 128, True) == 4 and tiles(112, 8192, 1536, 6, 128, False) == 4
+    assert tiles(1, 512, 96, 6, 64, False) == 1 and tiles(16, 4096, 768, 6, 128, True) == 1
+    # weights of four tiles that do not fit the LDS twice
+    assert tiles(112, 32768, 2048, 14, 128, True) == 2
+    # middle sizes: rows that take longer than a walk ...
+    assert tiles(40, 4096, 768, 6, 128, True) == 2 and tiles(48, 4096, 768, 6, 128, True) == 4
+    assert tiles(132, 1280, 256, 5, 128, True) == 4 and tiles(16, 8192, 1536, 6, 128, True) == 2
+    # ... and few bytes: 5 to 20 units of 8 to 32 columns, with 256 to 384 workgroups of the longer walk
+    for units, n, m, steps, columns in ((14, 31488, 2048, 13, 16), (15, 30976, 2048, 13, 8), (5, 48896, 4096, 11, 32), (54, 7348, 512, 13, 16),
+                                        (111, 3901, 256, 13, 24), (13, 13729, 2048, 7, 8)):
+        assert tiles(units, n, m, steps, columns, True) == 1
