@@ -1198,8 +1198,8 @@ __device__ __forceinline__ int side_div(int wave, int factor) { return wave * fa
 
 // One wave applies windows (32 grid points each) to the 16-token tiles they cover, 16 slots at a time.  Its work
 // is a list of segments: a window, a unit (four units at a time, one for each wave of a workgroup), a part of the
-// unit's slots; with few segments, and for fp32 always (split), a workgroup's waves take the parts of a unit side by side
-// instead of one after the other.  Rows are requested two tiles ahead and grid values one window ahead, across segments.
+// unit's slots; or (split) a workgroup's waves take the parts of a unit side by side instead of one
+// after the other.  Rows are requested two tiles ahead and grid values one window ahead, across segments.
 // Neighbouring windows read the same lines of the grid: an XCD takes a contiguous range of windows and its
 // workgroups walk (units, window) side by side, window fastest, so that its L2 serves what they share.  Launches with no
 // more than one segment for a wave (ONCE) ask for nothing ahead of a next one (one layer of 16384 tokens: 19.7 / 19.1 us).
@@ -1218,7 +1218,7 @@ __device__ __forceinline__ int side_div(int wave, int factor) { return wave * fa
 // tensor's slots take one pair of sums over the wave, items follow one another without a division and loads have scalar bases.
 // Residual of 112 units, us: M = 12288 681 / 654, 16384 tokens, M = 12288 715 / 680, 30011 tokens 505 / 490, M = 3072 449 / 443.
 template <typename T, bool KEEP, bool ONCE, bool BLOCKS, int BUF, int WAVES>
-__global__ __launch_bounds__(64 * WAVES, residual_waves(sizeof(T) == 2, ONCE) / 4) void residual_kernel(
+__global__ __launch_bounds__(64 * WAVES, sizeof(T) == 2 ? 2 : (ONCE ? 4 : 3)) void residual_kernel(
     const T* __restrict__ K, const T* __restrict__ V, KvStrides st, int u0, int u1, int n, int r, int d, int dtype,
     int m, int tpw, int wins, SlotMap sm, bool split, int blocks, SideBySide side, int along, WsHeader* hdr, const _Float16* __restrict__ winv,
     const float2* __restrict__ grid, float* __restrict__ scores,

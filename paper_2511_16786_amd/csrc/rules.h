@@ -112,20 +112,20 @@ constexpr int decimate_tiles(int m, int groups, int steps, bool bf16, int slots,
 constexpr int window_blocks(int tpw) { return tpw > 8 ? 4 : (tpw > 4 ? 2 : 1); }
 constexpr int window_block(int tpw) { return (tpw + window_blocks(tpw) - 1) / window_blocks(tpw); }
 
-// Waves of the residual kernel that a compute unit holds: of bf16 rows eight; a wave of fp32 rows has half the columns and so half the
-// registers, and twelve of them are under way, 16 in launches of one segment for each (ONCE).
-constexpr int residual_waves(bool bf16, bool once) { return bf16 ? 8 : (once ? 16 : 12); }
+// Waves of the residual kernel for a compute unit.  bf16 rows: eight, what it holds.  A wave of fp32 rows has half the columns and so half the
+// registers: 16 are under way in launches of one segment for each (ONCE); others have nine, in whole workgroups, though it holds twelve.  Scoring, us, by
+// workgroups of an XCD: of three waves, 64 and 96, 150 units of 9000 tokens, 72 columns 493 / 473; of four, 32, 64 and 96, 112 of 8192 555 / 507 /
+// 513, 300 of 8192, 64 columns 727 / 672 / 679, 400 of 8192, 32 columns 496 / 465 / 473 (80 and 112, which compute units share
+// unevenly, 5 % more); of five, 32, 64 and 96, 80 of 8192, 136 columns 467 / 469 / 474; of six, 50 of 8192, 192 columns 366 / 367 / 370.
+constexpr int residual_waves(bool bf16, bool once) { return bf16 ? 8 : (once ? 16 : 9); }
 
 // Work of a residual launch: windows (wins, of tpw tiles) along one side, units abreast in a workgroup along the other; a unit has as many parts
-// as slot_waves.  Workgroups of four waves take a unit each, or (split) a unit's parts side by side; of five to eight where a unit has
-// that many.
-//   bf16: split where workgroups of four units leave an XCD's compute units without two each.  Else the waves take the parts in turn, which
-//   needs no barriers.
-//   fp32: always split, as many workgroups as are resident.  Scoring, us, pieces of 32 bytes / parts in turn, two workgroups a compute unit / split,
-//   two / split, three: 112 units of 8192 tokens 572 / 526 / 510 / 514, 154 of 12032, 72 columns 643 / 587 / 580 / 558, 36 of 16384, 64 columns 170 / 188 / 165 / 162,
-//   3 of 48283 85 / 91 / 85 / 85, one of 55808 80 / 85 / 63 / 63, 50 of 9000, 256 columns 546 / - / 490 / 485; 80 and 112 workgroups an XCD, which compute units share
-//   unevenly, 534 and 539 where 96 take 514.  More than four parts, in turn / split: one of 512, 256 columns 56 / 23, 4 of 2048,
-//   136 columns 60 / 25, 16 of 4096, 256 columns 94 / 81 (pieces of 32 bytes 28, 32, 89).
+// as slot_waves.  Workgroups of four waves take a unit each and its parts in turn, or (split) a unit's parts side by side, of five to
+// eight waves where a unit has that many.
+// Split is what leaves an XCD's compute units two workgroups each where four units for one do not.  fp32 rows are split in others too, in
+// turn / side by side: 112 units of 8192 tokens 526 / 510 us, 154 of 12032, 72 columns 587 / 562, 50 of 9000, 256 columns 533 / 486, 36 of 16384,
+// 64 columns 184 / 171, one of 55808 85 / 62 (three of four waves had no unit).  Not so where a window is a single tile, for each of which
+// the waves would wait for one another: 50 of 8192, r = 3400 507 / 514, of 192 columns 760 / 847, 275 of 507, r = 163 164 / 178.
 // In launches that leave room for it each block of a window's tiles, of each part, has a wave of its own: all of them resident at
 // once (eight waves a compute unit), as workgroups of four to eight.  Scoring, us, a wave for a window / for a block: 8 units of 1381 tokens,
 // 64 columns (13 tiles) 30.4 / 23.1, 16 of 3697 38.7 / 28.4, 20 of 2304 38.5 / 33.3, 8 of 1024 27.3 / 24.8, 2 of 512 in fp32
@@ -140,14 +140,14 @@ constexpr ResidualPlan residual_plan(int wins, int tpw, int parts, int units, Si
   const int block_units = block_waves / unit_waves > 1 ? block_waves / unit_waves : 1;
   const Sides small{wins, (units + block_units - 1) / block_units}, fours{wins, (units + 3) / 4};
   if (blocks > 1 && unit_waves <= 8) {
-    const int at_once = 32 * 8 / block_waves, along = xcds_along(dec, small, at_once), items = xcd_items(along, small);
+    const int at_once = 32 * (8 / block_waves), along = xcds_along(dec, small, at_once), items = xcd_items(along, small);
     if (items <= at_once) return {block_waves, block_units, blocks, parts > 1, true, along, items};
   }
-  const bool split = parts > 1 && (!bf16 || xcd_items(xcds_along(dec, fours, 64), fours) < 64);
+  const bool many = xcd_items(xcds_along(dec, fours, 64), fours) >= 64, idle = 16 * fours.second > 5 * units;    // (a fifth of the waves)
+  const bool split = parts > 1 && !(many && (bf16 || (tpw == 1 && !idle)));
   const int abreast = split ? (parts < 4 ? 4 / parts : 1) : 4, waves = split ? abreast * parts : 4;
   const Sides all{wins, (units + abreast - 1) / abreast};
-  const int as_four = waves < 4 ? 4 : waves;
-  const int held = 32 * (residual_waves(bf16, false) / as_four), held_once = 32 * (residual_waves(bf16, true) / as_four);
+  const int held = 32 * (residual_waves(bf16, false) / waves), held_once = 32 * (residual_waves(bf16, true) / (waves < 4 ? 4 : waves));
   const int along = xcds_along(dec, all, split || parts == 1 ? held_once : held), items = xcd_items(along, all);
   const bool once = (split || parts == 1) && items <= held_once;
   return {waves, abreast, 1, split, once, along, once || items < held ? items : held};

@@ -161,10 +161,12 @@ def test_residual_workgroups_take_parts_side_by_side_and_are_resident(rules):
                         waves, abreast, blocks, split, once, along, workgroups = plan(wins, tpw, parts, units, dec, bf16)
                         of_unit = (parts if split else 1) * blocks
                         assert 1 <= waves <= 8 and abreast == waves // of_unit and waves == abreast * of_unit
-                        assert split == (parts > 1) or (bf16 and blocks == 1)
+                        assert split == (parts > 1) or (blocks == 1 and (bf16 or (tpw == 1 and units not in (1, 2, 3))))
                         items = rules.xcd_items(along, wins, -(-units // abreast))
-                        held = 32 * (rules.residual_waves(bf16, once) // max(4, waves))
-                        assert workgroups == (items if once else min(items, held)) and workgroups <= max(held, 32 * 8 // waves)
+                        held = 32 * (rules.residual_waves(bf16, once) // (max(4, waves) if once else waves))
+                        if blocks > 1:
+                            held = 32 * (8 // waves)                # (whole workgroups of a compute unit's eight waves)
+                        assert workgroups == (items if once else min(items, held)) and workgroups <= held
                         held_once = 32 * (rules.residual_waves(bf16, True) // max(4, waves))
                         assert blocks > 1 or once == ((split or parts == 1) and items <= held_once)
     # one layer of a head of 256 fp32 columns and the like: a wave for every part, one turn
