@@ -82,15 +82,15 @@ constexpr int lane_slot(int part, int lane, int slots) { return part * 16 + lane
 // Tiles of the grid for a decimation wave: four, two or one.  Fewer of them read the rows under the seams again (1.75 times the rows with one);
 // more make a wave's walk through the tokens longer, by half for two tiles where the tokens are many for a grid point, and workgroups
 // fewer.  So it depends on what a launch waits for: its rows, or the longest walk, which weighs the less the more workgroups there
-// are beside one another: 54 MB with 224 workgroups, 32 with 384 (fp32 86 with 256, 57 with 384).  Waves with empty lanes walk as long for fewer
+// are beside one another: 75 MB with 160 workgroups, 32 with 384 (fp32 86 with 256, 57 with 384).  Waves with empty lanes walk as long for fewer
 // bytes, which count the less; sequences of less than 16 groups of tiles have most of their rows under seams.
 // Workgroups' weights are to fit a compute unit's 160 KB of LDS twice (10 steps for four tiles, N/M up to 11; two tiles there:
 // 519 instead of 473 us at 32768 tokens, M = 3072).
 // Decimation alone, us, more tiles less fewer, mean of launches drawn at random (and the extremes), by workgroups of the more:
 //   bf16, four or two: rows below 55 MB, 224 to 255 +2.2 (+0.3 .. 7.8), 256 to 383 +0.5 (-2.6 .. 5.2), 384 to 511 -1.6 (-4.5 .. 0.3); above, 224
 //   to 255 0.0 (-2.0 .. 2.6), 256 to 383 -3.8 (-10.2 .. -0.1), 384 to 511 -4.8 (-8.4 .. -2.1).
-//   bf16, two or one: below, 256 to 383 +1.1 (-0.2 .. 4.2), 384 to 511 0.0 (-4.1 .. 3.3); above, 224 to 255 -2.2 (-3.9 .. -1.2), 256 to 383
-//   -2.7 (-5.5 .. 2.5), 384 to 511 -7.3 (-13.8 .. -3.2).
+//   bf16, two or one: below, 256 to 383 +1.1 (-0.2 .. 4.2), 384 to 511 0.0 (-4.1 .. 3.3); above, 128 to 159 +0.1 (-1.7 .. 3.1), 160 to 223 -1.3
+//   (-4.1 .. 1.4), 224 to 255 -2.2 (-3.9 .. -1.2), 256 to 383 -2.7 (-5.5 .. 2.5), 384 to 511 -7.3 (-13.8 .. -3.2).
 //   fp32, four or two: below, 384 to 511 +1.2 (-2.0 .. 3.4), 512 on +1.9 (-1.0 .. 6.2); above, 256 to 383 +4.5 (-0.5 .. 9.5), 384 to 511 -3.7 (-9.2
 //   .. 2.1), 112 units of 8192 tokens 230 / 270.  Two or one: below, 256 to 511 +1.0 (-3.4 .. 3.6), 640 on -0.5 (-2.0 .. 1.2); above, 256 to 383
 //   -1.3 (-4.4 .. 2.9), 384 to 511 -6.1 (-13.9 .. 1.8).
@@ -102,7 +102,7 @@ constexpr int decimate_tiles(int m, int groups, int steps, bool bf16, int slots,
     const long long workgroups = (long long)supers * groups;
     const bool rows_bound = carried * workgroups >= (bf16 ? 12000000000 : 22000000000) || (slots == lanes && supers < 16 && row_bytes >= 20000000);
     const int least = gt == 4 ? (bf16 ? (rows_bound ? 256 : 384) : (rows_bound ? 384 : 1 << 30))
-                              : (bf16 ? (rows_bound ? 224 : 512) : (rows_bound ? 256 : 640));
+                              : (bf16 ? (rows_bound ? 160 : 512) : (rows_bound ? 256 : 640));
     if (gt * steps * 2048 <= 80 * 1024 && workgroups >= least) return gt;
   }
   return 1;

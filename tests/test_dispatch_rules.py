@@ -202,6 +202,7 @@ def test_decimation_walks_more_tiles_where_the_rows_are_what_it_waits_for(rules)
     assert tiles(112, 32768, 2048, 14, 128, True) == 2
     # middle sizes: rows that take longer than a walk ...
     assert tiles(40, 4096, 768, 6, 128, True) == 2 and tiles(48, 4096, 768, 6, 128, True) == 4
+    assert tiles(60, 1055, 128, 7, 192, True) == 2 and tiles(90, 700, 128, 4, 128, True) == 2
     assert tiles(132, 1280, 256, 5, 128, True) == 4 and tiles(16, 8192, 1536, 6, 128, True) == 2
     # ... and few bytes: 5 to 20 units of 8 to 32 columns, with 256 to 384 workgroups of the longer walk
     for units, n, m, steps, columns in ((14, 31488, 2048, 13, 16), (15, 30976, 2048, 13, 8), (5, 48896, 4096, 11, 32), (54, 7348, 512, 13, 16),
