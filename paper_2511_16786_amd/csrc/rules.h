@@ -161,6 +161,25 @@ constexpr ResidualPlan residual_plan(int wins, int tpw, int parts, int units, Si
 // 314, but 32 504 / 477, 96 370 / 358, 160 395 / 383, 224 430 / 415; bf16: 8 columns 658 / 677, 24 448 / 481, 72 634 / 689, 136 571 / 604.
 constexpr bool round_keeps_rows(long long round_bytes, int row_bytes) { return row_bytes % 128 != 0 || round_bytes <= 256 * 1000 * 1000; }
 
+// Workgroups of a selection that copies the rows as well, 0: the copying is a launch of its own.  Those with an index set in common all make
+// the selection, so that there must be compute units to spare, and their own share of rows has to be short, since a workgroup copies it
+// alone, a 16-byte vector of K and of V a thread and turn: four turns at most, two and a half where each first looks a page up, and
+// 112 KB read and written.  The heads' scores of a shared set are read by each of its workgroups, 40 MB of them at most.
+// Two launches / one, us, with the bytes that a workgroup copies: 2 sets of 512 tokens (6 KB) 8.3 / 5.8, 16 of 4096 (52) 10.2 /
+// 8.5, 16 of 1280 (28) 8.7 / 6.5, 64 of 2048 (52) 9.6 / 7.8, 4 of 16384 (105) 11.6 / 11.0, 32 of 8192 (105) 13.2 / 12.4; 4 of 4096, heads'
+// rows alike (209) 10.8 / 13.1, 8 of 16384 (315) 17.3 / 19.3; 128 of 512 (92) 11.3 / 12.3.  One less two, launches drawn at random, up to 112 KB,
+// mean and extremes by turns: packed, 2 to 3 -1.0 (-1.6 .. -0.2), 3 to 4 -0.8 (-2.1 .. -0.1), 4 to 5 -0.3 (-0.7 .. 0.3), 5 to 7 +0.4 (-0.5 .. 0.8);
+// paged, 1.5 to 2 -1.2 (-3.0 .. 0.1), 2 to 2.5 -0.7 (-1.2 .. -0.1), 2.5 to 3 -0.2 (-1.9 .. 0.8), 3 to 5 +0.5 (-1.2 .. 1.5), 5 to 7 +2.6 (1.3 .. 3.9);
+// by the scores read: 20 to 30 MB -1.1 (-1.9 .. -0.5), 30 to 40 -0.6 (-1.6 .. 0.1), 40 to 50 +0.2 (-1.0 .. 2.2), more +1.7 (0.2 .. 4.0).
+constexpr int select_threads(int n) { return n <= 1024 ? 256 : (n <= 4096 ? 512 : 1024); }    // (of its workgroups, up to 32768 tokens)
+constexpr int copy_groups(int lists, int layers, int n, int heads, long long rows, int vec_per_row, bool paged) {
+  if (n > 16384 || lists > 64) return 0;
+  const int of_list = 256 / lists < 16 ? 256 / lists : 16, groups = lists * of_list, sharing = layers == 1 ? groups : groups - lists;
+  const long long vectors = rows * vec_per_row, a_turn = (long long)sharing * select_threads(n);
+  if (64 * vectors > (long long)sharing * (112 << 10) || 2 * vectors > (paged ? 5 : 8) * a_turn) return 0;
+  return heads > 1 && 4LL * groups * heads * n > 40000000 ? 0 : groups;
+}
+
 // Where the grid begins in its region of a workspace, both at multiples of 256 bytes: an odd multiple, whatever the
 // workspace's own address is.  A grid at a multiple of 512 costs the residual kernel a tenth where M is a power of two (28 layers of
 // 4096 tokens, M = 4096: 182 us at 128, 256, 768, 1280 and 2304 bytes past a multiple of 4096, 204 at 0 and 512).

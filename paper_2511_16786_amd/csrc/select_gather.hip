@@ -11,6 +11,7 @@
 #include <algorithm>
 
 #include "fc_common.h"
+#include "rules.h"
 
 namespace fc {
 
@@ -500,17 +501,6 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(
 
 }  // namespace
 
-// Workgroups of a selection that copies the rows as well, 0: the copying is a launch of its own.  Those with an index set in common all make
-// the selection, so that there must be compute units to spare, and their own share of rows has to be short, since a workgroup copies it
-// alone.  Two launches / one, us, with the bytes that a workgroup copies: 2 sets of 512 tokens (6 KB) 8.3 / 5.8, 16 of 4096 (52) 10.2 /
-// 8.5, 16 of 1280 (28) 8.7 / 6.5, 64 of 2048 (52) 9.6 / 7.8, 4 of 16384 (105) 11.6 / 11.0, 32 of 8192 (105) 13.2 / 12.4; 4 of 4096, heads'
-// rows alike (209) 10.8 / 13.1, 8 of 16384 (315) 17.3 / 19.3; 128 of 512 (92) 11.3 / 12.3.
-static int copy_groups(int lists, int layers, int n, long long rows, int row_bytes) {
-  if (n > 16384 || lists > 64) return 0;
-  const int groups = lists * std::min(16, 256 / lists), sharing = layers == 1 ? groups : groups - lists;
-  return 4 * rows * row_bytes <= (long long)sharing * (112 << 10) ? groups : 0;
-}
-
 hipError_t select_gather_launch(const void* K, const void* V, const fc_kv_desc& d, const float* scores,
                                 const int32_t* budgets, const int64_t* layer_offsets,
                                 int64_t rows_per_seq, bool shared, int32_t* idx_out, void* K_out,
@@ -526,7 +516,8 @@ hipError_t select_gather_launch(const void* K, const void* V, const fc_kv_desc& 
     for (vpr_shift = 0; (1 << vpr_shift) < vec_per_row; ++vpr_shift) {}
   const PagedDst pg{block_table, page_size, max_pages, (long long)num_pages};
   const int lists = shared ? units / d.kv_heads : units;           // index sets to be found
-  const int groups = copy_groups(lists, d.layers, d.n_tokens, (long long)rows_per_seq * d.batch, vec_per_row * 16);
+  const int groups = copy_groups(lists, d.layers, d.n_tokens, shared ? d.kv_heads : 1, (long long)rows_per_seq * d.batch, vec_per_row,
+                                 block_table != nullptr);
   {
     ProfileScope ps(shared ? "select_shared_kernel" : "select_kernel", s);
     const dim3 grid(groups ? groups : lists);
@@ -547,6 +538,7 @@ hipError_t select_gather_launch(const void* K, const void* V, const fc_kv_desc& 
     // 4096 tokens, 512 threads of 8 9.4 / 15.6, 1024 of 4 8.9 / 19.8; 8192 tokens, 1024 of 8 11.4 / 26.6, 512 of 16
     // 12.1 / 25.9; 16384 tokens, 1024 of 16 15.3 / 52.6, 512 of 32 19.2 / 48.7.
 #define FC_SELECT_N(SH)                                                                                        \
+  static_assert(select_threads(1024) == 256 && select_threads(4096) == 512 && select_threads(4097) == 1024);                    \
   if (n <= 1024) { FC_SELECT_COPY(SH, 256, 4); }                                                               \
   else if (n <= 2048) { FC_SELECT_COPY(SH, 512, 4); }                                                          \
   else if (n <= 4096) { FC_SELECT_COPY(SH, 512, 8); }                                                          \

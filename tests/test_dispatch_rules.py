@@ -34,6 +34,9 @@ int residual_waves(bool bf16, bool once) { return fc::residual_waves(bf16, once)
 int decimate_tiles(int m, int groups, int steps, bool bf16, int slots, long long row_bytes) {
   return fc::decimate_tiles(m, groups, steps, bf16, slots, row_bytes);
 }
+int copy_groups(int lists, int layers, int n, int heads, long long rows, int vec_per_row, bool paged) {
+  return fc::copy_groups(lists, layers, n, heads, rows, vec_per_row, paged);
+}
 bool keeps_rows(long long rows, int row_bytes) { return fc::keeps_rows(rows, row_bytes); }
 bool ranks_by_budget(long long rows, int layers, int splits, int row_bytes) { return fc::ranks_by_budget(rows, layers, splits, row_bytes); }
 }
@@ -208,3 +211,24 @@ def test_decimation_walks_more_tiles_where_the_rows_are_what_it_waits_for(rules)
     for units, n, m, steps, columns in ((14, 31488, 2048, 13, 16), (15, 30976, 2048, 13, 8), (5, 48896, 4096, 11, 32), (54, 7348, 512, 13, 16),
                                         (111, 3901, 256, 13, 24), (13, 13729, 2048, 7, 8)):
         assert tiles(units, n, m, steps, columns, True) == 1
+
+
+def test_selections_copy_rows_where_a_workgroups_share_is_short(rules):
+    rules.copy_groups.argtypes = [ctypes.c_int] * 4 + [ctypes.c_longlong, ctypes.c_int, ctypes.c_bool]
+
+    def groups(B, L, H, n, d, rho, element, shared, paged):
+        return rules.copy_groups(B * L if shared else B * L * H, L, n, H if shared else 1, B * H * int(rho * L * n), d * element // 16, paged)
+    # one launch: a layer of a short prompt, four layers of 4096 tokens, sixteen sets of 1280, few heads alike
+    assert groups(1, 1, 2, 512, 64, 0.2, 4, False, False) == 32 and groups(1, 4, 4, 4096, 128, 0.2, 2, False, False) == 256
+    assert groups(1, 4, 4, 1280, 128, 0.2, 2, False, True) == 256 and groups(1, 6, 2, 2048, 64, 0.1, 2, True, True) == 96
+    # two: many sets, long sequences, long shares
+    assert groups(1, 28, 4, 8192, 128, 0.2, 2, False, False) == groups(1, 1, 4, 32768, 128, 0.2, 2, False, False) == 0
+    assert groups(1, 2, 4, 16384, 128, 0.2, 2, False, False) == 0
+    # ... shares of more than two and a half turns of a workgroup's threads through tables, or four
+    for case in ((1, 9, 4, 567, 256, 0.328, 2, True), (3, 5, 8, 748, 128, 0.243, 2, True), (3, 2, 2, 577, 256, 0.311, 4, True),
+                 (1, 6, 2, 849, 256, 0.328, 4, False), (1, 2, 8, 2162, 128, 0.043, 4, True)):
+        assert groups(*case, True) == 0, case
+    assert groups(1, 12, 4, 945, 128, 0.397, 2, False, False) == 0
+    # ... and sets whose heads' scores each of their workgroups would read
+    for case in ((2, 18, 8, 8907, 8, 0.027, 4, True, False), (1, 24, 4, 13488, 8, 0.292, 2, True, False), (2, 28, 4, 13639, 8, 0.026, 2, True, True)):
+        assert groups(*case) == 0, case
