@@ -1043,8 +1043,7 @@ __global__ __launch_bounds__(SpreadPlan<M>::NT) void grid_spread_kernel(
     const bool mine = B >= NT || tid < B;
     // (addresses are a part of the thread's own and a constant: B q, and q NS or q of a group of NS R, are made of whole groups of
     // 2^kPadShift, or do not leave one)
-    static_assert(B % (1 << G::kPadShift) == 0 && (NS == 1 ? R <= (1 << G::kPadShift) || R % (1 << G::kPadShift) == 0
-                                                           : NS % (1 << G::kPadShift) == 0), "padding of a pass");
+    static_assert(B % (1 << G::kPadShift) == 0 && pads_apart(R, NS, 1 << G::kPadShift), "padding of a pass");
     C v[R];
     if (mine)
 #pragma unroll

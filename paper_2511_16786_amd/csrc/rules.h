@@ -180,6 +180,13 @@ constexpr int copy_groups(int lists, int layers, int n, int heads, long long row
   return heads > 1 && 4LL * groups * heads * n > 40000000 ? 0 : groups;
 }
 
+// The grid transforms' LDS has a free place after each `group` of points, point i is at i + i / group.  Whether the points of a butterfly, t R + q after the
+// first pass (done = 1) and t / done * done R + t % done + q done after others, are at the place of the first and that of q, or q done, alone:
+// their sum must not reach into a group's next one.
+constexpr bool pads_apart(int radix, int done, int group) {
+  return done == 1 ? group % radix == 0 || radix % group == 0 : done % group == 0;
+}
+
 // Where the grid begins in its region of a workspace, both at multiples of 256 bytes: an odd multiple, whatever the
 // workspace's own address is.  A grid at a multiple of 512 costs the residual kernel a tenth where M is a power of two (28 layers of
 // 4096 tokens, M = 4096: 182 us at 128, 256, 768, 1280 and 2304 bytes past a multiple of 4096, 204 at 0 and 512).

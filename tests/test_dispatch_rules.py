@@ -37,6 +37,7 @@ int decimate_tiles(int m, int groups, int steps, bool bf16, int slots, long long
 int copy_groups(int lists, int layers, int n, int heads, long long rows, int vec_per_row, bool paged) {
   return fc::copy_groups(lists, layers, n, heads, rows, vec_per_row, paged);
 }
+bool pads_apart(int radix, int done, int group) { return fc::pads_apart(radix, done, group); }
 bool keeps_rows(long long rows, int row_bytes) { return fc::keeps_rows(rows, row_bytes); }
 bool ranks_by_budget(long long rows, int layers, int splits, int row_bytes) { return fc::ranks_by_budget(rows, layers, splits, row_bytes); }
 }
@@ -232,3 +233,18 @@ def test_selections_copy_rows_where_a_workgroups_share_is_short(rules):
     # ... and sets whose heads' scores each of their workgroups would read
     for case in ((2, 18, 8, 8907, 8, 0.027, 4, True, False), (1, 24, 4, 13488, 8, 0.292, 2, True, False), (2, 28, 4, 13639, 8, 0.026, 2, True, True)):
         assert groups(*case) == 0, case
+
+
+def test_places_of_a_butterfly_are_sums_where_the_transforms_say_so(rules):
+    rules.pads_apart.restype = ctypes.c_bool
+    for group in (2, 4, 8, 16, 32):
+        def place(i):
+            return i + i // group
+        for radix in (2, 3, 4, 6, 8, 12, 16, 24, 32, 48):
+            for done in (1, 8, 16, 32, 64):
+                firsts = [t // done * done * radix + t % done for t in range(4 * max(group, done))]
+                holds = all(place(f + q * done) == place(f) + place(q * done) for f in firsts for q in range(radix))
+                assert holds or not rules.pads_apart(radix, done, group), (radix, done, group)
+                if done == 1:
+                    assert holds == rules.pads_apart(radix, done, group), (radix, group)
+    assert not rules.pads_apart(6, 1, 8) and not rules.pads_apart(12, 1, 16) and rules.pads_apart(16, 1, 16) and rules.pads_apart(32, 1, 16)
