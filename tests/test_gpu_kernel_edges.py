@@ -853,3 +853,107 @@ def test_decode_of_single_pieces_is_the_merged_one(dtype, d, group):
                 p = torch.softmax(Q[b, l, h * group:(h + 1) * group].double() @ rows[0].T * d ** -0.5, -1)
                 want = p @ rows[1]
                 assert float((out[0][b, l, h * group:(h + 1) * group] - want).abs().max()) <= 5e-5 * float(rows[1].abs().max())
+
+
+def _softmax64(Q, rows_k, rows_v, scale):
+    return torch.softmax(Q.double() @ rows_k.double().T.contiguous() * scale, -1) @ rows_v.double()
+
+
+# Single pieces of caches larger than the last-level cache: more than 1024 units, layers that keep nothing, little and much, packed and
+# through tables whose pool is as large
+@pytest.mark.parametrize("dtype,d,group", [("bf16", 128, 7), ("f32", 64, 4)])
+def test_decode_of_single_pieces_of_large_caches(dtype, d, group):
+    import paper_2511_16786_amd as fc
+    B, L, H, page = 8, 36, 4, 64
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    rng = np.random.default_rng(d)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    of_layers = np.concatenate(([0, 1, 63, 64, 2500], rng.integers(300, 620, L - 5)))
+    budgets = np.stack([rng.permutation(of_layers) for _ in range(B)])
+    offs = np.stack([ref.layer_offsets(x, H) for x in budgets])
+    rows = int(offs[0, -1])
+    assert 2 * B * rows * d * (4 if dtype == "f32" else 2) > 256e6 and B * L * H > 1024
+    Q = torch.randn((B, L, H * group, d), generator=gen, device="cuda").to(dt)
+    K, V = (torch.randn((B, rows, d), generator=gen, device="cuda").to(dt) for _ in range(2))
+    b_t, o_t = torch.from_numpy(budgets.astype(np.int32)).cuda(), torch.from_numpy(offs).cuda()
+    packed = fc.decode_attention(Q, K, V, H, b_t, o_t, rows, d ** -0.5)
+    # the same rows in pages of a shuffled pool, which holds what the budgets take
+    pages = -(-budgets // page)
+    table = np.full((B, L, H, int(pages.max())), -1, dtype=np.int32)
+    order, at = rng.permutation(int(pages.sum()) * H).astype(np.int32), 0
+    Kp, Vp = (torch.zeros((len(order), page, d), dtype=dt, device="cuda") for _ in range(2))
+    for b in range(B):
+        for l in range(L):
+            for h in range(H):
+                k, n = int(budgets[b, l]), int(pages[b, l])
+                table[b, l, h, :n] = order[at:at + n]
+                at += n
+                where = torch.from_numpy(table[b, l, h, :n].astype(np.int64)).cuda()
+                first = int(offs[b, l]) + h * k
+                for src, dst in ((K, Kp), (V, Vp)):
+                    x = torch.zeros((n * page, d), dtype=dt, device="cuda")
+                    x[:k] = src[b, first:first + k]
+                    dst[where] = x.view(n, page, d)
+    paged = fc.decode_attention_paged(Q, Kp, Vp, H, b_t, torch.from_numpy(table).cuda(), d ** -0.5)
+    assert bool(torch.isfinite(packed).all()) and bool(torch.isfinite(paged).all())
+    for b in (0, 3, B - 1):
+        for l in range(L):
+            k = int(budgets[b, l])
+            for h in range(H):
+                q = Q[b, l, h * group:(h + 1) * group]
+                got = [x[b, l, h * group:(h + 1) * group] for x in (packed, paged)]
+                if k == 0:
+                    assert all(bool((x == 0).all()) for x in got)
+                    continue
+                first = int(offs[b, l]) + h * k
+                want = _softmax64(q, K[b, first:first + k], V[b, first:first + k], d ** -0.5)
+                for x in got:
+                    assert float((x - want).abs().max()) <= 5e-5 * float(V[b, first:first + k].abs().max())
+
+
+# Packed sequences of no more than 128 rows a head make one piece of every unit as well
+@pytest.mark.parametrize("budgets", [[128], [1, 0, 127], [40, 41, 47]])
+@pytest.mark.parametrize("dtype,d,group", [("bf16", 128, 7), ("bf16", 64, 1), ("f32", 128, 8)])
+def test_decode_of_packed_single_pieces(budgets, dtype, d, group):
+    import paper_2511_16786_amd as fc
+    B, L, H = 3, len(budgets), 2
+    gen = torch.Generator(device="cuda").manual_seed(d + L)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    offs = ref.layer_offsets(np.array(budgets), H)
+    rows = int(offs[-1])
+    Q = torch.randn((B, L, H * group, d), generator=gen, device="cuda").to(dt)
+    K, V = (torch.randn((B, rows, d), generator=gen, device="cuda").to(dt) for _ in range(2))
+    b_t = torch.tensor([budgets] * B, dtype=torch.int32, device="cuda")
+    got = fc.decode_attention(Q, K, V, H, b_t, torch.from_numpy(np.stack([offs] * B)).cuda(), rows, d ** -0.5)
+    for b in range(B):
+        for l, k in enumerate(budgets):
+            for h in range(H):
+                x = got[b, l, h * group:(h + 1) * group]
+                if k == 0:
+                    assert bool((x == 0).all())
+                    continue
+                first = int(offs[l]) + h * k
+                want = _softmax64(Q[b, l, h * group:(h + 1) * group], K[b, first:first + k], V[b, first:first + k], d ** -0.5)
+                assert float((x - want).abs().max()) <= 5e-5 * float(V[b, first:first + k].abs().max())
+
+
+# Units of three and of five to eight parts, two with empty lanes: parts side by side in workgroups of three to eight waves, one segment for
+# each wave and more, and in turn, of windows of a single tile, of a few and of blocks
+@pytest.mark.parametrize("n,r", [(1500, 150), (690, 60), (2050, 900), (8200, 3500)])
+@pytest.mark.parametrize("d,dtype", [(40, "f32"), (72, "f32"), (136, "f32"), (192, "f32"), (224, "f32"), (256, "f32"), (136, "bf16"), (192, "bf16")])
+def test_parts_side_by_side_and_in_turn_are_the_same_bits(n, r, d, dtype):
+    import paper_2511_16786_amd as fc
+    if n < 8000:
+        _scores_and_energies_follow_the_oracle(n, r, d, dtype, 3)
+    gen = torch.Generator(device="cuda").manual_seed(n + d)
+    heads = 130 if n < 8000 else 30
+    K, V = (torch.randn((1, 1, heads, n, d), generator=gen, device="cuda").to(torch.float32 if dtype == "f32" else torch.bfloat16)
+            for _ in range(2))
+    every = fc.Compressor(K, r, fc.total_budget(1, n, 0.2))
+    every.run_score(K, V)
+    for first, count in ((0, 1), (3, 3), (7, 20)):
+        part = fc.Compressor(K[:, :, :count], r, fc.total_budget(1, n, 0.2))
+        part.run_score(K[:, :, first:first + count], V[:, :, first:first + count])
+        assert torch.equal(part.scores, every.scores[:, :, first:first + count])
+        assert torch.equal(part.energy, every.energy[:, :, first:first + count])
+    assert fc.workspace_error(every.workspace) == 0
