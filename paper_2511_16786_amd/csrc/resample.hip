@@ -1187,9 +1187,9 @@ __device__ __forceinline__ double row_sums(const float (&v)[4], int lane) {
 }
 
 // What a residual workgroup's waves take side by side: units, and of each the blocks of a window's tiles, and of each the parts.
-// (Divisors as factors: a wave's number divided by waves is one multiplication, and not the first tenth of a us of a small launch.)
+// (From the host, and divisors as factors: a division of the kernel's own is a tenth of a us before the first load is asked for.)
 struct SideBySide {
-  int units, parts;
+  int units, parts, sets;     // sets: of so many units, in the launch
   int per_unit, per_block;    // side_factor of the waves of a unit and of a block
 };
 constexpr int side_factor(int waves) { return 256 / waves + 1; }
@@ -1239,9 +1239,9 @@ __global__ __launch_bounds__(64 * WAVES, sizeof(T) == 2 ? 2 : (ONCE ? 4 : 3)) vo
   const int my_unit = side_div(wave, side.per_unit), of_unit = wave - my_unit * (BLOCKS ? side_parts * blocks : side_parts);
   const int my_block = BLOCKS ? side_div(of_unit, side.per_block) : 0, my_part = of_unit - my_block * side_parts;
   const int block_tiles = window_block(tpw), my_tile = my_block * block_tiles;
-  const int sets = (u1 - u0 + abreast - 1) / abreast, tok_tiles = (n + 15) >> 4;
+  const int tok_tiles = (n + 15) >> 4;
   const int peers = gridDim.x >> 3;
-  const Span mine_w = xcd_first(blockIdx.x & 7, along, wins), mine_s = xcd_second(blockIdx.x & 7, along, sets);
+  const Span mine_w = xcd_first(blockIdx.x & 7, along, wins), mine_s = xcd_second(blockIdx.x & 7, along, side.sets);
   const int items = mine_w.count * mine_s.count;
   int item = blockIdx.x >> 3, part = 0;                    // segment under way
   if (item >= items) return;
@@ -1732,7 +1732,7 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
           kern = res.once ? residual_kernel<T, KEEP, true, false, 2, 8>
                  : lay.tpw > 1 ? residual_kernel<T, KEEP, false, false, 2, 8> : residual_kernel<T, KEEP, false, false, 1, 8>;
       const int side_parts = res.split ? lay.wpu : 1;
-      const SideBySide side{res.abreast, side_parts, side_factor(side_parts * res.blocks), side_factor(side_parts)};
+      const SideBySide side{res.abreast, side_parts, (u1 - u0 + res.abreast - 1) / res.abreast, side_factor(side_parts * res.blocks), side_factor(side_parts)};
       hipLaunchKernelGGL(kern, dim3(8 * res.workgroups), dim3(64 * res.waves), 0, s, K, V, st, u0, u1, n, r,
                          d.head_dim, d.dtype, m, lay.tpw, lay.wins, sm, res.split, res.blocks, side, res.along, hdr, reinterpret_cast<const _Float16*>(base + lay.winv),
                          grid, scores, epart, um);
