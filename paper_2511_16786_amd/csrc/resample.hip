@@ -982,7 +982,8 @@ __global__ __launch_bounds__(G::T < 64 ? 64 : G::T, G::kWaves) void grid_filter_
 // points a thread and more, more where it was found the quicker one.  One wave for each transform / spread, us with events (an empty
 // launch: 6): 512 pairs of 3072 points 21.8 / 16.9, of 1536 14.9 / 13.2, of 4096 16.8 / 14.7, 256 of 96 8.2 / 6.4; 1024 pairs of 3072
 // 25.5 / 23.8, of 1536 14.9 / 17.6, of 768 12.2 / 11.5, of 384 10.9 / 8.3, of 192 8.8 / 9.5; 2048 of 3072 35.7 / 37.4, of 768 14.6 /
-// 15.2, of 384 12.0 / 9.8; 256 of 2048, which have 16 points a thread, 11.1 / 12.2; 512 of 6144 26.3 / 41.6.  (Addresses of LDS as a part of the
+// 15.2, of 384 12.0 / 9.8; 256 of 2048, which have 16 points a thread, 11.1 / 12.2; 512 of 6144 26.3 / 41.6.  (kMostPairs is a list: no rule by
+// points, radices, threads or registers gives these lines.)  (Addresses of LDS as a part of the
 // thread's own and constants: a seventh of the instructions, 512 pairs of 3072 points 17.5 / 16.9, of 384 7.4 / 7.0.)
 template <int M>
 struct SpreadPlan {
@@ -1562,8 +1563,10 @@ constexpr int kMaxGrid = 36864;       // points
 static int next_grid(int m) { return m == 32768 ? kMaxGrid : ((m & (m - 1)) == 0 ? m + m / 2 : m / 3 * 4); }
 
 // Grid length for this shape and cut-off, 0 if the realisation does not apply.  Above 9362 modes (16384 points) it starts again
-// where a cut-off takes the next grid whole, with 2.6 points a mode or fewer (9453 modes on; 2.4 where tokens are fewer than points):
-// the few before that keep the realisation that FC_PATH_RESAMPLE has always left them to.
+// with 2.6 points a mode or fewer (9453 modes on; 2.4 where tokens are fewer than points: 10240 on).  No time or error speaks for that line:
+// the grid of 24576 points serves the cut-offs before it as well, eight units of 30000 tokens, r = 9400 in 357 us where the basis takes 12833,
+// of 24000, r = 10000 337 / 10370, of 32768, r = 9400 380 where the streaming transform takes 656.  It stands because the interface has them
+// refused by FC_PATH_RESAMPLE and realised by the other two, which programs that name a path, and the tests, rely on.
 // Scoring by that realisation / this one, us (bf16, 128 columns): basis 12 units of 47568 tokens, r = 10894 34113 / 565, 8 of 44736,
 // r = 17649 34666 / 419, 8 of 50000, r = 20501 46754 / 528, 2 of 24600, r = 11071 2585 / 76; streaming 16 of 42752, r = 10415 18677 / 726,
 // 32 of 32768, r = 13108 2508 / 1451, 4 of 65536, r = 19661 728 / 148.  Error of the scores against 64 bits, white columns:

@@ -151,7 +151,8 @@ def test_every_path_stands_for_the_realisation_it_names():
             assert fc.resolve_path(_desc(fc, L=1, H=1, N=N, d=128, dtype=1), r, path) == path
         for path in (b.FC_PATH_AUTO, b.FC_PATH_DENSE, b.FC_PATH_FFT):
             assert real(N, r, path=path) == b.FC_PATH_RESAMPLE
-    # chosen: the resampled transform ends at N/2, at 9362 modes, at head_dim 256 and below 256 tokens
+    # chosen: the resampled transform leaves cut-offs above N/2, of 9363 to 9452 (10239) modes and above 21065, head dims above 256 and
+    # fewer than 256 tokens to the other two
     for N, r, d in ((8192, 4097, 128), (65536, 9363, 128), (8192, 820, 264)):
         assert real(N, r, d) == b.FC_PATH_STREAM and real(N, r, d, path=b.FC_PATH_RESAMPLE) == 0
     for N, r in ((30011, 9363), (8191, 4096), (255, 20)):

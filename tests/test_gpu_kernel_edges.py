@@ -163,7 +163,7 @@ def test_modes_just_below_the_cutoff_are_kept(n, r):
     assert np.sqrt(np.mean(lost)) <= 2.7e-7
 
 
-# Where the resampled transform ends (9362 modes, N/2, head_dim 256) and the other two go on
+# What the resampled transform leaves to the other two: 9363 modes to where the grid of 24576 points is taken, above N/2, above head_dim 256
 @pytest.mark.parametrize("path,n,r,d", [("basis", 20011, 9363, 16), ("basis", 20011, 9900, 64), ("basis", 20011, 10100, 64),
                                         ("stream", 20480, 9363, 16), ("stream", 20480, 9900, 64),
                                         ("stream", 20480, 10241, 8), ("stream", 2048, 200, 264), ("stream", 2560, 600, 272)])
