@@ -325,8 +325,8 @@ __global__ __launch_bounds__(256) void resample_table_kernel(TablePtrs tp, int n
 
 // A lane's piece of a row is 16 bytes, so that a load takes whole lines; the 2*nb pieces of a unit's K and V rows are dealt out
 // to waves of 16 slots.  (With pieces of 8 columns for fp32 too, each load took every other 16 bytes of its lines, rows could not be read past
-// the cache, and a wave had twice the work: scoring, us, with 8 columns / with 4: 28 layers of 8192 tokens 582 / 551, 16 of
-// 20000, r = 4001 1126 / 1027, one layer of 13648, 64 columns 49.6 / 37.5, two heads of 512 27.3 / 22.3.)
+// the cache, and a wave had twice the work: scoring, us, with 8 columns / with 4: 112 units of 8192 tokens 573 / 507, 64 of
+// 20000, r = 4001 1117 / 984, 4 of 13648, 64 columns 34.8 / 32.1, 32 of 8192, 256 columns 328 / 292, two of 512 26.9 / 19.5.)
 template <typename T>
 constexpr int kCols = 16 / (int)sizeof(T);
 struct SlotMap {
