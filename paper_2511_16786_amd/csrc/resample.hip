@@ -1699,7 +1699,7 @@ static hipError_t resample_score_t(const T* K, const T* V, const fc_kv_desc& d, 
     const int groups = ((u1 - u0) * sm.wpu + kDecWaves - 1) / kDecWaves;
     const int gt = decimate_tiles(m, groups, lay.steps, sizeof(T) == 2, 2 * lay.nb, (long long)(u1 - u0) * 2 * n * d.head_dim * (int)sizeof(T));
     const Sides dec{(m / 16 + gt - 1) / gt, groups};
-    const ResidualPlan res = residual_plan(lay.wins, lay.tpw, lay.wpu, u1 - u0, dec, sizeof(T) == 2);
+    const ResidualPlan res = residual_plan(lay.wins, lay.tpw, 2 * lay.nb, u1 - u0, dec, sizeof(T) == 2);
     const float* wfwd = reinterpret_cast<const float*>(base + lay.wfwd);
     auto decimate = gt == 4 ? launch_decimate_gt<T, 4, KEEP> : (gt == 2 ? launch_decimate_gt<T, 2, KEEP> : launch_decimate_gt<T, 1, KEEP>);
     hipError_t e = decimate(K, V, st, u0, u1, n, r, d, m, lay, sm, dec, res.along, hdr, wfwd, grid, s);

@@ -117,10 +117,18 @@ constexpr int window_block(int tpw) { return (tpw + window_blocks(tpw) - 1) / wi
 // workgroups of an XCD: of three waves, 64 and 96, 150 units of 9000 tokens, 72 columns 493 / 473; of four, 32, 64 and 96, 112 of 8192 555 / 507 /
 // 513, 300 of 8192, 64 columns 727 / 672 / 679, 400 of 8192, 32 columns 496 / 465 / 473 (80 and 112, which compute units share
 // unevenly, 5 % more); of five, 32, 64 and 96, 80 of 8192, 136 columns 467 / 469 / 474; of six, 50 of 8192, 192 columns 366 / 367 / 370.
-constexpr int residual_waves(bool bf16, bool once) { return bf16 ? 8 : (once ? 16 : 9); }
+// Where a fifth of the lanes of a unit's waves has no slot, workgroups of four are three: so much less is under way.  Two / three: 205 of
+// 3840, 40 columns 293 / 283, 145 of 4096 203 / 197, 600 of 8192, 8 columns 423 / 393, 280, 48 columns 551 / 543; random launches,
+// three over two, mean and extremes: 8 columns (12 of 16 lanes idle) 0.937 (0.89 .. 1.00), 40 (12 of 32) 0.984 (0.94 .. 1.02), 24 and 48 (a quarter)
+// 0.993 (0.95 .. 1.02), but 104 (12 of 64) 1.002 (0.97 .. 1.04), 56 and 112 (an eighth) 1.002 (0.95 .. 1.03), 120 1.007 (0.96 .. 1.03).
+// (Of three waves, three and four, 150 of 8192, 80 columns 469 / 507.)
+constexpr int residual_waves(bool bf16, bool once, bool full) { return bf16 ? 8 : (once ? 16 : (full ? 9 : 12)); }
+constexpr int residual_groups(bool bf16, bool once, int waves, int slots) {
+  return 32 * (residual_waves(bf16, once, waves != 4 || 64 * slot_waves(slots) < 5 * slots) / (once && waves < 4 ? 4 : waves));
+}
 
-// Work of a residual launch: windows (wins, of tpw tiles) along one side, units abreast in a workgroup along the other; a unit has as many parts
-// as slot_waves.  Workgroups of four waves take a unit each and its parts in turn, or (split) a unit's parts side by side, of five to
+// Work of a residual launch: windows (wins, of tpw tiles) along one side, units abreast in a workgroup along the other; a unit has slots, and
+// as many parts as slot_waves.  Workgroups of four waves take a unit each and its parts in turn, or (split) a unit's parts side by side, of five to
 // eight waves where a unit has that many.
 // Split is what leaves an XCD's compute units two workgroups each where four units for one do not.  fp32 rows are split in others too, in
 // turn / side by side: 112 units of 8192 tokens 526 / 510 us, 154 of 12032, 72 columns 587 / 562, 50 of 9000, 256 columns 533 / 486, 36 of 16384,
@@ -135,8 +143,8 @@ struct ResidualPlan {
   bool split, once;                   // parts side by side; no more than one segment for each wave
   int along, workgroups;              // the XCDs' cut; of an XCD
 };
-constexpr ResidualPlan residual_plan(int wins, int tpw, int parts, int units, Sides dec, bool bf16) {
-  const int blocks = window_blocks(tpw), unit_waves = parts * blocks, block_waves = unit_waves > 4 ? unit_waves : 4;
+constexpr ResidualPlan residual_plan(int wins, int tpw, int slots, int units, Sides dec, bool bf16) {
+  const int parts = slot_waves(slots), blocks = window_blocks(tpw), unit_waves = parts * blocks, block_waves = unit_waves > 4 ? unit_waves : 4;
   const int block_units = block_waves / unit_waves > 1 ? block_waves / unit_waves : 1;
   const Sides small{wins, (units + block_units - 1) / block_units}, fours{wins, (units + 3) / 4};
   if (blocks > 1 && unit_waves <= 8) {
@@ -147,7 +155,7 @@ constexpr ResidualPlan residual_plan(int wins, int tpw, int parts, int units, Si
   const bool split = parts > 1 && !(many && (bf16 || (tpw == 1 && !idle)));
   const int abreast = split ? (parts < 4 ? 4 / parts : 1) : 4, waves = split ? abreast * parts : 4;
   const Sides all{wins, (units + abreast - 1) / abreast};
-  const int held = 32 * (residual_waves(bf16, false) / waves), held_once = 32 * (residual_waves(bf16, true) / (waves < 4 ? 4 : waves));
+  const int held = residual_groups(bf16, false, waves, slots), held_once = residual_groups(bf16, true, waves, slots);
   const int along = xcds_along(dec, all, split || parts == 1 ? held_once : held), items = xcd_items(along, all);
   const bool once = (split || parts == 1) && items <= held_once;
   return {waves, abreast, 1, split, once, along, once || items < held ? items : held};

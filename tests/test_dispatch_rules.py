@@ -26,11 +26,11 @@ void xcd_rectangle(int xcd, int along, int first, int second, int* out) {
 int slot_waves(int slots) { return fc::slot_waves(slots); }
 int lane_slot(int part, int lane, int slots) { return fc::lane_slot(part, lane, slots); }
 bool round_keeps_rows(long long bytes, int row_bytes) { return fc::round_keeps_rows(bytes, row_bytes); }
-void residual_plan(int wins, int tpw, int parts, int units, int f, int sec, bool bf16, int* out) {
-  const fc::ResidualPlan p = fc::residual_plan(wins, tpw, parts, units, {f, sec}, bf16);
+void residual_plan(int wins, int tpw, int slots, int units, int f, int sec, bool bf16, int* out) {
+  const fc::ResidualPlan p = fc::residual_plan(wins, tpw, slots, units, {f, sec}, bf16);
   out[0] = p.waves; out[1] = p.abreast; out[2] = p.blocks; out[3] = p.split; out[4] = p.once; out[5] = p.along; out[6] = p.workgroups;
 }
-int residual_waves(bool bf16, bool once) { return fc::residual_waves(bf16, once); }
+int residual_groups(bool bf16, bool once, int waves, int slots) { return fc::residual_groups(bf16, once, waves, slots); }
 int decimate_tiles(int m, int groups, int steps, bool bf16, int slots, long long row_bytes) {
   return fc::decimate_tiles(m, groups, steps, bf16, slots, row_bytes);
 }
@@ -153,31 +153,38 @@ def test_rows_of_whole_lines_alone_are_read_past_the_cache(rules):
 def test_residual_workgroups_take_parts_side_by_side_and_are_resident(rules):
     out = (ctypes.c_int * 7)()
 
-    def plan(wins, tpw, parts, units, dec, bf16):
-        rules.residual_plan(wins, tpw, parts, units, *dec, bf16, out)
+    def plan(wins, tpw, slots, units, dec, bf16):
+        rules.residual_plan(wins, tpw, slots, units, *dec, bf16, out)
         return list(out)
     for bf16 in (False, True):
-        for parts in range(1, 5 if bf16 else 9):
+        for slots in (2, 10, 16, 18, 20, 32, 36, 48, 50, 52, 64) + (() if bf16 else (68, 80, 84, 96, 100, 112, 128)):
+            parts = rules.slot_waves(slots)
             for tpw in (1, 2, 3, 5, 9, 16):
                 for wins in (1, 4, 14, 100, 700):
                     for units in (1, 2, 3, 4, 16, 112, 900):
                         dec = (max(1, wins // 2), -(-units * parts // 4))
-                        waves, abreast, blocks, split, once, along, workgroups = plan(wins, tpw, parts, units, dec, bf16)
+                        waves, abreast, blocks, split, once, along, workgroups = plan(wins, tpw, slots, units, dec, bf16)
                         of_unit = (parts if split else 1) * blocks
                         assert 1 <= waves <= 8 and abreast == waves // of_unit and waves == abreast * of_unit
                         assert split == (parts > 1) or (blocks == 1 and (bf16 or (tpw == 1 and units not in (1, 2, 3))))
                         items = rules.xcd_items(along, wins, -(-units // abreast))
-                        held = 32 * (rules.residual_waves(bf16, once) // (max(4, waves) if once else waves))
+                        held = rules.residual_groups(bf16, bool(once), waves, slots)
                         if blocks > 1:
                             held = 32 * (8 // waves)                # (whole workgroups of a compute unit's eight waves)
                         assert workgroups == (items if once else min(items, held)) and workgroups <= held
-                        held_once = 32 * (rules.residual_waves(bf16, True) // max(4, waves))
+                        held_once = rules.residual_groups(bf16, True, waves, slots)
                         assert blocks > 1 or once == ((split or parts == 1) and items <= held_once)
     # one layer of a head of 256 fp32 columns and the like: a wave for every part, one turn
     for parts in (5, 6, 8):
         for wins, units in ((14, 1), (43, 4), (21, 4)):
-            waves, abreast, _, split, once, _, workgroups = plan(wins, 3, parts, units, (16, units * parts // 4), False)
+            waves, abreast, _, split, once, _, workgroups = plan(wins, 3, 16 * parts, units, (16, units * parts // 4), False)
             assert (waves, abreast, split, once) == (parts, 1, 1, 1) and workgroups <= 64
+    # workgroups of four waves in turn: three of a compute unit where a fifth of a unit's lanes is idle, else two
+    for slots, groups in ((4, 96), (12, 96), (14, 64), (16, 64), (20, 96), (24, 96), (28, 64), (32, 64), (52, 64), (64, 64)):
+        assert plan(86, 6, slots, 900, (48, 450), False)[4::2] == [0, groups]
+        assert rules.residual_groups(False, False, 4, slots) == groups and rules.residual_groups(False, True, 4, slots) == 128
+        assert rules.residual_groups(True, False, 4, slots) == rules.residual_groups(True, True, 4, slots) == 64
+    assert [rules.residual_groups(False, False, w, s) for w, s in ((3, 36), (3, 48), (5, 68), (6, 84), (7, 100), (8, 120))] == [96, 96, 32, 32, 32, 32]
 
 
 def test_the_cut_leaves_the_residuals_items_one_turn(rules):
